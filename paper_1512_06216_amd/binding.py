@@ -1,18 +1,24 @@
-"""ctypes binding of libpsd.so (declared in include/psd.h): argument marshalling only.
+"""Python binding of libpsd.so (declared in include/psd.h): argument marshalling only.
 
 Every step of the path runs inside the library's HIP kernels; torch is used for device
 memory and streams.  There is no CPU fallback: if the library has not been built, the
 first call raises.
+
+The calls a training step makes go through _psdpy.so (csrc/psd_py.cpp), which checks the
+tensors and collects their pointers natively; the host-only queries are plain ctypes.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libpsd.so")
+EXT_PATH = os.path.join(_PKG, "_psdpy.so")
 
 OK, E_INVALID, E_NULL, E_UNSUPPORTED, E_OVERFLOW, E_HIP, E_WORKSPACE = 0, -1, -2, -3, -4, -5, -6
 LAYER_CONV, LAYER_FC = 0, 1
@@ -135,6 +141,24 @@ def lib():
     return _lib
 
 
+_ext = None
+
+
+def _native():
+    """Loads _psdpy.so, the native half of this module; raises if it (or the library) is missing."""
+    global _ext
+    if _ext is None:
+        lib()
+        if not os.path.exists(EXT_PATH):
+            raise RuntimeError("_psdpy.so is not built (%s): run `python -c 'import __graft_entry__ as g; "
+                               "g.build()'`; there is no fallback path" % EXT_PATH)
+        loader = importlib.machinery.ExtensionFileLoader("_psdpy", EXT_PATH)
+        spec = importlib.util.spec_from_file_location("_psdpy", EXT_PATH, loader=loader)
+        _ext = importlib.util.module_from_spec(spec)
+        loader.exec_module(_ext)
+    return _ext
+
+
 def _check(status, where):
     if status != OK:
         raise PsdError(status, where)
@@ -148,25 +172,16 @@ def _stream_handle(stream):
     return ctypes.c_void_p(stream.cuda_stream)
 
 
-def _dev_ptr(t, dtype, min_elems, what):
-    """Device pointer of a tensor after checking it can hold what the kernel will touch."""
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous()):
-        raise ValueError("%s must be a contiguous CUDA tensor" % what)
-    if t.dtype not in (dtype if isinstance(dtype, tuple) else (dtype,)):
-        raise ValueError("%s has dtype %s" % (what, t.dtype))
-    if t.numel() < min_elems:
-        raise ValueError("%s holds %d elements, needs %d" % (what, t.numel(), min_elems))
-    return t.data_ptr()
+def _dev_ptr(t, factor_dtype, min_elems, what):
+    """Device pointer of a tensor after checking it can hold what the kernel will touch (factor_dtype F32: float32;
+    BF16: bfloat16 or its bits)."""
+    return (_ext or _native()).pointer(t, factor_dtype, min_elems, what)
 
 
-def _ptr_array(tensors, min_elems, what, dtype=torch.float32):
+def _ptr_array(tensors, min_elems, what, factor_dtype=F32):
     arr = (_f32p * len(tensors))()
-    for i, t in enumerate(tensors):
-        arr[i] = ctypes.cast(_dev_ptr(t, dtype, min_elems, "%s[%d]" % (what, i)), _f32p)
+    (_ext or _native()).fill_pointers(arr, tensors, factor_dtype, min_elems, what)
     return arr
-
-
-_FACTOR_TORCH = {F32: (torch.float32,), BF16: (torch.bfloat16, torch.int16, torch.uint16)}
 
 
 # ---------------------------------------------------------------------------------------
@@ -204,14 +219,9 @@ def alloc_factors(plan, dtype, device="cuda"):
 
 
 def pack_factors(plan, delta, act, out_dtype, U, ldu, V, ldv, stream=None):
-    if len(delta) != plan.P or len(act) != plan.P:
-        raise ValueError("need P per-worker blocks")
-    d = _ptr_array(delta, plan.B * plan.N, "delta")
-    a = _ptr_array(act, plan.B * plan.M, "act")
-    up = _dev_ptr(U, _FACTOR_TORCH.get(out_dtype, ()), plan.K * ldu, "U")
-    vp = _dev_ptr(V, _FACTOR_TORCH.get(out_dtype, ()), plan.K * ldv, "V")
-    _check(lib().psd_pack_factors(ctypes.byref(plan), d, a, out_dtype, up, ldu, vp, ldv, _stream_handle(stream)),
-           "psd_pack_factors")
+    st = (_ext or _native()).pack_factors(plan, delta, act, out_dtype, U, ldu, V, ldv, stream)
+    if st:
+        raise PsdError(st, "psd_pack_factors")
 
 
 def sfb_workspace_bytes(plan, factor_dtype):
@@ -233,23 +243,16 @@ def _workspace_args(workspace):
 
 
 def sync_fc_sfb(plan, factor_dtype, U, ldu, V, ldv, W, Mom, lr, mu, stream=None, wd=0.0, workspace=None):
-    up = _dev_ptr(U, _FACTOR_TORCH.get(factor_dtype, ()), plan.K * ldu, "U")
-    vp = _dev_ptr(V, _FACTOR_TORCH.get(factor_dtype, ()), plan.K * ldv, "V")
-    wp = _dev_ptr(W, torch.float32, plan.N * plan.M, "W")
-    mp = _dev_ptr(Mom, torch.float32, plan.N * plan.M, "Mom")
-    ws, ws_bytes = _workspace_args(workspace)
-    _check(lib().psd_sync_fc_sfb(ctypes.byref(plan), factor_dtype, up, ldu, vp, ldv, wp, mp, lr, mu, wd,
-                                 ws, ws_bytes, _stream_handle(stream)), "psd_sync_fc_sfb")
+    st = (_ext or _native()).sync_fc_sfb(plan, factor_dtype, U, ldu, V, ldv, W, Mom, lr, mu, wd, workspace, stream)
+    if st:
+        raise PsdError(st, "psd_sync_fc_sfb")
 
 
 def sync_fc_sfb_static(plan, factor_dtype, U, ldu, V, ldv, W, Mom, lr, mu, stream=None, wd=0.0):
     """sync_fc_sfb on the library's own fixed scratch array (allocates nothing)."""
-    up = _dev_ptr(U, _FACTOR_TORCH.get(factor_dtype, ()), plan.K * ldu, "U")
-    vp = _dev_ptr(V, _FACTOR_TORCH.get(factor_dtype, ()), plan.K * ldv, "V")
-    wp = _dev_ptr(W, torch.float32, plan.N * plan.M, "W")
-    mp = _dev_ptr(Mom, torch.float32, plan.N * plan.M, "Mom")
-    _check(lib().psd_sync_fc_sfb_static(ctypes.byref(plan), factor_dtype, up, ldu, vp, ldv, wp, mp, lr, mu, wd,
-                                        _stream_handle(stream)), "psd_sync_fc_sfb_static")
+    st = (_ext or _native()).sync_fc_sfb(plan, factor_dtype, U, ldu, V, ldv, W, Mom, lr, mu, wd, ..., stream)
+    if st:
+        raise PsdError(st, "psd_sync_fc_sfb_static")
 
 
 def sfb_blocks_supported(plan, factor_dtype=F32, ldu=0, ldv=0):
@@ -260,33 +263,22 @@ def sfb_blocks_supported(plan, factor_dtype=F32, ldu=0, ldv=0):
 def sync_fc_sfb_blocks(plan, factor_dtype, U_blocks, ldu, V_blocks, ldv, W, Mom, lr, mu, stream=None, wd=0.0):
     """Reconstruction + update straight from the P per-worker blocks (B x ldu and B x ldv elements of
     factor_dtype each), no stacked copy.  ldu / ldv = 0: dense blocks."""
-    if len(U_blocks) != plan.P or len(V_blocks) != plan.P:
-        raise ValueError("need P per-worker blocks")
-    ldu, ldv = ldu or plan.N, ldv or plan.M
-    fd = _FACTOR_TORCH.get(factor_dtype, ())
-    d = _ptr_array(U_blocks, plan.B * ldu, "U_blocks", fd)
-    a = _ptr_array(V_blocks, plan.B * ldv, "V_blocks", fd)
-    wp = _dev_ptr(W, torch.float32, plan.N * plan.M, "W")
-    mp = _dev_ptr(Mom, torch.float32, plan.N * plan.M, "Mom")
-    _check(lib().psd_sync_fc_sfb_blocks(ctypes.byref(plan), factor_dtype, d, ldu, a, ldv, wp, mp, lr, mu, wd,
-                                        _stream_handle(stream)), "psd_sync_fc_sfb_blocks")
+    st = (_ext or _native()).sync_fc_sfb_blocks(plan, factor_dtype, U_blocks, ldu or plan.N, V_blocks, ldv or plan.M, W, Mom, lr, mu, wd,
+                                                stream)
+    if st:
+        raise PsdError(st, "psd_sync_fc_sfb_blocks")
 
 
 def sync_fc_bias(plan, factor_dtype, U, ldu, bias, mom_bias, lr, mu, stream=None, wd=0.0):
-    up = _dev_ptr(U, _FACTOR_TORCH.get(factor_dtype, ()), plan.K * ldu, "U")
-    bp = _dev_ptr(bias, torch.float32, plan.N, "bias")
-    mp = _dev_ptr(mom_bias, torch.float32, plan.N, "mom_bias")
-    _check(lib().psd_sync_fc_bias(ctypes.byref(plan), factor_dtype, up, ldu, bp, mp, lr, mu, wd,
-                                  _stream_handle(stream)), "psd_sync_fc_bias")
+    st = (_ext or _native()).sync_fc_bias(plan, factor_dtype, U, ldu, bias, mom_bias, lr, mu, wd, stream)
+    if st:
+        raise PsdError(st, "psd_sync_fc_bias")
 
 
 def sync_dense_ps(G, W, Mom, lr, mu, S, stream=None, wd=0.0):
-    n = W.numel()
-    g = _ptr_array(G, n, "G")
-    wp = _dev_ptr(W, torch.float32, n, "W")
-    mp = _dev_ptr(Mom, torch.float32, n, "Mom")
-    _check(lib().psd_sync_dense_ps(n, len(G), g, wp, mp, lr, mu, wd, S, _stream_handle(stream)),
-           "psd_sync_dense_ps")
+    st = (_ext or _native()).sync_dense_ps(G, W, Mom, lr, mu, wd, S, stream)
+    if st:
+        raise PsdError(st, "psd_sync_dense_ps")
 
 
 class DenseMulti:
@@ -301,13 +293,12 @@ class DenseMulti:
             self._keep.append(g)
             self.segs[i].n, self.segs[i].P, self.segs[i].S = n, len(G), S
             self.segs[i].G = ctypes.cast(g, _f32pp)
-            self.segs[i].W = ctypes.cast(_dev_ptr(W, torch.float32, n, "W"), _f32p)
-            self.segs[i].Mom = ctypes.cast(_dev_ptr(Mom, torch.float32, n, "Mom"), _f32p)
+            self.segs[i].W = ctypes.cast(_dev_ptr(W, F32, n, "W"), _f32p)
+            self.segs[i].Mom = ctypes.cast(_dev_ptr(Mom, F32, n, "Mom"), _f32p)
         self.L = len(layers)
 
     def run(self, lr, mu, stream=None, wd=0.0):
-        _check(lib().psd_sync_dense_ps_multi(self.L, self.segs, lr, mu, wd, _stream_handle(stream)),
-               "psd_sync_dense_ps_multi")
+        _check((_ext or _native()).sync_dense_ps_multi(self.L, self.segs, lr, mu, wd, stream), "psd_sync_dense_ps_multi")
 
 
 def sync_dense_ps_multi(layers, lr, mu, stream=None, wd=0.0):
@@ -337,14 +328,8 @@ class SspFc:
 
     def clock(self, delta, act, W, Mom, lr, mu, wd=0.0, workspace=None, stream=None):
         """delta / act: this clock's per-worker blocks, or None, None to drain."""
-        plan = self.plan
-        d = _ptr_array(delta, plan.B * plan.N, "delta") if delta is not None else None
-        a = _ptr_array(act, plan.B * plan.M, "act") if act is not None else None
-        ws, ws_bytes = _workspace_args(workspace)
-        _check(lib().psd_ssp_clock_fc(ctypes.byref(self.state), ctypes.byref(plan), self.dtype, d, a, self.U_ring, self.ldu,
-                                      self.V_ring, self.ldv, _dev_ptr(W, torch.float32, plan.N * plan.M, "W"),
-                                      _dev_ptr(Mom, torch.float32, plan.N * plan.M, "Mom"), lr, mu, wd, ws, ws_bytes,
-                                      _stream_handle(stream)), "psd_ssp_clock_fc")
+        _check((_ext or _native()).ssp_clock_fc(self.state, self.plan, self.dtype, delta, act, self.U_ring, self.ldu, self.V_ring, self.ldv,
+                                                W, Mom, lr, mu, wd, workspace, stream), "psd_ssp_clock_fc")
 
 
 class SspDense:
@@ -371,8 +356,8 @@ class SspDense:
                 P = len(k[1])
         if P is None:
             raise ValueError("no gradient copies have been pushed yet")
-        _check(lib().psd_ssp_clock_dense(ctypes.byref(self.state), n, P, self.ring, _dev_ptr(W, torch.float32, n, "W"),
-                                         _dev_ptr(Mom, torch.float32, n, "Mom"), lr, mu, wd, S, _stream_handle(stream)),
+        _check(lib().psd_ssp_clock_dense(ctypes.byref(self.state), n, P, self.ring, _dev_ptr(W, F32, n, "W"),
+                                         _dev_ptr(Mom, F32, n, "Mom"), lr, mu, wd, S, _stream_handle(stream)),
                "psd_ssp_clock_dense")
 
 
@@ -396,8 +381,8 @@ class Iteration:
             plan = L["plan"]
             t.plan = plan
             n = plan.M * plan.N
-            t.W = ctypes.cast(_dev_ptr(L["W"], torch.float32, n, "W"), _f32p)
-            t.Mom = ctypes.cast(_dev_ptr(L["Mom"], torch.float32, n, "Mom"), _f32p)
+            t.W = ctypes.cast(_dev_ptr(L["W"], F32, n, "W"), _f32p)
+            t.Mom = ctypes.cast(_dev_ptr(L["Mom"], F32, n, "Mom"), _f32p)
             t.stream = _stream_handle(L.get("stream"))
             t.workspace, t.workspace_bytes = _workspace_args(L.get("workspace"))
             self._keep.append(L.get("workspace"))
@@ -410,7 +395,7 @@ class Iteration:
                 self._keep.append(g)
                 t.G = ctypes.cast(g, _f32pp)
             if L.get("delta") is not None:
-                fd = _FACTOR_TORCH.get(t.factor_dtype, ())
+                fd = t.factor_dtype
                 if L.get("U") is not None or L.get("V") is not None:
                     d = _ptr_array(L["delta"], plan.B * plan.N, "delta")
                     a = _ptr_array(L["act"], plan.B * plan.M, "act")
@@ -426,4 +411,4 @@ class Iteration:
         self.L = len(layers)
 
     def run(self, lr, mu, rule=RULE_ALG3, wd=0.0):
-        _check(lib().psd_sync_iteration(self.L, self.tasks, lr, mu, wd, rule), "psd_sync_iteration")
+        _check((_ext or _native()).sync_iteration(self.L, self.tasks, lr, mu, wd, rule), "psd_sync_iteration")

@@ -1,9 +1,10 @@
-"""Builds libpsd.so (the C-ABI HIP library) for gfx950 with hipcc, in-tree."""
+"""Builds libpsd.so (the C-ABI HIP library, gfx950, hipcc) and _psdpy.so (the Python binding's native half, g++), in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -11,6 +12,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libpsd.so")
+EXT = os.path.join(PKG, "_psdpy.so")
 SOURCES = ["psd_host.hip", "psd_dense.hip", "psd_pack.hip", "psd_sfb_f32.hip", "psd_sfb_bf16.hip", "psd_bias.hip", "psd_static.hip", "psd_ssp.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", os.path.join(ROOT, "include"),
@@ -29,16 +31,38 @@ def _compile(src):
     return obj, out
 
 
+def _torch_dir():
+    import torch
+    return os.path.dirname(os.path.abspath(torch.__file__))
+
+
+def _compile_binding():
+    """Host code only: the HIP headers are included for torch's stream type."""
+    obj = os.path.join(OBJ, "psd_py.o")
+    inc = os.path.join(_torch_dir(), "include")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-I", os.path.join(ROOT, "include"),
+           "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
+           "-I", sysconfig.get_paths()["include"], "-c", os.path.join(CSRC, "psd_py.cpp"), "-o", obj]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for psd_py.cpp:\n%s" % r.stdout)
+    return obj
+
+
 def build_library(verbose=False, jobs=None):
     os.makedirs(OBJ, exist_ok=True)
-    jobs = jobs or min(len(SOURCES), max(1, (os.cpu_count() or 2) // 2))
+    jobs = jobs or min(len(SOURCES) + 1, max(1, (os.cpu_count() or 2) // 2))
     with ThreadPoolExecutor(jobs) as ex:
+        binding_obj = ex.submit(_compile_binding)
         res = list(ex.map(_compile, SOURCES))
+        binding_obj = binding_obj.result()
     for obj, out in res:
         if out.strip() and verbose:
             print(out, file=sys.stderr)
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *[o for o, _ in res]]
     subprocess.check_call(cmd)
+    subprocess.check_call(["g++", "-shared", "-o", EXT, binding_obj, "-L", os.path.join(_torch_dir(), "lib"), "-ltorch_python", "-ltorch_cpu",
+                           "-lc10", "-lc10_hip", "-L", PKG, "-lpsd", "-Wl,-rpath,$ORIGIN"])
     return LIB
 
 

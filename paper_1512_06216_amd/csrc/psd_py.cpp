@@ -1,0 +1,360 @@
+// Native half of the Python binding: checks tensors, gathers their device pointers and makes the library call.
+//
+// Why it exists: a data-parallel worker hands over 2P block pointers per layer and step.  Checking and collecting
+// them in Python took 9-15 us per call, several times what the smaller kernels run for, so the GPU waited for the
+// host (1024 -> 1000 layer, B = 32, P = 8: 42 us per pass for 19 us of kernels).  Here the same checks cost about
+// 20 ns per tensor.  Everything that is not marshalling stays in the library; errors are raised with the same types
+// and texts as ever.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/Dtype.h>
+#include <torch/csrc/DynamicTypes.h>
+#include <torch/csrc/autograd/python_variable.h>
+#include "psd.h"
+
+namespace {
+
+// A ctypes structure or array, looked at through the buffer protocol for the length of one call.
+struct View {
+    Py_buffer b{};
+    bool held = false;
+    bool open(PyObject* o) { return held = PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) == 0; }
+    template <class T> T* as() const { return static_cast<T*>(b.buf); }
+    ~View() { if (held) PyBuffer_Release(&b); }
+};
+
+bool type_ok(c10::ScalarType t, long factor_dtype)
+{
+    if (factor_dtype == PSD_F32) return t == c10::kFloat;
+    if (factor_dtype == PSD_BF16) return t == c10::kBFloat16 || t == c10::kShort || t == c10::kUInt16;
+    return false;
+}
+
+// Device pointer of a tensor that can hold what the kernel will touch; false with ValueError set if it cannot.
+// index >= 0 names an element of a list in the error text.
+template <class T>
+bool dev_ptr(PyObject* o, long factor_dtype, int64_t min_elems, const char* what, T** out, Py_ssize_t index = -1)
+{
+    char name[64];
+    auto called = [&]() {
+        if (index < 0) snprintf(name, sizeof name, "%s", what);
+        else snprintf(name, sizeof name, "%s[%zd]", what, index);
+        return name;
+    };
+    if (!THPVariable_Check(o)) {
+        PyErr_Format(PyExc_ValueError, "%s must be a contiguous CUDA tensor", called());
+        return false;
+    }
+    const at::Tensor& t = THPVariable_Unpack(o);
+    if (!t.is_cuda() || !t.is_contiguous()) {
+        PyErr_Format(PyExc_ValueError, "%s must be a contiguous CUDA tensor", called());
+        return false;
+    }
+    if (!type_ok(t.scalar_type(), factor_dtype)) {
+        PyErr_Format(PyExc_ValueError, "%s has dtype %S", called(), reinterpret_cast<PyObject*>(torch::getTHPDtype(t.scalar_type())));
+        return false;
+    }
+    if (t.numel() < min_elems) {
+        PyErr_Format(PyExc_ValueError, "%s holds %lld elements, needs %lld", called(), static_cast<long long>(t.numel()),
+                     static_cast<long long>(min_elems));
+        return false;
+    }
+    *out = static_cast<T*>(t.data_ptr());
+    return true;
+}
+
+// Pointers of a sequence of tensors: all are checked and counted, the first `room` are stored (the library refuses
+// longer lists by their count); false with an exception set if one does not fit.
+bool dev_ptrs(PyObject* seq, long factor_dtype, int64_t min_elems, const char* what, const void** out, Py_ssize_t room, Py_ssize_t* count)
+{
+    PyObject* fast = PySequence_Fast(seq, "a sequence of tensors is needed");
+    if (!fast) return false;
+    *count = PySequence_Fast_GET_SIZE(fast);
+    bool ok = true;
+    for (Py_ssize_t i = 0; ok && i < *count; ++i) {
+        const void* p = nullptr;
+        ok = dev_ptr(PySequence_Fast_GET_ITEM(fast, i), factor_dtype, min_elems, what, &p, i);
+        if (ok && i < room) out[i] = p;
+    }
+    Py_DECREF(fast);
+    return ok;
+}
+
+// None: the current stream of the current device; an int: a raw handle; else an object with .cuda_stream
+bool stream_of(PyObject* o, void** out)
+{
+    if (o == Py_None) {
+        *out = c10::hip::getCurrentHIPStream().stream();
+        return true;
+    }
+    if (PyLong_Check(o)) {
+        *out = PyLong_AsVoidPtr(o);
+        return !PyErr_Occurred();
+    }
+    PyObject* h = PyObject_GetAttrString(o, "cuda_stream");
+    if (!h) return false;
+    *out = PyLong_AsVoidPtr(h);
+    Py_DECREF(h);
+    return !PyErr_Occurred();
+}
+
+bool workspace_of(PyObject* o, void** p, size_t* bytes)
+{
+    *p = nullptr;
+    *bytes = 0;
+    if (o == Py_None) return true;
+    if (!THPVariable_Check(o) || !THPVariable_Unpack(o).is_cuda() || !THPVariable_Unpack(o).is_contiguous()) {
+        PyErr_SetString(PyExc_ValueError, "workspace must be a contiguous CUDA tensor");
+        return false;
+    }
+    const at::Tensor& t = THPVariable_Unpack(o);
+    *p = t.data_ptr();
+    *bytes = t.nbytes();
+    return true;
+}
+
+int64_t as_i64(PyObject* o) { return PyLong_AsLongLong(o); }
+float as_f32(PyObject* o) { return static_cast<float>(PyFloat_AsDouble(o)); }
+
+bool arity(Py_ssize_t got, Py_ssize_t want)
+{
+    if (got == want) return true;
+    PyErr_Format(PyExc_TypeError, "%zd arguments, %zd wanted", got, want);
+    return false;
+}
+
+template <class F>
+PyObject* call(F f)
+{
+    psd_status r;
+    Py_BEGIN_ALLOW_THREADS
+    r = f();
+    Py_END_ALLOW_THREADS
+    return PyLong_FromLong(r);
+}
+
+struct Blocks {
+    const void* u[PSD_MAX_WORKERS];
+    const void* v[PSD_MAX_WORKERS];
+};
+
+// the P error and P activation blocks of a layer: `eu`, `ev` elements each at least
+bool blocks_of(PyObject* us, PyObject* vs, const psd_plan& plan, long dtype, int64_t eu, int64_t ev, const char* nu, const char* nv, Blocks* b)
+{
+    const Py_ssize_t n = PyObject_Length(us), m = PyObject_Length(vs);
+    if (n < 0 || m < 0) return false;
+    if (n != plan.P || m != plan.P) {
+        PyErr_SetString(PyExc_ValueError, "need P per-worker blocks");
+        return false;
+    }
+    Py_ssize_t c;
+    return dev_ptrs(us, dtype, eu, nu, b->u, PSD_MAX_WORKERS, &c) && dev_ptrs(vs, dtype, ev, nv, b->v, PSD_MAX_WORKERS, &c);
+}
+
+const float* const* f32s(const void* const* p) { return reinterpret_cast<const float* const*>(p); }
+
+// plan, delta, act, out_dtype, U, ldu, V, ldv, stream
+PyObject* pack_factors(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    View pv;
+    Blocks b;
+    void* st;
+    if (!arity(n, 9) || !pv.open(a[0])) return nullptr;
+    const psd_plan& plan = *pv.as<psd_plan>();
+    if (!blocks_of(a[1], a[2], plan, PSD_F32, plan.B * plan.N, plan.B * plan.M, "delta", "act", &b)) return nullptr;
+    const long dt = PyLong_AsLong(a[3]);
+    const int64_t ldu = as_i64(a[5]), ldv = as_i64(a[7]);
+    if (PyErr_Occurred()) return nullptr;
+    void *U, *V;
+    if (!dev_ptr(a[4], dt, plan.P * plan.B * ldu, "U", &U) || !dev_ptr(a[6], dt, plan.P * plan.B * ldv, "V", &V) ||
+        !stream_of(a[8], &st))
+        return nullptr;
+    return call([&] { return psd_pack_factors(&plan, f32s(b.u), f32s(b.v), dt, U, ldu, V, ldv, st); });
+}
+
+// plan, factor_dtype, U, ldu, V, ldv, W, Mom, lr, mu, wd, workspace (None, a tensor, or ... for the static array), stream
+PyObject* sync_fc_sfb(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    View pv;
+    void *st, *ws = nullptr;
+    size_t ws_bytes = 0;
+    if (!arity(n, 13) || !pv.open(a[0])) return nullptr;
+    const psd_plan& plan = *pv.as<psd_plan>();
+    const long dt = PyLong_AsLong(a[1]);
+    const int64_t ldu = as_i64(a[3]), ldv = as_i64(a[5]), K = plan.P * plan.B;
+    const float lr = as_f32(a[8]), mu = as_f32(a[9]), wd = as_f32(a[10]);
+    if (PyErr_Occurred()) return nullptr;
+    void *U, *V;
+    float *W, *Mom;
+    if (!dev_ptr(a[2], dt, K * ldu, "U", &U) || !dev_ptr(a[4], dt, K * ldv, "V", &V) ||
+        !dev_ptr(a[6], PSD_F32, plan.N * plan.M, "W", &W) ||
+        !dev_ptr(a[7], PSD_F32, plan.N * plan.M, "Mom", &Mom))
+        return nullptr;
+    const bool use_static = a[11] == Py_Ellipsis;
+    if ((!use_static && !workspace_of(a[11], &ws, &ws_bytes)) || !stream_of(a[12], &st)) return nullptr;
+    return call([&] {
+        return use_static ? psd_sync_fc_sfb_static(&plan, dt, U, ldu, V, ldv, W, Mom, lr, mu, wd, st)
+                          : psd_sync_fc_sfb(&plan, dt, U, ldu, V, ldv, W, Mom, lr, mu, wd, ws, ws_bytes, st);
+    });
+}
+
+// plan, factor_dtype, U_blocks, ldu, V_blocks, ldv, W, Mom, lr, mu, wd, stream
+PyObject* sync_fc_sfb_blocks(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    View pv;
+    Blocks b;
+    void* st;
+    if (!arity(n, 12) || !pv.open(a[0])) return nullptr;
+    const psd_plan& plan = *pv.as<psd_plan>();
+    const long dt = PyLong_AsLong(a[1]);
+    const int64_t ldu = as_i64(a[3]), ldv = as_i64(a[5]);
+    const float lr = as_f32(a[8]), mu = as_f32(a[9]), wd = as_f32(a[10]);
+    if (PyErr_Occurred() || !blocks_of(a[2], a[4], plan, dt, plan.B * ldu, plan.B * ldv, "U_blocks", "V_blocks", &b)) return nullptr;
+    float *W, *Mom;
+    if (!dev_ptr(a[6], PSD_F32, plan.N * plan.M, "W", &W) ||
+        !dev_ptr(a[7], PSD_F32, plan.N * plan.M, "Mom", &Mom) || !stream_of(a[11], &st))
+        return nullptr;
+    return call([&] { return psd_sync_fc_sfb_blocks(&plan, dt, b.u, ldu, b.v, ldv, W, Mom, lr, mu, wd, st); });
+}
+
+// plan, factor_dtype, U, ldu, bias, mom_bias, lr, mu, wd, stream
+PyObject* sync_fc_bias(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    View pv;
+    void* st;
+    if (!arity(n, 10) || !pv.open(a[0])) return nullptr;
+    const psd_plan& plan = *pv.as<psd_plan>();
+    const long dt = PyLong_AsLong(a[1]);
+    const int64_t ldu = as_i64(a[3]);
+    const float lr = as_f32(a[6]), mu = as_f32(a[7]), wd = as_f32(a[8]);
+    if (PyErr_Occurred()) return nullptr;
+    void* U;
+    float *bias, *mom;
+    if (!dev_ptr(a[2], dt, plan.P * plan.B * ldu, "U", &U) || !dev_ptr(a[4], PSD_F32, plan.N, "bias", &bias) ||
+        !dev_ptr(a[5], PSD_F32, plan.N, "mom_bias", &mom) || !stream_of(a[9], &st))
+        return nullptr;
+    return call([&] { return psd_sync_fc_bias(&plan, dt, U, ldu, bias, mom, lr, mu, wd, st); });
+}
+
+// G, W, Mom, lr, mu, wd, S, stream
+PyObject* sync_dense_ps(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    const void* g[PSD_MAX_WORKERS];
+    Py_ssize_t P;
+    void* st;
+    if (!arity(n, 8)) return nullptr;
+    const float lr = as_f32(a[3]), mu = as_f32(a[4]), wd = as_f32(a[5]);
+    const long S = PyLong_AsLong(a[6]);
+    if (PyErr_Occurred()) return nullptr;
+    float* W;
+    if (!dev_ptr(a[1], PSD_F32, 0, "W", &W)) return nullptr;
+    const int64_t keys = THPVariable_Unpack(a[1]).numel();
+    float* Mom;
+    if (!dev_ptrs(a[0], PSD_F32, keys, "G", g, PSD_MAX_WORKERS, &P) ||
+        !dev_ptr(a[2], PSD_F32, keys, "Mom", &Mom) || !stream_of(a[7], &st))
+        return nullptr;
+    return call([&] { return psd_sync_dense_ps(keys, static_cast<int32_t>(P), f32s(g), W, Mom, lr, mu, wd, static_cast<int32_t>(S), st); });
+}
+
+// L, segments, lr, mu, wd, stream
+PyObject* sync_dense_ps_multi(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    View sv;
+    void* st;
+    if (!arity(n, 6) || !sv.open(a[1])) return nullptr;
+    const long L = PyLong_AsLong(a[0]);
+    const float lr = as_f32(a[2]), mu = as_f32(a[3]), wd = as_f32(a[4]);
+    if (PyErr_Occurred() || !stream_of(a[5], &st)) return nullptr;
+    return call([&] { return psd_sync_dense_ps_multi(static_cast<int32_t>(L), sv.as<psd_dense_segment>(), lr, mu, wd, st); });
+}
+
+// L, tasks, lr, mu, wd, rule
+PyObject* sync_iteration(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    View tv;
+    if (!arity(n, 6) || !tv.open(a[1])) return nullptr;
+    const long L = PyLong_AsLong(a[0]), rule = PyLong_AsLong(a[5]);
+    const float lr = as_f32(a[2]), mu = as_f32(a[3]), wd = as_f32(a[4]);
+    if (PyErr_Occurred()) return nullptr;
+    return call([&] { return psd_sync_iteration(static_cast<int32_t>(L), tv.as<psd_layer_task>(), lr, mu, wd, static_cast<int32_t>(rule)); });
+}
+
+// state, plan, factor_dtype, delta (or None), act (or None), U_ring, ldu, V_ring, ldv, W, Mom, lr, mu, wd, workspace, stream
+PyObject* ssp_clock_fc(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    View sv, pv, uv, vv;
+    Blocks b;
+    void *st, *ws;
+    size_t ws_bytes;
+    if (!arity(n, 16) || !sv.open(a[0]) || !pv.open(a[1]) || !uv.open(a[5]) || !vv.open(a[7])) return nullptr;
+    const psd_plan& plan = *pv.as<psd_plan>();
+    const long dt = PyLong_AsLong(a[2]);
+    const int64_t ldu = as_i64(a[6]), ldv = as_i64(a[8]);
+    const float lr = as_f32(a[11]), mu = as_f32(a[12]), wd = as_f32(a[13]);
+    if (PyErr_Occurred()) return nullptr;
+    Py_ssize_t c;
+    const bool du = a[3] != Py_None, dv = a[4] != Py_None;
+    if ((du && !dev_ptrs(a[3], PSD_F32, plan.B * plan.N, "delta", b.u, PSD_MAX_WORKERS, &c)) || (du && c != plan.P) ||
+        (dv && !dev_ptrs(a[4], PSD_F32, plan.B * plan.M, "act", b.v, PSD_MAX_WORKERS, &c)) || (dv && c != plan.P)) {
+        if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "need P per-worker blocks");
+        return nullptr;
+    }
+    float *W, *Mom;
+    if (!dev_ptr(a[9], PSD_F32, plan.N * plan.M, "W", &W) ||
+        !dev_ptr(a[10], PSD_F32, plan.N * plan.M, "Mom", &Mom) || !workspace_of(a[14], &ws, &ws_bytes) ||
+        !stream_of(a[15], &st))
+        return nullptr;
+    return call([&] {
+        return psd_ssp_clock_fc(sv.as<psd_ssp_state>(), &plan, dt, du ? f32s(b.u) : nullptr, dv ? f32s(b.v) : nullptr, uv.as<void*>(), ldu,
+                                vv.as<void*>(), ldv, W, Mom, lr, mu, wd, ws, ws_bytes, st);
+    });
+}
+
+// table (a ctypes array of pointers), tensors, factor_dtype, min_elems, what: fills the table
+PyObject* fill_pointers(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    View tv;
+    if (!arity(n, 5) || !tv.open(a[0])) return nullptr;
+    const long dt = PyLong_AsLong(a[2]);
+    const int64_t least = as_i64(a[3]);
+    const char* what = PyUnicode_AsUTF8(a[4]);
+    Py_ssize_t c;
+    if (PyErr_Occurred() || !what ||
+        !dev_ptrs(a[1], dt, least, what, tv.as<const void*>(), tv.b.len / static_cast<Py_ssize_t>(sizeof(void*)), &c))
+        return nullptr;
+    Py_RETURN_NONE;
+}
+
+// tensor, factor_dtype, min_elems, what -> address
+PyObject* pointer(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    if (!arity(n, 4)) return nullptr;
+    const long dt = PyLong_AsLong(a[1]);
+    const int64_t least = as_i64(a[2]);
+    const char* what = PyUnicode_AsUTF8(a[3]);
+    if (PyErr_Occurred() || !what) return nullptr;
+    void* p;
+    return dev_ptr(a[0], dt, least, what, &p) ? PyLong_FromVoidPtr(p) : nullptr;
+}
+
+template <PyObject* (*F)(PyObject*, PyObject* const*, Py_ssize_t)>
+PyObject* guarded(PyObject* self, PyObject* const* a, Py_ssize_t n)
+{
+    try {
+        return F(self, a, n);
+    } catch (const std::exception& e) {          // torch reports its own errors by throwing
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+        return nullptr;
+    }
+}
+
+#define PSD_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(&guarded<f>)), METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {PSD_METHOD(pack_factors), PSD_METHOD(sync_fc_sfb), PSD_METHOD(sync_fc_sfb_blocks), PSD_METHOD(sync_fc_bias),
+                         PSD_METHOD(sync_dense_ps), PSD_METHOD(sync_dense_ps_multi), PSD_METHOD(sync_iteration),
+                         PSD_METHOD(ssp_clock_fc), PSD_METHOD(fill_pointers), PSD_METHOD(pointer), {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_psdpy", "argument marshalling of libpsd.so", -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__psdpy(void) { return PyModule_Create(&module); }
