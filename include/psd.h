@@ -168,7 +168,7 @@ psd_status psd_sync_fc_sfb_blocks(const psd_plan* plan, int32_t factor_dtype, co
  *     db[n] = sum_{k<K} U[k][n] ;  mom_bias <- mu*mom_bias + lr*(db + wd*bias) ;  bias <- bias - mom_bias.
  * No extra communication: U is what SFB already delivered (the paper's volumes count weights
  * only, Table 3).  U [dev] K x ldu as written by psd_pack_factors; bias, mom_bias [dev] N fp32,
- * in place, 16-byte aligned.  fp32 accumulation, 16 interleaved partial sums per column. */
+ * in place, 16-byte aligned.  fp32 accumulation of interleaved partial sums per column. */
 psd_status psd_sync_fc_bias(const psd_plan* plan, int32_t factor_dtype, const void* U, int64_t ldu,
                             float* bias, float* mom_bias, float lr, float mu, float wd, void* stream);
 

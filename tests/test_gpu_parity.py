@@ -500,6 +500,21 @@ def test_sfb_vgg16_first_fc_layer_at_full_batch_integer_bit_exact():
     assert np.array_equal(Mg, Mr) and np.array_equal(Wg, Wr)
 
 
+@pytest.mark.parametrize("N,K", [(31, 1), (33, 255), (8192, 257), (8193, 64), (8321, 129)])
+@pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
+def test_bias_column_blocks_bit_exact(N, K, dtype):
+    """Both column widths of the bias kernel (N up to and above 32 per compute unit), ragged last blocks and row rounds."""
+    d = inputs.fc_layer_integer(8, N, K, 1, seed=N + K)
+    plan, U, ldu, V, ldv = run_pack(d, dtype)
+    b0, m0 = d["W"][:, 0].copy(), d["Mom"][:, 0].copy()
+    bias, mom = dev(b0), dev(m0)
+    psd.sync_fc_bias(plan, dtype, U, ldu, bias, mom, 0.25, 0.5, wd=0.5)
+    torch.cuda.synchronize()
+    Uo, _ = orc.pack_factors(d["delta"], d["act"], "f32" if dtype == psd.F32 else "bf16")
+    br, mr = orc.sync_fc_bias(Uo, b0, m0, 0.25, 0.5, wd=0.5)
+    assert np.array_equal(mom.cpu().numpy(), mr) and np.array_equal(bias.cpu().numpy(), br)
+
+
 @pytest.mark.parametrize("M,N,B,P", [(16, 1, 1, 1), (40, 127, 3, 5), (64, 1000, 16, 8), (8, 21841, 4, 2), (32, 300, 1, 37)])
 @pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
 def test_bias_integer_errors_bit_exact(M, N, B, P, dtype):
