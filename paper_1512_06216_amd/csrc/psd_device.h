@@ -82,30 +82,126 @@ __device__ __forceinline__ i32x4 raw_rsrc(const void* X, uint32_t bytes)
 }
 
 // Scheduling pattern for one pipeline phase holding MF MFMAs and R LDS reads that do not depend
-// on each other: 1 MFMA, then its share of the reads, and so on.
-template <int R, int MF, int I = 0>
+// on each other: 1 MFMA, then PER reads, and so on until the reads are out.
+template <int R, int MF, int PER, int I = 0>
 __device__ __forceinline__ void interleave_groups()
 {
     if constexpr (I < MF) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                    // one MFMA
-        constexpr int n = R * (I + 1) / MF - R * I / MF;
+        constexpr int left = R - PER * I;
+        constexpr int n = I == MF - 1 ? left : (left < PER ? left : PER);
         if constexpr (n > 0) __builtin_amdgcn_sched_group_barrier(0x100, n, 0);  // n DS reads
-        interleave_groups<R, MF, I + 1>();
+        interleave_groups<R, MF, PER, I + 1>();
     }
 }
 
-// The same with V vector-memory loads spread over the phase as well.
-template <int R, int V, int MF, int I = 0>
-__device__ __forceinline__ void interleave_groups_vmem()
+// ---- Update of W and Mom from rows of dW in LDS ------------------------------------------------------------
+// A cache line holds 32 fp32.  Row n of W starts `line_shift(n)` elements into a line, a different number for every row
+// unless M is a multiple of 32, so a fixed split of a tile's columns over lanes makes every 128-byte access straddle two
+// lines: twice the requests on the path from L1 to L2, and stores that cover parts of lines.  Here each row of the tile is
+// put into LDS `line_shift` elements to the right, and what is read back from aligned places of LDS are whole lines of W.
+__device__ __forceinline__ int line_shift(const float* W, int64_t n, int64_t M)
 {
-    if constexpr (I < MF) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        constexpr int n = R * (I + 1) / MF - R * I / MF;
-        if constexpr (n > 0) __builtin_amdgcn_sched_group_barrier(0x100, n, 0);
-        constexpr int v = V * (I + 1) / MF - V * I / MF;
-        if constexpr (v > 0) __builtin_amdgcn_sched_group_barrier(0x020, v, 0);  // v VMEM reads
-        interleave_groups_vmem<R, V, MF, I + 1>();
-    }
+    return static_cast<int>((static_cast<uint32_t>(n) * static_cast<uint32_t>(M) +
+                             static_cast<uint32_t>(reinterpret_cast<uintptr_t>(W) >> 2)) & 31u);
 }
+
+// Row r (of ROWS) of the buffer starts at buf + r * STRIDE and holds dW[row_n(r)][m0 + c] at place c + line_shift, c < WIDTH.
+// Every wavefront access covers one line of eight rows (8 lanes of 16 bytes each).  W and Mom of DEPTH such line groups
+// are requested by fetch<0>() before the rows are even written, and those of the next DEPTH before the present ones are
+// used.  Lines that lie inside the tile are streamed (see load_stream4), the ones it shares with its neighbours go
+// through the caches.
+template <int ROWS, int WIDTH, int STRIDE, int WAVES, int DEPTH, class RowN>
+struct RowUpdate {
+    static constexpr int LINES = WIDTH / 32 + 1, UNITS = ROWS / 8 / WAVES * LINES, BATCHES = (UNITS + DEPTH - 1) / DEPTH;
+    static_assert(ROWS % (8 * WAVES) == 0 && WIDTH % 32 == 0 && STRIDE >= WIDTH + 32 && STRIDE % 4 == 0, "whole line groups per wavefront");
+    float* W;
+    float* Mom;
+    RowN row_n;
+    int64_t m0, N, M;
+    int wave, lane, cols;                          // cols: columns of the tile that exist
+    float4 w[2][DEPTH], mo[2][DEPTH];
+
+    __device__ __forceinline__ RowUpdate(float* W_, float* Mom_, RowN row, int64_t m0_, int64_t N_, int64_t M_, int wave_, int lane_)
+        : W(W_), Mom(Mom_), row_n(row), m0(m0_), N(N_), M(M_), wave(wave_), lane(lane_),
+          cols(static_cast<int>(M_ - m0_ < WIDTH ? M_ - m0_ : WIDTH))
+    {
+    }
+    struct Place {
+        int64_t off;                               // of this lane's quad in W
+        int at, c;                                 // ... in the row buffer; its first column
+        bool any, quad, whole_line;                // does the tile own some of it, all of it, all of its line
+    };
+    __device__ __forceinline__ Place place(int u) const
+    {
+        const int r = (wave + WAVES * (u / LINES)) * 8 + (lane >> 3), line = u % LINES, q = 4 * (lane & 7);
+        const int64_t n = row_n(r);
+        const int first = 32 * line - line_shift(W, n, M);       // column of the line's first element
+        Place p;
+        p.c = first + q;
+        p.at = r * STRIDE + 32 * line + q;
+        p.off = n * M + m0 + p.c;
+        p.any = n < N && p.c + 3 >= 0 && p.c < cols;
+        p.quad = n < N && p.c >= 0 && p.c + 3 < cols;
+        p.whole_line = first >= 0 && first + 32 <= cols;
+        return p;
+    }
+    template <int B>
+    __device__ __forceinline__ void fetch()
+    {
+#pragma unroll
+        for (int j = 0; j < DEPTH; ++j) {
+            if (B * DEPTH + j >= UNITS) continue;
+            const Place p = place(B * DEPTH + j);
+            if (!p.quad) continue;
+            if (p.whole_line) {
+                w[B & 1][j] = load_stream4(W + p.off);
+                mo[B & 1][j] = load_stream4(Mom + p.off);
+            } else {
+                w[B & 1][j] = *reinterpret_cast<const float4*>(W + p.off);
+                mo[B & 1][j] = *reinterpret_cast<const float4*>(Mom + p.off);
+            }
+        }
+    }
+    template <int B = 0>
+    __device__ __forceinline__ void run(const float* buf, float lr, float mu, float wd)
+    {
+        if constexpr (B < BATCHES) {
+            if constexpr (B + 1 < BATCHES) fetch<B + 1>();
+#pragma unroll
+            for (int j = 0; j < DEPTH; ++j) {
+                if (B * DEPTH + j >= UNITS) continue;
+                const Place p = place(B * DEPTH + j);
+                if (!p.any) continue;
+                const float4 d = *reinterpret_cast<const float4*>(buf + p.at);
+                if (p.quad) {
+                    float4 &wv = w[B & 1][j], &mv = mo[B & 1][j];
+                    upd(d.x, wv.x, mv.x, lr, mu, wd);
+                    upd(d.y, wv.y, mv.y, lr, mu, wd);
+                    upd(d.z, wv.z, mv.z, lr, mu, wd);
+                    upd(d.w, wv.w, mv.w, lr, mu, wd);
+                    if (p.whole_line) {
+                        store_stream4(Mom + p.off, mv);
+                        store_stream4(W + p.off, wv);
+                    } else {
+                        *reinterpret_cast<float4*>(Mom + p.off) = mv;
+                        *reinterpret_cast<float4*>(W + p.off) = wv;
+                    }
+                } else {                           // a quad that the tile shares with a neighbour (M not a multiple of 4)
+                    const float dv[4] = {d.x, d.y, d.z, d.w};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (p.c + i >= 0 && p.c + i < cols) {
+                            float wv = W[p.off + i], mv = Mom[p.off + i];
+                            upd(dv[i], wv, mv, lr, mu, wd);
+                            Mom[p.off + i] = mv;
+                            W[p.off + i] = wv;
+                        }
+                }
+            }
+            run<B + 1>(buf, lr, mu, wd);
+        }
+    }
+};
 
 }  // namespace psd

@@ -243,7 +243,7 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
     // A wavefront issues at most one LDS instruction per ~16 cycles and one MFMA per 32, in program
     // order; operand reads are therefore spread between the MFMAs they do not feed (1 MFMA, then
     // its share of reads, ...) so that their issue time hides under MFMA execution.
-    auto interleave = [&]() { interleave_groups<2 * (C::BN + C::BM), C::BN * C::BM>(); };
+    auto interleave = [&]() { interleave_groups<2 * (C::BN + C::BM), C::BN * C::BM, 2>(); };
     for (int t = 0; t < steps; ++t) {
         load_frags(stage_base(t), 16, a1, b1);
         mma(a0, b0);

@@ -6,17 +6,21 @@
 // (v_mfma_f32_32x32x2_f32: one k per lane, which is exactly how the K-outer stacked
 // factors sit in memory -- no transpose is needed for fp32).
 //
-// Tiling: a 256-lane workgroup (4 wavefronts, 2 x 2) owns a 128 x 128 (or 64 x 128) tile of W;
-// each wavefront a 64 x 64 (32 x 64) sub-tile of 32 x 32 MFMA blocks.  MFMA row i of block t
-// stands for n = n0 + 2*i + t (columns likewise), so one lane's LDS operand read is one
-// 8-byte load and one lane owns 2 adjacent m in the epilogue (8-byte W/Mom accesses,
-// 256 contiguous bytes per half wavefront).  dW lives only in accumulator registers.
+// Tiling: a 256-lane workgroup (4 wavefronts, 2 x 2) owns a 128 x 128, 64 x 128 or 64 x 64 tile of W; each wavefront a
+// quarter of it in 32 x 32 MFMA blocks.  MFMA row i of block t stands for n = n0 + BN*i + t (columns m likewise), so one
+// lane's LDS operand read is one 4- or 8-byte load.  dW lives only in accumulator registers.
+//
+// Bound by the fp32 MFMA pipe (157.3 TFLOP/s): what matters is that every compute unit holds the same number of tiles and
+// that the pipe never waits.  One launch therefore covers W with as many 128 x 128 tiles as divide evenly over the compute
+// units and the rest with smaller ones (choose_f32).
 //
 // Feeding: the same scheme as the bf16 kernel.  Tiles go global -> LDS without registers
 // (buffer_load_dwordx4 ... lds) into a ring of NSTAGE buffers with NSTAGE-1 stages in flight;
 // the buffer range check zero-fills the K tail.  A stage is 16 k rows = two half-stages of
 // 4 MFMA k-pairs; the operand reads of one half are issued before the MFMAs of the half before
-// and interleaved with them, and the workgroup barrier sits between the two halves.
+// and interleaved with its first MFMAs (two reads after each: they are back before the half ends, where the barrier
+// would wait for them; spread over the whole half they cost 3 % on every shape), and the workgroup barrier sits between
+// the two halves.
 #include "psd_device.h"
 #include "psd_internal.h"
 
@@ -27,90 +31,101 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int TM = 128;             // workgroup tile width (m)
 constexpr int KT = 16;              // k rows per LDS stage
 constexpr int THREADS = 256;
 constexpr int NSTAGE = 4;           // ring depth
 
-// BN = MFMA blocks per wavefront along n: workgroup tile (64*BN) x 128, wavefront tile (32*BN) x 64.
-// BN = 2 is the default; BN = 1 doubles the number of workgroups for layers with few tiles.
+template <int BN, int BM>
+struct Tile {                       // workgroup tile (64*BN) x (64*BM): 2 x 2 wavefronts of BN x BM MFMA blocks
+    static constexpr int TN = 64 * BN, TM = 64 * BM;
+    static constexpr int RA = TN * 4, RB = TM * 4;                                // LDS row bytes
+    static constexpr int A_BYTES = KT * RA, B_BYTES = KT * RB, STAGE_BYTES = A_BYTES + B_BYTES;
+    static constexpr int NI_A = A_BYTES / 1024 / 4, NI_B = B_BYTES / 1024 / 4;    // 1 KiB DMA runs per wavefront
+    static constexpr int STRIDE = TM + 36;                                        // row buffer of the update, in floats
+    static constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES > 64 * STRIDE * 4 ? NSTAGE * STAGE_BYTES : 64 * STRIDE * 4;
+};
+
+// Row k = p*B + b of U is row b of the p-th worker's B x ldu block (V likewise): the factors read where they were received.
+struct BlockPtrs { const float* u[PSD_MAX_WORKERS]; const float* v[PSD_MAX_WORKERS]; };
+
+struct Args {
+    const float* U; const float* V;
+    int64_t ldu, ldv;
+    float* W; float* Mom;
+    int N, M, K;
+    float lr, mu, wd;
+    int tiles_m;                    // tiles per row of tiles of the main grid
+    int big, tiles;                 // workgroups [0, big) own 128 x 128 tiles, the others smaller ones
+    uint32_t u_bytes, v_bytes;      // of the stacked matrices, or of ONE block
+    float* part;                    // PART: partial dW matrices, part_stride apart
+    int64_t part_stride;
+    int stages_per_split;
+    int n_blocks, stages_per_block; // BLK
+};
+
 // PART = true (layers with too few tiles to fill the chip): `splits` workgroups per tile, workgroup
 // (tile, s) contracts over k-stages [s * stages_per_split, (s+1) * stages_per_split) and stores its
 // partial dW tile to part + s * part_stride (N x M row-major); the partials are summed in split order
 // and the update applied by the parameter-server sum kernel afterwards.
-// BLK = true: the factors are not stacked.  Row k = p*B + b of U is row b of the p-th worker's B x N block
-// (V likewise, B x M), read where it lies: a stage of KT rows never straddles two blocks because KT divides
+// BLK = true: the factors are not stacked.  A stage of KT rows never straddles two blocks because KT divides
 // B, so the only difference is that the buffer descriptor is re-aimed whenever the stages move on to the
 // next block (and aimed at nothing past the last one, which reads as zeros like the K tail does).
-struct BlockPtrs { const float* u[PSD_MAX_WORKERS]; const float* v[PSD_MAX_WORKERS]; };
-
-template <int BN, bool PART, bool BLK>
-__device__ __forceinline__ void
-sfb_f32_body(const float* __restrict__ U, int64_t ldu, const float* __restrict__ V, int64_t ldv,
-             float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
-             int tiles_m, int tiles, uint32_t u_bytes, uint32_t v_bytes, float* __restrict__ part,
-             int64_t part_stride, int stages_per_split, const BlockPtrs* blocks, int n_blocks, int stages_per_block)
+template <int BN, int BM, bool PART, bool BLK>
+__device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks, char* lds, int64_t n0, int64_t m0, int split)
 {
     static_assert(!(PART && BLK), "blocks read in place are not combined with a split of K");
-    constexpr int TN = 64 * BN;
-    constexpr int RA = TN * 4, RB = TM * 4;                       // LDS row bytes
-    constexpr int A_BYTES = KT * RA, B_BYTES = KT * RB, STAGE_BYTES = A_BYTES + B_BYTES;
-    constexpr int NI_A = A_BYTES / 1024 / 4, NI_B = B_BYTES / 1024 / 4;   // 1 KiB DMA runs per wavefront
-    constexpr int LPS = NI_A + NI_B;
-    __shared__ __attribute__((aligned(1024))) char lds[NSTAGE * STAGE_BYTES];
+    using T = Tile<BN, BM>;
+    constexpr int LPS = T::NI_A + T::NI_B;
+    const int N = g.N, M = g.M;
     const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
         (__attribute__((address_space(3))) void*)lds));
-
-    const int split = PART ? __builtin_amdgcn_readfirstlane(blockIdx.x / tiles) : 0;   // (the division runs on the vector ALU)
-    const int tile = PART ? blockIdx.x - split * tiles : blockIdx.x;
-    const int tile_n = tile / tiles_m, tile_m = tile % tiles_m;
+    uint32_t u_bytes = g.u_bytes, v_bytes = g.v_bytes;
     // this workgroup's k range: rows at or past k_end read as zeros (descriptor size), rows before
     // k_begin are skipped (offsets)
-    const int k_begin = PART ? split * stages_per_split * KT : 0;
-    const int k_end = PART ? (k_begin + stages_per_split * KT < K ? k_begin + stages_per_split * KT : K) : K;
+    const int k_begin = PART ? split * g.stages_per_split * KT : 0;
+    const int k_end = PART ? (k_begin + g.stages_per_split * KT < g.K ? k_begin + g.stages_per_split * KT : g.K) : g.K;
     if constexpr (PART) {
-        u_bytes = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(int64_t(k_end) * ldu * 4));
-        v_bytes = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(int64_t(k_end) * ldv * 4));
+        u_bytes = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(int64_t(k_end) * g.ldu * 4));
+        v_bytes = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(int64_t(k_end) * g.ldv * 4));
     }
-    const int64_t n0 = int64_t(tile_n) * TN, m0 = int64_t(tile_m) * TM;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wn0 = (wave >> 1) * 32 * BN, wm0 = (wave & 1) * 64;     // wavefront sub-tile origin
+    const int wn0 = (wave >> 1) * 32 * BN, wm0 = (wave & 1) * 32 * BM;     // wavefront sub-tile origin
     const int l32 = lane & 31, lhi = lane >> 5;
 
     // DMA plan: run j of this wavefront covers chunks f = (wave*NI + j)*64 + lane of the stage
-    i32x4 rsrc_u = raw_rsrc(U, u_bytes), rsrc_v = raw_rsrc(V, v_bytes);
+    i32x4 rsrc_u = raw_rsrc(g.U, u_bytes), rsrc_v = raw_rsrc(g.V, v_bytes);
     int blk = 0, stage_in_blk = 0;               // BLK: where the next stage to be requested lies
     auto aim_block = [&]() {                     // BLK: descriptors over block `blk` (u_bytes, v_bytes = one block)
-        const bool live = blk < n_blocks;
+        const bool live = blk < g.n_blocks;
         const int i = live ? blk : 0;            // the table is never indexed past its end
         rsrc_u = raw_rsrc(uniform_ptr(blocks->u[i]), live ? u_bytes : 0u);
         rsrc_v = raw_rsrc(uniform_ptr(blocks->v[i]), live ? v_bytes : 0u);
     };
     if constexpr (BLK) aim_block();
-    uint32_t voff_a[NI_A], voff_b[NI_B];
+    uint32_t voff_a[T::NI_A], voff_b[T::NI_B];
 #pragma unroll
-    for (int j = 0; j < NI_A; ++j) {
-        const int f = (wave * NI_A + j) * 64 + lane;
-        voff_a[j] = static_cast<uint32_t>(((k_begin + f / (TN / 4)) * ldu + n0 + (f % (TN / 4)) * 4) * 4);
+    for (int j = 0; j < T::NI_A; ++j) {
+        const int f = (wave * T::NI_A + j) * 64 + lane;
+        voff_a[j] = static_cast<uint32_t>(((k_begin + f / (T::TN / 4)) * g.ldu + n0 + (f % (T::TN / 4)) * 4) * 4);
     }
 #pragma unroll
-    for (int j = 0; j < NI_B; ++j) {
-        const int f = (wave * NI_B + j) * 64 + lane;
-        voff_b[j] = static_cast<uint32_t>(((k_begin + f / (TM / 4)) * ldv + m0 + (f % (TM / 4)) * 4) * 4);
+    for (int j = 0; j < T::NI_B; ++j) {
+        const int f = (wave * T::NI_B + j) * 64 + lane;
+        voff_b[j] = static_cast<uint32_t>(((k_begin + f / (T::TM / 4)) * g.ldv + m0 + (f % (T::TM / 4)) * 4) * 4);
     }
-    const uint32_t step_a = static_cast<uint32_t>(KT * ldu * 4), step_b = static_cast<uint32_t>(KT * ldv * 4);
+    const uint32_t step_a = static_cast<uint32_t>(KT * g.ldu * 4), step_b = static_cast<uint32_t>(KT * g.ldv * 4);
     auto issue = [&](int t) {                    // stage t -> ring buffer t % NSTAGE; past K: zeros
-        const uint32_t base = lds0 + static_cast<uint32_t>(t % NSTAGE) * STAGE_BYTES;
+        const uint32_t base = lds0 + static_cast<uint32_t>(t % NSTAGE) * T::STAGE_BYTES;
         const uint32_t s = static_cast<uint32_t>(BLK ? stage_in_blk : t);     // stages are requested in order
 #pragma unroll
-        for (int j = 0; j < NI_A; ++j)
-            dma_b128(base + (wave * NI_A + j) * 1024, voff_a[j] + s * step_a, rsrc_u);
+        for (int j = 0; j < T::NI_A; ++j)
+            dma_b128(base + (wave * T::NI_A + j) * 1024, voff_a[j] + s * step_a, rsrc_u);
 #pragma unroll
-        for (int j = 0; j < NI_B; ++j)
-            dma_b128(base + A_BYTES + (wave * NI_B + j) * 1024, voff_b[j] + s * step_b, rsrc_v);
+        for (int j = 0; j < T::NI_B; ++j)
+            dma_b128(base + T::A_BYTES + (wave * T::NI_B + j) * 1024, voff_b[j] + s * step_b, rsrc_v);
         if constexpr (BLK) {
-            if (++stage_in_blk == stages_per_block) {
+            if (++stage_in_blk == g.stages_per_block) {
                 stage_in_blk = 0;
                 ++blk;
                 aim_block();
@@ -118,43 +133,42 @@ sfb_f32_body(const float* __restrict__ U, int64_t ldu, const float* __restrict__
         }
     };
 
-    f32x16 acc[BN][2];
+    f32x16 acc[BN][BM];
 #pragma unroll
     for (int a = 0; a < BN; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < BM; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
     // One half-stage = 4 MFMA k-pairs.  Lanes 0..31 feed k = 2*kk, lanes 32..63 feed k = 2*kk + 1.
-    // MFMA row i of block t stands for n = 2*i + t (BN = 2) or n = i (BN = 1); columns m = 2*j + t.
     struct Half { f32x2 a[4]; f32x2 b[4]; };
-    const uint32_t rd_a = static_cast<uint32_t>(lhi * RA + (wn0 + BN * l32) * 4);
-    const uint32_t rd_b = static_cast<uint32_t>(A_BYTES + lhi * RB + (wm0 + 2 * l32) * 4);
+    const uint32_t rd_a = static_cast<uint32_t>(lhi * T::RA + (wn0 + BN * l32) * 4);
+    const uint32_t rd_b = static_cast<uint32_t>(T::A_BYTES + lhi * T::RB + (wm0 + BM * l32) * 4);
     auto load_half = [&](int t, int h, Half& f) {
-        const uint32_t base = lds0 + static_cast<uint32_t>(t % NSTAGE) * STAGE_BYTES;
+        const uint32_t base = lds0 + static_cast<uint32_t>(t % NSTAGE) * T::STAGE_BYTES;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
             const int krow = 2 * (4 * h + kk);
-            const auto pa = reinterpret_cast<__attribute__((address_space(3))) const char*>(base + rd_a + krow * RA);
-            const auto pb = reinterpret_cast<__attribute__((address_space(3))) const char*>(base + rd_b + krow * RB);
+            const auto pa = reinterpret_cast<__attribute__((address_space(3))) const char*>(base + rd_a + krow * T::RA);
+            const auto pb = reinterpret_cast<__attribute__((address_space(3))) const char*>(base + rd_b + krow * T::RB);
             if constexpr (BN == 2) f.a[kk] = *reinterpret_cast<__attribute__((address_space(3))) const f32x2*>(pa);
             else f.a[kk].x = *reinterpret_cast<__attribute__((address_space(3))) const float*>(pa);
-            f.b[kk] = *reinterpret_cast<__attribute__((address_space(3))) const f32x2*>(pb);
+            if constexpr (BM == 2) f.b[kk] = *reinterpret_cast<__attribute__((address_space(3))) const f32x2*>(pb);
+            else f.b[kk].x = *reinterpret_cast<__attribute__((address_space(3))) const float*>(pb);
         }
     };
     auto mma_half = [&](const Half& f) {
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[kk].x, f.b[kk].x, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[kk].x, f.b[kk].y, acc[0][1], 0, 0, 0);
-            if constexpr (BN == 2) {
-                acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[kk].y, f.b[kk].x, acc[1][0], 0, 0, 0);
-                acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[kk].y, f.b[kk].y, acc[1][1], 0, 0, 0);
-            }
-        }
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+            for (int ta = 0; ta < BN; ++ta)
+#pragma unroll
+                for (int tb = 0; tb < BM; ++tb)
+                    acc[ta][tb] = __builtin_amdgcn_mfma_f32_32x32x2f32(ta ? f.a[kk].y : f.a[kk].x, tb ? f.b[kk].y : f.b[kk].x,
+                                                                       acc[ta][tb], 0, 0, 0);
     };
-    auto interleave = [&]() { interleave_groups<8, 8 * BN>(); };
+    auto interleave = [&]() { interleave_groups<8, 4 * BN * BM, 2>(); };
 
     const int steps = k_end > k_begin ? (k_end - k_begin + KT - 1) / KT : 0;
 #pragma unroll
@@ -176,154 +190,189 @@ sfb_f32_body(const float* __restrict__ U, int64_t ldu, const float* __restrict__
         interleave();
         __builtin_amdgcn_sched_barrier(0);
     }
-    wait_vmcnt<0>();                              // nothing may still be landing in LDS at exit
+    wait_vmcnt<0>();                              // nothing may still be landing in LDS when it is used for the update
 
-    // Epilogue.  Accumulator register r of a 32x32 block holds MFMA row 8*(r/4) + 4*(lane/32) + r%4,
-    // column lane%32.  Block (ta, tb): n = n0 + wn0 + BN*row + ta, m = m0 + wm0 + 2*col + tb.
-    const int64_t mcol = m0 + wm0 + 2 * l32;
-    const bool pair_ok = (M % 2 == 0);   // 8-byte accesses need an even row length
+    // Accumulator register r of a 32x32 block holds MFMA row 8*(r/4) + 4*(lane/32) + r%4, column lane%32.
+    // Block (ta, tb): n = n0 + wn0 + BN*row + ta, m = m0 + wm0 + BM*col + tb.
+    if constexpr (PART) {
+        const int64_t mcol = m0 + wm0 + BM * l32;
+        const bool pair_ok = BM == 2 && M % 2 == 0;   // 8-byte accesses need an even row length
 #pragma unroll
-    for (int ta = 0; ta < BN; ++ta) {
+        for (int ta = 0; ta < BN; ++ta)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = 8 * (r >> 2) + 4 * lhi + (r & 3);
-            const int64_t n = n0 + wn0 + BN * row + ta;
-            if (n >= N) continue;
-            const float d0 = acc[ta][0][r], d1 = acc[ta][1][r];
-            if constexpr (PART) {
-                float* dp = part + split * part_stride + n * int64_t(M) + mcol;
+            for (int r = 0; r < 16; ++r) {
+                const int64_t n = n0 + wn0 + BN * (8 * (r >> 2) + 4 * lhi + (r & 3)) + ta;
+                if (n >= N) continue;
+                float* dp = g.part + split * g.part_stride + n * int64_t(M) + mcol;
                 if (pair_ok && mcol + 1 < M) {
-                    *reinterpret_cast<float2*>(dp) = make_float2(d0, d1);
+                    *reinterpret_cast<float2*>(dp) = make_float2(acc[ta][0][r], acc[ta][BM - 1][r]);
                 } else {
-                    if (mcol < M) dp[0] = d0;
-                    if (mcol + 1 < M) dp[1] = d1;
-                }
-                continue;
-            }
-            float* wp = W + n * int64_t(M) + mcol;
-            float* mp = Mom + n * int64_t(M) + mcol;
-            if (pair_ok && mcol + 1 < M) {
-                float2 w = *reinterpret_cast<float2*>(wp), mo = *reinterpret_cast<float2*>(mp);
-                upd(d0, w.x, mo.x, lr, mu, wd);
-                upd(d1, w.y, mo.y, lr, mu, wd);
-                *reinterpret_cast<float2*>(mp) = mo;
-                *reinterpret_cast<float2*>(wp) = w;
-            } else {
-                if (mcol < M) {
-                    float w = wp[0], mo = mp[0];
-                    upd(d0, w, mo, lr, mu, wd);
-                    mp[0] = mo;
-                    wp[0] = w;
-                }
-                if (mcol + 1 < M) {
-                    float w = wp[1], mo = mp[1];
-                    upd(d1, w, mo, lr, mu, wd);
-                    mp[1] = mo;
-                    wp[1] = w;
+#pragma unroll
+                    for (int tb = 0; tb < BM; ++tb)
+                        if (mcol + tb < M) dp[tb] = acc[ta][tb][r];
                 }
             }
+    } else {
+        // The rows of one ta of all wavefronts (64 rows) go through LDS at a time, so that W and Mom move in whole cache
+        // lines.  Straight from the accumulators a lane owns 2 adjacent m: 8-byte accesses.  Update alone (9216 -> 4096,
+        // K = 16): 160 -> 124 us, with rows of odd length 212 -> 154 us.
+        float* buf = reinterpret_cast<float*>(lds);
+        const int64_t nw = n0 + wn0;
+#pragma unroll
+        for (int ta = 0; ta < BN; ++ta) {
+            auto row_n = [&](int r) { return n0 + (r >> 5) * 32 * BN + BN * (r & 31) + ta; };
+            RowUpdate<64, T::TM, T::STRIDE, 4, BM == 2 ? 5 : 3, decltype(row_n)> rows(g.W, g.Mom, row_n, m0, N, M, wave, lane);
+            rows.template fetch<0>();
+            __syncthreads();                          // the ring, or the rows before, are no longer read
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = 8 * (r >> 2) + 4 * lhi + (r & 3);
+                float* to = buf + ((wave >> 1) * 32 + row) * T::STRIDE + wm0 + BM * l32 + line_shift(g.W, nw + BN * row + ta, M);
+                if (BM == 2 && M % 2 == 0) {
+                    *reinterpret_cast<float2*>(to) = make_float2(acc[ta][0][r], acc[ta][BM - 1][r]);
+                } else {
+#pragma unroll
+                    for (int tb = 0; tb < BM; ++tb) to[tb] = acc[ta][tb][r];
+                }
+            }
+            __syncthreads();
+            rows.run(buf, g.lr, g.mu, g.wd);
         }
     }
 }
 
-template <int BN, bool PART>
-__global__ void __launch_bounds__(THREADS)
-sfb_f32_kernel(const float* __restrict__ U, int64_t ldu, const float* __restrict__ V, int64_t ldv,
-               float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
-               int tiles_m, int tiles, uint32_t u_bytes, uint32_t v_bytes, float* __restrict__ part,
-               int64_t part_stride, int stages_per_split)
+// Workgroups [0, big) own 128 x 128 tiles; the tiles after them are cut into (2 / BN) * (2 / BM) smaller ones.  big = 0:
+// small tiles only.
+template <int BN, int BM, bool PART, bool BLK>
+__device__ __forceinline__ void grid_body(const Args& g, const BlockPtrs* blocks)
 {
-    sfb_f32_body<BN, PART, false>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, tiles_m, tiles, u_bytes, v_bytes, part,
-                                  part_stride, stages_per_split, nullptr, 0, 0);
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const int b = blockIdx.x;
+    if constexpr (PART) {
+        const int split = __builtin_amdgcn_readfirstlane(b / g.tiles), tile = b - split * g.tiles;   // (the division runs on the vector ALU)
+        tile_body<BN, BM, true, false>(g, nullptr, lds, int64_t(tile / g.tiles_m) * 64 * BN, int64_t(tile % g.tiles_m) * 64 * BM, split);
+    } else if (b < g.big) {
+        tile_body<2, 2, false, BLK>(g, blocks, lds, int64_t(b / g.tiles_m) * 128, int64_t(b % g.tiles_m) * 128, 0);
+    } else if (g.big == 0) {
+        tile_body<BN, BM, false, BLK>(g, blocks, lds, int64_t(b / g.tiles_m) * 64 * BN, int64_t(b % g.tiles_m) * 64 * BM, 0);
+    } else {
+        constexpr int PN = 2 / BN, PM = 2 / BM;
+        const int i = b - g.big, tile = g.big + i / (PN * PM), sub = i % (PN * PM);
+        tile_body<BN, BM, false, BLK>(g, blocks, lds, int64_t(tile / g.tiles_m) * 128 + (sub / PM) * 64 * BN,
+                                      int64_t(tile % g.tiles_m) * 128 + (sub % PM) * 64 * BM, 0);
+    }
 }
 
-// the P per-worker blocks read in place (u_bytes, v_bytes: the size of ONE block)
-template <int BN>
-__global__ void __launch_bounds__(THREADS)
-sfb_f32_blocks_kernel(BlockPtrs blocks, int n_blocks, int stages_per_block, int64_t ldu, int64_t ldv,
-                      float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
-                      int tiles_m, int tiles, uint32_t u_bytes, uint32_t v_bytes)
+template <int BN, int BM, bool PART>
+__global__ void __launch_bounds__(THREADS) sfb_f32_kernel(const Args g)
 {
-    sfb_f32_body<BN, false, true>(nullptr, ldu, nullptr, ldv, W, Mom, N, M, K, lr, mu, wd, tiles_m, tiles, u_bytes, v_bytes,
-                                  nullptr, 0, 0, &blocks, n_blocks, stages_per_block);
+    grid_body<BN, BM, PART, false>(g, nullptr);
 }
 
-template <int BN>
-psd_status launch_f32(const float* U, int64_t ldu, const float* V, int64_t ldv, float* W, float* Mom,
-                      int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int splits,
-                      hipStream_t st)
+template <int BN, int BM>
+__global__ void __launch_bounds__(THREADS) sfb_f32_blocks_kernel(const Args g, const BlockPtrs blocks)
 {
-    constexpr int TN = 64 * BN;
-    const int64_t tiles_n = (N + TN - 1) / TN, tiles_m = (M + TM - 1) / TM;
-    const int64_t tiles = tiles_n * tiles_m;
-    if (tiles < 1 || tiles * splits > 0x7fffffff) return PSD_E_INVALID;
-    // 32-bit byte offsets into each factor matrix, with room for the stages of read-ahead
-    const int64_t u_bytes = K * ldu * 4, v_bytes = K * ldv * 4;
-    const int64_t reach = (int64_t(1) << 32) - (NSTAGE + 2) * KT * (ldu > ldv ? ldu : ldv) * 4 - 4096;
-    if (u_bytes > reach || v_bytes > reach) return PSD_E_UNSUPPORTED;
-    const int64_t stages = (K + KT - 1) / KT;
-    const int sps = static_cast<int>((stages + splits - 1) / splits);
-    auto kern = splits > 1 ? sfb_f32_kernel<BN, true> : sfb_f32_kernel<BN, false>;
-    hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(tiles * splits)), dim3(THREADS), 0, st, U, ldu, V, ldv, W, Mom,
-                       static_cast<int>(N), static_cast<int>(M), static_cast<int>(K), lr, mu, wd,
-                       static_cast<int>(tiles_m), static_cast<int>(tiles), static_cast<uint32_t>(u_bytes),
-                       static_cast<uint32_t>(v_bytes), part, sfb_part_stride(N, M), sps);
-    PSD_HIP_TRY(hipGetLastError());
-    if (splits > 1) return launch_sfb_reduce(part, splits, N, M, W, Mom, lr, mu, wd, st);
-    return PSD_OK;
+    grid_body<BN, BM, false, true>(g, &blocks);
 }
 
-template <int BN>
-psd_status launch_f32_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int64_t ldu, int64_t ldv, float* W,
-                             float* Mom, int64_t N, int64_t M, float lr, float mu, float wd, hipStream_t st)
+// How one layer is covered: `big` tiles of 128 x 128 and then tiles of (64*bn) x (64*bm).
+struct Cover { int bn, bm; int64_t big, tiles_m, groups; };
+
+Cover uniform_cover(int64_t N, int64_t M, int bn, int bm)
 {
-    constexpr int TN = 64 * BN;
-    const int64_t tiles_n = (N + TN - 1) / TN, tiles_m = (M + TM - 1) / TM;
-    const int64_t tiles = tiles_n * tiles_m;
-    if (tiles < 1 || tiles > 0x7fffffff) return PSD_E_INVALID;
-    const int64_t u_bytes = B * ldu * 4, v_bytes = B * ldv * 4;        // one block
-    if (u_bytes >= (int64_t(1) << 32) || v_bytes >= (int64_t(1) << 32)) return PSD_E_UNSUPPORTED;
-    hipLaunchKernelGGL(sfb_f32_blocks_kernel<BN>, dim3(static_cast<uint32_t>(tiles)), dim3(THREADS), 0, st, blocks,
-                       static_cast<int>(P), static_cast<int>(B / KT), ldu, ldv, W, Mom, static_cast<int>(N),
-                       static_cast<int>(M), static_cast<int>(P * B), lr, mu, wd, static_cast<int>(tiles_m), static_cast<int>(tiles),
-                       static_cast<uint32_t>(u_bytes), static_cast<uint32_t>(v_bytes));
-    PSD_HIP_TRY(hipGetLastError());
-    return PSD_OK;
+    const int64_t tm = (M + 64 * bm - 1) / (64 * bm), tn = (N + 64 * bn - 1) / (64 * bn);
+    return {bn, bm, bn * bm == 4 ? tn * tm : 0, tm, tn * tm};
 }
 
-// tile choice (and, with a workspace, the split of K) for one layer
-void choose_f32(int64_t N, int64_t M, int64_t K, bool may_split, int* bn, int* splits)
+Cover choose_f32(int64_t N, int64_t M, int64_t K)
 {
-    // 128 x 128 tiles unless that leaves fewer than two workgroups per compute unit (one workgroup's
-    // four wavefronts cannot hide LDS and barrier latency on their own); with a workspace, few tiles
-    // are made up for by splitting K instead of by halving the tile
-    const int64_t slots = 2 * int64_t(device_cu_count());
-    const int64_t tiles128 = ((N + 127) / 128) * ((M + TM - 1) / TM);
     const int forced = tune_value(PSD_TUNE_SFB_F32_TILE);
-    const int s128 = may_split ? sfb_splits_for(tiles128, slots, K) : 1;
-    if (forced == 1 || forced == 2) *bn = forced;
-    else *bn = (tiles128 < slots && s128 == 1) ? 1 : 2;
-    const int64_t tiles = ((N + 64 * *bn - 1) / (64 * *bn)) * ((M + TM - 1) / TM);
-    *splits = may_split ? sfb_splits_for(tiles, slots, K) : 1;
+    if (forced == 1 || forced == 2) return uniform_cover(N, M, forced, 2);
+    // A compute unit works through its tiles at the rate of its MFMA pipe, so the launch takes as long as the compute unit
+    // with the most tile area: count in units of 128 x 128 tiles per compute unit, smaller tiles with what their shorter
+    // runs between barriers cost (64 x 128: 6 %, 64 x 64: 20 %), a lone 128 x 128 tile (one wavefront per SIMD) with 7 %.
+    // 3000 -> 3000, K = 2048: 576 tiles are 2.25 units in 2 rounds of 128 x 128 and one of 64 x 64: 404 -> 304 us.
+    const int64_t cus = device_cu_count();
+    auto rounds = [&](int64_t workgroups, double unit) { return static_cast<double>((workgroups + cus - 1) / cus) * unit; };
+    const Cover half = uniform_cover(N, M, 1, 2), quarter = uniform_cover(N, M, 1, 1), all = uniform_cover(N, M, 2, 2);
+    Cover best = half;
+    double cost = rounds(half.groups, 0.53);
+    auto consider = [&](const Cover& c, double x) { if (x < cost) { cost = x; best = c; } };
+    consider(quarter, rounds(quarter.groups, 0.30));
+    // A short contraction is mostly W / Mom update, which three 64 x 128 tiles on a compute unit overlap better than two
+    // 128 x 128 ones (9216 -> 4096: K = 64 122 against 144 us, K = 256 201 / 225, K = 512 348 / 340).
+    if (K >= 448) {
+        const int64_t full = all.big / cus, rem = all.big % cus;
+        consider(all, rounds(all.big, 1.0) * (all.big <= cus ? 1.07 : 1.0));
+        if (full > 0 && rem > 0) {
+            consider({1, 2, full * cus, all.tiles_m, full * cus + 2 * rem}, full + rounds(2 * rem, 0.53));
+            consider({1, 1, full * cus, all.tiles_m, full * cus + 4 * rem}, full + rounds(4 * rem, 0.30));
+        }
+    }
+    return best;
+}
+
+template <int BN, int BM, bool PART>
+psd_status start(const Args& g, const BlockPtrs* blocks, int64_t groups, hipStream_t st)
+{
+    if (groups < 1 || groups > 0x7fffffff) return PSD_E_INVALID;
+    const size_t lds = g.big > 0 ? Tile<2, 2>::LDS_BYTES : Tile<BN, BM>::LDS_BYTES;
+    const dim3 grid(static_cast<uint32_t>(groups));
+    if constexpr (PART) hipLaunchKernelGGL((sfb_f32_kernel<BN, BM, true>), grid, dim3(THREADS), lds, st, g);
+    else if (blocks) hipLaunchKernelGGL((sfb_f32_blocks_kernel<BN, BM>), grid, dim3(THREADS), lds, st, g, *blocks);
+    else hipLaunchKernelGGL((sfb_f32_kernel<BN, BM, false>), grid, dim3(THREADS), lds, st, g);
+    PSD_HIP_TRY(hipGetLastError());
+    return PSD_OK;
+}
+
+Args common_args(int64_t ldu, int64_t ldv, float* W, float* Mom, int64_t N, int64_t M, int64_t K, float lr, float mu, float wd)
+{
+    Args g = {};
+    g.ldu = ldu; g.ldv = ldv; g.W = W; g.Mom = Mom;
+    g.N = static_cast<int>(N); g.M = static_cast<int>(M); g.K = static_cast<int>(K);
+    g.lr = lr; g.mu = mu; g.wd = wd;
+    return g;
+}
+
+psd_status launch_cover(Args& g, const BlockPtrs* blocks, hipStream_t st)
+{
+    const Cover c = choose_f32(g.N, g.M, g.K);
+    if (c.groups > 0x7fffffff) return PSD_E_INVALID;
+    g.big = static_cast<int>(c.big);
+    g.tiles_m = static_cast<int>(c.tiles_m);
+    return c.bm == 2 ? start<1, 2, false>(g, blocks, c.groups, st) : start<1, 1, false>(g, blocks, c.groups, st);
 }
 
 }  // namespace
 
+// how many ways psd_sync_fc_sfb may split this layer's sum over k when it is given a workspace (1 = not at all)
 int sfb_f32_splits(int64_t N, int64_t M, int64_t K)
 {
-    int bn, s;
-    choose_f32(N, M, K, true, &bn, &s);
-    return s;
+    const int64_t slots = 2 * int64_t(device_cu_count());
+    const int64_t tiles128 = ((N + 127) / 128) * ((M + 127) / 128);
+    return sfb_splits_for(tiles128, slots, K);
 }
 
 psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t ldv, float* W, float* Mom,
                           int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int splits,
                           hipStream_t st)
 {
-    int bn, s;
-    choose_f32(N, M, K, splits > 1, &bn, &s);
-    if (bn == 1) return launch_f32<1>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
-    return launch_f32<2>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
+    // 32-bit byte offsets into each factor matrix, with room for the stages of read-ahead
+    const int64_t u_bytes = K * ldu * 4, v_bytes = K * ldv * 4;
+    const int64_t reach = (int64_t(1) << 32) - (NSTAGE + 2) * KT * (ldu > ldv ? ldu : ldv) * 4 - 4096;
+    if (u_bytes > reach || v_bytes > reach) return PSD_E_UNSUPPORTED;
+    Args g = common_args(ldu, ldv, W, Mom, N, M, K, lr, mu, wd);
+    g.U = U; g.V = V;
+    g.u_bytes = static_cast<uint32_t>(u_bytes); g.v_bytes = static_cast<uint32_t>(v_bytes);
+    if (splits <= 1) return launch_cover(g, nullptr, st);
+    const Cover c = uniform_cover(N, M, 1, 1);
+    g.tiles_m = static_cast<int>(c.tiles_m);
+    g.tiles = static_cast<int>(c.groups);
+    g.part = part; g.part_stride = sfb_part_stride(N, M);
+    g.stages_per_split = static_cast<int>(((K + KT - 1) / KT + splits - 1) / splits);
+    const psd_status r = start<1, 1, true>(g, nullptr, c.groups * splits, st);
+    if (r != PSD_OK) return r;
+    return launch_sfb_reduce(part, splits, N, M, W, Mom, lr, mu, wd, st);
 }
 
 bool sfb_f32_blocks_supported(int64_t B) { return B % KT == 0; }     // whole k-stages per block
@@ -333,15 +382,17 @@ psd_status launch_sfb_f32_blocks(const float* const* U_p, int64_t ldu, const flo
                                  hipStream_t st)
 {
     if (P < 1 || P > PSD_MAX_WORKERS || !sfb_f32_blocks_supported(B)) return PSD_E_UNSUPPORTED;
+    const int64_t u_bytes = B * ldu * 4, v_bytes = B * ldv * 4;        // one block
+    if (u_bytes >= (int64_t(1) << 32) || v_bytes >= (int64_t(1) << 32)) return PSD_E_UNSUPPORTED;
     BlockPtrs blocks;
     for (int64_t p = 0; p < PSD_MAX_WORKERS; ++p) {
         blocks.u[p] = p < P ? U_p[p] : nullptr;
         blocks.v[p] = p < P ? V_p[p] : nullptr;
     }
-    int bn, s;
-    choose_f32(N, M, P * B, false, &bn, &s);
-    if (bn == 1) return launch_f32_blocks<1>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
-    return launch_f32_blocks<2>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
+    Args g = common_args(ldu, ldv, W, Mom, N, M, P * B, lr, mu, wd);
+    g.u_bytes = static_cast<uint32_t>(u_bytes); g.v_bytes = static_cast<uint32_t>(v_bytes);
+    g.n_blocks = static_cast<int>(P); g.stages_per_block = static_cast<int>(B / KT);
+    return launch_cover(g, &blocks, st);
 }
 
 }  // namespace psd

@@ -244,6 +244,46 @@ def test_sfb_f32_both_tile_shapes_bit_exact(tile, pinned_tile):
     assert np.array_equal(Mg, Mr) and np.array_equal(Wg, Wr)
 
 
+@pytest.mark.parametrize("M,N", [(2181, 2170),       # 306 tiles of 128 x 128 on 256 compute units: the last 50 as 64 x 64; odd rows
+                                 (2400, 2404)])      # 361 tiles: the last 105 as 64 x 128
+def test_sfb_f32_mixed_tile_sizes_bit_exact(M, N):
+    """One launch that covers W with 128 x 128 tiles and cuts the rest smaller, stacked and (aligned rows) from blocks."""
+    d = inputs.fc_layer_integer(M, N, B=112, P=4, seed=M + N)
+    Wg, Mg, _ = run_sfb(d, psd.F32, 0.25, 0.5)
+    U, V = orc.pack_factors(d["delta"], d["act"])
+    Wr, Mr = orc.sync_fc_sfb(U, V, d["W"], d["Mom"], 0.25, 0.5)
+    assert np.array_equal(Mg, Mr), np.argwhere(Mg != Mr)[:8]
+    assert np.array_equal(Wg, Wr)
+    if M % 4 == 0 and N % 4 == 0:
+        plan = psd.plan_layer(psd.LAYER_FC, M, N, 112, 4)
+        W, Mom = dev(d["W"]), dev(d["Mom"])
+        psd.sync_fc_sfb_blocks(plan, psd.F32, [dev(x) for x in d["delta"]], 0, [dev(x) for x in d["act"]], 0, W, Mom, 0.25, 0.5)
+        torch.cuda.synchronize()
+        assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr)
+
+
+@pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
+@pytest.mark.parametrize("M", [31, 33, 64, 95, 126, 130, 193, 257])
+def test_sfb_row_starts_at_every_place_of_a_cache_line(M, dtype):
+    """Rows of W that start at every offset into a cache line, and tiles that share quads and lines with their neighbours;
+    W and Mom are surrounded by guard values that must survive."""
+    d = inputs.fc_layer_integer(M, 133, B=5, P=3, seed=M)
+    plan, U, ldu, V, ldv = run_pack(d, dtype)
+    n = 133 * M
+    for lead in (0, 4, 12):                              # base addresses that are 16-byte but not line aligned
+        flat = [torch.full((n + 64,), 77.0, device=DEV) for _ in range(2)]
+        W, Mom = flat[0][lead:lead + n].view(133, M), flat[1][lead:lead + n].view(133, M)
+        W.copy_(dev(d["W"]))
+        Mom.copy_(dev(d["Mom"]))
+        psd.sync_fc_sfb(plan, dtype, U, ldu, V, ldv, W, Mom, 0.25, 0.5)
+        torch.cuda.synchronize()
+        Uo, Vo = orc.pack_factors(d["delta"], d["act"])
+        Wr, Mr = orc.sync_fc_sfb(Uo, Vo, d["W"], d["Mom"], 0.25, 0.5)
+        assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr)
+        for f in flat:
+            assert bool((f[:lead] == 77).all()) and bool((f[lead + n:] == 77).all())
+
+
 @pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
 def test_weight_decay_bit_exact_on_both_routes(dtype):
     # wd, lr, mu powers of two and integer data: every intermediate is exact in fp32
