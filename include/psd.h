@@ -115,9 +115,9 @@ psd_status psd_pack_factors(const psd_plan* plan, const float* const* delta_p,
  * workspace [dev] (optional): scratch for layers with so few output tiles (128 x 128 weights each)
  * that most compute units would get none (e.g. a 1024 -> 1000 classifier).  With workspace_bytes == 0 (workspace may be NULL) every tile is contracted
  * over all of K by one workgroup.  With a workspace of at least psd_sfb_workspace_bytes() bytes,
- * 16-byte aligned, the sum over k is split over up to 4 workgroups per tile: each stores a partial dW
- * (N x M fp32) to the workspace, then the partials are added in split order and the update is applied
- * (same arithmetic; only the order of the fp32 additions over k changes).  A non-zero workspace_bytes
+ * 16-byte aligned, the sum over k may be split over up to 4 workgroups per tile where that is faster: each
+ * stores a partial dW (N x M fp32) to the workspace, then the partials are added in split order and the
+ * update is applied (same arithmetic; only the order of the fp32 additions over k changes).  A non-zero workspace_bytes
  * below the queried size is refused with PSD_E_WORKSPACE.  The workspace is not retained; its contents
  * after the call are unspecified; calls that share one workspace must not overlap in time. */
 psd_status psd_sync_fc_sfb(const psd_plan* plan, int32_t factor_dtype,
@@ -125,7 +125,7 @@ psd_status psd_sync_fc_sfb(const psd_plan* plan, int32_t factor_dtype,
                            float* W, float* Mom, float lr, float mu, float wd,
                            void* workspace, size_t workspace_bytes, void* stream);
 
-/* Bytes of workspace with which psd_sync_fc_sfb would split this layer's sum over k (a multiple of
+/* Bytes of workspace with which psd_sync_fc_sfb may split this layer's sum over k (a multiple of
  * 16), or 0 if it would not split it (enough tiles already, K too short, bad arguments).  Host only;
  * depends on the layer shape, the factor dtype, the current device's CU count and the pinned tile. */
 size_t psd_sfb_workspace_bytes(const psd_plan* plan, int32_t factor_dtype);

@@ -65,14 +65,14 @@ struct PackArgs {
 };
 psd_status launch_pack(PackArgs& a, int32_t out_dtype, hipStream_t st);
 
-// ---- reconstruction.  part / splits: with splits > 1 the contraction is split over `splits`
-// workgroups per tile, each storing a partial dW (N x M, sfb_part_stride apart) to `part`, and the
-// partials are summed in split order and the update applied by launch_sfb_reduce.
+// ---- reconstruction.  part / most_splits: with a workspace for most_splits > 1 partial sums the contraction
+// may be split over up to that many workgroups per tile, each storing a partial dW (N x M, sfb_part_stride
+// apart) to `part`, and the partials are summed in split order and the update applied by launch_sfb_reduce.
 psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t ldv, float* W, float* Mom,
-                          int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int splits,
+                          int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int most_splits,
                           hipStream_t st);
 psd_status launch_sfb_bf16(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t ldv, float* W, float* Mom,
-                           int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int splits,
+                           int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int most_splits,
                            hipStream_t st);
 // reconstruction straight from the P per-worker blocks (B x ld each, no stacked copy); served when a block
 // holds whole k-stages of the kernel (16 rows fp32, 32 rows bf16)
@@ -84,19 +84,16 @@ psd_status launch_sfb_f32_blocks(const float* const* U_p, int64_t ldu, const flo
 psd_status launch_sfb_bf16_blocks(const uint16_t* const* U_p, int64_t ldu, const uint16_t* const* V_p, int64_t ldv,
                                   int64_t P, int64_t B, float* W, float* Mom, int64_t N, int64_t M, float lr, float mu,
                                   float wd, hipStream_t st);
-// how many ways each kernel would split K for this layer when it is given a workspace (1 = not at all)
+// how many ways each kernel may split K for this layer when it is given a workspace (1 = not at all)
 int sfb_f32_splits(int64_t N, int64_t M, int64_t K);
 int sfb_bf16_splits(int64_t N, int64_t M, int64_t K);
 psd_status launch_sfb_reduce(const float* part, int splits, int64_t N, int64_t M, float* W, float* Mom, float lr,
                              float mu, float wd, hipStream_t st);
 
 constexpr int kMaxSplits = 4;
-// Split only for layers that leave most of the chip idle: while the split workgroups still number at
-// most one per CU (half the slots) and every split keeps at least kMinSplitRows k rows.  A split
-// costs 8 extra bytes of HBM traffic per weight and split (partial written, then read) plus a second
-// launch.  Measured: 64 tiles (1024 -> 1000, K = 8192) 64 -> 32 us, 16 tiles (512 -> 512, K = 16384)
-// 115 -> 37 us; but 256 tiles (4096 -> 1000, one workgroup per CU already) lose at every K tried
-// (K = 2048: 39 -> 49 us, K = 8192: 103 -> 107 us), so such layers are not split.
+// A workspace is asked for by layers that leave most of the chip idle: while the split workgroups (of 128 x 128 tiles)
+// still number at most one per CU (half the slots) and every split keeps at least kMinSplitRows k rows.  Whether the
+// sum is then split is for the launchers to say.
 constexpr int64_t kMinSplitRows = 512;
 inline int sfb_splits_for(int64_t tiles, int64_t slots, int64_t K)
 {

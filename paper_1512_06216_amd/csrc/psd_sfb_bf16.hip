@@ -18,7 +18,7 @@
 //
 // MFMA operand roles are swapped (rows = m, columns = n) so that the four consecutive
 // accumulator rows a lane owns are four adjacent m of one W row; the epilogue turns each
-// block through LDS so that W and Mom move in 16-byte accesses, 128 contiguous bytes per row.
+// block through LDS so that W and Mom move in 16-byte accesses, one whole cache line per row.
 #include <atomic>
 #include "psd_device.h"
 #include "psd_internal.h"
@@ -47,8 +47,10 @@ struct Cfg {
     static constexpr int NI_A = A_BYTES / 1024 / WAVES;          // 1 KiB DMA instructions per wavefront
     static constexpr int NI_B = B_BYTES / 1024 / WAVES;
     static constexpr int PATCH_BYTES = WAVES * 32 * PLD * 4;
-    static constexpr size_t LDS_BYTES =
-        size_t(NSTAGE) * STAGE_BYTES > size_t(PATCH_BYTES) ? size_t(NSTAGE) * STAGE_BYTES : size_t(PATCH_BYTES);
+    static constexpr int STRIDE = TM + 36, ROWS = 32 * WN;       // row buffer of the update (RowUpdate), in floats
+    static constexpr size_t larger(size_t a, size_t b) { return a > b ? a : b; }
+    static constexpr size_t LDS_BYTES = larger(size_t(NSTAGE) * STAGE_BYTES, PATCH_BYTES);
+    static constexpr size_t LDS_BYTES_ROWS = larger(LDS_BYTES, size_t(ROWS) * STRIDE * 4);
     static_assert(A_BYTES % (1024 * WAVES) == 0 && B_BYTES % (1024 * WAVES) == 0, "stage must split into 1 KiB runs");
     static_assert(RA % 128 == 0 && RB % 128 == 0, "the swizzle permutes chunks inside 128-byte groups");
     static_assert(NSTAGE >= 3, "the pipeline keeps at least one stage in flight beyond the one being awaited");
@@ -70,6 +72,7 @@ __device__ __forceinline__ bf16x4 read_tr(uint32_t lds_addr)
 // block (and aimed at nothing past the last one, which reads as zeros like the K tail does).
 struct BlockPtrs { const uint16_t* u[PSD_MAX_WORKERS]; const uint16_t* v[PSD_MAX_WORKERS]; };
 
+// STREAM: the rows of W and Mom start on cache-line boundaries (see the epilogue).
 template <class C, bool PART, bool BLK, bool STREAM>
 __device__ __forceinline__ void
 sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __restrict__ V, int64_t ldv,
@@ -241,8 +244,9 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
     __syncthreads();
     load_frags(stage_base(0), 0, a0, b0);
     // A wavefront issues at most one LDS instruction per ~16 cycles and one MFMA per 32, in program
-    // order; operand reads are therefore spread between the MFMAs they do not feed (1 MFMA, then
-    // its share of reads, ...) so that their issue time hides under MFMA execution.
+    // order; operand reads are therefore interleaved with the MFMAs they do not feed, two after each
+    // of the first ones, so that their issue time hides under MFMA execution and the last of them is
+    // back before it is waited for (spread evenly to the end: 1-2 % slower).
     auto interleave = [&]() { interleave_groups<2 * (C::BN + C::BM), C::BN * C::BM, 2>(); };
     for (int t = 0; t < steps; ++t) {
         load_frags(stage_base(t), 16, a1, b1);
@@ -263,18 +267,36 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
     // Epilogue.  Accumulator register r of block (bn, bm) holds MFMA row 8*(r/4) + 4*(lane/32) + r%4
     // (= m offset) and column lane%32 (= n offset): four adjacent m per register quad.
     const int l32 = lane & 31, lhi = lane >> 5;
-    if (M % 4 == 0) {
-        // Fast path.  Held as they are, the quads of one W row sit in 2 lanes x 4 registers, and a
+    if constexpr (PART) {
+#pragma unroll
+        for (int bn = 0; bn < C::BN; ++bn) {
+            const int64_t n = n0 + wn0 + 32 * bn + l32;
+            if (n >= N) continue;
+#pragma unroll
+            for (int bm = 0; bm < C::BM; ++bm)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int64_t m = m0 + wm0 + 32 * bm + 8 * q + 4 * lhi;
+                    float* to = part + split * part_stride + n * int64_t(M) + m;
+                    if (M % 4 == 0) {
+                        if (m < M) *reinterpret_cast<float4*>(to) = make_float4(acc[bn][bm][4 * q], acc[bn][bm][4 * q + 1],
+                                                                                acc[bn][bm][4 * q + 2], acc[bn][bm][4 * q + 3]);
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (m + i < M) to[i] = acc[bn][bm][4 * q + i];
+                    }
+                }
+        }
+    } else if constexpr (STREAM) {
+        // Rows of W start on cache-line boundaries (M a multiple of 32).
+        // Held as they are, the quads of one W row sit in 2 lanes x 4 registers, and a
         // wavefront access would touch 32 rows x 32 bytes: measured at ~3.1 TB/s for the W/Mom
         // read-modify-write, against ~4.9 TB/s once every row gets >= 128 contiguous bytes per
         // instruction.  So each 32 x 32 block is turned through a private LDS patch: written as
-        // held, read back with 8 lanes per row, then 8 rows x 128 bytes per global access.
+        // held, read back with 8 lanes per row, then 8 rows x 128 bytes per global access, streamed.
         float* patch = reinterpret_cast<float*>(lds) + wave * (32 * PLD);
         const int prow = lane >> 3, pcol = 4 * (lane & 7);
-        // STREAM: W / Mom with the streaming hint.  The host asks for it when their rows start on cache-line
-        // boundaries (every 128-byte access is then a whole line); with rows that start mid-line (M = 3000)
-        // the hint makes the partial-line stores expensive (measured 3000 -> 21841: 468 -> 534 us).
-        constexpr bool stream = STREAM;
 #pragma unroll
         for (int bn = 0; bn < C::BN; ++bn) {
 #pragma unroll
@@ -286,25 +308,13 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
                                     acc[bn][bm][4 * q + 3]);
                 float4 d[4], w[4], mo[4];
                 const int64_t m = m0 + wm0 + 32 * bm + pcol;
-                if constexpr (PART) {
-                    float* dst = part + split * part_stride;
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) {
-                        const int64_t n = n0 + wn0 + 32 * bn + prow + 8 * jj;
-                        d[jj] = *reinterpret_cast<const float4*>(patch + (prow + 8 * jj) * PLD + pcol);
-                        if (n < N && m < M) *reinterpret_cast<float4*>(dst + n * int64_t(M) + m) = d[jj];
-                    }
-                    continue;
-                }
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) {
                     const int64_t n = n0 + wn0 + 32 * bn + prow + 8 * jj;
                     d[jj] = *reinterpret_cast<const float4*>(patch + (prow + 8 * jj) * PLD + pcol);
                     if (n < N && m < M) {                  // m % 4 == 0 and M % 4 == 0: whole quad inside
-                        const float* wp = W + n * int64_t(M) + m;
-                        const float* mp = Mom + n * int64_t(M) + m;
-                        w[jj] = stream ? load_stream4(wp) : *reinterpret_cast<const float4*>(wp);
-                        mo[jj] = stream ? load_stream4(mp) : *reinterpret_cast<const float4*>(mp);
+                        w[jj] = load_stream4(W + n * int64_t(M) + m);
+                        mo[jj] = load_stream4(Mom + n * int64_t(M) + m);
                     }
                 }
 #pragma unroll
@@ -315,41 +325,40 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
                         upd(d[jj].y, w[jj].y, mo[jj].y, lr, mu, wd);
                         upd(d[jj].z, w[jj].z, mo[jj].z, lr, mu, wd);
                         upd(d[jj].w, w[jj].w, mo[jj].w, lr, mu, wd);
-                        if (stream) {
-                            store_stream4(Mom + n * int64_t(M) + m, mo[jj]);
-                            store_stream4(W + n * int64_t(M) + m, w[jj]);
-                        } else {
-                            *reinterpret_cast<float4*>(Mom + n * int64_t(M) + m) = mo[jj];
-                            *reinterpret_cast<float4*>(W + n * int64_t(M) + m) = w[jj];
-                        }
+                        store_stream4(Mom + n * int64_t(M) + m, mo[jj]);
+                        store_stream4(W + n * int64_t(M) + m, w[jj]);
                     }
                 }
             }
         }
     } else {
-        // rows of W are not 16-byte aligned: plain 4-byte accesses straight from the accumulators
+        // Rows of W start anywhere in a cache line: the rows of one bn of all wavefronts go through LDS at a time and come back
+        // as whole lines of W (RowUpdate).  With the patch above every access would straddle two lines: 3000 -> 21841,
+        // K = 2048 468 -> 401 us; rows that are not even 16-byte aligned (3001 -> 21841), element by element before,
+        // 1873 -> 445 us.
+        float* buf = reinterpret_cast<float*>(lds);
 #pragma unroll
         for (int bn = 0; bn < C::BN; ++bn) {
-            const int64_t n = n0 + wn0 + 32 * bn + l32;
-            if (n >= N) continue;
-            float* wrow = W + n * int64_t(M);
-            float* mrow = Mom + n * int64_t(M);
+            auto row_n = [&](int r) { return n0 + (r >> 5) * 32 * C::BN + 32 * bn + (r & 31); };
+            RowUpdate<C::ROWS, C::TM, C::STRIDE, C::WAVES, C::BM == 4 ? 4 : 5, decltype(row_n)> rows(W, Mom, row_n, m0, N, M, wave, lane);
+            rows.template fetch<0>();
+            if (bn > 0) __syncthreads();           // the rows before are no longer read
+            const int r = (wave / C::WM) * 32 + l32;
+            float* to = buf + r * C::STRIDE + wm0 + 4 * lhi + line_shift(W, row_n(r), M);
 #pragma unroll
             for (int bm = 0; bm < C::BM; ++bm)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int64_t m = m0 + wm0 + 32 * bm + 8 * (r >> 2) + 4 * lhi + (r & 3);
-                    if constexpr (PART) {
-                        if (m < M) part[split * part_stride + n * int64_t(M) + m] = acc[bn][bm][r];
-                        continue;
-                    }
-                    if (m < M) {
-                        float wv = wrow[m], mv = mrow[m];
-                        upd(acc[bn][bm][r], wv, mv, lr, mu, wd);
-                        mrow[m] = mv;
-                        wrow[m] = wv;
+                for (int q = 0; q < 4; ++q) {
+                    const f32x16& a = acc[bn][bm];
+                    if (M % 4 == 0) {              // shifts are multiples of 4: 16-byte LDS writes
+                        *reinterpret_cast<float4*>(to + 32 * bm + 8 * q) = make_float4(a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]);
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) to[32 * bm + 8 * q + i] = a[4 * q + i];
                     }
                 }
+            __syncthreads();
+            rows.run(buf, lr, mu, wd);
         }
     }
 }
@@ -376,6 +385,12 @@ sfb_bf16_blocks_kernel(BlockPtrs blocks, int n_blocks, int stages_per_block, int
                                   v_bytes, nullptr, 0, 0, 0, 0, &blocks, n_blocks, stages_per_block);
 }
 
+// do all rows of W and Mom start on cache-line boundaries (128 bytes)?
+bool rows_on_lines(const float* W, const float* Mom, int64_t M)
+{
+    return M % 32 == 0 && (reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(Mom)) % 128 == 0;
+}
+
 template <class C>
 psd_status launch_cfg_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int64_t ldu, int64_t ldv, float* W, float* Mom,
                              int64_t N, int64_t M, float lr, float mu, float wd, hipStream_t st)
@@ -385,16 +400,18 @@ psd_status launch_cfg_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int6
     if (tiles < 1 || tiles > 0x3fffffff) return PSD_E_INVALID;
     const int64_t u_bytes = B * ldu * 2, v_bytes = B * ldv * 2;          // one block
     if (u_bytes >= (int64_t(1) << 32) || v_bytes >= (int64_t(1) << 32)) return PSD_E_UNSUPPORTED;
-    auto kern = M % 32 == 0 ? sfb_bf16_blocks_kernel<C, true> : sfb_bf16_blocks_kernel<C, false>;
+    const bool lines = rows_on_lines(W, Mom, M);
+    auto kern = lines ? sfb_bf16_blocks_kernel<C, true> : sfb_bf16_blocks_kernel<C, false>;
+    const size_t lds = lines ? C::LDS_BYTES : C::LDS_BYTES_ROWS;
     static std::atomic<bool> attr_done{false};
     if (!attr_done.load(std::memory_order_acquire)) {
         PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_blocks_kernel<C, true>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES)));
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_blocks_kernel<C, false>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES)));
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         attr_done.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(tiles)), dim3(C::THREADS), C::LDS_BYTES, st,
+    hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(tiles)), dim3(C::THREADS), lds, st,
                        blocks, static_cast<int>(P), static_cast<int>(B / KT), ldu, ldv, W, Mom, static_cast<int>(N),
                        static_cast<int>(M), static_cast<int>(P * B), lr, mu, wd, static_cast<int>(tiles_n),
                        static_cast<int>(tiles_m), static_cast<uint32_t>(u_bytes), static_cast<uint32_t>(v_bytes));
@@ -414,25 +431,26 @@ psd_status launch_cfg(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t
     const int64_t u_bytes = K * ldu * 2, v_bytes = K * ldv * 2;
     const int64_t reach = (int64_t(1) << 32) - (C::NSTAGE + 2) * KT * (ldu > ldv ? ldu : ldv) * 2 - 4096;
     if (u_bytes > reach || v_bytes > reach) return PSD_E_UNSUPPORTED;
-    // W / Mom are streamed when their rows start on cache-line boundaries (see the epilogue)
+    const bool lines = rows_on_lines(W, Mom, M);
     auto kern = splits > 1 ? sfb_bf16_kernel<C, true, false>
-                           : (M % 32 == 0 ? sfb_bf16_kernel<C, false, true> : sfb_bf16_kernel<C, false, false>);
+                           : (lines ? sfb_bf16_kernel<C, false, true> : sfb_bf16_kernel<C, false, false>);
+    const size_t lds = splits > 1 || lines ? C::LDS_BYTES : C::LDS_BYTES_ROWS;
     // raise the dynamic LDS limit once per process (idempotent, so a race between two first
     // callers is harmless; the flag only saves the call on later launches)
     static std::atomic<bool> attr_done{false};
     if (!attr_done.load(std::memory_order_acquire)) {
         PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_kernel<C, true, false>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES)));
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_kernel<C, false, true>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES)));
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_kernel<C, false, false>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES)));
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         attr_done.store(true, std::memory_order_release);
     }
     const int skew = tune_value(PSD_TUNE_SFB_BF16_SKEW_US);
     const int64_t stages = (K + KT - 1) / KT;
     const int sps = static_cast<int>((stages + splits - 1) / splits);
-    hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(tiles * splits)), dim3(C::THREADS), C::LDS_BYTES, st, U, ldu, V,
+    hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(tiles * splits)), dim3(C::THREADS), lds, st, U, ldu, V,
                        ldv, W, Mom, static_cast<int>(N), static_cast<int>(M), static_cast<int>(K), lr, mu, wd,
                        static_cast<int>(tiles_n), static_cast<int>(tiles_m), static_cast<uint32_t>(u_bytes),
                        static_cast<uint32_t>(v_bytes), part, sfb_part_stride(N, M), sps,
@@ -444,54 +462,92 @@ psd_status launch_cfg(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t
 
 using Cfg128x256w4 = Cfg<2, 2, 2, 4, 3, 2>;   // 4 wavefronts of 64 x 128, 3 stages (72 KiB), two workgroups per CU
 using Cfg128x192w4 = Cfg<2, 2, 2, 3, 4, 2>;   // 4 wavefronts of 64 x 96, 4 stages (80 KiB), two workgroups per CU
-using Cfg128x128w4 = Cfg<2, 2, 2, 2, 4, 2>;   // small layers: more workgroups (64 KiB, two per CU)
+using Cfg128x128w4 = Cfg<2, 2, 2, 2, 4, 2>;   // 64 KiB, two per CU
+using Cfg64x128w4 = Cfg<2, 2, 1, 2, 4, 3>;    // 48 KiB, three per CU
+using Cfg64x64w4 = Cfg<2, 2, 1, 1, 4, 4>;     // 32 KiB, five per CU: small layers
 
 }  // namespace
 
 namespace {
-struct Bf16Tile { int id, tn, tm; };
-// tile choice (and, with a workspace, the split of K) for one layer
-void choose_bf16(int64_t N, int64_t M, int64_t K, bool may_split, Bf16Tile* tile, int* splits)
+// What one tile costs a compute unit, in us: `area` times the update of 64 x 64 weights of W and Mom at the compute unit's
+// share of HBM (3.1 us) plus `loop` per 1024 k rows; alone on its compute unit, `first` plus `solo` per 1024 k rows.
+// Fitted to 9216 -> 4096 and 1024 -> 1000 over K = 256 .. 2048; predicts the other shapes tried within 10 %.
+struct Bf16Tile { int id, tn, tm; double area, loop, first, solo; };
+const Bf16Tile kTiles[] = {{0, 128, 256, 8, 9.9, 16.6, 15.1}, {1, 128, 192, 6, 6.6, 14.0, 8.3}, {2, 128, 128, 4, 5.7, 10.5, 7.1},
+                           {3, 64, 128, 2, 3.8, 7.0, 6.6}, {4, 64, 64, 1, 2.5, 4.7, 6.5}};
+
+// us for the launch that covers N x M over K rows.  Layers whose rows of W do not start on cache lines touch one more
+// line per row of a tile.
+double launch_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K)
 {
-    static const Bf16Tile tiles_by_id[] = {{0, 128, 256}, {1, 128, 192}, {2, 128, 128}};
-    const int64_t slots = int64_t(device_cu_count()) * 2;
-    int pick = tune_value(PSD_TUNE_SFB_BF16_TILE);
-    if (pick < 0 || pick > 2) {
-        // Workgroups of one launch run in rounds of (CUs x workgroups per CU); a partly filled last
-        // round costs as much as a full one.  Pick the tile whose rounds x tile area is smallest
-        // (ties go to the larger tile; the 128 x 128 tile pays ~10% for its lower MFMA duty).
-        const int weight[] = {100, 100, 110};
-        int64_t best = -1;
-        for (const Bf16Tile& c : tiles_by_id) {
-            const int64_t tiles = ((N + c.tn - 1) / c.tn) * ((M + c.tm - 1) / c.tm);
-            const int64_t cost = ((tiles + slots - 1) / slots) * c.tn * c.tm * weight[c.id];
-            if (best < 0 || cost < best) { best = cost; pick = c.id; }
-        }
+    const int64_t cus = device_cu_count(), tiles = ((N + t.tn - 1) / t.tn) * ((M + t.tm - 1) / t.tm);
+    const double k = static_cast<double>(K) / 1024, lines = t.tm / 32;
+    const double update = 3.1 * t.area * (M % 32 ? (lines + 1) / lines : 1);
+    if (tiles > cus) return 5 + static_cast<double>((tiles + cus - 1) / cus) * (update + t.loop * k);
+    const double solo = t.first + t.solo * k, shared = 5 + update * static_cast<double>(tiles) / cus + t.loop * k;
+    return solo > shared ? solo : shared;
+}
+
+// ... and when `splits` workgroups per tile store partial sums that a second launch adds up
+double split_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K, int splits)
+{
+    const int64_t cus = device_cu_count(), groups = ((N + t.tn - 1) / t.tn) * ((M + t.tm - 1) / t.tm) * splits;
+    const double k = static_cast<double>(K) / splits / 1024, sum = 4 + (16.0 + 4 * splits) * N * M / 5e6;
+    if (groups > cus) return sum + 5 + static_cast<double>((groups + cus - 1) / cus) * (0.8 * t.area + t.loop * k);
+    return sum + t.first + t.solo * k;
+}
+
+// tile choice for one layer
+Bf16Tile choose_bf16(int64_t N, int64_t M, int64_t K)
+{
+    const int pinned = tune_value(PSD_TUNE_SFB_BF16_TILE);
+    if (pinned >= 0 && pinned <= 2) return kTiles[pinned];
+    const Bf16Tile* best = &kTiles[0];
+    for (const Bf16Tile& t : kTiles)
+        if (launch_cost(t, N, M, K) < launch_cost(*best, N, M, K)) best = &t;
+    return *best;
+}
+
+// ... and how many ways to split the sum over k, at most `most`
+Bf16Tile choose_bf16_split(int64_t N, int64_t M, int64_t K, int most, int* splits)
+{
+    Bf16Tile best = choose_bf16(N, M, K);
+    *splits = 1;
+    if (tune_value(PSD_TUNE_SFB_BF16_TILE) >= 0) {
+        *splits = most;
+        return best;
     }
-    *tile = tiles_by_id[pick];
-    const int64_t tiles = ((N + tile->tn - 1) / tile->tn) * ((M + tile->tm - 1) / tile->tm);
-    *splits = may_split ? sfb_splits_for(tiles, slots, K) : 1;
+    double cost = launch_cost(best, N, M, K);
+    for (int s = 2; s <= most; ++s)
+        for (const Bf16Tile& t : kTiles)
+            if (split_cost(t, N, M, K, s) < cost) {
+                cost = split_cost(t, N, M, K, s);
+                best = t;
+                *splits = s;
+            }
+    return best;
 }
 }  // namespace
 
+// how many ways psd_sync_fc_sfb may split this layer's sum over k when it is given a workspace (1 = not at all)
 int sfb_bf16_splits(int64_t N, int64_t M, int64_t K)
 {
-    Bf16Tile t;
-    int s;
-    choose_bf16(N, M, K, true, &t, &s);
-    return s;
+    const int pinned = tune_value(PSD_TUNE_SFB_BF16_TILE);
+    const Bf16Tile& t = kTiles[pinned >= 0 && pinned <= 2 ? pinned : 2];
+    return sfb_splits_for(((N + t.tn - 1) / t.tn) * ((M + t.tm - 1) / t.tm), int64_t(device_cu_count()) * 2, K);
 }
 
 psd_status launch_sfb_bf16(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t ldv, float* W, float* Mom,
-                           int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int splits,
+                           int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int most_splits,
                            hipStream_t st)
 {
-    Bf16Tile t;
-    int unused;
-    choose_bf16(N, M, K, false, &t, &unused);
+    int splits;
+    const Bf16Tile t = choose_bf16_split(N, M, K, most_splits, &splits);
     switch (t.id) {
         case 0: return launch_cfg<Cfg128x256w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
         case 1: return launch_cfg<Cfg128x192w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
+        case 3: return launch_cfg<Cfg64x128w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
+        case 4: return launch_cfg<Cfg64x64w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
         default: return launch_cfg<Cfg128x128w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
     }
 }
@@ -508,12 +564,12 @@ psd_status launch_sfb_bf16_blocks(const uint16_t* const* U_p, int64_t ldu, const
         blocks.u[p] = p < P ? U_p[p] : nullptr;
         blocks.v[p] = p < P ? V_p[p] : nullptr;
     }
-    Bf16Tile t;
-    int unused;
-    choose_bf16(N, M, P * B, false, &t, &unused);
+    const Bf16Tile t = choose_bf16(N, M, P * B);
     switch (t.id) {
         case 0: return launch_cfg_blocks<Cfg128x256w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         case 1: return launch_cfg_blocks<Cfg128x192w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
+        case 3: return launch_cfg_blocks<Cfg64x128w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
+        case 4: return launch_cfg_blocks<Cfg64x64w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         default: return launch_cfg_blocks<Cfg128x128w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
     }
 }

@@ -284,9 +284,10 @@ Cover uniform_cover(int64_t N, int64_t M, int bn, int bm)
     return {bn, bm, bn * bm == 4 ? tn * tm : 0, tm, tn * tm};
 }
 
-Cover choose_f32(int64_t N, int64_t M, int64_t K)
+Cover choose_f32(int64_t N, int64_t M, int64_t K, double* units)
 {
     const int forced = tune_value(PSD_TUNE_SFB_F32_TILE);
+    *units = 0;
     if (forced == 1 || forced == 2) return uniform_cover(N, M, forced, 2);
     // A compute unit works through its tiles at the rate of its MFMA pipe, so the launch takes as long as the compute unit
     // with the most tile area: count in units of 128 x 128 tiles per compute unit, smaller tiles with what their shorter
@@ -309,6 +310,7 @@ Cover choose_f32(int64_t N, int64_t M, int64_t K)
             consider({1, 1, full * cus, all.tiles_m, full * cus + 4 * rem}, full + rounds(4 * rem, 0.30));
         }
     }
+    *units = quarter.groups <= cus && best.bm == 1 ? 0.36 : cost;     // a lone 64 x 64 tile per compute unit
     return best;
 }
 
@@ -336,7 +338,8 @@ Args common_args(int64_t ldu, int64_t ldv, float* W, float* Mom, int64_t N, int6
 
 psd_status launch_cover(Args& g, const BlockPtrs* blocks, hipStream_t st)
 {
-    const Cover c = choose_f32(g.N, g.M, g.K);
+    double units;
+    const Cover c = choose_f32(g.N, g.M, g.K, &units);
     if (c.groups > 0x7fffffff) return PSD_E_INVALID;
     g.big = static_cast<int>(c.big);
     g.tiles_m = static_cast<int>(c.tiles_m);
@@ -354,7 +357,7 @@ int sfb_f32_splits(int64_t N, int64_t M, int64_t K)
 }
 
 psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t ldv, float* W, float* Mom,
-                          int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int splits,
+                          int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int most_splits,
                           hipStream_t st)
 {
     // 32-bit byte offsets into each factor matrix, with room for the stages of read-ahead
@@ -364,8 +367,25 @@ psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t l
     Args g = common_args(ldu, ldv, W, Mom, N, M, K, lr, mu, wd);
     g.U = U; g.V = V;
     g.u_bytes = static_cast<uint32_t>(u_bytes); g.v_bytes = static_cast<uint32_t>(v_bytes);
-    if (splits <= 1) return launch_cover(g, nullptr, st);
+    // Split the sum over k where the shorter loops save more than storing and adding the partial sums costs: a unit is 63 us
+    // per 1024 rows, the second launch 4 us and its bytes.  512 -> 512, K = 2048: 47 us unsplit, 19 us in four;
+    // 1024 -> 1000 (a 64 x 64 tile for every compute unit), K = 2048: 51 and 49.5 us, K = 8192: 178 and 154 us.
     const Cover c = uniform_cover(N, M, 1, 1);
+    const int64_t cus = device_cu_count();
+    double units;
+    choose_f32(N, M, K, &units);
+    int splits = 1;
+    double cost = units * 63 * static_cast<double>(K) / 1024;
+    for (int s = 2; s <= most_splits; ++s) {
+        const int64_t groups = c.groups * s;
+        const double loop = groups <= cus ? 0.36 : static_cast<double>((groups + cus - 1) / cus) * 0.30;
+        const double x = loop * 63 * static_cast<double>(K) / s / 1024 + 4 + (16.0 + 4 * s) * N * M / 5e6;
+        if (x < cost || units == 0) {
+            cost = x;
+            splits = s;
+        }
+    }
+    if (splits <= 1) return launch_cover(g, nullptr, st);
     g.tiles_m = static_cast<int>(c.tiles_m);
     g.tiles = static_cast<int>(c.groups);
     g.part = part; g.part_stride = sfb_part_stride(N, M);
