@@ -106,25 +106,33 @@ __device__ __forceinline__ int line_shift(const float* W, int64_t n, int64_t M)
                              static_cast<uint32_t>(reinterpret_cast<uintptr_t>(W) >> 2)) & 31u);
 }
 
-// Row r (of ROWS) of the buffer starts at buf + r * STRIDE and holds dW[row_n(r)][m0 + c] at place c + line_shift, c < WIDTH.
+// Row length of the LDS buffer, in floats: room for the shift, and such that (row length + M) / 4 is odd for M a multiple
+// of 4: the 16-byte writes of rows r, r + 1, ... then fall on different banks (1500 -> 1400: all on the same ones with
+// WIDTH + 36, 8 us of conflicts).
+__host__ __device__ constexpr int row_stride(int width, int64_t M) { return width + 32 + (M % 8 == 0 ? 4 : 0); }
+
+// Row r (of ROWS) of the buffer starts at buf + r * row_stride and holds dW[row_n(r)][m0 + c] at place c + line_shift,
+// c < WIDTH; with PARTS > 1 there are that many buffers one after the other, whose sum is dW.
 // Every wavefront access covers one line of eight rows (8 lanes of 16 bytes each).  W and Mom of DEPTH such line groups
 // are requested by fetch<0>() before the rows are even written, and those of the next DEPTH before the present ones are
 // used.  Lines that lie inside the tile are streamed (see load_stream4), the ones it shares with its neighbours go
-// through the caches.
-template <int ROWS, int WIDTH, int STRIDE, int WAVES, int DEPTH, class RowN>
+// through the caches, but for the stores of the narrow tiles of small layers: what lies dirty in L2 when a kernel ends has
+// to be written back before the next one starts, a microsecond that large layers do not notice.
+template <int ROWS, int WIDTH, int WAVES, int DEPTH, int PARTS, class RowN>
 struct RowUpdate {
-    static constexpr int LINES = WIDTH / 32 + 1, UNITS = ROWS / 8 / WAVES * LINES, BATCHES = (UNITS + DEPTH - 1) / DEPTH;
-    static_assert(ROWS % (8 * WAVES) == 0 && WIDTH % 32 == 0 && STRIDE >= WIDTH + 32 && STRIDE % 4 == 0, "whole line groups per wavefront");
+    static constexpr int LINES = WIDTH / 32 + 1, GROUPS = ROWS / 8, ALL = GROUPS * LINES;       // units: one line of eight rows
+    static constexpr int UNITS = (ALL + WAVES - 1) / WAVES, BATCHES = (UNITS + DEPTH - 1) / DEPTH;
+    static_assert(ROWS % 8 == 0 && WIDTH % 32 == 0, "whole lines of eight rows");
     float* W;
     float* Mom;
     RowN row_n;
     int64_t m0, N, M;
-    int wave, lane, cols;                          // cols: columns of the tile that exist
+    int wave, lane, cols, stride;                  // cols: columns of the tile that exist
     float4 w[2][DEPTH], mo[2][DEPTH];
 
     __device__ __forceinline__ RowUpdate(float* W_, float* Mom_, RowN row, int64_t m0_, int64_t N_, int64_t M_, int wave_, int lane_)
         : W(W_), Mom(Mom_), row_n(row), m0(m0_), N(N_), M(M_), wave(wave_), lane(lane_),
-          cols(static_cast<int>(M_ - m0_ < WIDTH ? M_ - m0_ : WIDTH))
+          cols(static_cast<int>(M_ - m0_ < WIDTH ? M_ - m0_ : WIDTH)), stride(row_stride(WIDTH, M_))
     {
     }
     struct Place {
@@ -134,15 +142,22 @@ struct RowUpdate {
     };
     __device__ __forceinline__ Place place(int u) const
     {
-        const int r = (wave + WAVES * (u / LINES)) * 8 + (lane >> 3), line = u % LINES, q = 4 * (lane & 7);
+        // A wavefront takes the lines of eight rows one after the other, next to wavefronts that do so with the next rows
+        // (line by line across the rows, or with rows further apart, the update is 3-8 % slower); with more wavefronts than
+        // groups of rows, neighbouring wavefronts take neighbouring lines.
+        constexpr bool WALK = GROUPS % WAVES == 0;
+        const int id = wave + WAVES * u;
+        const int line = WALK ? u % LINES : id % LINES, r = (WALK ? wave + WAVES * (u / LINES) : id / LINES) * 8 + (lane >> 3);
+        const int q = 4 * (lane & 7);
         const int64_t n = row_n(r);
         const int first = 32 * line - line_shift(W, n, M);       // column of the line's first element
         Place p;
         p.c = first + q;
-        p.at = r * STRIDE + 32 * line + q;
+        p.at = r * stride + 32 * line + q;
         p.off = n * M + m0 + p.c;
-        p.any = n < N && p.c + 3 >= 0 && p.c < cols;
-        p.quad = n < N && p.c >= 0 && p.c + 3 < cols;
+        const bool mine = n < N && (WALK || id < ALL);
+        p.any = mine && p.c + 3 >= 0 && p.c < cols;
+        p.quad = mine && p.c >= 0 && p.c + 3 < cols;
         p.whole_line = first >= 0 && first + 32 <= cols;
         return p;
     }
@@ -173,14 +188,19 @@ struct RowUpdate {
                 if (B * DEPTH + j >= UNITS) continue;
                 const Place p = place(B * DEPTH + j);
                 if (!p.any) continue;
-                const float4 d = *reinterpret_cast<const float4*>(buf + p.at);
+                float4 d = *reinterpret_cast<const float4*>(buf + p.at);
+#pragma unroll
+                for (int i = 1; i < PARTS; ++i) {
+                    const float4 e = *reinterpret_cast<const float4*>(buf + i * ROWS * stride + p.at);
+                    d.x += e.x; d.y += e.y; d.z += e.z; d.w += e.w;
+                }
                 if (p.quad) {
                     float4 &wv = w[B & 1][j], &mv = mo[B & 1][j];
                     upd(d.x, wv.x, mv.x, lr, mu, wd);
                     upd(d.y, wv.y, mv.y, lr, mu, wd);
                     upd(d.z, wv.z, mv.z, lr, mu, wd);
                     upd(d.w, wv.w, mv.w, lr, mu, wd);
-                    if (p.whole_line) {
+                    if (WIDTH < 128 || p.whole_line) {
                         store_stream4(Mom + p.off, mv);
                         store_stream4(W + p.off, wv);
                     } else {
@@ -194,8 +214,8 @@ struct RowUpdate {
                         if (p.c + i >= 0 && p.c + i < cols) {
                             float wv = W[p.off + i], mv = Mom[p.off + i];
                             upd(dv[i], wv, mv, lr, mu, wd);
-                            Mom[p.off + i] = mv;
-                            W[p.off + i] = wv;
+                            __builtin_nontemporal_store(mv, Mom + p.off + i);
+                            __builtin_nontemporal_store(wv, W + p.off + i);
                         }
                 }
             }

@@ -31,28 +31,31 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
-constexpr int KT = 32;         // k rows per LDS stage (two MFMA k-steps of 16)
+constexpr int SLICE = 32;      // k rows of a stage that one group of wavefronts contracts (two MFMA k-steps of 16)
 constexpr int GROUP_N = 8;     // tile rows per raster group (L2 reuse of the V panels)
 constexpr int PLD = 36;        // epilogue patch row stride in floats (144 B: conflict-free)
 
 // WN x WM wavefronts, each owning BN x BM MFMA blocks of 32 x 32; NSTAGE LDS buffers;
 // OCC = wavefronts per SIMD the register budget is sized for
-template <int WN_, int WM_, int BN_, int BM_, int NSTAGE_, int OCC_>
+// G > 1: that many groups of WN x WM wavefronts own the same tile; a stage holds G slices of k rows, one for each
+// group, and the groups' accumulators are added up in LDS before the update.
+template <int WN_, int WM_, int BN_, int BM_, int NSTAGE_, int OCC_, int G_ = 1>
 struct Cfg {
-    static constexpr int WN = WN_, WM = WM_, BN = BN_, BM = BM_, NSTAGE = NSTAGE_, OCC = OCC_;
-    static constexpr int WAVES = WN * WM, THREADS = 64 * WAVES;
+    static constexpr int WN = WN_, WM = WM_, BN = BN_, BM = BM_, NSTAGE = NSTAGE_, OCC = OCC_, G = G_;
+    static constexpr int WAVES = WN * WM * G, THREADS = 64 * WAVES, KT = SLICE * G;
     static constexpr int TN = 32 * BN * WN, TM = 32 * BM * WM;   // workgroup tile
     static constexpr int RA = TN * 2, RB = TM * 2;               // LDS row bytes (U tile, V tile)
     static constexpr int A_BYTES = KT * RA, B_BYTES = KT * RB, STAGE_BYTES = A_BYTES + B_BYTES;
     static constexpr int NI_A = A_BYTES / 1024 / WAVES;          // 1 KiB DMA instructions per wavefront
     static constexpr int NI_B = B_BYTES / 1024 / WAVES;
     static constexpr int PATCH_BYTES = WAVES * 32 * PLD * 4;
-    static constexpr int STRIDE = TM + 36, ROWS = 32 * WN;       // row buffer of the update (RowUpdate), in floats
+    static constexpr int ROWS = 32 * WN;                         // rows in the buffer of the update (RowUpdate)
     static constexpr size_t larger(size_t a, size_t b) { return a > b ? a : b; }
     static constexpr size_t LDS_BYTES = larger(size_t(NSTAGE) * STAGE_BYTES, PATCH_BYTES);
-    static constexpr size_t LDS_BYTES_ROWS = larger(LDS_BYTES, size_t(ROWS) * STRIDE * 4);
+    static constexpr size_t LDS_BYTES_ROWS = larger(LDS_BYTES, size_t(G) * ROWS * row_stride(TM, 0) * 4);
     static_assert(A_BYTES % (1024 * WAVES) == 0 && B_BYTES % (1024 * WAVES) == 0, "stage must split into 1 KiB runs");
     static_assert(RA % 128 == 0 && RB % 128 == 0, "the swizzle permutes chunks inside 128-byte groups");
+    static_assert(G == 1 || (RA == RB && NI_A * (1024 / RA) * (WAVES / G) == SLICE), "a wavefront's runs lie in one slice");
     static_assert(NSTAGE >= 3, "the pipeline keeps at least one stage in flight beyond the one being awaited");
 };
 
@@ -67,8 +70,8 @@ __device__ __forceinline__ bf16x4 read_tr(uint32_t lds_addr)
 // and stores its partial dW tile to part + s * part_stride (N x M row-major); the partials are summed
 // in split order and the update applied by the parameter-server sum kernel afterwards.
 // BLK = true: the factors are not stacked.  Row k = p*B + b of U is row b of the p-th worker's B x ldu block
-// (V likewise), read where it lies: a stage of KT rows never straddles two blocks because KT divides B, so
-// the only difference is that the buffer descriptors are re-aimed whenever the stages move on to the next
+// (V likewise), read where it lies: a slice never straddles two blocks because SLICE divides B, so
+// the only difference is that the buffer descriptors are re-aimed whenever a wavefront's slices move on to the next
 // block (and aimed at nothing past the last one, which reads as zeros like the K tail does).
 struct BlockPtrs { const uint16_t* u[PSD_MAX_WORKERS]; const uint16_t* v[PSD_MAX_WORKERS]; };
 
@@ -79,9 +82,11 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
               float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
               int tiles_n, int tiles_m, uint32_t u_bytes, uint32_t v_bytes, float* __restrict__ part,
               int64_t part_stride, int stages_per_split, int skew_blocks, int skew_ticks,
-              const BlockPtrs* blocks, int n_blocks, int stages_per_block)
+              const BlockPtrs* blocks, int n_blocks, int block_rows)
 {
-    static_assert(!(PART && BLK), "blocks read in place are not combined with a split of K");
+    static_assert(!(PART && (BLK || C::G > 1)), "a split of K over workgroups is not combined with blocks read in place or groups");
+    static_assert(!(STREAM && C::G > 1), "the groups' sums go through the row buffers");
+    constexpr int KT = C::KT;
     // Measurement aid (off unless asked for): the workgroups that start first on the odd-numbered
     // XCDs wait skew_ticks of the 100 MHz wall clock, which puts the two halves of the chip out of
     // phase (MFMA loop on one, W / Mom update on the other).  The wait ends by the clock; the
@@ -109,7 +114,8 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
     const int64_t n0 = int64_t(tile_n) * C::TN, m0 = int64_t(tile_m) * C::TM;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wn0 = (wave / C::WM) * 32 * C::BN, wm0 = (wave % C::WM) * 32 * C::BM;
+    const int group = wave / (C::WN * C::WM), wg = wave % (C::WN * C::WM);
+    const int wn0 = (wg / C::WM) * 32 * C::BN, wm0 = (wg % C::WM) * 32 * C::BM;
     const int grp = lane >> 4, l16 = lane & 15;
 
     // ---- DMA plan: instruction j of this wavefront moves one 1 KiB run of a stage (a whole number
@@ -125,8 +131,12 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
         v_bytes = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(int64_t(k_end) * ldv * 2));
     }
     i32x4 rsrc_u = raw_rsrc(U, u_bytes), rsrc_v = raw_rsrc(V, v_bytes);
-    int blk = 0, stage_in_blk = 0;               // BLK: where the next stage to be requested lies
-    auto aim_block = [&]() {                     // BLK: descriptors over block `blk` (u_bytes, v_bytes = one block)
+    int blk = 0, row_in_blk = group * SLICE;     // BLK: where this wavefront's next slice lies (its runs are all in slice `group`)
+    auto aim_block = [&]() {                     // BLK: descriptors over the block the slice lies in (u_bytes, v_bytes = one block)
+        while (row_in_blk >= block_rows) {
+            row_in_blk -= block_rows;
+            ++blk;
+        }
         const bool live = blk < n_blocks;
         const int i = live ? blk : 0;            // the table is never indexed past its end
         rsrc_u = raw_rsrc(uniform_ptr(blocks->u[i]), live ? u_bytes : 0u);
@@ -141,7 +151,7 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
             const int f = (wave * C::NI_A + j) * 64 + lane;   // chunk index inside the stage
             const int r = f / LPR;
             const int lc = (f % LPR) ^ ((r & 3) << 1);
-            voff_a[j] = static_cast<uint32_t>(((k_begin + r) * ldu + n0 + lc * 8) * 2);
+            voff_a[j] = static_cast<uint32_t>(((BLK ? r % SLICE : k_begin + r) * ldu + n0 + lc * 8) * 2);
         }
     }
     {
@@ -151,25 +161,22 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
             const int f = (wave * C::NI_B + j) * 64 + lane;
             const int r = f / LPR;
             const int lc = (f % LPR) ^ ((r & 3) << 1);
-            voff_b[j] = static_cast<uint32_t>(((k_begin + r) * ldv + m0 + lc * 8) * 2);
+            voff_b[j] = static_cast<uint32_t>(((BLK ? r % SLICE : k_begin + r) * ldv + m0 + lc * 8) * 2);
         }
     }
-    const uint32_t step_a = static_cast<uint32_t>(KT * ldu * 2), step_b = static_cast<uint32_t>(KT * ldv * 2);
+    const uint32_t row_a = static_cast<uint32_t>(ldu * 2), row_b = static_cast<uint32_t>(ldv * 2);
     auto issue = [&](int t) {                    // stage t -> ring buffer t % NSTAGE (stages are requested in order)
         const uint32_t base = lds0 + static_cast<uint32_t>(t % C::NSTAGE) * C::STAGE_BYTES;
-        const uint32_t s = static_cast<uint32_t>(BLK ? stage_in_blk : t);
+        const uint32_t row = static_cast<uint32_t>(BLK ? row_in_blk : t * KT);
 #pragma unroll
         for (int j = 0; j < C::NI_A; ++j)
-            dma_b128(base + (wave * C::NI_A + j) * 1024, voff_a[j] + s * step_a, rsrc_u);
+            dma_b128(base + (wave * C::NI_A + j) * 1024, voff_a[j] + row * row_a, rsrc_u);
 #pragma unroll
         for (int j = 0; j < C::NI_B; ++j)
-            dma_b128(base + C::A_BYTES + (wave * C::NI_B + j) * 1024, voff_b[j] + s * step_b, rsrc_v);
+            dma_b128(base + C::A_BYTES + (wave * C::NI_B + j) * 1024, voff_b[j] + row * row_b, rsrc_v);
         if constexpr (BLK) {
-            if (++stage_in_blk == stages_per_block) {
-                stage_in_blk = 0;
-                ++blk;
-                aim_block();
-            }
+            row_in_blk += KT;
+            if (row_in_blk >= block_rows) aim_block();
         }
     };
 
@@ -179,7 +186,7 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
     // The byte address of this lane's piece inside a stage buffer, for k-step 0, low half:
     uint32_t rd_a[C::BN], rd_b[C::BM];
     {
-        const int row = 8 * (grp >> 1) + (l16 >> 2);           // row & 3 == l16 >> 2
+        const int row = group * SLICE + 8 * (grp >> 1) + (l16 >> 2);           // row & 3 == l16 >> 2
         const int sw = (l16 >> 2) << 1;
 #pragma unroll
         for (int bn = 0; bn < C::BN; ++bn) {
@@ -340,11 +347,11 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
 #pragma unroll
         for (int bn = 0; bn < C::BN; ++bn) {
             auto row_n = [&](int r) { return n0 + (r >> 5) * 32 * C::BN + 32 * bn + (r & 31); };
-            RowUpdate<C::ROWS, C::TM, C::STRIDE, C::WAVES, C::BM == 4 ? 4 : 5, decltype(row_n)> rows(W, Mom, row_n, m0, N, M, wave, lane);
+            RowUpdate<C::ROWS, C::TM, C::WAVES, C::BM == 4 ? 4 : C::BM == 1 ? 6 : 5, C::G, decltype(row_n)> rows(W, Mom, row_n, m0, N, M, wave, lane);
             rows.template fetch<0>();
             if (bn > 0) __syncthreads();           // the rows before are no longer read
-            const int r = (wave / C::WM) * 32 + l32;
-            float* to = buf + r * C::STRIDE + wm0 + 4 * lhi + line_shift(W, row_n(r), M);
+            const int r = (wg / C::WM) * 32 + l32;
+            float* to = buf + (group * C::ROWS + r) * rows.stride + wm0 + 4 * lhi + line_shift(W, row_n(r), M);
 #pragma unroll
             for (int bm = 0; bm < C::BM; ++bm)
 #pragma unroll
@@ -377,12 +384,12 @@ sfb_bf16_kernel(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __r
 // the P per-worker blocks read in place (u_bytes, v_bytes: the size of ONE block)
 template <class C, bool STREAM>
 __global__ void __launch_bounds__(C::THREADS, C::OCC)
-sfb_bf16_blocks_kernel(BlockPtrs blocks, int n_blocks, int stages_per_block, int64_t ldu, int64_t ldv,
+sfb_bf16_blocks_kernel(BlockPtrs blocks, int n_blocks, int block_rows, int64_t ldu, int64_t ldv,
                        float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
                        int tiles_n, int tiles_m, uint32_t u_bytes, uint32_t v_bytes)
 {
     sfb_bf16_body<C, false, true, STREAM>(nullptr, ldu, nullptr, ldv, W, Mom, N, M, K, lr, mu, wd, tiles_n, tiles_m, u_bytes,
-                                  v_bytes, nullptr, 0, 0, 0, 0, &blocks, n_blocks, stages_per_block);
+                                  v_bytes, nullptr, 0, 0, 0, 0, &blocks, n_blocks, block_rows);
 }
 
 // do all rows of W and Mom start on cache-line boundaries (128 bytes)?
@@ -400,19 +407,20 @@ psd_status launch_cfg_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int6
     if (tiles < 1 || tiles > 0x3fffffff) return PSD_E_INVALID;
     const int64_t u_bytes = B * ldu * 2, v_bytes = B * ldv * 2;          // one block
     if (u_bytes >= (int64_t(1) << 32) || v_bytes >= (int64_t(1) << 32)) return PSD_E_UNSUPPORTED;
-    const bool lines = rows_on_lines(W, Mom, M);
-    auto kern = lines ? sfb_bf16_blocks_kernel<C, true> : sfb_bf16_blocks_kernel<C, false>;
+    const bool lines = C::G == 1 && rows_on_lines(W, Mom, M);
+    constexpr bool can_stream = C::G == 1;
+    auto kern = lines ? sfb_bf16_blocks_kernel<C, can_stream> : sfb_bf16_blocks_kernel<C, false>;
     const size_t lds = lines ? C::LDS_BYTES : C::LDS_BYTES_ROWS;
     static std::atomic<bool> attr_done{false};
     if (!attr_done.load(std::memory_order_acquire)) {
-        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_blocks_kernel<C, true>),
+        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_blocks_kernel<C, can_stream>),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_blocks_kernel<C, false>),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         attr_done.store(true, std::memory_order_release);
     }
     hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(tiles)), dim3(C::THREADS), lds, st,
-                       blocks, static_cast<int>(P), static_cast<int>(B / KT), ldu, ldv, W, Mom, static_cast<int>(N),
+                       blocks, static_cast<int>(P), static_cast<int>(B), ldu, ldv, W, Mom, static_cast<int>(N),
                        static_cast<int>(M), static_cast<int>(P * B), lr, mu, wd, static_cast<int>(tiles_n),
                        static_cast<int>(tiles_m), static_cast<uint32_t>(u_bytes), static_cast<uint32_t>(v_bytes));
     PSD_HIP_TRY(hipGetLastError());
@@ -429,26 +437,27 @@ psd_status launch_cfg(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t
     if (tiles < 1 || tiles * splits > 0x3fffffff) return PSD_E_INVALID;
     // 32-bit byte offsets into each factor matrix, with room for the stages of read-ahead
     const int64_t u_bytes = K * ldu * 2, v_bytes = K * ldv * 2;
-    const int64_t reach = (int64_t(1) << 32) - (C::NSTAGE + 2) * KT * (ldu > ldv ? ldu : ldv) * 2 - 4096;
+    const int64_t reach = (int64_t(1) << 32) - (C::NSTAGE + 2) * C::KT * (ldu > ldv ? ldu : ldv) * 2 - 4096;
     if (u_bytes > reach || v_bytes > reach) return PSD_E_UNSUPPORTED;
-    const bool lines = rows_on_lines(W, Mom, M);
-    auto kern = splits > 1 ? sfb_bf16_kernel<C, true, false>
-                           : (lines ? sfb_bf16_kernel<C, false, true> : sfb_bf16_kernel<C, false, false>);
+    const bool lines = C::G == 1 && rows_on_lines(W, Mom, M);
+    constexpr bool alone = C::G == 1;            // groups come neither split nor streamed
+    auto kern = splits > 1 ? sfb_bf16_kernel<C, alone, false>
+                           : (lines ? sfb_bf16_kernel<C, false, alone> : sfb_bf16_kernel<C, false, false>);
     const size_t lds = splits > 1 || lines ? C::LDS_BYTES : C::LDS_BYTES_ROWS;
     // raise the dynamic LDS limit once per process (idempotent, so a race between two first
     // callers is harmless; the flag only saves the call on later launches)
     static std::atomic<bool> attr_done{false};
     if (!attr_done.load(std::memory_order_acquire)) {
-        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_kernel<C, true, false>),
+        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_kernel<C, alone, false>),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
-        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_kernel<C, false, true>),
+        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_kernel<C, false, alone>),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_kernel<C, false, false>),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         attr_done.store(true, std::memory_order_release);
     }
     const int skew = tune_value(PSD_TUNE_SFB_BF16_SKEW_US);
-    const int64_t stages = (K + KT - 1) / KT;
+    const int64_t stages = (K + C::KT - 1) / C::KT;
     const int sps = static_cast<int>((stages + splits - 1) / splits);
     hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(tiles * splits)), dim3(C::THREADS), lds, st, U, ldu, V,
                        ldv, W, Mom, static_cast<int>(N), static_cast<int>(M), static_cast<int>(K), lr, mu, wd,
@@ -465,36 +474,43 @@ using Cfg128x192w4 = Cfg<2, 2, 2, 3, 4, 2>;   // 4 wavefronts of 64 x 96, 4 stag
 using Cfg128x128w4 = Cfg<2, 2, 2, 2, 4, 2>;   // 64 KiB, two per CU
 using Cfg64x128w4 = Cfg<2, 2, 1, 2, 4, 3>;    // 48 KiB, three per CU
 using Cfg64x64w4 = Cfg<2, 2, 1, 1, 4, 4>;     // 32 KiB, five per CU: small layers
+using Cfg64x64w16 = Cfg<2, 2, 1, 1, 4, 4, 4>; // four groups, 128 KiB, one per CU
+using Cfg128x128w8 = Cfg<2, 2, 2, 2, 4, 2, 2>; // two groups, 128 KiB, one per CU
 
 }  // namespace
 
 namespace {
-// What one tile costs a compute unit, in us: `area` times the update of 64 x 64 weights of W and Mom at the compute unit's
-// share of HBM (3.1 us) plus `loop` per 1024 k rows; alone on its compute unit, `first` plus `solo` per 1024 k rows.
-// Fitted to 9216 -> 4096 and 1024 -> 1000 over K = 256 .. 2048; predicts the other shapes tried within 10 %.
-struct Bf16Tile { int id, tn, tm; double area, loop, first, solo; };
-const Bf16Tile kTiles[] = {{0, 128, 256, 8, 9.9, 16.6, 15.1}, {1, 128, 192, 6, 6.6, 14.0, 8.3}, {2, 128, 128, 4, 5.7, 10.5, 7.1},
-                           {3, 64, 128, 2, 3.8, 7.0, 6.6}, {4, 64, 64, 1, 2.5, 4.7, 6.5}};
+// What a tile costs, in us: `area` times the update of 64 x 64 weights at a compute unit's share of HBM (3.1 us) and `loop`
+// per 1024 k rows where compute units hold several tiles; `first` and `solo` per 1024 k rows where each holds one at most.
+// Fitted to 9216 -> 4096, 4096 -> 1000 and 1024 -> 1000 over K = 32 .. 2048; predicts the other shapes tried (W of 1 to 90 M
+// weights) within 10 %.  The tiles contracted by several groups of wavefronts fill a compute unit, so they are for layers
+// that have one tile for each at most: 1024 -> 1000, K = 2048 17.4 us with four wavefronts per 64 x 64 tile, 12.5 with sixteen.
+struct Bf16Tile { int id, tn, tm; bool alone; double area, loop, first, solo; };
+const Bf16Tile kTiles[] = {{0, 128, 256, false, 8, 9.9, 14.7, 15.1}, {1, 128, 192, false, 6, 6.6, 11.9, 8.3},
+                           {2, 128, 128, false, 4, 5.7, 8.6, 7.1},   {3, 64, 128, false, 2, 3.8, 5.1, 6.6},
+                           {4, 64, 64, false, 1, 2.5, 3.9, 6.0},     {5, 64, 64, true, 1, 0, 3.75, 3.4},
+                           {6, 128, 128, true, 4, 0, 8.3, 5.9}};
+const double kNever = 1e30;
 
-// us for the launch that covers N x M over K rows.  Layers whose rows of W do not start on cache lines touch one more
-// line per row of a tile.
+// us for the launch that covers N x M over K rows
 double launch_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K)
 {
     const int64_t cus = device_cu_count(), tiles = ((N + t.tn - 1) / t.tn) * ((M + t.tm - 1) / t.tm);
-    const double k = static_cast<double>(K) / 1024, lines = t.tm / 32;
-    const double update = 3.1 * t.area * (M % 32 ? (lines + 1) / lines : 1);
-    if (tiles > cus) return 5 + static_cast<double>((tiles + cus - 1) / cus) * (update + t.loop * k);
-    const double solo = t.first + t.solo * k, shared = 5 + update * static_cast<double>(tiles) / cus + t.loop * k;
-    return solo > shared ? solo : shared;
+    const double k = static_cast<double>(K) / 1024, share = static_cast<double>(tiles) / cus, update = 3.1 * t.area;
+    if (tiles <= cus) return t.first + (M % 32 ? 1.5 : 0) + 0.6 * update * share + t.solo * k;
+    // the last, partly filled round: the loop takes as long as a full one, the update shares HBM among fewer
+    const double rounds = static_cast<double>((tiles + cus - 1) / cus), tail = (rounds - share) * (t.area > 2 ? 0.5 : 0.2);
+    return t.alone ? kNever : 5 + update * (share + tail) + t.loop * k * rounds;
 }
 
 // ... and when `splits` workgroups per tile store partial sums that a second launch adds up
 double split_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K, int splits)
 {
     const int64_t cus = device_cu_count(), groups = ((N + t.tn - 1) / t.tn) * ((M + t.tm - 1) / t.tm) * splits;
+    if (t.alone) return kNever;
     const double k = static_cast<double>(K) / splits / 1024, sum = 4 + (16.0 + 4 * splits) * N * M / 5e6;
     if (groups > cus) return sum + 5 + static_cast<double>((groups + cus - 1) / cus) * (0.8 * t.area + t.loop * k);
-    return sum + t.first + t.solo * k;
+    return sum + t.first + t.solo * k;              // (the partial sums stay in the caches)
 }
 
 // tile choice for one layer
@@ -542,17 +558,21 @@ psd_status launch_sfb_bf16(const uint16_t* U, int64_t ldu, const uint16_t* V, in
                            hipStream_t st)
 {
     int splits;
-    const Bf16Tile t = choose_bf16_split(N, M, K, most_splits, &splits);
+    Bf16Tile t = choose_bf16_split(N, M, K, most_splits, &splits);
+    // the longer stages of the grouped tiles read further ahead than the 32-bit offsets reach in a very large factor matrix
+    if (t.alone && K * (ldu > ldv ? ldu : ldv) > (int64_t(1) << 29)) t = kTiles[t.id == 5 ? 4 : 2];
     switch (t.id) {
         case 0: return launch_cfg<Cfg128x256w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
         case 1: return launch_cfg<Cfg128x192w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
         case 3: return launch_cfg<Cfg64x128w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
+        case 5: return launch_cfg<Cfg64x64w16>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, 1, st);
+        case 6: return launch_cfg<Cfg128x128w8>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, 1, st);
         case 4: return launch_cfg<Cfg64x64w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
         default: return launch_cfg<Cfg128x128w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
     }
 }
 
-bool sfb_bf16_blocks_supported(int64_t B) { return B % KT == 0; }
+bool sfb_bf16_blocks_supported(int64_t B) { return B % SLICE == 0; }
 
 psd_status launch_sfb_bf16_blocks(const uint16_t* const* U_p, int64_t ldu, const uint16_t* const* V_p, int64_t ldv,
                                   int64_t P, int64_t B, float* W, float* Mom, int64_t N, int64_t M, float lr, float mu,
@@ -569,6 +589,8 @@ psd_status launch_sfb_bf16_blocks(const uint16_t* const* U_p, int64_t ldu, const
         case 0: return launch_cfg_blocks<Cfg128x256w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         case 1: return launch_cfg_blocks<Cfg128x192w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         case 3: return launch_cfg_blocks<Cfg64x128w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
+        case 5: return launch_cfg_blocks<Cfg64x64w16>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
+        case 6: return launch_cfg_blocks<Cfg128x128w8>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         case 4: return launch_cfg_blocks<Cfg64x64w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         default: return launch_cfg_blocks<Cfg128x128w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
     }

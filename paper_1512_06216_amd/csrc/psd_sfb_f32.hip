@@ -41,8 +41,8 @@ struct Tile {                       // workgroup tile (64*BN) x (64*BM): 2 x 2 w
     static constexpr int RA = TN * 4, RB = TM * 4;                                // LDS row bytes
     static constexpr int A_BYTES = KT * RA, B_BYTES = KT * RB, STAGE_BYTES = A_BYTES + B_BYTES;
     static constexpr int NI_A = A_BYTES / 1024 / 4, NI_B = B_BYTES / 1024 / 4;    // 1 KiB DMA runs per wavefront
-    static constexpr int STRIDE = TM + 36;                                        // row buffer of the update, in floats
-    static constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES > 64 * STRIDE * 4 ? NSTAGE * STAGE_BYTES : 64 * STRIDE * 4;
+    static constexpr int ROW_BYTES = 64 * row_stride(TM, 0) * 4;                  // row buffer of the update
+    static constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES > ROW_BYTES ? NSTAGE * STAGE_BYTES : ROW_BYTES;
 };
 
 // Row k = p*B + b of U is row b of the p-th worker's B x ldu block (V likewise): the factors read where they were received.
@@ -221,13 +221,13 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
 #pragma unroll
         for (int ta = 0; ta < BN; ++ta) {
             auto row_n = [&](int r) { return n0 + (r >> 5) * 32 * BN + BN * (r & 31) + ta; };
-            RowUpdate<64, T::TM, T::STRIDE, 4, BM == 2 ? 5 : 3, decltype(row_n)> rows(g.W, g.Mom, row_n, m0, N, M, wave, lane);
+            RowUpdate<64, T::TM, 4, BM == 2 ? 5 : 6, 1, decltype(row_n)> rows(g.W, g.Mom, row_n, m0, N, M, wave, lane);
             rows.template fetch<0>();
             __syncthreads();                          // the ring, or the rows before, are no longer read
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int row = 8 * (r >> 2) + 4 * lhi + (r & 3);
-                float* to = buf + ((wave >> 1) * 32 + row) * T::STRIDE + wm0 + BM * l32 + line_shift(g.W, nw + BN * row + ta, M);
+                float* to = buf + ((wave >> 1) * 32 + row) * rows.stride + wm0 + BM * l32 + line_shift(g.W, nw + BN * row + ta, M);
                 if (BM == 2 && M % 2 == 0) {
                     *reinterpret_cast<float2*>(to) = make_float2(acc[ta][0][r], acc[ta][BM - 1][r]);
                 } else {
