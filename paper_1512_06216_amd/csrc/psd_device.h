@@ -168,7 +168,9 @@ struct RowUpdate {
         for (int j = 0; j < DEPTH; ++j) {
             if (B * DEPTH + j >= UNITS) continue;
             const Place p = place(B * DEPTH + j);
-            if (!p.quad) continue;
+            // A quad that the tile shares with a neighbour (M not a multiple of 4) is loaded whole like any other, the neighbour's
+            // elements for nothing; an aligned 16-byte piece with an element of W in it lies in one page with that element.
+            if (!p.any) continue;
             if (p.whole_line) {
                 w[B & 1][j] = load_stream4(W + p.off);
                 mo[B & 1][j] = load_stream4(Mom + p.off);
@@ -194,12 +196,12 @@ struct RowUpdate {
                     const float4 e = *reinterpret_cast<const float4*>(buf + i * ROWS * stride + p.at);
                     d.x += e.x; d.y += e.y; d.z += e.z; d.w += e.w;
                 }
+                float4 &wv = w[B & 1][j], &mv = mo[B & 1][j];
+                upd(d.x, wv.x, mv.x, lr, mu, wd);
+                upd(d.y, wv.y, mv.y, lr, mu, wd);
+                upd(d.z, wv.z, mv.z, lr, mu, wd);
+                upd(d.w, wv.w, mv.w, lr, mu, wd);
                 if (p.quad) {
-                    float4 &wv = w[B & 1][j], &mv = mo[B & 1][j];
-                    upd(d.x, wv.x, mv.x, lr, mu, wd);
-                    upd(d.y, wv.y, mv.y, lr, mu, wd);
-                    upd(d.z, wv.z, mv.z, lr, mu, wd);
-                    upd(d.w, wv.w, mv.w, lr, mu, wd);
                     if (WIDTH < 128 || p.whole_line) {
                         store_stream4(Mom + p.off, mv);
                         store_stream4(W + p.off, wv);
@@ -207,15 +209,13 @@ struct RowUpdate {
                         *reinterpret_cast<float4*>(Mom + p.off) = mv;
                         *reinterpret_cast<float4*>(W + p.off) = wv;
                     }
-                } else {                           // a quad that the tile shares with a neighbour (M not a multiple of 4)
-                    const float dv[4] = {d.x, d.y, d.z, d.w};
+                } else {                           // only the tile's own elements are stored
+                    const float we[4] = {wv.x, wv.y, wv.z, wv.w}, me[4] = {mv.x, mv.y, mv.z, mv.w};
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
                         if (p.c + i >= 0 && p.c + i < cols) {
-                            float wv = W[p.off + i], mv = Mom[p.off + i];
-                            upd(dv[i], wv, mv, lr, mu, wd);
-                            __builtin_nontemporal_store(mv, Mom + p.off + i);
-                            __builtin_nontemporal_store(wv, W + p.off + i);
+                            Mom[p.off + i] = me[i];
+                            W[p.off + i] = we[i];
                         }
                 }
             }

@@ -21,6 +21,7 @@
 // and interleaved with its first MFMAs (two reads after each: they are back before the half ends, where the barrier
 // would wait for them; spread over the whole half they cost 3 % on every shape), and the workgroup barrier sits between
 // the two halves.
+#include <atomic>
 #include "psd_device.h"
 #include "psd_internal.h"
 
@@ -31,17 +32,19 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int KT = 16;              // k rows per LDS stage
-constexpr int THREADS = 256;
+constexpr int SLICE = 16;           // k rows of a stage that one group of four wavefronts contracts
 constexpr int NSTAGE = 4;           // ring depth
 
-template <int BN, int BM>
-struct Tile {                       // workgroup tile (64*BN) x (64*BM): 2 x 2 wavefronts of BN x BM MFMA blocks
+// Workgroup tile (64*BN) x (64*BM): 2 x 2 wavefronts of BN x BM MFMA blocks.  G > 1: that many groups of four wavefronts own
+// the same tile; a stage holds G slices of k rows, one for each group, and their accumulators are added up in LDS.
+template <int BN, int BM, int G>
+struct Tile {
+    static constexpr int WAVES = 4 * G, THREADS = 64 * WAVES, KT = SLICE * G;
     static constexpr int TN = 64 * BN, TM = 64 * BM;
     static constexpr int RA = TN * 4, RB = TM * 4;                                // LDS row bytes
     static constexpr int A_BYTES = KT * RA, B_BYTES = KT * RB, STAGE_BYTES = A_BYTES + B_BYTES;
-    static constexpr int NI_A = A_BYTES / 1024 / 4, NI_B = B_BYTES / 1024 / 4;    // 1 KiB DMA runs per wavefront
-    static constexpr int ROW_BYTES = 64 * row_stride(TM, 0) * 4;                  // row buffer of the update
+    static constexpr int NI_A = A_BYTES / 1024 / WAVES, NI_B = B_BYTES / 1024 / WAVES;   // 1 KiB DMA runs per wavefront
+    static constexpr int ROW_BYTES = G * 64 * row_stride(TM, 0) * 4;              // row buffer of the update
     static constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES > ROW_BYTES ? NSTAGE * STAGE_BYTES : ROW_BYTES;
 };
 
@@ -60,21 +63,23 @@ struct Args {
     float* part;                    // PART: partial dW matrices, part_stride apart
     int64_t part_stride;
     int stages_per_split;
-    int n_blocks, stages_per_block; // BLK
+    int n_blocks, block_rows;       // BLK
 };
 
 // PART = true (layers with too few tiles to fill the chip): `splits` workgroups per tile, workgroup
 // (tile, s) contracts over k-stages [s * stages_per_split, (s+1) * stages_per_split) and stores its
 // partial dW tile to part + s * part_stride (N x M row-major); the partials are summed in split order
 // and the update applied by the parameter-server sum kernel afterwards.
-// BLK = true: the factors are not stacked.  A stage of KT rows never straddles two blocks because KT divides
-// B, so the only difference is that the buffer descriptor is re-aimed whenever the stages move on to the
+// BLK = true: the factors are not stacked.  A slice never straddles two blocks because SLICE divides
+// B, so the only difference is that the buffer descriptor is re-aimed whenever a wavefront's slices move on to the
 // next block (and aimed at nothing past the last one, which reads as zeros like the K tail does).
-template <int BN, int BM, bool PART, bool BLK>
+template <int BN, int BM, int G, bool PART, bool BLK>
 __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks, char* lds, int64_t n0, int64_t m0, int split)
 {
     static_assert(!(PART && BLK), "blocks read in place are not combined with a split of K");
-    using T = Tile<BN, BM>;
+    static_assert(!(PART && G > 1), "a split of K over workgroups is not combined with groups");
+    using T = Tile<BN, BM, G>;
+    constexpr int KT = T::KT;
     constexpr int LPS = T::NI_A + T::NI_B;
     const int N = g.N, M = g.M;
     const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
@@ -90,13 +95,18 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
     }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wn0 = (wave >> 1) * 32 * BN, wm0 = (wave & 1) * 32 * BM;     // wavefront sub-tile origin
+    const int group = wave >> 2;
+    const int wn0 = ((wave >> 1) & 1) * 32 * BN, wm0 = (wave & 1) * 32 * BM;     // wavefront sub-tile origin
     const int l32 = lane & 31, lhi = lane >> 5;
 
     // DMA plan: run j of this wavefront covers chunks f = (wave*NI + j)*64 + lane of the stage
     i32x4 rsrc_u = raw_rsrc(g.U, u_bytes), rsrc_v = raw_rsrc(g.V, v_bytes);
-    int blk = 0, stage_in_blk = 0;               // BLK: where the next stage to be requested lies
-    auto aim_block = [&]() {                     // BLK: descriptors over block `blk` (u_bytes, v_bytes = one block)
+    int blk = 0, row_in_blk = group * SLICE;     // BLK: where this wavefront's next slice lies (its runs are all in slice `group`)
+    auto aim_block = [&]() {                     // BLK: descriptors over the block the slice lies in (u_bytes, v_bytes = one block)
+        while (row_in_blk >= g.block_rows) {
+            row_in_blk -= g.block_rows;
+            ++blk;
+        }
         const bool live = blk < g.n_blocks;
         const int i = live ? blk : 0;            // the table is never indexed past its end
         rsrc_u = raw_rsrc(uniform_ptr(blocks->u[i]), live ? u_bytes : 0u);
@@ -107,29 +117,28 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
 #pragma unroll
     for (int j = 0; j < T::NI_A; ++j) {
         const int f = (wave * T::NI_A + j) * 64 + lane;
-        voff_a[j] = static_cast<uint32_t>(((k_begin + f / (T::TN / 4)) * g.ldu + n0 + (f % (T::TN / 4)) * 4) * 4);
+        const int r = f / (T::TN / 4);
+        voff_a[j] = static_cast<uint32_t>(((BLK ? r % SLICE : k_begin + r) * g.ldu + n0 + (f % (T::TN / 4)) * 4) * 4);
     }
 #pragma unroll
     for (int j = 0; j < T::NI_B; ++j) {
         const int f = (wave * T::NI_B + j) * 64 + lane;
-        voff_b[j] = static_cast<uint32_t>(((k_begin + f / (T::TM / 4)) * g.ldv + m0 + (f % (T::TM / 4)) * 4) * 4);
+        const int r = f / (T::TM / 4);
+        voff_b[j] = static_cast<uint32_t>(((BLK ? r % SLICE : k_begin + r) * g.ldv + m0 + (f % (T::TM / 4)) * 4) * 4);
     }
-    const uint32_t step_a = static_cast<uint32_t>(KT * g.ldu * 4), step_b = static_cast<uint32_t>(KT * g.ldv * 4);
-    auto issue = [&](int t) {                    // stage t -> ring buffer t % NSTAGE; past K: zeros
+    const uint32_t row_a = static_cast<uint32_t>(g.ldu * 4), row_b = static_cast<uint32_t>(g.ldv * 4);
+    auto issue = [&](int t) {                    // stage t -> ring buffer t % NSTAGE (stages are requested in order); past K: zeros
         const uint32_t base = lds0 + static_cast<uint32_t>(t % NSTAGE) * T::STAGE_BYTES;
-        const uint32_t s = static_cast<uint32_t>(BLK ? stage_in_blk : t);     // stages are requested in order
+        const uint32_t row = static_cast<uint32_t>(BLK ? row_in_blk : t * KT);
 #pragma unroll
         for (int j = 0; j < T::NI_A; ++j)
-            dma_b128(base + (wave * T::NI_A + j) * 1024, voff_a[j] + s * step_a, rsrc_u);
+            dma_b128(base + (wave * T::NI_A + j) * 1024, voff_a[j] + row * row_a, rsrc_u);
 #pragma unroll
         for (int j = 0; j < T::NI_B; ++j)
-            dma_b128(base + T::A_BYTES + (wave * T::NI_B + j) * 1024, voff_b[j] + s * step_b, rsrc_v);
+            dma_b128(base + T::A_BYTES + (wave * T::NI_B + j) * 1024, voff_b[j] + row * row_b, rsrc_v);
         if constexpr (BLK) {
-            if (++stage_in_blk == g.stages_per_block) {
-                stage_in_blk = 0;
-                ++blk;
-                aim_block();
-            }
+            row_in_blk += KT;
+            if (row_in_blk >= g.block_rows) aim_block();
         }
     };
 
@@ -143,8 +152,8 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
 
     // One half-stage = 4 MFMA k-pairs.  Lanes 0..31 feed k = 2*kk, lanes 32..63 feed k = 2*kk + 1.
     struct Half { f32x2 a[4]; f32x2 b[4]; };
-    const uint32_t rd_a = static_cast<uint32_t>(lhi * T::RA + (wn0 + BN * l32) * 4);
-    const uint32_t rd_b = static_cast<uint32_t>(T::A_BYTES + lhi * T::RB + (wm0 + BM * l32) * 4);
+    const uint32_t rd_a = static_cast<uint32_t>((group * SLICE + lhi) * T::RA + (wn0 + BN * l32) * 4);
+    const uint32_t rd_b = static_cast<uint32_t>(T::A_BYTES + (group * SLICE + lhi) * T::RB + (wm0 + BM * l32) * 4);
     auto load_half = [&](int t, int h, Half& f) {
         const uint32_t base = lds0 + static_cast<uint32_t>(t % NSTAGE) * T::STAGE_BYTES;
 #pragma unroll
@@ -221,13 +230,13 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
 #pragma unroll
         for (int ta = 0; ta < BN; ++ta) {
             auto row_n = [&](int r) { return n0 + (r >> 5) * 32 * BN + BN * (r & 31) + ta; };
-            RowUpdate<64, T::TM, 4, BM == 2 ? 5 : 6, 1, decltype(row_n)> rows(g.W, g.Mom, row_n, m0, N, M, wave, lane);
+            RowUpdate<64, T::TM, T::WAVES, BM == 2 ? 5 : 6, G, decltype(row_n)> rows(g.W, g.Mom, row_n, m0, N, M, wave, lane);
             rows.template fetch<0>();
             __syncthreads();                          // the ring, or the rows before, are no longer read
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int row = 8 * (r >> 2) + 4 * lhi + (r & 3);
-                float* to = buf + ((wave >> 1) * 32 + row) * rows.stride + wm0 + BM * l32 + line_shift(g.W, nw + BN * row + ta, M);
+                float* to = buf + (group * 64 + ((wave >> 1) & 1) * 32 + row) * rows.stride + wm0 + BM * l32 + line_shift(g.W, nw + BN * row + ta, M);
                 if (BM == 2 && M % 2 == 0) {
                     *reinterpret_cast<float2*>(to) = make_float2(acc[ta][0][r], acc[ta][BM - 1][r]);
                 } else {
@@ -250,33 +259,47 @@ __device__ __forceinline__ void grid_body(const Args& g, const BlockPtrs* blocks
     const int b = blockIdx.x;
     if constexpr (PART) {
         const int split = __builtin_amdgcn_readfirstlane(b / g.tiles), tile = b - split * g.tiles;   // (the division runs on the vector ALU)
-        tile_body<BN, BM, true, false>(g, nullptr, lds, int64_t(tile / g.tiles_m) * 64 * BN, int64_t(tile % g.tiles_m) * 64 * BM, split);
+        tile_body<BN, BM, 1, true, false>(g, nullptr, lds, int64_t(tile / g.tiles_m) * 64 * BN, int64_t(tile % g.tiles_m) * 64 * BM, split);
     } else if (b < g.big) {
-        tile_body<2, 2, false, BLK>(g, blocks, lds, int64_t(b / g.tiles_m) * 128, int64_t(b % g.tiles_m) * 128, 0);
+        tile_body<2, 2, 1, false, BLK>(g, blocks, lds, int64_t(b / g.tiles_m) * 128, int64_t(b % g.tiles_m) * 128, 0);
     } else if (g.big == 0) {
-        tile_body<BN, BM, false, BLK>(g, blocks, lds, int64_t(b / g.tiles_m) * 64 * BN, int64_t(b % g.tiles_m) * 64 * BM, 0);
+        tile_body<BN, BM, 1, false, BLK>(g, blocks, lds, int64_t(b / g.tiles_m) * 64 * BN, int64_t(b % g.tiles_m) * 64 * BM, 0);
     } else {
         constexpr int PN = 2 / BN, PM = 2 / BM;
         const int i = b - g.big, tile = g.big + i / (PN * PM), sub = i % (PN * PM);
-        tile_body<BN, BM, false, BLK>(g, blocks, lds, int64_t(tile / g.tiles_m) * 128 + (sub / PM) * 64 * BN,
+        tile_body<BN, BM, 1, false, BLK>(g, blocks, lds, int64_t(tile / g.tiles_m) * 128 + (sub / PM) * 64 * BN,
                                       int64_t(tile % g.tiles_m) * 128 + (sub % PM) * 64 * BM, 0);
     }
 }
 
 template <int BN, int BM, bool PART>
-__global__ void __launch_bounds__(THREADS) sfb_f32_kernel(const Args g)
+__global__ void __launch_bounds__(256) sfb_f32_kernel(const Args g)
 {
     grid_body<BN, BM, PART, false>(g, nullptr);
 }
 
 template <int BN, int BM>
-__global__ void __launch_bounds__(THREADS) sfb_f32_blocks_kernel(const Args g, const BlockPtrs blocks)
+__global__ void __launch_bounds__(256) sfb_f32_blocks_kernel(const Args g, const BlockPtrs blocks)
 {
     grid_body<BN, BM, false, true>(g, &blocks);
 }
 
-// How one layer is covered: `big` tiles of 128 x 128 and then tiles of (64*bn) x (64*bm).
-struct Cover { int bn, bm; int64_t big, tiles_m, groups; };
+template <int BN, int BM, int G>
+__global__ void __launch_bounds__(256 * G) sfb_f32_groups_kernel(const Args g)
+{
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    tile_body<BN, BM, G, false, false>(g, nullptr, lds, int64_t(blockIdx.x / g.tiles_m) * 64 * BN, int64_t(blockIdx.x % g.tiles_m) * 64 * BM, 0);
+}
+
+template <int BN, int BM, int G>
+__global__ void __launch_bounds__(256 * G) sfb_f32_groups_blocks_kernel(const Args g, const BlockPtrs blocks)
+{
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    tile_body<BN, BM, G, false, true>(g, &blocks, lds, int64_t(blockIdx.x / g.tiles_m) * 64 * BN, int64_t(blockIdx.x % g.tiles_m) * 64 * BM, 0);
+}
+
+// How one layer is covered: `big` tiles of 128 x 128 and then tiles of (64*bn) x (64*bm), each contracted by `g` groups.
+struct Cover { int bn, bm; int64_t big, tiles_m, groups; int g = 1; };
 
 Cover uniform_cover(int64_t N, int64_t M, int bn, int bm)
 {
@@ -300,17 +323,24 @@ Cover choose_f32(int64_t N, int64_t M, int64_t K, double* units)
     double cost = rounds(half.groups, 0.53);
     auto consider = [&](const Cover& c, double x) { if (x < cost) { cost = x; best = c; } };
     consider(quarter, rounds(quarter.groups, 0.30));
+    // At most one 64 x 64 tile per compute unit: four groups of wavefronts contract it (1024 -> 1000: K = 2048 53 -> 45 us,
+    // K = 256 11.4 -> 11.0; two groups on a lone 128 x 128 tile are no faster than two 64 x 128 tiles).
+    if (quarter.groups <= cus) {
+        Cover c = quarter;
+        c.g = 4;
+        *units = 0.30;
+        return c;
+    }
     // A short contraction is mostly W / Mom update, which three 64 x 128 tiles on a compute unit overlap better than two
     // 128 x 128 ones (9216 -> 4096: K = 64 122 against 144 us, K = 256 201 / 225, K = 512 348 / 340).
-    if (K >= 448) {
-        const int64_t full = all.big / cus, rem = all.big % cus;
-        consider(all, rounds(all.big, 1.0) * (all.big <= cus ? 1.07 : 1.0));
-        if (full > 0 && rem > 0) {
-            consider({1, 2, full * cus, all.tiles_m, full * cus + 2 * rem}, full + rounds(2 * rem, 0.53));
-            consider({1, 1, full * cus, all.tiles_m, full * cus + 4 * rem}, full + rounds(4 * rem, 0.30));
-        }
+    const double big = K >= 512 ? 1.0 : 1.0 + 0.25 * static_cast<double>(512 - K) / 448;
+    const int64_t full = all.big / cus, rem = all.big % cus;
+    consider(all, big * rounds(all.big, 1.0) * (all.big <= cus ? 1.07 : 1.0));
+    if (full > 0 && rem > 0) {
+        consider({1, 2, full * cus, all.tiles_m, full * cus + 2 * rem}, big * full + rounds(2 * rem, 0.53));
+        consider({1, 1, full * cus, all.tiles_m, full * cus + 4 * rem}, big * full + rounds(4 * rem, 0.30));
     }
-    *units = quarter.groups <= cus && best.bm == 1 ? 0.36 : cost;     // a lone 64 x 64 tile per compute unit
+    *units = cost;
     return best;
 }
 
@@ -318,11 +348,32 @@ template <int BN, int BM, bool PART>
 psd_status start(const Args& g, const BlockPtrs* blocks, int64_t groups, hipStream_t st)
 {
     if (groups < 1 || groups > 0x7fffffff) return PSD_E_INVALID;
-    const size_t lds = g.big > 0 ? Tile<2, 2>::LDS_BYTES : Tile<BN, BM>::LDS_BYTES;
+    const size_t lds = g.big > 0 ? Tile<2, 2, 1>::LDS_BYTES : Tile<BN, BM, 1>::LDS_BYTES;
     const dim3 grid(static_cast<uint32_t>(groups));
-    if constexpr (PART) hipLaunchKernelGGL((sfb_f32_kernel<BN, BM, true>), grid, dim3(THREADS), lds, st, g);
-    else if (blocks) hipLaunchKernelGGL((sfb_f32_blocks_kernel<BN, BM>), grid, dim3(THREADS), lds, st, g, *blocks);
-    else hipLaunchKernelGGL((sfb_f32_kernel<BN, BM, false>), grid, dim3(THREADS), lds, st, g);
+    if constexpr (PART) hipLaunchKernelGGL((sfb_f32_kernel<BN, BM, true>), grid, dim3(256), lds, st, g);
+    else if (blocks) hipLaunchKernelGGL((sfb_f32_blocks_kernel<BN, BM>), grid, dim3(256), lds, st, g, *blocks);
+    else hipLaunchKernelGGL((sfb_f32_kernel<BN, BM, false>), grid, dim3(256), lds, st, g);
+    PSD_HIP_TRY(hipGetLastError());
+    return PSD_OK;
+}
+
+// one tile per workgroup of G groups
+template <int BN, int BM, int G>
+psd_status start_groups(const Args& g, const BlockPtrs* blocks, int64_t groups, hipStream_t st)
+{
+    using T = Tile<BN, BM, G>;
+    // raise the dynamic LDS limit once per process (idempotent, so a race between two first callers is harmless)
+    static std::atomic<bool> attr_done{false};
+    if (!attr_done.load(std::memory_order_acquire)) {
+        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_f32_groups_kernel<BN, BM, G>),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES));
+        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_f32_groups_blocks_kernel<BN, BM, G>),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES));
+        attr_done.store(true, std::memory_order_release);
+    }
+    const dim3 grid(static_cast<uint32_t>(groups));
+    if (blocks) hipLaunchKernelGGL((sfb_f32_groups_blocks_kernel<BN, BM, G>), grid, dim3(T::THREADS), T::LDS_BYTES, st, g, *blocks);
+    else hipLaunchKernelGGL((sfb_f32_groups_kernel<BN, BM, G>), grid, dim3(T::THREADS), T::LDS_BYTES, st, g);
     PSD_HIP_TRY(hipGetLastError());
     return PSD_OK;
 }
@@ -343,6 +394,7 @@ psd_status launch_cover(Args& g, const BlockPtrs* blocks, hipStream_t st)
     if (c.groups > 0x7fffffff) return PSD_E_INVALID;
     g.big = static_cast<int>(c.big);
     g.tiles_m = static_cast<int>(c.tiles_m);
+    if (c.g == 4) return start_groups<1, 1, 4>(g, blocks, c.groups, st);
     return c.bm == 2 ? start<1, 2, false>(g, blocks, c.groups, st) : start<1, 1, false>(g, blocks, c.groups, st);
 }
 
@@ -362,7 +414,7 @@ psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t l
 {
     // 32-bit byte offsets into each factor matrix, with room for the stages of read-ahead
     const int64_t u_bytes = K * ldu * 4, v_bytes = K * ldv * 4;
-    const int64_t reach = (int64_t(1) << 32) - (NSTAGE + 2) * KT * (ldu > ldv ? ldu : ldv) * 4 - 4096;
+    const int64_t reach = (int64_t(1) << 32) - (NSTAGE + 2) * 4 * SLICE * (ldu > ldv ? ldu : ldv) * 4 - 4096;
     if (u_bytes > reach || v_bytes > reach) return PSD_E_UNSUPPORTED;
     Args g = common_args(ldu, ldv, W, Mom, N, M, K, lr, mu, wd);
     g.U = U; g.V = V;
@@ -389,13 +441,13 @@ psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t l
     g.tiles_m = static_cast<int>(c.tiles_m);
     g.tiles = static_cast<int>(c.groups);
     g.part = part; g.part_stride = sfb_part_stride(N, M);
-    g.stages_per_split = static_cast<int>(((K + KT - 1) / KT + splits - 1) / splits);
+    g.stages_per_split = static_cast<int>(((K + SLICE - 1) / SLICE + splits - 1) / splits);
     const psd_status r = start<1, 1, true>(g, nullptr, c.groups * splits, st);
     if (r != PSD_OK) return r;
     return launch_sfb_reduce(part, splits, N, M, W, Mom, lr, mu, wd, st);
 }
 
-bool sfb_f32_blocks_supported(int64_t B) { return B % KT == 0; }     // whole k-stages per block
+bool sfb_f32_blocks_supported(int64_t B) { return B % SLICE == 0; }     // whole k-stages per block
 
 psd_status launch_sfb_f32_blocks(const float* const* U_p, int64_t ldu, const float* const* V_p, int64_t ldv, int64_t P,
                                  int64_t B, float* W, float* Mom, int64_t N, int64_t M, float lr, float mu, float wd,
@@ -411,7 +463,7 @@ psd_status launch_sfb_f32_blocks(const float* const* U_p, int64_t ldu, const flo
     }
     Args g = common_args(ldu, ldv, W, Mom, N, M, P * B, lr, mu, wd);
     g.u_bytes = static_cast<uint32_t>(u_bytes); g.v_bytes = static_cast<uint32_t>(v_bytes);
-    g.n_blocks = static_cast<int>(P); g.stages_per_block = static_cast<int>(B / KT);
+    g.n_blocks = static_cast<int>(P); g.block_rows = static_cast<int>(B);
     return launch_cover(g, &blocks, st);
 }
 
