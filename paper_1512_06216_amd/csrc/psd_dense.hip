@@ -16,14 +16,17 @@
 
 namespace psd {
 
-constexpr int kDenseThreads = 256;
-constexpr int kDenseUnroll = 2;                                   // float4 per lane per chunk
-constexpr int64_t kDenseChunk = int64_t(kDenseThreads) * 4 * kDenseUnroll;  // keys per workgroup
+// One float4 of every array per lane: with two, a workgroup's loads wait for each other's registers.  Small launches take
+// small workgroups (more of them to deal out), large ones large ones (longer contiguous pieces of each of the P + 2 arrays).
+// us at P = 8, with two float4 per lane of 256 -> now: 100 K keys 4.9 -> 4.0, 2.3 M 21.2 -> 20.2 (256 lanes; 512: 20.5,
+// 1024: 23.2), 16.8 M 123.2 -> 120.4 (512; 256: 125.0, 1024: 124.3), 37.7 M 314.8 -> 306.9 (1024; 512: 310.1, 256: 334.9).
+int32_t dense_threads_for(int64_t keys) { return keys < 4000000 ? 256 : keys < 19000000 ? 512 : 1024; }
 
-int32_t dense_chunks_for(int64_t n, int32_t S)
+int32_t dense_chunks_for(int64_t n, int32_t S, int32_t threads)
 {
     const int64_t longest = (n + S - 1) / S;   // floor((s+1)n/S) - floor(sn/S) <= ceil(n/S)
-    return static_cast<int32_t>((longest + kDenseChunk - 1) / kDenseChunk);
+    const int64_t chunk = int64_t(threads) * 4;
+    return static_cast<int32_t>((longest + chunk - 1) / chunk);
 }
 
 namespace {
@@ -38,7 +41,7 @@ __device__ __forceinline__ float4 ld_stream(const float* p) { return load_stream
 // 89.5 M 67.8 / 70.5.
 constexpr int64_t kDenseStreamKeys = 19000000;
 
-// keys [lo, hi) of one layer; PC > 0: number of copies known at compile time; stream: W / Mom streamed
+// keys [lo, hi) of one layer, at most 4 per lane; PC > 0: number of copies known at compile time; stream: W / Mom streamed
 // (the same for every lane of the launch's layer: a uniform branch around each access)
 template <int PC>
 __device__ __forceinline__ void dense_span(const float* const* __restrict__ G, int P, float* __restrict__ W,
@@ -50,48 +53,70 @@ __device__ __forceinline__ void dense_span(const float* const* __restrict__ G, i
     if (lo4 > hi) lo4 = hi;
     const int64_t hi4 = lo4 + ((hi - lo4) & ~int64_t(3));
 
-    int64_t idx[kDenseUnroll];
-    float4 acc[kDenseUnroll], w[kDenseUnroll], m[kDenseUnroll];
+    const int64_t i = lo4 + int64_t(threadIdx.x) * 4;
+    if (i < hi4) {
+        float4 acc, w, m;
+        if constexpr (PC > 0) {
+            float4 g[PC];
 #pragma unroll
-    for (int u = 0; u < kDenseUnroll; ++u) {
-        idx[u] = lo4 + (int64_t(u) * kDenseThreads + threadIdx.x) * 4;
-        if (idx[u] < hi4) {
-            if constexpr (PC > 0) {
-                float4 g[PC];
+            for (int p = 0; p < PC; ++p) g[p] = ld_stream(G[p] + i);
+            w = stream ? load_stream4(W + i) : *reinterpret_cast<const float4*>(W + i);
+            m = stream ? load_stream4(Mom + i) : *reinterpret_cast<const float4*>(Mom + i);
+            acc = g[0];
 #pragma unroll
-                for (int p = 0; p < PC; ++p) g[p] = ld_stream(G[p] + idx[u]);
-                w[u] = stream ? load_stream4(W + idx[u]) : *reinterpret_cast<const float4*>(W + idx[u]);
-                m[u] = stream ? load_stream4(Mom + idx[u]) : *reinterpret_cast<const float4*>(Mom + idx[u]);
-                acc[u] = g[0];
-#pragma unroll
-                for (int p = 1; p < PC; ++p) {
-                    acc[u].x += g[p].x; acc[u].y += g[p].y; acc[u].z += g[p].z; acc[u].w += g[p].w;
-                }
-            } else {
-                w[u] = stream ? load_stream4(W + idx[u]) : *reinterpret_cast<const float4*>(W + idx[u]);
-                m[u] = stream ? load_stream4(Mom + idx[u]) : *reinterpret_cast<const float4*>(Mom + idx[u]);
-                acc[u] = ld_stream(G[0] + idx[u]);
-                for (int p = 1; p < nP; ++p) {
-                    const float4 g = ld_stream(G[p] + idx[u]);
-                    acc[u].x += g.x; acc[u].y += g.y; acc[u].z += g.z; acc[u].w += g.w;
-                }
+            for (int p = 1; p < PC; ++p) {
+                acc.x += g[p].x; acc.y += g[p].y; acc.z += g[p].z; acc.w += g[p].w;
             }
+        } else {
+            w = stream ? load_stream4(W + i) : *reinterpret_cast<const float4*>(W + i);
+            m = stream ? load_stream4(Mom + i) : *reinterpret_cast<const float4*>(Mom + i);
+            // Any number of copies: eight at a time, then four, two and one, each group's loads in flight together and the copies
+            // added in order (one copy after the other, each waited for: 3 M keys, P = 7 27.5 us against 25.3).
+            bool none = true;
+            auto add = [&](const float4& g) {
+                if (none) acc = g;
+                else { acc.x += g.x; acc.y += g.y; acc.z += g.z; acc.w += g.w; }
+                none = false;
+            };
+            int p = 0;
+            for (; p + 8 <= nP; p += 8) {
+                float4 g[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) g[j] = ld_stream(G[p + j] + i);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) add(g[j]);
+            }
+            float4 g4[4], g2[2], g1;
+            if (nP & 4) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) g4[j] = ld_stream(G[p + j] + i);
+            }
+            const int p2 = p + (nP & 4), p1 = p2 + (nP & 2);
+            if (nP & 2) {
+                g2[0] = ld_stream(G[p2] + i);
+                g2[1] = ld_stream(G[p2 + 1] + i);
+            }
+            if (nP & 1) g1 = ld_stream(G[p1] + i);
+            if (nP & 4) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) add(g4[j]);
+            }
+            if (nP & 2) {
+                add(g2[0]);
+                add(g2[1]);
+            }
+            if (nP & 1) add(g1);
         }
-    }
-#pragma unroll
-    for (int u = 0; u < kDenseUnroll; ++u) {
-        if (idx[u] < hi4) {
-            upd(acc[u].x, w[u].x, m[u].x, lr, mu, wd);
-            upd(acc[u].y, w[u].y, m[u].y, lr, mu, wd);
-            upd(acc[u].z, w[u].z, m[u].z, lr, mu, wd);
-            upd(acc[u].w, w[u].w, m[u].w, lr, mu, wd);
-            if (stream) {
-                store_stream4(Mom + idx[u], m[u]);
-                store_stream4(W + idx[u], w[u]);
-            } else {
-                *reinterpret_cast<float4*>(Mom + idx[u]) = m[u];
-                *reinterpret_cast<float4*>(W + idx[u]) = w[u];
-            }
+        upd(acc.x, w.x, m.x, lr, mu, wd);
+        upd(acc.y, w.y, m.y, lr, mu, wd);
+        upd(acc.z, w.z, m.z, lr, mu, wd);
+        upd(acc.w, w.w, m.w, lr, mu, wd);
+        if (stream) {
+            store_stream4(Mom + i, m);
+            store_stream4(W + i, w);
+        } else {
+            *reinterpret_cast<float4*>(Mom + i) = m;
+            *reinterpret_cast<float4*>(W + i) = w;
         }
     }
     // at most 3 unaligned keys at each end of the span
@@ -126,9 +151,9 @@ __device__ __forceinline__ void dense_block(const float* const* G, int P, float*
         begin = int64_t(s) * q + (int64_t(s) * r) / S;
         end = int64_t(s + 1) * q + (int64_t(s + 1) * r) / S;
     }
-    const int64_t lo = begin + c * kDenseChunk;
+    const int64_t chunk = int64_t(blockDim.x) * 4, lo = begin + c * chunk;
     if (lo >= end) return;
-    const int64_t hi = lo + kDenseChunk < end ? lo + kDenseChunk : end;
+    const int64_t hi = lo + chunk < end ? lo + chunk : end;
     const bool stream = q * S + r >= kDenseStreamKeys;       // n = q S + r
     switch (P) {
         case 8: dense_span<8>(G, P, W, Mom, lo, hi, lr, mu, wd, stream); break;
@@ -139,7 +164,8 @@ __device__ __forceinline__ void dense_block(const float* const* G, int P, float*
     }
 }
 
-__global__ void __launch_bounds__(kDenseThreads) dense_ps_table_kernel(const DenseTable t, float lr, float mu, float wd)
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS) dense_ps_table_kernel(const DenseTable t, float lr, float mu, float wd)
 {
     // which layer does this workgroup belong to (at most 16 segments: linear scan)
     int l = 0;
@@ -150,7 +176,8 @@ __global__ void __launch_bounds__(kDenseThreads) dense_ps_table_kernel(const Den
     dense_block(sg.G, sg.P, sg.W, sg.Mom, sg.q, sg.r, sg.S, sg.chunks, b - sg.block_begin, lr, mu, wd);
 }
 
-__global__ void __launch_bounds__(kDenseThreads) dense_ps_wide_kernel(const DenseWide a, float lr, float mu, float wd)
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS) dense_ps_wide_kernel(const DenseWide a, float lr, float mu, float wd)
 {
     dense_block(a.G, a.P, a.W, a.Mom, a.q, a.r, a.S, a.chunks, blockIdx.x, lr, mu, wd);
 }
@@ -159,16 +186,20 @@ __global__ void __launch_bounds__(kDenseThreads) dense_ps_wide_kernel(const Dens
 
 psd_status launch_dense_table(const DenseTable& t, int32_t total_blocks, float lr, float mu, float wd, hipStream_t st)
 {
-    hipLaunchKernelGGL(dense_ps_table_kernel, dim3(total_blocks), dim3(kDenseThreads), 0, st, t, lr, mu, wd);
+    auto kern = t.threads == 256 ? dense_ps_table_kernel<256> : t.threads == 512 ? dense_ps_table_kernel<512> : dense_ps_table_kernel<1024>;
+    hipLaunchKernelGGL(kern, dim3(total_blocks), dim3(t.threads), 0, st, t, lr, mu, wd);
     PSD_HIP_TRY(hipGetLastError());
     return PSD_OK;
 }
 
-psd_status launch_dense_wide(const DenseWide& a, float lr, float mu, float wd, hipStream_t st)
+psd_status launch_dense_wide(DenseWide& a, float lr, float mu, float wd, hipStream_t st)
 {
+    const int threads = dense_threads_for(a.n);
+    a.chunks = dense_chunks_for(a.n, a.S, threads);
     const int64_t blocks = int64_t(a.chunks) * a.S;
     if (blocks < 1 || blocks > (int64_t(1) << 30)) return PSD_E_INVALID;
-    hipLaunchKernelGGL(dense_ps_wide_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(kDenseThreads), 0, st, a, lr, mu, wd);
+    auto kern = threads == 256 ? dense_ps_wide_kernel<256> : threads == 512 ? dense_ps_wide_kernel<512> : dense_ps_wide_kernel<1024>;
+    hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(blocks)), dim3(threads), 0, st, a, lr, mu, wd);
     PSD_HIP_TRY(hipGetLastError());
     return PSD_OK;
 }
@@ -182,7 +213,6 @@ psd_status launch_sfb_reduce(const float* part, int splits, int64_t N, int64_t M
     for (int p = 0; p < PSD_MAX_WORKERS; ++p) a.G[p] = p < splits ? part + p * sfb_part_stride(N, M) : nullptr;
     a.W = W; a.Mom = Mom; a.n = N * M; a.P = splits; a.S = 1;
     a.q = a.n; a.r = 0;
-    a.chunks = dense_chunks_for(a.n, 1);
     return launch_dense_wide(a, lr, mu, wd, st);
 }
 

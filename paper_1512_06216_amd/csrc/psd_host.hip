@@ -265,7 +265,6 @@ psd_status psd_sync_dense_ps(int64_t n, int32_t P, const float* const* G, float*
     for (int p = 0; p < PSD_MAX_WORKERS; ++p) a.G[p] = p < P ? G[p] : nullptr;
     a.W = W; a.Mom = Mom; a.n = n; a.P = P; a.S = S;
     a.q = n / S; a.r = n % S;
-    a.chunks = dense_chunks_for(n, S);
     return launch_dense_wide(a, lr, mu, wd, static_cast<hipStream_t>(stream));
 }
 
@@ -274,8 +273,10 @@ psd_status psd_sync_dense_ps_multi(int32_t L, const psd_dense_segment* segs, flo
     if (!segs) return PSD_E_NULL;
     if (L < 1 || L > PSD_MAX_MULTI_SEGMENTS || !(wd >= 0.0f)) return PSD_E_INVALID;
     DenseTable t;
-    int64_t blocks = 0;
+    int64_t blocks = 0, keys = 0;
     int32_t used = 0;
+    for (int32_t l = 0; l < L; ++l) keys += segs[l].n > 0 && segs[l].n < (int64_t(1) << 40) ? segs[l].n : 0;
+    t.threads = dense_threads_for(keys);
     for (int32_t l = 0; l < L; ++l) {
         const psd_dense_segment& s = segs[l];
         psd_status r = check_dense(s.n, s.P, PSD_MAX_MULTI_WORKERS, s.G, s.W, s.Mom, s.S);
@@ -285,7 +286,7 @@ psd_status psd_sync_dense_ps_multi(int32_t L, const psd_dense_segment* segs, flo
         for (int p = 0; p < PSD_MAX_MULTI_WORKERS; ++p) d.G[p] = p < s.P ? s.G[p] : nullptr;
         d.W = s.W; d.Mom = s.Mom; d.n = s.n; d.P = s.P; d.S = s.S;
         d.q = s.n / s.S; d.r = s.n % s.S;
-        d.chunks = dense_chunks_for(s.n, s.S);
+        d.chunks = dense_chunks_for(s.n, s.S, t.threads);
         d.block_begin = static_cast<int32_t>(blocks);
         blocks += static_cast<int64_t>(d.chunks) * s.S;
         if (blocks > (int64_t(1) << 30)) return PSD_E_INVALID;

@@ -37,6 +37,7 @@ struct DenseSeg {
 struct DenseTable {
     DenseSeg seg[PSD_MAX_MULTI_SEGMENTS];
     int32_t L;
+    int32_t threads;       // lanes per workgroup (dense_threads_for)
 };
 struct DenseWide {          // single layer, up to PSD_MAX_WORKERS copies
     const float* G[PSD_MAX_WORKERS];
@@ -46,11 +47,12 @@ struct DenseWide {          // single layer, up to PSD_MAX_WORKERS copies
     int64_t q, r;          // n = q * S + r, 0 <= r < S
     int32_t P;
     int32_t S;
-    int32_t chunks;
+    int32_t chunks;        // filled in by launch_dense_wide
 };
 psd_status launch_dense_table(const DenseTable& t, int32_t total_blocks, float lr, float mu, float wd, hipStream_t st);
-psd_status launch_dense_wide(const DenseWide& a, float lr, float mu, float wd, hipStream_t st);
-int32_t dense_chunks_for(int64_t n, int32_t S);   // workgroups per shard
+psd_status launch_dense_wide(DenseWide& a, float lr, float mu, float wd, hipStream_t st);
+int32_t dense_threads_for(int64_t keys);          // lanes per workgroup of a launch over this many keys
+int32_t dense_chunks_for(int64_t n, int32_t S, int32_t threads);   // workgroups per shard
 
 struct PackSide {            // one of the two stacked matrices of a layer
     const float* src[PSD_MAX_WORKERS];

@@ -404,6 +404,27 @@ def test_sfb_random_shapes_bit_exact(dtype):
         assert np.array_equal(bias.cpu().numpy(), br) and np.array_equal(mb.cpu().numpy(), mr), (M, N, B, P)
 
 
+@pytest.mark.parametrize("P", [1, 3, 7, 9, 11, 15, 24, 31])
+@pytest.mark.parametrize("n,S", [(4099, 3), (4_000_003, 7)])            # workgroups of 256 and of 512 lanes
+def test_dense_any_number_of_copies_bit_exact(n, S, P):
+    d = inputs.dense_layer_integer(n, P, seed=P)
+    W, Mom = dev(d["W"]), dev(d["Mom"])
+    psd.sync_dense_ps([dev(g) for g in d["G"]], W, Mom, 0.125, 0.5, S, wd=0.5)
+    torch.cuda.synchronize()
+    Wr, Mr = orc.sync_dense_ps(d["G"], d["W"], d["Mom"], 0.125, 0.5, S, wd=0.5)
+    assert np.array_equal(W.cpu().numpy(), Wr) and np.array_equal(Mom.cpu().numpy(), Mr)
+
+
+def test_dense_largest_workgroups_bit_exact():
+    n = 19_000_001
+    d = inputs.dense_layer_integer(n, 2, seed=19)
+    W, Mom = dev(d["W"]), dev(d["Mom"])
+    psd.sync_dense_ps([dev(g) for g in d["G"]], W, Mom, 0.125, 0.5, 5)
+    torch.cuda.synchronize()
+    Wr, Mr = orc.sync_dense_ps(d["G"], d["W"], d["Mom"], 0.125, 0.5, 5)
+    assert np.array_equal(W.cpu().numpy(), Wr) and np.array_equal(Mom.cpu().numpy(), Mr)
+
+
 def test_dense_random_sizes_bit_exact():
     rng = np.random.default_rng(77)
     for _ in range(24):
