@@ -54,16 +54,20 @@ psd_status launch_dense_wide(DenseWide& a, float lr, float mu, float wd, hipStre
 int32_t dense_threads_for(int64_t keys);          // lanes per workgroup of a launch over this many keys
 int32_t dense_chunks_for(int64_t n, int32_t S, int32_t threads);   // workgroups per shard
 
+struct FastDiv { uint32_t d, mul, shift1, shift2; };   // division by d, see psd_pack.hip
 struct PackSide {            // one of the two stacked matrices of a layer
     const float* src[PSD_MAX_WORKERS];
     void* dst;
     int64_t cols, ld;
+    FastDiv chunks;          // by the 16-byte chunks of a row (this and what follows is filled in by launch_pack)
 };
 struct PackArgs {
     PackSide u, v;           // errors (B x N blocks -> K x ldu), activations (B x M blocks -> K x ldv)
     int64_t B;
     int32_t P;
-    int32_t bx_u;            // workgroup columns serving u (filled in by launch_pack)
+    int32_t groups_u;        // workgroups serving u
+    uint32_t row0, rows;     // rows of this launch
+    FastDiv block;           // by B
 };
 psd_status launch_pack(PackArgs& a, int32_t out_dtype, hipStream_t st);
 

@@ -1,21 +1,23 @@
 // Factor stacking (SFB steps 1-2 of Section 4.3.1, receiver side): P per-worker blocks of
 // B samples become one K x ld matrix, row k = p*B + b, optionally rounded to bf16.
 //
-// Memcpy-class, HBM-bound.  One lane produces one 16-byte output chunk (4 fp32 or 8 bf16),
-// so every store is a full aligned 16 bytes and a wavefront writes 1 KiB contiguous.
-// Source rows start at b*cols floats, which is only 4-byte aligned when cols is odd
-// (e.g. 21841 classes); loads therefore use a 4-byte-aligned vector type and leave the
-// choice of instruction to the compiler.  U (errors) and V (activations) of a layer are
-// stacked by ONE launch: the first bx_u workgroup columns serve U, the rest V.
+// Memcpy-class, HBM-bound.  One lane produces one 16-byte output chunk (4 fp32 or 8 bf16).  A stacked matrix is dealt out
+// as one sequence of chunks, 256 to a workgroup, so the lanes are all busy and a workgroup reads one contiguous piece
+// whatever the width (a workgroup per 2048 columns of a row left most lanes of narrow rows idle and the last workgroup of
+// every row part empty; us: 64 + 64 columns, 4096 rows, bf16 5.4 -> 3.2; 4096 + 4096, 2048 rows, fp32 26.1 -> 24.5;
+// 3000 + 21841, 2048 rows, bf16 54.5 -> 52.7).  One chunk per lane: with two or four the loads of a workgroup wait for each
+// other (9216 + 4096 in units of 4 columns: 31.4, 33.1 and 34.2 us with one, two and four).
+// Source rows start at b*cols floats, which is only 4-byte aligned when cols is odd (e.g. 21841 classes); loads therefore use
+// a 4-byte-aligned vector type and leave the choice of instruction to the compiler.  U (errors) and V (activations) of a
+// layer are stacked by ONE launch: the first workgroups serve U, the rest V.
 #include "psd_internal.h"
 
 namespace psd {
 namespace {
 
-constexpr int kPackThreads = 256;
-constexpr int64_t kPackMaxRows = 65535;            // grid.y limit; longer stacks loop over rows
+constexpr int kThreads = 256;
 
-struct __attribute__((packed, aligned(4))) f32x4_a4 { float x, y, z, w; };
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 // fp32 -> bf16 bits, round to nearest even; NaN keeps sign and top payload bits, made quiet.
 __device__ __forceinline__ uint32_t bf16_rne(float f)
@@ -25,60 +27,94 @@ __device__ __forceinline__ uint32_t bf16_rne(float f)
     return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
 }
 
-template <bool BF16>
-__global__ void __launch_bounds__(kPackThreads) pack_kernel(const PackArgs a)
+// n / d for any 32-bit n (Granlund & Montgomery, division by invariant integers using multiplication)
+__device__ __forceinline__ uint32_t divide(uint32_t n, const FastDiv& f)
 {
-    constexpr int E = BF16 ? 8 : 4;                     // elements per 16-byte output chunk
-    const bool is_v = static_cast<int>(blockIdx.x) >= a.bx_u;
+    const uint32_t t = __umulhi(f.mul, n);
+    return (t + ((n - t) >> f.shift1)) >> f.shift2;
+}
+
+template <bool BF16>
+__global__ void __launch_bounds__(kThreads) pack_kernel(const PackArgs a)
+{
+    constexpr int E = BF16 ? 8 : 4;                    // columns per lane: one 16-byte store
+    const bool is_v = static_cast<int>(blockIdx.x) >= a.groups_u;
     const PackSide& s = is_v ? a.v : a.u;
-    const int64_t chunk = int64_t(is_v ? blockIdx.x - a.bx_u : blockIdx.x) * kPackThreads + threadIdx.x;
-    const int64_t j0 = chunk * E;
-    if (j0 >= s.ld) return;
-    const int64_t K = a.B * a.P;
-    for (int64_t k = blockIdx.y; k < K; k += gridDim.y) {           // stacked row
-        const int p = static_cast<int>(k / a.B);
-        const int64_t b = k - int64_t(p) * a.B;
-        const float* __restrict__ src = s.src[p] + b * s.cols + j0;
-        float v[E];
-        if (j0 + E <= s.cols) {
-#pragma unroll
-            for (int q = 0; q < E / 4; ++q) {
-                const f32x4_a4 t = *reinterpret_cast<const f32x4_a4*>(src + 4 * q);
-                v[4 * q + 0] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < E; ++e) v[e] = (j0 + e < s.cols) ? src[e] : 0.0f;   // zero the padding columns
-        }
-        if constexpr (BF16) {
-            uint4 o;
-            o.x = bf16_rne(v[0]) | (bf16_rne(v[1]) << 16);
-            o.y = bf16_rne(v[2]) | (bf16_rne(v[3]) << 16);
-            o.z = bf16_rne(v[4]) | (bf16_rne(v[5]) << 16);
-            o.w = bf16_rne(v[6]) | (bf16_rne(v[7]) << 16);
-            *reinterpret_cast<uint4*>(static_cast<uint16_t*>(s.dst) + k * s.ld + j0) = o;
-        } else {
-            *reinterpret_cast<float4*>(static_cast<float*>(s.dst) + k * s.ld + j0) = make_float4(v[0], v[1], v[2], v[3]);
-        }
+    const uint32_t first = static_cast<uint32_t>(is_v ? blockIdx.x - a.groups_u : blockIdx.x) * kThreads;
+    const int cols = static_cast<int>(s.cols);
+    // Nearly always all of the workgroup's rows come from one worker's block: its address is then a scalar.
+    const uint32_t k_first = a.row0 + divide(first, s.chunks);
+    const uint32_t p_first = __builtin_amdgcn_readfirstlane(divide(k_first, a.block));
+    const float* __restrict__ src = s.src[p_first];
+    const uint32_t q = first + threadIdx.x, row = divide(q, s.chunks);
+    const int col = static_cast<int>(q - row * s.chunks.d) * E;
+    if (row >= a.rows) return;
+    const uint32_t k = a.row0 + row;
+    uint32_t b = k - p_first * a.block.d;              // row of the block
+    if (b >= a.block.d) {                              // not the first row's block
+        const uint32_t p = divide(k, a.block);
+        src = s.src[p];
+        b = k - p * a.block.d;
     }
+    src += int64_t(b) * cols + col;
+    float v[E];
+    if (col + E <= cols) {
+#pragma unroll
+        for (int e = 0; e < E; e += 4) {
+            const f32x4_a4 t = *reinterpret_cast<const f32x4_a4*>(src + e);
+            v[e] = t.x; v[e + 1] = t.y; v[e + 2] = t.z; v[e + 3] = t.w;
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < E; ++e) v[e] = col + e < cols ? src[e] : 0.0f;   // zero the padding columns
+    }
+    const int64_t at = int64_t(k) * s.ld + col;
+    if constexpr (BF16) {
+        uint4 o;
+        o.x = bf16_rne(v[0]) | (bf16_rne(v[1]) << 16);
+        o.y = bf16_rne(v[2]) | (bf16_rne(v[3]) << 16);
+        o.z = bf16_rne(v[4]) | (bf16_rne(v[5]) << 16);
+        o.w = bf16_rne(v[6]) | (bf16_rne(v[7]) << 16);
+        *reinterpret_cast<uint4*>(static_cast<uint16_t*>(s.dst) + at) = o;
+    } else {
+        *reinterpret_cast<float4*>(static_cast<float*>(s.dst) + at) = make_float4(v[0], v[1], v[2], v[3]);
+    }
+}
+
+FastDiv fast_div(uint32_t d)
+{
+    int l = 0;                                         // ceil(log2(d))
+    while ((uint64_t(1) << l) < d) ++l;
+    FastDiv f;
+    f.d = d;
+    f.mul = static_cast<uint32_t>((uint64_t(1) << 32) * ((uint64_t(1) << l) - d) / d + 1);
+    f.shift1 = l < 1 ? l : 1;
+    f.shift2 = l < 1 ? 0 : l - 1;
+    return f;
 }
 
 }  // namespace
 
 psd_status launch_pack(PackArgs& a, int32_t out_dtype, hipStream_t st)
 {
-    const int E = out_dtype == PSD_BF16 ? 8 : 4;
     const int64_t K = a.B * a.P;
-    // ld is a multiple of E (validated)
-    const int64_t bx_u = (a.u.ld / E + kPackThreads - 1) / kPackThreads, bx_v = (a.v.ld / E + kPackThreads - 1) / kPackThreads;
-    if (bx_u < 1 || bx_v < 1 || bx_u + bx_v > 0x7fffffff || K < 1) return PSD_E_INVALID;
-    a.bx_u = static_cast<int32_t>(bx_u);
-    dim3 grid(static_cast<uint32_t>(bx_u + bx_v), static_cast<uint32_t>(K < kPackMaxRows ? K : kPackMaxRows));
-    if (out_dtype == PSD_BF16)
-        hipLaunchKernelGGL(pack_kernel<true>, grid, dim3(kPackThreads), 0, st, a);
-    else
-        hipLaunchKernelGGL(pack_kernel<false>, grid, dim3(kPackThreads), 0, st, a);
-    PSD_HIP_TRY(hipGetLastError());
+    if (K < 1) return PSD_E_INVALID;
+    const int64_t E = out_dtype == PSD_BF16 ? 8 : 4;              // ld is a multiple of E (validated)
+    const int64_t cu = a.u.ld / E, cv = a.v.ld / E;               // chunks per row
+    a.u.chunks = fast_div(static_cast<uint32_t>(cu));
+    a.v.chunks = fast_div(static_cast<uint32_t>(cv));
+    a.block = fast_div(static_cast<uint32_t>(a.B));
+    // 32-bit chunk numbers: a longer stack takes several launches
+    const int64_t most = (int64_t(1) << 31) / (cu > cv ? cu : cv);
+    for (int64_t row0 = 0; row0 < K; row0 += most) {
+        a.row0 = static_cast<uint32_t>(row0);
+        a.rows = static_cast<uint32_t>(K - row0 < most ? K - row0 : most);
+        const int64_t gu = (a.rows * cu + kThreads - 1) / kThreads, gv = (a.rows * cv + kThreads - 1) / kThreads;
+        a.groups_u = static_cast<int32_t>(gu);
+        auto kern = out_dtype == PSD_BF16 ? pack_kernel<true> : pack_kernel<false>;
+        hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(gu + gv)), dim3(kThreads), 0, st, a);
+        PSD_HIP_TRY(hipGetLastError());
+    }
     return PSD_OK;
 }
 

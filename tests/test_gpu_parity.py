@@ -81,6 +81,18 @@ def test_pack_bit_exact(M, N, B, P, dtype):
     assert not Ug[:, N:].any() and not Vg[:, M:].any()          # padding columns are zero
 
 
+@pytest.mark.parametrize("M,N,B,P", [(64, 8, 5, 7), (8, 16, 1, 64), (72, 520, 3, 33), (2056, 4, 9, 3)])
+@pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
+def test_pack_workgroups_across_rows_and_blocks(M, N, B, P, dtype):
+    """Narrow rows: a workgroup's chunks span many rows and several workers' blocks."""
+    d = inputs.fc_layer(M, N, B, P, seed=M + N + P)
+    plan, U, ldu, V, ldv = run_pack(d, dtype)
+    Uo, Vo = orc.pack_factors(d["delta"], d["act"], "f32" if dtype == psd.F32 else "bf16")
+    Ug, Vg = (U.cpu().numpy(), V.cpu().numpy()) if dtype == psd.F32 else (bits16(U), bits16(V))
+    assert np.array_equal(Ug[:, :N], Uo) and np.array_equal(Vg[:, :M], Vo)
+    assert not Ug[:, N:].any() and not Vg[:, M:].any()
+
+
 def test_pack_maximum_worker_count():
     d = inputs.fc_layer(40, 24, 1, 64, seed=64)                  # P = 64 workers, one sample each
     for dtype, name in ((psd.F32, "f32"), (psd.BF16, "bf16")):
