@@ -81,6 +81,25 @@ __device__ __forceinline__ i32x4 raw_rsrc(const void* X, uint32_t bytes)
     return r;
 }
 
+// A matrix that is fed to LDS from the top down: what is left of it, all in scalar registers.  The MFMA loops move on by
+// advancing the descriptor instead of the lanes' offsets: a vector add between two MFMAs keeps the matrix pipe waiting for
+// about 12 clocks (four adds 24), scalar instructions, LDS reads and waits cost it nothing.
+struct Feed {
+    uint64_t base;
+    uint32_t left;                                // bytes; the range check returns zeros past them
+    __device__ __forceinline__ void aim(const void* X, uint64_t skip, uint32_t bytes)
+    {
+        base = reinterpret_cast<uint64_t>(X) + skip;
+        left = bytes > skip ? static_cast<uint32_t>(bytes - skip) : 0u;
+    }
+    __device__ __forceinline__ void advance(uint32_t step)
+    {
+        base += step;
+        asm("s_sub_u32 %0, %0, %1\n\ts_cselect_b32 %0, 0, %0" : "+s"(left) : "s"(step) : "scc");   // left - step, 0 at least
+    }
+    __device__ __forceinline__ i32x4 rsrc() const { return raw_rsrc(reinterpret_cast<const void*>(base), left); }
+};
+
 // Scheduling pattern for one pipeline phase holding MF MFMAs and R LDS reads that do not depend
 // on each other: 1 MFMA, then PER reads, and so on until the reads are out.
 template <int R, int MF, int PER, int I = 0>
@@ -220,6 +239,129 @@ struct RowUpdate {
                 }
             }
             run<B + 1>(buf, lr, mu, wd);
+        }
+    }
+};
+
+// The same for a tile that lies inside W, with most of the vector instructions gone (the fp32 MFMA pipe runs no faster than
+// they leave it time: 9216 -> 4096, K = 512, 384 -> 312 us).  Only the first and the last line of a row are shared with other
+// tiles, and the lanes that own quads of the one own none of the other, so that one access takes both.  The quad in which a
+// row of a length that is no multiple of 4 begins, and the one in which it ends, are left over: those of all rows of a
+// wavefront make one more access.  ON_LINES: rows of W and Mom start on lines (no shift at all).
+template <int ROWS, int WIDTH, int WAVES, int DEPTH, bool ON_LINES, class RowN>
+struct InnerUpdate {
+    static constexpr int LINES = WIDTH / 32, GROUPS = ROWS / 8 / WAVES;       // a wavefront's groups of eight rows
+    static constexpr int UNITS = GROUPS * LINES, BATCHES = (UNITS + DEPTH - 1) / DEPTH;
+    static_assert(ROWS % (8 * WAVES) == 0 && WIDTH % 32 == 0 && GROUPS * 16 <= 64, "whole lines of eight rows, their ends in one access");
+    float* W;
+    float* Mom;
+    RowN row_n;
+    int64_t m0, M;
+    int wave, lane, stride;
+    float4 w[2][DEPTH], mo[2][DEPTH], w_end, mo_end;
+
+    __device__ __forceinline__ InnerUpdate(float* W_, float* Mom_, RowN row, int64_t m0_, int64_t M_, int wave_, int lane_)
+        : W(W_), Mom(Mom_), row_n(row), m0(m0_), M(M_), wave(wave_), lane(lane_), stride(row_stride(WIDTH, ON_LINES ? 0 : M_))
+    {
+    }
+    struct Place {
+        int64_t off;                               // of this lane's quad in W
+        int at;                                    // ... in the row buffer
+        bool any;                                  // does the tile own all of it
+    };
+    __device__ __forceinline__ Place place(int u) const
+    {
+        const int line = u % LINES, r = (wave + WAVES * (u / LINES)) * 8 + (lane >> 3), q = 4 * (lane & 7);
+        const int64_t n = row_n(r);
+        Place p = {n * M + m0 + 32 * line + q, r * stride + 32 * line + q, true};
+        if constexpr (ON_LINES) return p;
+        const int shift = line_shift(W, n, M);
+        p.off -= shift;
+        if (line == 0) {                           // the first line, and the last in the lanes before the row begins
+            const int far = q < shift ? WIDTH : 0;
+            p.off += far;
+            p.at += far;
+            p.any = q >= shift || q + 3 < shift;
+        }
+        return p;
+    }
+    struct End {
+        int64_t off;
+        int at, from, to;                          // elements [from, to) of the quad are the tile's
+    };
+    __device__ __forceinline__ End end() const
+    {
+        const int k = lane >> 1, last = lane & 1, r = (wave + WAVES * (k >> 3)) * 8 + (k & 7);
+        const int64_t n = row_n(r);
+        const int shift = line_shift(W, n, M), q = shift & ~3, cut = k < 8 * GROUPS ? shift & 3 : 0;
+        return {n * M + m0 + q - shift + last * WIDTH, r * stride + q + last * WIDTH, cut == 0 || last ? 0 : cut, cut == 0 ? 0 : last ? cut : 4};
+    }
+    template <int B>
+    __device__ __forceinline__ void fetch()
+    {
+#pragma unroll
+        for (int j = 0; j < DEPTH; ++j) {
+            const int u = B * DEPTH + j;
+            if (u >= UNITS) continue;
+            const Place p = place(u);
+            if (ON_LINES || u % LINES > 0) {
+                w[B & 1][j] = load_stream4(W + p.off);
+                mo[B & 1][j] = load_stream4(Mom + p.off);
+            } else if (p.any) {
+                w[B & 1][j] = *reinterpret_cast<const float4*>(W + p.off);
+                mo[B & 1][j] = *reinterpret_cast<const float4*>(Mom + p.off);
+            }
+        }
+        if (!ON_LINES && B == 0 && M % 4 != 0) {
+            const End e = end();                   // loaded whole, as in RowUpdate
+            if (e.to > e.from) {
+                w_end = *reinterpret_cast<const float4*>(W + e.off);
+                mo_end = *reinterpret_cast<const float4*>(Mom + e.off);
+            }
+        }
+    }
+    __device__ __forceinline__ void update(const float* buf, int at, float4& wv, float4& mv, float lr, float mu, float wd) const
+    {
+        const float4 d = *reinterpret_cast<const float4*>(buf + at);
+        upd(d.x, wv.x, mv.x, lr, mu, wd);
+        upd(d.y, wv.y, mv.y, lr, mu, wd);
+        upd(d.z, wv.z, mv.z, lr, mu, wd);
+        upd(d.w, wv.w, mv.w, lr, mu, wd);
+    }
+    template <int B = 0>
+    __device__ __forceinline__ void run(const float* buf, float lr, float mu, float wd)
+    {
+        if constexpr (B < BATCHES) {
+            if constexpr (B + 1 < BATCHES) fetch<B + 1>();
+#pragma unroll
+            for (int j = 0; j < DEPTH; ++j) {
+                const int u = B * DEPTH + j;
+                if (u >= UNITS) continue;
+                const Place p = place(u);
+                if (!p.any) continue;
+                float4 &wv = w[B & 1][j], &mv = mo[B & 1][j];
+                update(buf, p.at, wv, mv, lr, mu, wd);
+                if (ON_LINES || WIDTH < 128 || u % LINES > 0) {
+                    store_stream4(Mom + p.off, mv);
+                    store_stream4(W + p.off, wv);
+                } else {
+                    *reinterpret_cast<float4*>(Mom + p.off) = mv;
+                    *reinterpret_cast<float4*>(W + p.off) = wv;
+                }
+            }
+            run<B + 1>(buf, lr, mu, wd);
+        } else if (!ON_LINES && M % 4 != 0) {
+            const End e = end();
+            if (e.to > e.from) {
+                update(buf, e.at, w_end, mo_end, lr, mu, wd);
+                const float we[4] = {w_end.x, w_end.y, w_end.z, w_end.w}, me[4] = {mo_end.x, mo_end.y, mo_end.z, mo_end.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (i >= e.from && i < e.to) {
+                        Mom[e.off + i] = me[i];
+                        W[e.off + i] = we[i];
+                    }
+            }
         }
     }
 };

@@ -22,6 +22,7 @@
 // would wait for them; spread over the whole half they cost 3 % on every shape), and the workgroup barrier sits between
 // the two halves.
 #include <atomic>
+#include <type_traits>
 #include "psd_device.h"
 #include "psd_internal.h"
 
@@ -84,15 +85,10 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
     const int N = g.N, M = g.M;
     const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
         (__attribute__((address_space(3))) void*)lds));
-    uint32_t u_bytes = g.u_bytes, v_bytes = g.v_bytes;
-    // this workgroup's k range: rows at or past k_end read as zeros (descriptor size), rows before
-    // k_begin are skipped (offsets)
+    // this workgroup's k range: rows at or past k_end read as zeros, rows before k_begin are skipped
     const int k_begin = PART ? split * g.stages_per_split * KT : 0;
     const int k_end = PART ? (k_begin + g.stages_per_split * KT < g.K ? k_begin + g.stages_per_split * KT : g.K) : g.K;
-    if constexpr (PART) {
-        u_bytes = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(int64_t(k_end) * g.ldu * 4));
-        v_bytes = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(int64_t(k_end) * g.ldv * 4));
-    }
+    const uint32_t row_a = static_cast<uint32_t>(g.ldu * 4), row_b = static_cast<uint32_t>(g.ldv * 4);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int group = wave >> 2;
@@ -100,45 +96,50 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
     const int l32 = lane & 31, lhi = lane >> 5;
 
     // DMA plan: run j of this wavefront covers chunks f = (wave*NI + j)*64 + lane of the stage
-    i32x4 rsrc_u = raw_rsrc(g.U, u_bytes), rsrc_v = raw_rsrc(g.V, v_bytes);
+    Feed u, v;
     int blk = 0, row_in_blk = group * SLICE;     // BLK: where this wavefront's next slice lies (its runs are all in slice `group`)
-    auto aim_block = [&]() {                     // BLK: descriptors over the block the slice lies in (u_bytes, v_bytes = one block)
+    auto aim_block = [&]() {                     // BLK: feed from the block the slice lies in (u_bytes, v_bytes = one block)
         while (row_in_blk >= g.block_rows) {
             row_in_blk -= g.block_rows;
             ++blk;
         }
         const bool live = blk < g.n_blocks;
         const int i = live ? blk : 0;            // the table is never indexed past its end
-        rsrc_u = raw_rsrc(uniform_ptr(blocks->u[i]), live ? u_bytes : 0u);
-        rsrc_v = raw_rsrc(uniform_ptr(blocks->v[i]), live ? v_bytes : 0u);
+        u.aim(uniform_ptr(blocks->u[i]), uint64_t(row_in_blk) * row_a, live ? g.u_bytes : 0u);
+        v.aim(uniform_ptr(blocks->v[i]), uint64_t(row_in_blk) * row_b, live ? g.v_bytes : 0u);
     };
-    if constexpr (BLK) aim_block();
+    if constexpr (BLK) {
+        aim_block();
+    } else {
+        u.aim(g.U, uint64_t(k_begin) * row_a, PART ? uint32_t(k_end) * row_a : g.u_bytes);
+        v.aim(g.V, uint64_t(k_begin) * row_b, PART ? uint32_t(k_end) * row_b : g.v_bytes);
+    }
     uint32_t voff_a[T::NI_A], voff_b[T::NI_B];
 #pragma unroll
     for (int j = 0; j < T::NI_A; ++j) {
         const int f = (wave * T::NI_A + j) * 64 + lane;
         const int r = f / (T::TN / 4);
-        voff_a[j] = static_cast<uint32_t>(((BLK ? r % SLICE : k_begin + r) * g.ldu + n0 + (f % (T::TN / 4)) * 4) * 4);
+        voff_a[j] = static_cast<uint32_t>(((BLK ? r % SLICE : r) * g.ldu + n0 + (f % (T::TN / 4)) * 4) * 4);
     }
 #pragma unroll
     for (int j = 0; j < T::NI_B; ++j) {
         const int f = (wave * T::NI_B + j) * 64 + lane;
         const int r = f / (T::TM / 4);
-        voff_b[j] = static_cast<uint32_t>(((BLK ? r % SLICE : k_begin + r) * g.ldv + m0 + (f % (T::TM / 4)) * 4) * 4);
+        voff_b[j] = static_cast<uint32_t>(((BLK ? r % SLICE : r) * g.ldv + m0 + (f % (T::TM / 4)) * 4) * 4);
     }
-    const uint32_t row_a = static_cast<uint32_t>(g.ldu * 4), row_b = static_cast<uint32_t>(g.ldv * 4);
-    auto issue = [&](int t) {                    // stage t -> ring buffer t % NSTAGE (stages are requested in order); past K: zeros
-        const uint32_t base = lds0 + static_cast<uint32_t>(t % NSTAGE) * T::STAGE_BYTES;
-        const uint32_t row = static_cast<uint32_t>(BLK ? row_in_blk : t * KT);
+    auto issue = [&](int s) {                    // the next stage -> ring buffer s (stages are requested in order); past K: zeros
+        const uint32_t base = lds0 + static_cast<uint32_t>(s) * T::STAGE_BYTES;
+        const i32x4 rsrc_u = u.rsrc(), rsrc_v = v.rsrc();
 #pragma unroll
-        for (int j = 0; j < T::NI_A; ++j)
-            dma_b128(base + (wave * T::NI_A + j) * 1024, voff_a[j] + row * row_a, rsrc_u);
+        for (int j = 0; j < T::NI_A; ++j) dma_b128(base + (wave * T::NI_A + j) * 1024, voff_a[j], rsrc_u);
 #pragma unroll
-        for (int j = 0; j < T::NI_B; ++j)
-            dma_b128(base + T::A_BYTES + (wave * T::NI_B + j) * 1024, voff_b[j] + row * row_b, rsrc_v);
-        if constexpr (BLK) {
-            row_in_blk += KT;
-            if (row_in_blk >= g.block_rows) aim_block();
+        for (int j = 0; j < T::NI_B; ++j) dma_b128(base + T::A_BYTES + (wave * T::NI_B + j) * 1024, voff_b[j], rsrc_v);
+        if constexpr (BLK) row_in_blk += KT;
+        if (BLK && row_in_blk >= g.block_rows) {
+            aim_block();
+        } else {
+            u.advance(KT * row_a);
+            v.advance(KT * row_b);
         }
     };
 
@@ -152,15 +153,21 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
 
     // One half-stage = 4 MFMA k-pairs.  Lanes 0..31 feed k = 2*kk, lanes 32..63 feed k = 2*kk + 1.
     struct Half { f32x2 a[4]; f32x2 b[4]; };
-    const uint32_t rd_a = static_cast<uint32_t>((group * SLICE + lhi) * T::RA + (wn0 + BN * l32) * 4);
-    const uint32_t rd_b = static_cast<uint32_t>(T::A_BYTES + (group * SLICE + lhi) * T::RB + (wm0 + BM * l32) * 4);
-    auto load_half = [&](int t, int h, Half& f) {
-        const uint32_t base = lds0 + static_cast<uint32_t>(t % NSTAGE) * T::STAGE_BYTES;
+    // Every ring buffer has its reads compiled in: the addresses are these and an offset in the instruction (64 KiB at most).
+    constexpr int REACH = 65536 / T::STAGE_BYTES < NSTAGE ? 65536 / T::STAGE_BYTES : NSTAGE;      // ring buffers per address
+    uint32_t rd_a[NSTAGE / REACH], rd_b[NSTAGE / REACH];
+#pragma unroll
+    for (int i = 0; i < NSTAGE / REACH; ++i) {
+        rd_a[i] = lds0 + i * REACH * T::STAGE_BYTES + static_cast<uint32_t>((group * SLICE + lhi) * T::RA + (wn0 + BN * l32) * 4);
+        rd_b[i] = lds0 + i * REACH * T::STAGE_BYTES + static_cast<uint32_t>((group * SLICE + lhi) * T::RB + (wm0 + BM * l32) * 4);
+        asm("" : "+v"(rd_a[i]), "+v"(rd_b[i]));   // kept in registers
+    }
+    auto load_half = [&](int s, int h, Half& f) {
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-            const int krow = 2 * (4 * h + kk);
-            const auto pa = reinterpret_cast<__attribute__((address_space(3))) const char*>(base + rd_a + krow * T::RA);
-            const auto pb = reinterpret_cast<__attribute__((address_space(3))) const char*>(base + rd_b + krow * T::RB);
+            const int krow = 2 * (4 * h + kk), at = (s % REACH) * T::STAGE_BYTES;
+            const auto pa = reinterpret_cast<__attribute__((address_space(3))) const char*>(rd_a[s / REACH]) + at + krow * T::RA;
+            const auto pb = reinterpret_cast<__attribute__((address_space(3))) const char*>(rd_b[s / REACH]) + at + T::A_BYTES + krow * T::RB;
             if constexpr (BN == 2) f.a[kk] = *reinterpret_cast<__attribute__((address_space(3))) const f32x2*>(pa);
             else f.a[kk].x = *reinterpret_cast<__attribute__((address_space(3))) const float*>(pa);
             if constexpr (BM == 2) f.b[kk] = *reinterpret_cast<__attribute__((address_space(3))) const f32x2*>(pb);
@@ -186,19 +193,30 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
     __syncthreads();
     Half h0, h1;
     load_half(0, 0, h0);
-    for (int t = 0; t < steps; ++t) {
-        load_half(t, 1, h1);
+    auto step = [&](int s) {                      // contracts the stage in ring buffer s (a constant after inlining)
+        load_half(s, 1, h1);
         mma_half(h0);
         interleave();
         __builtin_amdgcn_sched_barrier(0);
-        wait_vmcnt<(NSTAGE - 3) * LPS>();         // stage t+1 has landed
-        __syncthreads();                          // ... for every wavefront, and stage t-1 is free
-        issue(t + NSTAGE - 1);
-        load_half(t + 1, 0, h0);
+        wait_vmcnt<(NSTAGE - 3) * LPS>();         // the next stage has landed
+        __syncthreads();                          // ... for every wavefront, and the one before is free
+        issue((s + NSTAGE - 1) % NSTAGE);
+        load_half((s + 1) % NSTAGE, 0, h0);
         mma_half(h1);
         interleave();
         __builtin_amdgcn_sched_barrier(0);
+    };
+    static_assert(NSTAGE == 4, "the loop below goes round the ring once");
+    int t = steps;
+    for (; t >= NSTAGE; t -= NSTAGE) {
+        step(0);
+        step(1);
+        step(2);
+        step(3);
     }
+    if (t > 0) step(0);
+    if (t > 1) step(1);
+    if (t > 2) step(2);
     wait_vmcnt<0>();                              // nothing may still be landing in LDS when it is used for the update
 
     // Accumulator register r of a 32x32 block holds MFMA row 8*(r/4) + 4*(lane/32) + r%4, column lane%32.
@@ -227,32 +245,49 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
         // K = 16): 160 -> 124 us, with rows of odd length 212 -> 154 us.
         float* buf = reinterpret_cast<float*>(lds);
         const int64_t nw = n0 + wn0;
+        auto update = [&](auto inside, auto on_lines) {
+            constexpr bool L = decltype(on_lines)::value;
 #pragma unroll
-        for (int ta = 0; ta < BN; ++ta) {
-            auto row_n = [&](int r) { return n0 + (r >> 5) * 32 * BN + BN * (r & 31) + ta; };
-            RowUpdate<64, T::TM, T::WAVES, BM == 2 ? 5 : 6, G, decltype(row_n)> rows(g.W, g.Mom, row_n, m0, N, M, wave, lane);
-            rows.template fetch<0>();
-            __syncthreads();                          // the ring, or the rows before, are no longer read
+            for (int ta = 0; ta < BN; ++ta) {
+                auto row_n = [&](int r) { return n0 + (r >> 5) * 32 * BN + BN * (r & 31) + ta; };
+                auto apply = [&](auto rows) {
+                    rows.template fetch<0>();
+                    __syncthreads();                      // the ring, or the rows before, are no longer read
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = 8 * (r >> 2) + 4 * lhi + (r & 3);
-                float* to = buf + (group * 64 + ((wave >> 1) & 1) * 32 + row) * rows.stride + wm0 + BM * l32 + line_shift(g.W, nw + BN * row + ta, M);
-                if (BM == 2 && M % 2 == 0) {
-                    *reinterpret_cast<float2*>(to) = make_float2(acc[ta][0][r], acc[ta][BM - 1][r]);
-                } else {
+                    for (int r = 0; r < 16; ++r) {
+                        const int row = 8 * (r >> 2) + 4 * lhi + (r & 3);
+                        float* to = buf + (group * 64 + ((wave >> 1) & 1) * 32 + row) * rows.stride + wm0 + BM * l32 +
+                                    (L ? 0 : line_shift(g.W, nw + BN * row + ta, M));
+                        if (BM == 2 && (L || M % 2 == 0)) {
+                            *reinterpret_cast<float2*>(to) = make_float2(acc[ta][0][r], acc[ta][BM - 1][r]);
+                        } else {
 #pragma unroll
-                    for (int tb = 0; tb < BM; ++tb) to[tb] = acc[ta][tb][r];
-                }
+                            for (int tb = 0; tb < BM; ++tb) to[tb] = acc[ta][tb][r];
+                        }
+                    }
+                    __syncthreads();
+                    rows.run(buf, g.lr, g.mu, g.wd);
+                };
+                if constexpr (decltype(inside)::value)
+                    apply(InnerUpdate<64, T::TM, T::WAVES, 4, L, decltype(row_n)>(g.W, g.Mom, row_n, m0, M, wave, lane));
+                else
+                    apply(RowUpdate<64, T::TM, T::WAVES, BM == 2 ? 5 : 6, G, decltype(row_n)>(g.W, g.Mom, row_n, m0, N, M, wave, lane));
             }
-            __syncthreads();
-            rows.run(buf, g.lr, g.mu, g.wd);
+        };
+        if (G == 1 && n0 + T::TN <= N && m0 + T::TM <= M) {
+            if (M % 32 == 0 && ((reinterpret_cast<uintptr_t>(g.W) | reinterpret_cast<uintptr_t>(g.Mom)) & 127) == 0)
+                update(std::bool_constant<G == 1>{}, std::bool_constant<G == 1>{});
+            else
+                update(std::bool_constant<G == 1>{}, std::false_type{});
+        } else {
+            update(std::false_type{}, std::false_type{});
         }
     }
 }
 
-// Workgroups [0, big) own 128 x 128 tiles; the tiles after them are cut into (2 / BN) * (2 / BM) smaller ones.  big = 0:
-// small tiles only.
-template <int BN, int BM, bool PART, bool BLK>
+// Workgroup b owns tile b of (64*BN) x (64*BM).  MIXED: workgroups [0, big) own 128 x 128 tiles and the tiles after them are cut
+// into (2 / BN) * (2 / BM) smaller ones.
+template <int BN, int BM, bool MIXED, bool PART, bool BLK>
 __device__ __forceinline__ void grid_body(const Args& g, const BlockPtrs* blocks)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -260,10 +295,10 @@ __device__ __forceinline__ void grid_body(const Args& g, const BlockPtrs* blocks
     if constexpr (PART) {
         const int split = __builtin_amdgcn_readfirstlane(b / g.tiles), tile = b - split * g.tiles;   // (the division runs on the vector ALU)
         tile_body<BN, BM, 1, true, false>(g, nullptr, lds, int64_t(tile / g.tiles_m) * 64 * BN, int64_t(tile % g.tiles_m) * 64 * BM, split);
+    } else if constexpr (!MIXED) {
+        tile_body<BN, BM, 1, false, BLK>(g, blocks, lds, int64_t(b / g.tiles_m) * 64 * BN, int64_t(b % g.tiles_m) * 64 * BM, 0);
     } else if (b < g.big) {
         tile_body<2, 2, 1, false, BLK>(g, blocks, lds, int64_t(b / g.tiles_m) * 128, int64_t(b % g.tiles_m) * 128, 0);
-    } else if (g.big == 0) {
-        tile_body<BN, BM, 1, false, BLK>(g, blocks, lds, int64_t(b / g.tiles_m) * 64 * BN, int64_t(b % g.tiles_m) * 64 * BM, 0);
     } else {
         constexpr int PN = 2 / BN, PM = 2 / BM;
         const int i = b - g.big, tile = g.big + i / (PN * PM), sub = i % (PN * PM);
@@ -272,16 +307,18 @@ __device__ __forceinline__ void grid_body(const Args& g, const BlockPtrs* blocks
     }
 }
 
-template <int BN, int BM, bool PART>
-__global__ void __launch_bounds__(256) sfb_f32_kernel(const Args g)
+// Tiles of one size have a kernel of their own: three of 64 x 128 and five of 64 x 64 fit a compute unit then (with the 128 x 128
+// code beside them two, for its registers; 6000 -> 6000, K = 384: 265 against 272 us).
+template <int BN, int BM, bool MIXED, bool PART>
+__global__ void __launch_bounds__(256, MIXED ? 2 : BM == 2 ? 3 : 5) sfb_f32_kernel(const Args g)
 {
-    grid_body<BN, BM, PART, false>(g, nullptr);
+    grid_body<BN, BM, MIXED, PART, false>(g, nullptr);
 }
 
-template <int BN, int BM>
-__global__ void __launch_bounds__(256) sfb_f32_blocks_kernel(const Args g, const BlockPtrs blocks)
+template <int BN, int BM, bool MIXED>
+__global__ void __launch_bounds__(256, MIXED ? 2 : BM == 2 ? 3 : 5) sfb_f32_blocks_kernel(const Args g, const BlockPtrs blocks)
 {
-    grid_body<BN, BM, false, true>(g, &blocks);
+    grid_body<BN, BM, MIXED, false, true>(g, &blocks);
 }
 
 template <int BN, int BM, int G>
@@ -307,52 +344,51 @@ Cover uniform_cover(int64_t N, int64_t M, int bn, int bm)
     return {bn, bm, bn * bm == 4 ? tn * tm : 0, tm, tn * tm};
 }
 
-Cover choose_f32(int64_t N, int64_t M, int64_t K, double* units)
+Cover choose_f32(int64_t N, int64_t M, int64_t K, double* us)
 {
     const int forced = tune_value(PSD_TUNE_SFB_F32_TILE);
-    *units = 0;
+    *us = 0;
     if (forced == 1 || forced == 2) return uniform_cover(N, M, forced, 2);
-    // A compute unit works through its tiles at the rate of its MFMA pipe, so the launch takes as long as the compute unit
-    // with the most tile area: count in units of 128 x 128 tiles per compute unit, smaller tiles with what their shorter
-    // runs between barriers cost (64 x 128: 6 %, 64 x 64: 20 %), a lone 128 x 128 tile (one wavefront per SIMD) with 7 %.
-    // 3000 -> 3000, K = 2048: 576 tiles are 2.25 units in 2 rounds of 128 x 128 and one of 64 x 64: 404 -> 304 us.
+    // A compute unit works through its tiles at the rate of its MFMA pipe, so the launch takes as long as the compute unit with
+    // the most tile area: 57 us per 1024 rows and 128 x 128 tile, smaller tiles with what their shorter runs between barriers
+    // cost; what the loops of other tiles do not hide of the W / Mom update (12.5 us per 128 x 128 tile of a compute unit's
+    // share); and a start.  Fitted to eleven shapes of 2 to 36 M weights over K = 64 .. 2048, where the choice costs 0.7 %.
+    // 3000 -> 3000, K = 2048: 576 tiles are 2.25 rounds; two of 128 x 128 and the rest in 64 x 64: 358 -> 276 us.
     const int64_t cus = device_cu_count();
-    auto rounds = [&](int64_t workgroups, double unit) { return static_cast<double>((workgroups + cus - 1) / cus) * unit; };
+    auto rounds = [&](int64_t workgroups) { return static_cast<double>((workgroups + cus - 1) / cus); };
+    constexpr double kHalf = 0.507, kQuarter = 0.281;
+    const double round = 57 * static_cast<double>(K) / 1024, update = 12.5 * static_cast<double>(N) * M / 16384 / cus;
     const Cover half = uniform_cover(N, M, 1, 2), quarter = uniform_cover(N, M, 1, 1), all = uniform_cover(N, M, 2, 2);
-    Cover best = half;
-    double cost = rounds(half.groups, 0.53);
-    auto consider = [&](const Cover& c, double x) { if (x < cost) { cost = x; best = c; } };
-    consider(quarter, rounds(quarter.groups, 0.30));
-    // At most one 64 x 64 tile per compute unit: four groups of wavefronts contract it (1024 -> 1000: K = 2048 53 -> 45 us,
-    // K = 256 11.4 -> 11.0; two groups on a lone 128 x 128 tile are no faster than two 64 x 128 tiles).
+    // At most one 64 x 64 tile per compute unit: four groups of wavefronts contract it (1024 -> 1000, K = 2048: 42 -> 36 us;
+    // two groups on a lone 128 x 128 tile are no faster than two 64 x 128 tiles).
     if (quarter.groups <= cus) {
         Cover c = quarter;
         c.g = 4;
-        *units = 0.30;
+        *us = 4.5 + 0.267 * round + 0.7 * update;
         return c;
     }
-    // A short contraction is mostly W / Mom update, which three 64 x 128 tiles on a compute unit overlap better than two
-    // 128 x 128 ones (9216 -> 4096: K = 64 122 against 144 us, K = 256 201 / 225, K = 512 348 / 340).
-    const double big = K >= 512 ? 1.0 : 1.0 + 0.25 * static_cast<double>(512 - K) / 448;
+    Cover best = half;
+    *us = 6.6 + rounds(half.groups) * kHalf * round + 0.67 * update;
+    auto consider = [&](const Cover& c, double x) { if (x < *us) { *us = x; best = c; } };
+    consider(quarter, 5.8 + rounds(quarter.groups) * kQuarter * round + 0.7 * update);
+    consider(all, 8.5 + rounds(all.groups) * round + 0.7 * update);
     const int64_t full = all.big / cus, rem = all.big % cus;
-    consider(all, big * rounds(all.big, 1.0) * (all.big <= cus ? 1.07 : 1.0));
     if (full > 0 && rem > 0) {
-        consider({1, 2, full * cus, all.tiles_m, full * cus + 2 * rem}, big * full + rounds(2 * rem, 0.53));
-        consider({1, 1, full * cus, all.tiles_m, full * cus + 4 * rem}, big * full + rounds(4 * rem, 0.30));
+        consider({1, 2, full * cus, all.tiles_m, full * cus + 2 * rem}, 7.0 + (full + rounds(2 * rem) * kHalf) * round + 0.7 * update);
+        consider({1, 1, full * cus, all.tiles_m, full * cus + 4 * rem}, 9.4 + (full + rounds(4 * rem) * kQuarter) * round + 0.8 * update);
     }
-    *units = cost;
     return best;
 }
 
-template <int BN, int BM, bool PART>
+template <int BN, int BM, bool MIXED, bool PART>
 psd_status start(const Args& g, const BlockPtrs* blocks, int64_t groups, hipStream_t st)
 {
     if (groups < 1 || groups > 0x7fffffff) return PSD_E_INVALID;
-    const size_t lds = g.big > 0 ? Tile<2, 2, 1>::LDS_BYTES : Tile<BN, BM, 1>::LDS_BYTES;
+    const size_t lds = MIXED ? Tile<2, 2, 1>::LDS_BYTES : Tile<BN, BM, 1>::LDS_BYTES;
     const dim3 grid(static_cast<uint32_t>(groups));
-    if constexpr (PART) hipLaunchKernelGGL((sfb_f32_kernel<BN, BM, true>), grid, dim3(256), lds, st, g);
-    else if (blocks) hipLaunchKernelGGL((sfb_f32_blocks_kernel<BN, BM>), grid, dim3(256), lds, st, g, *blocks);
-    else hipLaunchKernelGGL((sfb_f32_kernel<BN, BM, false>), grid, dim3(256), lds, st, g);
+    if constexpr (PART) hipLaunchKernelGGL((sfb_f32_kernel<BN, BM, MIXED, true>), grid, dim3(256), lds, st, g);
+    else if (blocks) hipLaunchKernelGGL((sfb_f32_blocks_kernel<BN, BM, MIXED>), grid, dim3(256), lds, st, g, *blocks);
+    else hipLaunchKernelGGL((sfb_f32_kernel<BN, BM, MIXED, false>), grid, dim3(256), lds, st, g);
     PSD_HIP_TRY(hipGetLastError());
     return PSD_OK;
 }
@@ -389,13 +425,14 @@ Args common_args(int64_t ldu, int64_t ldv, float* W, float* Mom, int64_t N, int6
 
 psd_status launch_cover(Args& g, const BlockPtrs* blocks, hipStream_t st)
 {
-    double units;
-    const Cover c = choose_f32(g.N, g.M, g.K, &units);
+    double us;
+    const Cover c = choose_f32(g.N, g.M, g.K, &us);
     if (c.groups > 0x7fffffff) return PSD_E_INVALID;
     g.big = static_cast<int>(c.big);
     g.tiles_m = static_cast<int>(c.tiles_m);
     if (c.g == 4) return start_groups<1, 1, 4>(g, blocks, c.groups, st);
-    return c.bm == 2 ? start<1, 2, false>(g, blocks, c.groups, st) : start<1, 1, false>(g, blocks, c.groups, st);
+    if (c.big > 0) return c.bm == 2 ? start<1, 2, true, false>(g, blocks, c.groups, st) : start<1, 1, true, false>(g, blocks, c.groups, st);
+    return c.bm == 2 ? start<1, 2, false, false>(g, blocks, c.groups, st) : start<1, 1, false, false>(g, blocks, c.groups, st);
 }
 
 }  // namespace
@@ -419,21 +456,19 @@ psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t l
     Args g = common_args(ldu, ldv, W, Mom, N, M, K, lr, mu, wd);
     g.U = U; g.V = V;
     g.u_bytes = static_cast<uint32_t>(u_bytes); g.v_bytes = static_cast<uint32_t>(v_bytes);
-    // Split the sum over k where the shorter loops save more than storing and adding the partial sums costs: a unit is 63 us
-    // per 1024 rows, the second launch 4 us and its bytes.  512 -> 512, K = 2048: 47 us unsplit, 19 us in four;
-    // 1024 -> 1000 (a 64 x 64 tile for every compute unit), K = 2048: 51 and 49.5 us, K = 8192: 178 and 154 us.
+    // Split the sum over k where the shorter loops save more than storing and adding the partial sums costs: the second launch
+    // 4 us and its bytes.  512 -> 512, K = 2048: 34 us unsplit, 17 us in four.
     const Cover c = uniform_cover(N, M, 1, 1);
     const int64_t cus = device_cu_count();
-    double units;
-    choose_f32(N, M, K, &units);
+    double us;
+    choose_f32(N, M, K, &us);
     int splits = 1;
-    double cost = units * 63 * static_cast<double>(K) / 1024;
     for (int s = 2; s <= most_splits; ++s) {
         const int64_t groups = c.groups * s;
-        const double loop = groups <= cus ? 0.36 : static_cast<double>((groups + cus - 1) / cus) * 0.30;
-        const double x = loop * 63 * static_cast<double>(K) / s / 1024 + 4 + (16.0 + 4 * s) * N * M / 5e6;
-        if (x < cost || units == 0) {
-            cost = x;
+        const double loop = groups <= cus ? 0.32 : static_cast<double>((groups + cus - 1) / cus) * 0.281;
+        const double x = 5 + loop * 57 * static_cast<double>(K) / s / 1024 + 4 + (16.0 + 4 * s) * N * M / 5e6;
+        if (x < us || us == 0) {
+            us = x;
             splits = s;
         }
     }
@@ -442,7 +477,7 @@ psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t l
     g.tiles = static_cast<int>(c.groups);
     g.part = part; g.part_stride = sfb_part_stride(N, M);
     g.stages_per_split = static_cast<int>(((K + SLICE - 1) / SLICE + splits - 1) / splits);
-    const psd_status r = start<1, 1, true>(g, nullptr, c.groups * splits, st);
+    const psd_status r = start<1, 1, false, true>(g, nullptr, c.groups * splits, st);
     if (r != PSD_OK) return r;
     return launch_sfb_reduce(part, splits, N, M, W, Mom, lr, mu, wd, st);
 }

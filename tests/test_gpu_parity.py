@@ -296,6 +296,25 @@ def test_sfb_row_starts_at_every_place_of_a_cache_line(M, dtype):
             assert bool((f[:lead] == 77).all()) and bool((f[lead + n:] == 77).all())
 
 
+@pytest.mark.parametrize("tile", [None, 1, 2])        # 64 x 64 (324 tiles), 64 x 128, 128 x 128
+@pytest.mark.parametrize("M,B", [(1120, 5), (1101, 11), (1130, 22), (1036, 37), (1099, 48)])
+def test_sfb_f32_inner_tiles_bit_exact(M, B, tile, pinned_tile):
+    """Tiles inside W for rows on lines, on quads, on pairs and anywhere; 1 to 9 stages of the ring; misaligned W."""
+    if tile is not None:
+        pinned_tile(psd.TUNE_SFB_F32_TILE, tile)
+    d = inputs.fc_layer_integer(M, 1101, B=B, P=3, seed=M)
+    plan, U, ldu, V, ldv = run_pack(d, psd.F32)
+    Uo, Vo = orc.pack_factors(d["delta"], d["act"])
+    Wr, Mr = orc.sync_fc_sfb(Uo, Vo, d["W"], d["Mom"], 0.25, 0.5)
+    for lead in (0, 12):
+        W, Mom = (torch.empty(1101 * M + 64, device=DEV)[lead:lead + 1101 * M].view(1101, M) for _ in range(2))
+        W.copy_(dev(d["W"]))
+        Mom.copy_(dev(d["Mom"]))
+        psd.sync_fc_sfb(plan, psd.F32, U, ldu, V, ldv, W, Mom, 0.25, 0.5)
+        torch.cuda.synchronize()
+        assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr)
+
+
 @pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
 def test_weight_decay_bit_exact_on_both_routes(dtype):
     # wd, lr, mu powers of two and integer data: every intermediate is exact in fp32
