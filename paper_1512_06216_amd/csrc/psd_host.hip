@@ -309,31 +309,90 @@ psd_status fuse_event(hipEvent_t* out)
 }
 
 // may this layer's parameter-server sum share a launch with others that wait for the same event `ready`?
-// may this layer's parameter-server sum share a launch with others that wait for the same event `ready`?
-// Events that order the reconstruction kernels of one iteration one after the other (one per host thread
-// and position, created on first use, never destroyed).
-psd_status chain_event(int i, hipEvent_t* out)
-{
-    static thread_local hipEvent_t ev[2] = {nullptr, nullptr};
-    if (!ev[i & 1]) PSD_HIP_TRY(hipEventCreateWithFlags(&ev[i & 1], hipEventDisableTiming));
-    *out = ev[i & 1];
-    return PSD_OK;
-}
-
 bool fusable_ps_layer(const psd_layer_task& t, int32_t rule, const void* ready)
 {
     const int32_t route = rule == PSD_RULE_ALG3 ? t.plan.route_alg3 : t.plan.route_vs_dense;
     return route == PSD_ROUTE_PS_DENSE && t.ev_ready == ready && t.G && t.plan.P <= PSD_MAX_MULTI_WORKERS;
 }
 
+// The sums of layers [lo, hi] in ONE launch on the top one's stream; the other layers' streams are ordered after it.
+psd_status sync_ps_group(const psd_layer_task* layers, int32_t lo, int32_t hi, float lr, float mu, float wd)
+{
+    const psd_layer_task& t = layers[hi];
+    hipStream_t st = static_cast<hipStream_t>(t.stream);
+    if (t.ev_ready) PSD_HIP_TRY(hipStreamWaitEvent(st, static_cast<hipEvent_t>(t.ev_ready), 0));
+    psd_dense_segment segs[PSD_MAX_MULTI_SEGMENTS];
+    for (int32_t j = hi; j >= lo; --j) {
+        const psd_layer_task& u = layers[j];
+        uint64_t n;
+        if (mul_u64(static_cast<uint64_t>(u.plan.M), static_cast<uint64_t>(u.plan.N), &n) || n > (uint64_t(1) << 40))
+            return PSD_E_INVALID;
+        psd_dense_segment& sg = segs[hi - j];
+        sg.n = static_cast<int64_t>(n); sg.P = static_cast<int32_t>(u.plan.P); sg.S = u.S;
+        sg.G = u.G; sg.W = u.W; sg.Mom = u.Mom;
+        if (u.ev_begin) PSD_HIP_TRY(hipEventRecord(static_cast<hipEvent_t>(u.ev_begin), st));
+    }
+    const psd_status r = psd_sync_dense_ps_multi(hi - lo + 1, segs, lr, mu, wd, t.stream);
+    if (r != PSD_OK) return r;
+    hipEvent_t done = nullptr;
+    bool other_streams = false;
+    for (int32_t j = hi; j >= lo; --j) {
+        const psd_layer_task& u = layers[j];
+        if (u.ev_end) PSD_HIP_TRY(hipEventRecord(static_cast<hipEvent_t>(u.ev_end), st));
+        other_streams = other_streams || u.stream != t.stream;
+    }
+    if (other_streams) {
+        const psd_status e = fuse_event(&done);
+        if (e != PSD_OK) return e;
+        PSD_HIP_TRY(hipEventRecord(done, st));
+        for (int32_t j = hi - 1; j >= lo; --j)
+            if (layers[j].stream != t.stream)
+                PSD_HIP_TRY(hipStreamWaitEvent(static_cast<hipStream_t>(layers[j].stream), done, 0));
+    }
+    return PSD_OK;
+}
+
+// The lowest layer of a parameter-server group that is to be issued before the reconstructions above it, -1: none.  Only where
+// nothing tells them apart in time: one and the same readiness event (or none).  Beside three or more packs and bf16
+// reconstructions the sum's accesses and theirs hinder each other, and the group's waits end up behind the last
+// reconstruction; first and by itself it takes 20 us and they fill the chip afterwards (AlexNet, 8 x 256 samples: 470 -> 445 us a
+// step; 8 x 32: 289 -> 273).  One or two layers leave gaps that the sum fills (4096 -> 4096 alone: 185 us last, 203 first),
+// fp32 reconstructions leave HBM idle (1830 against 1860), and small layers end before the hand-over between streams does.
+int32_t group_to_issue_first(int32_t L, const psd_layer_task* layers, int32_t rule, int32_t* hi)
+{
+    constexpr int32_t kLayers = 3;
+    constexpr double kWeights = 25e6;              // 80 us of update
+    const void* ready = layers[L - 1].ev_ready;
+    int32_t l = L - 1;
+    double weights = 0;
+    for (; l >= 0; --l) {
+        const psd_layer_task& t = layers[l];
+        const int32_t route = rule == PSD_RULE_ALG3 ? t.plan.route_alg3 : t.plan.route_vs_dense;
+        if (t.ev_ready != ready || (route != PSD_ROUTE_SFB && route != PSD_ROUTE_SF_PS) || t.factor_dtype != PSD_BF16) break;
+        weights += static_cast<double>(t.plan.M) * static_cast<double>(t.plan.N);
+    }
+    if (L - 1 - l < kLayers || weights < kWeights) return -1;
+    int32_t lo = l + 1;
+    while (lo > 0 && l - lo + 2 <= PSD_MAX_MULTI_SEGMENTS && fusable_ps_layer(layers[lo - 1], rule, ready)) --lo;
+    if (lo >= l) return -1;
+    *hi = l;
+    return lo;
+}
+
 }  // namespace
 
 // Algorithm 2's order: the top layer's gradient exists first, so its synchronisation is
-// issued first; every layer goes to its own stream.
+// issued first; every layer goes to its own stream.  (Layers that share one readiness event may be reordered.)
 psd_status psd_sync_iteration(int32_t L, const psd_layer_task* layers, float lr, float mu, float wd, int32_t rule)
 {
     if (!layers) return PSD_E_NULL;
     if (L < 1 || (rule != PSD_RULE_ALG3 && rule != PSD_RULE_SFB_VS_DENSE)) return PSD_E_INVALID;
+    int32_t first_hi = -1;
+    const int32_t first_lo = group_to_issue_first(L, layers, rule, &first_hi);
+    if (first_lo >= 0) {
+        const psd_status r = sync_ps_group(layers, first_lo, first_hi, lr, mu, wd);
+        if (r != PSD_OK) return r;
+    }
     for (int32_t l = L - 1; l >= 0; --l) {
         const psd_layer_task& t = layers[l];
         const int32_t route = rule == PSD_RULE_ALG3 ? t.plan.route_alg3 : t.plan.route_vs_dense;
@@ -346,35 +405,8 @@ psd_status psd_sync_iteration(int32_t L, const psd_layer_task* layers, float lr,
         if (fusable_ps_layer(t, rule, t.ev_ready))
             while (lo > 0 && l - lo + 1 < PSD_MAX_MULTI_SEGMENTS && fusable_ps_layer(layers[lo - 1], rule, t.ev_ready)) --lo;
         if (lo < l) {
-            if (t.ev_ready) PSD_HIP_TRY(hipStreamWaitEvent(st, static_cast<hipEvent_t>(t.ev_ready), 0));
-            psd_dense_segment segs[PSD_MAX_MULTI_SEGMENTS];
-            for (int32_t j = l; j >= lo; --j) {
-                const psd_layer_task& u = layers[j];
-                uint64_t n;
-                if (mul_u64(static_cast<uint64_t>(u.plan.M), static_cast<uint64_t>(u.plan.N), &n) || n > (uint64_t(1) << 40))
-                    return PSD_E_INVALID;
-                psd_dense_segment& sg = segs[l - j];
-                sg.n = static_cast<int64_t>(n); sg.P = static_cast<int32_t>(u.plan.P); sg.S = u.S;
-                sg.G = u.G; sg.W = u.W; sg.Mom = u.Mom;
-                if (u.ev_begin) PSD_HIP_TRY(hipEventRecord(static_cast<hipEvent_t>(u.ev_begin), st));
-            }
-            const psd_status r = psd_sync_dense_ps_multi(l - lo + 1, segs, lr, mu, wd, t.stream);
+            const psd_status r = lo == first_lo ? PSD_OK : sync_ps_group(layers, lo, l, lr, mu, wd);
             if (r != PSD_OK) return r;
-            hipEvent_t done = nullptr;
-            bool other_streams = false;
-            for (int32_t j = l; j >= lo; --j) {
-                const psd_layer_task& u = layers[j];
-                if (u.ev_end) PSD_HIP_TRY(hipEventRecord(static_cast<hipEvent_t>(u.ev_end), st));
-                other_streams = other_streams || u.stream != t.stream;
-            }
-            if (other_streams) {
-                const psd_status e = fuse_event(&done);
-                if (e != PSD_OK) return e;
-                PSD_HIP_TRY(hipEventRecord(done, st));
-                for (int32_t j = l - 1; j >= lo; --j)
-                    if (layers[j].stream != t.stream)
-                        PSD_HIP_TRY(hipStreamWaitEvent(static_cast<hipStream_t>(layers[j].stream), done, 0));
-            }
             l = lo;               // the loop's --l moves below the group
             continue;
         }
