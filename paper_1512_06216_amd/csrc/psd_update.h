@@ -56,13 +56,17 @@ __host__ __device__ constexpr int row_stride(int width, int64_t M) { return widt
 // c < WIDTH; with PARTS > 1 there are that many buffers one after the other, whose sum is dW.
 // Every wavefront access covers one line of eight rows (8 lanes of 16 bytes each).  W and Mom of DEPTH such line groups
 // are requested by fetch<0>() before the rows are even written, and those of the next DEPTH before the present ones are
-// used.  Lines that lie inside the tile are streamed (see load_stream4), the ones it shares with its neighbours go
+// used.  The quad in which a row begins and the one in which it ends, where M is not a multiple of 4, are shared with the
+// neighbouring tiles: their elements, three at most at each end, are read and written one by one, by lane 4 * end + i of the
+// eight that stand for a row, so that no workgroup touches an element of another's (nor one past the end of W).
+// Lines that lie inside the tile are streamed (see load_stream4), the ones it shares with its neighbours go
 // through the caches, but for the stores of the narrow tiles of small layers: what lies dirty in L2 when a kernel ends has
 // to be written back before the next one starts, a microsecond that large layers do not notice.
 template <int ROWS, int WIDTH, int WAVES, int DEPTH, int PARTS, class RowN>
 struct RowUpdate {
     static constexpr int LINES = WIDTH / 32 + 1, GROUPS = ROWS / 8, ALL = GROUPS * LINES;       // units: one line of eight rows
     static constexpr int UNITS = (ALL + WAVES - 1) / WAVES, BATCHES = (UNITS + DEPTH - 1) / DEPTH;
+    static constexpr int ENDS = (GROUPS + WAVES - 1) / WAVES;                                   // a wavefront's groups of eight rows
     static_assert(ROWS % 8 == 0 && WIDTH % 32 == 0, "whole lines of eight rows");
     float* W;
     float* Mom;
@@ -70,6 +74,7 @@ struct RowUpdate {
     int64_t m0, N, M;
     int wave, lane, cols, stride;                  // cols: columns of the tile that exist
     float4 w[2][DEPTH], mo[2][DEPTH];
+    float w_end[ENDS], mo_end[ENDS];
 
     __device__ __forceinline__ RowUpdate(float* W_, float* Mom_, RowN row, int64_t m0_, int64_t N_, int64_t M_, int wave_, int lane_)
         : W(W_), Mom(Mom_), row_n(row), m0(m0_), N(N_), M(M_), wave(wave_), lane(lane_),
@@ -78,8 +83,8 @@ struct RowUpdate {
     }
     struct Place {
         int64_t off;                               // of this lane's quad in W
-        int at, c;                                 // ... in the row buffer; its first column
-        bool any, quad, whole_line;                // does the tile own some of it, all of it, all of its line
+        int at;                                    // ... in the row buffer
+        bool quad, whole_line;                     // does the tile own all of it, all of its line
     };
     __device__ __forceinline__ Place place(int u) const
     {
@@ -92,15 +97,28 @@ struct RowUpdate {
         const int q = 4 * (lane & 7);
         const int64_t n = row_n(r);
         const int first = 32 * line - line_shift(W, n, M);       // column of the line's first element
+        const int c = first + q;
         Place p;
-        p.c = first + q;
         p.at = r * stride + 32 * line + q;
-        p.off = n * M + m0 + p.c;
-        const bool mine = n < N && (WALK || id < ALL);
-        p.any = mine && p.c + 3 >= 0 && p.c < cols;
-        p.quad = mine && p.c >= 0 && p.c + 3 < cols;
+        p.off = n * M + m0 + c;
+        p.quad = n < N && (WALK || id < ALL) && c >= 0 && c + 3 < cols;
         p.whole_line = first >= 0 && first + 32 <= cols;
         return p;
+    }
+    struct End {
+        int64_t off;
+        int at;
+        bool any;
+    };
+    __device__ __forceinline__ End end(int e) const
+    {
+        const int group = wave + WAVES * e, r = group * 8 + (lane >> 3), i = lane & 3;
+        const int64_t n = row_n(r);
+        const int shift = line_shift(W, n, M), before = -shift & 3;
+        const int lead = before < cols ? before : cols;          // columns before the first whole quad
+        const int last = ((cols + shift) & ~3) - shift;          // column where the quad begins that the tile owns in part
+        const int c = lane & 4 ? (last > lead ? last : lead) + i : i;
+        return {n * M + m0 + c, r * stride + shift + c, n < N && group < GROUPS && c < (lane & 4 ? cols : lead)};
     }
     template <int B>
     __device__ __forceinline__ void fetch()
@@ -109,15 +127,22 @@ struct RowUpdate {
         for (int j = 0; j < DEPTH; ++j) {
             if (B * DEPTH + j >= UNITS) continue;
             const Place p = place(B * DEPTH + j);
-            // A quad that the tile shares with a neighbour (M not a multiple of 4) is loaded whole like any other, the neighbour's
-            // elements for nothing; an aligned 16-byte piece with an element of W in it lies in one page with that element.
-            if (!p.any) continue;
+            if (!p.quad) continue;
             if (p.whole_line) {
                 w[B & 1][j] = load_stream4(W + p.off);
                 mo[B & 1][j] = load_stream4(Mom + p.off);
             } else {
                 w[B & 1][j] = *reinterpret_cast<const float4*>(W + p.off);
                 mo[B & 1][j] = *reinterpret_cast<const float4*>(Mom + p.off);
+            }
+        }
+        if (B == 0 && M % 4 != 0) {
+#pragma unroll
+            for (int e = 0; e < ENDS; ++e) {
+                const End p = end(e);
+                if (!p.any) continue;
+                w_end[e] = W[p.off];
+                mo_end[e] = Mom[p.off];
             }
         }
     }
@@ -130,7 +155,7 @@ struct RowUpdate {
             for (int j = 0; j < DEPTH; ++j) {
                 if (B * DEPTH + j >= UNITS) continue;
                 const Place p = place(B * DEPTH + j);
-                if (!p.any) continue;
+                if (!p.quad) continue;
                 float4 d = *reinterpret_cast<const float4*>(buf + p.at);
 #pragma unroll
                 for (int i = 1; i < PARTS; ++i) {
@@ -142,45 +167,48 @@ struct RowUpdate {
                 upd(d.y, wv.y, mv.y, lr, mu, wd);
                 upd(d.z, wv.z, mv.z, lr, mu, wd);
                 upd(d.w, wv.w, mv.w, lr, mu, wd);
-                if (p.quad) {
-                    if (WIDTH < 128 || p.whole_line) {
-                        store_stream4(Mom + p.off, mv);
-                        store_stream4(W + p.off, wv);
-                    } else {
-                        *reinterpret_cast<float4*>(Mom + p.off) = mv;
-                        *reinterpret_cast<float4*>(W + p.off) = wv;
-                    }
-                } else {                           // only the tile's own elements are stored
-                    const float we[4] = {wv.x, wv.y, wv.z, wv.w}, me[4] = {mv.x, mv.y, mv.z, mv.w};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (p.c + i >= 0 && p.c + i < cols) {
-                            Mom[p.off + i] = me[i];
-                            W[p.off + i] = we[i];
-                        }
+                if (WIDTH < 128 || p.whole_line) {
+                    store_stream4(Mom + p.off, mv);
+                    store_stream4(W + p.off, wv);
+                } else {
+                    *reinterpret_cast<float4*>(Mom + p.off) = mv;
+                    *reinterpret_cast<float4*>(W + p.off) = wv;
                 }
             }
             run<B + 1>(buf, lr, mu, wd);
+        } else if (M % 4 != 0) {
+#pragma unroll
+            for (int e = 0; e < ENDS; ++e) {
+                const End p = end(e);
+                if (!p.any) continue;
+                float d = buf[p.at];
+#pragma unroll
+                for (int i = 1; i < PARTS; ++i) d += buf[i * ROWS * stride + p.at];
+                upd(d, w_end[e], mo_end[e], lr, mu, wd);
+                Mom[p.off] = mo_end[e];
+                W[p.off] = w_end[e];
+            }
         }
     }
 };
 
 // The same for a tile that lies inside W, with most of the vector instructions gone (the fp32 MFMA pipe runs no faster than
 // they leave it time: 9216 -> 4096, K = 512, 384 -> 312 us).  Only the first and the last line of a row are shared with other
-// tiles, and the lanes that own quads of the one own none of the other, so that one access takes both.  The quad in which a
-// row of a length that is no multiple of 4 begins, and the one in which it ends, are left over: those of all rows of a
-// wavefront make one more access.  ON_LINES: rows of W and Mom start on lines (no shift at all).
+// tiles, and the lanes that own quads of the one own none of the other, so that one access takes both.  The elements of a row
+// before its first whole quad and behind its last are taken one by one, as in RowUpdate.  ON_LINES: rows of W and Mom start on
+// lines (no shift at all).
 template <int ROWS, int WIDTH, int WAVES, int DEPTH, bool ON_LINES, class RowN>
 struct InnerUpdate {
     static constexpr int LINES = WIDTH / 32, GROUPS = ROWS / 8 / WAVES;       // a wavefront's groups of eight rows
     static constexpr int UNITS = GROUPS * LINES, BATCHES = (UNITS + DEPTH - 1) / DEPTH;
-    static_assert(ROWS % (8 * WAVES) == 0 && WIDTH % 32 == 0 && GROUPS * 16 <= 64, "whole lines of eight rows, their ends in one access");
+    static_assert(ROWS % (8 * WAVES) == 0 && WIDTH % 32 == 0, "whole lines of eight rows");
     float* W;
     float* Mom;
     RowN row_n;
     int64_t m0, M;
     int wave, lane, stride;
-    float4 w[2][DEPTH], mo[2][DEPTH], w_end, mo_end;
+    float4 w[2][DEPTH], mo[2][DEPTH];
+    float w_end[GROUPS], mo_end[GROUPS];
 
     __device__ __forceinline__ InnerUpdate(float* W_, float* Mom_, RowN row, int64_t m0_, int64_t M_, int wave_, int lane_)
         : W(W_), Mom(Mom_), row_n(row), m0(m0_), M(M_), wave(wave_), lane(lane_), stride(row_stride(WIDTH, ON_LINES ? 0 : M_))
@@ -209,14 +237,15 @@ struct InnerUpdate {
     }
     struct End {
         int64_t off;
-        int at, from, to;                          // elements [from, to) of the quad are the tile's
+        int at;
+        bool any;
     };
-    __device__ __forceinline__ End end() const
+    __device__ __forceinline__ End end(int e) const
     {
-        const int k = lane >> 1, last = lane & 1, r = (wave + WAVES * (k >> 3)) * 8 + (k & 7);
+        const int r = (wave + WAVES * e) * 8 + (lane >> 3), i = lane & 3;
         const int64_t n = row_n(r);
-        const int shift = line_shift(W, n, M), q = shift & ~3, cut = k < 8 * GROUPS ? shift & 3 : 0;
-        return {n * M + m0 + q - shift + last * WIDTH, r * stride + q + last * WIDTH, cut == 0 || last ? 0 : cut, cut == 0 ? 0 : last ? cut : 4};
+        const int shift = line_shift(W, n, M), behind = shift & 3, c = lane & 4 ? WIDTH - behind + i : i;
+        return {n * M + m0 + c, r * stride + shift + c, i < (lane & 4 ? behind : -shift & 3)};
     }
     template <int B>
     __device__ __forceinline__ void fetch()
@@ -235,10 +264,12 @@ struct InnerUpdate {
             }
         }
         if (!ON_LINES && B == 0 && M % 4 != 0) {
-            const End e = end();                   // loaded whole, as in RowUpdate
-            if (e.to > e.from) {
-                w_end = *reinterpret_cast<const float4*>(W + e.off);
-                mo_end = *reinterpret_cast<const float4*>(Mom + e.off);
+#pragma unroll
+            for (int e = 0; e < GROUPS; ++e) {
+                const End p = end(e);
+                if (!p.any) continue;
+                w_end[e] = W[p.off];
+                mo_end[e] = Mom[p.off];
             }
         }
     }
@@ -273,16 +304,13 @@ struct InnerUpdate {
             }
             run<B + 1>(buf, lr, mu, wd);
         } else if (!ON_LINES && M % 4 != 0) {
-            const End e = end();
-            if (e.to > e.from) {
-                update(buf, e.at, w_end, mo_end, lr, mu, wd);
-                const float we[4] = {w_end.x, w_end.y, w_end.z, w_end.w}, me[4] = {mo_end.x, mo_end.y, mo_end.z, mo_end.w};
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (i >= e.from && i < e.to) {
-                        Mom[e.off + i] = me[i];
-                        W[e.off + i] = we[i];
-                    }
+            for (int e = 0; e < GROUPS; ++e) {
+                const End p = end(e);
+                if (!p.any) continue;
+                upd(buf[p.at], w_end[e], mo_end[e], lr, mu, wd);
+                Mom[p.off] = mo_end[e];
+                W[p.off] = w_end[e];
             }
         }
     }

@@ -1,0 +1,136 @@
+// The update classes of csrc/psd_update.h run on the CPU, lane after lane, under the address sanitizer.  W and Mom end where
+// their allocation ends, and while a tile is updated everything that is not the tile's own is poisoned: a read or write of a
+// neighbour's element or past the end stops the program.  (The sanitizer keeps 8-byte granules: an element before a tile that
+// starts in the middle of one goes unseen, one behind a tile never does.)  The results are compared with the plain update.
+#define __fmaf_rn __builtin_fmaf
+#include <sanitizer/asan_interface.h>
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+#include "psd_update.h"
+
+namespace {
+
+const float kLr = 0.25f, kMu = 0.5f, kWd = 0.5f;
+float dw_of(int64_t n, int64_t m) { return static_cast<float>((n * 31 + m * 7) % 61 - 30); }
+
+struct Array {                                    // `lead` elements into an aligned allocation; what lies behind the data stays poisoned
+    int64_t lead, count;
+    size_t bytes;
+    float* base;
+    Array(int64_t lead_, int64_t count_)
+        : lead(lead_), count(count_), bytes((static_cast<size_t>(lead_ + count_) * 4 + 127) / 128 * 128),
+          base(static_cast<float*>(std::aligned_alloc(128, bytes)))
+    {
+        hide();
+        show();
+    }
+    ~Array()
+    {
+        ASAN_UNPOISON_MEMORY_REGION(base, bytes);
+        std::free(base);
+    }
+    float* data() const { return base + lead; }
+    void hide() const { ASAN_POISON_MEMORY_REGION(base, bytes); }
+    void show() const { ASAN_UNPOISON_MEMORY_REGION(data(), count * 4); }
+};
+
+// the rows of W behind the rows of the buffer, as the kernels deal them out
+struct RowOf {
+    int64_t n0;
+    int bn, step;
+    bool pairs;                                   // rows of the wavefronts' blocks interleaved (fp32) or one block after the other (bf16)
+    int64_t operator()(int r) const { return n0 + (r >> 5) * 32 * bn + (pairs ? bn * (r & 31) + step : 32 * step + (r & 31)); }
+};
+
+template <template <class> class Make, int ROWS, int WIDTH, int WAVES, int PARTS, int BN, bool PAIRS, bool INNER>
+bool layer(int64_t N, int64_t M, int64_t lead, const char* name)
+{
+    std::printf("%s: N %lld, M %lld, lead %lld\n", name, static_cast<long long>(N), static_cast<long long>(M), static_cast<long long>(lead));
+    std::fflush(stdout);
+    Array W(lead, N * M), Mom(lead, N * M);
+    auto w0 = [](int64_t i) { return static_cast<float>(i % 17 - 8); };
+    auto m0_of = [](int64_t i) { return static_cast<float>(i % 5 - 2); };
+    for (int64_t i = 0; i < N * M; ++i) {
+        W.data()[i] = w0(i);
+        Mom.data()[i] = m0_of(i);
+    }
+    using Update = typename Make<RowOf>::type;
+    for (int64_t n0 = 0; n0 < N; n0 += ROWS * BN)
+        for (int64_t m0 = 0; m0 < M; m0 += WIDTH) {
+            if (INNER && (n0 + ROWS * BN > N || m0 + WIDTH > M)) continue;
+            W.hide();
+            Mom.hide();
+            const int64_t cols = M - m0 < WIDTH ? M - m0 : WIDTH;
+            for (int64_t n = n0; n < n0 + ROWS * BN && n < N; ++n) {
+                ASAN_UNPOISON_MEMORY_REGION(W.data() + n * M + m0, cols * 4);
+                ASAN_UNPOISON_MEMORY_REGION(Mom.data() + n * M + m0, cols * 4);
+            }
+            for (int step = 0; step < BN; ++step) {
+                const RowOf row_n{n0, BN, step, PAIRS};
+                std::vector<Update> lanes;
+                for (int wave = 0; wave < WAVES; ++wave)
+                    for (int lane = 0; lane < 64; ++lane) {
+                        if constexpr (INNER) lanes.emplace_back(W.data(), Mom.data(), row_n, m0, M, wave, lane);
+                        else lanes.emplace_back(W.data(), Mom.data(), row_n, m0, N, M, wave, lane);
+                        lanes.back().template fetch<0>();
+                    }
+                const int stride = lanes[0].stride;
+                std::vector<float> buf(static_cast<size_t>(PARTS) * ROWS * stride);
+                for (int p = 0; p < PARTS; ++p)
+                    for (int r = 0; r < ROWS; ++r)
+                        for (int c = 0; c < WIDTH; ++c)
+                            buf[(p * ROWS + r) * stride + c + psd::line_shift(W.data(), row_n(r), M)] =
+                                p == 0 ? dw_of(row_n(r), m0 + c) - (PARTS - 1) : 1.0f;
+                for (Update& u : lanes) u.run(buf.data(), kLr, kMu, kWd);
+            }
+            W.show();
+            Mom.show();
+        }
+    const int64_t n_end = INNER ? N / (ROWS * BN) * (ROWS * BN) : N, m_end = INNER ? M / WIDTH * WIDTH : M;
+    for (int64_t n = 0; n < N; ++n)
+        for (int64_t m = 0; m < M; ++m) {
+            const int64_t i = n * M + m;
+            float w = w0(i), mo = m0_of(i);
+            if (n < n_end && m < m_end) psd::upd(dw_of(n, m), w, mo, kLr, kMu, kWd);
+            if (W.data()[i] != w || Mom.data()[i] != mo) {
+                std::printf("wrong at n %lld, m %lld\n", static_cast<long long>(n), static_cast<long long>(m));
+                return false;
+            }
+        }
+    return true;
+}
+
+// the instantiations of the kernels: rows, width, wavefronts, depth, parts / on lines
+template <class R> struct F32Edge128 { using type = psd::RowUpdate<64, 128, 4, 5, 1, R>; };
+template <class R> struct F32Edge64 { using type = psd::RowUpdate<64, 64, 4, 6, 1, R>; };
+template <class R> struct F32Groups { using type = psd::RowUpdate<64, 64, 16, 6, 4, R>; };
+template <class R> struct Bf16w256 { using type = psd::RowUpdate<64, 256, 4, 4, 1, R>; };
+template <class R> struct Bf16w192 { using type = psd::RowUpdate<64, 192, 4, 5, 1, R>; };
+template <class R> struct Bf16Two { using type = psd::RowUpdate<64, 128, 8, 5, 2, R>; };
+template <class R> struct Inner128 { using type = psd::InnerUpdate<64, 128, 4, 4, false, R>; };
+template <class R> struct Inner64 { using type = psd::InnerUpdate<64, 64, 4, 4, false, R>; };
+template <class R> struct InnerLines { using type = psd::InnerUpdate<64, 128, 4, 4, true, R>; };
+
+}  // namespace
+
+int main()
+{
+    bool ok = true;
+    for (int64_t lead : {0, 4, 12})
+        for (int64_t M : {1, 2, 3, 5, 31, 33, 64, 65, 126, 129, 131, 193, 257, 258, 260, 387}) {
+            for (int64_t N : {1, 70, 133}) {
+                ok = ok && layer<F32Edge128, 64, 128, 4, 1, 2, true, false>(N, M, lead, "fp32, edges, 128 x 128");
+                ok = ok && layer<F32Edge64, 64, 64, 4, 1, 1, true, false>(N, M, lead, "fp32, edges, 64 x 64");
+                ok = ok && layer<F32Groups, 64, 64, 16, 4, 1, true, false>(N, M, lead, "fp32, four groups, 64 x 64");
+                ok = ok && layer<Bf16w256, 64, 256, 4, 1, 2, false, false>(N, M, lead, "bf16, 128 x 256");
+                ok = ok && layer<Bf16w192, 64, 192, 4, 1, 2, false, false>(N, M, lead, "bf16, 128 x 192");
+                ok = ok && layer<Bf16Two, 64, 128, 8, 2, 2, false, false>(N, M, lead, "bf16, two groups, 128 x 128");
+            }
+            ok = ok && layer<Inner128, 64, 128, 4, 1, 2, true, true>(133, M, lead, "fp32, inside, 128 x 128");
+            ok = ok && layer<Inner64, 64, 64, 4, 1, 1, true, true>(133, M, lead, "fp32, inside, 64 x 64");
+        }
+    ok = ok && layer<InnerLines, 64, 128, 4, 1, 1, true, true>(130, 288, 0, "fp32, inside, on lines");
+    std::printf(ok ? "all right\n" : "failed\n");
+    return ok ? 0 : 1;
+}
