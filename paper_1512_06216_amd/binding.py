@@ -154,8 +154,10 @@ def _native():
                                "g.build()'`; there is no fallback path" % EXT_PATH)
         loader = importlib.machinery.ExtensionFileLoader("_psdpy", EXT_PATH)
         spec = importlib.util.spec_from_file_location("_psdpy", EXT_PATH, loader=loader)
-        _ext = importlib.util.module_from_spec(spec)
-        loader.exec_module(_ext)
+        ext = importlib.util.module_from_spec(spec)
+        loader.exec_module(ext)
+        ext.bind(Plan, SspState, DenseSegment, LayerTask, ctypes.c_void_p)
+        _ext = ext
     return _ext
 
 

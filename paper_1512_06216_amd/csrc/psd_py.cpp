@@ -3,8 +3,8 @@
 // Why it exists: a data-parallel worker hands over 2P block pointers per layer and step.  Checking and collecting
 // them in Python took 9-15 us per call, several times what the smaller kernels run for, so the GPU waited for the
 // host (1024 -> 1000 layer, B = 32, P = 8: 42 us per pass for 19 us of kernels).  Here the same checks cost about
-// 20 ns per tensor.  Everything that is not marshalling stays in the library; errors are raised with the same types
-// and texts as ever.
+// 20 ns per tensor.  Everything that is not marshalling stays in the library.  A tensor that does not fit is a ValueError, an
+// argument of the wrong kind (a structure above all) a TypeError.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <c10/hip/HIPStream.h>
@@ -15,14 +15,40 @@
 
 namespace {
 
+// The binding's ctypes classes, handed over by bind() when it loads this module, and kept for good.
+struct Classes { PyObject *plan, *ssp_state, *segment, *task, *void_p; } classes;
+
 // A ctypes structure or array, looked at through the buffer protocol for the length of one call.
 struct View {
     Py_buffer b{};
     bool held = false;
-    bool open(PyObject* o) { return held = PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) == 0; }
     template <class T> T* as() const { return static_cast<T*>(b.buf); }
     ~View() { if (held) PyBuffer_Release(&b); }
+
+    bool open(PyObject* o, int flags) { return held = PyObject_GetBuffer(o, &b, flags) == 0; }
+    // an instance of a structure class
+    bool open_struct(PyObject* o, PyObject* type, size_t bytes, const char* what, int flags = PyBUF_SIMPLE)
+    {
+        if (!type || !PyObject_TypeCheck(o, reinterpret_cast<PyTypeObject*>(type))) return refuse(o, what);
+        return open(o, flags) && (b.len >= static_cast<Py_ssize_t>(bytes) || refuse(o, what));
+    }
+    // an array of at least `count` elements of a class
+    bool open_array(PyObject* o, PyObject* type, int64_t count, size_t bytes, const char* what)
+    {
+        PyObject* element = PyObject_GetAttrString(reinterpret_cast<PyObject*>(Py_TYPE(o)), "_type_");
+        PyErr_Clear();
+        Py_XDECREF(element);                       // (borrowed from the type from here on)
+        if (!element || element != type) return refuse(o, what);
+        return open(o, PyBUF_SIMPLE) && (b.len / static_cast<int64_t>(bytes) >= count || refuse(o, what));
+    }
+    bool refuse(PyObject* o, const char* what)
+    {
+        PyErr_Format(PyExc_TypeError, "%s expected, not %s", what, Py_TYPE(o)->tp_name);
+        return false;
+    }
 };
+
+bool plan_of(PyObject* o, View& v) { return v.open_struct(o, classes.plan, sizeof(psd_plan), "a Plan"); }
 
 bool type_ok(c10::ScalarType t, long factor_dtype)
 {
@@ -160,7 +186,7 @@ PyObject* pack_factors(PyObject*, PyObject* const* a, Py_ssize_t n)
     View pv;
     Blocks b;
     void* st;
-    if (!arity(n, 9) || !pv.open(a[0])) return nullptr;
+    if (!arity(n, 9) || !plan_of(a[0], pv)) return nullptr;
     const psd_plan& plan = *pv.as<psd_plan>();
     if (!blocks_of(a[1], a[2], plan, PSD_F32, plan.B * plan.N, plan.B * plan.M, "delta", "act", &b)) return nullptr;
     const long dt = PyLong_AsLong(a[3]);
@@ -179,7 +205,7 @@ PyObject* sync_fc_sfb(PyObject*, PyObject* const* a, Py_ssize_t n)
     View pv;
     void *st, *ws = nullptr;
     size_t ws_bytes = 0;
-    if (!arity(n, 13) || !pv.open(a[0])) return nullptr;
+    if (!arity(n, 13) || !plan_of(a[0], pv)) return nullptr;
     const psd_plan& plan = *pv.as<psd_plan>();
     const long dt = PyLong_AsLong(a[1]);
     const int64_t ldu = as_i64(a[3]), ldv = as_i64(a[5]), K = plan.P * plan.B;
@@ -205,7 +231,7 @@ PyObject* sync_fc_sfb_blocks(PyObject*, PyObject* const* a, Py_ssize_t n)
     View pv;
     Blocks b;
     void* st;
-    if (!arity(n, 12) || !pv.open(a[0])) return nullptr;
+    if (!arity(n, 12) || !plan_of(a[0], pv)) return nullptr;
     const psd_plan& plan = *pv.as<psd_plan>();
     const long dt = PyLong_AsLong(a[1]);
     const int64_t ldu = as_i64(a[3]), ldv = as_i64(a[5]);
@@ -223,7 +249,7 @@ PyObject* sync_fc_bias(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     View pv;
     void* st;
-    if (!arity(n, 10) || !pv.open(a[0])) return nullptr;
+    if (!arity(n, 10) || !plan_of(a[0], pv)) return nullptr;
     const psd_plan& plan = *pv.as<psd_plan>();
     const long dt = PyLong_AsLong(a[1]);
     const int64_t ldu = as_i64(a[3]);
@@ -262,8 +288,9 @@ PyObject* sync_dense_ps_multi(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     View sv;
     void* st;
-    if (!arity(n, 6) || !sv.open(a[1])) return nullptr;
+    if (!arity(n, 6)) return nullptr;
     const long L = PyLong_AsLong(a[0]);
+    if (PyErr_Occurred() || !sv.open_array(a[1], classes.segment, L, sizeof(psd_dense_segment), "an array of L DenseSegments")) return nullptr;
     const float lr = as_f32(a[2]), mu = as_f32(a[3]), wd = as_f32(a[4]);
     if (PyErr_Occurred() || !stream_of(a[5], &st)) return nullptr;
     return call([&] { return psd_sync_dense_ps_multi(static_cast<int32_t>(L), sv.as<psd_dense_segment>(), lr, mu, wd, st); });
@@ -273,8 +300,9 @@ PyObject* sync_dense_ps_multi(PyObject*, PyObject* const* a, Py_ssize_t n)
 PyObject* sync_iteration(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     View tv;
-    if (!arity(n, 6) || !tv.open(a[1])) return nullptr;
+    if (!arity(n, 6)) return nullptr;
     const long L = PyLong_AsLong(a[0]), rule = PyLong_AsLong(a[5]);
+    if (PyErr_Occurred() || !tv.open_array(a[1], classes.task, L, sizeof(psd_layer_task), "an array of L LayerTasks")) return nullptr;
     const float lr = as_f32(a[2]), mu = as_f32(a[3]), wd = as_f32(a[4]);
     if (PyErr_Occurred()) return nullptr;
     return call([&] { return psd_sync_iteration(static_cast<int32_t>(L), tv.as<psd_layer_task>(), lr, mu, wd, static_cast<int32_t>(rule)); });
@@ -287,8 +315,14 @@ PyObject* ssp_clock_fc(PyObject*, PyObject* const* a, Py_ssize_t n)
     Blocks b;
     void *st, *ws;
     size_t ws_bytes;
-    if (!arity(n, 16) || !sv.open(a[0]) || !pv.open(a[1]) || !uv.open(a[5]) || !vv.open(a[7])) return nullptr;
+    if (!arity(n, 16) || !sv.open_struct(a[0], classes.ssp_state, sizeof(psd_ssp_state), "an SspState", PyBUF_WRITABLE) ||
+        !plan_of(a[1], pv))
+        return nullptr;
     const psd_plan& plan = *pv.as<psd_plan>();
+    const int64_t ring = int64_t(sv.as<psd_ssp_state>()->s) + 1;
+    if (!uv.open_array(a[5], classes.void_p, ring, sizeof(void*), "an array of s + 1 pointers") ||
+        !vv.open_array(a[7], classes.void_p, ring, sizeof(void*), "an array of s + 1 pointers"))
+        return nullptr;
     const long dt = PyLong_AsLong(a[2]);
     const int64_t ldu = as_i64(a[6]), ldv = as_i64(a[8]);
     const float lr = as_f32(a[11]), mu = as_f32(a[12]), wd = as_f32(a[13]);
@@ -315,7 +349,7 @@ PyObject* ssp_clock_fc(PyObject*, PyObject* const* a, Py_ssize_t n)
 PyObject* fill_pointers(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     View tv;
-    if (!arity(n, 5) || !tv.open(a[0])) return nullptr;
+    if (!arity(n, 5) || !tv.open(a[0], PyBUF_WRITABLE)) return nullptr;
     const long dt = PyLong_AsLong(a[2]);
     const int64_t least = as_i64(a[3]);
     const char* what = PyUnicode_AsUTF8(a[4]);
@@ -338,6 +372,23 @@ PyObject* pointer(PyObject*, PyObject* const* a, Py_ssize_t n)
     return dev_ptr(a[0], dt, least, what, &p) ? PyLong_FromVoidPtr(p) : nullptr;
 }
 
+// Plan, SspState, DenseSegment, LayerTask, c_void_p
+PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    if (!arity(n, 5)) return nullptr;
+    for (Py_ssize_t i = 0; i < n; ++i)
+        if (!PyType_Check(a[i])) {
+            PyErr_SetString(PyExc_TypeError, "classes expected");
+            return nullptr;
+        }
+    PyObject** to[] = {&classes.plan, &classes.ssp_state, &classes.segment, &classes.task, &classes.void_p};
+    for (Py_ssize_t i = 0; i < n; ++i) {
+        Py_INCREF(a[i]);
+        Py_XSETREF(*to[i], a[i]);
+    }
+    Py_RETURN_NONE;
+}
+
 template <PyObject* (*F)(PyObject*, PyObject* const*, Py_ssize_t)>
 PyObject* guarded(PyObject* self, PyObject* const* a, Py_ssize_t n)
 {
@@ -352,7 +403,7 @@ PyObject* guarded(PyObject* self, PyObject* const* a, Py_ssize_t n)
 #define PSD_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(&guarded<f>)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {PSD_METHOD(pack_factors), PSD_METHOD(sync_fc_sfb), PSD_METHOD(sync_fc_sfb_blocks), PSD_METHOD(sync_fc_bias),
                          PSD_METHOD(sync_dense_ps), PSD_METHOD(sync_dense_ps_multi), PSD_METHOD(sync_iteration),
-                         PSD_METHOD(ssp_clock_fc), PSD_METHOD(fill_pointers), PSD_METHOD(pointer), {nullptr, nullptr, 0, nullptr}};
+                         PSD_METHOD(ssp_clock_fc), PSD_METHOD(fill_pointers), PSD_METHOD(pointer), PSD_METHOD(bind), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_psdpy", "argument marshalling of libpsd.so", -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
