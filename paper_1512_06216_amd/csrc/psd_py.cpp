@@ -90,22 +90,31 @@ bool dev_ptr(PyObject* o, long factor_dtype, int64_t min_elems, const char* what
     return true;
 }
 
-// Pointers of a sequence of tensors: all are checked and counted, the first `room` are stored (the library refuses
-// longer lists by their count); false with an exception set if one does not fit.
-bool dev_ptrs(PyObject* seq, long factor_dtype, int64_t min_elems, const char* what, const void** out, Py_ssize_t room, Py_ssize_t* count)
-{
-    PyObject* fast = PySequence_Fast(seq, "a sequence of tensors is needed");
-    if (!fast) return false;
-    *count = PySequence_Fast_GET_SIZE(fast);
-    bool ok = true;
-    for (Py_ssize_t i = 0; ok && i < *count; ++i) {
-        const void* p = nullptr;
-        ok = dev_ptr(PySequence_Fast_GET_ITEM(fast, i), factor_dtype, min_elems, what, &p, i);
-        if (ok && i < room) out[i] = p;
+// A sequence of tensors, held until the library has been called: a caller's sequence may make its tensors as it is read.
+class Tensors {
+    PyObject* held = nullptr;
+
+public:
+    Tensors() = default;
+    Tensors(const Tensors&) = delete;
+    ~Tensors() { Py_XDECREF(held); }
+    Py_ssize_t count() const { return PyTuple_GET_SIZE(held); }
+
+    // All are checked, the pointers of the first `room` are stored (the library refuses longer lists by their count); false
+    // with an exception set if one does not fit.
+    bool take(PyObject* seq, long factor_dtype, int64_t min_elems, const char* what, const void** out, Py_ssize_t room)
+    {
+        if (PyObject_Size(seq) < 0) return false;        // an iterator is no sequence
+        held = PySequence_Tuple(seq);
+        if (!held) return false;
+        for (Py_ssize_t i = 0; i < count(); ++i) {
+            const void* p = nullptr;
+            if (!dev_ptr(PyTuple_GET_ITEM(held, i), factor_dtype, min_elems, what, &p, i)) return false;
+            if (i < room) out[i] = p;
+        }
+        return true;
     }
-    Py_DECREF(fast);
-    return ok;
-}
+};
 
 // None: the current stream of the current device; an int: a raw handle; else an object with .cuda_stream
 bool stream_of(PyObject* o, void** out)
@@ -160,23 +169,34 @@ PyObject* call(F f)
     return PyLong_FromLong(r);
 }
 
+bool need_P_blocks()
+{
+    PyErr_SetString(PyExc_ValueError, "need P per-worker blocks");
+    return false;
+}
+
+// the P error and P activation blocks of a layer: `eu`, `ev` elements each at least
 struct Blocks {
     const void* u[PSD_MAX_WORKERS];
     const void* v[PSD_MAX_WORKERS];
-};
+    Tensors tu, tv;
 
-// the P error and P activation blocks of a layer: `eu`, `ev` elements each at least
-bool blocks_of(PyObject* us, PyObject* vs, const psd_plan& plan, long dtype, int64_t eu, int64_t ev, const char* nu, const char* nv, Blocks* b)
-{
-    const Py_ssize_t n = PyObject_Length(us), m = PyObject_Length(vs);
-    if (n < 0 || m < 0) return false;
-    if (n != plan.P || m != plan.P) {
-        PyErr_SetString(PyExc_ValueError, "need P per-worker blocks");
-        return false;
+    bool take_u(PyObject* us, const psd_plan& plan, long dtype, int64_t eu, const char* name)
+    {
+        return tu.take(us, dtype, eu, name, u, PSD_MAX_WORKERS) && (tu.count() == plan.P || need_P_blocks());
     }
-    Py_ssize_t c;
-    return dev_ptrs(us, dtype, eu, nu, b->u, PSD_MAX_WORKERS, &c) && dev_ptrs(vs, dtype, ev, nv, b->v, PSD_MAX_WORKERS, &c);
-}
+    bool take_v(PyObject* vs, const psd_plan& plan, long dtype, int64_t ev, const char* name)
+    {
+        return tv.take(vs, dtype, ev, name, v, PSD_MAX_WORKERS) && (tv.count() == plan.P || need_P_blocks());
+    }
+    bool take(PyObject* us, PyObject* vs, const psd_plan& plan, long dtype, int64_t eu, int64_t ev, const char* nu, const char* nv)
+    {
+        const Py_ssize_t n = PyObject_Size(us), m = n < 0 ? n : PyObject_Size(vs);
+        if (n < 0 || m < 0) return false;
+        if (n != plan.P || m != plan.P) return need_P_blocks();
+        return take_u(us, plan, dtype, eu, nu) && take_v(vs, plan, dtype, ev, nv);
+    }
+};
 
 const float* const* f32s(const void* const* p) { return reinterpret_cast<const float* const*>(p); }
 
@@ -188,7 +208,7 @@ PyObject* pack_factors(PyObject*, PyObject* const* a, Py_ssize_t n)
     void* st;
     if (!arity(n, 9) || !plan_of(a[0], pv)) return nullptr;
     const psd_plan& plan = *pv.as<psd_plan>();
-    if (!blocks_of(a[1], a[2], plan, PSD_F32, plan.B * plan.N, plan.B * plan.M, "delta", "act", &b)) return nullptr;
+    if (!b.take(a[1], a[2], plan, PSD_F32, plan.B * plan.N, plan.B * plan.M, "delta", "act")) return nullptr;
     const long dt = PyLong_AsLong(a[3]);
     const int64_t ldu = as_i64(a[5]), ldv = as_i64(a[7]);
     if (PyErr_Occurred()) return nullptr;
@@ -236,7 +256,7 @@ PyObject* sync_fc_sfb_blocks(PyObject*, PyObject* const* a, Py_ssize_t n)
     const long dt = PyLong_AsLong(a[1]);
     const int64_t ldu = as_i64(a[3]), ldv = as_i64(a[5]);
     const float lr = as_f32(a[8]), mu = as_f32(a[9]), wd = as_f32(a[10]);
-    if (PyErr_Occurred() || !blocks_of(a[2], a[4], plan, dt, plan.B * ldu, plan.B * ldv, "U_blocks", "V_blocks", &b)) return nullptr;
+    if (PyErr_Occurred() || !b.take(a[2], a[4], plan, dt, plan.B * ldu, plan.B * ldv, "U_blocks", "V_blocks")) return nullptr;
     float *W, *Mom;
     if (!dev_ptr(a[6], PSD_F32, plan.N * plan.M, "W", &W) ||
         !dev_ptr(a[7], PSD_F32, plan.N * plan.M, "Mom", &Mom) || !stream_of(a[11], &st))
@@ -267,9 +287,9 @@ PyObject* sync_fc_bias(PyObject*, PyObject* const* a, Py_ssize_t n)
 PyObject* sync_dense_ps(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     const void* g[PSD_MAX_WORKERS];
-    Py_ssize_t P;
+    Tensors G;
     void* st;
-    if (!arity(n, 8)) return nullptr;
+    if (!arity(n, 8) || PyObject_Size(a[0]) < 0) return nullptr;
     const float lr = as_f32(a[3]), mu = as_f32(a[4]), wd = as_f32(a[5]);
     const long S = PyLong_AsLong(a[6]);
     if (PyErr_Occurred()) return nullptr;
@@ -277,10 +297,10 @@ PyObject* sync_dense_ps(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (!dev_ptr(a[1], PSD_F32, 0, "W", &W)) return nullptr;
     const int64_t keys = THPVariable_Unpack(a[1]).numel();
     float* Mom;
-    if (!dev_ptrs(a[0], PSD_F32, keys, "G", g, PSD_MAX_WORKERS, &P) ||
+    if (!G.take(a[0], PSD_F32, keys, "G", g, PSD_MAX_WORKERS) ||
         !dev_ptr(a[2], PSD_F32, keys, "Mom", &Mom) || !stream_of(a[7], &st))
         return nullptr;
-    return call([&] { return psd_sync_dense_ps(keys, static_cast<int32_t>(P), f32s(g), W, Mom, lr, mu, wd, static_cast<int32_t>(S), st); });
+    return call([&] { return psd_sync_dense_ps(keys, static_cast<int32_t>(G.count()), f32s(g), W, Mom, lr, mu, wd, static_cast<int32_t>(S), st); });
 }
 
 // L, segments, lr, mu, wd, stream
@@ -327,13 +347,9 @@ PyObject* ssp_clock_fc(PyObject*, PyObject* const* a, Py_ssize_t n)
     const int64_t ldu = as_i64(a[6]), ldv = as_i64(a[8]);
     const float lr = as_f32(a[11]), mu = as_f32(a[12]), wd = as_f32(a[13]);
     if (PyErr_Occurred()) return nullptr;
-    Py_ssize_t c;
     const bool du = a[3] != Py_None, dv = a[4] != Py_None;
-    if ((du && !dev_ptrs(a[3], PSD_F32, plan.B * plan.N, "delta", b.u, PSD_MAX_WORKERS, &c)) || (du && c != plan.P) ||
-        (dv && !dev_ptrs(a[4], PSD_F32, plan.B * plan.M, "act", b.v, PSD_MAX_WORKERS, &c)) || (dv && c != plan.P)) {
-        if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "need P per-worker blocks");
+    if ((du && !b.take_u(a[3], plan, PSD_F32, plan.B * plan.N, "delta")) || (dv && !b.take_v(a[4], plan, PSD_F32, plan.B * plan.M, "act")))
         return nullptr;
-    }
     float *W, *Mom;
     if (!dev_ptr(a[9], PSD_F32, plan.N * plan.M, "W", &W) ||
         !dev_ptr(a[10], PSD_F32, plan.N * plan.M, "Mom", &Mom) || !workspace_of(a[14], &ws, &ws_bytes) ||
@@ -353,9 +369,8 @@ PyObject* fill_pointers(PyObject*, PyObject* const* a, Py_ssize_t n)
     const long dt = PyLong_AsLong(a[2]);
     const int64_t least = as_i64(a[3]);
     const char* what = PyUnicode_AsUTF8(a[4]);
-    Py_ssize_t c;
-    if (PyErr_Occurred() || !what ||
-        !dev_ptrs(a[1], dt, least, what, tv.as<const void*>(), tv.b.len / static_cast<Py_ssize_t>(sizeof(void*)), &c))
+    Tensors t;
+    if (PyErr_Occurred() || !what || !t.take(a[1], dt, least, what, tv.as<const void*>(), tv.b.len / static_cast<Py_ssize_t>(sizeof(void*))))
         return nullptr;
     Py_RETURN_NONE;
 }
