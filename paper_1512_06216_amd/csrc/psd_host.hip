@@ -43,7 +43,7 @@ bool valid_plan_sizes(const psd_plan* p)
 {
     return p->M >= 1 && p->N >= 1 && p->B >= 1 && p->P >= 1 && p->P <= PSD_MAX_WORKERS &&
            p->M < (int64_t(1) << 31) && p->N < (int64_t(1) << 31) &&
-           p->B * p->P < (int64_t(1) << 31);
+           p->B < (int64_t(1) << 31) && p->B * p->P < (int64_t(1) << 31);      // (the product cannot wrap)
 }
 
 bool valid_ld(int64_t ld, int64_t cols, int32_t dtype)

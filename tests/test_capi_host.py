@@ -303,3 +303,20 @@ def test_blocks_in_place_support_rule_and_argument_checks():
     assert call(ctypes.byref(plan), pp, pp, W, Mom) == psd.E_INVALID
     ptrs[1] = ctypes.cast(None, ctypes.POINTER(ctypes.c_float))
     assert call(ctypes.byref(plan), pp, pp, W, Mom) == psd.E_NULL
+
+
+def test_a_batch_whose_product_with_the_workers_wraps_is_refused():
+    """psd_plan_layer returns no such plan, but the structure is the caller's to fill: 64 workers of 2^58 samples are 2^64."""
+    L = psd.lib()
+    plan = psd.Plan(M=64, N=32, B=2 ** 58, P=64, kind=psd.LAYER_FC)
+    fake = lambda i: ctypes.c_void_p(0x10000000 + 0x100000 * i)
+    ptrs = (ctypes.POINTER(ctypes.c_float) * 64)(*[ctypes.cast(0x20000000, ctypes.POINTER(ctypes.c_float))] * 64)
+    pp = ctypes.cast(ptrs, ctypes.POINTER(ctypes.POINTER(ctypes.c_float)))
+    for dtype in (psd.F32, psd.BF16):
+        assert L.psd_sfb_blocks_supported(ctypes.byref(plan), dtype, 32, 64) == 0
+        assert L.psd_sfb_workspace_bytes(ctypes.byref(plan), dtype) == 0
+        args = (fake(2), fake(3), 0.1, 0.9, 0.0)
+        assert L.psd_sync_fc_sfb_blocks(ctypes.byref(plan), dtype, pp, 32, pp, 64, *args, None) == psd.E_INVALID
+        assert L.psd_sync_fc_sfb(ctypes.byref(plan), dtype, fake(0), 32, fake(1), 64, *args, None, 0, None) == psd.E_INVALID
+        assert L.psd_sync_fc_bias(ctypes.byref(plan), dtype, fake(0), 32, *args, None) == psd.E_INVALID
+    assert L.psd_pack_factors(ctypes.byref(plan), pp, pp, psd.F32, fake(0), 32, fake(1), 64, None) == psd.E_INVALID
