@@ -16,19 +16,6 @@
 
 namespace psd {
 
-// One float4 of every array per lane: with two, a workgroup's loads wait for each other's registers.  Small launches take
-// small workgroups (more of them to deal out), large ones large ones (longer contiguous pieces of each of the P + 2 arrays).
-// us at P = 8, with two float4 per lane of 256 -> now: 100 K keys 4.9 -> 4.0, 2.3 M 21.2 -> 20.2 (256 lanes; 512: 20.5,
-// 1024: 23.2), 16.8 M 123.2 -> 120.4 (512; 256: 125.0, 1024: 124.3), 37.7 M 314.8 -> 306.9 (1024; 512: 310.1, 256: 334.9).
-int32_t dense_threads_for(int64_t keys) { return keys < 4000000 ? 256 : keys < 19000000 ? 512 : 1024; }
-
-int32_t dense_chunks_for(int64_t n, int32_t S, int32_t threads)
-{
-    const int64_t longest = (n + S - 1) / S;   // floor((s+1)n/S) - floor(sn/S) <= ceil(n/S)
-    const int64_t chunk = int64_t(threads) * 4;
-    return static_cast<int32_t>((longest + chunk - 1) / chunk);
-}
-
 namespace {
 
 // 16-byte streaming load: the gradient copies are read exactly once
@@ -165,11 +152,11 @@ __device__ __forceinline__ void dense_block(const float* const* G, int P, float*
 }
 
 template <int THREADS>
-__global__ void __launch_bounds__(THREADS) dense_ps_table_kernel(const DenseTable t, float lr, float mu, float wd)
+__global__ void __launch_bounds__(THREADS) dense_ps_table_kernel(const DenseTable t, int first, float lr, float mu, float wd)
 {
     // which layer does this workgroup belong to (at most 16 segments: linear scan)
     int l = 0;
-    const int b = blockIdx.x;
+    const int b = first + blockIdx.x;
     for (int j = 1; j < t.L; ++j)
         if (b >= t.seg[j].block_begin) l = j;
     const DenseSeg& sg = t.seg[l];
@@ -177,9 +164,23 @@ __global__ void __launch_bounds__(THREADS) dense_ps_table_kernel(const DenseTabl
 }
 
 template <int THREADS>
-__global__ void __launch_bounds__(THREADS) dense_ps_wide_kernel(const DenseWide a, float lr, float mu, float wd)
+__global__ void __launch_bounds__(THREADS) dense_ps_wide_kernel(const DenseWide a, int first, float lr, float mu, float wd)
 {
-    dense_block(a.G, a.P, a.W, a.Mom, a.q, a.r, a.S, a.chunks, blockIdx.x, lr, mu, wd);
+    dense_block(a.G, a.P, a.W, a.Mom, a.q, a.r, a.S, a.chunks, first + blockIdx.x, lr, mu, wd);
+}
+
+// `blocks` workgroups, in as many launches as it takes (one but for millions of short shards)
+template <class Args>
+psd_status launch_blocks(void (*kern)(Args, int, float, float, float), const Args& a, int threads, int64_t blocks, float lr, float mu,
+                         float wd, hipStream_t st)
+{
+    const int64_t most = kMaxItems / threads;
+    for (int64_t first = 0; first < blocks; first += most) {
+        const int64_t n = blocks - first < most ? blocks - first : most;
+        hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(n)), dim3(threads), 0, st, a, static_cast<int>(first), lr, mu, wd);
+        PSD_HIP_TRY(hipGetLastError());
+    }
+    return PSD_OK;
 }
 
 }  // namespace
@@ -187,21 +188,17 @@ __global__ void __launch_bounds__(THREADS) dense_ps_wide_kernel(const DenseWide 
 psd_status launch_dense_table(const DenseTable& t, int32_t total_blocks, float lr, float mu, float wd, hipStream_t st)
 {
     auto kern = t.threads == 256 ? dense_ps_table_kernel<256> : t.threads == 512 ? dense_ps_table_kernel<512> : dense_ps_table_kernel<1024>;
-    hipLaunchKernelGGL(kern, dim3(total_blocks), dim3(t.threads), 0, st, t, lr, mu, wd);
-    PSD_HIP_TRY(hipGetLastError());
-    return PSD_OK;
+    return launch_blocks<DenseTable>(kern, t, t.threads, total_blocks, lr, mu, wd, st);
 }
 
 psd_status launch_dense_wide(DenseWide& a, float lr, float mu, float wd, hipStream_t st)
 {
-    const int threads = dense_threads_for(a.n);
+    const int threads = dense_threads_for(a.n, a.S);
     a.chunks = dense_chunks_for(a.n, a.S, threads);
     const int64_t blocks = int64_t(a.chunks) * a.S;
     if (blocks < 1 || blocks > (int64_t(1) << 30)) return PSD_E_INVALID;
     auto kern = threads == 256 ? dense_ps_wide_kernel<256> : threads == 512 ? dense_ps_wide_kernel<512> : dense_ps_wide_kernel<1024>;
-    hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(blocks)), dim3(threads), 0, st, a, lr, mu, wd);
-    PSD_HIP_TRY(hipGetLastError());
-    return PSD_OK;
+    return launch_blocks<DenseWide>(kern, a, threads, blocks, lr, mu, wd, st);
 }
 
 // Second stage of a split reconstruction: the `splits` partial dW matrices are exactly "several dense

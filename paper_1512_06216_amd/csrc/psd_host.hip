@@ -273,10 +273,14 @@ psd_status psd_sync_dense_ps_multi(int32_t L, const psd_dense_segment* segs, flo
     if (!segs) return PSD_E_NULL;
     if (L < 1 || L > PSD_MAX_MULTI_SEGMENTS || !(wd >= 0.0f)) return PSD_E_INVALID;
     DenseTable t;
-    int64_t blocks = 0, keys = 0;
+    int64_t blocks = 0, keys = 0, shards = 0;
     int32_t used = 0;
-    for (int32_t l = 0; l < L; ++l) keys += segs[l].n > 0 && segs[l].n < (int64_t(1) << 40) ? segs[l].n : 0;
-    t.threads = dense_threads_for(keys);
+    for (int32_t l = 0; l < L; ++l) {
+        if (segs[l].n < 1 || segs[l].n >= (int64_t(1) << 40) || segs[l].S < 1) continue;      // empty, or refused below
+        keys += segs[l].n;
+        shards += segs[l].S;
+    }
+    t.threads = dense_threads_for(keys, shards > 0 ? shards : 1);
     for (int32_t l = 0; l < L; ++l) {
         const psd_dense_segment& s = segs[l];
         psd_status r = check_dense(s.n, s.P, PSD_MAX_MULTI_WORKERS, s.G, s.W, s.Mom, s.S);

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "psd.h"
+#include "psd_rules.h"
 
 namespace psd {
 
@@ -51,8 +52,6 @@ struct DenseWide {          // single layer, up to PSD_MAX_WORKERS copies
 };
 psd_status launch_dense_table(const DenseTable& t, int32_t total_blocks, float lr, float mu, float wd, hipStream_t st);
 psd_status launch_dense_wide(DenseWide& a, float lr, float mu, float wd, hipStream_t st);
-int32_t dense_threads_for(int64_t keys);          // lanes per workgroup of a launch over this many keys
-int32_t dense_chunks_for(int64_t n, int32_t S, int32_t threads);   // workgroups per shard
 
 struct FastDiv { uint32_t d, mul, shift1, shift2; };   // division by d, see psd_pack.hip
 struct PackSide {            // one of the two stacked matrices of a layer

@@ -1,0 +1,33 @@
+// The rules by which the host shapes a launch: integer arithmetic and fitted costs, no HIP (not installed).
+#pragma once
+#include <stdint.h>
+
+namespace psd {
+
+// HIP counts the work items of a launch in 32 bits.
+constexpr int64_t kMaxItems = (int64_t(1) << 32) - 1;
+
+// ---- parameter-server sum: one float4 of every array per lane
+// Lanes per workgroup of a launch over `keys` keys in `shards` shards.  One float4 per lane: with two, a workgroup's loads wait
+// for each other's registers.  Small launches take small workgroups (more of them to deal out), large ones large ones (longer
+// contiguous pieces of each of the P + 2 arrays).
+// us at P = 8, with two float4 per lane of 256 -> now: 100 K keys 4.9 -> 4.0, 2.3 M 21.2 -> 20.2 (256 lanes; 512: 20.5,
+// 1024: 23.2), 16.8 M 123.2 -> 120.4 (512; 256: 125.0, 1024: 124.3), 37.7 M 314.8 -> 306.9 (1024; 512: 310.1, 256: 334.9).
+// A workgroup serves one shard, so it is never larger than a shard of average length has work for: 20 M keys in 200 000
+// shards 1027 us with 1024 lanes, 222 with 256 (in 20 000 shards, 1000 keys each, 166 and 171).
+inline int32_t dense_threads_for(int64_t keys, int64_t shards)
+{
+    int32_t threads = keys < 4000000 ? 256 : keys < 19000000 ? 512 : 1024;
+    while (threads > 256 && keys / shards < int64_t(threads) * 4) threads /= 2;
+    return threads;
+}
+
+// workgroups per shard
+inline int32_t dense_chunks_for(int64_t n, int32_t S, int32_t threads)
+{
+    const int64_t longest = (n + S - 1) / S;   // floor((s+1)n/S) - floor(sn/S) <= ceil(n/S)
+    const int64_t chunk = int64_t(threads) * 4;
+    return static_cast<int32_t>((longest + chunk - 1) / chunk);
+}
+
+}  // namespace psd

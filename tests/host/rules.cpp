@@ -1,0 +1,8 @@
+// C entry points over csrc/psd_rules.h for tests/test_rules.py.
+#include "psd_rules.h"
+
+extern "C" {
+int64_t max_items() { return psd::kMaxItems; }
+int32_t dense_threads(int64_t keys, int64_t shards) { return psd::dense_threads_for(keys, shards); }
+int32_t dense_chunks(int64_t n, int32_t S, int32_t threads) { return psd::dense_chunks_for(n, S, threads); }
+}

@@ -456,6 +456,25 @@ def test_dense_largest_workgroups_bit_exact():
     assert np.array_equal(W.cpu().numpy(), Wr) and np.array_equal(Mom.cpu().numpy(), Mr)
 
 
+@pytest.mark.parametrize("n,S", [(20_000_000, 5_000_000),        # four keys a shard
+                                 (17_000_003, 17_000_003)])      # one key a shard: more workgroups than one launch takes
+def test_dense_millions_of_short_shards_bit_exact(n, S):
+    d = inputs.dense_layer_integer(n, 2, seed=S % 1000)
+    Wr, Mr = orc.sync_dense_ps(d["G"], d["W"], d["Mom"], 0.125, 0.5, 1)       # (sharding never changes a value)
+    G = [dev(g) for g in d["G"]]
+    W, Mom = dev(d["W"]), dev(d["Mom"])
+    psd.sync_dense_ps(G, W, Mom, 0.125, 0.5, S)
+    torch.cuda.synchronize()
+    assert np.array_equal(W.cpu().numpy(), Wr) and np.array_equal(Mom.cpu().numpy(), Mr)
+    s = inputs.dense_layer_integer(5003, 2, seed=6)                          # ... and as the first of two layers in one call
+    Ws, Ms = orc.sync_dense_ps(s["G"], s["W"], s["Mom"], 0.125, 0.5, 3)
+    W, Mom, W2, Mom2 = dev(d["W"]), dev(d["Mom"]), dev(s["W"]), dev(s["Mom"])
+    psd.sync_dense_ps_multi([(G, W, Mom, S), ([dev(g) for g in s["G"]], W2, Mom2, 3)], 0.125, 0.5)
+    torch.cuda.synchronize()
+    assert np.array_equal(W.cpu().numpy(), Wr) and np.array_equal(Mom.cpu().numpy(), Mr)
+    assert np.array_equal(W2.cpu().numpy(), Ws) and np.array_equal(Mom2.cpu().numpy(), Ms)
+
+
 def test_dense_random_sizes_bit_exact():
     rng = np.random.default_rng(77)
     for _ in range(24):

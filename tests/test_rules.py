@@ -1,0 +1,42 @@
+"""The host's rules for shaping launches (csrc/psd_rules.h), compiled for the CPU: whole ranges, without running a kernel."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+from paper_1512_06216_amd import build
+from tests.conftest import ROOT
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("rules") / "rules.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-shared", "-fPIC", "-I", build.CSRC, "-I", os.path.join(ROOT, "include"),
+                    os.path.join(ROOT, "tests", "host", "rules.cpp"), "-o", so], check=True)
+    L = ctypes.CDLL(so)
+    i32, i64 = ctypes.c_int32, ctypes.c_int64
+    for name, res, args in (("max_items", i64, []), ("dense_threads", i32, [i64, i64]), ("dense_chunks", i32, [i64, i32, i32])):
+        getattr(L, name).restype, getattr(L, name).argtypes = res, args
+    return L
+
+
+def test_dense_workgroups_are_no_larger_than_a_shard_has_work_for(rules):
+    for n in (1, 4096, 3999999, 4000000, 18999999, 19000000, 20000000, 37748736, 60000000, 1 << 34):
+        for S in (1, 2, 8, 61, 1000, 4000, 5000, 9000, 20000, 100000, 5000000, 20000000):
+            if S > n:
+                continue
+            t = rules.dense_threads(n, S)
+            assert t in (256, 512, 1024)
+            assert t == 256 or n // S >= 4 * t, (n, S, t)
+            if n // S >= 4096:                                  # long shards: by the number of keys alone
+                assert t == (256 if n < 4000000 else 512 if n < 19000000 else 1024)
+            c = rules.dense_chunks(n, S, t)
+            assert c * t * 4 >= -(-n // S) > (c - 1) * t * 4
+
+
+def test_dense_launches_of_short_shards_that_fit_one_launch_with_256_lanes_still_do(rules):
+    """20 M keys in 5 M shards: 5 M workgroups are 1.3e9 work items with 256 lanes, more than a launch can hold with 1024."""
+    n, S = 20000000, 5000000
+    t = rules.dense_threads(n, S)
+    assert S * rules.dense_chunks(n, S, t) * t <= rules.max_items() < 2 ** 32
