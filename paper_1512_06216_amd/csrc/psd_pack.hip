@@ -104,8 +104,7 @@ psd_status launch_pack(PackArgs& a, int32_t out_dtype, hipStream_t st)
     a.u.chunks = fast_div(static_cast<uint32_t>(cu));
     a.v.chunks = fast_div(static_cast<uint32_t>(cv));
     a.block = fast_div(static_cast<uint32_t>(a.B));
-    // 32-bit chunk numbers: a longer stack takes several launches
-    const int64_t most = (int64_t(1) << 31) / (cu > cv ? cu : cv);
+    const int64_t most = pack_rows_per_launch(cu, cv);
     for (int64_t row0 = 0; row0 < K; row0 += most) {
         a.row0 = static_cast<uint32_t>(row0);
         a.rows = static_cast<uint32_t>(K - row0 < most ? K - row0 : most);

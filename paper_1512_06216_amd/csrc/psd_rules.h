@@ -30,4 +30,9 @@ inline int32_t dense_chunks_for(int64_t n, int32_t S, int32_t threads)
     return static_cast<int32_t>((longest + chunk - 1) / chunk);
 }
 
+// ---- pack
+// Rows of one launch over rows of `cu` and `cv` 16-byte chunks: one lane per chunk of both matrices, and chunk numbers that fit
+// 31 bits with room to spare for the last, partly filled workgroups.  A longer stack takes several launches.
+inline int64_t pack_rows_per_launch(int64_t cu, int64_t cv) { return (int64_t(1) << 31) / (cu + cv); }
+
 }  // namespace psd

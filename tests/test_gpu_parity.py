@@ -93,6 +93,24 @@ def test_pack_workgroups_across_rows_and_blocks(M, N, B, P, dtype):
     assert not Ug[:, N:].any() and not Vg[:, M:].any()
 
 
+def test_pack_stack_longer_than_one_launch():
+    """2^30 + 64 rows of one chunk in each matrix (34 GB stacked; the workers share one block of each kind)."""
+    B, P = (1 << 24) + 1, 64
+    plan = psd.plan_layer(psd.LAYER_FC, 8, 5, B, P)
+    delta = torch.arange(B * 5, device=DEV, dtype=torch.int32).remainder_(251).float().view(B, 5)
+    act = torch.arange(B * 8, device=DEV, dtype=torch.int32).remainder_(241).float().view(B, 8)
+    U = torch.empty(plan.K, 8, dtype=torch.bfloat16, device=DEV)
+    V = torch.empty(plan.K, 8, dtype=torch.bfloat16, device=DEV)
+    U.view(torch.int16).fill_(0x7fc1)
+    V.view(torch.int16).fill_(0x7fc1)
+    psd.pack_factors(plan, [delta] * P, [act] * P, psd.BF16, U, 8, V, 8)
+    want_u, want_v = torch.nn.functional.pad(delta, (0, 3)).bfloat16(), act.bfloat16()     # (small whole numbers: exact)
+    for p in range(P):
+        assert torch.equal(U[p * B:(p + 1) * B], want_u) and torch.equal(V[p * B:(p + 1) * B], want_v), p
+    del U, V
+    torch.cuda.empty_cache()
+
+
 def test_pack_maximum_worker_count():
     d = inputs.fc_layer(40, 24, 1, 64, seed=64)                  # P = 64 workers, one sample each
     for dtype, name in ((psd.F32, "f32"), (psd.BF16, "bf16")):

@@ -16,7 +16,8 @@ def rules(tmp_path_factory):
                     os.path.join(ROOT, "tests", "host", "rules.cpp"), "-o", so], check=True)
     L = ctypes.CDLL(so)
     i32, i64 = ctypes.c_int32, ctypes.c_int64
-    for name, res, args in (("max_items", i64, []), ("dense_threads", i32, [i64, i64]), ("dense_chunks", i32, [i64, i32, i32])):
+    for name, res, args in (("max_items", i64, []), ("dense_threads", i32, [i64, i64]), ("dense_chunks", i32, [i64, i32, i32]),
+                            ("pack_rows", i64, [i64, i64])):
         getattr(L, name).restype, getattr(L, name).argtypes = res, args
     return L
 
@@ -40,3 +41,14 @@ def test_dense_launches_of_short_shards_that_fit_one_launch_with_256_lanes_still
     n, S = 20000000, 5000000
     t = rules.dense_threads(n, S)
     assert S * rules.dense_chunks(n, S, t) * t <= rules.max_items() < 2 ** 32
+
+
+def test_pack_launches_hold_both_matrices(rules):
+    """Workgroups of 256 lanes, one 16-byte chunk each, for the two matrices together."""
+    widths = [1, 2, 3, 16, 250, 1152, 2731, 65536, 1 << 20, (1 << 28) - 1, 1 << 28, (1 << 29) - 1]
+    for cu in widths:                                          # (a leading dimension stays below 2^31: at most 2^29 chunks)
+        for cv in widths:
+            rows = rules.pack_rows(cu, cv)
+            groups = -(-rows * cu // 256) + -(-rows * cv // 256)
+            assert rows >= 1 and groups * 256 <= rules.max_items(), (cu, cv)
+            assert rows * max(cu, cv) + 255 < 2 ** 32          # chunk numbers of the last workgroup
