@@ -30,6 +30,19 @@ inline int32_t dense_chunks_for(int64_t n, int32_t S, int32_t threads)
     return static_cast<int32_t>((longest + chunk - 1) / chunk);
 }
 
+// ---- reconstruction
+// Is every offset into the two stacked matrices (K rows of ldu and ldv elements of `bytes` bytes) below 2^32, with
+// `reserve` rows kept free behind the last one and the columns by which a tile may overhang?
+inline bool factors_in_reach(int64_t K, int64_t ldu, int64_t ldv, int64_t bytes, int64_t reserve)
+{
+    const int64_t ld = ldu > ldv ? ldu : ldv;
+    return K * ld <= ((int64_t(1) << 32) - 4096) / bytes - reserve * ld;      // K, ld < 2^31
+}
+
+// The fp32 kernels advance the descriptor and read no further ahead than its end: what has to fit 32 bits besides the matrix is
+// one stage, 64 rows where four groups contract a tile.  96 rows is what the kernels of all tile sizes have always been given.
+constexpr int64_t kF32Reserve = 96;
+
 // ---- pack
 // Rows of one launch over rows of `cu` and `cv` 16-byte chunks: one lane per chunk of both matrices, and chunk numbers that fit
 // 31 bits with room to spare for the last, partly filled workgroups.  A longer stack takes several launches.

@@ -81,6 +81,7 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
     static_assert(!(PART && G > 1), "a split of K over workgroups is not combined with groups");
     using T = Tile<BN, BM, G>;
     constexpr int KT = T::KT;
+    static_assert(KT <= kF32Reserve, "a stage lies within the reach of 32-bit offsets");
     constexpr int LPS = T::NI_A + T::NI_B;
     const int N = g.N, M = g.M;
     const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
@@ -449,10 +450,8 @@ psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t l
                           int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int most_splits,
                           hipStream_t st)
 {
-    // 32-bit byte offsets into each factor matrix, with room for the stages of read-ahead
+    if (!factors_in_reach(K, ldu, ldv, 4, kF32Reserve)) return PSD_E_UNSUPPORTED;
     const int64_t u_bytes = K * ldu * 4, v_bytes = K * ldv * 4;
-    const int64_t reach = (int64_t(1) << 32) - (NSTAGE + 2) * 4 * SLICE * (ldu > ldv ? ldu : ldv) * 4 - 4096;
-    if (u_bytes > reach || v_bytes > reach) return PSD_E_UNSUPPORTED;
     Args g = common_args(ldu, ldv, W, Mom, N, M, K, lr, mu, wd);
     g.U = U; g.V = V;
     g.u_bytes = static_cast<uint32_t>(u_bytes); g.v_bytes = static_cast<uint32_t>(v_bytes);

@@ -423,6 +423,29 @@ def test_sfb_workspace_is_ignored_by_layers_that_fill_the_gpu():
     assert torch.isnan(spare).all()                              # untouched
 
 
+def _wide_rows_layer(dtype, ldu, K, P):
+    """A 64 -> 64 layer whose stacked errors have rows of ldu elements."""
+    d = inputs.fc_layer_integer(64, 64, K // P, P, seed=K % 1000, amax=2)
+    plan = psd.plan_layer(psd.LAYER_FC, 64, 64, K // P, P)
+    td = torch.float32 if dtype == psd.F32 else torch.bfloat16
+    U, V = torch.empty(plan.K, ldu, dtype=td, device=DEV), torch.empty(plan.K, 64, dtype=td, device=DEV)
+    psd.pack_factors(plan, [dev(x) for x in d["delta"]], [dev(x) for x in d["act"]], dtype, U, ldu, V, 64)
+    U[:, 64:] = float("nan")                               # the padding is no part of the sum
+    Uo, Vo = orc.pack_factors(d["delta"], d["act"])
+    Wr, Mr = orc.sync_fc_sfb(Uo, Vo, d["W"], d["Mom"], 0.25, 0.5)
+    for ws in (None, psd.alloc_workspace(plan, dtype, DEV)):
+        W, Mom = dev(d["W"]), dev(d["Mom"])
+        psd.sync_fc_sfb(plan, dtype, U, ldu, V, 64, W, Mom, 0.25, 0.5, workspace=ws)
+        torch.cuda.synchronize()
+        assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr)
+    del U
+    torch.cuda.empty_cache()
+
+
+def test_sfb_f32_factors_just_below_4_gib():
+    _wide_rows_layer(psd.F32, 65536, 16284, 4)             # 16288 rows are the most that are in reach
+
+
 def _random_shapes(count, seed):
     rng = np.random.default_rng(seed)
     out = []

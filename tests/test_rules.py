@@ -17,7 +17,7 @@ def rules(tmp_path_factory):
     L = ctypes.CDLL(so)
     i32, i64 = ctypes.c_int32, ctypes.c_int64
     for name, res, args in (("max_items", i64, []), ("dense_threads", i32, [i64, i64]), ("dense_chunks", i32, [i64, i32, i32]),
-                            ("pack_rows", i64, [i64, i64])):
+                            ("pack_rows", i64, [i64, i64]), ("f32_reach", i32, [i64, i64, i64])):
         getattr(L, name).restype, getattr(L, name).argtypes = res, args
     return L
 
@@ -52,3 +52,14 @@ def test_pack_launches_hold_both_matrices(rules):
             groups = -(-rows * cu // 256) + -(-rows * cv // 256)
             assert rows >= 1 and groups * 256 <= rules.max_items(), (cu, cv)
             assert rows * max(cu, cv) + 255 < 2 ** 32          # chunk numbers of the last workgroup
+
+
+def test_fp32_layers_up_to_96_rows_short_of_4_gib_are_in_reach(rules):
+    for ld in (4, 64, 1000, 65536, 1 << 20, 1 << 22, 11184810, 1 << 24, 1 << 29, 2 ** 31 - 4):
+        most = (2 ** 32 - 4096) // 4 // ld - 96                # rows
+        for K in {1, 16, most - 1, most, most + 1, most + 96, 2 ** 31 - 1}:
+            if K < 1 or K >= 2 ** 31:
+                continue
+            assert rules.f32_reach(K, ld, 4) == rules.f32_reach(K, 4, ld) == (K <= most), (K, ld)
+        if most >= 1:                                          # ... and then a stage of 64 rows, overhanging by a tile, is too
+            assert (64 * ld + 127) * 4 < 2 ** 32 and most * ld * 4 < 2 ** 32
