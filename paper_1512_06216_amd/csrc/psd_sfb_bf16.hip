@@ -435,10 +435,9 @@ psd_status launch_cfg(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t
     const int64_t tiles_n = (N + C::TN - 1) / C::TN, tiles_m = (M + C::TM - 1) / C::TM;
     const int64_t tiles = tiles_n * tiles_m;
     if (tiles < 1 || tiles * splits > 0x3fffffff) return PSD_E_INVALID;
-    // 32-bit byte offsets into each factor matrix, with room for the stages of read-ahead
+    static_assert(C::NSTAGE <= kBf16Stages, "the reserve covers the ring");
+    if (!factors_in_reach(K, ldu, ldv, 2, bf16_reserve(C::KT))) return PSD_E_UNSUPPORTED;
     const int64_t u_bytes = K * ldu * 2, v_bytes = K * ldv * 2;
-    const int64_t reach = (int64_t(1) << 32) - (C::NSTAGE + 2) * C::KT * (ldu > ldv ? ldu : ldv) * 2 - 4096;
-    if (u_bytes > reach || v_bytes > reach) return PSD_E_UNSUPPORTED;
     const bool lines = C::G == 1 && rows_on_lines(W, Mom, M);
     constexpr bool alone = C::G == 1;            // groups come neither split nor streamed
     auto kern = splits > 1 ? sfb_bf16_kernel<C, alone, false>
@@ -560,7 +559,8 @@ psd_status launch_sfb_bf16(const uint16_t* U, int64_t ldu, const uint16_t* V, in
     int splits;
     Bf16Tile t = choose_bf16_split(N, M, K, most_splits, &splits);
     // the longer stages of the grouped tiles read further ahead than the 32-bit offsets reach in a very large factor matrix
-    if (t.alone && K * (ldu > ldv ? ldu : ldv) > (int64_t(1) << 29)) t = kTiles[t.id == 5 ? 4 : 2];
+    if (t.alone && !factors_in_reach(K, ldu, ldv, 2, bf16_reserve(t.id == 5 ? Cfg64x64w16::KT : Cfg128x128w8::KT)))
+        t = kTiles[t.id == 5 ? 4 : 2];
     switch (t.id) {
         case 0: return launch_cfg<Cfg128x256w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
         case 1: return launch_cfg<Cfg128x192w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);

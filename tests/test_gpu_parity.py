@@ -446,6 +446,12 @@ def test_sfb_f32_factors_just_below_4_gib():
     _wide_rows_layer(psd.F32, 65536, 16284, 4)             # 16288 rows are the most that are in reach
 
 
+@pytest.mark.parametrize("ldu,K", [(1 << 22, 64),          # out of reach of the grouped tiles' long stages: a plain tile
+                                   (65536, 32600)])        # 32607 rows are the most that are in reach of a plain tile
+def test_sfb_bf16_factors_with_very_wide_rows(ldu, K):
+    _wide_rows_layer(psd.BF16, ldu, K, 4)
+
+
 def _random_shapes(count, seed):
     rng = np.random.default_rng(seed)
     out = []

@@ -17,7 +17,8 @@ def rules(tmp_path_factory):
     L = ctypes.CDLL(so)
     i32, i64 = ctypes.c_int32, ctypes.c_int64
     for name, res, args in (("max_items", i64, []), ("dense_threads", i32, [i64, i64]), ("dense_chunks", i32, [i64, i32, i32]),
-                            ("pack_rows", i64, [i64, i64]), ("f32_reach", i32, [i64, i64, i64])):
+                            ("pack_rows", i64, [i64, i64]), ("f32_reach", i32, [i64, i64, i64]),
+                            ("bf16_reach", i32, [i64, i64, i64, i64])):
         getattr(L, name).restype, getattr(L, name).argtypes = res, args
     return L
 
@@ -63,3 +64,19 @@ def test_fp32_layers_up_to_96_rows_short_of_4_gib_are_in_reach(rules):
             assert rules.f32_reach(K, ld, 4) == rules.f32_reach(K, 4, ld) == (K <= most), (K, ld)
         if most >= 1:                                          # ... and then a stage of 64 rows, overhanging by a tile, is too
             assert (64 * ld + 127) * 4 < 2 ** 32 and most * ld * 4 < 2 ** 32
+
+
+def test_bf16_offsets_of_every_stage_requested_stay_below_2_to_the_32(rules):
+    for rows in (32, 64, 128):                                 # of a stage: one, two and four groups
+        for ld in (8, 64, 1000, 65536, 1 << 20, 1 << 22, 1 << 23, 11184808, 1 << 29, 2 ** 31 - 8):
+            most = (2 ** 32 - 4096) // 2 // ld - 5 * rows
+            for K in {1, 32, most - 1, most, most + 1, most + 6 * rows, 2 ** 31 - 1}:
+                if K < 1 or K >= 2 ** 31:
+                    continue
+                assert rules.bf16_reach(K, ld, 8, rows) == rules.bf16_reach(K, 8, ld, rows) == (K <= most), (K, ld)
+                # a ring of 3 or 4 buffers was given 5 or 6 stages of 32 rows: what those let through still is
+                if K * ld * 2 <= 2 ** 32 - 5 * 32 * ld * 2 - 4096:
+                    assert rules.bf16_reach(K, ld, 8, 32)
+                if rules.bf16_reach(K, ld, 8, rows):
+                    last = -(-K // rows) * rows + 3 * rows - 1   # row of the last stage requested
+                    assert (last * ld + ld + 255) * 2 < 2 ** 32
