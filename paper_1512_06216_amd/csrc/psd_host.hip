@@ -51,6 +51,67 @@ bool valid_ld(int64_t ld, int64_t cols, int32_t dtype)
     return ld >= cols && ld < (int64_t(1) << 31) && (static_cast<uint64_t>(ld) * elem_size(dtype)) % 16 == 0;
 }
 
+// ---- what the entry points of an FC layer refuse (nothing is launched, nothing on the device is looked at)
+psd_status check_pack(const psd_plan* plan, const float* const* delta_p, const float* const* act_p, int32_t out_dtype, const void* U,
+                      int64_t ldu, const void* V, int64_t ldv)
+{
+    if (!plan || !delta_p || !act_p || !U || !V) return PSD_E_NULL;
+    if (out_dtype != PSD_F32 && out_dtype != PSD_BF16) return PSD_E_INVALID;
+    if (!valid_plan_sizes(plan)) return PSD_E_INVALID;
+    if (!valid_ld(ldu, plan->N, out_dtype) || !valid_ld(ldv, plan->M, out_dtype)) return PSD_E_INVALID;
+    if (!aligned16(U) || !aligned16(V)) return PSD_E_INVALID;
+    for (int64_t p = 0; p < plan->P; ++p) {
+        if (!delta_p[p] || !act_p[p]) return PSD_E_NULL;
+        if (!aligned16(delta_p[p]) || !aligned16(act_p[p])) return PSD_E_INVALID;
+    }
+    return PSD_OK;
+}
+
+// *splits: how many ways the sum over k may be split.  No workspace: not at all.  A workspace: what the query sized it for.
+psd_status check_sfb(const psd_plan* plan, int32_t factor_dtype, const void* U, int64_t ldu, const void* V, int64_t ldv, const float* W,
+                     const float* Mom, float wd, const void* workspace, size_t workspace_bytes, int* splits)
+{
+    if (!plan || !U || !V || !W || !Mom) return PSD_E_NULL;
+    if (factor_dtype != PSD_F32 && factor_dtype != PSD_BF16) return PSD_E_INVALID;
+    if (!(wd >= 0.0f)) return PSD_E_INVALID;          // also rejects NaN
+    if (!valid_plan_sizes(plan)) return PSD_E_INVALID;
+    if (!valid_ld(ldu, plan->N, factor_dtype) || !valid_ld(ldv, plan->M, factor_dtype)) return PSD_E_INVALID;
+    if (!aligned16(U) || !aligned16(V) || !aligned16(W) || !aligned16(Mom)) return PSD_E_INVALID;
+    if (W == Mom) return PSD_E_INVALID;
+    *splits = 1;
+    if (workspace_bytes != 0) {
+        if (!workspace) return PSD_E_NULL;
+        if (!aligned16(workspace)) return PSD_E_INVALID;
+        const size_t need = psd_sfb_workspace_bytes(plan, factor_dtype);
+        if (workspace_bytes < need) return PSD_E_WORKSPACE;
+        if (need != 0) *splits = static_cast<int>(need / (static_cast<size_t>(sfb_part_stride(plan->N, plan->M)) * sizeof(float)));
+    }
+    const bool f32 = factor_dtype == PSD_F32;
+    if (!factors_in_reach(plan->P * plan->B, ldu, ldv, f32 ? 4 : 2, f32 ? kF32Reserve : bf16_reserve(kBf16StageRows)))
+        return PSD_E_UNSUPPORTED;
+    return PSD_OK;
+}
+
+psd_status check_blocks(const psd_plan* plan, int32_t factor_dtype, const void* const* U_p, int64_t ldu, const void* const* V_p,
+                        int64_t ldv, const float* W, const float* Mom, float wd)
+{
+    if (!plan || !U_p || !V_p || !W || !Mom) return PSD_E_NULL;
+    if (factor_dtype != PSD_F32 && factor_dtype != PSD_BF16) return PSD_E_INVALID;
+    if (!(wd >= 0.0f)) return PSD_E_INVALID;          // also rejects NaN
+    if (!valid_plan_sizes(plan)) return PSD_E_INVALID;
+    if (!aligned16(W) || !aligned16(Mom) || W == Mom) return PSD_E_INVALID;
+    for (int64_t p = 0; p < plan->P; ++p) {
+        if (!U_p[p] || !V_p[p]) return PSD_E_NULL;
+        if (!aligned16(U_p[p]) || !aligned16(V_p[p])) return PSD_E_INVALID;
+    }
+    // rows that are not a multiple of 16 bytes (or shorter than the layer is wide), or blocks that do not hold
+    // whole k-stages: this layer has to be stacked
+    if (!psd_sfb_blocks_supported(plan, factor_dtype, ldu, ldv)) return PSD_E_UNSUPPORTED;
+    const int64_t most = (int64_t(1) << 32) / static_cast<int64_t>(elem_size(factor_dtype));      // elements of one block
+    if (plan->B * ldu >= most || plan->B * ldv >= most) return PSD_E_UNSUPPORTED;
+    return PSD_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -133,15 +194,8 @@ int64_t psd_factor_ld(int64_t cols, int32_t dtype)
 psd_status psd_pack_factors(const psd_plan* plan, const float* const* delta_p, const float* const* act_p,
                             int32_t out_dtype, void* U, int64_t ldu, void* V, int64_t ldv, void* stream)
 {
-    if (!plan || !delta_p || !act_p || !U || !V) return PSD_E_NULL;
-    if (out_dtype != PSD_F32 && out_dtype != PSD_BF16) return PSD_E_INVALID;
-    if (!valid_plan_sizes(plan)) return PSD_E_INVALID;
-    if (!valid_ld(ldu, plan->N, out_dtype) || !valid_ld(ldv, plan->M, out_dtype)) return PSD_E_INVALID;
-    if (!aligned16(U) || !aligned16(V)) return PSD_E_INVALID;
-    for (int64_t p = 0; p < plan->P; ++p) {
-        if (!delta_p[p] || !act_p[p]) return PSD_E_NULL;
-        if (!aligned16(delta_p[p]) || !aligned16(act_p[p])) return PSD_E_INVALID;
-    }
+    const psd_status bad = check_pack(plan, delta_p, act_p, out_dtype, U, ldu, V, ldv);
+    if (bad != PSD_OK) return bad;
     hipStream_t st = static_cast<hipStream_t>(stream);
     PackArgs a;
     a.P = static_cast<int32_t>(plan->P);
@@ -168,22 +222,9 @@ psd_status psd_sync_fc_sfb(const psd_plan* plan, int32_t factor_dtype, const voi
                            const void* V, int64_t ldv, float* W, float* Mom, float lr, float mu, float wd,
                            void* workspace, size_t workspace_bytes, void* stream)
 {
-    if (!plan || !U || !V || !W || !Mom) return PSD_E_NULL;
-    if (factor_dtype != PSD_F32 && factor_dtype != PSD_BF16) return PSD_E_INVALID;
-    if (!(wd >= 0.0f)) return PSD_E_INVALID;          // also rejects NaN
-    if (!valid_plan_sizes(plan)) return PSD_E_INVALID;
-    if (!valid_ld(ldu, plan->N, factor_dtype) || !valid_ld(ldv, plan->M, factor_dtype)) return PSD_E_INVALID;
-    if (!aligned16(U) || !aligned16(V) || !aligned16(W) || !aligned16(Mom)) return PSD_E_INVALID;
-    if (W == Mom) return PSD_E_INVALID;
-    // no workspace: one workgroup per tile over all of K.  A workspace: the split the query sized it for.
-    int splits = 1;
-    if (workspace_bytes != 0) {
-        if (!workspace) return PSD_E_NULL;
-        if (!aligned16(workspace)) return PSD_E_INVALID;
-        const size_t need = psd_sfb_workspace_bytes(plan, factor_dtype);
-        if (workspace_bytes < need) return PSD_E_WORKSPACE;
-        if (need != 0) splits = static_cast<int>(need / (static_cast<size_t>(sfb_part_stride(plan->N, plan->M)) * sizeof(float)));
-    }
+    int splits;
+    const psd_status bad = check_sfb(plan, factor_dtype, U, ldu, V, ldv, W, Mom, wd, workspace, workspace_bytes, &splits);
+    if (bad != PSD_OK) return bad;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int64_t K = plan->P * plan->B;
     float* part = splits > 1 ? static_cast<float*>(workspace) : nullptr;
@@ -205,18 +246,8 @@ psd_status psd_sync_fc_sfb_blocks(const psd_plan* plan, int32_t factor_dtype, co
                                   const void* const* V_p, int64_t ldv, float* W, float* Mom, float lr, float mu,
                                   float wd, void* stream)
 {
-    if (!plan || !U_p || !V_p || !W || !Mom) return PSD_E_NULL;
-    if (factor_dtype != PSD_F32 && factor_dtype != PSD_BF16) return PSD_E_INVALID;
-    if (!(wd >= 0.0f)) return PSD_E_INVALID;          // also rejects NaN
-    if (!valid_plan_sizes(plan)) return PSD_E_INVALID;
-    if (!aligned16(W) || !aligned16(Mom) || W == Mom) return PSD_E_INVALID;
-    for (int64_t p = 0; p < plan->P; ++p) {
-        if (!U_p[p] || !V_p[p]) return PSD_E_NULL;
-        if (!aligned16(U_p[p]) || !aligned16(V_p[p])) return PSD_E_INVALID;
-    }
-    // rows that are not a multiple of 16 bytes (or shorter than the layer is wide), or blocks that do not hold
-    // whole k-stages: this layer has to be stacked
-    if (!psd_sfb_blocks_supported(plan, factor_dtype, ldu, ldv)) return PSD_E_UNSUPPORTED;
+    const psd_status bad = check_blocks(plan, factor_dtype, U_p, ldu, V_p, ldv, W, Mom, wd);
+    if (bad != PSD_OK) return bad;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (factor_dtype == PSD_F32)
         return launch_sfb_f32_blocks(reinterpret_cast<const float* const*>(U_p), ldu,

@@ -70,7 +70,7 @@ struct PackArgs {
 };
 psd_status launch_pack(PackArgs& a, int32_t out_dtype, hipStream_t st);
 
-// ---- reconstruction.  part / most_splits: with a workspace for most_splits > 1 partial sums the contraction
+// ---- reconstruction (factors in reach of 32-bit offsets).  part / most_splits: with a workspace for most_splits > 1 partial sums the contraction
 // may be split over up to that many workgroups per tile, each storing a partial dW (N x M, sfb_part_stride
 // apart) to `part`, and the partials are summed in split order and the update applied by launch_sfb_reduce.
 psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t ldv, float* W, float* Mom,

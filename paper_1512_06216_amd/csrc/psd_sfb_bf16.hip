@@ -31,7 +31,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
-constexpr int SLICE = 32;      // k rows of a stage that one group of wavefronts contracts (two MFMA k-steps of 16)
+constexpr int SLICE = kBf16StageRows;   // k rows of a stage that one group of wavefronts contracts (two MFMA k-steps of 16)
 constexpr int GROUP_N = 8;     // tile rows per raster group (L2 reuse of the V panels)
 constexpr int PLD = 36;        // epilogue patch row stride in floats (144 B: conflict-free)
 
@@ -406,7 +406,6 @@ psd_status launch_cfg_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int6
     const int64_t tiles = tiles_n * tiles_m;
     if (tiles < 1 || tiles > 0x3fffffff) return PSD_E_INVALID;
     const int64_t u_bytes = B * ldu * 2, v_bytes = B * ldv * 2;          // one block
-    if (u_bytes >= (int64_t(1) << 32) || v_bytes >= (int64_t(1) << 32)) return PSD_E_UNSUPPORTED;
     const bool lines = C::G == 1 && rows_on_lines(W, Mom, M);
     constexpr bool can_stream = C::G == 1;
     auto kern = lines ? sfb_bf16_blocks_kernel<C, can_stream> : sfb_bf16_blocks_kernel<C, false>;
@@ -436,7 +435,6 @@ psd_status launch_cfg(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t
     const int64_t tiles = tiles_n * tiles_m;
     if (tiles < 1 || tiles * splits > 0x3fffffff) return PSD_E_INVALID;
     static_assert(C::NSTAGE <= kBf16Stages, "the reserve covers the ring");
-    if (!factors_in_reach(K, ldu, ldv, 2, bf16_reserve(C::KT))) return PSD_E_UNSUPPORTED;
     const int64_t u_bytes = K * ldu * 2, v_bytes = K * ldv * 2;
     const bool lines = C::G == 1 && rows_on_lines(W, Mom, M);
     constexpr bool alone = C::G == 1;            // groups come neither split nor streamed

@@ -450,7 +450,6 @@ psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t l
                           int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int most_splits,
                           hipStream_t st)
 {
-    if (!factors_in_reach(K, ldu, ldv, 4, kF32Reserve)) return PSD_E_UNSUPPORTED;
     const int64_t u_bytes = K * ldu * 4, v_bytes = K * ldv * 4;
     Args g = common_args(ldu, ldv, W, Mom, N, M, K, lr, mu, wd);
     g.U = U; g.V = V;
@@ -489,7 +488,6 @@ psd_status launch_sfb_f32_blocks(const float* const* U_p, int64_t ldu, const flo
 {
     if (P < 1 || P > PSD_MAX_WORKERS || !sfb_f32_blocks_supported(B)) return PSD_E_UNSUPPORTED;
     const int64_t u_bytes = B * ldu * 4, v_bytes = B * ldv * 4;        // one block
-    if (u_bytes >= (int64_t(1) << 32) || v_bytes >= (int64_t(1) << 32)) return PSD_E_UNSUPPORTED;
     BlockPtrs blocks;
     for (int64_t p = 0; p < PSD_MAX_WORKERS; ++p) {
         blocks.u[p] = p < P ? U_p[p] : nullptr;
