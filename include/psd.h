@@ -239,7 +239,10 @@ typedef struct psd_layer_task {
  * psd_sync_dense_ps_multi launch on the stream of the topmost of them (up to PSD_MAX_MULTI_SEGMENTS
  * per launch); the streams of the other layers of the group are made to wait for that launch, and
  * every group member's ev_begin / ev_end are recorded around it.
- * Stops at and returns the first error. */
+ * Where the topmost layers and such a group below them name one ev_ready (not NULL), so that they become available
+ * together, the group's launch may be issued before the work of the layers above it, provided that no stream of theirs
+ * is a stream of the group's and that the arguments of all of them have been checked.
+ * Stops at and returns the first error; the layers below one whose arguments are refused are not touched. */
 psd_status psd_sync_iteration(int32_t L, const psd_layer_task* layers, float lr, float mu, float wd,
                               int32_t rule);
 

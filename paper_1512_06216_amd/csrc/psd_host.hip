@@ -387,17 +387,32 @@ psd_status sync_ps_group(const psd_layer_task* layers, int32_t lo, int32_t hi, f
     return PSD_OK;
 }
 
-// The lowest layer of a parameter-server group that is to be issued before the reconstructions above it, -1: none.  Only where
-// nothing tells them apart in time: one and the same readiness event (or none).  Beside three or more packs and bf16
-// reconstructions the sum's accesses and theirs hinder each other, and the group's waits end up behind the last
-// reconstruction; first and by itself it takes 20 us and they fill the chip afterwards (AlexNet, 8 x 256 samples: 470 -> 445 us a
-// step; 8 x 32: 289 -> 273).  One or two layers leave gaps that the sum fills (4096 -> 4096 alone: 185 us last, 203 first),
+// the arguments of an FC layer that goes through the factors, as its entry points will check them
+psd_status check_factor_layer(const psd_layer_task& t, float wd)
+{
+    if (t.plan.kind != PSD_LAYER_FC) return PSD_E_INVALID;
+    if (!t.U && !t.V)
+        return check_blocks(&t.plan, t.factor_dtype, t.delta_p, t.ldu ? t.ldu : t.plan.N, t.act_p, t.ldv ? t.ldv : t.plan.M, t.W, t.Mom, wd);
+    const psd_status r = check_pack(&t.plan, static_cast<const float* const*>(static_cast<const void*>(t.delta_p)),
+                                    static_cast<const float* const*>(static_cast<const void*>(t.act_p)), t.factor_dtype, t.U, t.ldu, t.V, t.ldv);
+    int splits;
+    return r != PSD_OK ? r : check_sfb(&t.plan, t.factor_dtype, t.U, t.ldu, t.V, t.ldv, t.W, t.Mom, wd, t.workspace, t.workspace_bytes, &splits);
+}
+
+// The lowest layer of a parameter-server group that is to be issued before the reconstructions above it, -1: none.
+// Only where nothing tells them apart: they name one readiness event, share no stream, and none of them will be refused (a layer
+// that is refused leaves those below it untouched, and those above it issued).  Without an event a layer's readiness is the order
+// of its own stream, which the library cannot see.
+// Beside three or more packs and bf16 reconstructions the sum's accesses and theirs hinder each other, and the group's waits end up
+// behind the last reconstruction; first and by itself it takes 20 us and they fill the chip afterwards (AlexNet, 8 x 256 samples:
+// 470 -> 445 us a step; 8 x 32: 289 -> 273).  One or two layers leave gaps that the sum fills (4096 -> 4096 alone: 185 us last, 203 first),
 // fp32 reconstructions leave HBM idle (1830 against 1860), and small layers end before the hand-over between streams does.
-int32_t group_to_issue_first(int32_t L, const psd_layer_task* layers, int32_t rule, int32_t* hi)
+int32_t group_to_issue_first(int32_t L, const psd_layer_task* layers, float wd, int32_t rule, int32_t* hi)
 {
     constexpr int32_t kLayers = 3;
     constexpr double kWeights = 25e6;              // 80 us of update
     const void* ready = layers[L - 1].ev_ready;
+    if (!ready) return -1;
     int32_t l = L - 1;
     double weights = 0;
     for (; l >= 0; --l) {
@@ -410,6 +425,18 @@ int32_t group_to_issue_first(int32_t L, const psd_layer_task* layers, int32_t ru
     int32_t lo = l + 1;
     while (lo > 0 && l - lo + 2 <= PSD_MAX_MULTI_SEGMENTS && fusable_ps_layer(layers[lo - 1], rule, ready)) --lo;
     if (lo >= l) return -1;
+    for (int32_t i = l + 1; i < L; ++i) {
+        if (!layers[i].stream) return -1;              // (the default stream waits for others by itself)
+        for (int32_t j = lo; j <= l; ++j)
+            if (layers[i].stream == layers[j].stream) return -1;
+        if (check_factor_layer(layers[i], wd) != PSD_OK) return -1;
+    }
+    for (int32_t j = lo; j <= l; ++j) {
+        const psd_layer_task& t = layers[j];
+        uint64_t n;
+        if (mul_u64(static_cast<uint64_t>(t.plan.M), static_cast<uint64_t>(t.plan.N), &n) || n > (uint64_t(1) << 40)) return -1;
+        if (check_dense(static_cast<int64_t>(n), static_cast<int32_t>(t.plan.P), PSD_MAX_MULTI_WORKERS, t.G, t.W, t.Mom, t.S) != PSD_OK) return -1;
+    }
     *hi = l;
     return lo;
 }
@@ -417,13 +444,13 @@ int32_t group_to_issue_first(int32_t L, const psd_layer_task* layers, int32_t ru
 }  // namespace
 
 // Algorithm 2's order: the top layer's gradient exists first, so its synchronisation is
-// issued first; every layer goes to its own stream.  (Layers that share one readiness event may be reordered.)
+// issued first; every layer goes to its own stream.  (group_to_issue_first is the one exception.)
 psd_status psd_sync_iteration(int32_t L, const psd_layer_task* layers, float lr, float mu, float wd, int32_t rule)
 {
     if (!layers) return PSD_E_NULL;
     if (L < 1 || (rule != PSD_RULE_ALG3 && rule != PSD_RULE_SFB_VS_DENSE)) return PSD_E_INVALID;
     int32_t first_hi = -1;
-    const int32_t first_lo = group_to_issue_first(L, layers, rule, &first_hi);
+    const int32_t first_lo = group_to_issue_first(L, layers, wd, rule, &first_hi);
     if (first_lo >= 0) {
         const psd_status r = sync_ps_group(layers, first_lo, first_hi, lr, mu, wd);
         if (r != PSD_OK) return r;

@@ -320,3 +320,30 @@ def test_a_batch_whose_product_with_the_workers_wraps_is_refused():
         assert L.psd_sync_fc_sfb(ctypes.byref(plan), dtype, fake(0), 32, fake(1), 64, *args, None, 0, None) == psd.E_INVALID
         assert L.psd_sync_fc_bias(ctypes.byref(plan), dtype, fake(0), 32, *args, None) == psd.E_INVALID
     assert L.psd_pack_factors(ctypes.byref(plan), pp, pp, psd.F32, fake(0), 32, fake(1), 64, None) == psd.E_INVALID
+
+
+def _big_step(ev_ready=None):
+    """Two parameter-server layers below three 3000 -> 3000 layers with bf16 factors; every address is made up."""
+    f32p = ctypes.POINTER(ctypes.c_float)
+    ptrs = (f32p * 2)(ctypes.cast(0x10000000, f32p), ctypes.cast(0x20000000, f32p))
+    pp = ctypes.cast(ptrs, ctypes.POINTER(f32p))
+    tasks = (psd.LayerTask * 5)()
+    for i, t in enumerate(tasks):
+        t.W, t.Mom = ctypes.cast(0x30000000 + i * 0x10000000, f32p), ctypes.cast(0x38000000 + i * 0x10000000, f32p)
+        t.stream, t.ev_ready, t.S, t.factor_dtype = 0x1000 * (i + 1), ev_ready, 1, psd.BF16
+        if i < 2:
+            t.plan, t.G = psd.plan_layer(psd.LAYER_CONV, 1000, 1, 16, 2), pp
+        else:
+            t.plan, t.delta_p, t.act_p = psd.plan_layer(psd.LAYER_FC, 3000, 3000, 16, 2), pp, pp
+            t.U, t.ldu, t.V, t.ldv = 0x90000000, 3008, 0xa0000000, 3008
+    return tasks, ptrs
+
+
+@pytest.mark.parametrize("layer,field,value,status", [(4, "ldu", 3001, psd.E_INVALID), (4, "U", None, psd.E_NULL), (4, "ldv", 3004, psd.E_INVALID),
+                                                      (4, "factor_dtype", 5, psd.E_INVALID), (4, "act_p", None, psd.E_NULL)])
+def test_iteration_without_events_comes_to_a_refused_layer_before_the_layers_below_it(layer, field, value, status):
+    """Without readiness events the issue order is top-down: the top layer is refused before anything is launched
+    (a launch would be PSD_E_HIP here, where there is no GPU)."""
+    tasks, keep = _big_step()
+    setattr(tasks[layer], field, value)
+    assert psd.lib().psd_sync_iteration(5, tasks, 0.1, 0.9, 0.0, psd.RULE_ALG3) == status

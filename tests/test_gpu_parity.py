@@ -1045,6 +1045,76 @@ def test_iteration_waits_for_the_layers_gradient_event():
     hip.hipEventDestroy(ev_conv)
 
 
+def _step_with_three_large_layers():
+    layers = [dict(kind="conv", P=4, **{k: v for k, v in inputs.dense_layer_integer(n, 4, seed=n % 97).items() if k != "P"})
+              for n in (70001, 300000)]
+    for M, N in ((3000, 3008), (3008, 3000), (3000, 3000)):              # 27 M weights
+        d = inputs.fc_layer_integer(M, N, 16, 4, seed=M + N)
+        layers.append(dict(kind="fc", M=M, N=N, B=16, P=4, **{k: d[k] for k in ("delta", "act", "W", "Mom")}))
+    return layers, [torch.cuda.Stream(device=DEV) for _ in layers]
+
+
+def _oracle_layer(L):
+    if L["kind"] == "conv":
+        return orc.sync_dense_ps(L["G"], L["W"], L["Mom"], 0.25, 0.5, min(inputs.CNN_S, L["n"]))
+    U, V = orc.pack_factors(L["delta"], L["act"])
+    return orc.sync_fc_sfb(U, V, L["W"], L["Mom"], 0.25, 0.5)
+
+
+@pytest.mark.parametrize("streams_of", ["own", "shared", "default"])
+def test_iteration_of_layers_behind_one_event_that_fires_late(streams_of):
+    """All layers name one event, which fires long after the call: the gradients are written by another stream meanwhile.  On
+    streams of their own the parameter-server group goes first; on one stream the order is top-down."""
+    layers, streams = _step_with_three_large_layers()
+    if streams_of != "own":
+        streams = [streams[0] if streams_of == "shared" else None] * len(layers)
+    tasks, state = _build_iteration(layers, psd.BF16, streams)
+    ready, backward = torch.cuda.Event(), torch.cuda.Stream(device=DEV)
+    late = []                                                            # the buffers that are written late
+    for t in tasks:
+        for key in ("G", "delta", "act"):
+            late += t.get(key, [])
+    values = [x.clone() for x in late]
+    for x in late:
+        x.zero_()
+    big = torch.randn(4096, 4096, device=DEV)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(backward):
+        for _ in range(20):
+            big = (big @ big) * 1e-3
+        for x, v in zip(late, values):
+            x.copy_(v)
+        ready.record()
+    for t in tasks:
+        t["ev_ready"] = ready.cuda_event
+    psd.Iteration(tasks).run(0.25, 0.5, psd.RULE_ALG3)
+    torch.cuda.synchronize()
+    for L, (W, Mom) in zip(layers, state):
+        Wr, Mr = _oracle_layer(L)
+        assert np.array_equal(W.cpu().numpy(), Wr) and np.array_equal(Mom.cpu().numpy(), Mr)
+
+
+@pytest.mark.parametrize("event", [False, True])
+def test_iteration_stops_at_a_refused_layer_and_leaves_those_below_it_alone(event):
+    layers, streams = _step_with_three_large_layers()
+    tasks, state = _build_iteration(layers, psd.BF16, streams)
+    ready = torch.cuda.Event()
+    ready.record()
+    if event:
+        for t in tasks:
+            t["ev_ready"] = ready.cuda_event
+    it = psd.Iteration(tasks)
+    it.tasks[3].ldv = 3001                                               # the middle one of the three
+    torch.cuda.synchronize()
+    with pytest.raises(psd.PsdError) as e:
+        it.run(0.25, 0.5, psd.RULE_ALG3)
+    assert e.value.status == psd.E_INVALID
+    torch.cuda.synchronize()
+    for i, (L, (W, Mom)) in enumerate(zip(layers, state)):
+        Wr, Mr = _oracle_layer(L) if i == 4 else (L["W"], L["Mom"])
+        assert np.array_equal(W.cpu().numpy(), Wr) and np.array_equal(Mom.cpu().numpy(), Mr), i
+
+
 def test_iteration_fused_parameter_server_launch_orders_every_layers_stream():
     """Conv layers without a readiness event are summed by one launch on the top conv layer's stream; work
     a caller then enqueues on ANY of those layers' own streams must see that layer updated."""
