@@ -323,7 +323,7 @@ def test_a_batch_whose_product_with_the_workers_wraps_is_refused():
 
 
 def _big_step(ev_ready=None):
-    """Two parameter-server layers below three 3000 -> 3000 layers with bf16 factors; every address is made up."""
+    """Two parameter-server layers below three 3500 -> 3500 layers with bf16 factors; every address is made up."""
     f32p = ctypes.POINTER(ctypes.c_float)
     ptrs = (f32p * 2)(ctypes.cast(0x10000000, f32p), ctypes.cast(0x20000000, f32p))
     pp = ctypes.cast(ptrs, ctypes.POINTER(f32p))
@@ -334,12 +334,12 @@ def _big_step(ev_ready=None):
         if i < 2:
             t.plan, t.G = psd.plan_layer(psd.LAYER_CONV, 1000, 1, 16, 2), pp
         else:
-            t.plan, t.delta_p, t.act_p = psd.plan_layer(psd.LAYER_FC, 3000, 3000, 16, 2), pp, pp
-            t.U, t.ldu, t.V, t.ldv = 0x90000000, 3008, 0xa0000000, 3008
+            t.plan, t.delta_p, t.act_p = psd.plan_layer(psd.LAYER_FC, 3500, 3500, 16, 2), pp, pp
+            t.U, t.ldu, t.V, t.ldv = 0x90000000, 3520, 0xa0000000, 3520
     return tasks, ptrs
 
 
-@pytest.mark.parametrize("layer,field,value,status", [(4, "ldu", 3001, psd.E_INVALID), (4, "U", None, psd.E_NULL), (4, "ldv", 3004, psd.E_INVALID),
+@pytest.mark.parametrize("layer,field,value,status", [(4, "ldu", 3501, psd.E_INVALID), (4, "U", None, psd.E_NULL), (4, "ldv", 3508, psd.E_INVALID),
                                                       (4, "factor_dtype", 5, psd.E_INVALID), (4, "act_p", None, psd.E_NULL)])
 def test_iteration_without_events_comes_to_a_refused_layer_before_the_layers_below_it(layer, field, value, status):
     """Without readiness events the issue order is top-down: the top layer is refused before anything is launched

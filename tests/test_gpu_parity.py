@@ -1048,7 +1048,7 @@ def test_iteration_waits_for_the_layers_gradient_event():
 def _step_with_three_large_layers():
     layers = [dict(kind="conv", P=4, **{k: v for k, v in inputs.dense_layer_integer(n, 4, seed=n % 97).items() if k != "P"})
               for n in (70001, 300000)]
-    for M, N in ((3000, 3008), (3008, 3000), (3000, 3000)):              # 27 M weights
+    for M, N in ((4000, 4008), (4008, 4000), (4000, 4000)):              # 48 M weights
         d = inputs.fc_layer_integer(M, N, 16, 4, seed=M + N)
         layers.append(dict(kind="fc", M=M, N=N, B=16, P=4, **{k: d[k] for k in ("delta", "act", "W", "Mom")}))
     return layers, [torch.cuda.Stream(device=DEV) for _ in layers]
@@ -1104,7 +1104,7 @@ def test_iteration_stops_at_a_refused_layer_and_leaves_those_below_it_alone(even
         for t in tasks:
             t["ev_ready"] = ready.cuda_event
     it = psd.Iteration(tasks)
-    it.tasks[3].ldv = 3001                                               # the middle one of the three
+    it.tasks[3].ldv = 4001                                               # the middle one of the three
     torch.cuda.synchronize()
     with pytest.raises(psd.PsdError) as e:
         it.run(0.25, 0.5, psd.RULE_ALG3)
