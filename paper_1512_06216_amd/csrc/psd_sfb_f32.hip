@@ -311,7 +311,7 @@ __device__ __forceinline__ void grid_body(const Args& g, const BlockPtrs* blocks
 // Tiles of one size have a kernel of their own: three of 64 x 128 and five of 64 x 64 fit a compute unit then (with the 128 x 128
 // code beside them two, for its registers; 6000 -> 6000, K = 384: 265 against 272 us).
 template <int BN, int BM, bool MIXED, bool PART>
-__global__ void __launch_bounds__(256, MIXED ? 2 : BM == 2 ? 3 : 5) sfb_f32_kernel(const Args g)
+__global__ void __launch_bounds__(256, MIXED || BN == 2 ? 2 : BM == 2 ? 3 : 5) sfb_f32_kernel(const Args g)
 {
     grid_body<BN, BM, MIXED, PART, false>(g, nullptr);
 }
@@ -345,11 +345,18 @@ Cover uniform_cover(int64_t N, int64_t M, int bn, int bm)
     return {bn, bm, bn * bm == 4 ? tn * tm : 0, tm, tn * tm};
 }
 
+// the pinned tile is (64 * pinned) x 128; 0: none is pinned
+int pinned_tile()
+{
+    const int t = tune_value(PSD_TUNE_SFB_F32_TILE);
+    return t == 1 || t == 2 ? t : 0;
+}
+
+// *us: what the launch takes, by estimate (0 with a pinned tile)
 Cover choose_f32(int64_t N, int64_t M, int64_t K, double* us)
 {
-    const int forced = tune_value(PSD_TUNE_SFB_F32_TILE);
     *us = 0;
-    if (forced == 1 || forced == 2) return uniform_cover(N, M, forced, 2);
+    if (const int pinned = pinned_tile()) return uniform_cover(N, M, pinned, 2);
     // A compute unit works through its tiles at the rate of its MFMA pipe, so the launch takes as long as the compute unit with
     // the most tile area: 57 us per 1024 rows and 128 x 128 tile, smaller tiles with what their shorter runs between barriers
     // cost; what the loops of other tiles do not hide of the W / Mom update (12.5 us per 128 x 128 tile of a compute unit's
@@ -441,9 +448,8 @@ psd_status launch_cover(Args& g, const BlockPtrs* blocks, hipStream_t st)
 // how many ways psd_sync_fc_sfb may split this layer's sum over k when it is given a workspace (1 = not at all)
 int sfb_f32_splits(int64_t N, int64_t M, int64_t K)
 {
-    const int64_t slots = 2 * int64_t(device_cu_count());
-    const int64_t tiles128 = ((N + 127) / 128) * ((M + 127) / 128);
-    return sfb_splits_for(tiles128, slots, K);
+    const int64_t rows = pinned_tile() == 1 ? 64 : 128;
+    return sfb_splits_for(((N + rows - 1) / rows) * ((M + 127) / 128), 2 * int64_t(device_cu_count()), K);
 }
 
 psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t ldv, float* W, float* Mom,
@@ -454,18 +460,19 @@ psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t l
     Args g = common_args(ldu, ldv, W, Mom, N, M, K, lr, mu, wd);
     g.U = U; g.V = V;
     g.u_bytes = static_cast<uint32_t>(u_bytes); g.v_bytes = static_cast<uint32_t>(v_bytes);
-    // Split the sum over k where the shorter loops save more than storing and adding the partial sums costs: the second launch
+    // A pinned tile is split as far as the workspace was asked for.  Otherwise the sum is split where the shorter loops save more than storing and adding the partial sums costs: the second launch
     // 4 us and its bytes.  512 -> 512, K = 2048: 34 us unsplit, 17 us in four.
-    const Cover c = uniform_cover(N, M, 1, 1);
+    const int pinned = pinned_tile();
+    const Cover c = pinned ? uniform_cover(N, M, pinned, 2) : uniform_cover(N, M, 1, 1);
     const int64_t cus = device_cu_count();
     double us;
     choose_f32(N, M, K, &us);
-    int splits = 1;
-    for (int s = 2; s <= most_splits; ++s) {
+    int splits = pinned ? most_splits : 1;
+    for (int s = 2; !pinned && s <= most_splits; ++s) {
         const int64_t groups = c.groups * s;
         const double loop = groups <= cus ? 0.32 : static_cast<double>((groups + cus - 1) / cus) * 0.281;
         const double x = 5 + loop * 57 * static_cast<double>(K) / s / 1024 + 4 + (16.0 + 4 * s) * N * M / 5e6;
-        if (x < us || us == 0) {
+        if (x < us) {
             us = x;
             splits = s;
         }
@@ -475,7 +482,9 @@ psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t l
     g.tiles = static_cast<int>(c.groups);
     g.part = part; g.part_stride = sfb_part_stride(N, M);
     g.stages_per_split = static_cast<int>(((K + SLICE - 1) / SLICE + splits - 1) / splits);
-    const psd_status r = start<1, 1, false, true>(g, nullptr, c.groups * splits, st);
+    const psd_status r = pinned == 2   ? start<2, 2, false, true>(g, nullptr, c.groups * splits, st)
+                         : pinned == 1 ? start<1, 2, false, true>(g, nullptr, c.groups * splits, st)
+                                       : start<1, 1, false, true>(g, nullptr, c.groups * splits, st);
     if (r != PSD_OK) return r;
     return launch_sfb_reduce(part, splits, N, M, W, Mom, lr, mu, wd, st);
 }

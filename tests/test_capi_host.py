@@ -347,3 +347,15 @@ def test_iteration_without_events_comes_to_a_refused_layer_before_the_layers_bel
     tasks, keep = _big_step()
     setattr(tasks[layer], field, value)
     assert psd.lib().psd_sync_iteration(5, tasks, 0.1, 0.9, 0.0, psd.RULE_ALG3) == status
+
+
+def test_workspace_query_follows_a_pinned_tile():
+    """1024 -> 1000: 64 tiles of 128 x 128 take four partial sums, 128 tiles of 64 x 128 two, 32 of 128 x 256 four."""
+    plan = psd.plan_layer(psd.LAYER_FC, 1024, 1000, 256, 8)
+    for knob, dtype, want in ((psd.TUNE_SFB_F32_TILE, psd.F32, {-1: 4, 1: 2, 2: 4}), (psd.TUNE_SFB_BF16_TILE, psd.BF16, {-1: 4, 0: 4, 1: 4, 2: 4})):
+        try:
+            for tile, partials in want.items():
+                psd.tune_set(knob, tile)
+                assert psd.sfb_workspace_bytes(plan, dtype) == partials * 1024 * 1000 * 4, (dtype, tile)
+        finally:
+            psd.tune_set(knob, -1)

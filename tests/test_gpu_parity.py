@@ -409,6 +409,28 @@ def test_sfb_split_k_with_workspace_bit_exact_and_equal_to_unsplit(M, N, B, P, d
     assert orc.rel_frob(outs[0], outs[1]) <= TOL_F32
 
 
+@pytest.mark.parametrize("dtype,tile", [(psd.F32, 1), (psd.F32, 2), (psd.BF16, 0), (psd.BF16, 1), (psd.BF16, 2)])
+@pytest.mark.parametrize("M,N,B,P", SPLIT_SHAPES)
+def test_sfb_split_k_of_a_pinned_tile_bit_exact(M, N, B, P, dtype, tile, pinned_tile):
+    """A pinned tile is split into as many partial sums as its workspace holds, and only those are written."""
+    pinned_tile(psd.TUNE_SFB_F32_TILE if dtype == psd.F32 else psd.TUNE_SFB_BF16_TILE, tile)
+    d = inputs.fc_layer_integer(M, N, B, P, seed=M + N + tile)
+    plan, U, ldu, V, ldv = run_pack(d, dtype)
+    stride = (N * M + 3) // 4 * 4
+    splits = psd.sfb_workspace_bytes(plan, dtype) // (4 * stride)
+    ws = torch.full(((splits + 1) * stride,), float("nan"), device=DEV)
+    W, Mom = dev(d["W"]), dev(d["Mom"])
+    psd.sync_fc_sfb(plan, dtype, U, ldu, V, ldv, W, Mom, 0.25, 0.5, wd=0.25, workspace=ws)
+    torch.cuda.synchronize()
+    Uo, Vo = orc.pack_factors(d["delta"], d["act"])
+    Wr, Mr = orc.sync_fc_sfb(Uo, Vo, d["W"], d["Mom"], 0.25, 0.5, wd=0.25)
+    assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr)
+    parts = ws.view(-1, stride)
+    assert splits >= 2 and bool(torch.isnan(parts[splits]).all())
+    assert not bool(torch.isnan(parts[:splits, :N * M]).any())
+    assert torch.equal(parts[:splits, :N * M].sum(0).cpu(), torch.from_numpy(orc.rebuild(Uo, Vo)).float().flatten())
+
+
 def test_sfb_workspace_is_ignored_by_layers_that_fill_the_gpu():
     d = inputs.fc_layer_integer(2048, 2048, 8, 4, seed=12)      # 256 tiles of 128 x 128 ... K = 32: no split either way
     plan, U, ldu, V, ldv = run_pack(d, psd.BF16)
