@@ -95,17 +95,6 @@ int sfb_bf16_splits(int64_t N, int64_t M, int64_t K);
 psd_status launch_sfb_reduce(const float* part, int splits, int64_t N, int64_t M, float* W, float* Mom, float lr,
                              float mu, float wd, hipStream_t st);
 
-constexpr int kMaxSplits = 4;
-// A workspace is asked for by layers that leave most of the chip idle: while the split workgroups (of 128 x 128 tiles)
-// still number at most one per CU (half the slots) and every split keeps at least kMinSplitRows k rows.  Whether the
-// sum is then split is for the launchers to say.
-constexpr int64_t kMinSplitRows = 512;
-inline int sfb_splits_for(int64_t tiles, int64_t slots, int64_t K)
-{
-    int s = 1;
-    while (s < kMaxSplits && tiles * (s + 1) <= slots / 2 && K / (s + 1) >= kMinSplitRows) ++s;
-    return s;
-}
 // elements between two partials: N*M rounded up so that every partial starts 16-byte aligned
 inline int64_t sfb_part_stride(int64_t N, int64_t M) { return (N * M + 3) / 4 * 4; }
 

@@ -49,6 +49,152 @@ constexpr int64_t kF32Reserve = 96;
 constexpr int64_t kBf16Stages = 4, kBf16StageRows = 32;
 constexpr int64_t bf16_reserve(int64_t rows) { return (kBf16Stages + 1) * rows; }
 
+// ---- split of the sum over k
+constexpr int kMaxSplits = 4;
+// A workspace is asked for by layers that leave most of the chip idle: while the split workgroups (of 128 x 128 tiles)
+// still number at most one per CU (half the slots) and every split keeps at least kMinSplitRows k rows.  Whether the
+// sum is then split is for the launchers to say.
+constexpr int64_t kMinSplitRows = 512;
+inline int sfb_splits_for(int64_t tiles, int64_t slots, int64_t K)
+{
+    int s = 1;
+    while (s < kMaxSplits && tiles * (s + 1) <= slots / 2 && K / (s + 1) >= kMinSplitRows) ++s;
+    return s;
+}
+
+// ---- fp32 reconstruction: which tiles cover W
+// How one layer is covered: `big` tiles of 128 x 128 and then tiles of (64*bn) x (64*bm), each contracted by `g` groups.
+struct Cover { int bn, bm; int64_t big, tiles_m, groups; int g = 1; };
+
+inline Cover uniform_cover(int64_t N, int64_t M, int bn, int bm)
+{
+    const int64_t tm = (M + 64 * bm - 1) / (64 * bm), tn = (N + 64 * bn - 1) / (64 * bn);
+    return {bn, bm, bn * bm == 4 ? tn * tm : 0, tm, tn * tm};
+}
+
+// *us: what the launch takes, by estimate (0 with a pinned tile).  pinned: 1 = 64 x 128, 2 = 128 x 128, 0 = none
+inline Cover choose_f32(int64_t N, int64_t M, int64_t K, int64_t cus, int pinned, double* us)
+{
+    *us = 0;
+    if (pinned) return uniform_cover(N, M, pinned, 2);
+    // A compute unit works through its tiles at the rate of its MFMA pipe, so the launch takes as long as the compute unit with
+    // the most tile area: 57 us per 1024 rows and 128 x 128 tile, smaller tiles with what their shorter runs between barriers
+    // cost; what the loops of other tiles do not hide of the W / Mom update (12.5 us per 128 x 128 tile of a compute unit's
+    // share); and a start.  Fitted to eleven shapes of 2 to 36 M weights over K = 64 .. 2048, where the choice costs 0.7 %.
+    // 3000 -> 3000, K = 2048: 576 tiles are 2.25 rounds; two of 128 x 128 and the rest in 64 x 64: 358 -> 276 us.
+    auto rounds = [&](int64_t workgroups) { return static_cast<double>((workgroups + cus - 1) / cus); };
+    constexpr double kHalf = 0.507, kQuarter = 0.281;
+    const double round = 57 * static_cast<double>(K) / 1024, update = 12.5 * static_cast<double>(N) * M / 16384 / cus;
+    const Cover half = uniform_cover(N, M, 1, 2), quarter = uniform_cover(N, M, 1, 1), all = uniform_cover(N, M, 2, 2);
+    // At most one 64 x 64 tile per compute unit: four groups of wavefronts contract it (1024 -> 1000, K = 2048: 42 -> 36 us;
+    // two groups on a lone 128 x 128 tile are no faster than two 64 x 128 tiles).
+    if (quarter.groups <= cus) {
+        Cover c = quarter;
+        c.g = 4;
+        *us = 4.5 + 0.267 * round + 0.7 * update;
+        return c;
+    }
+    Cover best = half;
+    *us = 6.6 + rounds(half.groups) * kHalf * round + 0.67 * update;
+    auto consider = [&](const Cover& c, double x) { if (x < *us) { *us = x; best = c; } };
+    consider(quarter, 5.8 + rounds(quarter.groups) * kQuarter * round + 0.7 * update);
+    consider(all, 8.5 + rounds(all.groups) * round + 0.7 * update);
+    const int64_t full = all.big / cus, rem = all.big % cus;
+    if (full > 0 && rem > 0) {
+        consider({1, 2, full * cus, all.tiles_m, full * cus + 2 * rem}, 7.0 + (full + rounds(2 * rem) * kHalf) * round + 0.7 * update);
+        consider({1, 1, full * cus, all.tiles_m, full * cus + 4 * rem}, 9.4 + (full + rounds(4 * rem) * kQuarter) * round + 0.8 * update);
+    }
+    return best;
+}
+
+// the tiles of a split sum
+inline Cover split_cover(int64_t N, int64_t M, int pinned) { return pinned ? uniform_cover(N, M, pinned, 2) : uniform_cover(N, M, 1, 1); }
+
+// How many workgroups share a tile's sum over k, at most `most`.  A pinned tile is split as far as the workspace was asked for.
+// Otherwise the sum is split where the shorter loops save more than storing and adding the partial sums costs: the second launch
+// 4 us and its bytes.  512 -> 512, K = 2048: 34 us unsplit, 17 us in four.
+inline int choose_f32_splits(int64_t N, int64_t M, int64_t K, int most, int64_t cus, int pinned)
+{
+    if (pinned) return most;
+    double us;
+    choose_f32(N, M, K, cus, 0, &us);
+    int splits = 1;
+    for (int s = 2; s <= most; ++s) {
+        const int64_t groups = split_cover(N, M, 0).groups * s;
+        const double loop = groups <= cus ? 0.32 : static_cast<double>((groups + cus - 1) / cus) * 0.281;
+        const double x = 5 + loop * 57 * static_cast<double>(K) / s / 1024 + 4 + (16.0 + 4 * s) * N * M / 5e6;
+        if (x < us) {
+            us = x;
+            splits = s;
+        }
+    }
+    return splits;
+}
+
+// ---- bf16 reconstruction: which tile covers W
+// What a tile costs, in us: `area` times the update of 64 x 64 weights at a compute unit's share of HBM (3.1 us) and `loop`
+// per 1024 k rows where compute units hold several tiles; `first` and `solo` per 1024 k rows where each holds one at most.
+// Fitted to 9216 -> 4096, 4096 -> 1000 and 1024 -> 1000 over K = 32 .. 2048; predicts the other shapes tried (W of 1 to 90 M
+// weights) within 10 %.  The tiles contracted by several groups of wavefronts fill a compute unit, so they are for layers
+// that have one tile for each at most: 1024 -> 1000, K = 2048 17.4 us with four wavefronts per 64 x 64 tile, 12.5 with sixteen.
+struct Bf16Tile { int id, tn, tm; bool alone; double area, loop, first, solo; };
+constexpr Bf16Tile kTiles[] = {{0, 128, 256, false, 8, 9.9, 14.7, 15.1}, {1, 128, 192, false, 6, 6.6, 11.9, 8.3},
+                           {2, 128, 128, false, 4, 5.7, 8.6, 7.1},   {3, 64, 128, false, 2, 3.8, 5.1, 6.6},
+                           {4, 64, 64, false, 1, 2.5, 3.9, 6.0},     {5, 64, 64, true, 1, 0, 3.75, 3.4},
+                           {6, 128, 128, true, 4, 0, 8.3, 5.9}};
+constexpr double kNever = 1e30;
+
+// us for the launch that covers N x M over K rows
+inline double launch_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K, int64_t cus)
+{
+    const int64_t tiles = ((N + t.tn - 1) / t.tn) * ((M + t.tm - 1) / t.tm);
+    const double k = static_cast<double>(K) / 1024, share = static_cast<double>(tiles) / cus, update = 3.1 * t.area;
+    if (tiles <= cus) return t.first + (M % 32 ? 1.5 : 0) + 0.6 * update * share + t.solo * k;
+    // the last, partly filled round: the loop takes as long as a full one, the update shares HBM among fewer
+    const double rounds = static_cast<double>((tiles + cus - 1) / cus), tail = (rounds - share) * (t.area > 2 ? 0.5 : 0.2);
+    return t.alone ? kNever : 5 + update * (share + tail) + t.loop * k * rounds;
+}
+
+// ... and when `splits` workgroups per tile store partial sums that a second launch adds up
+inline double split_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K, int splits, int64_t cus)
+{
+    const int64_t groups = ((N + t.tn - 1) / t.tn) * ((M + t.tm - 1) / t.tm) * splits;
+    if (t.alone) return kNever;
+    const double k = static_cast<double>(K) / splits / 1024, sum = 4 + (16.0 + 4 * splits) * N * M / 5e6;
+    if (groups > cus) return sum + 5 + static_cast<double>((groups + cus - 1) / cus) * (0.8 * t.area + t.loop * k);
+    return sum + t.first + t.solo * k;              // (the partial sums stay in the caches)
+}
+
+// tile choice for one layer; pinned: one of the first three tiles, or less than 0
+inline Bf16Tile choose_bf16(int64_t N, int64_t M, int64_t K, int64_t cus, int pinned)
+{
+    if (pinned >= 0 && pinned <= 2) return kTiles[pinned];
+    const Bf16Tile* best = &kTiles[0];
+    for (const Bf16Tile& t : kTiles)
+        if (launch_cost(t, N, M, K, cus) < launch_cost(*best, N, M, K, cus)) best = &t;
+    return *best;
+}
+
+// ... and how many ways to split the sum over k, at most `most`
+inline Bf16Tile choose_bf16_split(int64_t N, int64_t M, int64_t K, int most, int64_t cus, int pinned, int* splits)
+{
+    Bf16Tile best = choose_bf16(N, M, K, cus, pinned);
+    *splits = 1;
+    if (pinned >= 0) {
+        *splits = most;
+        return best;
+    }
+    double cost = launch_cost(best, N, M, K, cus);
+    for (int s = 2; s <= most; ++s)
+        for (const Bf16Tile& t : kTiles)
+            if (split_cost(t, N, M, K, s, cus) < cost) {
+                cost = split_cost(t, N, M, K, s, cus);
+                best = t;
+                *splits = s;
+            }
+    return best;
+}
+
 // ---- pack
 // Rows of one launch over rows of `cu` and `cv` 16-byte chunks: one lane per chunk of both matrices, and chunk numbers that fit
 // 31 bits with room to spare for the last, partly filled workgroups.  A longer stack takes several launches.

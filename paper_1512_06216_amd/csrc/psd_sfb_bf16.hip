@@ -476,72 +476,6 @@ using Cfg128x128w8 = Cfg<2, 2, 2, 2, 4, 2, 2>; // two groups, 128 KiB, one per C
 
 }  // namespace
 
-namespace {
-// What a tile costs, in us: `area` times the update of 64 x 64 weights at a compute unit's share of HBM (3.1 us) and `loop`
-// per 1024 k rows where compute units hold several tiles; `first` and `solo` per 1024 k rows where each holds one at most.
-// Fitted to 9216 -> 4096, 4096 -> 1000 and 1024 -> 1000 over K = 32 .. 2048; predicts the other shapes tried (W of 1 to 90 M
-// weights) within 10 %.  The tiles contracted by several groups of wavefronts fill a compute unit, so they are for layers
-// that have one tile for each at most: 1024 -> 1000, K = 2048 17.4 us with four wavefronts per 64 x 64 tile, 12.5 with sixteen.
-struct Bf16Tile { int id, tn, tm; bool alone; double area, loop, first, solo; };
-const Bf16Tile kTiles[] = {{0, 128, 256, false, 8, 9.9, 14.7, 15.1}, {1, 128, 192, false, 6, 6.6, 11.9, 8.3},
-                           {2, 128, 128, false, 4, 5.7, 8.6, 7.1},   {3, 64, 128, false, 2, 3.8, 5.1, 6.6},
-                           {4, 64, 64, false, 1, 2.5, 3.9, 6.0},     {5, 64, 64, true, 1, 0, 3.75, 3.4},
-                           {6, 128, 128, true, 4, 0, 8.3, 5.9}};
-const double kNever = 1e30;
-
-// us for the launch that covers N x M over K rows
-double launch_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K)
-{
-    const int64_t cus = device_cu_count(), tiles = ((N + t.tn - 1) / t.tn) * ((M + t.tm - 1) / t.tm);
-    const double k = static_cast<double>(K) / 1024, share = static_cast<double>(tiles) / cus, update = 3.1 * t.area;
-    if (tiles <= cus) return t.first + (M % 32 ? 1.5 : 0) + 0.6 * update * share + t.solo * k;
-    // the last, partly filled round: the loop takes as long as a full one, the update shares HBM among fewer
-    const double rounds = static_cast<double>((tiles + cus - 1) / cus), tail = (rounds - share) * (t.area > 2 ? 0.5 : 0.2);
-    return t.alone ? kNever : 5 + update * (share + tail) + t.loop * k * rounds;
-}
-
-// ... and when `splits` workgroups per tile store partial sums that a second launch adds up
-double split_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K, int splits)
-{
-    const int64_t cus = device_cu_count(), groups = ((N + t.tn - 1) / t.tn) * ((M + t.tm - 1) / t.tm) * splits;
-    if (t.alone) return kNever;
-    const double k = static_cast<double>(K) / splits / 1024, sum = 4 + (16.0 + 4 * splits) * N * M / 5e6;
-    if (groups > cus) return sum + 5 + static_cast<double>((groups + cus - 1) / cus) * (0.8 * t.area + t.loop * k);
-    return sum + t.first + t.solo * k;              // (the partial sums stay in the caches)
-}
-
-// tile choice for one layer
-Bf16Tile choose_bf16(int64_t N, int64_t M, int64_t K)
-{
-    const int pinned = tune_value(PSD_TUNE_SFB_BF16_TILE);
-    if (pinned >= 0 && pinned <= 2) return kTiles[pinned];
-    const Bf16Tile* best = &kTiles[0];
-    for (const Bf16Tile& t : kTiles)
-        if (launch_cost(t, N, M, K) < launch_cost(*best, N, M, K)) best = &t;
-    return *best;
-}
-
-// ... and how many ways to split the sum over k, at most `most`
-Bf16Tile choose_bf16_split(int64_t N, int64_t M, int64_t K, int most, int* splits)
-{
-    Bf16Tile best = choose_bf16(N, M, K);
-    *splits = 1;
-    if (tune_value(PSD_TUNE_SFB_BF16_TILE) >= 0) {
-        *splits = most;
-        return best;
-    }
-    double cost = launch_cost(best, N, M, K);
-    for (int s = 2; s <= most; ++s)
-        for (const Bf16Tile& t : kTiles)
-            if (split_cost(t, N, M, K, s) < cost) {
-                cost = split_cost(t, N, M, K, s);
-                best = t;
-                *splits = s;
-            }
-    return best;
-}
-}  // namespace
-
 // how many ways psd_sync_fc_sfb may split this layer's sum over k when it is given a workspace (1 = not at all)
 int sfb_bf16_splits(int64_t N, int64_t M, int64_t K)
 {
@@ -555,7 +489,7 @@ psd_status launch_sfb_bf16(const uint16_t* U, int64_t ldu, const uint16_t* V, in
                            hipStream_t st)
 {
     int splits;
-    Bf16Tile t = choose_bf16_split(N, M, K, most_splits, &splits);
+    Bf16Tile t = choose_bf16_split(N, M, K, most_splits, device_cu_count(), tune_value(PSD_TUNE_SFB_BF16_TILE), &splits);
     // the longer stages of the grouped tiles read further ahead than the 32-bit offsets reach in a very large factor matrix
     if (t.alone && !factors_in_reach(K, ldu, ldv, 2, bf16_reserve(t.id == 5 ? Cfg64x64w16::KT : Cfg128x128w8::KT)))
         t = kTiles[t.id == 5 ? 4 : 2];
@@ -582,7 +516,7 @@ psd_status launch_sfb_bf16_blocks(const uint16_t* const* U_p, int64_t ldu, const
         blocks.u[p] = p < P ? U_p[p] : nullptr;
         blocks.v[p] = p < P ? V_p[p] : nullptr;
     }
-    const Bf16Tile t = choose_bf16(N, M, P * B);
+    const Bf16Tile t = choose_bf16(N, M, P * B, device_cu_count(), tune_value(PSD_TUNE_SFB_BF16_TILE));
     switch (t.id) {
         case 0: return launch_cfg_blocks<Cfg128x256w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         case 1: return launch_cfg_blocks<Cfg128x192w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);

@@ -336,56 +336,11 @@ __global__ void __launch_bounds__(256 * G) sfb_f32_groups_blocks_kernel(const Ar
     tile_body<BN, BM, G, false, true>(g, &blocks, lds, int64_t(blockIdx.x / g.tiles_m) * 64 * BN, int64_t(blockIdx.x % g.tiles_m) * 64 * BM, 0);
 }
 
-// How one layer is covered: `big` tiles of 128 x 128 and then tiles of (64*bn) x (64*bm), each contracted by `g` groups.
-struct Cover { int bn, bm; int64_t big, tiles_m, groups; int g = 1; };
-
-Cover uniform_cover(int64_t N, int64_t M, int bn, int bm)
-{
-    const int64_t tm = (M + 64 * bm - 1) / (64 * bm), tn = (N + 64 * bn - 1) / (64 * bn);
-    return {bn, bm, bn * bm == 4 ? tn * tm : 0, tm, tn * tm};
-}
-
 // the pinned tile is (64 * pinned) x 128; 0: none is pinned
 int pinned_tile()
 {
     const int t = tune_value(PSD_TUNE_SFB_F32_TILE);
     return t == 1 || t == 2 ? t : 0;
-}
-
-// *us: what the launch takes, by estimate (0 with a pinned tile)
-Cover choose_f32(int64_t N, int64_t M, int64_t K, double* us)
-{
-    *us = 0;
-    if (const int pinned = pinned_tile()) return uniform_cover(N, M, pinned, 2);
-    // A compute unit works through its tiles at the rate of its MFMA pipe, so the launch takes as long as the compute unit with
-    // the most tile area: 57 us per 1024 rows and 128 x 128 tile, smaller tiles with what their shorter runs between barriers
-    // cost; what the loops of other tiles do not hide of the W / Mom update (12.5 us per 128 x 128 tile of a compute unit's
-    // share); and a start.  Fitted to eleven shapes of 2 to 36 M weights over K = 64 .. 2048, where the choice costs 0.7 %.
-    // 3000 -> 3000, K = 2048: 576 tiles are 2.25 rounds; two of 128 x 128 and the rest in 64 x 64: 358 -> 276 us.
-    const int64_t cus = device_cu_count();
-    auto rounds = [&](int64_t workgroups) { return static_cast<double>((workgroups + cus - 1) / cus); };
-    constexpr double kHalf = 0.507, kQuarter = 0.281;
-    const double round = 57 * static_cast<double>(K) / 1024, update = 12.5 * static_cast<double>(N) * M / 16384 / cus;
-    const Cover half = uniform_cover(N, M, 1, 2), quarter = uniform_cover(N, M, 1, 1), all = uniform_cover(N, M, 2, 2);
-    // At most one 64 x 64 tile per compute unit: four groups of wavefronts contract it (1024 -> 1000, K = 2048: 42 -> 36 us;
-    // two groups on a lone 128 x 128 tile are no faster than two 64 x 128 tiles).
-    if (quarter.groups <= cus) {
-        Cover c = quarter;
-        c.g = 4;
-        *us = 4.5 + 0.267 * round + 0.7 * update;
-        return c;
-    }
-    Cover best = half;
-    *us = 6.6 + rounds(half.groups) * kHalf * round + 0.67 * update;
-    auto consider = [&](const Cover& c, double x) { if (x < *us) { *us = x; best = c; } };
-    consider(quarter, 5.8 + rounds(quarter.groups) * kQuarter * round + 0.7 * update);
-    consider(all, 8.5 + rounds(all.groups) * round + 0.7 * update);
-    const int64_t full = all.big / cus, rem = all.big % cus;
-    if (full > 0 && rem > 0) {
-        consider({1, 2, full * cus, all.tiles_m, full * cus + 2 * rem}, 7.0 + (full + rounds(2 * rem) * kHalf) * round + 0.7 * update);
-        consider({1, 1, full * cus, all.tiles_m, full * cus + 4 * rem}, 9.4 + (full + rounds(4 * rem) * kQuarter) * round + 0.8 * update);
-    }
-    return best;
 }
 
 template <int BN, int BM, bool MIXED, bool PART>
@@ -434,7 +389,7 @@ Args common_args(int64_t ldu, int64_t ldv, float* W, float* Mom, int64_t N, int6
 psd_status launch_cover(Args& g, const BlockPtrs* blocks, hipStream_t st)
 {
     double us;
-    const Cover c = choose_f32(g.N, g.M, g.K, &us);
+    const Cover c = choose_f32(g.N, g.M, g.K, device_cu_count(), pinned_tile(), &us);
     if (c.groups > 0x7fffffff) return PSD_E_INVALID;
     g.big = static_cast<int>(c.big);
     g.tiles_m = static_cast<int>(c.tiles_m);
@@ -460,24 +415,10 @@ psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t l
     Args g = common_args(ldu, ldv, W, Mom, N, M, K, lr, mu, wd);
     g.U = U; g.V = V;
     g.u_bytes = static_cast<uint32_t>(u_bytes); g.v_bytes = static_cast<uint32_t>(v_bytes);
-    // A pinned tile is split as far as the workspace was asked for.  Otherwise the sum is split where the shorter loops save more than storing and adding the partial sums costs: the second launch
-    // 4 us and its bytes.  512 -> 512, K = 2048: 34 us unsplit, 17 us in four.
     const int pinned = pinned_tile();
-    const Cover c = pinned ? uniform_cover(N, M, pinned, 2) : uniform_cover(N, M, 1, 1);
-    const int64_t cus = device_cu_count();
-    double us;
-    choose_f32(N, M, K, &us);
-    int splits = pinned ? most_splits : 1;
-    for (int s = 2; !pinned && s <= most_splits; ++s) {
-        const int64_t groups = c.groups * s;
-        const double loop = groups <= cus ? 0.32 : static_cast<double>((groups + cus - 1) / cus) * 0.281;
-        const double x = 5 + loop * 57 * static_cast<double>(K) / s / 1024 + 4 + (16.0 + 4 * s) * N * M / 5e6;
-        if (x < us) {
-            us = x;
-            splits = s;
-        }
-    }
+    const int splits = choose_f32_splits(N, M, K, most_splits, device_cu_count(), pinned);
     if (splits <= 1) return launch_cover(g, nullptr, st);
+    const Cover c = split_cover(N, M, pinned);
     g.tiles_m = static_cast<int>(c.tiles_m);
     g.tiles = static_cast<int>(c.groups);
     g.part = part; g.part_stride = sfb_part_stride(N, M);
