@@ -8,4 +8,20 @@ int32_t dense_chunks(int64_t n, int32_t S, int32_t threads) { return psd::dense_
 int64_t pack_rows(int64_t cu, int64_t cv) { return psd::pack_rows_per_launch(cu, cv); }
 int32_t f32_reach(int64_t K, int64_t ldu, int64_t ldv) { return psd::factors_in_reach(K, ldu, ldv, 4, psd::kF32Reserve); }
 int32_t bf16_reach(int64_t K, int64_t ldu, int64_t ldv, int64_t rows) { return psd::factors_in_reach(K, ldu, ldv, 2, psd::bf16_reserve(rows)); }
+// 10 * tile + workgroups per tile
+int32_t bf16_choice(int64_t N, int64_t M, int64_t K, int most, int64_t cus)
+{
+    int splits;
+    const psd::Bf16Tile t = psd::choose_bf16_split(N, M, K, most, cus, -1, &splits);
+    return 10 * t.id + splits;
+}
+int32_t splits_asked(int64_t tiles, int64_t cus, int64_t K) { return psd::sfb_splits_for(tiles, 2 * cus, K); }
+// bn, bm, whether there are 128 x 128 tiles before them, groups: as decimal digits
+int32_t f32_choice(int64_t N, int64_t M, int64_t K, int64_t cus)
+{
+    double us;
+    const psd::Cover c = psd::choose_f32(N, M, K, cus, 0, &us);
+    return 1000 * c.bn + 100 * c.bm + 10 * (c.big > 0) + c.g;
+}
+int32_t f32_splits(int64_t N, int64_t M, int64_t K, int most, int64_t cus) { return psd::choose_f32_splits(N, M, K, most, cus, 0); }
 }

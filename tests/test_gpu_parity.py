@@ -245,7 +245,7 @@ def pinned_tile():
 @pytest.mark.parametrize("M,N,B,P", [(520, 300, 11, 5),       # ragged tiles both ways, K tail, K shorter than the row prefetch
                                      (700, 260, 160, 9)])     # K = 1440: past the unrolled prefetch stages, ragged stage tail
 def test_sfb_bf16_every_tile_shape_bit_exact(tile, M, N, B, P, pinned_tile):
-    # every kernel instantiation the tile heuristic can pick (and the tuning-only one)
+    # the three tiles that can be pinned
     pinned_tile(psd.TUNE_SFB_BF16_TILE, tile)
     d = inputs.fc_layer_integer(M=M, N=N, B=B, P=P, seed=tile + 50, amax=2 if B * P > 1000 else 3)
     Wg, Mg, _ = run_sfb(d, psd.BF16, 0.25, 0.5)
@@ -272,6 +272,54 @@ def test_sfb_f32_both_tile_shapes_bit_exact(tile, pinned_tile):
     U, V = orc.pack_factors(d["delta"], d["act"])
     Wr, Mr = orc.sync_fc_sfb(U, V, d["W"], d["Mom"], 0.25, 0.5)
     assert np.array_equal(Mg, Mr) and np.array_equal(Wg, Wr)
+
+
+# Layers for which the rules choose each tile, with rows of W on cache lines and not, and K such that the ring of LDS buffers goes
+# round.  (tests/test_rules.py checks that the rules do choose them, on 256 compute units.)
+BF16_TILE_LAYERS = [  # tile, M, N, B, P
+    (0, 4768, 3055, 32, 6), (0, 4783, 3055, 32, 6), (1, 3040, 1642, 32, 6), (1, 1329, 4311, 32, 6), (2, 1952, 3683, 32, 6),
+    (2, 1957, 3683, 32, 6), (3, 5536, 130, 32, 6), (3, 5881, 130, 32, 6), (4, 288, 5567, 32, 6), (4, 5567, 130, 32, 6),
+    (5, 64, 64, 32, 20), (5, 65, 64, 64, 10), (6, 5536, 328, 32, 10), (6, 4939, 592, 64, 5)]
+BF16_SPLIT_LAYERS = [  # tile, workgroups per tile, M, N, B, P
+    (2, 2, 10944, 128, 1024, 8), (2, 3, 4155, 196, 512, 8), (3, 4, 2692, 65, 375, 8), (3, 4, 2689, 65, 375, 8),
+    (4, 4, 64, 64, 750, 4), (4, 4, 65, 64, 750, 4)]
+F32_COVER_LAYERS = [  # 1000 * bn + 100 * bm + 10 * (128 x 128 tiles before them) + groups, M, N, B, P
+    (1104, 64, 64, 48, 6), (1104, 65, 64, 16, 18), (1101, 5536, 130, 32, 2), (1101, 5567, 130, 16, 4), (1201, 5536, 130, 64, 4),
+    (1201, 5567, 130, 64, 4), (1111, 2720, 1485, 128, 8), (1111, 1485, 2741, 128, 8), (1211, 4928, 1799, 128, 8),
+    (1211, 1799, 4939, 128, 8), (2211, 5536, 526, 512, 8), (2211, 4939, 592, 512, 8)]
+
+
+@pytest.mark.parametrize("dtype,M,N,B,P", [(psd.BF16, *c[1:]) for c in BF16_TILE_LAYERS] + [(psd.F32, *c[1:]) for c in F32_COVER_LAYERS])
+def test_sfb_every_tile_the_rules_choose_bit_exact(dtype, M, N, B, P):
+    """Stacked, and the same rows read in place as P blocks."""
+    d = inputs.fc_layer_integer(M, N, B, P, seed=M + N)
+    plan, U, ldu, V, ldv = run_pack(d, dtype)
+    Uo, Vo = orc.pack_factors(d["delta"], d["act"])
+    Wr, Mr = orc.sync_fc_sfb(Uo, Vo, d["W"], d["Mom"], 0.25, 0.5, wd=0.25)
+    W, Mom = dev(d["W"]), dev(d["Mom"])
+    psd.sync_fc_sfb(plan, dtype, U, ldu, V, ldv, W, Mom, 0.25, 0.5, wd=0.25)
+    torch.cuda.synchronize()
+    assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr)
+    W, Mom = dev(d["W"]), dev(d["Mom"])
+    psd.sync_fc_sfb_blocks(plan, dtype, list(U.split(B)), ldu, list(V.split(B)), ldv, W, Mom, 0.25, 0.5, wd=0.25)
+    torch.cuda.synchronize()
+    assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr)
+
+
+@pytest.mark.parametrize("tile,splits,M,N,B,P", BF16_SPLIT_LAYERS)
+def test_sfb_bf16_every_tile_that_is_split_bit_exact(tile, splits, M, N, B, P):
+    d = inputs.fc_layer_integer(M, N, B, P, seed=M + N)
+    plan, U, ldu, V, ldv = run_pack(d, psd.BF16)
+    stride = (N * M + 3) // 4 * 4
+    ws = torch.full((4 * stride,), float("nan"), device=DEV)
+    W, Mom = dev(d["W"]), dev(d["Mom"])
+    psd.sync_fc_sfb(plan, psd.BF16, U, ldu, V, ldv, W, Mom, 0.25, 0.5, wd=0.25, workspace=ws)
+    torch.cuda.synchronize()
+    Uo, Vo = orc.pack_factors(d["delta"], d["act"])
+    Wr, Mr = orc.sync_fc_sfb(Uo, Vo, d["W"], d["Mom"], 0.25, 0.5, wd=0.25)
+    assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr)
+    written = ~torch.isnan(ws.view(4, stride)[:, :N * M])
+    assert bool(written[:splits].all()) and not bool(written[splits:].any())
 
 
 @pytest.mark.parametrize("M,N", [(2181, 2170),       # 306 tiles of 128 x 128 on 256 compute units: the last 50 as 64 x 64; odd rows
@@ -366,8 +414,9 @@ def test_weight_decay_gaussian_within_tolerance():
         assert max(e) <= TOL_F32, (name, e)
 
 
-SPLIT_SHAPES = [  # M, N, B, P: few output tiles and K >= 1024, so that a workspace makes the kernels split K
-    (1024, 1000, 256, 8),      # GoogLeNet-sized classifier at batch 256 per worker: 64 tiles, split in four
+SPLIT_SHAPES = [  # M, N, B, P: few output tiles and K >= 1024, so that a workspace lets the kernels split K (where the rules
+                  # find it faster; BF16_SPLIT_LAYERS and the pinned tiles reach every kernel that does)
+    (1024, 1000, 256, 8),      # GoogLeNet-sized classifier at batch 256 per worker: 64 tiles, room for four partial sums
     (520, 300, 220, 5),        # ragged tiles both ways, K = 1100: ragged last stage and uneven splits
     (521, 130, 128, 9),        # rows of W not 16-byte aligned (element-wise epilogue), K = 1152
     (128, 128, 512, 4),        # a single tile, K = 2048: the deepest split
@@ -377,7 +426,7 @@ SPLIT_SHAPES = [  # M, N, B, P: few output tiles and K >= 1024, so that a worksp
 @pytest.mark.parametrize("M,N,B,P", SPLIT_SHAPES)
 @pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
 def test_sfb_split_k_with_workspace_bit_exact_and_equal_to_unsplit(M, N, B, P, dtype):
-    """With a workspace the sum over k is split over several workgroups per tile and finished by the
+    """With a workspace the sum over k may be split over several workgroups per tile and finished by the
     parameter-server sum kernel.  Integer-valued factors: bit-exact against the oracle; Gaussian factors:
     within tolerance of the oracle and of the unsplit kernel."""
     d = inputs.fc_layer_integer(M, N, B, P, seed=M + 3 * N)

@@ -6,6 +6,7 @@ import subprocess
 import pytest
 
 from paper_1512_06216_amd import build
+from tests import test_gpu_parity as parity
 from tests.conftest import ROOT
 
 
@@ -15,10 +16,12 @@ def rules(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-shared", "-fPIC", "-I", build.CSRC, "-I", os.path.join(ROOT, "include"),
                     os.path.join(ROOT, "tests", "host", "rules.cpp"), "-o", so], check=True)
     L = ctypes.CDLL(so)
-    i32, i64 = ctypes.c_int32, ctypes.c_int64
+    i32, i64, c_int = ctypes.c_int32, ctypes.c_int64, ctypes.c_int
     for name, res, args in (("max_items", i64, []), ("dense_threads", i32, [i64, i64]), ("dense_chunks", i32, [i64, i32, i32]),
                             ("pack_rows", i64, [i64, i64]), ("f32_reach", i32, [i64, i64, i64]),
-                            ("bf16_reach", i32, [i64, i64, i64, i64])):
+                            ("bf16_reach", i32, [i64, i64, i64, i64]), ("bf16_choice", i32, [i64, i64, i64, c_int, i64]),
+                            ("splits_asked", i32, [i64, i64, i64]), ("f32_choice", i32, [i64, i64, i64, i64]),
+                            ("f32_splits", i32, [i64, i64, i64, c_int, i64])):
         getattr(L, name).restype, getattr(L, name).argtypes = res, args
     return L
 
@@ -80,3 +83,33 @@ def test_bf16_offsets_of_every_stage_requested_stay_below_2_to_the_32(rules):
                 if rules.bf16_reach(K, ld, 8, rows):
                     last = -(-K // rows) * rows + 3 * rows - 1   # row of the last stage requested
                     assert (last * ld + ld + 255) * 2 < 2 ** 32
+
+
+CUS = 256
+
+
+def test_the_parity_tests_reach_every_tile_stacked_from_blocks_and_split(rules):
+    """Every kernel of the reconstructions: tiles, with rows of W on lines and not (the grouped ones make no difference)."""
+    seen = set()
+    for tile, M, N, B, P in parity.BF16_TILE_LAYERS:
+        assert rules.bf16_choice(N, M, B * P, 1, CUS) == 10 * tile + 1, (M, N)
+        assert B % 32 == 0 and B * P > 128 * {5: 4, 6: 2}.get(tile, 1)
+        seen.add((tile, M % 32 == 0))
+    assert seen == {(t, lines) for t in range(7) for lines in (True, False)}
+    seen = set()
+    for tile, splits, M, N, B, P in parity.BF16_SPLIT_LAYERS:
+        most = rules.splits_asked(-(-N // 128) * -(-M // 128), CUS, B * P)
+        assert most >= splits and rules.bf16_choice(N, M, B * P, most, CUS) == 10 * tile + splits, (M, N)
+        seen.add((tile, M % 4 == 0))
+    assert seen == {(t, quads) for t in (2, 3, 4) for quads in (True, False)}       # (tiles 0 and 1: only when pinned)
+    seen = set()
+    for cover, M, N, B, P in parity.F32_COVER_LAYERS:
+        assert rules.f32_choice(N, M, B * P, CUS) == cover and B % 16 == 0, (M, N, rules.f32_choice(N, M, B * P, CUS))
+        seen.add((cover, M % 32 == 0))
+    assert seen == {(c, lines) for c in (1104, 1101, 1201, 1111, 1211, 2211) for lines in (True, False)}
+    split = set()                                              # fp32, 64 x 64 tiles; rows of W on quads and anywhere
+    for M, N, B, P in parity.SPLIT_SHAPES:
+        most = rules.splits_asked(-(-N // 128) * -(-M // 128), CUS, B * P)
+        if rules.f32_splits(N, M, B * P, most, CUS) > 1:
+            split.add(M % 4 == 0)
+    assert split == {True, False}
