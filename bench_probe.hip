@@ -4,6 +4,7 @@
 //     ./bench_probe stream          # bare streams: what HBM gives a "P reads + read-modify-write of two arrays" pattern
 //     ./bench_probe coresident      # MFMA-only workgroups and streaming workgroups sharing the compute units
 //     ./bench_probe xcd             # the same read-modify-write stream from the CUs of 1, 2, 4 or all 8 XCDs only
+//     ./bench_probe issue           # what other instructions between two MFMAs cost the MFMA pipe
 // Every access is bounds-checked by construction (fixed sizes below); every loop has a fixed trip count.
 #include <hip/hip_runtime.h>
 #include <cstdio>
@@ -248,6 +249,92 @@ static void run_xcd(hipEvent_t e0, hipEvent_t e1)
             }
 }
 
+// ---------------------------------------------------------------------------------------------------
+// issue: N instructions of one kind between every two MFMAs of a wavefront (operands in registers, four independent
+// accumulators, so that the pipe never waits for a result)
+// ---------------------------------------------------------------------------------------------------
+enum { VALU, SALU, LDS_READ };
+
+template <bool BF16, int KIND, int N>
+__global__ void issue_kernel(float* __restrict__ out, long long* __restrict__ clocks, int iters)
+{
+    __shared__ float lds[1024];
+    lds[threadIdx.x] = threadIdx.x * 0.001f;
+    __syncthreads();
+    f32x16 acc[4] = {};
+    const float a = 1.0f + threadIdx.x * 0.01f, b = 0.5f - threadIdx.x * 0.02f;
+    bf16x8 va, vb;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { va[i] = static_cast<__bf16>(a + i); vb[i] = static_cast<__bf16>(b - i); }
+    unsigned x[4] = {threadIdx.x, 1, 2, 3}, s = 0;
+    float r[4] = {};
+    const unsigned at = static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) float*)lds)) + (threadIdx.x & 63) * 4;
+    __syncthreads();
+    const long long t0 = clock64();
+    for (int i = 0; i < iters; ++i) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            if constexpr (BF16) acc[k & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, vb, acc[k & 3], 0, 0, 0);
+            else acc[k & 3] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc[k & 3], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                if constexpr (KIND == VALU) asm volatile("v_add_u32 %0, 1, %0" : "+v"(x[j & 3]));
+                if constexpr (KIND == SALU) asm volatile("s_add_u32 %0, %0, 1" : "+s"(s) : : "scc");
+                if constexpr (KIND == LDS_READ) asm volatile("ds_read_b32 %0, %1" : "=v"(r[j & 3]) : "v"(at));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (KIND == LDS_READ) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]));
+    }
+    __syncthreads();                                                     // all wavefronts of the SIMD have issued theirs
+    const long long t1 = clock64();
+    float sum = s + x[0] + x[1] + x[2] + x[3] + r[0] + r[1] + r[2] + r[3];
+    for (int k = 0; k < 4; ++k)
+        for (int i = 0; i < 16; ++i) sum += acc[k][i];
+    out[size_t(blockIdx.x) * blockDim.x + threadIdx.x] = sum;
+    if (threadIdx.x == 0) clocks[blockIdx.x] = t1 - t0;
+}
+
+template <bool BF16, int KIND, int N>
+static void run_issue(const char* what, float* out, long long* clocks)
+{
+    const int iters = 2000, grid = 256;
+    for (int lanes : {256, 512}) {                                       // one and two wavefronts per SIMD
+        double best = 1e30;
+        for (int rep = 0; rep < 4; ++rep) {
+            issue_kernel<BF16, KIND, N><<<grid, lanes>>>(out, clocks, iters);
+            std::vector<long long> h(grid);
+            CK(hipMemcpy(h.data(), clocks, grid * sizeof(long long), hipMemcpyDeviceToHost));
+            double mean = 0;
+            for (long long c : h) mean += double(c) / grid;
+            mean /= iters * 16.0 * (lanes / 256);
+            if (rep > 0 && mean < best) best = mean;
+        }
+        printf("  %s, %d %-10s between MFMAs, %d wavefront%s per SIMD: %6.2f clocks per MFMA\n", BF16 ? "bf16 32x32x16" : "fp32 32x32x2 ", N, what,
+               lanes / 256, lanes > 256 ? "s" : " ", best);
+    }
+}
+
+template <bool BF16>
+static void run_issue_all()
+{
+    float* out;
+    long long* clocks;
+    CK(hipMalloc(&out, 256 * 512 * sizeof(float)));
+    CK(hipMalloc(&clocks, 256 * sizeof(long long)));
+    run_issue<BF16, VALU, 0>("vector adds", out, clocks);
+    run_issue<BF16, VALU, 1>("vector adds", out, clocks);
+    run_issue<BF16, VALU, 2>("vector adds", out, clocks);
+    run_issue<BF16, VALU, 4>("vector adds", out, clocks);
+    run_issue<BF16, SALU, 1>("scalar adds", out, clocks);
+    run_issue<BF16, SALU, 4>("scalar adds", out, clocks);
+    run_issue<BF16, LDS_READ, 1>("LDS reads", out, clocks);
+    run_issue<BF16, LDS_READ, 2>("LDS reads", out, clocks);
+    CK(hipFree(out));
+    CK(hipFree(clocks));
+}
+
 int main(int argc, char** argv)
 {
     hipEvent_t e0, e1; CK(hipEventCreate(&e0)); CK(hipEventCreate(&e1));
@@ -269,8 +356,12 @@ int main(int argc, char** argv)
     } else if (!strcmp(what, "xcd")) {
         printf("read-modify-write stream of two arrays (2.36 MB per array and workgroup) from the CUs of a subset of the XCDs:\n");
         run_xcd(e0, e1);
+    } else if (!strcmp(what, "issue")) {
+        printf("clocks from one MFMA to the next of a SIMD (clock64 over 32 000 MFMAs per wavefront, 256 workgroups, best of 3 means):\n");
+        run_issue_all<false>();
+        run_issue_all<true>();
     } else {
-        printf("usage: bench_probe stream|coresident|xcd\n");
+        printf("usage: bench_probe stream|coresident|xcd|issue\n");
         return 2;
     }
     return 0;

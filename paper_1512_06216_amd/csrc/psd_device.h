@@ -51,9 +51,10 @@ __device__ __forceinline__ i32x4 raw_rsrc(const void* X, uint32_t bytes)
     return r;
 }
 
-// A matrix that is fed to LDS from the top down: what is left of it, all in scalar registers.  The MFMA loops move on by
-// advancing the descriptor instead of the lanes' offsets: a vector add between two MFMAs keeps the matrix pipe waiting for
-// about 12 clocks (four adds 24), scalar instructions, LDS reads and waits cost it nothing.
+// A matrix that is fed to LDS from the top down: what is left of it, all in scalar registers.  The fp32 MFMA loop moves on by
+// advancing the descriptor instead of the lanes' offsets: a vector add between two fp32 MFMAs keeps the matrix pipe waiting for
+// 14 clocks (four adds for 26; 7 and 13 with two wavefronts per SIMD), scalar adds and LDS reads for less than one (bench_probe
+// issue).  The bf16 pipe does not wait for vector adds (1 clock), so the bf16 loop adds to the lanes' offsets.
 struct Feed {
     uint64_t base;
     uint32_t left;                                // bytes; the range check returns zeros past them
