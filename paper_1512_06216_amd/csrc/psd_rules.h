@@ -134,14 +134,16 @@ inline int choose_f32_splits(int64_t N, int64_t M, int64_t K, int most, int64_t 
 // ---- bf16 reconstruction: which tile covers W
 // What a tile costs, in us: `area` times the update of 64 x 64 weights at a compute unit's share of HBM (3.1 us) and `loop`
 // per 1024 k rows where compute units hold several tiles; `first` and `solo` per 1024 k rows where each holds one at most.
-// Fitted to 9216 -> 4096, 4096 -> 1000 and 1024 -> 1000 over K = 32 .. 2048; predicts the other shapes tried (W of 1 to 90 M
-// weights) within 10 %.  The tiles contracted by several groups of wavefronts fill a compute unit, so they are for layers
+// Fitted to 9216 -> 4096, 4096 -> 1000 and 1024 -> 1000 over K = 32 .. 2048.  Against what launches alone take: 3000 -> 21841 352
+// for 392 us, 4096 -> 21841 479 for 447, 25088 -> 4096 540 for 535, 4096 -> 4096 94 for 97, 3000 -> 3000 64 for 67, 4096 -> 1000
+// 27.5 for 30.5, 1024 -> 1000, K = 256 6.5 for 6.4; 9216 -> 4096 within 4 % for K = 512 .. 2048, 11 % short at K = 32, 12 % at
+// K = 4096.  The tiles contracted by several groups of wavefronts fill a compute unit, so they are for layers
 // that have one tile for each at most: 1024 -> 1000, K = 2048 17.4 us with four wavefronts per 64 x 64 tile, 12.5 with sixteen.
 struct Bf16Tile { int id, tn, tm; bool alone; double area, loop, first, solo; };
 constexpr Bf16Tile kTiles[] = {{0, 128, 256, false, 8, 9.9, 14.7, 15.1}, {1, 128, 192, false, 6, 6.6, 11.9, 8.3},
-                           {2, 128, 128, false, 4, 5.7, 8.6, 7.1},   {3, 64, 128, false, 2, 3.8, 5.1, 6.6},
-                           {4, 64, 64, false, 1, 2.5, 3.9, 6.0},     {5, 64, 64, true, 1, 0, 3.75, 3.4},
-                           {6, 128, 128, true, 4, 0, 8.3, 5.9}};
+                               {2, 128, 128, false, 4, 5.7, 8.6, 7.1},   {3, 64, 128, false, 2, 3.8, 5.1, 6.6},
+                               {4, 64, 64, false, 1, 2.5, 3.9, 6.0},     {5, 64, 64, true, 1, 0, 3.75, 3.4},
+                               {6, 128, 128, true, 4, 0, 8.3, 5.9}};
 constexpr double kNever = 1e30;
 
 // us for the launch that covers N x M over K rows

@@ -341,8 +341,8 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
     } else {
         // Rows of W start anywhere in a cache line: the rows of one bn of all wavefronts go through LDS at a time and come back
         // as whole lines of W (RowUpdate).  With the patch above every access would straddle two lines: 3000 -> 21841,
-        // K = 2048 468 -> 401 us; rows that are not even 16-byte aligned (3001 -> 21841), element by element before,
-        // 1873 -> 445 us.
+        // K = 2048 468 -> 392 us; rows that are not even 16-byte aligned (3001 -> 21841), element by element before,
+        // 1873 -> 420 us.
         float* buf = reinterpret_cast<float*>(lds);
 #pragma unroll
         for (int bn = 0; bn < C::BN; ++bn) {
