@@ -79,7 +79,7 @@ psd_status psd_shard_range(int64_t n, int32_t S, int32_t s, int64_t* begin, int6
  * cols rounded up to a multiple of 128 bytes (32 f32 or 64 bf16 elements), so that every row starts
  * on a cache-line boundary.  The entry points accept any leading dimension >= cols whose rows are a
  * multiple of 16 bytes (4 f32 / 8 bf16 elements); rows that start mid-line cost the bf16
- * reconstruction of odd-width layers 3-7 % (a 256-byte tile row then spans three lines, not two).
+ * reconstruction of odd-width layers 8-9 % (a 256-byte tile row then spans three lines, not two).
  * Returns 0 for bad arguments. */
 int64_t psd_factor_ld(int64_t cols, int32_t dtype);
 

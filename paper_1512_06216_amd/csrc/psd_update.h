@@ -36,6 +36,16 @@ __device__ __forceinline__ void store_stream4(float* p, float4 x)
     __builtin_nontemporal_store(v, reinterpret_cast<f32x4_nt*>(p));
 }
 
+// The same number, of which the compiler does not know that it is: what is computed from it anew does not stay in registers
+// from where it was computed before.
+__device__ __forceinline__ int anew(int x)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    asm("" : "+v"(x));
+#endif
+    return x;
+}
+
 // ---- Update of W and Mom from rows of dW in LDS ------------------------------------------------------------
 // A cache line holds 32 fp32.  Row n of W starts `line_shift(n)` elements into a line, a different number for every row
 // unless M is a multiple of 32, so a fixed split of a tile's columns over lanes makes every 128-byte access straddle two
@@ -110,7 +120,7 @@ struct RowUpdate {
         int at;
         bool any;
     };
-    __device__ __forceinline__ End end(int e) const
+    __device__ __forceinline__ End end(int e, int lane) const
     {
         const int group = wave + WAVES * e, r = group * 8 + (lane >> 3), i = lane & 3;
         const int64_t n = row_n(r);
@@ -139,7 +149,7 @@ struct RowUpdate {
         if (B == 0 && M % 4 != 0) {
 #pragma unroll
             for (int e = 0; e < ENDS; ++e) {
-                const End p = end(e);
+                const End p = end(e, lane);
                 if (!p.any) continue;
                 w_end[e] = W[p.off];
                 mo_end[e] = Mom[p.off];
@@ -175,19 +185,23 @@ struct RowUpdate {
                     *reinterpret_cast<float4*>(W + p.off) = wv;
                 }
             }
+            if constexpr (B == 0) run_ends(buf, lr, mu, wd);
             run<B + 1>(buf, lr, mu, wd);
-        } else if (M % 4 != 0) {
+        }
+    }
+    __device__ __forceinline__ void run_ends(const float* buf, float lr, float mu, float wd)
+    {
+        if (M % 4 == 0) return;
 #pragma unroll
-            for (int e = 0; e < ENDS; ++e) {
-                const End p = end(e);
-                if (!p.any) continue;
-                float d = buf[p.at];
+        for (int e = 0; e < ENDS; ++e) {
+            const End p = end(e, anew(lane));
+            if (!p.any) continue;
+            float d = buf[p.at];
 #pragma unroll
-                for (int i = 1; i < PARTS; ++i) d += buf[i * ROWS * stride + p.at];
-                upd(d, w_end[e], mo_end[e], lr, mu, wd);
-                Mom[p.off] = mo_end[e];
-                W[p.off] = w_end[e];
-            }
+            for (int i = 1; i < PARTS; ++i) d += buf[i * ROWS * stride + p.at];
+            upd(d, w_end[e], mo_end[e], lr, mu, wd);
+            Mom[p.off] = mo_end[e];
+            W[p.off] = w_end[e];
         }
     }
 };
@@ -240,7 +254,7 @@ struct InnerUpdate {
         int at;
         bool any;
     };
-    __device__ __forceinline__ End end(int e) const
+    __device__ __forceinline__ End end(int e, int lane) const
     {
         const int r = (wave + WAVES * e) * 8 + (lane >> 3), i = lane & 3;
         const int64_t n = row_n(r);
@@ -266,7 +280,7 @@ struct InnerUpdate {
         if (!ON_LINES && B == 0 && M % 4 != 0) {
 #pragma unroll
             for (int e = 0; e < GROUPS; ++e) {
-                const End p = end(e);
+                const End p = end(e, lane);
                 if (!p.any) continue;
                 w_end[e] = W[p.off];
                 mo_end[e] = Mom[p.off];
@@ -302,16 +316,20 @@ struct InnerUpdate {
                     *reinterpret_cast<float4*>(W + p.off) = wv;
                 }
             }
+            if constexpr (!ON_LINES && B == 0) run_ends(buf, lr, mu, wd);
             run<B + 1>(buf, lr, mu, wd);
-        } else if (!ON_LINES && M % 4 != 0) {
+        }
+    }
+    __device__ __forceinline__ void run_ends(const float* buf, float lr, float mu, float wd)
+    {
+        if (M % 4 == 0) return;
 #pragma unroll
-            for (int e = 0; e < GROUPS; ++e) {
-                const End p = end(e);
-                if (!p.any) continue;
-                upd(buf[p.at], w_end[e], mo_end[e], lr, mu, wd);
-                Mom[p.off] = mo_end[e];
-                W[p.off] = w_end[e];
-            }
+        for (int e = 0; e < GROUPS; ++e) {
+            const End p = end(e, anew(lane));
+            if (!p.any) continue;
+            upd(buf[p.at], w_end[e], mo_end[e], lr, mu, wd);
+            Mom[p.off] = mo_end[e];
+            W[p.off] = w_end[e];
         }
     }
 };
