@@ -34,7 +34,7 @@ sys.path.insert(0, ROOT)
 
 METRIC = "SFB reconstruct+update TFLOP/s (MFMA util %); dense shard-sum GB/s; ms/iter"
 PEAK_HBM_GBS = 8000.0
-PEAK_MFMA_TFLOPS = {"bf16": 2500.0, "f32": 157.3}
+PEAK_MFMA_TFLOPS = {"bf16": 2500.0, "f32": 2500.0 / 6}   # fp32 factors: six bf16 products for one (157.3 on the fp32 MFMA)
 PREWARM_MS = 150.0      # untimed work before the W warm-up steps: the clocks of an idle GPU take ~0.1 s to settle
 
 # HBM bytes per launch of the dominant kernel measured with rocprofv3 --pmc (FETCH_SIZE and
@@ -342,7 +342,7 @@ def roofline_of(leg, dur, layers, name, alone=True):
     else:
         r = dict(bound="mfma", achieved=inside["mfma_tflops"], peak=peak_tf, unit="TFLOP/s", frac=inside["mfma_frac"],
                  traffic=MEASURED_TRAFFIC_BYTES["f32"])
-    r.update(kernel="sfb_%s_kernel, fc6 launches (9216 -> 4096, K = 2048)" % name,
+    r.update(kernel="%s, fc6 launches (9216 -> 4096, K = 2048)" % {"bf16": "sfb_bf16_kernel", "f32": "sfb_f32_planes_kernel"}[name],
              algorithmic_bytes_per_launch=int(w["bytes"]), flops_per_launch=int(w["flops"]),
              note="achieved / frac: mean launch duration inside the timed iterations (other layers' kernels run "
                   "beside it on their own streams); 'alone': the same launch back to back with an idle GPU",

@@ -104,7 +104,8 @@ psd_status psd_pack_factors(const psd_plan* plan, const float* const* delta_p,
  *                                                      gives plain momentum SGD)
  * U, V [dev] as written by psd_pack_factors (same dtype and leading dimensions);
  * W, Mom [dev] N x M fp32 row-major, updated in place; dW is never stored.
- * fp32 factors: fp32 MFMA, fp32 accumulation.  bf16 factors: bf16 MFMA with fp32
+ * fp32 factors: fp32 accumulation; small layers and short contractions on the fp32 MFMA, the others on the bf16 MFMA with every
+ * factor cut into three bf16 numbers that add up to it exactly (no further from the sum in 64 bits).  bf16 factors: bf16 MFMA with fp32
  * accumulation; W and Mom stay fp32.  The same call serves the SF_PS route (the server
  * runs the identical reconstruction over the same P*B factors).
  * Size limit: the kernels address each stacked factor matrix with 32-bit byte offsets, so K * ldu and

@@ -76,6 +76,11 @@ psd_status launch_pack(PackArgs& a, int32_t out_dtype, hipStream_t st);
 psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t ldv, float* W, float* Mom,
                           int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int most_splits,
                           hipStream_t st);
+// ... on the bf16 pipe, from factors cut into three bf16 planes; `tile`: see kPlaneTiles
+psd_status launch_sfb_f32_planes(int tile, const float* U, int64_t ldu, const float* V, int64_t ldv, float* W, float* Mom, int64_t N,
+                                 int64_t M, int64_t K, float lr, float mu, float wd, hipStream_t st);
+psd_status launch_sfb_f32_planes_blocks(int tile, const float* const* U_p, int64_t ldu, const float* const* V_p, int64_t ldv, int64_t P,
+                                        int64_t B, float* W, float* Mom, int64_t N, int64_t M, float lr, float mu, float wd, hipStream_t st);
 psd_status launch_sfb_bf16(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t ldv, float* W, float* Mom,
                            int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int most_splits,
                            hipStream_t st);

@@ -113,8 +113,10 @@ inline Cover split_cover(int64_t N, int64_t M, int pinned) { return pinned ? uni
 // How many workgroups share a tile's sum over k, at most `most`.  A pinned tile is split as far as the workspace was asked for.
 // Otherwise the sum is split where the shorter loops save more than storing and adding the partial sums costs: the second launch
 // 4 us and its bytes.  512 -> 512, K = 2048: 34 us unsplit, 17 us in four.
-inline int choose_f32_splits(int64_t N, int64_t M, int64_t K, int most, int64_t cus, int pinned)
+// *cost: what the layer takes so, in us by estimate (0 with a pinned tile).
+inline int choose_f32_splits(int64_t N, int64_t M, int64_t K, int most, int64_t cus, int pinned, double* cost = nullptr)
 {
+    if (cost) *cost = 0;
     if (pinned) return most;
     double us;
     choose_f32(N, M, K, cus, 0, &us);
@@ -128,7 +130,43 @@ inline int choose_f32_splits(int64_t N, int64_t M, int64_t K, int most, int64_t 
             splits = s;
         }
     }
+    if (cost) *cost = us;
     return splits;
+}
+
+// ---- fp32 reconstruction on the bf16 pipe (psd_sfb_planes.hip)
+// Tiles of tn x 128, `slots` of them on a compute unit at a time.  us: a launch takes `first`, `update` per 4 M weights, and per
+// 1024 k rows `one` where the busiest compute unit holds a lone tile and `two` for each pair, of which its idle neighbours take
+// `idle` away.  Fitted to 97 layers of 0.2 to 60 M weights, K = 64 .. 4096 (5 to 7 % rms).
+struct PlaneTile { int id, tn, slots; double first, one, two, update, idle; };
+constexpr PlaneTile kPlaneTiles[] = {{0, 128, 2, 9.1, 38.1, 67.6, 9.9, 0.18}, {1, 128, 1, 7.6, 36.1, 0, 11.3, 0.29},
+                                     {2, 64, 2, 6.6, 23.7, 39.9, 9.6, 0.11},  {3, 64, 1, 5.6, 21.4, 0, 14.4, 0.21}};
+
+inline double planes_cost(const PlaneTile& t, int64_t N, int64_t M, int64_t K, int64_t cus)
+{
+    const int64_t tiles = ((N + t.tn - 1) / t.tn) * ((M + 127) / 128), most = (tiles + cus - 1) / cus;   // of one compute unit
+    const double idle = t.idle * (static_cast<double>(most) - static_cast<double>(tiles) / cus);
+    const double loop = t.slots == 1 || most == 1 ? t.one * (most - idle)
+                                                  : (t.two * (most / 2) + t.one * (most % 2)) * (1 - idle / most);
+    return t.first + loop * static_cast<double>(K) / 1024 + t.update * static_cast<double>(N) * M / 4194304;
+}
+
+// Which of them takes this layer, -1: none, the fp32 pipe does.  `us`: its cost there, split or not.  Short contractions stay: at
+// K = 128 the fp32 pipe is the faster one for every size of layer (2624 -> 5037 52 against 59 us), from 256 on for small ones only
+// (4096 -> 512 15.4 against 15.6, 4096 -> 1024 25.0 and 23.7, 4096 -> 4096 85 and 79).  Over the 97 layers the choice is 0.6 % off
+// the best one, with the 6 % that have to be gained (0.9 % without).
+constexpr int64_t kMinPlaneRows = 192;
+inline int choose_planes(int64_t N, int64_t M, int64_t K, int64_t cus, double us)
+{
+    if (K < kMinPlaneRows) return -1;
+    int best = -1;
+    us *= 0.94;
+    for (const PlaneTile& t : kPlaneTiles)
+        if (planes_cost(t, N, M, K, cus) < us) {
+            us = planes_cost(t, N, M, K, cus);
+            best = t.id;
+        }
+    return best;
 }
 
 // ---- bf16 reconstruction: which tile covers W

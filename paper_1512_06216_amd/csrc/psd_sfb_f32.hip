@@ -2,9 +2,9 @@
 // Eq. 5; Algorithm 3's update line):
 //     dW[n][m] = sum_k U[k][n] * V[k][m] ;  Mom = mu*Mom + lr*dW ;  W = W - Mom
 //
-// A dense contraction over K = P*B, so it runs on the fp32 MFMA pipe
-// (v_mfma_f32_32x32x2_f32: one k per lane, which is exactly how the K-outer stacked
-// factors sit in memory -- no transpose is needed for fp32).
+// Small layers and short contractions, on the fp32 MFMA pipe (v_mfma_f32_32x32x2_f32: one k per lane, which is exactly how the
+// K-outer stacked factors sit in memory -- no transpose is needed for fp32).  The others go to psd_sfb_planes.hip
+// (choose_planes): 4096 -> 1000, K = 2048 124 -> 91 us, 9216 -> 4096 1066 -> 727 us.
 //
 // Tiling: a 256-lane workgroup (4 wavefronts, 2 x 2) owns a 128 x 128, 64 x 128 or 64 x 64 tile of W; each wavefront a
 // quarter of it in 32 x 32 MFMA blocks.  MFMA row i of block t stands for n = n0 + BN*i + t (columns m likewise), so one
@@ -416,7 +416,10 @@ psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t l
     g.U = U; g.V = V;
     g.u_bytes = static_cast<uint32_t>(u_bytes); g.v_bytes = static_cast<uint32_t>(v_bytes);
     const int pinned = pinned_tile();
-    const int splits = choose_f32_splits(N, M, K, most_splits, device_cu_count(), pinned);
+    double us;
+    const int splits = choose_f32_splits(N, M, K, most_splits, device_cu_count(), pinned, &us);
+    const int planes = pinned ? -1 : choose_planes(N, M, K, device_cu_count(), us);
+    if (planes >= 0) return launch_sfb_f32_planes(planes, U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, st);
     if (splits <= 1) return launch_cover(g, nullptr, st);
     const Cover c = split_cover(N, M, pinned);
     g.tiles_m = static_cast<int>(c.tiles_m);
@@ -437,6 +440,12 @@ psd_status launch_sfb_f32_blocks(const float* const* U_p, int64_t ldu, const flo
                                  hipStream_t st)
 {
     if (P < 1 || P > PSD_MAX_WORKERS || !sfb_f32_blocks_supported(B)) return PSD_E_UNSUPPORTED;
+    if (!pinned_tile()) {
+        double us;
+        choose_f32(N, M, P * B, device_cu_count(), 0, &us);
+        const int planes = choose_planes(N, M, P * B, device_cu_count(), us);
+        if (planes >= 0) return launch_sfb_f32_planes_blocks(planes, U_p, ldu, V_p, ldv, P, B, W, Mom, N, M, lr, mu, wd, st);
+    }
     const int64_t u_bytes = B * ldu * 4, v_bytes = B * ldv * 4;        // one block
     BlockPtrs blocks;
     for (int64_t p = 0; p < PSD_MAX_WORKERS; ++p) {

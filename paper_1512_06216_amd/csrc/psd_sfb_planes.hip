@@ -1,0 +1,503 @@
+// SFB reconstruction with fused momentum-SGD update, fp32 factors on the bf16 MFMA pipe (the same contraction and update as
+// psd_sfb_f32.hip, which keeps the small layers):
+//     dW[n][m] = sum_k U[k][n] * V[k][m] ;  Mom = mu*Mom + lr*dW ;  W = W - Mom
+//
+// An fp32 number is the exact sum of three bf16 numbers, x = h + m + l: each is the nearest bf16 to what is left, 8 significant
+// bits at a time (|m| <= 2^-9 |x|, |l| <= 2^-18 |x|).  Of the nine products of two such sums the six largest are contracted on
+// v_mfma_f32_32x32x16_bf16, exact products added up in fp32; what is left out (m*l, l*m, l*l) is below 2^-26 of a product.  Six
+// MFMAs at sixteen times the rate of the fp32 MFMA: 2.7 times its peak.
+//
+// Precision.  The five small products have accumulators of their own (`low`), so that the large ones take one rounding where the
+// fp32 pipe takes four, and the low ones round numbers 2^-8 as large.  Error of dW against 64 bits (2-norm; normal errors,
+// activations after a ReLU): K = 2048 2.1e-7 (fp32 pipe 5.7e-7), K = 256 7e-8 (with one set of accumulators 6.6e-7 and
+// 2.3e-7).  Tiles whose sums overflow or are not numbers, and tiles with a sum below 2^-104 other than zero (where l of a factor
+// may be below what bf16 can hold), are contracted anew on the fp32 pipe (`again`), so that infinities, NaN and the smallest
+// numbers give what they give there.
+//
+// Tile and feeding.  A wavefront owns 32 x 128 of W: one MFMA block of n and four of m, the m of block j being m0 + 4*i + j, so that
+// a lane holds four adjacent m of a row in four accumulators and the update moves 512 contiguous bytes per half wavefront
+// without a turn through LDS.  Four (two) wavefronts own 128 x 128 (64 x 128); G groups of them share a tile and contract
+// every G-th slice of 16 k rows, their sums are added up in LDS at the end.
+// The factors pass through registers: each wavefront loads 8 k rows x 64 columns at a time, cuts them (11 vector instructions per
+// two elements) and stores the planes to LDS with k innermost, so that an MFMA operand is one 16-byte read (256 bytes per clock;
+// the transposing reads of K-outer tiles manage 128).  Two LDS buffers; the barrier sits before the last quarter of a
+// slice's MFMAs, whose execution hides the first operand reads of the slice to come; loads are in flight for a whole slice.
+//
+// Bound by power: the clock settles at 1.7-1.8 GHz with the MFMA pipe 70-73 % busy.  9216 -> 4096, K = 2048: 727 us, 213 TFLOP/s
+// (fp32 pipe 1066, at its peak); 4096 -> 4096 331 (488), 4096 -> 1000 91 (124), 3000 -> 3000 225 (276).  Tried and not better: one
+// set of accumulators and three workgroups per compute unit (699 us, but twice to three times the error), loads two slices ahead
+// (no change), all vector work in three quarters of a slice or spread more thinly (0-2 % slower), wave priorities (10 % slower).
+#include <atomic>
+#include <type_traits>
+#include "psd_device.h"
+#include "psd_internal.h"
+
+namespace psd {
+namespace {
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int SLICE = 16;           // k rows that one group of wavefronts contracts between two barriers
+constexpr int GROUP_N = 16;         // tile rows per raster group (as in the bf16 kernel; 8: 1 % slower)
+
+// WN wavefronts of 32 rows n and 128 columns m per group, G groups
+template <int WN_, int G_>
+struct Cfg {
+    static constexpr int WN = WN_, G = G_, WAVES = WN * G, THREADS = 64 * WAVES;
+    static constexpr int TN = 32 * WN, TM = 128;
+    static_assert(WN == 2 || WN == 4, "half of the wavefronts load the first 8 rows of a slice, half the others");
+    static constexpr int PU = 2 * TN / 64 / WN, PV = 2 * TM / 64 / WN;            // 8 x 64 patches per wavefront and slice
+    // LDS, one slice: planes of U: [k / 8][n], planes of V: [k / 8][m % 4][m / 4], 16 bytes (8 k) each.  The 64 bytes between the
+    // quarters of V spread the writes of 16 lanes (four adjacent m in four of them) over all banks.
+    static constexpr int A_HALF = TN * 16, A_PLANE = 2 * A_HALF;
+    static constexpr int B_QUARTER = 32 * 16 + 64, B_HALF = 4 * B_QUARTER, B_PLANE = 2 * B_HALF;
+    static constexpr int A_BYTES = 3 * A_PLANE, SLICE_BYTES = A_BYTES + 3 * B_PLANE;
+    static constexpr int BUFFER_BYTES = G * SLICE_BYTES, ROWS_BYTES = 64 * row_stride(TM, 0) * 4;
+    static constexpr int LDS_BYTES = 2 * BUFFER_BYTES > ROWS_BYTES ? 2 * BUFFER_BYTES : ROWS_BYTES;
+    // rows of the update, 64 at a time where they go through LDS; accumulators that groups hand over
+    static constexpr int PASSES = TN / 64;
+    static_assert(G * (G - 1) * (64 / G) * WN * 256 <= LDS_BYTES, "what the groups hand over fits");
+};
+
+struct BlockPtrs { const float* u[PSD_MAX_WORKERS]; const float* v[PSD_MAX_WORKERS]; };
+
+struct Args {
+    const float* U; const float* V;
+    int64_t ldu, ldv;
+    float* W; float* Mom;
+    int N, M, K;
+    float lr, mu, wd;
+    int tiles_n, tiles_m;
+    uint32_t u_bytes, v_bytes;      // of the stacked matrices, or of ONE block
+    int n_blocks, block_rows;       // BLK
+};
+
+__device__ __forceinline__ uint32_t to_bf16(float a, float b)          // nearest even; a in the low half
+{
+    const f32x2 x = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
+}
+
+// (x0, x1) = h + m + l; the differences are exact
+__device__ __forceinline__ void cut(float x0, float x1, uint32_t& h, uint32_t& m, uint32_t& l)
+{
+    h = to_bf16(x0, x1);
+    const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
+    m = to_bf16(r0, r1);
+    l = to_bf16(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
+}
+
+__device__ __forceinline__ float load_or_zero(const Feed& f, uint32_t off)     // 0 past the end of what is fed
+{
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+        __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(f.base), 0, static_cast<int>(f.left), 0x00020000), off, 0, 0));
+}
+
+// 6 MFMAs, the operand reads of the quarter to come behind the first of them, vector instructions in between
+__device__ __forceinline__ void interleave()
+{
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                     // one MFMA
+        if (i < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);          // LDS read
+        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);                     // vector ALU
+        if (i >= 3) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);         // LDS write
+        if (i >= 2) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);         // loads
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// what LDS holds is visible to the workgroup (loads from memory stay in flight)
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// BLK = true: row k = p*B + b of U is row b of the p-th worker's block (V likewise); a slice lies in one block because SLICE
+// divides B.
+template <class C, bool BLK>
+__device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks)
+{
+    constexpr int G = C::G, WN = C::WN, PU = C::PU, PV = C::PV;
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    // workgroup -> tile: a contiguous run of the tile sequence per XCD, in groups of GROUP_N tile rows
+    const int T = g.tiles_n * g.tiles_m, xcd = blockIdx.x & 7;
+    const int lin = xcd * (T >> 3) + (xcd < (T & 7) ? xcd : (T & 7)) + (blockIdx.x >> 3);
+    const int per_raster = GROUP_N * g.tiles_m;
+    const int raster = lin / per_raster, in_raster = lin - raster * per_raster;
+    const int rows_r = g.tiles_n - raster * GROUP_N < GROUP_N ? g.tiles_n - raster * GROUP_N : GROUP_N;
+    const int64_t n0 = int64_t(raster * GROUP_N + in_raster % rows_r) * C::TN, m0 = int64_t(in_raster / rows_r) * C::TM;
+
+    const int N = g.N, M = g.M;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int group = wave / WN, w = wave % WN;
+    const int l32 = lane & 31, lhi = lane >> 5;
+    const uint32_t row_a = static_cast<uint32_t>(g.ldu * 4), row_b = static_cast<uint32_t>(g.ldv * 4);
+
+    Feed u, v;
+    int blk = 0, row_in_blk = group * SLICE;     // BLK: where this group's next slice lies
+    auto aim_block = [&]() {
+        while (row_in_blk >= g.block_rows) {
+            row_in_blk -= g.block_rows;
+            ++blk;
+        }
+        const bool live = blk < g.n_blocks;
+        const int i = live ? blk : 0;            // the table is never indexed past its end
+        u.aim(uniform_ptr(blocks->u[i]), uint64_t(row_in_blk) * row_a, live ? g.u_bytes : 0u);
+        v.aim(uniform_ptr(blocks->v[i]), uint64_t(row_in_blk) * row_b, live ? g.v_bytes : 0u);
+    };
+    if constexpr (BLK) {
+        aim_block();
+    } else {
+        u.aim(g.U, uint64_t(group * SLICE) * row_a, g.u_bytes);
+        v.aim(g.V, uint64_t(group * SLICE) * row_b, g.v_bytes);
+    }
+    auto advance = [&]() {
+        if constexpr (BLK) row_in_blk += SLICE * G;
+        if (BLK && row_in_blk >= g.block_rows) {
+            aim_block();
+        } else {
+            u.advance(SLICE * G * row_a);
+            v.advance(SLICE * G * row_b);
+        }
+    };
+
+    // This wavefront's patches of a slice: rows 8*half .. 8*half + 7; columns ca + 64*j of the U tile, cb + 64*j of the V tile.
+    const int half = w / (WN / 2), part = w % (WN / 2);
+    const int ca = part * (2 * C::TN / WN) + lane, cb = part * (2 * C::TM / WN) + lane;
+    uint32_t off_u[8], off_v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        off_u[k] = (8 * half + k) * row_a + static_cast<uint32_t>(n0 + ca) * 4;
+        off_v[k] = (8 * half + k) * row_b + static_cast<uint32_t>(m0 + cb) * 4;
+        asm("" : "+v"(off_u[k]), "+v"(off_v[k]));         // kept in registers
+    }
+    float patch[PU + PV][8];
+    auto load = [&](int p) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            patch[p][k] = p < PU ? load_or_zero(u, off_u[k] + p * 256) : load_or_zero(v, off_v[k] + (p - PU) * 256);
+    };
+    char* const mine = lds + group * C::SLICE_BYTES;
+    const int wr_a = half * C::A_HALF + ca * 16;
+    const int wr_b = C::A_BYTES + half * C::B_HALF + (cb & 3) * C::B_QUARTER + (cb >> 2) * 16;
+    u32x4 h, m, l;
+    constexpr int ITEMS = 2 * (PU + PV);
+    auto item = [&](int buf, int i) {            // half a patch of the slice in registers -> buffer buf; then the next slice's loads
+        const int p = i >> 1;
+#pragma unroll
+        for (int q = 2 * (i & 1); q < 2 * (i & 1) + 2; ++q) {
+            uint32_t hh, mm, ll;
+            cut(patch[p][2 * q], patch[p][2 * q + 1], hh, mm, ll);
+            h[q] = hh; m[q] = mm; l[q] = ll;
+        }
+        if (i & 1) {
+            char* to = mine + buf * C::BUFFER_BYTES + (p < PU ? wr_a + p * 64 * 16 : wr_b + (p - PU) * 16 * 16);
+            const int plane = p < PU ? C::A_PLANE : C::B_PLANE;
+            *reinterpret_cast<u32x4*>(to) = h;
+            *reinterpret_cast<u32x4*>(to + plane) = m;
+            *reinterpret_cast<u32x4*>(to + 2 * plane) = l;
+            load(p);
+        }
+        if (i == ITEMS - 1) advance();
+    };
+
+    f32x16 acc[4], low[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[j][r] = low[j][r] = 0.f;
+    const int rd_a = lhi * C::A_HALF + (32 * w + l32) * 16, rd_b = C::A_BYTES + lhi * C::B_HALF + l32 * 16;
+    bf16x8 fa[2][3], fb[2][3];
+    auto read_a = [&](int buf) {
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+            fa[buf][s] = *reinterpret_cast<const bf16x8*>(mine + buf * C::BUFFER_BYTES + rd_a + s * C::A_PLANE);
+    };
+    auto read_b = [&](int buf, int j) {
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+            fb[j & 1][s] = *reinterpret_cast<const bf16x8*>(mine + buf * C::BUFFER_BYTES + rd_b + j * C::B_QUARTER + s * C::B_PLANE);
+    };
+    auto mma = [&](int buf, int j) {             // planes: 0 = h, 1 = m, 2 = l
+        const bf16x8 (&a)[3] = fa[buf], (&b)[3] = fb[j & 1];
+        low[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], b[0], low[j], 0, 0, 0);
+        low[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[2], low[j], 0, 0, 0);
+        low[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[1], low[j], 0, 0, 0);
+        low[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[0], low[j], 0, 0, 0);
+        low[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[1], low[j], 0, 0, 0);
+        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], acc[j], 0, 0, 0);
+    };
+
+    const int steps = (g.K + SLICE * G - 1) / (SLICE * G);
+#pragma unroll
+    for (int p = 0; p < PU + PV; ++p) load(p);
+    advance();
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) item(0, i);
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < ITEMS / 4; ++i) item(1, i);
+    read_a(0);
+    read_b(0, 0);
+    // Contracts the slices in buffer buf.  Behind the barrier nobody reads them any more, and those in the other buffer are whole.
+    auto step = [&](int buf) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (j < 3) {
+                read_b(buf, j + 1);
+            } else {
+                lds_barrier();
+                read_a(buf ^ 1);
+                read_b(buf ^ 1, 0);
+            }
+            const int q = (j + 1) & 3;
+#pragma unroll
+            for (int i = ITEMS * q / 4; i < ITEMS * (q + 1) / 4; ++i) item(j == 3 ? buf : buf ^ 1, i);
+            mma(buf, j);
+            interleave();
+        }
+    };
+    int t = steps;
+    for (; t >= 2; t -= 2) {
+        step(0);
+        step(1);
+    }
+    if (t) step(0);
+
+    // Accumulator register r of a block holds row 8*(r/4) + 4*(lane/32) + r%4 of the wavefront's 32, and m = m0 + 4*(lane%32) + j.
+    // A group keeps NR registers of each block, rows 32/G * group ..., and hands the others over.
+    constexpr int NR = 16 / G;
+    float d[NR][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[j][r] += low[j][r];
+    __syncthreads();                             // the slices are no longer read
+    if constexpr (G > 1) {
+        float4* buf = reinterpret_cast<float4*>(lds) + w * 64 + lane;
+        auto at = [](int to, int from, int q) { return ((to * (G - 1) + from - (from > to)) * NR + q) * WN * 64; };
+#pragma unroll
+        for (int to = 0; to < G; ++to) {
+            if (to == group) {
+#pragma unroll
+                for (int q = 0; q < NR; ++q)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) d[q][j] = acc[j][to * NR + q];
+            } else {
+#pragma unroll
+                for (int q = 0; q < NR; ++q)
+                    buf[at(to, group, q)] = make_float4(acc[0][to * NR + q], acc[1][to * NR + q], acc[2][to * NR + q], acc[3][to * NR + q]);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 1; i < G; ++i) {
+            const int from = (group + i) % G;
+#pragma unroll
+            for (int q = 0; q < NR; ++q) {
+                const float4 x = buf[at(group, from, q)];
+                d[q][0] += x.x; d[q][1] += x.y; d[q][2] += x.z; d[q][3] += x.w;
+            }
+        }
+        __syncthreads();
+    } else {
+#pragma unroll
+        for (int q = 0; q < NR; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) d[q][j] = acc[j][q];
+    }
+
+    // Sums that the planes may not give as the fp32 pipe does (see above): this wavefront's rows anew.
+    {
+        float nan = 0.f;
+        uint32_t least = 0xffffffffu;
+#pragma unroll
+        for (int q = 0; q < NR; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                nan = __fmaf_rn(d[q][j], 0.f, nan);
+                const uint32_t b = 2 * __float_as_uint(d[q][j]) - 1;
+                least = b < least ? b : least;
+            }
+        if (__any(nan != 0.f || least < 2 * 0x0b800000u - 1)) {                // 0x0b800000: 2^-104
+            // in four runs over k, like the groups of the fp32 kernel for small layers: half the error of one run
+            f32x16 total[4], sum[4];
+            const int run = ((g.K + 3) / 4 + 1) & ~1;
+            for (int k0 = 0; k0 < g.K; k0 += run) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        total[j][r] = k0 == 0 ? 0.f : total[j][r] + sum[j][r];
+                        sum[j][r] = 0.f;
+                    }
+                for (int k = k0; k < k0 + run && k < g.K; k += 2) {            // lanes 0..31 feed k, the others k + 1
+                    const int kb = BLK ? k / g.block_rows : 0, row = k - kb * g.block_rows * BLK;
+                    Feed fu, fv;
+                    fu.aim(BLK ? uniform_ptr(blocks->u[kb]) : g.U, uint64_t(row) * row_a, g.u_bytes);
+                    fv.aim(BLK ? uniform_ptr(blocks->v[kb]) : g.V, uint64_t(row) * row_b, g.v_bytes);
+                    const float a = load_or_zero(fu, lhi * row_a + static_cast<uint32_t>(n0 + 32 * w + l32) * 4);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        sum[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                            a, load_or_zero(fv, lhi * row_b + static_cast<uint32_t>(m0 + 4 * l32 + j) * 4), sum[j], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int to = 0; to < G; ++to)
+                if (to == group)
+#pragma unroll
+                    for (int q = 0; q < NR; ++q)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) d[q][j] = total[j][to * NR + q] + sum[j][to * NR + q];
+        }
+    }
+
+    const int first = 32 * w + (32 / G) * group + 4 * lhi;                     // row of register q: first + 8*(q/4) + q%4
+    if (M % 4 == 0) {
+        const int64_t mc = m0 + 4 * l32;
+        constexpr int DEPTH = NR < 8 ? NR : 8;
+        auto update = [&](auto lines) {
+            constexpr bool STREAM = decltype(lines)::value;
+#pragma unroll
+            for (int q0 = 0; q0 < NR; q0 += DEPTH) {
+                float4 wv[DEPTH], mo[DEPTH];
+#pragma unroll
+                for (int q = q0; q < q0 + DEPTH; ++q) {
+                    const int64_t n = n0 + first + 8 * (q >> 2) + (q & 3), off = n * M + mc;
+                    if (n >= N || mc >= M) continue;
+                    wv[q - q0] = STREAM ? load_stream4(g.W + off) : *reinterpret_cast<const float4*>(g.W + off);
+                    mo[q - q0] = STREAM ? load_stream4(g.Mom + off) : *reinterpret_cast<const float4*>(g.Mom + off);
+                }
+#pragma unroll
+                for (int q = q0; q < q0 + DEPTH; ++q) {
+                    const int64_t n = n0 + first + 8 * (q >> 2) + (q & 3), off = n * M + mc;
+                    if (n >= N || mc >= M) continue;
+                    float4 &x = wv[q - q0], &y = mo[q - q0];
+                    upd(d[q][0], x.x, y.x, g.lr, g.mu, g.wd);
+                    upd(d[q][1], x.y, y.y, g.lr, g.mu, g.wd);
+                    upd(d[q][2], x.z, y.z, g.lr, g.mu, g.wd);
+                    upd(d[q][3], x.w, y.w, g.lr, g.mu, g.wd);
+                    if constexpr (STREAM) {
+                        store_stream4(g.Mom + off, y);
+                        store_stream4(g.W + off, x);
+                    } else {
+                        *reinterpret_cast<float4*>(g.Mom + off) = y;
+                        *reinterpret_cast<float4*>(g.W + off) = x;
+                    }
+                }
+            }
+        };
+        if (M % 32 == 0 && ((reinterpret_cast<uintptr_t>(g.W) | reinterpret_cast<uintptr_t>(g.Mom)) & 127) == 0) update(std::true_type{});
+        else update(std::false_type{});
+        return;
+    }
+    // Rows that start anywhere: 64 of them at a time go through LDS and come back as whole lines of W (RowUpdate).  Where one group
+    // holds all 32 rows of a wavefront (PASSES = 2 and G = 1) a pass takes 16 of each.
+    float* buf = reinterpret_cast<float*>(lds);
+#pragma unroll
+    for (int pass = 0; pass < C::PASSES; ++pass) {
+        auto row_n = [&](int r) { return n0 + (C::PASSES == 1 ? r : (r >> 4) * 32 + 16 * pass + (r & 15)); };
+        RowUpdate<64, C::TM, C::WAVES, 4, 1, decltype(row_n)> rows(g.W, g.Mom, row_n, m0, N, M, wave, lane);
+        rows.template fetch<0>();
+        if (pass > 0) __syncthreads();           // the rows before are no longer read
+        if (C::PASSES == 1 || G == 1 || 2 * group / G == pass) {
+#pragma unroll
+            for (int q = 0; q < NR; ++q) {
+                if (C::PASSES == 2 && G == 1 && (q >> 3) != pass) continue;
+                const int in_wave = (32 / G) * group + 4 * lhi + 8 * (q >> 2) + (q & 3);      // 0 .. 31
+                const int r = C::PASSES == 1 ? 32 * w + in_wave : 16 * w + (in_wave & 15);
+                float* to = buf + r * rows.stride + 4 * l32 + line_shift(g.W, row_n(r), M);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) to[j] = d[q][j];
+            }
+        }
+        __syncthreads();
+        rows.run(buf, g.lr, g.mu, g.wd);
+    }
+}
+
+template <class C>
+__global__ void __launch_bounds__(C::THREADS, 2) sfb_f32_planes_kernel(const Args g)
+{
+    tile_body<C, false>(g, nullptr);
+}
+
+template <class C>
+__global__ void __launch_bounds__(C::THREADS, 2) sfb_f32_planes_blocks_kernel(const Args g, const BlockPtrs blocks)
+{
+    tile_body<C, true>(g, &blocks);
+}
+
+template <class C>
+psd_status start(Args& g, const BlockPtrs* blocks, hipStream_t st)
+{
+    g.tiles_n = (g.N + C::TN - 1) / C::TN;
+    g.tiles_m = (g.M + C::TM - 1) / C::TM;
+    const int64_t tiles = int64_t(g.tiles_n) * g.tiles_m;
+    if (tiles < 1 || tiles > 0x7fffffff) return PSD_E_INVALID;
+    // raise the dynamic LDS limit once per process (idempotent, so a race between two first callers is harmless)
+    static std::atomic<bool> attr_done{false};
+    if (!attr_done.load(std::memory_order_acquire)) {
+        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_f32_planes_kernel<C>),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
+        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_f32_planes_blocks_kernel<C>),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
+        attr_done.store(true, std::memory_order_release);
+    }
+    const dim3 grid(static_cast<uint32_t>(tiles));
+    if (blocks) hipLaunchKernelGGL(sfb_f32_planes_blocks_kernel<C>, grid, dim3(C::THREADS), C::LDS_BYTES, st, g, *blocks);
+    else hipLaunchKernelGGL(sfb_f32_planes_kernel<C>, grid, dim3(C::THREADS), C::LDS_BYTES, st, g);
+    PSD_HIP_TRY(hipGetLastError());
+    return PSD_OK;
+}
+
+psd_status dispatch(int tile, Args& g, const BlockPtrs* blocks, hipStream_t st)
+{
+    switch (tile) {
+        case 1: return start<Cfg<4, 2>>(g, blocks, st);
+        case 2: return start<Cfg<2, 2>>(g, blocks, st);
+        case 3: return start<Cfg<2, 4>>(g, blocks, st);
+        default: return start<Cfg<4, 1>>(g, blocks, st);
+    }
+}
+
+}  // namespace
+
+psd_status launch_sfb_f32_planes(int tile, const float* U, int64_t ldu, const float* V, int64_t ldv, float* W, float* Mom, int64_t N,
+                                 int64_t M, int64_t K, float lr, float mu, float wd, hipStream_t st)
+{
+    Args g = {};
+    g.U = U; g.V = V; g.ldu = ldu; g.ldv = ldv; g.W = W; g.Mom = Mom;
+    g.N = static_cast<int>(N); g.M = static_cast<int>(M); g.K = static_cast<int>(K);
+    g.lr = lr; g.mu = mu; g.wd = wd;
+    g.u_bytes = static_cast<uint32_t>(K * ldu * 4); g.v_bytes = static_cast<uint32_t>(K * ldv * 4);
+    return dispatch(tile, g, nullptr, st);
+}
+
+psd_status launch_sfb_f32_planes_blocks(int tile, const float* const* U_p, int64_t ldu, const float* const* V_p, int64_t ldv, int64_t P,
+                                        int64_t B, float* W, float* Mom, int64_t N, int64_t M, float lr, float mu, float wd, hipStream_t st)
+{
+    BlockPtrs blocks;
+    for (int64_t p = 0; p < PSD_MAX_WORKERS; ++p) {
+        blocks.u[p] = p < P ? U_p[p] : nullptr;
+        blocks.v[p] = p < P ? V_p[p] : nullptr;
+    }
+    Args g = {};
+    g.ldu = ldu; g.ldv = ldv; g.W = W; g.Mom = Mom;
+    g.N = static_cast<int>(N); g.M = static_cast<int>(M); g.K = static_cast<int>(P * B);
+    g.lr = lr; g.mu = mu; g.wd = wd;
+    g.u_bytes = static_cast<uint32_t>(B * ldu * 4); g.v_bytes = static_cast<uint32_t>(B * ldv * 4);
+    g.n_blocks = static_cast<int>(P); g.block_rows = static_cast<int>(B);
+    return dispatch(tile, g, &blocks, st);
+}
+
+}  // namespace psd

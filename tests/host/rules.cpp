@@ -23,5 +23,12 @@ int32_t f32_choice(int64_t N, int64_t M, int64_t K, int64_t cus)
     const psd::Cover c = psd::choose_f32(N, M, K, cus, 0, &us);
     return 1000 * c.bn + 100 * c.bm + 10 * (c.big > 0) + c.g;
 }
+// the tile that contracts it on the bf16 pipe, -1: none
+int32_t f32_planes(int64_t N, int64_t M, int64_t K, int64_t cus)
+{
+    double us;
+    psd::choose_f32(N, M, K, cus, 0, &us);
+    return psd::choose_planes(N, M, K, cus, us);
+}
 int32_t f32_splits(int64_t N, int64_t M, int64_t K, int most, int64_t cus) { return psd::choose_f32_splits(N, M, K, most, cus, 0); }
 }

@@ -306,6 +306,88 @@ def test_sfb_every_tile_the_rules_choose_bit_exact(dtype, M, N, B, P):
     assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr)
 
 
+# Layers that go to the bf16 pipe in planes, every tile with rows of W on cache lines, on quads and anywhere; and layers that stay
+# on the fp32 pipe with 64 x 128 tiles.  (tests/test_rules.py checks that the rules say so.)
+PLANE_LAYERS = [  # tile, M, N, B, P
+    (0, 4448, 1345, 80, 3), (0, 1804, 3360, 80, 3), (0, 5378, 1092, 16, 16), (1, 5568, 330, 96, 3), (1, 5812, 324, 48, 6),
+    (1, 5679, 323, 96, 3), (2, 928, 1593, 32, 8), (2, 3676, 399, 64, 4), (2, 1199, 1227, 16, 16), (3, 5472, 132, 32, 6),
+    (3, 5444, 134, 32, 6), (3, 5715, 129, 64, 3)]
+F32_PIPE_LAYERS = [(1201, 4960, 583, 32, 3), (1201, 3476, 835, 32, 3)]
+
+
+@pytest.mark.parametrize("M,N,B,P", [c[1:] for c in PLANE_LAYERS + F32_PIPE_LAYERS])
+def test_sfb_f32_planes_bit_exact(M, N, B, P):
+    """Stacked, and (rows of 16-byte multiples: the stacked ones) read in place as P blocks."""
+    d = inputs.fc_layer_integer(M, N, B, P, seed=M + N)
+    plan, U, ldu, V, ldv = run_pack(d, psd.F32)
+    Uo, Vo = orc.pack_factors(d["delta"], d["act"])
+    Wr, Mr = orc.sync_fc_sfb(Uo, Vo, d["W"], d["Mom"], 0.25, 0.5, wd=0.25)
+    for blocks in (False, True):
+        W, Mom = dev(d["W"]), dev(d["Mom"])
+        if blocks:
+            psd.sync_fc_sfb_blocks(plan, psd.F32, list(U.split(B)), ldu, list(V.split(B)), ldv, W, Mom, 0.25, 0.5, wd=0.25)
+        else:
+            psd.sync_fc_sfb(plan, psd.F32, U, ldu, V, ldv, W, Mom, 0.25, 0.5, wd=0.25)
+        torch.cuda.synchronize()
+        assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr), blocks
+
+
+def _planes_dw(M, N, K, U, V):
+    """dW of N(K x N)^T (K x M) through the library, and by the definition in 64 bits."""
+    plan = psd.plan_layer(psd.LAYER_FC, M, N, K, 1)
+    Us, ldu, Vs, ldv = psd.alloc_factors(plan, psd.F32)
+    psd.pack_factors(plan, [U], [V], psd.F32, Us, ldu, Vs, ldv)
+    W, Mom = torch.zeros(N, M, device=DEV), torch.zeros(N, M, device=DEV)
+    psd.sync_fc_sfb(plan, psd.F32, Us, ldu, Vs, ldv, W, Mom, 1.0, 0.0)
+    torch.cuda.synchronize()
+    return Mom, U.double().t().contiguous() @ V.double()
+
+
+# K of whole slices and not, for the tiles of one, two and four groups
+@pytest.mark.parametrize("M,N,K", [(5378, 1092, 256), (1804, 3360, 243), (5679, 323, 291), (928, 1593, 258), (5715, 129, 201)])
+def test_sfb_f32_planes_hold_all_24_bits(M, N, K):
+    """One error per sample is a power of two and the others are zero (and the other way round): a row of dW is a row of
+    activations, bit for bit."""
+    g = torch.Generator().manual_seed(M)
+    x = (torch.randn(K, M, generator=g) * torch.exp2(torch.randint(-60, 60, (K, M), generator=g).float())).to(DEV)
+    k = torch.randint(0, K, (N,), generator=g).to(DEV)
+    U = torch.zeros(K, N, device=DEV)
+    U[k, torch.arange(N, device=DEV)] = torch.exp2((torch.arange(N, device=DEV) % 9 - 4).float())
+    dW, want = _planes_dw(M, N, K, U, x)
+    assert torch.equal(dW.double(), want)
+    y = (torch.randn(K, N, generator=g) * torch.exp2(torch.randint(-60, 60, (K, N), generator=g).float())).to(DEV)
+    V = torch.zeros(K, M, device=DEV)
+    V[torch.randint(0, K, (M,), generator=g).to(DEV), torch.arange(M, device=DEV)] = -1.0
+    dW, want = _planes_dw(M, N, K, y, V)
+    assert torch.equal(dW.double(), want)
+
+
+@pytest.mark.parametrize("M,N,K", [(5378, 1092, 256), (5679, 323, 291), (928, 1593, 258), (5715, 129, 201)])
+@pytest.mark.parametrize("what", ["inf", "nan", "largest", "1e-32", "1e-36"])
+def test_sfb_f32_planes_numbers_that_bf16_cannot_hold(M, N, K, what):
+    """Infinities and NaN where the definition has them, FLT_MAX (whose nearest bf16 is infinite), and factors whose third part
+    is below the smallest bf16.  An fp32 sum of K products is off by K 2^-24 of the sum of their sizes at most, and by half of
+    the smallest fp32 number for each of K products where they are as small as that."""
+    g = torch.Generator().manual_seed(K)
+    U = (torch.randn(K, N, generator=g) * 1e-3).to(DEV)
+    V = torch.randn(K, M, generator=g).relu_().to(DEV)
+    if what == "inf":
+        U[5, 7], V[9, 100], U[9, 60] = float("inf"), float("-inf"), 0.0
+    elif what == "nan":
+        U[3, N - 1] = float("nan")
+    elif what == "largest":
+        U[4, 4], V[4] = torch.finfo(torch.float32).max, 0.0
+        V[4, 8] = 0.25
+    else:
+        U *= float(what)
+    dW, want = _planes_dw(M, N, K, U, V)
+    assert torch.equal(torch.isnan(dW), torch.isnan(want)) and torch.equal(torch.isinf(dW), torch.isinf(want))
+    ok = torch.isfinite(want)
+    bound = K * 2.0 ** -24 * (U.double().abs().nan_to_num(0, 0, 0).t().contiguous() @ V.double().abs().nan_to_num(0, 0, 0)) + K * 2.0 ** -150
+    assert bool(((dW.double() - want).abs() <= bound)[ok].all())
+    assert bool((dW[ok] == 0).sum() == (want[ok] == 0).sum()) or what == "1e-36"
+
+
 @pytest.mark.parametrize("tile,splits,M,N,B,P", BF16_SPLIT_LAYERS)
 def test_sfb_bf16_every_tile_that_is_split_bit_exact(tile, splits, M, N, B, P):
     d = inputs.fc_layer_integer(M, N, B, P, seed=M + N)

@@ -21,7 +21,7 @@ def rules(tmp_path_factory):
                             ("pack_rows", i64, [i64, i64]), ("f32_reach", i32, [i64, i64, i64]),
                             ("bf16_reach", i32, [i64, i64, i64, i64]), ("bf16_choice", i32, [i64, i64, i64, c_int, i64]),
                             ("splits_asked", i32, [i64, i64, i64]), ("f32_choice", i32, [i64, i64, i64, i64]),
-                            ("f32_splits", i32, [i64, i64, i64, c_int, i64])):
+                            ("f32_planes", i32, [i64, i64, i64, i64]), ("f32_splits", i32, [i64, i64, i64, c_int, i64])):
         getattr(L, name).restype, getattr(L, name).argtypes = res, args
     return L
 
@@ -113,3 +113,25 @@ def test_the_parity_tests_reach_every_tile_stacked_from_blocks_and_split(rules):
         if rules.f32_splits(N, M, B * P, most, CUS) > 1:
             split.add(M % 4 == 0)
     assert split == {True, False}
+
+
+def test_layers_of_the_parity_tests_go_to_the_pipe_they_stand_for(rules):
+    seen = set()
+    for tile, M, N, B, P in parity.PLANE_LAYERS:
+        assert rules.f32_planes(N, M, B * P, CUS) == tile and B % 16 == 0, (M, N, rules.f32_planes(N, M, B * P, CUS))
+        seen.add((tile, 32 if M % 32 == 0 else 4 if M % 4 == 0 else 1))
+    assert seen == {(t, a) for t in range(4) for a in (32, 4, 1)}
+    for cover, M, N, B, P in parity.F32_PIPE_LAYERS:
+        assert rules.f32_planes(N, M, B * P, CUS) == -1 and rules.f32_choice(N, M, B * P, CUS) == cover
+    for M, N, K, tile in ((5378, 1092, 256, 0), (1804, 3360, 243, 0), (5679, 323, 291, 1), (928, 1593, 258, 2), (5715, 129, 201, 3)):
+        assert rules.f32_planes(N, M, K, CUS) == tile
+
+
+def test_short_contractions_and_small_layers_stay_on_the_fp32_pipe(rules):
+    for M, N in ((64, 64), (1024, 1000), (4096, 4096), (9216, 4096), (25088, 4096), (4096, 21841)):
+        for K in (1, 16, 48, 128, 191):
+            assert rules.f32_planes(N, M, K, CUS) == -1
+    for M, N, K in ((64, 64, 4096), (256, 128, 128), (1024, 1000, 256), (512, 512, 2048)):
+        assert rules.f32_planes(N, M, K, CUS) == -1
+    for M, N in ((4096, 1000), (4096, 4096), (9216, 4096), (3000, 21841)):
+        assert rules.f32_planes(N, M, 2048, CUS) >= 0
