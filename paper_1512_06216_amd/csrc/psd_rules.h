@@ -40,7 +40,7 @@ inline bool factors_in_reach(int64_t K, int64_t ldu, int64_t ldv, int64_t bytes,
 }
 
 // The fp32 kernels advance the descriptor and read no further ahead than its end: what has to fit 32 bits besides the matrix is
-// one stage, 64 rows where four groups contract a tile.  96 rows is what the kernels of all tile sizes have always been given.
+// one stage, 32 rows where two groups contract a tile.  96 rows is what the kernels of all tile sizes have always been given.
 constexpr int64_t kF32Reserve = 96;
 
 // The bf16 kernels add the row to every offset: the stages they request past the last row, up to `stages` - 1 of `rows` rows, and
@@ -63,7 +63,7 @@ inline int sfb_splits_for(int64_t tiles, int64_t slots, int64_t K)
 }
 
 // ---- fp32 reconstruction: which tiles cover W
-// How one layer is covered: `big` tiles of 128 x 128 and then tiles of (64*bn) x (64*bm), each contracted by `g` groups.
+// How one layer is covered: `big` tiles of 128 x 128 and then tiles of (64*bn) x (64*bm), each summed in `g` chains.
 struct Cover { int bn, bm; int64_t big, tiles_m, groups; int g = 1; };
 
 inline Cover uniform_cover(int64_t N, int64_t M, int bn, int bm)
@@ -86,12 +86,12 @@ inline Cover choose_f32(int64_t N, int64_t M, int64_t K, int64_t cus, int pinned
     constexpr double kHalf = 0.507, kQuarter = 0.281;
     const double round = 57 * static_cast<double>(K) / 1024, update = 12.5 * static_cast<double>(N) * M / 16384 / cus;
     const Cover half = uniform_cover(N, M, 1, 2), quarter = uniform_cover(N, M, 1, 1), all = uniform_cover(N, M, 2, 2);
-    // At most one 64 x 64 tile per compute unit: four groups of wavefronts contract it (1024 -> 1000, K = 2048: 42 -> 36 us;
-    // two groups on a lone 128 x 128 tile are no faster than two 64 x 128 tiles).
+    // At most one 64 x 64 tile per compute unit: two groups of wavefronts contract it, in four chains (1024 -> 1000, K = 2048:
+    // 42 -> 36 us; two groups on a lone 128 x 128 tile are no faster than two 64 x 128 tiles).
     if (quarter.groups <= cus) {
         Cover c = quarter;
         c.g = 4;
-        *us = 4.5 + 0.267 * round + 0.7 * update;
+        *us = 3.7 + 0.264 * round + 0.7 * update;
         return c;
     }
     Cover best = half;
@@ -214,6 +214,12 @@ inline Bf16Tile choose_bf16(int64_t N, int64_t M, int64_t K, int64_t cus, int pi
         if (launch_cost(t, N, M, K, cus) < launch_cost(*best, N, M, K, cus)) best = &t;
     return *best;
 }
+
+// Groups of four wavefronts for a 64 x 64 tile that is alone on its compute unit (id 5), summed in four chains: two groups keep
+// two sets of accumulators each, which is half the wavefronts for the same work outside the loop, and meet a barrier twice as
+// often inside.  us with two and four groups: 500 -> 700, K = 64 4.9 and 5.7; 700 -> 500, K = 256 5.7 and 6.1, K = 512 6.6 and 7.1;
+// 1024 -> 1000, K = 256 6.8 and 6.8, K = 512 8.2 and 8.2, K = 1024 11.2 and 10.6.
+inline int lone_groups_bf16(int64_t K) { return K <= 512 ? 2 : 4; }
 
 // ... and how many ways to split the sum over k, at most `most`
 inline Bf16Tile choose_bf16_split(int64_t N, int64_t M, int64_t K, int most, int64_t cus, int pinned, int* splits)

@@ -38,10 +38,11 @@ constexpr int PLD = 36;        // epilogue patch row stride in floats (144 B: co
 // WN x WM wavefronts, each owning BN x BM MFMA blocks of 32 x 32; NSTAGE LDS buffers;
 // OCC = wavefronts per SIMD the register budget is sized for
 // G > 1: that many groups of WN x WM wavefronts own the same tile; a stage holds G slices of k rows, one for each
-// group, and the groups' accumulators are added up in LDS before the update.
-template <int WN_, int WM_, int BN_, int BM_, int NSTAGE_, int OCC_, int G_ = 1>
+// group, and the groups' accumulators are added up in LDS before the update.  CH > 1: every group keeps that many sets of
+// accumulators for stages in turn, added up at the end (a sum in G * CH chains whatever the number of wavefronts).
+template <int WN_, int WM_, int BN_, int BM_, int NSTAGE_, int OCC_, int G_ = 1, int CH_ = 1>
 struct Cfg {
-    static constexpr int WN = WN_, WM = WM_, BN = BN_, BM = BM_, NSTAGE = NSTAGE_, OCC = OCC_, G = G_;
+    static constexpr int WN = WN_, WM = WM_, BN = BN_, BM = BM_, NSTAGE = NSTAGE_, OCC = OCC_, G = G_, CH = CH_;
     static constexpr int WAVES = WN * WM * G, THREADS = 64 * WAVES, KT = SLICE * G;
     static constexpr int TN = 32 * BN * WN, TM = 32 * BM * WM;   // workgroup tile
     static constexpr int RA = TN * 2, RB = TM * 2;               // LDS row bytes (U tile, V tile)
@@ -200,13 +201,15 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
         }
     }
 
-    f32x16 acc[C::BN][C::BM];
+    f32x16 chain[C::CH][C::BN][C::BM];
 #pragma unroll
-    for (int a = 0; a < C::BN; ++a)
+    for (int i = 0; i < C::CH; ++i)
 #pragma unroll
-        for (int c = 0; c < C::BM; ++c)
+        for (int a = 0; a < C::BN; ++a)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][c][r] = 0.f;
+            for (int c = 0; c < C::BM; ++c)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) chain[i][a][c][r] = 0.f;
 
     // this lane's 8 k values of a 16-row MFMA step: ks + 8*(grp/2) + 0..7 (the same for both operands)
     auto load_frags = [&](uint32_t base, int ks, bf16x8 (&a)[C::BN], bf16x8 (&bb)[C::BM]) {
@@ -224,7 +227,7 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
         }
     };
     // rows of the MFMA block = m (V operand), columns = n (U operand)
-    auto mma = [&](const bf16x8 (&a)[C::BN], const bf16x8 (&bb)[C::BM]) {
+    auto mma = [&](const bf16x8 (&a)[C::BN], const bf16x8 (&bb)[C::BM], f32x16 (&acc)[C::BN][C::BM]) {
 #pragma unroll
         for (int bn = 0; bn < C::BN; ++bn)
 #pragma unroll
@@ -255,21 +258,40 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
     // of the first ones, so that their issue time hides under MFMA execution and the last of them is
     // back before it is waited for (spread evenly to the end: 1-2 % slower).
     auto interleave = [&]() { interleave_groups<2 * (C::BN + C::BM), C::BN * C::BM, 2>(); };
-    for (int t = 0; t < steps; ++t) {
+    auto stage = [&](int t, f32x16 (&acc)[C::BN][C::BM]) {
         load_frags(stage_base(t), 16, a1, b1);
-        mma(a0, b0);
+        mma(a0, b0, acc);
         interleave();
         __builtin_amdgcn_sched_barrier(0);
         wait_vmcnt<(C::NSTAGE - 3) * LPS>();
         __syncthreads();
         issue(t + C::NSTAGE - 1);
         load_frags(stage_base(t + 1), 0, a0, b0);
-        mma(a1, b1);
+        mma(a1, b1, acc);
         interleave();
         __builtin_amdgcn_sched_barrier(0);
+    };
+    static_assert(C::CH <= 2, "stages come singly or in pairs");
+    if constexpr (C::CH == 1) {
+        for (int t = 0; t < steps; ++t) stage(t, chain[0]);
+    } else {
+        int t = 0;
+        for (; t + 1 < steps; t += 2) {
+            stage(t, chain[0]);
+            stage(t + 1, chain[1]);
+        }
+        if (t < steps) stage(t, chain[0]);
     }
     wait_vmcnt<0>();                             // trailing zero stages must not land on the epilogue patch
     __syncthreads();
+    f32x16 (&acc)[C::BN][C::BM] = chain[0];
+    if constexpr (C::CH == 2)
+#pragma unroll
+        for (int a = 0; a < C::BN; ++a)
+#pragma unroll
+            for (int c = 0; c < C::BM; ++c)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[a][c][r] += chain[1][a][c][r];
 
     // Epilogue.  Accumulator register r of block (bn, bm) holds MFMA row 8*(r/4) + 4*(lane/32) + r%4
     // (= m offset) and column lane%32 (= n offset): four adjacent m per register quad.
@@ -472,6 +494,7 @@ using Cfg128x128w4 = Cfg<2, 2, 2, 2, 4, 2>;   // 64 KiB, two per CU
 using Cfg64x128w4 = Cfg<2, 2, 1, 2, 4, 3>;    // 48 KiB, three per CU
 using Cfg64x64w4 = Cfg<2, 2, 1, 1, 4, 4>;     // 32 KiB, five per CU: small layers
 using Cfg64x64w16 = Cfg<2, 2, 1, 1, 4, 4, 4>; // four groups, 128 KiB, one per CU
+using Cfg64x64w8 = Cfg<2, 2, 1, 1, 4, 4, 2, 2>; // two groups of two chains, 64 KiB
 using Cfg128x128w8 = Cfg<2, 2, 2, 2, 4, 2, 2>; // two groups, 128 KiB, one per CU
 
 }  // namespace
@@ -497,7 +520,10 @@ psd_status launch_sfb_bf16(const uint16_t* U, int64_t ldu, const uint16_t* V, in
         case 0: return launch_cfg<Cfg128x256w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
         case 1: return launch_cfg<Cfg128x192w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
         case 3: return launch_cfg<Cfg64x128w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
-        case 5: return launch_cfg<Cfg64x64w16>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, 1, st);
+        case 5:
+            if (lone_groups_bf16(K) == 2)
+                return launch_cfg<Cfg64x64w8>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, 1, st);
+            return launch_cfg<Cfg64x64w16>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, 1, st);
         case 6: return launch_cfg<Cfg128x128w8>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, 1, st);
         case 4: return launch_cfg<Cfg64x64w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
         default: return launch_cfg<Cfg128x128w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
@@ -521,7 +547,9 @@ psd_status launch_sfb_bf16_blocks(const uint16_t* const* U_p, int64_t ldu, const
         case 0: return launch_cfg_blocks<Cfg128x256w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         case 1: return launch_cfg_blocks<Cfg128x192w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         case 3: return launch_cfg_blocks<Cfg64x128w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
-        case 5: return launch_cfg_blocks<Cfg64x64w16>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
+        case 5:
+            if (lone_groups_bf16(P * B) == 2) return launch_cfg_blocks<Cfg64x64w8>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
+            return launch_cfg_blocks<Cfg64x64w16>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         case 6: return launch_cfg_blocks<Cfg128x128w8>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         case 4: return launch_cfg_blocks<Cfg64x64w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         default: return launch_cfg_blocks<Cfg128x128w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);

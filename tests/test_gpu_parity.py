@@ -388,6 +388,19 @@ def test_sfb_f32_planes_numbers_that_bf16_cannot_hold(M, N, K, what):
     assert bool((dW[ok] == 0).sum() == (want[ok] == 0).sum()) or what == "1e-36"
 
 
+# Tiles that are alone on their compute unit, summed in four chains: K around the stages of one slice (16 / 32 rows), of two and
+# four groups, of odd and even numbers of stages, and where bf16 goes from two groups to four.
+@pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
+@pytest.mark.parametrize("K", [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 96, 127, 129, 193, 320, 511, 512, 513, 640])
+def test_sfb_lone_tiles_bit_exact(K, dtype):
+    for M, N in ((64, 64), (66, 129)):
+        d = inputs.fc_layer_integer(M, N, K, 1, seed=K + M, amax=2)
+        Wg, Mg, _ = run_sfb(d, dtype, 0.25, 0.5)
+        U, V = orc.pack_factors(d["delta"], d["act"])
+        Wr, Mr = orc.sync_fc_sfb(U, V, d["W"], d["Mom"], 0.25, 0.5)
+        assert np.array_equal(Mg, Mr) and np.array_equal(Wg, Wr), (M, N)
+
+
 @pytest.mark.parametrize("tile,splits,M,N,B,P", BF16_SPLIT_LAYERS)
 def test_sfb_bf16_every_tile_that_is_split_bit_exact(tile, splits, M, N, B, P):
     d = inputs.fc_layer_integer(M, N, B, P, seed=M + N)
