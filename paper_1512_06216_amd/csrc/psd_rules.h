@@ -137,10 +137,10 @@ inline int choose_f32_splits(int64_t N, int64_t M, int64_t K, int most, int64_t 
 // ---- fp32 reconstruction on the bf16 pipe (psd_sfb_planes.hip)
 // Tiles of tn x 128, `slots` of them on a compute unit at a time.  us: a launch takes `first`, `update` per 4 M weights, and per
 // 1024 k rows `one` where the busiest compute unit holds a lone tile and `two` for each pair, of which its idle neighbours take
-// `idle` away.  Fitted to 97 layers of 0.2 to 60 M weights, K = 64 .. 4096 (5 to 7 % rms).
+// `idle` away.  Fitted to 114 layers of 0.2 to 60 M weights, K = 64 .. 4096 (5 to 7 % rms).
 struct PlaneTile { int id, tn, slots; double first, one, two, update, idle; };
-constexpr PlaneTile kPlaneTiles[] = {{0, 128, 2, 9.1, 38.1, 67.6, 9.9, 0.18}, {1, 128, 1, 7.6, 36.1, 0, 11.3, 0.29},
-                                     {2, 64, 2, 6.6, 23.7, 39.9, 9.6, 0.11},  {3, 64, 1, 5.6, 21.4, 0, 14.4, 0.21}};
+constexpr PlaneTile kPlaneTiles[] = {{0, 128, 2, 8.5, 37.5, 65.7, 11.0, 0.26}, {1, 128, 1, 7.3, 34.5, 0, 12.1, 0.36},
+                                     {2, 64, 2, 6.0, 22.5, 38.6, 10.9, 0.17},  {3, 64, 1, 5.2, 20.9, 0, 14.6, 0.30}};
 
 inline double planes_cost(const PlaneTile& t, int64_t N, int64_t M, int64_t K, int64_t cus)
 {
@@ -152,15 +152,17 @@ inline double planes_cost(const PlaneTile& t, int64_t N, int64_t M, int64_t K, i
 }
 
 // Which of them takes this layer, -1: none, the fp32 pipe does.  `us`: its cost there, split or not.  Short contractions stay: at
-// K = 128 the fp32 pipe is the faster one for every size of layer (2624 -> 5037 52 against 59 us), from 256 on for small ones only
-// (4096 -> 512 15.4 against 15.6, 4096 -> 1024 25.0 and 23.7, 4096 -> 4096 85 and 79).  Over the 97 layers the choice is 0.6 % off
-// the best one, with the 6 % that have to be gained (0.9 % without).
-constexpr int64_t kMinPlaneRows = 192;
+// K = 128 the fp32 pipe is the faster one for every size of layer (2624 -> 5037 51 against 57 us for the best of the tiles), at
+// K = 192 for some (4720 -> 868 26.7 and 29.6, 1669 -> 780 15.0 and 12.3), at K = 256 for hardly any (672 -> 3462 19.1 and 20.1,
+// 4096 -> 1024 25.2 and 23.9, 4096 -> 4096 90 and 86, 9216 -> 4096 195 and 158), and at K = 320 for none (4096 -> 4096 107 and 91).
+// A tenth has to be gained by these costs: of 132 layers none then gets slower, and the choice is 0.8 % off the best one over the
+// 114; with 6 % it is 0.7 % off, and 672 -> 3462 among the slower ones.
+constexpr int64_t kMinPlaneRows = 256;
 inline int choose_planes(int64_t N, int64_t M, int64_t K, int64_t cus, double us)
 {
     if (K < kMinPlaneRows) return -1;
     int best = -1;
-    us *= 0.94;
+    us *= 0.9;
     for (const PlaneTile& t : kPlaneTiles)
         if (planes_cost(t, N, M, K, cus) < us) {
             us = planes_cost(t, N, M, K, cus);

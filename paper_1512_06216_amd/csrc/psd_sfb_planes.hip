@@ -18,15 +18,19 @@
 // a lane holds four adjacent m of a row in four accumulators and the update moves 512 contiguous bytes per half wavefront
 // without a turn through LDS.  Four (two) wavefronts own 128 x 128 (64 x 128); G groups of them share a tile and contract
 // every G-th slice of 16 k rows, their sums are added up in LDS at the end.
-// The factors pass through registers: each wavefront loads 8 k rows x 64 columns at a time, cuts them (11 vector instructions per
-// two elements) and stores the planes to LDS with k innermost, so that an MFMA operand is one 16-byte read (256 bytes per clock;
-// the transposing reads of K-outer tiles manage 128).  Two LDS buffers; the barrier sits before the last quarter of a
-// slice's MFMAs, whose execution hides the first operand reads of the slice to come; loads are in flight for a whole slice.
+// The factors pass through registers, cut there (11 vector instructions per two elements).  U: a lane loads the 8 k rows of its own
+// n, which is what it feeds to the MFMA, so the planes of U never leave its registers.  V: each wavefront loads 8 k rows x 64
+// columns at a time and stores the planes to LDS with k innermost, so that an MFMA operand is one 16-byte read (256 bytes per
+// clock; the transposing reads of K-outer tiles manage 128) and all wavefronts share them.  Two LDS buffers; the barrier sits
+// before the last quarter of a slice's MFMAs, whose execution hides the first operand reads of the slice to come; loads are in
+// flight for a whole slice.
 //
-// Bound by power: the clock settles at 1.7-1.8 GHz with the MFMA pipe 70-73 % busy.  9216 -> 4096, K = 2048: 727 us, 213 TFLOP/s
-// (fp32 pipe 1066, at its peak); 4096 -> 4096 331 (488), 4096 -> 1000 91 (124), 3000 -> 3000 225 (276).  Tried and not better: one
-// set of accumulators and three workgroups per compute unit (699 us, but twice to three times the error), loads two slices ahead
-// (no change), all vector work in three quarters of a slice or spread more thinly (0-2 % slower), wave priorities (10 % slower).
+// Bound by power: the clock settles at 1.7-1.8 GHz with the MFMA pipe 70-73 % busy.  9216 -> 4096, K = 2048: 700 us, 221 TFLOP/s
+// (fp32 pipe 1066, at its peak; with U through LDS too 727); 4096 -> 4096 319 (488; 331), 4096 -> 1000 89 (124; 91),
+// 3000 -> 3000 222 (276; 225).  Tried and not better: one set of accumulators and three workgroups per compute unit (699 us with U
+// through LDS, but twice to three times the error), loads two slices ahead (no change), all vector work in three quarters of a
+// slice or spread more thinly (0-2 % slower), all operand reads of a quarter before its MFMAs (2-4 % slower), wave priorities
+// (10 % slower).
 #include <atomic>
 #include <type_traits>
 #include "psd_device.h"
@@ -50,17 +54,15 @@ struct Cfg {
     static constexpr int WN = WN_, G = G_, WAVES = WN * G, THREADS = 64 * WAVES;
     static constexpr int TN = 32 * WN, TM = 128;
     static_assert(WN == 2 || WN == 4, "half of the wavefronts load the first 8 rows of a slice, half the others");
-    static constexpr int PU = 2 * TN / 64 / WN, PV = 2 * TM / 64 / WN;            // 8 x 64 patches per wavefront and slice
-    // LDS, one slice: planes of U: [k / 8][n], planes of V: [k / 8][m % 4][m / 4], 16 bytes (8 k) each.  The 64 bytes between the
-    // quarters of V spread the writes of 16 lanes (four adjacent m in four of them) over all banks.
-    static constexpr int A_HALF = TN * 16, A_PLANE = 2 * A_HALF;
-    static constexpr int B_QUARTER = 32 * 16 + 64, B_HALF = 4 * B_QUARTER, B_PLANE = 2 * B_HALF;
-    static constexpr int A_BYTES = 3 * A_PLANE, SLICE_BYTES = A_BYTES + 3 * B_PLANE;
+    static constexpr int PV = 2 * TM / 64 / WN;                                   // 8 x 64 patches of V per wavefront and slice
+    // LDS, one slice: planes of V: [k / 8][m % 4][m / 4], 16 bytes (8 k) each.  The 64 bytes between the quarters spread the writes
+    // of 16 lanes (four adjacent m in four of them) over all banks.
+    static constexpr int B_QUARTER = 32 * 16 + 64, B_HALF = 4 * B_QUARTER, B_PLANE = 2 * B_HALF, SLICE_BYTES = 3 * B_PLANE;
     static constexpr int BUFFER_BYTES = G * SLICE_BYTES, ROWS_BYTES = 64 * row_stride(TM, 0) * 4;
-    static constexpr int LDS_BYTES = 2 * BUFFER_BYTES > ROWS_BYTES ? 2 * BUFFER_BYTES : ROWS_BYTES;
-    // rows of the update, 64 at a time where they go through LDS; accumulators that groups hand over
-    static constexpr int PASSES = TN / 64;
-    static_assert(G * (G - 1) * (64 / G) * WN * 256 <= LDS_BYTES, "what the groups hand over fits");
+    static constexpr int HANDED_BYTES = G * (G - 1) * (64 / G) * WN * 256;        // accumulators that groups hand over
+    static constexpr int larger(int x, int y) { return x > y ? x : y; }
+    static constexpr int LDS_BYTES = larger(2 * BUFFER_BYTES, larger(ROWS_BYTES, HANDED_BYTES));
+    static constexpr int PASSES = TN / 64;                                        // of the update, 64 rows at a time
 };
 
 struct BlockPtrs { const float* u[PSD_MAX_WORKERS]; const float* v[PSD_MAX_WORKERS]; };
@@ -124,7 +126,7 @@ __device__ __forceinline__ void lds_barrier()
 template <class C, bool BLK>
 __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks)
 {
-    constexpr int G = C::G, WN = C::WN, PU = C::PU, PV = C::PV;
+    constexpr int G = C::G, WN = C::WN, PV = C::PV;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     // workgroup -> tile: a contiguous run of the tile sequence per XCD, in groups of GROUP_N tile rows
     const int T = g.tiles_n * g.tiles_m, xcd = blockIdx.x & 7;
@@ -169,41 +171,46 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
         }
     };
 
-    // This wavefront's patches of a slice: rows 8*half .. 8*half + 7; columns ca + 64*j of the U tile, cb + 64*j of the V tile.
-    const int half = w / (WN / 2), part = w % (WN / 2);
-    const int ca = part * (2 * C::TN / WN) + lane, cb = part * (2 * C::TM / WN) + lane;
+    // U: lane l32 + 32*lhi loads rows 8*lhi .. 8*lhi + 7 of column n0 + 32*w + l32, what it feeds to the MFMA.
+    // V: this wavefront's patches are rows 8*half .. 8*half + 7, columns cb + 64*j of the tile.
+    const int half = w / (WN / 2), cb = (w % (WN / 2)) * (2 * C::TM / WN) + lane;
     uint32_t off_u[8], off_v[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        off_u[k] = (8 * half + k) * row_a + static_cast<uint32_t>(n0 + ca) * 4;
+        off_u[k] = (8 * lhi + k) * row_a + static_cast<uint32_t>(n0 + 32 * w + l32) * 4;
         off_v[k] = (8 * half + k) * row_b + static_cast<uint32_t>(m0 + cb) * 4;
         asm("" : "+v"(off_u[k]), "+v"(off_v[k]));         // kept in registers
     }
-    float patch[PU + PV][8];
+    float patch[PV + 1][8];                      // the last one of U
     auto load = [&](int p) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            patch[p][k] = p < PU ? load_or_zero(u, off_u[k] + p * 256) : load_or_zero(v, off_v[k] + (p - PU) * 256);
+        for (int k = 0; k < 8; ++k) patch[p][k] = p < PV ? load_or_zero(v, off_v[k] + p * 256) : load_or_zero(u, off_u[k]);
     };
     char* const mine = lds + group * C::SLICE_BYTES;
-    const int wr_a = half * C::A_HALF + ca * 16;
-    const int wr_b = C::A_BYTES + half * C::B_HALF + (cb & 3) * C::B_QUARTER + (cb >> 2) * 16;
-    u32x4 h, m, l;
-    constexpr int ITEMS = 2 * (PU + PV);
-    auto item = [&](int buf, int i) {            // half a patch of the slice in registers -> buffer buf; then the next slice's loads
+    const int wr_b = half * C::B_HALF + (cb & 3) * C::B_QUARTER + (cb >> 2) * 16;
+    u32x4 fa[2][3];                              // operand of U: planes h, m, l
+    u32x4 fb[2][3], h, m, l;
+    constexpr int ITEMS = 2 * (PV + 1);
+    // Half a patch of the slice in registers -> LDS buffer (operand) buf; then the next slice's loads.
+    auto item = [&](int buf, int i) {
         const int p = i >> 1;
 #pragma unroll
         for (int q = 2 * (i & 1); q < 2 * (i & 1) + 2; ++q) {
             uint32_t hh, mm, ll;
             cut(patch[p][2 * q], patch[p][2 * q + 1], hh, mm, ll);
-            h[q] = hh; m[q] = mm; l[q] = ll;
+            if (p < PV) {
+                h[q] = hh; m[q] = mm; l[q] = ll;
+            } else {
+                fa[buf][0][q] = hh; fa[buf][1][q] = mm; fa[buf][2][q] = ll;
+            }
         }
         if (i & 1) {
-            char* to = mine + buf * C::BUFFER_BYTES + (p < PU ? wr_a + p * 64 * 16 : wr_b + (p - PU) * 16 * 16);
-            const int plane = p < PU ? C::A_PLANE : C::B_PLANE;
-            *reinterpret_cast<u32x4*>(to) = h;
-            *reinterpret_cast<u32x4*>(to + plane) = m;
-            *reinterpret_cast<u32x4*>(to + 2 * plane) = l;
+            if (p < PV) {
+                char* to = mine + buf * C::BUFFER_BYTES + wr_b + p * 16 * 16;
+                *reinterpret_cast<u32x4*>(to) = h;
+                *reinterpret_cast<u32x4*>(to + C::B_PLANE) = m;
+                *reinterpret_cast<u32x4*>(to + 2 * C::B_PLANE) = l;
+            }
             load(p);
         }
         if (i == ITEMS - 1) advance();
@@ -214,38 +221,34 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
     for (int j = 0; j < 4; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[j][r] = low[j][r] = 0.f;
-    const int rd_a = lhi * C::A_HALF + (32 * w + l32) * 16, rd_b = C::A_BYTES + lhi * C::B_HALF + l32 * 16;
-    bf16x8 fa[2][3], fb[2][3];
-    auto read_a = [&](int buf) {
-#pragma unroll
-        for (int s = 0; s < 3; ++s)
-            fa[buf][s] = *reinterpret_cast<const bf16x8*>(mine + buf * C::BUFFER_BYTES + rd_a + s * C::A_PLANE);
-    };
+    const int rd_b = lhi * C::B_HALF + l32 * 16;
     auto read_b = [&](int buf, int j) {
 #pragma unroll
         for (int s = 0; s < 3; ++s)
-            fb[j & 1][s] = *reinterpret_cast<const bf16x8*>(mine + buf * C::BUFFER_BYTES + rd_b + j * C::B_QUARTER + s * C::B_PLANE);
+            fb[j & 1][s] = *reinterpret_cast<const u32x4*>(mine + buf * C::BUFFER_BYTES + rd_b + j * C::B_QUARTER + s * C::B_PLANE);
     };
     auto mma = [&](int buf, int j) {             // planes: 0 = h, 1 = m, 2 = l
-        const bf16x8 (&a)[3] = fa[buf], (&b)[3] = fb[j & 1];
-        low[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], b[0], low[j], 0, 0, 0);
-        low[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[2], low[j], 0, 0, 0);
-        low[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[1], low[j], 0, 0, 0);
-        low[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[0], low[j], 0, 0, 0);
-        low[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[1], low[j], 0, 0, 0);
-        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], acc[j], 0, 0, 0);
+        auto product = [&](int pa, int pb, const f32x16& c) {
+            return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[buf][pa]), __builtin_bit_cast(bf16x8, fb[j & 1][pb]),
+                                                           c, 0, 0, 0);
+        };
+        low[j] = product(2, 0, low[j]);
+        low[j] = product(0, 2, low[j]);
+        low[j] = product(1, 1, low[j]);
+        low[j] = product(1, 0, low[j]);
+        low[j] = product(0, 1, low[j]);
+        acc[j] = product(0, 0, acc[j]);
     };
 
     const int steps = (g.K + SLICE * G - 1) / (SLICE * G);
 #pragma unroll
-    for (int p = 0; p < PU + PV; ++p) load(p);
+    for (int p = 0; p < PV + 1; ++p) load(p);
     advance();
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) item(0, i);
     lds_barrier();
 #pragma unroll
     for (int i = 0; i < ITEMS / 4; ++i) item(1, i);
-    read_a(0);
     read_b(0, 0);
     // Contracts the slices in buffer buf.  Behind the barrier nobody reads them any more, and those in the other buffer are whole.
     auto step = [&](int buf) {
@@ -255,7 +258,6 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
                 read_b(buf, j + 1);
             } else {
                 lds_barrier();
-                read_a(buf ^ 1);
                 read_b(buf ^ 1, 0);
             }
             const int q = (j + 1) & 3;
@@ -328,36 +330,39 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
                 least = b < least ? b : least;
             }
         if (__any(nan != 0.f || least < 2 * 0x0b800000u - 1)) {                // 0x0b800000: 2^-104
-            // in four runs over k, like the groups of the fp32 kernel for small layers: half the error of one run
-            f32x16 total[4], sum[4];
+            // Two blocks at a time, in four runs over k as in the fp32 kernel for small layers: half the error of one run.
             const int run = ((g.K + 3) / 4 + 1) & ~1;
-            for (int k0 = 0; k0 < g.K; k0 += run) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+            for (int j0 = 0; j0 < 4; j0 += 2) {
+                f32x16 total[2], sum[2];
+                for (int k0 = 0; k0 < g.K; k0 += run) {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        total[j][r] = k0 == 0 ? 0.f : total[j][r] + sum[j][r];
-                        sum[j][r] = 0.f;
+                    for (int j = 0; j < 2; ++j)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            total[j][r] = k0 == 0 ? 0.f : total[j][r] + sum[j][r];
+                            sum[j][r] = 0.f;
+                        }
+                    for (int k = k0; k < k0 + run && k < g.K; k += 2) {        // lanes 0..31 feed k, the others k + 1
+                        const int kb = BLK ? k / g.block_rows : 0, row = k - kb * g.block_rows * BLK;
+                        Feed fu, fv;
+                        fu.aim(BLK ? uniform_ptr(blocks->u[kb]) : g.U, uint64_t(row) * row_a, g.u_bytes);
+                        fv.aim(BLK ? uniform_ptr(blocks->v[kb]) : g.V, uint64_t(row) * row_b, g.v_bytes);
+                        const float a = load_or_zero(fu, lhi * row_a + static_cast<uint32_t>(n0 + 32 * w + l32) * 4);
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            sum[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                                a, load_or_zero(fv, lhi * row_b + static_cast<uint32_t>(m0 + 4 * l32 + j0 + j) * 4), sum[j], 0, 0, 0);
                     }
-                for (int k = k0; k < k0 + run && k < g.K; k += 2) {            // lanes 0..31 feed k, the others k + 1
-                    const int kb = BLK ? k / g.block_rows : 0, row = k - kb * g.block_rows * BLK;
-                    Feed fu, fv;
-                    fu.aim(BLK ? uniform_ptr(blocks->u[kb]) : g.U, uint64_t(row) * row_a, g.u_bytes);
-                    fv.aim(BLK ? uniform_ptr(blocks->v[kb]) : g.V, uint64_t(row) * row_b, g.v_bytes);
-                    const float a = load_or_zero(fu, lhi * row_a + static_cast<uint32_t>(n0 + 32 * w + l32) * 4);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        sum[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-                            a, load_or_zero(fv, lhi * row_b + static_cast<uint32_t>(m0 + 4 * l32 + j) * 4), sum[j], 0, 0, 0);
                 }
+#pragma unroll
+                for (int to = 0; to < G; ++to)
+                    if (to == group)
+#pragma unroll
+                        for (int q = 0; q < NR; ++q)
+#pragma unroll
+                            for (int j = 0; j < 2; ++j) d[q][j0 + j] = total[j][to * NR + q] + sum[j][to * NR + q];
             }
-#pragma unroll
-            for (int to = 0; to < G; ++to)
-                if (to == group)
-#pragma unroll
-                    for (int q = 0; q < NR; ++q)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) d[q][j] = total[j][to * NR + q] + sum[j][to * NR + q];
         }
     }
 

@@ -309,9 +309,9 @@ def test_sfb_every_tile_the_rules_choose_bit_exact(dtype, M, N, B, P):
 # Layers that go to the bf16 pipe in planes, every tile with rows of W on cache lines, on quads and anywhere; and layers that stay
 # on the fp32 pipe with 64 x 128 tiles.  (tests/test_rules.py checks that the rules say so.)
 PLANE_LAYERS = [  # tile, M, N, B, P
-    (0, 4448, 1345, 80, 3), (0, 1804, 3360, 80, 3), (0, 5378, 1092, 16, 16), (1, 5568, 330, 96, 3), (1, 5812, 324, 48, 6),
-    (1, 5679, 323, 96, 3), (2, 928, 1593, 32, 8), (2, 3676, 399, 64, 4), (2, 1199, 1227, 16, 16), (3, 5472, 132, 32, 6),
-    (3, 5444, 134, 32, 6), (3, 5715, 129, 64, 3)]
+    (0, 4896, 1220, 64, 4), (0, 5808, 1033, 128, 2), (0, 5814, 1029, 32, 8), (1, 5664, 324, 48, 6), (1, 5640, 333, 144, 2),
+    (1, 5693, 322, 96, 3), (2, 4704, 395, 144, 2), (2, 4788, 396, 48, 6), (2, 4713, 392, 48, 6), (3, 5600, 131, 144, 2),
+    (3, 5744, 133, 32, 8), (3, 5506, 133, 48, 6)]
 F32_PIPE_LAYERS = [(1201, 4960, 583, 32, 3), (1201, 3476, 835, 32, 3)]
 
 
@@ -344,7 +344,7 @@ def _planes_dw(M, N, K, U, V):
 
 
 # K of whole slices and not, for the tiles of one, two and four groups
-@pytest.mark.parametrize("M,N,K", [(5378, 1092, 256), (1804, 3360, 243), (5679, 323, 291), (928, 1593, 258), (5715, 129, 201)])
+@pytest.mark.parametrize("M,N,K", [(4896, 1220, 272), (5808, 1033, 257), (5693, 322, 293), (4713, 392, 299), (5506, 133, 303)])
 def test_sfb_f32_planes_hold_all_24_bits(M, N, K):
     """One error per sample is a power of two and the others are zero (and the other way round): a row of dW is a row of
     activations, bit for bit."""
@@ -362,7 +362,7 @@ def test_sfb_f32_planes_hold_all_24_bits(M, N, K):
     assert torch.equal(dW.double(), want)
 
 
-@pytest.mark.parametrize("M,N,K", [(5378, 1092, 256), (5679, 323, 291), (928, 1593, 258), (5715, 129, 201)])
+@pytest.mark.parametrize("M,N,K", [(4896, 1220, 272), (5693, 322, 293), (4713, 392, 299), (5506, 133, 303)])
 @pytest.mark.parametrize("what", ["inf", "nan", "largest", "1e-32", "1e-36"])
 def test_sfb_f32_planes_numbers_that_bf16_cannot_hold(M, N, K, what):
     """Infinities and NaN where the definition has them, FLT_MAX (whose nearest bf16 is infinite), and factors whose third part

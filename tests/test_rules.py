@@ -123,13 +123,13 @@ def test_layers_of_the_parity_tests_go_to_the_pipe_they_stand_for(rules):
     assert seen == {(t, a) for t in range(4) for a in (32, 4, 1)}
     for cover, M, N, B, P in parity.F32_PIPE_LAYERS:
         assert rules.f32_planes(N, M, B * P, CUS) == -1 and rules.f32_choice(N, M, B * P, CUS) == cover
-    for M, N, K, tile in ((5378, 1092, 256, 0), (1804, 3360, 243, 0), (5679, 323, 291, 1), (928, 1593, 258, 2), (5715, 129, 201, 3)):
+    for M, N, K, tile in ((4896, 1220, 272, 0), (5808, 1033, 257, 0), (5693, 322, 293, 1), (4713, 392, 299, 2), (5506, 133, 303, 3)):
         assert rules.f32_planes(N, M, K, CUS) == tile
 
 
 def test_short_contractions_and_small_layers_stay_on_the_fp32_pipe(rules):
     for M, N in ((64, 64), (1024, 1000), (4096, 4096), (9216, 4096), (25088, 4096), (4096, 21841)):
-        for K in (1, 16, 48, 128, 191):
+        for K in (1, 16, 48, 128, 255):
             assert rules.f32_planes(N, M, K, CUS) == -1
     for M, N, K in ((64, 64, 4096), (256, 128, 128), (1024, 1000, 256), (512, 512, 2048)):
         assert rules.f32_planes(N, M, K, CUS) == -1
