@@ -177,31 +177,43 @@ inline int choose_planes(int64_t N, int64_t M, int64_t K, int64_t cus, double us
 // Fitted to 9216 -> 4096, 4096 -> 1000 and 1024 -> 1000 over K = 32 .. 2048.  Against what launches alone take: 3000 -> 21841 352
 // for 392 us, 4096 -> 21841 479 for 447, 25088 -> 4096 540 for 535, 4096 -> 4096 94 for 97, 3000 -> 3000 64 for 67, 4096 -> 1000
 // 27.5 for 30.5, 1024 -> 1000, K = 256 6.5 for 6.4; 9216 -> 4096 within 4 % for K = 512 .. 2048, 11 % short at K = 32, 12 % at
-// K = 4096.  The tiles contracted by several groups of wavefronts fill a compute unit, so they are for layers
-// that have one tile for each at most: 1024 -> 1000, K = 2048 17.4 us with four wavefronts per 64 x 64 tile, 12.5 with sixteen.
-struct Bf16Tile { int id, tn, tm; bool alone; double area, loop, first, solo; };
-constexpr Bf16Tile kTiles[] = {{0, 128, 256, false, 8, 9.9, 14.7, 15.1}, {1, 128, 192, false, 6, 6.6, 11.9, 8.3},
-                               {2, 128, 128, false, 4, 5.7, 8.6, 7.1},   {3, 64, 128, false, 2, 3.8, 5.1, 6.6},
-                               {4, 64, 64, false, 1, 2.5, 3.9, 6.0},     {5, 64, 64, true, 1, 0, 3.75, 3.4},
-                               {6, 128, 128, true, 4, 0, 8.3, 5.9}};
+// K = 4096.  The tiles contracted by several groups of wavefronts are for layers that have `most` of them for each compute unit
+// at most, which they fill: 1024 -> 1000, K = 2048 17.4 us with four wavefronts per 64 x 64 tile, 12.5 with sixteen.  Two tiles of
+// two groups each (id 7) against the better one of the tiles of four wavefronts, of which a compute unit then holds one or two:
+// 2048 -> 1024 11.7 -> 9.7 us at K = 384, 16.1 -> 12.8 at K = 1024, 23.5 -> 21.6 at K = 2560; 768 -> 2048, K = 1024 14.7 -> 12.2,
+// 2149 -> 768 14.1 -> 13.2.  With a third tile on some compute unit that is over: 5460 -> 384 (516 tiles), K = 384 12.1 and 13.2;
+// short sums gain only where rows of W start on cache lines (224 -> 6787, K = 136 9.2 and 7.7, 12928 -> 96, K = 416 10.3 and 8.8;
+// 9964 -> 182, K = 160 8.6 and 9.1, 229 -> 5600, K = 312 9.4 and 9.7, 2149 -> 768, K = 384 10.4 and 10.1); and
+// from 4096 on a sum split over workgroups is the better one for some (1088 -> 1024 24.0 and 25.8, 320 -> 5280 43.4 and 38.1).
+struct Bf16Tile { int id, tn, tm, most; double area, loop, first, solo; };
+constexpr Bf16Tile kTiles[] = {{0, 128, 256, 0, 8, 9.9, 14.7, 15.1}, {1, 128, 192, 0, 6, 6.6, 11.9, 8.3},
+                               {2, 128, 128, 0, 4, 5.7, 8.6, 7.1},   {3, 64, 128, 0, 2, 3.8, 5.1, 6.6},
+                               {4, 64, 64, 0, 1, 2.5, 3.9, 6.0},     {5, 64, 64, 1, 1, 0, 3.75, 3.4},
+                               {6, 128, 128, 1, 4, 0, 8.3, 5.9},     {7, 64, 64, 2, 1, 0.3, 5.3, 4.6}};
 constexpr double kNever = 1e30;
+constexpr int64_t kMinPairRows = 256, kMinPairRowsOffLines = 384, kMaxPairRows = 3072;
 
 // us for the launch that covers N x M over K rows
 inline double launch_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K, int64_t cus)
 {
     const int64_t tiles = ((N + t.tn - 1) / t.tn) * ((M + t.tm - 1) / t.tm);
     const double k = static_cast<double>(K) / 1024, share = static_cast<double>(tiles) / cus, update = 3.1 * t.area;
+    if (t.most > 0 && tiles > t.most * cus) return kNever;
+    if (t.most == 2) {                              // (fitted to 50 layers of K = 36 .. 3584)
+        if (tiles <= cus || K < (M % 32 ? kMinPairRowsOffLines : kMinPairRows) || K > kMaxPairRows) return kNever;
+        return t.first + (M % 32 ? 1.1 : 0) + 0.4 * update * share + (t.solo + t.loop * share) * k;
+    }
     if (tiles <= cus) return t.first + (M % 32 ? 1.5 : 0) + 0.6 * update * share + t.solo * k;
     // the last, partly filled round: the loop takes as long as a full one, the update shares HBM among fewer
     const double rounds = static_cast<double>((tiles + cus - 1) / cus), tail = (rounds - share) * (t.area > 2 ? 0.5 : 0.2);
-    return t.alone ? kNever : 5 + update * (share + tail) + t.loop * k * rounds;
+    return 5 + update * (share + tail) + t.loop * k * rounds;
 }
 
 // ... and when `splits` workgroups per tile store partial sums that a second launch adds up
 inline double split_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K, int splits, int64_t cus)
 {
     const int64_t groups = ((N + t.tn - 1) / t.tn) * ((M + t.tm - 1) / t.tm) * splits;
-    if (t.alone) return kNever;
+    if (t.most > 0) return kNever;
     const double k = static_cast<double>(K) / splits / 1024, sum = 4 + (16.0 + 4 * splits) * N * M / 5e6;
     if (groups > cus) return sum + 5 + static_cast<double>((groups + cus - 1) / cus) * (0.8 * t.area + t.loop * k);
     return sum + t.first + t.solo * k;              // (the partial sums stay in the caches)
@@ -220,8 +232,9 @@ inline Bf16Tile choose_bf16(int64_t N, int64_t M, int64_t K, int64_t cus, int pi
 // Groups of four wavefronts for a 64 x 64 tile that is alone on its compute unit (id 5), summed in four chains: two groups keep
 // two sets of accumulators each, which is half the wavefronts for the same work outside the loop, and meet a barrier twice as
 // often inside.  us with two and four groups: 500 -> 700, K = 64 4.9 and 5.7; 700 -> 500, K = 256 5.7 and 6.1, K = 512 6.6 and 7.1;
-// 1024 -> 1000, K = 256 6.8 and 6.8, K = 512 8.2 and 8.2, K = 1024 11.2 and 10.6.
-inline int lone_groups_bf16(int64_t K) { return K <= 512 ? 2 : 4; }
+// 576 -> 913, K = 640 6.8 and 7.3; 192 -> 3422, K = 864 7.7 and 7.9; 660 -> 448, K = 1168 8.7 and 8.7; 1024 -> 1000, K = 1024 11.2
+// and 10.6; 845 -> 384, K = 1920 11.1 and 10.3.
+inline int lone_groups_bf16(int64_t K) { return K <= 896 ? 2 : 4; }
 
 // ... and how many ways to split the sum over k, at most `most`
 inline Bf16Tile choose_bf16_split(int64_t N, int64_t M, int64_t K, int most, int64_t cus, int pinned, int* splits)

@@ -494,7 +494,7 @@ using Cfg128x128w4 = Cfg<2, 2, 2, 2, 4, 2>;   // 64 KiB, two per CU
 using Cfg64x128w4 = Cfg<2, 2, 1, 2, 4, 3>;    // 48 KiB, three per CU
 using Cfg64x64w4 = Cfg<2, 2, 1, 1, 4, 4>;     // 32 KiB, five per CU: small layers
 using Cfg64x64w16 = Cfg<2, 2, 1, 1, 4, 4, 4>; // four groups, 128 KiB, one per CU
-using Cfg64x64w8 = Cfg<2, 2, 1, 1, 4, 4, 2, 2>; // two groups of two chains, 64 KiB
+using Cfg64x64w8 = Cfg<2, 2, 1, 1, 4, 4, 2, 2>; // two groups of two chains, 64 KiB, two per CU
 using Cfg128x128w8 = Cfg<2, 2, 2, 2, 4, 2, 2>; // two groups, 128 KiB, one per CU
 
 }  // namespace
@@ -514,8 +514,8 @@ psd_status launch_sfb_bf16(const uint16_t* U, int64_t ldu, const uint16_t* V, in
     int splits;
     Bf16Tile t = choose_bf16_split(N, M, K, most_splits, device_cu_count(), tune_value(PSD_TUNE_SFB_BF16_TILE), &splits);
     // the longer stages of the grouped tiles read further ahead than the 32-bit offsets reach in a very large factor matrix
-    if (t.alone && !factors_in_reach(K, ldu, ldv, 2, bf16_reserve(t.id == 5 ? Cfg64x64w16::KT : Cfg128x128w8::KT)))
-        t = kTiles[t.id == 5 ? 4 : 2];
+    if (t.most > 0 && !factors_in_reach(K, ldu, ldv, 2, bf16_reserve(t.id == 5 ? Cfg64x64w16::KT : Cfg128x128w8::KT)))
+        t = kTiles[t.id == 6 ? 2 : 4];
     switch (t.id) {
         case 0: return launch_cfg<Cfg128x256w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
         case 1: return launch_cfg<Cfg128x192w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
@@ -524,6 +524,7 @@ psd_status launch_sfb_bf16(const uint16_t* U, int64_t ldu, const uint16_t* V, in
             if (lone_groups_bf16(K) == 2)
                 return launch_cfg<Cfg64x64w8>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, 1, st);
             return launch_cfg<Cfg64x64w16>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, 1, st);
+        case 7: return launch_cfg<Cfg64x64w8>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, 1, st);
         case 6: return launch_cfg<Cfg128x128w8>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, 1, st);
         case 4: return launch_cfg<Cfg64x64w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
         default: return launch_cfg<Cfg128x128w4>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, part, splits, st);
@@ -550,6 +551,7 @@ psd_status launch_sfb_bf16_blocks(const uint16_t* const* U_p, int64_t ldu, const
         case 5:
             if (lone_groups_bf16(P * B) == 2) return launch_cfg_blocks<Cfg64x64w8>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
             return launch_cfg_blocks<Cfg64x64w16>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
+        case 7: return launch_cfg_blocks<Cfg64x64w8>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         case 6: return launch_cfg_blocks<Cfg128x128w8>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         case 4: return launch_cfg_blocks<Cfg64x64w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         default: return launch_cfg_blocks<Cfg128x128w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);

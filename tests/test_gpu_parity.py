@@ -401,6 +401,28 @@ def test_sfb_lone_tiles_bit_exact(K, dtype):
         assert np.array_equal(Mg, Mr) and np.array_equal(Wg, Wr), (M, N)
 
 
+# Layers of two 64 x 64 tiles of two groups for each compute unit: the fewest and the most of them, the shortest and longest sums,
+# rows of W on lines and not, K of whole stages (64 rows) and not.  (tests/test_rules.py checks that the rules choose them.)
+BF16_PAIR_LAYERS = [(16448, 64, 32, 8), (2017, 1001, 32, 12), (263, 3521, 55, 7), (2048, 1024, 384, 8), (1088, 1027, 181, 2)]
+
+
+@pytest.mark.parametrize("M,N,B,P", BF16_PAIR_LAYERS)
+def test_sfb_bf16_two_grouped_tiles_per_compute_unit_bit_exact(M, N, B, P):
+    """Stacked, and (blocks of whole slices) read in place as P blocks."""
+    d = inputs.fc_layer_integer(M, N, B, P, seed=M + N, amax=2)
+    plan, U, ldu, V, ldv = run_pack(d, psd.BF16)
+    Uo, Vo = orc.pack_factors(d["delta"], d["act"])
+    Wr, Mr = orc.sync_fc_sfb(Uo, Vo, d["W"], d["Mom"], 0.25, 0.5, wd=0.25)
+    for blocks in (False, True)[:1 + (B % 32 == 0)]:
+        W, Mom = dev(d["W"]), dev(d["Mom"])
+        if blocks:
+            psd.sync_fc_sfb_blocks(plan, psd.BF16, list(U.split(B)), ldu, list(V.split(B)), ldv, W, Mom, 0.25, 0.5, wd=0.25)
+        else:
+            psd.sync_fc_sfb(plan, psd.BF16, U, ldu, V, ldv, W, Mom, 0.25, 0.5, wd=0.25)
+        torch.cuda.synchronize()
+        assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr), blocks
+
+
 @pytest.mark.parametrize("tile,splits,M,N,B,P", BF16_SPLIT_LAYERS)
 def test_sfb_bf16_every_tile_that_is_split_bit_exact(tile, splits, M, N, B, P):
     d = inputs.fc_layer_integer(M, N, B, P, seed=M + N)

@@ -115,6 +115,17 @@ def test_the_parity_tests_reach_every_tile_stacked_from_blocks_and_split(rules):
     assert split == {True, False}
 
 
+def test_pairs_of_grouped_tiles_are_for_layers_that_have_two_for_each_compute_unit_at_most(rules):
+    tiles = set()
+    for M, N, B, P in parity.BF16_PAIR_LAYERS:
+        assert rules.bf16_choice(N, M, B * P, 1, CUS) == 71, (M, N)
+        tiles.add(-(-N // 64) * -(-M // 64))
+    assert min(tiles) == CUS + 1 and max(tiles) == 2 * CUS
+    for M, N, K in ((64, 64, 512), (1024, 1000, 2048), (1024, 1024, 256), (5460, 384, 512), (4096, 1000, 512), (9216, 4096, 2048),
+                    (2048, 1024, 255), (2017, 1001, 383), (2048, 1024, 3073)):
+        assert rules.bf16_choice(N, M, K, 1, CUS) // 10 != 7
+
+
 def test_layers_of_the_parity_tests_go_to_the_pipe_they_stand_for(rules):
     seen = set()
     for tile, M, N, B, P in parity.PLANE_LAYERS:
