@@ -65,7 +65,8 @@ struct Args {
     int N, M, K;
     float lr, mu, wd;
     int tiles_m;                    // tiles per row of tiles of the main grid
-    int big, tiles;                 // workgroups [0, big) own 128 x 128 tiles, the others smaller ones
+    bool runs;                      // place_of
+    int big, tiles;                 // tiles (PART: of one split), the first `big` of 128 x 128, the others smaller ones
     uint32_t u_bytes, v_bytes;      // of the stacked matrices, or of ONE block
     float* part;                    // PART: partial dW matrices, part_stride apart
     int64_t part_stride;
@@ -305,6 +306,19 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
     }
 }
 
+// Workgroup b of T -> place in the sequence of tiles, along the rows of W.  Workgroups go round-robin over the 8 XCDs, whose L2s do
+// not see each other's lines.  Where rows of W do not start on cache lines, neighbouring tiles share the lines at their borders
+// (`runs`), and each XCD takes a contiguous run of the sequence: a line that two XCDs write parts of goes to memory in parts.
+// 1399 -> 1365, K = 128 15.8 -> 12.0 us, 2149 -> 768 14.5 -> 11.4, 1001 -> 999, K = 256 12.4 -> 10.4, 4095 -> 1000, K = 64
+// 23.5 -> 19.0, 9215 -> 4096, K = 128 150 -> 150.  On lines the tiles of an XCD are every eighth of a row, which re-use the same
+// columns of V: 9216 -> 4096, K = 128 130 us, in runs 137; 4096 -> 1000, K = 64 16.9 and 17.5.
+__device__ __forceinline__ int place_of(const Args& g, int b, int T)
+{
+    if (!g.runs) return b;
+    const int xcd = b & 7;
+    return xcd * (T >> 3) + (xcd < (T & 7) ? xcd : (T & 7)) + (b >> 3);
+}
+
 // Workgroup b owns tile b of (64*BN) x (64*BM).  MIXED: workgroups [0, big) own 128 x 128 tiles and the tiles after them are cut
 // into (2 / BN) * (2 / BM) smaller ones.
 template <int BN, int BM, bool MIXED, bool PART, bool BLK>
@@ -316,12 +330,14 @@ __device__ __forceinline__ void grid_body(const Args& g, const BlockPtrs* blocks
         const int split = __builtin_amdgcn_readfirstlane(b / g.tiles), tile = b - split * g.tiles;   // (the division runs on the vector ALU)
         tile_body<BN, BM, 1, true, false>(g, nullptr, lds, int64_t(tile / g.tiles_m) * 64 * BN, int64_t(tile % g.tiles_m) * 64 * BM, split);
     } else if constexpr (!MIXED) {
-        tile_body<BN, BM, 1, false, BLK>(g, blocks, lds, int64_t(b / g.tiles_m) * 64 * BN, int64_t(b % g.tiles_m) * 64 * BM, 0);
+        const int lin = place_of(g, b, g.tiles);
+        tile_body<BN, BM, 1, false, BLK>(g, blocks, lds, int64_t(lin / g.tiles_m) * 64 * BN, int64_t(lin % g.tiles_m) * 64 * BM, 0);
     } else if (b < g.big) {
-        tile_body<2, 2, 1, false, BLK>(g, blocks, lds, int64_t(b / g.tiles_m) * 128, int64_t(b % g.tiles_m) * 128, 0);
+        const int lin = place_of(g, b, g.big);
+        tile_body<2, 2, 1, false, BLK>(g, blocks, lds, int64_t(lin / g.tiles_m) * 128, int64_t(lin % g.tiles_m) * 128, 0);
     } else {
         constexpr int PN = 2 / BN, PM = 2 / BM;
-        const int i = b - g.big, tile = g.big + i / (PN * PM), sub = i % (PN * PM);
+        const int i = place_of(g, b - g.big, g.tiles - g.big), tile = g.big + i / (PN * PM), sub = i % (PN * PM);
         tile_body<BN, BM, 1, false, BLK>(g, blocks, lds, int64_t(tile / g.tiles_m) * 128 + (sub / PM) * 64 * BN,
                                       int64_t(tile % g.tiles_m) * 128 + (sub % PM) * 64 * BM, 0);
     }
@@ -345,14 +361,16 @@ template <int BN, int BM>
 __global__ void __launch_bounds__(256 * LONE_GROUPS) sfb_f32_groups_kernel(const Args g)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    tile_body<BN, BM, LONE_GROUPS, false, false, CHAINS / LONE_GROUPS>(g, nullptr, lds, int64_t(blockIdx.x / g.tiles_m) * 64 * BN, int64_t(blockIdx.x % g.tiles_m) * 64 * BM, 0);
+    const int lin = place_of(g, blockIdx.x, g.tiles);
+    tile_body<BN, BM, LONE_GROUPS, false, false, CHAINS / LONE_GROUPS>(g, nullptr, lds, int64_t(lin / g.tiles_m) * 64 * BN, int64_t(lin % g.tiles_m) * 64 * BM, 0);
 }
 
 template <int BN, int BM>
 __global__ void __launch_bounds__(256 * LONE_GROUPS) sfb_f32_groups_blocks_kernel(const Args g, const BlockPtrs blocks)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    tile_body<BN, BM, LONE_GROUPS, false, true, CHAINS / LONE_GROUPS>(g, &blocks, lds, int64_t(blockIdx.x / g.tiles_m) * 64 * BN, int64_t(blockIdx.x % g.tiles_m) * 64 * BM, 0);
+    const int lin = place_of(g, blockIdx.x, g.tiles);
+    tile_body<BN, BM, LONE_GROUPS, false, true, CHAINS / LONE_GROUPS>(g, &blocks, lds, int64_t(lin / g.tiles_m) * 64 * BN, int64_t(lin % g.tiles_m) * 64 * BM, 0);
 }
 
 // the pinned tile is (64 * pinned) x 128; 0: none is pinned
@@ -402,6 +420,7 @@ Args common_args(int64_t ldu, int64_t ldv, float* W, float* Mom, int64_t N, int6
     g.ldu = ldu; g.ldv = ldv; g.W = W; g.Mom = Mom;
     g.N = static_cast<int>(N); g.M = static_cast<int>(M); g.K = static_cast<int>(K);
     g.lr = lr; g.mu = mu; g.wd = wd;
+    g.runs = M % 32 != 0 || reinterpret_cast<uintptr_t>(W) % 128 != 0 || reinterpret_cast<uintptr_t>(Mom) % 128 != 0;
     return g;
 }
 
@@ -412,6 +431,7 @@ psd_status launch_cover(Args& g, const BlockPtrs* blocks, hipStream_t st)
     if (c.groups > 0x7fffffff) return PSD_E_INVALID;
     g.big = static_cast<int>(c.big);
     g.tiles_m = static_cast<int>(c.tiles_m);
+    g.tiles = static_cast<int>(c.groups);
     if (c.g == 4) return start_groups<1, 1>(g, blocks, c.groups, st);
     if (c.big > 0) return c.bm == 2 ? start<1, 2, true, false>(g, blocks, c.groups, st) : start<1, 1, true, false>(g, blocks, c.groups, st);
     return c.bm == 2 ? start<1, 2, false, false>(g, blocks, c.groups, st) : start<1, 1, false, false>(g, blocks, c.groups, st);

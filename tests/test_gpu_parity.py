@@ -401,6 +401,23 @@ def test_sfb_lone_tiles_bit_exact(K, dtype):
         assert np.array_equal(Mg, Mr) and np.array_equal(Wg, Wr), (M, N)
 
 
+@pytest.mark.parametrize("M,N,B,P,shift", [(2720, 96, 16, 4, 4), (2720, 800, 16, 4, 8), (2720, 1485, 16, 15, 4), (8192, 200, 16, 4, 0)])
+def test_sfb_f32_rows_of_whole_lines_that_do_not_start_on_lines_bit_exact(M, N, B, P, shift):
+    """M is a multiple of 32, W and Mom begin `shift` elements into a line: tiles share lines all the same."""
+    d = inputs.fc_layer_integer(M, N, B, P, seed=M + N)
+    plan, U, ldu, V, ldv = run_pack(d, psd.F32)
+    Uo, Vo = orc.pack_factors(d["delta"], d["act"])
+    Wr, Mr = orc.sync_fc_sfb(Uo, Vo, d["W"], d["Mom"], 0.25, 0.5)
+    room = [torch.full((N * M + 64,), 3.0, device=DEV) for _ in range(2)]
+    W, Mom = (r[shift:shift + N * M].view(N, M) for r in room)
+    W.copy_(dev(d["W"]))
+    Mom.copy_(dev(d["Mom"]))
+    psd.sync_fc_sfb(plan, psd.F32, U, ldu, V, ldv, W, Mom, 0.25, 0.5)
+    torch.cuda.synchronize()
+    assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr)
+    assert all(bool((r[:shift] == 3).all()) and bool((r[shift + N * M:] == 3).all()) for r in room)
+
+
 # Layers of two 64 x 64 tiles of two groups for each compute unit: the fewest and the most of them, the shortest and longest sums,
 # rows of W on lines and not, K of whole stages (64 rows) and not.  (tests/test_rules.py checks that the rules choose them.)
 BF16_PAIR_LAYERS = [(16448, 64, 32, 8), (2017, 1001, 32, 12), (263, 3521, 55, 7), (2048, 1024, 384, 8), (1088, 1027, 181, 2)]
