@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "psd_rules.h"
 #include "psd_update.h"
 
 namespace psd {
@@ -27,6 +28,13 @@ __device__ __forceinline__ void wait_vmcnt()
 {
     static_assert(N >= 0 && N <= 63, "vmcnt is a 6-bit counter");
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+
+// n / d for any 32-bit n (Granlund & Montgomery, division by invariant integers using multiplication)
+__device__ __forceinline__ uint32_t divide(uint32_t n, const FastDiv& f)
+{
+    const uint32_t t = __umulhi(f.mul, n);
+    return (t + ((n - t) >> f.shift1)) >> f.shift2;
 }
 
 // A pointer every lane holds alike, moved to scalar registers (buffer descriptors live there).

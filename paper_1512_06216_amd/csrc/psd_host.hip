@@ -317,17 +317,19 @@ psd_status psd_sync_dense_ps_multi(int32_t L, const psd_dense_segment* segs, flo
         psd_status r = check_dense(s.n, s.P, PSD_MAX_MULTI_WORKERS, s.G, s.W, s.Mom, s.S);
         if (r != PSD_OK) return r;
         if (s.n == 0) continue;
+        t.begin[used] = static_cast<int32_t>(blocks);
         DenseSeg& d = t.seg[used++];
         for (int p = 0; p < PSD_MAX_MULTI_WORKERS; ++p) d.G[p] = p < s.P ? s.G[p] : nullptr;
-        d.W = s.W; d.Mom = s.Mom; d.n = s.n; d.P = s.P; d.S = s.S;
+        d.W = s.W; d.Mom = s.Mom; d.P = s.P; d.S = s.S;
         d.q = s.n / s.S; d.r = s.n % s.S;
-        d.chunks = dense_chunks_for(s.n, s.S, t.threads);
-        d.block_begin = static_cast<int32_t>(blocks);
-        blocks += static_cast<int64_t>(d.chunks) * s.S;
+        const int32_t chunks = dense_chunks_for(s.n, s.S, t.threads);
+        d.by_S = fast_div(static_cast<uint32_t>(s.S));
+        d.by_chunks = fast_div(static_cast<uint32_t>(chunks));
+        blocks += static_cast<int64_t>(chunks) * s.S;
         if (blocks > (int64_t(1) << 30)) return PSD_E_INVALID;
     }
     if (used == 0) return PSD_OK;
-    t.L = used;
+    for (; used < PSD_MAX_MULTI_SEGMENTS; ++used) t.begin[used] = 0x7fffffff;
     return launch_dense_table(t, static_cast<int32_t>(blocks), lr, mu, wd, static_cast<hipStream_t>(stream));
 }
 

@@ -28,16 +28,14 @@ struct DenseSeg {
     const float* G[PSD_MAX_MULTI_WORKERS];
     float* W;
     float* Mom;
-    int64_t n;
-    int64_t q, r;          // n = q * S + r, 0 <= r < S
+    int64_t q, r;          // keys = q * S + r, 0 <= r < S
     int32_t P;
     int32_t S;
-    int32_t block_begin;   // first workgroup of this segment
-    int32_t chunks;        // workgroups per shard
+    FastDiv by_S, by_chunks;       // (chunks: workgroups per shard)
 };
 struct DenseTable {
+    int32_t begin[PSD_MAX_MULTI_SEGMENTS];       // first workgroup of each segment; past the last one: none
     DenseSeg seg[PSD_MAX_MULTI_SEGMENTS];
-    int32_t L;
     int32_t threads;       // lanes per workgroup (dense_threads_for)
 };
 struct DenseWide {          // single layer, up to PSD_MAX_WORKERS copies
@@ -48,12 +46,11 @@ struct DenseWide {          // single layer, up to PSD_MAX_WORKERS copies
     int64_t q, r;          // n = q * S + r, 0 <= r < S
     int32_t P;
     int32_t S;
-    int32_t chunks;        // filled in by launch_dense_wide
+    FastDiv by_S, by_chunks;       // filled in by launch_dense_wide
 };
 psd_status launch_dense_table(const DenseTable& t, int32_t total_blocks, float lr, float mu, float wd, hipStream_t st);
 psd_status launch_dense_wide(DenseWide& a, float lr, float mu, float wd, hipStream_t st);
 
-struct FastDiv { uint32_t d, mul, shift1, shift2; };   // division by d, see psd_pack.hip
 struct PackSide {            // one of the two stacked matrices of a layer
     const float* src[PSD_MAX_WORKERS];
     void* dst;

@@ -10,6 +10,7 @@
 // Source rows start at b*cols floats, which is only 4-byte aligned when cols is odd (e.g. 21841 classes); loads therefore use
 // a 4-byte-aligned vector type and leave the choice of instruction to the compiler.  U (errors) and V (activations) of a
 // layer are stacked by ONE launch: the first workgroups serve U, the rest V.
+#include "psd_device.h"
 #include "psd_internal.h"
 
 namespace psd {
@@ -25,13 +26,6 @@ __device__ __forceinline__ uint32_t bf16_rne(float f)
     const uint32_t u = __float_as_uint(f);
     if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
     return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-}
-
-// n / d for any 32-bit n (Granlund & Montgomery, division by invariant integers using multiplication)
-__device__ __forceinline__ uint32_t divide(uint32_t n, const FastDiv& f)
-{
-    const uint32_t t = __umulhi(f.mul, n);
-    return (t + ((n - t) >> f.shift1)) >> f.shift2;
 }
 
 template <bool BF16>
@@ -79,18 +73,6 @@ __global__ void __launch_bounds__(kThreads) pack_kernel(const PackArgs a)
     } else {
         *reinterpret_cast<float4*>(static_cast<float*>(s.dst) + at) = make_float4(v[0], v[1], v[2], v[3]);
     }
-}
-
-FastDiv fast_div(uint32_t d)
-{
-    int l = 0;                                         // ceil(log2(d))
-    while ((uint64_t(1) << l) < d) ++l;
-    FastDiv f;
-    f.d = d;
-    f.mul = static_cast<uint32_t>((uint64_t(1) << 32) * ((uint64_t(1) << l) - d) / d + 1);
-    f.shift1 = l < 1 ? l : 1;
-    f.shift2 = l < 1 ? 0 : l - 1;
-    return f;
 }
 
 }  // namespace

@@ -256,6 +256,21 @@ inline Bf16Tile choose_bf16_split(int64_t N, int64_t M, int64_t K, int most, int
     return best;
 }
 
+// ---- division by a number that a launch knows: multiplier and shifts of `divide` (psd_device.h)
+struct FastDiv { uint32_t d, mul, shift1, shift2; };
+
+inline FastDiv fast_div(uint32_t d)
+{
+    int l = 0;                                         // ceil(log2(d))
+    while ((uint64_t(1) << l) < d) ++l;
+    FastDiv f;
+    f.d = d;
+    f.mul = static_cast<uint32_t>((uint64_t(1) << 32) * ((uint64_t(1) << l) - d) / d + 1);
+    f.shift1 = l < 1 ? l : 1;
+    f.shift2 = l < 1 ? 0 : l - 1;
+    return f;
+}
+
 // ---- pack
 // Rows of one launch over rows of `cu` and `cv` 16-byte chunks: one lane per chunk of both matrices, and chunk numbers that fit
 // 31 bits with room to spare for the last, partly filled workgroups.  A longer stack takes several launches.

@@ -187,6 +187,25 @@ def test_dense_multi_equals_single_calls():
         assert np.array_equal(W.cpu().numpy(), Wr) and np.array_equal(Mom.cpu().numpy(), Mr)
 
 
+@pytest.mark.parametrize("L", [1, 2, 7, 8, 9, 15, 16])
+def test_dense_multi_finds_each_workgroups_segment_and_shard_bit_exact(L):
+    """Segments of one workgroup and of many, shards of uneven length, for every number of halvings."""
+    rng = np.random.default_rng(L)
+    segs, want = [], []
+    for l in range(L):
+        P, S = int(rng.integers(1, 17)), int(rng.integers(1, 40))
+        n = int(rng.integers(S, 400)) if l % 3 else int(rng.integers(4000, 60000))
+        d = inputs.dense_layer_integer(n, P, seed=100 * L + l)
+        Wr, Mr = orc.sync_dense_ps(d["G"], d["W"], d["Mom"], 0.25, 0.5, S)
+        W, Mom = dev(d["W"]), dev(d["Mom"])
+        segs.append(([dev(g) for g in d["G"]], W, Mom, S))
+        want.append((Wr, Mr))
+    psd.sync_dense_ps_multi(segs, 0.25, 0.5)
+    torch.cuda.synchronize()
+    for (_, W, Mom, _), (Wr, Mr) in zip(segs, want):
+        assert np.array_equal(W.cpu().numpy(), Wr) and np.array_equal(Mom.cpu().numpy(), Mr)
+
+
 # ---------------------------------------------------------------------------------------
 # SFB reconstruct + update
 # ---------------------------------------------------------------------------------------

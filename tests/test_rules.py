@@ -18,7 +18,7 @@ def rules(tmp_path_factory):
     L = ctypes.CDLL(so)
     i32, i64, c_int = ctypes.c_int32, ctypes.c_int64, ctypes.c_int
     for name, res, args in (("max_items", i64, []), ("dense_threads", i32, [i64, i64]), ("dense_chunks", i32, [i64, i32, i32]),
-                            ("pack_rows", i64, [i64, i64]), ("f32_reach", i32, [i64, i64, i64]),
+                            ("pack_rows", i64, [i64, i64]), ("divided", ctypes.c_uint32, [ctypes.c_uint32, ctypes.c_uint32]), ("f32_reach", i32, [i64, i64, i64]),
                             ("bf16_reach", i32, [i64, i64, i64, i64]), ("bf16_choice", i32, [i64, i64, i64, c_int, i64]),
                             ("splits_asked", i32, [i64, i64, i64]), ("f32_choice", i32, [i64, i64, i64, i64]),
                             ("f32_planes", i32, [i64, i64, i64, i64]), ("f32_splits", i32, [i64, i64, i64, c_int, i64])):
@@ -45,6 +45,14 @@ def test_dense_launches_of_short_shards_that_fit_one_launch_with_256_lanes_still
     n, S = 20000000, 5000000
     t = rules.dense_threads(n, S)
     assert S * rules.dense_chunks(n, S, t) * t <= rules.max_items() < 2 ** 32
+
+
+def test_division_by_multiplication_is_exact(rules):
+    ds = [d for e in range(32) for d in (2 ** e - 1, 2 ** e, 2 ** e + 1) if 1 <= d < 2 ** 32] + [2 ** 32 - 1, 3, 5, 7, 61, 1000, 65535]
+    for d in ds:
+        ns = {0, 1, d - 1, d, 2 ** 32 - 1, 2 ** 32 // d * d - 1, 2 ** 32 // d * d % 2 ** 32, 2 ** 31, 65534 * 65535}
+        for n in ns:
+            assert rules.divided(n % 2 ** 32, d) == n % 2 ** 32 // d, (n, d)
 
 
 def test_pack_launches_hold_both_matrices(rules):
