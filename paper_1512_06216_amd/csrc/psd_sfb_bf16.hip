@@ -297,26 +297,37 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
     // (= m offset) and column lane%32 (= n offset): four adjacent m per register quad.
     const int l32 = lane & 31, lhi = lane >> 5;
     if constexpr (PART) {
+        // Each 32 x 32 block is turned through a private LDS patch, as below: 128 contiguous bytes of a row per access instead of
+        // 32, or, where rows are no multiples of 16 bytes, instead of single elements: 4160 -> 196, K = 4096 25.9 -> 25.2 us,
+        // 4155 -> 196 32.0 -> 28.0, 511 -> 512 15.5 -> 13.8.
+        float* patch = reinterpret_cast<float*>(lds) + wave * (32 * PLD);
+        const bool quads = M % 4 == 0;
+        const int prow = quads ? lane >> 3 : lane >> 5, pcol = quads ? 4 * (lane & 7) : lane & 31;
 #pragma unroll
-        for (int bn = 0; bn < C::BN; ++bn) {
-            const int64_t n = n0 + wn0 + 32 * bn + l32;
-            if (n >= N) continue;
+        for (int bn = 0; bn < C::BN; ++bn)
 #pragma unroll
-            for (int bm = 0; bm < C::BM; ++bm)
+            for (int bm = 0; bm < C::BM; ++bm) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int64_t m = m0 + wm0 + 32 * bm + 8 * q + 4 * lhi;
-                    float* to = part + split * part_stride + n * int64_t(M) + m;
-                    if (M % 4 == 0) {
-                        if (m < M) *reinterpret_cast<float4*>(to) = make_float4(acc[bn][bm][4 * q], acc[bn][bm][4 * q + 1],
-                                                                                acc[bn][bm][4 * q + 2], acc[bn][bm][4 * q + 3]);
-                    } else {
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<float4*>(patch + l32 * PLD + 8 * q + 4 * lhi) =
+                        make_float4(acc[bn][bm][4 * q], acc[bn][bm][4 * q + 1], acc[bn][bm][4 * q + 2], acc[bn][bm][4 * q + 3]);
+                const int64_t m = m0 + wm0 + 32 * bm + pcol;
+                float* const to = part + split * part_stride + m;
+                if (quads) {
 #pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (m + i < M) to[i] = acc[bn][bm][4 * q + i];
+                    for (int jj = 0; jj < 4; ++jj) {
+                        const int64_t n = n0 + wn0 + 32 * bn + prow + 8 * jj;
+                        if (n < N && m < M)
+                            *reinterpret_cast<float4*>(to + n * int64_t(M)) = *reinterpret_cast<const float4*>(patch + (prow + 8 * jj) * PLD + pcol);
+                    }
+                } else {
+#pragma unroll
+                    for (int jj = 0; jj < 16; ++jj) {
+                        const int64_t n = n0 + wn0 + 32 * bn + prow + 2 * jj;
+                        if (n < N && m < M) to[n * int64_t(M)] = patch[(prow + 2 * jj) * PLD + pcol];
                     }
                 }
-        }
+            }
     } else if constexpr (STREAM) {
         // Rows of W start on cache-line boundaries (M a multiple of 32).
         // Held as they are, the quads of one W row sit in 2 lanes x 4 registers, and a
