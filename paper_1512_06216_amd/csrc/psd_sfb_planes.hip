@@ -55,9 +55,11 @@ struct Cfg {
     static constexpr int TN = 32 * WN, TM = 128;
     static_assert(WN == 2 || WN == 4, "half of the wavefronts load the first 8 rows of a slice, half the others");
     static constexpr int PV = 2 * TM / 64 / WN;                                   // 8 x 64 patches of V per wavefront and slice
-    // LDS, one slice: planes of V: [k / 8][m % 4][m / 4], 16 bytes (8 k) each.  The 64 bytes between the quarters spread the writes
-    // of 16 lanes (four adjacent m in four of them) over all banks.
-    static constexpr int B_QUARTER = 32 * 16 + 64, B_HALF = 4 * B_QUARTER, B_PLANE = 2 * B_HALF, SLICE_BYTES = 3 * B_PLANE;
+    // LDS, one slice: planes of V: [k / 8][m % 4][m / 4], 16 bytes (8 k) each.  The 32 bytes between the quarters spread the writes
+    // of 8 lanes (four adjacent m in two of them), which is what LDS takes in a clock, over 128 bytes.  With 64 (16 lanes over 256
+    // bytes) a write takes four clocks more: 28 M cycles of conflicts in a launch over 9216 -> 4096, K = 2048, now none; 758 and
+    // 755 us on the same card, 3000 -> 3000 234 and 230.  With none the two are 2 and 8 % slower than with 64.
+    static constexpr int B_QUARTER = 32 * 16 + 32, B_HALF = 4 * B_QUARTER, B_PLANE = 2 * B_HALF, SLICE_BYTES = 3 * B_PLANE;
     static constexpr int BUFFER_BYTES = G * SLICE_BYTES, ROWS_BYTES = 64 * row_stride(TM, 0) * 4;
     static constexpr int HANDED_BYTES = G * (G - 1) * (64 / G) * WN * 256;        // accumulators that groups hand over
     static constexpr int larger(int x, int y) { return x > y ? x : y; }
