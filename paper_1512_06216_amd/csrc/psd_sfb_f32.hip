@@ -65,13 +65,13 @@ struct Args {
     int N, M, K;
     float lr, mu, wd;
     int tiles_m;                    // tiles per row of tiles of the main grid
-    bool runs;                      // place_of
     int big, tiles;                 // tiles (PART: of one split), the first `big` of 128 x 128, the others smaller ones
     uint32_t u_bytes, v_bytes;      // of the stacked matrices, or of ONE block
     float* part;                    // PART: partial dW matrices, part_stride apart
     int64_t part_stride;
     int stages_per_split;
     int n_blocks, block_rows;       // BLK
+    int runs;                       // place_of
 };
 
 // PART = true (layers with too few tiles to fill the chip): `splits` workgroups per tile, workgroup
@@ -312,16 +312,15 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
 // 1399 -> 1365, K = 128 15.8 -> 12.0 us, 2149 -> 768 14.5 -> 11.4, 1001 -> 999, K = 256 12.4 -> 10.4, 4095 -> 1000, K = 64
 // 23.5 -> 19.0, 9215 -> 4096, K = 128 150 -> 150.  On lines the tiles of an XCD are every eighth of a row, which re-use the same
 // columns of V: 9216 -> 4096, K = 128 130 us, in runs 137; 4096 -> 1000, K = 64 16.9 and 17.5.
-__device__ __forceinline__ int place_of(const Args& g, int b, int T)
+__device__ __forceinline__ int place_of(bool runs, int b, int T)
 {
-    if (!g.runs) return b;
-    const int xcd = b & 7;
-    return xcd * (T >> 3) + (xcd < (T & 7) ? xcd : (T & 7)) + (b >> 3);
+    const int xcd = b & 7, run = xcd * (T >> 3) + (xcd < (T & 7) ? xcd : (T & 7)) + (b >> 3);
+    return runs ? run : b;
 }
 
 // Workgroup b owns tile b of (64*BN) x (64*BM).  MIXED: workgroups [0, big) own 128 x 128 tiles and the tiles after them are cut
 // into (2 / BN) * (2 / BM) smaller ones.
-template <int BN, int BM, bool MIXED, bool PART, bool BLK>
+template <int BN, int BM, bool MIXED, bool PART, bool BLK, bool RUNS>
 __device__ __forceinline__ void grid_body(const Args& g, const BlockPtrs* blocks)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -330,38 +329,39 @@ __device__ __forceinline__ void grid_body(const Args& g, const BlockPtrs* blocks
         const int split = __builtin_amdgcn_readfirstlane(b / g.tiles), tile = b - split * g.tiles;   // (the division runs on the vector ALU)
         tile_body<BN, BM, 1, true, false>(g, nullptr, lds, int64_t(tile / g.tiles_m) * 64 * BN, int64_t(tile % g.tiles_m) * 64 * BM, split);
     } else if constexpr (!MIXED) {
-        const int lin = place_of(g, b, g.tiles);
+        const int lin = place_of(RUNS, b, g.tiles);
         tile_body<BN, BM, 1, false, BLK>(g, blocks, lds, int64_t(lin / g.tiles_m) * 64 * BN, int64_t(lin % g.tiles_m) * 64 * BM, 0);
     } else if (b < g.big) {
-        const int lin = place_of(g, b, g.big);
+        const int lin = place_of(RUNS, b, g.big);
         tile_body<2, 2, 1, false, BLK>(g, blocks, lds, int64_t(lin / g.tiles_m) * 128, int64_t(lin % g.tiles_m) * 128, 0);
     } else {
         constexpr int PN = 2 / BN, PM = 2 / BM;
-        const int i = place_of(g, b - g.big, g.tiles - g.big), tile = g.big + i / (PN * PM), sub = i % (PN * PM);
+        const int i = place_of(RUNS, b - g.big, g.tiles - g.big), tile = g.big + i / (PN * PM), sub = i % (PN * PM);
         tile_body<BN, BM, 1, false, BLK>(g, blocks, lds, int64_t(tile / g.tiles_m) * 128 + (sub / PM) * 64 * BN,
                                       int64_t(tile % g.tiles_m) * 128 + (sub % PM) * 64 * BM, 0);
     }
 }
 
 // Tiles of one size have a kernel of their own: three of 64 x 128 and five of 64 x 64 fit a compute unit then (with the 128 x 128
-// code beside them two, for its registers; 6000 -> 6000, K = 384: 265 against 272 us).
-template <int BN, int BM, bool MIXED, bool PART>
+// code beside them two, for its registers; 6000 -> 6000, K = 384: 265 against 272 us).  RUNS: as place_of has it (asked at run
+// time it costs rows on lines up to 1 %: 6656 -> 2259, K = 216 75.9 and 76.5 us).
+template <int BN, int BM, bool MIXED, bool PART, bool RUNS>
 __global__ void __launch_bounds__(256, MIXED || BN == 2 ? 2 : BM == 2 ? 3 : 5) sfb_f32_kernel(const Args g)
 {
-    grid_body<BN, BM, MIXED, PART, false>(g, nullptr);
+    grid_body<BN, BM, MIXED, PART, false, RUNS>(g, nullptr);
 }
 
-template <int BN, int BM, bool MIXED>
+template <int BN, int BM, bool MIXED, bool RUNS>
 __global__ void __launch_bounds__(256, MIXED ? 2 : BM == 2 ? 3 : 5) sfb_f32_blocks_kernel(const Args g, const BlockPtrs blocks)
 {
-    grid_body<BN, BM, MIXED, false, true>(g, &blocks);
+    grid_body<BN, BM, MIXED, false, true, RUNS>(g, &blocks);
 }
 
 template <int BN, int BM>
 __global__ void __launch_bounds__(256 * LONE_GROUPS) sfb_f32_groups_kernel(const Args g)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    const int lin = place_of(g, blockIdx.x, g.tiles);
+    const int lin = place_of(g.runs, blockIdx.x, g.tiles);
     tile_body<BN, BM, LONE_GROUPS, false, false, CHAINS / LONE_GROUPS>(g, nullptr, lds, int64_t(lin / g.tiles_m) * 64 * BN, int64_t(lin % g.tiles_m) * 64 * BM, 0);
 }
 
@@ -369,7 +369,7 @@ template <int BN, int BM>
 __global__ void __launch_bounds__(256 * LONE_GROUPS) sfb_f32_groups_blocks_kernel(const Args g, const BlockPtrs blocks)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    const int lin = place_of(g, blockIdx.x, g.tiles);
+    const int lin = place_of(g.runs, blockIdx.x, g.tiles);
     tile_body<BN, BM, LONE_GROUPS, false, true, CHAINS / LONE_GROUPS>(g, &blocks, lds, int64_t(lin / g.tiles_m) * 64 * BN, int64_t(lin % g.tiles_m) * 64 * BM, 0);
 }
 
@@ -380,15 +380,17 @@ int pinned_tile()
     return t == 1 || t == 2 ? t : 0;
 }
 
-template <int BN, int BM, bool MIXED, bool PART>
+template <int BN, int BM, bool MIXED, bool PART, bool RUNS = false>
 psd_status start(const Args& g, const BlockPtrs* blocks, int64_t groups, hipStream_t st)
 {
+    if constexpr (!PART && !RUNS)
+        if (g.runs) return start<BN, BM, MIXED, PART, true>(g, blocks, groups, st);
     if (groups < 1 || groups > 0x7fffffff) return PSD_E_INVALID;
     const size_t lds = MIXED ? Tile<2, 2, 1>::LDS_BYTES : Tile<BN, BM, 1>::LDS_BYTES;
     const dim3 grid(static_cast<uint32_t>(groups));
-    if constexpr (PART) hipLaunchKernelGGL((sfb_f32_kernel<BN, BM, MIXED, true>), grid, dim3(256), lds, st, g);
-    else if (blocks) hipLaunchKernelGGL((sfb_f32_blocks_kernel<BN, BM, MIXED>), grid, dim3(256), lds, st, g, *blocks);
-    else hipLaunchKernelGGL((sfb_f32_kernel<BN, BM, MIXED, false>), grid, dim3(256), lds, st, g);
+    if constexpr (PART) hipLaunchKernelGGL((sfb_f32_kernel<BN, BM, MIXED, true, false>), grid, dim3(256), lds, st, g);
+    else if (blocks) hipLaunchKernelGGL((sfb_f32_blocks_kernel<BN, BM, MIXED, RUNS>), grid, dim3(256), lds, st, g, *blocks);
+    else hipLaunchKernelGGL((sfb_f32_kernel<BN, BM, MIXED, false, RUNS>), grid, dim3(256), lds, st, g);
     PSD_HIP_TRY(hipGetLastError());
     return PSD_OK;
 }
