@@ -152,11 +152,11 @@ inline double planes_cost(const PlaneTile& t, int64_t N, int64_t M, int64_t K, i
 }
 
 // Which of them takes this layer, -1: none, the fp32 pipe does.  `us`: its cost there, split or not.  Short contractions stay: at
-// K = 128 the fp32 pipe is the faster one for every size of layer (2624 -> 5037 51 against 57 us for the best of the tiles), at
-// K = 192 for some (4720 -> 868 26.7 and 29.6, 1669 -> 780 15.0 and 12.3), at K = 256 for hardly any (672 -> 3462 19.1 and 20.1,
-// 4096 -> 1024 25.2 and 23.9, 4096 -> 4096 90 and 86, 9216 -> 4096 195 and 158), and at K = 320 for none (4096 -> 4096 107 and 91).
-// A tenth has to be gained by these costs: of 132 layers none then gets slower, and the choice is 0.8 % off the best one over the
-// 114; with 6 % it is 0.7 % off, and 672 -> 3462 among the slower ones.
+// K = 128 the fp32 pipe is the faster one for every size of layer (2624 -> 5037 52 against 58 us for the best of the tiles), at
+// K = 192 for some (4720 -> 868 26.1 and 29.6, 1669 -> 780 12.5 and 12.2, 8404 -> 321 21.1 and 17.5), at K = 256 for hardly any
+// (672 -> 3462 19.8 and 20.4, 4096 -> 1024 26.1 and 24.5, 4096 -> 4096 90 and 84, 9216 -> 4096 192 and 159), and at K = 320 for
+// none (4096 -> 4096 106 and 89).  A tenth has to be gained by these costs: of 132 layers none then gets slower, and the choice is
+// 0.8 % off the best one over the 114; with 6 % it is 0.7 % off, and 672 -> 3462 among the slower ones.
 constexpr int64_t kMinPlaneRows = 256;
 inline int choose_planes(int64_t N, int64_t M, int64_t K, int64_t cus, double us)
 {

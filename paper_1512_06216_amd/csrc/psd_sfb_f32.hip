@@ -4,7 +4,7 @@
 //
 // Small layers and short contractions, on the fp32 MFMA pipe (v_mfma_f32_32x32x2_f32: one k per lane, which is exactly how the
 // K-outer stacked factors sit in memory -- no transpose is needed for fp32).  The others go to psd_sfb_planes.hip
-// (choose_planes): 4096 -> 1000, K = 2048 124 -> 89 us, 9216 -> 4096 1066 -> 700 us.
+// (choose_planes): 4096 -> 1000, K = 2048 124 -> 88 us, 9216 -> 4096 1066 -> 700 us.
 //
 // Tiling: a 256-lane workgroup (4 wavefronts, 2 x 2) owns a 128 x 128, 64 x 128 or 64 x 64 tile of W; each wavefront a
 // quarter of it in 32 x 32 MFMA blocks.  MFMA row i of block t stands for n = n0 + BN*i + t (columns m likewise), so one
