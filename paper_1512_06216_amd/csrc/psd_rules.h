@@ -206,7 +206,11 @@ inline double launch_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K, in
     if (tiles <= cus) return t.first + (M % 32 ? 1.5 : 0) + 0.6 * update * share + t.solo * k;
     // the last, partly filled round: the loop takes as long as a full one, the update shares HBM among fewer
     const double rounds = static_cast<double>((tiles + cus - 1) / cus), tail = (rounds - share) * (t.area > 2 ? 0.5 : 0.2);
-    return 5 + update * (share + tail) + t.loop * k * rounds;
+    // 64 columns off cache lines are pieces of three lines, two of which the neighbours have too: with more tiles than fit the
+    // compute units at once 64 x 128 ones are faster (1428 -> 4174, K = 128 25.9 and 22.3 us, 4526 -> 1135, K = 100 24.5 and 20.8,
+    // 2807 -> 1518, K = 384 24.6 and 21.4), but for layers of few rows (9476 -> 442, K = 96 16.8 and 17.7)
+    const double torn = t.id == 4 && share > 4 && M % 32 && M < 8 * N ? 0.7 * share : 0;
+    return 5 + update * (share + tail) + torn + t.loop * k * rounds;
 }
 
 // ... and when `splits` workgroups per tile store partial sums that a second launch adds up

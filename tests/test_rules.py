@@ -134,6 +134,12 @@ def test_pairs_of_grouped_tiles_are_for_layers_that_have_two_for_each_compute_un
         assert rules.bf16_choice(N, M, K, 1, CUS) // 10 != 7
 
 
+def test_rows_off_lines_get_wider_tiles_where_they_do_not_all_fit_the_compute_units(rules):
+    for M, N, K, tile in ((1428, 4174, 128, 3), (1440, 4174, 128, 4), (4526, 1135, 100, 3), (1027, 4508, 207, 3), (9476, 442, 96, 4),
+                          (124, 17184, 244, 4), (3464, 610, 752, 4)):
+        assert rules.bf16_choice(N, M, K, 1, CUS) == 10 * tile + 1, (M, N, rules.bf16_choice(N, M, K, 1, CUS))
+
+
 def test_layers_of_the_parity_tests_go_to_the_pipe_they_stand_for(rules):
     seen = set()
     for tile, M, N, B, P in parity.PLANE_LAYERS:
