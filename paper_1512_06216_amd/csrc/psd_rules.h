@@ -206,10 +206,13 @@ inline double launch_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K, in
     if (tiles <= cus) return t.first + (M % 32 ? 1.5 : 0) + 0.6 * update * share + t.solo * k;
     // the last, partly filled round: the loop takes as long as a full one, the update shares HBM among fewer
     const double rounds = static_cast<double>((tiles + cus - 1) / cus), tail = (rounds - share) * (t.area > 2 ? 0.5 : 0.2);
-    // 64 columns off cache lines are pieces of three lines, two of which the neighbours have too: with more tiles than fit the
-    // compute units at once 64 x 128 ones are faster (1428 -> 4174, K = 128 25.9 and 22.3 us, 4526 -> 1135, K = 100 24.5 and 20.8,
-    // 2807 -> 1518, K = 384 24.6 and 21.4), but for layers of few rows (9476 -> 442, K = 96 16.8 and 17.7)
-    const double torn = t.id == 4 && share > 4 && M % 32 && M < 8 * N ? 0.7 * share : 0;
+    // Off cache lines, with more tiles than fit the compute units at once.  64 columns are pieces of three lines, two of which the
+    // neighbours have too: 64 x 128 tiles are faster (1428 -> 4174, K = 128 25.9 and 22.3 us, 4526 -> 1135, K = 100 24.5 and
+    // 20.8, 2807 -> 1518, K = 384 24.6 and 21.4), but for layers of few rows (9476 -> 442, K = 96 16.8 and 17.7).  The 128 x 128
+    // tile takes 175 registers there, 113 on lines, and half as many fit: 891 -> 12360, K = 280 56.3 and, 128 x 192, 44.8,
+    // 988 -> 19501, K = 263 84.2 and, 64 x 128, 74.3, 2643 -> 7618, K = 951 116 and, 128 x 192, 105.
+    const bool off_lines = M % 32 != 0;
+    const double torn = off_lines && t.id == 4 && share > 4 && M < 8 * N ? 0.7 * share : off_lines && t.id == 2 && share > 2 ? 2 * share : 0;
     return 5 + update * (share + tail) + torn + t.loop * k * rounds;
 }
 

@@ -134,9 +134,10 @@ def test_pairs_of_grouped_tiles_are_for_layers_that_have_two_for_each_compute_un
         assert rules.bf16_choice(N, M, K, 1, CUS) // 10 != 7
 
 
-def test_rows_off_lines_get_wider_tiles_where_they_do_not_all_fit_the_compute_units(rules):
+def test_rows_off_lines_get_other_tiles_where_they_do_not_all_fit_the_compute_units(rules):
     for M, N, K, tile in ((1428, 4174, 128, 3), (1440, 4174, 128, 4), (4526, 1135, 100, 3), (1027, 4508, 207, 3), (9476, 442, 96, 4),
-                          (124, 17184, 244, 4), (3464, 610, 752, 4)):
+                          (124, 17184, 244, 4), (3464, 610, 752, 4), (891, 12360, 280, 1), (896, 12360, 280, 2),
+                          (988, 19501, 263, 3), (5617, 3497, 327, 3)):
         assert rules.bf16_choice(N, M, K, 1, CUS) == 10 * tile + 1, (M, N, rules.bf16_choice(N, M, K, 1, CUS))
 
 
