@@ -10,9 +10,9 @@
 // Precision.  The five small products have accumulators of their own (`low`), so that the large ones take one rounding where the
 // fp32 pipe takes four, and the low ones round numbers 2^-8 as large.  Error of dW against 64 bits (2-norm; normal errors,
 // activations after a ReLU): K = 2048 2.1e-7 (fp32 pipe 5.7e-7), K = 256 7e-8 (with one set of accumulators 6.6e-7 and
-// 2.3e-7).  Tiles whose sums overflow or are not numbers, and tiles with a sum below 2^-104 other than zero (where l of a factor
-// may be below what bf16 can hold), are contracted anew on the fp32 pipe (`again`), so that infinities, NaN and the smallest
-// numbers give what they give there.
+// 2.3e-7).  Factors are cut 2^24 times as large (psd_planes.h), so that small numbers keep all their bits too.  Rows of tiles
+// with a sum that is not finite (infinities, NaN, factors above 2^104, sums above 2^80) are contracted anew on the fp32 pipe, so
+// that they give what they give there.
 //
 // Tile and feeding.  A wavefront owns 32 x 128 of W: one MFMA block of n and four of m, the m of block j being m0 + 4*i + j, so that
 // a lane holds four adjacent m of a row in four accumulators and the update moves 512 contiguous bytes per half wavefront
@@ -35,6 +35,7 @@
 #include <type_traits>
 #include "psd_device.h"
 #include "psd_internal.h"
+#include "psd_planes.h"
 
 namespace psd {
 namespace {
@@ -84,15 +85,6 @@ __device__ __forceinline__ uint32_t to_bf16(float a, float b)          // neares
 {
     const f32x2 x = {a, b};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
-}
-
-// (x0, x1) = h + m + l; the differences are exact
-__device__ __forceinline__ void cut(float x0, float x1, uint32_t& h, uint32_t& m, uint32_t& l)
-{
-    h = to_bf16(x0, x1);
-    const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
-    m = to_bf16(r0, r1);
-    l = to_bf16(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
 }
 
 __device__ __forceinline__ float load_or_zero(const Feed& f, uint32_t off)     // 0 past the end of what is fed
@@ -199,7 +191,7 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
 #pragma unroll
         for (int q = 2 * (i & 1); q < 2 * (i & 1) + 2; ++q) {
             uint32_t hh, mm, ll;
-            cut(patch[p][2 * q], patch[p][2 * q + 1], hh, mm, ll);
+            cut(patch[p][2 * q], patch[p][2 * q + 1], hh, mm, ll, to_bf16);
             if (p < PV) {
                 h[q] = hh; m[q] = mm; l[q] = ll;
             } else {
@@ -319,19 +311,17 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
             for (int j = 0; j < 4; ++j) d[q][j] = acc[j][q];
     }
 
-    // Sums that the planes may not give as the fp32 pipe does (see above): this wavefront's rows anew.
+    // Sums that are not finite as the planes give them (see above): this wavefront's rows anew.
     {
         float nan = 0.f;
-        uint32_t least = 0xffffffffu;
 #pragma unroll
         for (int q = 0; q < NR; ++q)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 nan = __fmaf_rn(d[q][j], 0.f, nan);
-                const uint32_t b = 2 * __float_as_uint(d[q][j]) - 1;
-                least = b < least ? b : least;
+                d[q][j] *= kPlaneUnscale;
             }
-        if (__any(nan != 0.f || least < 2 * 0x0b800000u - 1)) {                // 0x0b800000: 2^-104
+        if (__any(nan != 0.f)) {
             // Two blocks at a time, in four runs over k as in the fp32 kernel for small layers: half the error of one run.
             const int run = ((g.K + 3) / 4 + 1) & ~1;
 #pragma unroll

@@ -407,6 +407,20 @@ def test_sfb_f32_planes_numbers_that_bf16_cannot_hold(M, N, K, what):
     assert bool((dW[ok] == 0).sum() == (want[ok] == 0).sum()) or what == "1e-36"
 
 
+@pytest.mark.parametrize("M,N,K", [(4896, 1220, 272), (5693, 322, 293), (4713, 392, 299), (5506, 133, 303)])
+@pytest.mark.parametrize("us,vs", [(1e-37, 1e9), (1e9, 1e-37), (1e-41, 1e12), (1e12, 1e-41), (1e-44, 1.0), (1.0, 1e-44), (1e-20, 1e-18)])
+def test_sfb_f32_planes_hold_small_numbers_beside_large_ones(M, N, K, us, vs):
+    """Factors down to the smallest fp32 numbers, beside ones that make the sums ordinary numbers, or sums that are as small
+    themselves.  K roundings of half an ulp, of either sign, are sqrt(K) 2^-24 in the 2-norm; a sum below 2^-126 is rounded to
+    a multiple of 2^-149."""
+    g = torch.Generator().manual_seed(K)
+    U = (torch.randn(K, N, generator=g) * us).to(DEV)
+    V = (torch.randn(K, M, generator=g).relu_() * vs).to(DEV)
+    dW, want = _planes_dw(M, N, K, U, V)
+    err, size = (dW.double() - want).norm(), want.norm()
+    assert size > 0 and err <= K ** 0.5 * 2.0 ** -24 * size + 2.0 ** -150 * (N * M) ** 0.5, (float(err), float(size))
+
+
 # Tiles that are alone on their compute unit, summed in four chains: K around the stages of one slice (16 / 32 rows), of two and
 # four groups, of odd and even numbers of stages, and where bf16 goes from two groups to four.
 @pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
