@@ -311,14 +311,16 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
             for (int j = 0; j < 4; ++j) d[q][j] = acc[j][q];
     }
 
-    // Sums that are not finite as the planes give them (see above): this wavefront's rows anew.
+    // Sums that are not finite as the planes give them (see above): this wavefront's rows anew.  Only sums of the layer count:
+    // those past N and M are made of what lies between the rows of the factors, which nobody has to fill.
+    const int first = 32 * w + (32 / G) * group + 4 * lhi;                     // row of register q: first + 8*(q/4) + q%4
     {
         float nan = 0.f;
 #pragma unroll
         for (int q = 0; q < NR; ++q)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                nan = __fmaf_rn(d[q][j], 0.f, nan);
+                if (n0 + first + 8 * (q >> 2) + (q & 3) < N && m0 + 4 * l32 + j < M) nan = __fmaf_rn(d[q][j], 0.f, nan);
                 d[q][j] *= kPlaneUnscale;
             }
         if (__any(nan != 0.f)) {
@@ -358,7 +360,6 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
         }
     }
 
-    const int first = 32 * w + (32 / G) * group + 4 * lhi;                     // row of register q: first + 8*(q/4) + q%4
     if (M % 4 == 0) {
         const int64_t mc = m0 + 4 * l32;
         constexpr int DEPTH = NR < 8 ? NR : 8;

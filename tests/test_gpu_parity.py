@@ -421,6 +421,29 @@ def test_sfb_f32_planes_hold_small_numbers_beside_large_ones(M, N, K, us, vs):
     assert size > 0 and err <= K ** 0.5 * 2.0 ** -24 * size + 2.0 ** -150 * (N * M) ** 0.5, (float(err), float(size))
 
 
+@pytest.mark.parametrize("M,N,B,P", [c[1:] for c in PLANE_LAYERS])
+def test_sfb_f32_planes_do_not_look_at_what_lies_between_rows(M, N, B, P):
+    """Behind the N errors and M activations of a row up to its leading dimension lies what nobody has filled: the same bits come
+    out whatever it is, read in place and stacked."""
+    g = torch.Generator().manual_seed(M + N)
+    ldu, ldv = (N + 3) // 4 * 4 + 8, (M + 3) // 4 * 4 + 4
+    plan = psd.plan_layer(psd.LAYER_FC, M, N, B, P)
+    u, v = torch.randn(B * P, N, generator=g).to(DEV), torch.randn(B * P, M, generator=g).relu_().to(DEV)
+    seen = []
+    for fill in (0.0, float("inf"), 1e-30, float("nan")):
+        U, V = torch.full((B * P, ldu), fill, device=DEV), torch.full((B * P, ldv), fill, device=DEV)
+        U[:, :N], V[:, :M] = u, v
+        for blocks in (False, True):
+            W, Mom = torch.zeros(N, M, device=DEV), torch.zeros(N, M, device=DEV)
+            if blocks:
+                psd.sync_fc_sfb_blocks(plan, psd.F32, list(U.split(B)), ldu, list(V.split(B)), ldv, W, Mom, 1.0, 0.0)
+            else:
+                psd.sync_fc_sfb(plan, psd.F32, U, ldu, V, ldv, W, Mom, 1.0, 0.0)
+            torch.cuda.synchronize()
+            seen.append(Mom)
+    assert all(torch.equal(x, seen[0]) for x in seen)
+
+
 # Tiles that are alone on their compute unit, summed in four chains: K around the stages of one slice (16 / 32 rows), of two and
 # four groups, of odd and even numbers of stages, and where bf16 goes from two groups to four.
 @pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
