@@ -11,8 +11,8 @@
 // fp32 pipe takes four, and the low ones round numbers 2^-8 as large.  Error of dW against 64 bits (2-norm; normal errors,
 // activations after a ReLU): K = 2048 2.1e-7 (fp32 pipe 5.7e-7), K = 256 7e-8 (with one set of accumulators 6.6e-7 and
 // 2.3e-7).  Factors are cut 2^24 times as large (psd_planes.h), so that small numbers keep all their bits too.  Rows of tiles
-// with a sum that is not finite (infinities, NaN, factors above 2^104, sums above 2^80) are contracted anew on the fp32 pipe, so
-// that they give what they give there.
+// with a sum that is not finite (infinities, NaN, factors above 2^104, sums above 2^78) are contracted anew on the fp32 pipe
+// (`again`), so that they give what they give there.
 //
 // Tile and feeding.  A wavefront owns 32 x 128 of W: one MFMA block of n and four of m, the m of block j being m0 + 4*i + j, so that
 // a lane holds four adjacent m of a row in four accumulators and the update moves 512 contiguous bytes per half wavefront
@@ -41,6 +41,7 @@ namespace psd {
 namespace {
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -64,7 +65,7 @@ struct Cfg {
     static constexpr int BUFFER_BYTES = G * SLICE_BYTES, ROWS_BYTES = 64 * row_stride(TM, 0) * 4;
     static constexpr int HANDED_BYTES = G * (G - 1) * (64 / G) * WN * 256;        // accumulators that groups hand over
     static constexpr int larger(int x, int y) { return x > y ? x : y; }
-    static constexpr int LDS_BYTES = larger(2 * BUFFER_BYTES, larger(ROWS_BYTES, HANDED_BYTES));
+    static constexpr int LDS_BYTES = larger(2 * BUFFER_BYTES, larger(ROWS_BYTES, HANDED_BYTES + WAVES * 4));  // (and a flag each)
     static constexpr int PASSES = TN / 64;                                        // of the update, 64 rows at a time
 };
 
@@ -87,10 +88,17 @@ __device__ __forceinline__ uint32_t to_bf16(float a, float b)          // neares
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
 }
 
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const Feed& f)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(f.base), 0, static_cast<int>(f.left), 0x00020000);
+}
 __device__ __forceinline__ float load_or_zero(const Feed& f, uint32_t off)     // 0 past the end of what is fed
 {
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-        __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(f.base), 0, static_cast<int>(f.left), 0x00020000), off, 0, 0));
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc_of(f), off, 0, 0));
+}
+__device__ __forceinline__ f32x4 load4_or_zero(const Feed& f, uint32_t off)
+{
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc_of(f), off, 0, 0));
 }
 
 // 6 MFMAs, the operand reads of the quarter to come behind the first of them, vector instructions in between
@@ -269,97 +277,123 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
     if (t) step(0);
 
     // Accumulator register r of a block holds row 8*(r/4) + 4*(lane/32) + r%4 of the wavefront's 32, and m = m0 + 4*(lane%32) + j.
-    // A group keeps NR registers of each block, rows 32/G * group ..., and hands the others over.
-    constexpr int NR = 16 / G;
-    float d[NR][4];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[j][r] += low[j][r];
+    // Does one of this wavefront's sums overflow, alone or with those of three other groups, or is one not a number?  Only sums of
+    // the layer count: those past N and M are made of what lies between the rows of the factors, which nobody has to fill.
+    uint32_t largest = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const uint32_t x = 2 * __float_as_uint(acc[j][r]);                 // without the sign
+            if (n0 + 32 * w + 8 * (r >> 2) + 4 * lhi + (r & 3) < N && m0 + 4 * l32 + j < M) largest = x > largest ? x : largest;
+        }
+    bool again = __any(largest >= 2 * 0x7e800000u);                            // 2^126
+    int* const flags = reinterpret_cast<int*>(lds + C::HANDED_BYTES);
     __syncthreads();                             // the slices are no longer read
-    if constexpr (G > 1) {
-        float4* buf = reinterpret_cast<float4*>(lds) + w * 64 + lane;
-        auto at = [](int to, int from, int q) { return ((to * (G - 1) + from - (from > to)) * NR + q) * WN * 64; };
+    if (G > 1 && lane == 0) flags[wave] = again;
+    // d: the sums of all groups.  A group keeps NR registers of each block, rows 32/G * group ..., and hands the others over.
+    constexpr int NR = 16 / G;
+    float d[NR][4];
+    auto gather = [&]() {
+        if constexpr (G > 1) {
+            float4* buf = reinterpret_cast<float4*>(lds) + w * 64 + lane;
+            auto at = [](int to, int from, int q) { return ((to * (G - 1) + from - (from > to)) * NR + q) * WN * 64; };
 #pragma unroll
-        for (int to = 0; to < G; ++to) {
-            if (to == group) {
+            for (int to = 0; to < G; ++to) {
+                if (to == group) {
 #pragma unroll
-                for (int q = 0; q < NR; ++q)
+                    for (int q = 0; q < NR; ++q)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) d[q][j] = acc[j][to * NR + q];
-            } else {
+                        for (int j = 0; j < 4; ++j) d[q][j] = acc[j][to * NR + q];
+                } else {
 #pragma unroll
-                for (int q = 0; q < NR; ++q)
-                    buf[at(to, group, q)] = make_float4(acc[0][to * NR + q], acc[1][to * NR + q], acc[2][to * NR + q], acc[3][to * NR + q]);
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 1; i < G; ++i) {
-            const int from = (group + i) % G;
-#pragma unroll
-            for (int q = 0; q < NR; ++q) {
-                const float4 x = buf[at(group, from, q)];
-                d[q][0] += x.x; d[q][1] += x.y; d[q][2] += x.z; d[q][3] += x.w;
-            }
-        }
-        __syncthreads();
-    } else {
-#pragma unroll
-        for (int q = 0; q < NR; ++q)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) d[q][j] = acc[j][q];
-    }
-
-    // Sums that are not finite as the planes give them (see above): this wavefront's rows anew.  Only sums of the layer count:
-    // those past N and M are made of what lies between the rows of the factors, which nobody has to fill.
-    const int first = 32 * w + (32 / G) * group + 4 * lhi;                     // row of register q: first + 8*(q/4) + q%4
-    {
-        float nan = 0.f;
-#pragma unroll
-        for (int q = 0; q < NR; ++q)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (n0 + first + 8 * (q >> 2) + (q & 3) < N && m0 + 4 * l32 + j < M) nan = __fmaf_rn(d[q][j], 0.f, nan);
-                d[q][j] *= kPlaneUnscale;
-            }
-        if (__any(nan != 0.f)) {
-            // Two blocks at a time, in four runs over k as in the fp32 kernel for small layers: half the error of one run.
-            const int run = ((g.K + 3) / 4 + 1) & ~1;
-#pragma unroll
-            for (int j0 = 0; j0 < 4; j0 += 2) {
-                f32x16 total[2], sum[2];
-                for (int k0 = 0; k0 < g.K; k0 += run) {
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            total[j][r] = k0 == 0 ? 0.f : total[j][r] + sum[j][r];
-                            sum[j][r] = 0.f;
-                        }
-                    for (int k = k0; k < k0 + run && k < g.K; k += 2) {        // lanes 0..31 feed k, the others k + 1
-                        const int kb = BLK ? k / g.block_rows : 0, row = k - kb * g.block_rows * BLK;
-                        Feed fu, fv;
-                        fu.aim(BLK ? uniform_ptr(blocks->u[kb]) : g.U, uint64_t(row) * row_a, g.u_bytes);
-                        fv.aim(BLK ? uniform_ptr(blocks->v[kb]) : g.V, uint64_t(row) * row_b, g.v_bytes);
-                        const float a = load_or_zero(fu, lhi * row_a + static_cast<uint32_t>(n0 + 32 * w + l32) * 4);
-#pragma unroll
-                        for (int j = 0; j < 2; ++j)
-                            sum[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-                                a, load_or_zero(fv, lhi * row_b + static_cast<uint32_t>(m0 + 4 * l32 + j0 + j) * 4), sum[j], 0, 0, 0);
-                    }
+                    for (int q = 0; q < NR; ++q)
+                        buf[at(to, group, q)] = make_float4(acc[0][to * NR + q], acc[1][to * NR + q], acc[2][to * NR + q], acc[3][to * NR + q]);
                 }
-#pragma unroll
-                for (int to = 0; to < G; ++to)
-                    if (to == group)
-#pragma unroll
-                        for (int q = 0; q < NR; ++q)
-#pragma unroll
-                            for (int j = 0; j < 2; ++j) d[q][j0 + j] = total[j][to * NR + q] + sum[j][to * NR + q];
             }
+            __syncthreads();
+            again = __any(flags[lane % C::WAVES]);
+#pragma unroll
+            for (int i = 1; i < G; ++i) {
+                const int from = (group + i) % G;
+#pragma unroll
+                for (int q = 0; q < NR; ++q) {
+                    const float4 x = buf[at(group, from, q)];
+                    d[q][0] += x.x; d[q][1] += x.y; d[q][2] += x.z; d[q][3] += x.w;
+                }
+            }
+            __syncthreads();
+        } else {
+#pragma unroll
+            for (int q = 0; q < NR; ++q)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) d[q][j] = acc[j][q];
         }
+    };
+    gather();
+    if (!again) {
+#pragma unroll
+        for (int q = 0; q < NR; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) d[q][j] *= kPlaneUnscale;
+    } else {
+        // Anew on the fp32 MFMA (with groups: all wavefronts, as they hand sums over), in four runs over k as in the fp32 kernel
+        // for small layers: half the error of one run.  The operands come from memory as they are, 8 rows ahead of 16 MFMAs: they
+        // are wanted by lanes as they lie there, and 20 bytes per clock of a compute unit feed its fp32 MFMA.  A launch that does
+        // this in every tile takes its own loop and that of the fp32 pipe: 9216 -> 4096, K = 2048 1845 us (finite numbers 760; with
+        // every operand waited for 5025; a 128 x 128 tile of the fp32 kernel 1060), 4096 -> 1000 216 (92; 811; 133), 5506 -> 133
+        // 108 (44; 882, each of the four groups over all of K; 123).
+        struct Rows { float a[4]; f32x4 b[4]; };
+        const uint32_t col_u = lhi * row_a + static_cast<uint32_t>(n0 + 32 * w + l32) * 4, col_v = lhi * row_b + static_cast<uint32_t>(m0 + 4 * l32) * 4;
+        auto fetch = [&](int k, Rows& x) {       // rows k .. k + 7, lanes 0..31 the even ones; 0 past K
+            const int kb = BLK ? __builtin_amdgcn_readfirstlane(k / g.block_rows) : 0, row = BLK ? k - kb * g.block_rows : k;
+            Feed fu, fv;
+            fu.aim(BLK ? uniform_ptr(blocks->u[kb]) : g.U, uint64_t(row) * row_a, g.u_bytes);
+            fv.aim(BLK ? uniform_ptr(blocks->v[kb]) : g.V, uint64_t(row) * row_b, g.v_bytes);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                x.a[i] = load_or_zero(fu, 2 * i * row_a + col_u);
+                x.b[i] = load4_or_zero(fv, 2 * i * row_b + col_v);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        f32x16 sum[4];
+        auto contract = [&](const Rows& x) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) sum[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.a[i], x.b[i][j], sum[j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        constexpr int RUNS = 4 / G;              // of a group
+        const int run = (g.K + 4 * SLICE - 1) / (4 * SLICE) * SLICE;
+        for (int i = 0; i < RUNS; ++i) {
+            const int k0 = (group * RUNS + i) * run, k1 = k0 + run < g.K ? k0 + run : g.K;
+            Rows x0, x1;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sum[j][r] = 0.f;
+            if (k0 < k1) fetch(k0, x0);
+            for (int k = k0; k < k1; k += SLICE) {
+                fetch(k + 8, x1);                // (a slice lies in one block)
+                contract(x0);
+                if (k + SLICE < k1) fetch(k + SLICE, x0);
+                contract(x1);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[j][r] = i == 0 ? sum[j][r] : acc[j][r] + sum[j][r];
+        }
+        gather();
     }
 
+    const int first = 32 * w + (32 / G) * group + 4 * lhi;                     // row of register q: first + 8*(q/4) + q%4
     if (M % 4 == 0) {
         const int64_t mc = m0 + 4 * l32;
         constexpr int DEPTH = NR < 8 ? NR : 8;

@@ -444,6 +444,26 @@ def test_sfb_f32_planes_do_not_look_at_what_lies_between_rows(M, N, B, P):
     assert all(torch.equal(x, seen[0]) for x in seen)
 
 
+@pytest.mark.parametrize("eu,ev", [(106, -100), (-90, 110), (39, 39), (38, 38)])
+@pytest.mark.parametrize("M,N,B,P", [c[1:] for c in PLANE_LAYERS])
+def test_sfb_f32_planes_contracted_anew_bit_exact(M, N, B, P, eu, ev):
+    """Small whole numbers times powers of two that the planes, or sums of them, cannot hold (the last: some sums), stacked and
+    read in place."""
+    d = inputs.fc_layer_integer(M, N, B, P, seed=M + N + eu)
+    for side, e in (("delta", eu), ("act", ev)):
+        d[side] = [x * np.float32(2.0) ** np.float32(e) for x in d[side]]
+    plan, U, ldu, V, ldv = run_pack(d, psd.F32)
+    want = (U[:, :N].double().t().contiguous() @ V[:, :M].double()).float()
+    for blocks in (False, True):
+        W, Mom = torch.zeros(N, M, device=DEV), torch.zeros(N, M, device=DEV)
+        if blocks:
+            psd.sync_fc_sfb_blocks(plan, psd.F32, list(U.split(B)), ldu, list(V.split(B)), ldv, W, Mom, 1.0, 0.0)
+        else:
+            psd.sync_fc_sfb(plan, psd.F32, U, ldu, V, ldv, W, Mom, 1.0, 0.0)
+        torch.cuda.synchronize()
+        assert torch.equal(Mom, want), blocks
+
+
 # Tiles that are alone on their compute unit, summed in four chains: K around the stages of one slice (16 / 32 rows), of two and
 # four groups, of odd and even numbers of stages, and where bf16 goes from two groups to four.
 @pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
