@@ -11,6 +11,9 @@ and two studies of how the MFMA loop and the W / Mom traffic share the chip (tex
     python3 bench_extras.py --study skew         # odd XCDs start late: does putting the phases out of step pay?
     python3 bench_extras.py --study partition    # reconstruction and a dense stream on disjoint sets of CUs
     python3 bench_extras.py --study ksweep       # time over the contraction length on the fc6 and fc8 shapes
+and two that say what figures elsewhere are compared with:
+    python3 bench_extras.py --study accuracy     # error of dW against 64 bits, fp32 factors in bf16 planes and on the fp32 pipe
+    python3 bench_extras.py --study rates        # what a large copy, read-modify-write and matrix product reach on this card
 """
 from __future__ import annotations
 
@@ -273,6 +276,63 @@ def k_sweep_study(psd, inputs, torch, dev):
             torch.cuda.empty_cache()
 
 
+# M, N, K of layers that are contracted in planes, every tile of theirs among them
+ACCURACY_LAYERS = [(4096, 4096, 256), (4096, 4096, 512), (4096, 4096, 1024), (4096, 4096, 2048), (4096, 4096, 4032), (9216, 4096, 2048),
+                   (4096, 1000, 2048), (4096, 1000, 512), (3000, 3000, 2048), (1024, 10000, 2048), (5693, 322, 1024), (4713, 392, 1024),
+                   (5506, 133, 2048), (5506, 133, 304)]
+
+
+def accuracy_study(psd, torch, dev, layers=ACCURACY_LAYERS):
+    """2-norm of the error of dW over the 2-norm of dW, against the product in 64 bits of the same factors: as the library contracts the
+    layer, and with a tile of the fp32 pipe pinned (one chain of additions over k)."""
+    def dw(M, N, K, U, V):
+        plan = psd.plan_layer(psd.LAYER_FC, M, N, K, 1)
+        Us, ldu, Vs, ldv = psd.alloc_factors(plan, psd.F32, dev)
+        psd.pack_factors(plan, [U], [V], psd.F32, Us, ldu, Vs, ldv)
+        out = []
+        for tile in (-1, 2):
+            psd.tune_set(psd.TUNE_SFB_F32_TILE, tile)
+            W, Mom = torch.zeros(N, M, device=dev), torch.zeros(N, M, device=dev)
+            psd.sync_fc_sfb(plan, psd.F32, Us, ldu, Vs, ldv, W, Mom, 1.0, 0.0)
+            out.append(Mom)
+        psd.tune_set(psd.TUNE_SFB_F32_TILE, -1)
+        return out, U.double().t().contiguous() @ V.double()
+
+    gen = torch.Generator(device=dev).manual_seed(24)
+    randn = lambda *shape: torch.randn(*shape, generator=gen, device=dev)
+    print("relative error of dW:     M      N      K  errors    planes   fp32 pipe   ratio")
+    for M, N, K in layers:
+        for how in ("gauss", "softmax"):
+            U = randn(K, N) * 1e-3
+            if how == "softmax":
+                y = torch.randint(0, N, (K, 1), generator=gen, device=dev)
+                U = (torch.softmax(randn(K, N), dim=1).scatter_add_(1, y, torch.full((K, 1), -1.0, device=dev)) / 256)
+            got, want = dw(M, N, K, U, randn(K, M).relu_())
+            e = [float((g.double() - want).norm() / want.norm()) for g in got]
+            print("                     %6d %6d %6d  %-8s %.2e   %.2e   %.2f" % (M, N, K, how, e[0], e[1], e[0] / e[1]), flush=True)
+    # one product per sum: an error of a sample is not zero in one column only
+    M, N, K = 5693, 322, 293
+    U, cols = torch.zeros(K, N, device=dev), torch.arange(N, device=dev)
+    U[torch.randint(0, K, (N,), generator=gen, device=dev), cols] = randn(N)
+    got, want = dw(M, N, K, U, randn(K, M))
+    ulp = torch.exp2(torch.floor(torch.log2(want.abs())) - 23)
+    for name, g in zip(("planes", "fp32 pipe"), got):
+        e = ((g.double() - want).abs() / ulp)[want != 0]
+        print("one product per sum (%d -> %d, K = %d), %s: largest error %.3f ulp, rms %.3f" % (M, N, K, name, float(e.max()), float(e.square().mean().sqrt())), flush=True)
+
+
+def rates_study(torch, dev):
+    x, y = torch.empty(1 << 30, device=dev), torch.empty(1 << 30, device=dev)
+    ms = _time_ms(torch, lambda i: y.copy_(x), 1)
+    print("copy of 4 GiB: %.0f us, %.0f GB/s" % (ms * 1e3, 8 * 2 ** 30 / ms / 1e6))
+    ms = _time_ms(torch, lambda i: x.mul_(1.0), 1)
+    print("read-modify-write of 4 GiB: %.0f us, %.0f GB/s" % (ms * 1e3, 8 * 2 ** 30 / ms / 1e6), flush=True)
+    for dt, n in ((torch.bfloat16, 8192), (torch.float32, 8192)):
+        a, b = torch.randn(n, n, device=dev).to(dt), torch.randn(n, n, device=dev).to(dt)
+        ms = _time_ms(torch, lambda i: a @ b, 1, iters=5)
+        print("matrix product %d x %d x %d, %s: %.0f us, %.0f TFLOP/s" % (n, n, n, str(dt)[6:], ms * 1e3, 2 * n ** 3 / ms / 1e9), flush=True)
+
+
 def dense_only(psd, inputs, torch, dev, n, iters, P=8, S=8):
     sets = [([torch.randn(n, device=dev) * 1e-3 for _ in range(P)], torch.randn(n, device=dev) * 1e-2,
              torch.zeros(n, device=dev)) for _ in range(2)]
@@ -412,7 +472,7 @@ def main():
     ap.add_argument("--dtype", choices=["bf16", "f32"], default="bf16")
     ap.add_argument("--dense", type=int, default=0, metavar="KEYS")
     ap.add_argument("--iters", type=int, default=40)
-    ap.add_argument("--study", choices=["skew", "partition", "ksweep"], default=None)
+    ap.add_argument("--study", choices=["skew", "partition", "ksweep", "accuracy", "rates"], default=None)
     args = ap.parse_args()
     import torch
     from paper_1512_06216_amd import binding as psd
@@ -425,6 +485,10 @@ def main():
         cu_partition_study(psd, torch, dev)
     elif args.study == "ksweep":
         k_sweep_study(psd, inputs, torch, dev)
+    elif args.study == "accuracy":
+        accuracy_study(psd, torch, dev)
+    elif args.study == "rates":
+        rates_study(torch, dev)
     elif args.dense:
         dense_only(psd, inputs, torch, dev, args.dense, args.iters)
     elif args.layer in NAMED_LAYERS:

@@ -3,14 +3,15 @@
 //     dW[n][m] = sum_k U[k][n] * V[k][m] ;  Mom = mu*Mom + lr*dW ;  W = W - Mom
 //
 // An fp32 number is the exact sum of three bf16 numbers, x = h + m + l: each is the nearest bf16 to what is left, 8 significant
-// bits at a time (|m| <= 2^-9 |x|, |l| <= 2^-18 |x|).  Of the nine products of two such sums the six largest are contracted on
-// v_mfma_f32_32x32x16_bf16, exact products added up in fp32; what is left out (m*l, l*m, l*l) is below 2^-26 of a product.  Six
+// bits at a time (|m| <= 2^-8 |x|, |l| <= 2^-17 |x|).  Of the nine products of two such sums the six largest are contracted on
+// v_mfma_f32_32x32x16_bf16, exact products added up in fp32; what is left out (m*l, l*m, l*l) is 2^-24 of a product at most.  Six
 // MFMAs at sixteen times the rate of the fp32 MFMA: 2.7 times its peak.
 //
 // Precision.  The five small products have accumulators of their own (`low`), so that the large ones take one rounding where the
 // fp32 pipe takes four, and the low ones round numbers 2^-8 as large.  Error of dW against 64 bits (2-norm; normal errors,
-// activations after a ReLU): K = 2048 2.1e-7 (fp32 pipe 5.7e-7), K = 256 7e-8 (with one set of accumulators 6.6e-7 and
-// 2.3e-7).  Factors are cut 2^24 times as large (psd_planes.h), so that small numbers keep all their bits too.  Rows of tiles
+// activations after a ReLU): K = 2048 2.1e-7 (fp32 pipe 5.7e-7), K = 256 7e-8 (2.0e-7; with one set of accumulators 6.6e-7 and
+// 2.3e-7); softmax errors 3.0e-7 (5.7e-7) and 1.4e-7 (2.0e-7).  A sum of one single product alone is further off: 0.91 units in
+// the last place at most, 0.297 rms (0.5 and 0.289).  Factors are cut 2^24 times as large (psd_planes.h), so that small numbers keep all their bits too.  Rows of tiles
 // with a sum that is not finite (infinities, NaN, factors above 2^104, sums above 2^78) are contracted anew on the fp32 pipe
 // (`again`), so that they give what they give there.
 //

@@ -464,6 +464,41 @@ def test_sfb_f32_planes_contracted_anew_bit_exact(M, N, B, P, eu, ev):
         assert torch.equal(Mom, want), blocks
 
 
+@pytest.mark.parametrize("M,N,K", [(4096, 4096, 2048), (5693, 322, 1024), (4713, 392, 1000), (5506, 133, 2040), (4896, 1220, 257)])
+@pytest.mark.parametrize("how", ["gauss", "softmax"])
+def test_sfb_f32_planes_are_no_further_from_64_bits_than_the_fp32_pipe(M, N, K, how, pinned_tile):
+    """The large products are added up 16 at a time.  A rounding of a number spread over its binade is 0.4 x 2^-24 of it (rms), and
+    normal products make the sum after i of n = K/16 roundings sqrt(i/n) of the last one: 0.4 x 2^-24 sqrt(n/2), half as much again
+    for what is not counted.  With the small products in the same accumulators it would be sqrt(6) of that, above the bound."""
+    g = torch.Generator().manual_seed(K + N)
+    U = (torch.randn(K, N, generator=g) * 1e-3).to(DEV)
+    if how == "softmax":
+        y = torch.randint(0, N, (K, 1), generator=g).to(DEV)
+        U = torch.softmax(U * 1e3, dim=1).scatter_add_(1, y, torch.full((K, 1), -1.0, device=DEV)) / 256
+    V = torch.randn(K, M, generator=g).relu_().to(DEV)
+    dW, want = _planes_dw(M, N, K, U, V)
+    err = float((dW.double() - want).norm() / want.norm())
+    pinned_tile(psd.TUNE_SFB_F32_TILE, 2)
+    pipe, _ = _planes_dw(M, N, K, U, V)
+    assert err <= float((pipe.double() - want).norm() / want.norm()), err
+    assert how == "softmax" or err <= 1.5 * 0.4 * 2.0 ** -24 * (K / 32) ** 0.5, err
+
+
+@pytest.mark.parametrize("M,N,K", [(4896, 1220, 272), (5693, 322, 293), (4713, 392, 299), (5506, 133, 303)])
+def test_sfb_f32_planes_single_products(M, N, K):
+    """One error per column is not zero: every sum is one product.  Half a unit in the last place for its rounding, half a unit at
+    most for the products of planes that are left out (m l and l m: 2^-25 of 2^(e+f) each, e and f the exponents), a thirtieth for
+    the roundings of the small ones."""
+    g = torch.Generator().manual_seed(N)
+    cols = torch.arange(N)
+    U = torch.zeros(K, N)
+    U[torch.randint(0, K, (N,), generator=g), cols] = torch.randn(N, generator=g)
+    dW, want = _planes_dw(M, N, K, U.to(DEV), torch.randn(K, M, generator=g).to(DEV))
+    assert bool((dW[want == 0] == 0).all())      # (an activation of zero: no last place to count in)
+    off = ((dW.double() - want).abs() / torch.exp2(torch.floor(torch.log2(want.abs())) - 23))[want != 0]
+    assert float(off.max()) <= 0.5 + 0.5 + 1 / 30 and float(off.square().mean().sqrt()) <= 0.31      # 1 / sqrt(12) = 0.289
+
+
 # Tiles that are alone on their compute unit, summed in four chains: K around the stages of one slice (16 / 32 rows), of two and
 # four groups, of odd and even numbers of stages, and where bf16 goes from two groups to four.
 @pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
