@@ -155,8 +155,10 @@ inline double planes_cost(const PlaneTile& t, int64_t N, int64_t M, int64_t K, i
 // K = 128 the fp32 pipe is the faster one for every size of layer (2624 -> 5037 52 against 58 us for the best of the tiles), at
 // K = 192 for some (4720 -> 868 26.1 and 29.6, 1669 -> 780 12.5 and 12.2, 8404 -> 321 21.1 and 17.5), at K = 256 for hardly any
 // (672 -> 3462 19.8 and 20.4, 4096 -> 1024 26.1 and 24.5, 4096 -> 4096 90 and 84, 9216 -> 4096 192 and 159), and at K = 320 for
-// none (4096 -> 4096 106 and 89).  A tenth has to be gained by these costs: of 132 layers none then gets slower, and the choice is
-// 0.8 % off the best one over the 114; with 6 % it is 0.7 % off, and 672 -> 3462 among the slower ones.
+// none (4096 -> 4096 106 and 89).  A tenth has to be gained by these costs: of 132 layers none then got slower, and the choice was
+// 0.8 % off the best one over the 114; with 6 % it was 0.7 % off, and 672 -> 3462 among the slower ones.  All of this was measured
+// before the factors were scaled (psd_planes.h), which costs 1 % and 3 % where tiles of 64 rows are alone: at K = 256 some are even
+// now, 4096 -> 4096 86.9 and 87.5 us, 4096 -> 3072 66.4 and 67.8, 1040 -> 5052 35.2 and 35.4, 480 -> 11166 34.3 and 34.1.
 constexpr int64_t kMinPlaneRows = 256;
 inline int choose_planes(int64_t N, int64_t M, int64_t K, int64_t cus, double us)
 {
@@ -210,7 +212,9 @@ inline double launch_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K, in
     // neighbours have too: 64 x 128 tiles are faster (1428 -> 4174, K = 128 25.9 and 22.3 us, 4526 -> 1135, K = 100 24.5 and
     // 20.8, 2807 -> 1518, K = 384 24.6 and 21.4), but for layers of few rows (9476 -> 442, K = 96 16.8 and 17.7).  The 128 x 128
     // tile takes 175 registers there, 113 on lines, and half as many fit: 891 -> 12360, K = 280 56.3 and, 128 x 192, 44.8,
-    // 988 -> 19501, K = 263 84.2 and, 64 x 128, 74.3, 2643 -> 7618, K = 951 116 and, 128 x 192, 105.
+    // 988 -> 19501, K = 263 84.2 and, 64 x 128, 74.3, 2643 -> 7618, K = 951 116 and, 128 x 192, 105.  Of 24 further layers whose
+    // tile this changes 22 are 2 to 16 % faster, 984 -> 12243 is the same, and 3100 -> 5022, K = 1098 is slower, 87.9 and 92.7: the 680 tiles of
+    // 128 x 192 that it gets fill the compute units one and a third times, which the cost of that tile counts as less than it is.
     const bool off_lines = M % 32 != 0;
     const double torn = off_lines && t.id == 4 && share > 4 && M < 8 * N ? 0.7 * share : off_lines && t.id == 2 && share > 2 ? 2 * share : 0;
     return 5 + update * (share + tail) + torn + t.loop * k * rounds;

@@ -12,7 +12,7 @@
 // activations after a ReLU): K = 2048 2.1e-7 (fp32 pipe 5.7e-7), K = 256 7e-8 (2.0e-7; with one set of accumulators 6.6e-7 and
 // 2.3e-7); softmax errors 3.0e-7 (5.7e-7) and 1.4e-7 (2.0e-7).  A sum of one single product alone is further off: 0.91 units in
 // the last place at most, 0.297 rms (0.5 and 0.289).  Factors are cut 2^24 times as large (psd_planes.h), so that small numbers keep all their bits too.  Rows of tiles
-// with a sum that is not finite (infinities, NaN, factors above 2^104, sums above 2^78) are contracted anew on the fp32 pipe
+// with a sum that is not finite (infinities, NaN, factors above 2^104, sums above 2^80) are contracted anew on the fp32 pipe
 // (`again`), so that they give what they give there.
 //
 // Tile and feeding.  A wavefront owns 32 x 128 of W: one MFMA block of n and four of m, the m of block j being m0 + 4*i + j, so that
@@ -66,7 +66,7 @@ struct Cfg {
     static constexpr int BUFFER_BYTES = G * SLICE_BYTES, ROWS_BYTES = 64 * row_stride(TM, 0) * 4;
     static constexpr int HANDED_BYTES = G * (G - 1) * (64 / G) * WN * 256;        // accumulators that groups hand over
     static constexpr int larger(int x, int y) { return x > y ? x : y; }
-    static constexpr int LDS_BYTES = larger(2 * BUFFER_BYTES, larger(ROWS_BYTES, HANDED_BYTES + WAVES * 4));  // (and a flag each)
+    static constexpr int LDS_BYTES = larger(2 * BUFFER_BYTES, larger(ROWS_BYTES, HANDED_BYTES)) + (G > 1 ? WAVES * 4 : 0);  // and a flag each
     static constexpr int PASSES = TN / 64;                                        // of the update, 64 rows at a time
 };
 
@@ -102,14 +102,17 @@ __device__ __forceinline__ f32x4 load4_or_zero(const Feed& f, uint32_t off)
     return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc_of(f), off, 0, 0));
 }
 
-// 6 MFMAs, the operand reads of the quarter to come behind the first of them, vector instructions in between
+// 6 MFMAs, the operand reads of the quarter to come behind the first of them, VALU vector instructions after each: 4, or 5 where
+// wavefronts cut three patches a slice instead of two (5506 -> 133, K = 2048 41.9 -> 41.5 us; with 6 42.3, and the others with 5
+// 0.5-1 % slower)
+template <int VALU>
 __device__ __forceinline__ void interleave()
 {
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                     // one MFMA
         if (i < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);          // LDS read
-        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);                     // vector ALU
+        __builtin_amdgcn_sched_group_barrier(0x002, VALU, 0);                     // vector ALU
         if (i >= 3) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);         // LDS write
         if (i >= 2) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);         // loads
     }
@@ -267,7 +270,7 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
 #pragma unroll
             for (int i = ITEMS * q / 4; i < ITEMS * (q + 1) / 4; ++i) item(j == 3 ? buf : buf ^ 1, i);
             mma(buf, j);
-            interleave();
+            interleave<WN == 2 ? 5 : 4>();
         }
     };
     int t = steps;
@@ -282,20 +285,7 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
     for (int j = 0; j < 4; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[j][r] += low[j][r];
-    // Does one of this wavefront's sums overflow, alone or with those of three other groups, or is one not a number?  Only sums of
-    // the layer count: those past N and M are made of what lies between the rows of the factors, which nobody has to fill.
-    uint32_t largest = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const uint32_t x = 2 * __float_as_uint(acc[j][r]);                 // without the sign
-            if (n0 + 32 * w + 8 * (r >> 2) + 4 * lhi + (r & 3) < N && m0 + 4 * l32 + j < M) largest = x > largest ? x : largest;
-        }
-    bool again = __any(largest >= 2 * 0x7e800000u);                            // 2^126
-    int* const flags = reinterpret_cast<int*>(lds + C::HANDED_BYTES);
     __syncthreads();                             // the slices are no longer read
-    if (G > 1 && lane == 0) flags[wave] = again;
     // d: the sums of all groups.  A group keeps NR registers of each block, rows 32/G * group ..., and hands the others over.
     constexpr int NR = 16 / G;
     float d[NR][4];
@@ -317,7 +307,6 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
                 }
             }
             __syncthreads();
-            again = __any(flags[lane % C::WAVES]);
 #pragma unroll
             for (int i = 1; i < G; ++i) {
                 const int from = (group + i) % G;
@@ -327,7 +316,6 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
                     d[q][0] += x.x; d[q][1] += x.y; d[q][2] += x.z; d[q][3] += x.w;
                 }
             }
-            __syncthreads();
         } else {
 #pragma unroll
             for (int q = 0; q < NR; ++q)
@@ -336,6 +324,29 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
         }
     };
     gather();
+    const int first = 32 * w + (32 / G) * group + 4 * lhi;                     // row of register q: first + 8*(q/4) + q%4
+    // Is one of the sums not finite?  Only those of the layer count: the ones past N and M are made of what lies between the rows of
+    // the factors, which nobody has to fill.  (Tiles inside W without the comparisons, and only the sums that a group keeps: 5506 ->
+    // 133, K = 304 13.3 us; with all 64 sums of a lane compared, before they are handed over, 14.2.)
+    float nan = 0.f;
+    auto look = [&](auto whole) {
+#pragma unroll
+        for (int q = 0; q < NR; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool own = decltype(whole)::value || (n0 + first + 8 * (q >> 2) + (q & 3) < N && m0 + 4 * l32 + j < M);
+                if (own) nan = __fmaf_rn(d[q][j], 0.f, nan);
+            }
+    };
+    if (n0 + C::TN <= N && m0 + C::TM <= M) look(std::true_type{});
+    else look(std::false_type{});
+    bool again = __any(nan != 0.f);
+    if constexpr (G > 1) {
+        int* const flags = reinterpret_cast<int*>(lds + C::LDS_BYTES) - C::WAVES;        // behind what the update uses
+        if (lane == 0) flags[wave] = again;
+        __syncthreads();                         // ... and the sums handed over are no longer read
+        again = __any(flags[lane % C::WAVES]);
+    }
     if (!again) {
 #pragma unroll
         for (int q = 0; q < NR; ++q)
@@ -345,9 +356,9 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
         // Anew on the fp32 MFMA (with groups: all wavefronts, as they hand sums over), in four runs over k as in the fp32 kernel
         // for small layers: half the error of one run.  The operands come from memory as they are, 8 rows ahead of 16 MFMAs: they
         // are wanted by lanes as they lie there, and 20 bytes per clock of a compute unit feed its fp32 MFMA.  A launch that does
-        // this in every tile takes its own loop and that of the fp32 pipe: 9216 -> 4096, K = 2048 1845 us (finite numbers 760; with
-        // every operand waited for 5025; a 128 x 128 tile of the fp32 kernel 1060), 4096 -> 1000 216 (92; 811; 133), 5506 -> 133
-        // 108 (44; 882, each of the four groups over all of K; 123).
+        // this in every tile takes its own loop and that of the fp32 pipe: 9216 -> 4096, K = 2048 1720 us (finite numbers 731; with
+        // every operand waited for 5025; the 128 x 128 tile of the fp32 kernel 1055), 4096 -> 1000 204 (89; 811; 129), 5506 -> 133
+        // 105 (42; 882, each of the four groups over all of K; 121).
         struct Rows { float a[4]; f32x4 b[4]; };
         const uint32_t col_u = lhi * row_a + static_cast<uint32_t>(n0 + 32 * w + l32) * 4, col_v = lhi * row_b + static_cast<uint32_t>(m0 + 4 * l32) * 4;
         auto fetch = [&](int k, Rows& x) {       // rows k .. k + 7, lanes 0..31 the even ones; 0 past K
@@ -392,9 +403,9 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
                 for (int r = 0; r < 16; ++r) acc[j][r] = i == 0 ? sum[j][r] : acc[j][r] + sum[j][r];
         }
         gather();
+        if constexpr (G > 1) __syncthreads();
     }
 
-    const int first = 32 * w + (32 / G) * group + 4 * lhi;                     // row of register q: first + 8*(q/4) + q%4
     if (M % 4 == 0) {
         const int64_t mc = m0 + 4 * l32;
         constexpr int DEPTH = NR < 8 ? NR : 8;
