@@ -129,7 +129,8 @@ psd_status psd_sync_fc_sfb(const psd_plan* plan, int32_t factor_dtype,
                            void* workspace, size_t workspace_bytes, void* stream);
 
 /* Bytes of workspace with which psd_sync_fc_sfb may split this layer's sum over k (a multiple of
- * 16), or 0 if it would not split it (enough tiles already, K too short, bad arguments).  Host only;
+ * 16), or 0 if it would not split it (enough tiles already, K too short, bad arguments).  Goes by the room a layer
+ * leaves; whether the sum is then split, which fp32 layers on the bf16 MFMA never are, is decided in the call.  Host only;
  * depends on the layer shape, the factor dtype, the current device's CU count and the pinned tile. */
 size_t psd_sfb_workspace_bytes(const psd_plan* plan, int32_t factor_dtype);
 

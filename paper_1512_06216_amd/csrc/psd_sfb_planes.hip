@@ -26,9 +26,10 @@
 // before the last quarter of a slice's MFMAs, whose execution hides the first operand reads of the slice to come; loads are in
 // flight for a whole slice.
 //
-// Bound by power: the clock settles at 1.7-1.8 GHz with the MFMA pipe 76 % busy.  9216 -> 4096, K = 2048: 700 us, 221 TFLOP/s
-// (fp32 pipe 1066, at its peak; with U through LDS too 727); 4096 -> 4096 319 (488; 331), 4096 -> 1000 88 (124; 91),
-// 3000 -> 3000 220 (276; 225).  Tried and not better: one set of accumulators and three workgroups per compute unit (699 us with U
+// Bound by power: the clock settles at 1.7-1.8 GHz with the MFMA pipe 74 % busy.  9216 -> 4096, K = 2048: 701 us, 221 TFLOP/s
+// (fp32 pipe 1066, at its peak), 4096 -> 4096 321 (488), 4096 -> 1000 88 (124), 3000 -> 3000 226 (276); scaling the factors is 1 %
+// of that (side by side 720 and 711 us, 325 and 322, 90.2 and 89.1, 228 and 225), with U through LDS too it was 727, 331, 91 and 225
+// against 700, 319, 88 and 220.  Tried and not better: one set of accumulators and three workgroups per compute unit (699 us with U
 // through LDS, but twice to three times the error), loads two slices ahead (no change), all vector work in three quarters of a
 // slice or spread more thinly (0-2 % slower), all operand reads of a quarter before its MFMAs (2-4 % slower), wave priorities
 // (10 % slower).
