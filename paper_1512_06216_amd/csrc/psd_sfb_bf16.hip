@@ -110,7 +110,14 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
     const int per_group = GROUP_N * tiles_m;
     const int g = lin / per_group, in_g = lin - g * per_group;
     const int rows_g = tiles_n - g * GROUP_N < GROUP_N ? tiles_n - g * GROUP_N : GROUP_N;
-    const int tile_n = g * GROUP_N + in_g % rows_g, tile_m = in_g / rows_g;
+    // Up to 8 groups, the XCDs work on several of them at the same time, and each group starts an eighth of the columns behind the
+    // one before: a panel of V that is not in the Infinity Cache is then fetched from HBM by one XCD and found there by the
+    // others.  All at the same columns, they all fetch it: 25088 -> 4096, K = 2048 with the factors cold 560 us, now 550 (790 and
+    // 777 mJ; warm 537 both).  Rows of W of a power of two also reach other channels of HBM then: 16384 -> 2048, K = 1024 165 -> 148.
+    // With more groups than XCDs these are spread already (3000 -> 21841 397 both, turned or not).
+    int tile_m = in_g / rows_g + (tiles_n <= 8 * GROUP_N ? g * tiles_m / 8 : 0);
+    if (tile_m >= tiles_m) tile_m -= tiles_m;
+    const int tile_n = g * GROUP_N + in_g % rows_g;
 
     const int64_t n0 = int64_t(tile_n) * C::TN, m0 = int64_t(tile_m) * C::TM;
     const int tid = threadIdx.x, lane = tid & 63;

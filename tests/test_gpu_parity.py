@@ -626,6 +626,17 @@ def test_sfb_f32_inner_tiles_bit_exact(M, B, tile, pinned_tile):
         assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr)
 
 
+@pytest.mark.parametrize("M,N", [(1100, 2170), (1100, 8190), (1100, 8200), (130, 8192), (2000, 1025)])
+def test_sfb_bf16_groups_of_tile_rows_that_start_at_other_columns_bit_exact(M, N, pinned_tile):
+    """3, 8, 9 (not turned), 8 and 2 groups of eight tile rows, over 9, 2 and 16 tile columns: every tile once."""
+    pinned_tile(psd.TUNE_SFB_BF16_TILE, 2)
+    d = inputs.fc_layer_integer(M, N, B=12, P=3, seed=N)
+    Wg, Mg, _ = run_sfb(d, psd.BF16, 0.25, 0.5)
+    U, V = orc.pack_factors(d["delta"], d["act"])
+    Wr, Mr = orc.sync_fc_sfb(U, V, d["W"], d["Mom"], 0.25, 0.5)
+    assert np.array_equal(Mg, Mr) and np.array_equal(Wg, Wr)
+
+
 @pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
 def test_weight_decay_bit_exact_on_both_routes(dtype):
     # wd, lr, mu powers of two and integer data: every intermediate is exact in fp32
