@@ -17,9 +17,10 @@
 // by the buffer range check, so there is no tail code.
 //
 // MFMA operand roles are swapped (rows = m, columns = n) so that the four consecutive
-// accumulator rows a lane owns are four adjacent m of one W row; the epilogue turns each
-// block through LDS so that W and Mom move in 16-byte accesses, one whole cache line per row.
+// accumulator rows a lane owns are four adjacent m of one W row; the epilogue turns them
+// through LDS so that W and Mom move in 16-byte accesses, whole cache lines of eight rows each.
 #include <atomic>
+#include <type_traits>
 #include "psd_device.h"
 #include "psd_internal.h"
 
@@ -50,7 +51,8 @@ struct Cfg {
     static constexpr int NI_A = A_BYTES / 1024 / WAVES;          // 1 KiB DMA instructions per wavefront
     static constexpr int NI_B = B_BYTES / 1024 / WAVES;
     static constexpr int PATCH_BYTES = WAVES * 32 * PLD * 4;
-    static constexpr int ROWS = 32 * WN;                         // rows in the buffer of the update (RowUpdate)
+    static constexpr int ROWS = 32 * WN;                         // rows in the buffer of the update (RowUpdate, InnerUpdate)
+    static constexpr bool PATCHES = BM == 4 && G == 1;           // may it run ON_LINES_AT_ONCE
     static constexpr size_t larger(size_t a, size_t b) { return a > b ? a : b; }
     static constexpr size_t LDS_BYTES = larger(size_t(NSTAGE) * STAGE_BYTES, PATCH_BYTES);
     static constexpr size_t LDS_BYTES_ROWS = larger(LDS_BYTES, size_t(G) * ROWS * row_stride(TM, 0) * 4);
@@ -76,8 +78,11 @@ __device__ __forceinline__ bf16x4 read_tr(uint32_t lds_addr)
 // block (and aimed at nothing past the last one, which reads as zeros like the K tail does).
 struct BlockPtrs { const uint16_t* u[PSD_MAX_WORKERS]; const uint16_t* v[PSD_MAX_WORKERS]; };
 
-// STREAM: the rows of W and Mom start on cache-line boundaries (see the epilogue).
-template <class C, bool PART, bool BLK, bool STREAM>
+// Where the rows of W and Mom start, and with it how the update reaches them (see the epilogue): anywhere in a cache line; on
+// lines; on lines, in a launch whose tiles all run at once (bf16_patches in psd_rules.h).
+enum Rows { ANYWHERE, ON_LINES, ON_LINES_AT_ONCE };
+
+template <class C, bool PART, bool BLK, Rows AT>
 __device__ __forceinline__ void
 sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __restrict__ V, int64_t ldv,
               float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
@@ -86,7 +91,8 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
               const BlockPtrs* blocks, int n_blocks, int block_rows)
 {
     static_assert(!(PART && (BLK || C::G > 1)), "a split of K over workgroups is not combined with blocks read in place or groups");
-    static_assert(!(STREAM && C::G > 1), "the groups' sums go through the row buffers");
+    static_assert(AT == ANYWHERE || C::G == 1, "grouped tiles make no difference between rows");
+    static_assert(AT != ON_LINES_AT_ONCE || C::PATCHES, "what is not launched is not compiled");
     constexpr int KT = C::KT;
     // Measurement aid (off unless asked for): the workgroups that start first on the odd-numbered
     // XCDs wait skew_ticks of the 100 MHz wall clock, which puts the two halves of the chip out of
@@ -335,8 +341,8 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
                     }
                 }
             }
-    } else if constexpr (STREAM) {
-        // Rows of W start on cache-line boundaries (M a multiple of 32).
+    } else if constexpr (AT == ON_LINES_AT_ONCE) {
+        // Every wavefront by itself, no barrier, 8 loads of a lane in flight.
         // Held as they are, the quads of one W row sit in 2 lanes x 4 registers, and a
         // wavefront access would touch 32 rows x 32 bytes: measured at ~3.1 TB/s for the W/Mom
         // read-modify-write, against ~4.9 TB/s once every row gets >= 128 contiguous bytes per
@@ -379,63 +385,84 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
             }
         }
     } else {
-        // Rows of W start anywhere in a cache line: the rows of one bn of all wavefronts go through LDS at a time and come back
-        // as whole lines of W (RowUpdate).  With the patch above every access would straddle two lines: 3000 -> 21841,
-        // K = 2048 468 -> 392 us; rows that are not even 16-byte aligned (3001 -> 21841), element by element before,
-        // 1873 -> 420 us.
+        // The rows of one bn of all wavefronts go through LDS at a time and come back as whole lines of W: a wavefront takes eight
+        // rows of the tile's whole width, and while it updates them those of the next eight are on their way.  Tiles inside W of one
+        // group of wavefronts by InnerUpdate, whose batches are whole rows of the tile (768 bytes of W, then of Mom; half of that is
+        // up to 7 % slower than all of it: 25088 -> 4096 518 and 580 us); what is left at the edges of W, and the tiles of several
+        // groups, by RowUpdate.  us with a patch of LDS for each wavefront on lines (128 bytes of 32 rows, then the next) and
+        // RowUpdate for every tile off lines -> now, K = 2048 unless said: 25088 -> 4096 531 -> 514, 9216 -> 4096 198 -> 196,
+        // 4096 -> 21841 465 -> 460, 3840 -> 2020, K = 56 30.3 -> 27.0, 4096 -> 8192 in 128 x 128, K = 1024 148 -> 128;
+        // 3000 -> 21841 395 -> 360, 3001 -> 21841 411 -> 370, 9999 -> 4095 262 -> 233, 2545 -> 15057, K = 1072 209 -> 164,
+        // 20280 -> 1582, K = 296 124 -> 104.  (These launches are bound by power, 1.4 kW, or by HBM: RowUpdate has two to three times
+        // the vector instructions.)  64 x 64 tiles off lines, of which a third and more are edges, gain nothing: 172 -> 11620,
+        // K = 88 9.9 and 10.5.
         float* buf = reinterpret_cast<float*>(lds);
+        constexpr bool SHIFTED = AT == ANYWHERE, INNER = C::G == 1 && (C::BM >= 2 || !SHIFTED);
+        const bool inside = n0 + C::TN <= N && m0 + C::TM <= M;
 #pragma unroll
         for (int bn = 0; bn < C::BN; ++bn) {
             auto row_n = [&](int r) { return n0 + (r >> 5) * 32 * C::BN + 32 * bn + (r & 31); };
-            RowUpdate<C::ROWS, C::TM, C::WAVES, C::BM == 4 ? 4 : C::BM == 1 ? 6 : 5, C::G, decltype(row_n)> rows(W, Mom, row_n, m0, N, M, wave, lane);
-            rows.template fetch<0>();
-            if (bn > 0) __syncthreads();           // the rows before are no longer read
-            const int r = (wg / C::WM) * 32 + l32;
-            float* to = buf + (group * C::ROWS + r) * rows.stride + wm0 + 4 * lhi + line_shift(W, row_n(r), M);
+            auto update = [&](auto rows) {
+                rows.template fetch<0>();
+                if (bn > 0) __syncthreads();       // the rows before are no longer read
+                const int r = (wg / C::WM) * 32 + l32;
+                float* to = buf + (group * C::ROWS + r) * rows.stride + wm0 + 4 * lhi + (SHIFTED ? line_shift(W, row_n(r), M) : 0);
 #pragma unroll
-            for (int bm = 0; bm < C::BM; ++bm)
+                for (int bm = 0; bm < C::BM; ++bm)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x16& a = acc[bn][bm];
-                    if (M % 4 == 0) {              // shifts are multiples of 4: 16-byte LDS writes
-                        *reinterpret_cast<float4*>(to + 32 * bm + 8 * q) = make_float4(a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]);
-                    } else {
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x16& a = acc[bn][bm];
+                        if (!SHIFTED || M % 4 == 0) {          // shifts are multiples of 4: 16-byte LDS writes
+                            *reinterpret_cast<float4*>(to + 32 * bm + 8 * q) = make_float4(a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]);
+                        } else {
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) to[32 * bm + 8 * q + i] = a[4 * q + i];
+                            for (int i = 0; i < 4; ++i) to[32 * bm + 8 * q + i] = a[4 * q + i];
+                        }
                     }
+                __syncthreads();
+                rows.run(buf, lr, mu, wd);
+            };
+            if constexpr (INNER) {
+                if (inside) {
+                    update(InnerUpdate<C::ROWS, C::TM, C::WAVES, C::TM / 32, !SHIFTED, decltype(row_n)>(W, Mom, row_n, m0, M, wave, lane));
+                    continue;
                 }
-            __syncthreads();
-            rows.run(buf, lr, mu, wd);
+            }
+            // (64 x 128 tiles: no deeper than their 168 registers hold)
+            constexpr int DEPTH = C::BM == 4 ? 4 : C::BM == 1 ? 6 : C::BN == 1 ? 4 : 5;
+            update(RowUpdate<C::ROWS, C::TM, C::WAVES, DEPTH, C::G, decltype(row_n)>(W, Mom, row_n, m0, N, M, wave, lane));
         }
     }
 }
 
-template <class C, bool PART, bool STREAM>
+template <class C, bool PART, Rows AT>
 __global__ void __launch_bounds__(C::THREADS, C::OCC)
 sfb_bf16_kernel(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __restrict__ V, int64_t ldv,
                 float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
                 int tiles_n, int tiles_m, uint32_t u_bytes, uint32_t v_bytes, float* __restrict__ part,
                 int64_t part_stride, int stages_per_split, int skew_blocks, int skew_ticks)
 {
-    sfb_bf16_body<C, PART, false, STREAM>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, tiles_n, tiles_m, u_bytes, v_bytes, part,
+    sfb_bf16_body<C, PART, false, AT>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, tiles_n, tiles_m, u_bytes, v_bytes, part,
                                   part_stride, stages_per_split, skew_blocks, skew_ticks, nullptr, 0, 0);
 }
 
 // the P per-worker blocks read in place (u_bytes, v_bytes: the size of ONE block)
-template <class C, bool STREAM>
+template <class C, Rows AT>
 __global__ void __launch_bounds__(C::THREADS, C::OCC)
 sfb_bf16_blocks_kernel(BlockPtrs blocks, int n_blocks, int block_rows, int64_t ldu, int64_t ldv,
                        float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
                        int tiles_n, int tiles_m, uint32_t u_bytes, uint32_t v_bytes)
 {
-    sfb_bf16_body<C, false, true, STREAM>(nullptr, ldu, nullptr, ldv, W, Mom, N, M, K, lr, mu, wd, tiles_n, tiles_m, u_bytes,
+    sfb_bf16_body<C, false, true, AT>(nullptr, ldu, nullptr, ldv, W, Mom, N, M, K, lr, mu, wd, tiles_n, tiles_m, u_bytes,
                                   v_bytes, nullptr, 0, 0, 0, 0, &blocks, n_blocks, block_rows);
 }
 
-// do all rows of W and Mom start on cache-line boundaries (128 bytes)?
-bool rows_on_lines(const float* W, const float* Mom, int64_t M)
+// where the rows of W and Mom start, for the tile C (cache lines have 128 bytes)
+template <class C>
+Rows rows_at(const float* W, const float* Mom, int64_t N, int64_t M, int64_t K)
 {
-    return M % 32 == 0 && (reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(Mom)) % 128 == 0;
+    if (C::G > 1 || M % 32 != 0 || (reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(Mom)) % 128 != 0) return ANYWHERE;
+    return C::PATCHES && bf16_patches(N, M, K, C::TN, C::TM, device_cu_count()) ? ON_LINES_AT_ONCE : ON_LINES;
 }
 
 template <class C>
@@ -446,16 +473,15 @@ psd_status launch_cfg_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int6
     const int64_t tiles = tiles_n * tiles_m;
     if (tiles < 1 || tiles > 0x3fffffff) return PSD_E_INVALID;
     const int64_t u_bytes = B * ldu * 2, v_bytes = B * ldv * 2;          // one block
-    const bool lines = C::G == 1 && rows_on_lines(W, Mom, M);
-    constexpr bool can_stream = C::G == 1;
-    auto kern = lines ? sfb_bf16_blocks_kernel<C, can_stream> : sfb_bf16_blocks_kernel<C, false>;
-    const size_t lds = lines ? C::LDS_BYTES : C::LDS_BYTES_ROWS;
+    constexpr Rows on_lines = C::G == 1 ? ON_LINES : ANYWHERE, at_once = C::PATCHES ? ON_LINES_AT_ONCE : on_lines;   // what there is
+    const Rows at = rows_at<C>(W, Mom, N, M, P * B);
+    auto kern = at == ON_LINES_AT_ONCE ? sfb_bf16_blocks_kernel<C, at_once>
+                                       : at == ON_LINES ? sfb_bf16_blocks_kernel<C, on_lines> : sfb_bf16_blocks_kernel<C, ANYWHERE>;
+    const size_t lds = at == ON_LINES_AT_ONCE ? C::LDS_BYTES : C::LDS_BYTES_ROWS;
     static std::atomic<bool> attr_done{false};
     if (!attr_done.load(std::memory_order_acquire)) {
-        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_blocks_kernel<C, can_stream>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
-        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_blocks_kernel<C, false>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
+        for (auto k : {sfb_bf16_blocks_kernel<C, at_once>, sfb_bf16_blocks_kernel<C, on_lines>, sfb_bf16_blocks_kernel<C, ANYWHERE>})
+            PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         attr_done.store(true, std::memory_order_release);
     }
     hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(tiles)), dim3(C::THREADS), lds, st,
@@ -476,21 +502,20 @@ psd_status launch_cfg(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t
     if (tiles < 1 || tiles * splits > 0x3fffffff) return PSD_E_INVALID;
     static_assert(C::NSTAGE <= kBf16Stages, "the reserve covers the ring");
     const int64_t u_bytes = K * ldu * 2, v_bytes = K * ldv * 2;
-    const bool lines = C::G == 1 && rows_on_lines(W, Mom, M);
-    constexpr bool alone = C::G == 1;            // groups come neither split nor streamed
-    auto kern = splits > 1 ? sfb_bf16_kernel<C, alone, false>
-                           : (lines ? sfb_bf16_kernel<C, false, alone> : sfb_bf16_kernel<C, false, false>);
-    const size_t lds = splits > 1 || lines ? C::LDS_BYTES : C::LDS_BYTES_ROWS;
+    constexpr bool alone = C::G == 1;            // groups are not split
+    constexpr Rows on_lines = alone ? ON_LINES : ANYWHERE, at_once = C::PATCHES ? ON_LINES_AT_ONCE : on_lines;   // what there is
+    const Rows at = rows_at<C>(W, Mom, N, M, K);
+    auto kern = splits > 1 ? sfb_bf16_kernel<C, alone, ANYWHERE>
+                : at == ON_LINES_AT_ONCE ? sfb_bf16_kernel<C, false, at_once>
+                : at == ON_LINES ? sfb_bf16_kernel<C, false, on_lines> : sfb_bf16_kernel<C, false, ANYWHERE>;
+    const size_t lds = splits > 1 || at == ON_LINES_AT_ONCE ? C::LDS_BYTES : C::LDS_BYTES_ROWS;
     // raise the dynamic LDS limit once per process (idempotent, so a race between two first
     // callers is harmless; the flag only saves the call on later launches)
     static std::atomic<bool> attr_done{false};
     if (!attr_done.load(std::memory_order_acquire)) {
-        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_kernel<C, alone, false>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
-        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_kernel<C, false, alone>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
-        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_bf16_kernel<C, false, false>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
+        for (auto k : {sfb_bf16_kernel<C, alone, ANYWHERE>, sfb_bf16_kernel<C, false, at_once>, sfb_bf16_kernel<C, false, on_lines>,
+                       sfb_bf16_kernel<C, false, ANYWHERE>})
+            PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         attr_done.store(true, std::memory_order_release);
     }
     const int skew = tune_value(PSD_TUNE_SFB_BF16_SKEW_US);

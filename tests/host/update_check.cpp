@@ -107,9 +107,15 @@ template <class R> struct F32Edge64 { using type = psd::RowUpdate<64, 64, 4, 6, 
 template <class R> struct F32Groups { using type = psd::RowUpdate<64, 64, 16, 6, 4, R>; };
 template <class R> struct Bf16w256 { using type = psd::RowUpdate<64, 256, 4, 4, 1, R>; };
 template <class R> struct Bf16w192 { using type = psd::RowUpdate<64, 192, 4, 5, 1, R>; };
+template <class R> struct Bf16h128 { using type = psd::RowUpdate<64, 128, 4, 4, 1, R>; };
 template <class R> struct Bf16Two { using type = psd::RowUpdate<64, 128, 8, 5, 2, R>; };
 template <class R> struct Inner128 { using type = psd::InnerUpdate<64, 128, 4, 4, false, R>; };
 template <class R> struct Inner64 { using type = psd::InnerUpdate<64, 64, 4, 4, false, R>; };
+template <class R> struct Inner256 { using type = psd::InnerUpdate<64, 256, 4, 8, false, R>; };
+template <class R> struct Inner192 { using type = psd::InnerUpdate<64, 192, 4, 6, false, R>; };
+template <class R> struct Lines256 { using type = psd::InnerUpdate<64, 256, 4, 8, true, R>; };
+template <class R> struct Lines192 { using type = psd::InnerUpdate<64, 192, 4, 6, true, R>; };
+template <class R> struct Lines64 { using type = psd::InnerUpdate<64, 64, 4, 2, true, R>; };
 template <class R> struct InnerLines { using type = psd::InnerUpdate<64, 128, 4, 4, true, R>; };
 
 }  // namespace
@@ -125,12 +131,19 @@ int main()
                 ok = ok && layer<F32Groups, 64, 64, 16, 4, 1, true, false>(N, M, lead, "fp32, four groups, 64 x 64");
                 ok = ok && layer<Bf16w256, 64, 256, 4, 1, 2, false, false>(N, M, lead, "bf16, 128 x 256");
                 ok = ok && layer<Bf16w192, 64, 192, 4, 1, 2, false, false>(N, M, lead, "bf16, 128 x 192");
+                ok = ok && layer<Bf16h128, 64, 128, 4, 1, 1, false, false>(N, M, lead, "bf16, 64 x 128");
                 ok = ok && layer<Bf16Two, 64, 128, 8, 2, 2, false, false>(N, M, lead, "bf16, two groups, 128 x 128");
             }
             ok = ok && layer<Inner128, 64, 128, 4, 1, 2, true, true>(133, M, lead, "fp32, inside, 128 x 128");
             ok = ok && layer<Inner64, 64, 64, 4, 1, 1, true, true>(133, M, lead, "fp32, inside, 64 x 64");
+            ok = ok && layer<Inner256, 64, 256, 4, 1, 2, false, true>(133, M, lead, "bf16, inside, 128 x 256");
+            ok = ok && layer<Inner192, 64, 192, 4, 1, 2, false, true>(133, M, lead, "bf16, inside, 128 x 192");
+            ok = ok && layer<Inner128, 64, 128, 4, 1, 1, false, true>(133, M, lead, "bf16, inside, 64 x 128");
         }
     ok = ok && layer<InnerLines, 64, 128, 4, 1, 1, true, true>(130, 288, 0, "fp32, inside, on lines");
+    ok = ok && layer<Lines256, 64, 256, 4, 1, 2, false, true>(130, 544, 0, "bf16, inside, on lines, 128 x 256");
+    ok = ok && layer<Lines192, 64, 192, 4, 1, 2, false, true>(130, 416, 0, "bf16, inside, on lines, 128 x 192");
+    ok = ok && layer<Lines64, 64, 64, 4, 1, 1, false, true>(130, 160, 0, "bf16, inside, on lines, 64 x 64");
     std::printf(ok ? "all right\n" : "failed\n");
     return ok ? 0 : 1;
 }

@@ -637,6 +637,29 @@ def test_sfb_bf16_groups_of_tile_rows_that_start_at_other_columns_bit_exact(M, N
     assert np.array_equal(Mg, Mr) and np.array_equal(Wg, Wr)
 
 
+@pytest.mark.parametrize("tile", [0, 1, 2])           # 128 x 256, 128 x 192, 128 x 128
+@pytest.mark.parametrize("M,B", [(544, 5), (544, 342), (572, 11), (577, 11), (602, 5)])
+def test_sfb_bf16_tiles_inside_w_and_at_its_edges_bit_exact(M, B, tile, pinned_tile):
+    """Rows on lines (K = 1026: 128 x 256 tiles in patches), on quads, anywhere and on pairs; W and Mom that start in the middle of
+    a line, between guard values that must survive."""
+    pinned_tile(psd.TUNE_SFB_BF16_TILE, tile)
+    d = inputs.fc_layer_integer(M, 300, B=B, P=3, seed=M, amax=2)
+    plan, U, ldu, V, ldv = run_pack(d, psd.BF16)
+    Uo, Vo = orc.pack_factors(d["delta"], d["act"])
+    Wr, Mr = orc.sync_fc_sfb(Uo, Vo, d["W"], d["Mom"], 0.25, 0.5)
+    n = 300 * M
+    for lead in (0, 12):
+        flat = [torch.full((n + 64,), 77.0, device=DEV) for _ in range(2)]
+        W, Mom = (f[lead:lead + n].view(300, M) for f in flat)
+        W.copy_(dev(d["W"]))
+        Mom.copy_(dev(d["Mom"]))
+        psd.sync_fc_sfb(plan, psd.BF16, U, ldu, V, ldv, W, Mom, 0.25, 0.5)
+        torch.cuda.synchronize()
+        assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr)
+        for f in flat:
+            assert bool((f[:lead] == 77).all()) and bool((f[lead + n:] == 77).all())
+
+
 @pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
 def test_weight_decay_bit_exact_on_both_routes(dtype):
     # wd, lr, mu powers of two and integer data: every intermediate is exact in fp32
