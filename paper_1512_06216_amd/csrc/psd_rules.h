@@ -280,6 +280,16 @@ inline bool bf16_patches(int64_t N, int64_t M, int64_t K, int64_t tn, int64_t tm
     return K >= kPatchRows && ((N + tn - 1) / tn) * ((M + tm - 1) / tm) <= 2 * cus;
 }
 
+// Does the 64 x 128 tile apply the update of all tiles as at the edges of W (RowUpdate), where rows are not even on quads: with two
+// tiles for each compute unit at most the code for the tiles inside (InnerUpdate) costs more than it saves.  us with and without
+// it: 20281 -> 187, K = 352 (477 tiles) 17.6 and 15.7; 3523 -> 891, K = 92 (392) 15.4 and 13.8; 615 -> 2216, K = 32 (175) 9.0 and
+// 8.0; the other way 2383 -> 593, K = 114 (190) 7.9 and 8.6; of 15 such layers 11 lose 4 to 11 % with it, 4 gain.  On quads 4628 -> 337,
+// K = 140 (222) 8.2 and 8.7, with more tiles 3543 -> 1273, K = 42 (560) 18.5 and 19.1, 21485 -> 397, K = 456 (1176) 37.2 and 44.1.
+inline bool bf16_few_tiles(int64_t N, int64_t M, int64_t tn, int64_t tm, int64_t cus)
+{
+    return M % 4 != 0 && ((N + tn - 1) / tn) * ((M + tm - 1) / tm) <= 2 * cus;
+}
+
 // ---- division by a number that a launch knows: multiplier and shifts of `divide` (psd_device.h)
 struct FastDiv { uint32_t d, mul, shift1, shift2; };
 

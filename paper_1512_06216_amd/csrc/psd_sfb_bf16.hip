@@ -53,6 +53,7 @@ struct Cfg {
     static constexpr int PATCH_BYTES = WAVES * 32 * PLD * 4;
     static constexpr int ROWS = 32 * WN;                         // rows in the buffer of the update (RowUpdate, InnerUpdate)
     static constexpr bool PATCHES = BM == 4 && G == 1;           // may it run ON_LINES_AT_ONCE
+    static constexpr bool FEW = BN == 1 && BM == 2 && G == 1;    // ... and ANYWHERE_FEW
     static constexpr size_t larger(size_t a, size_t b) { return a > b ? a : b; }
     static constexpr size_t LDS_BYTES = larger(size_t(NSTAGE) * STAGE_BYTES, PATCH_BYTES);
     static constexpr size_t LDS_BYTES_ROWS = larger(LDS_BYTES, size_t(G) * ROWS * row_stride(TM, 0) * 4);
@@ -78,9 +79,9 @@ __device__ __forceinline__ bf16x4 read_tr(uint32_t lds_addr)
 // block (and aimed at nothing past the last one, which reads as zeros like the K tail does).
 struct BlockPtrs { const uint16_t* u[PSD_MAX_WORKERS]; const uint16_t* v[PSD_MAX_WORKERS]; };
 
-// Where the rows of W and Mom start, and with it how the update reaches them (see the epilogue): anywhere in a cache line; on
-// lines; on lines, in a launch whose tiles all run at once (bf16_patches in psd_rules.h).
-enum Rows { ANYWHERE, ON_LINES, ON_LINES_AT_ONCE };
+// Where the rows of W and Mom start, and with it how the update reaches them (see the epilogue): anywhere in a cache line, in a
+// launch of few tiles (bf16_few_tiles in psd_rules.h) or not; on lines, in a launch whose tiles all run at once (bf16_patches) or not.
+enum Rows { ANYWHERE, ANYWHERE_FEW, ON_LINES, ON_LINES_AT_ONCE };
 
 template <class C, bool PART, bool BLK, Rows AT>
 __device__ __forceinline__ void
@@ -92,7 +93,7 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
 {
     static_assert(!(PART && (BLK || C::G > 1)), "a split of K over workgroups is not combined with blocks read in place or groups");
     static_assert(AT == ANYWHERE || C::G == 1, "grouped tiles make no difference between rows");
-    static_assert(AT != ON_LINES_AT_ONCE || C::PATCHES, "what is not launched is not compiled");
+    static_assert((AT != ON_LINES_AT_ONCE || C::PATCHES) && (AT != ANYWHERE_FEW || C::FEW), "what is not launched is not compiled");
     constexpr int KT = C::KT;
     // Measurement aid (off unless asked for): the workgroups that start first on the odd-numbered
     // XCDs wait skew_ticks of the 100 MHz wall clock, which puts the two halves of the chip out of
@@ -397,7 +398,7 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
         // the vector instructions.)  64 x 64 tiles off lines, of which a third and more are edges, gain nothing: 172 -> 11620,
         // K = 88 9.9 and 10.5.
         float* buf = reinterpret_cast<float*>(lds);
-        constexpr bool SHIFTED = AT == ANYWHERE, INNER = C::G == 1 && (C::BM >= 2 || !SHIFTED);
+        constexpr bool SHIFTED = AT == ANYWHERE || AT == ANYWHERE_FEW, INNER = C::G == 1 && AT != ANYWHERE_FEW && (C::BM >= 2 || !SHIFTED);
         const bool inside = n0 + C::TN <= N && m0 + C::TM <= M;
 #pragma unroll
         for (int bn = 0; bn < C::BN; ++bn) {
@@ -428,8 +429,8 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
                     continue;
                 }
             }
-            // (64 x 128 tiles: no deeper than their 168 registers hold)
-            constexpr int DEPTH = C::BM == 4 ? 4 : C::BM == 1 ? 6 : C::BN == 1 ? 4 : 5;
+            // (64 x 128 tiles beside InnerUpdate: no deeper than their 168 registers hold)
+            constexpr int DEPTH = C::BM == 4 ? 4 : C::BM == 1 ? 6 : C::FEW && INNER ? 4 : 5;
             update(RowUpdate<C::ROWS, C::TM, C::WAVES, DEPTH, C::G, decltype(row_n)>(W, Mom, row_n, m0, N, M, wave, lane));
         }
     }
@@ -461,9 +462,16 @@ sfb_bf16_blocks_kernel(BlockPtrs blocks, int n_blocks, int block_rows, int64_t l
 template <class C>
 Rows rows_at(const float* W, const float* Mom, int64_t N, int64_t M, int64_t K)
 {
-    if (C::G > 1 || M % 32 != 0 || (reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(Mom)) % 128 != 0) return ANYWHERE;
-    return C::PATCHES && bf16_patches(N, M, K, C::TN, C::TM, device_cu_count()) ? ON_LINES_AT_ONCE : ON_LINES;
+    if (C::G > 1) return ANYWHERE;
+    if (M % 32 == 0 && (reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(Mom)) % 128 == 0)
+        return C::PATCHES && bf16_patches(N, M, K, C::TN, C::TM, device_cu_count()) ? ON_LINES_AT_ONCE : ON_LINES;
+    return C::FEW && bf16_few_tiles(N, M, C::TN, C::TM, device_cu_count()) ? ANYWHERE_FEW : ANYWHERE;
 }
+
+// ... and what there is of a tile C
+template <class C> constexpr Rows kOnLines = C::G == 1 ? ON_LINES : ANYWHERE;
+template <class C> constexpr Rows kAtOnce = C::PATCHES ? ON_LINES_AT_ONCE : kOnLines<C>;
+template <class C> constexpr Rows kFew = C::FEW ? ANYWHERE_FEW : ANYWHERE;
 
 template <class C>
 psd_status launch_cfg_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int64_t ldu, int64_t ldv, float* W, float* Mom,
@@ -473,14 +481,15 @@ psd_status launch_cfg_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int6
     const int64_t tiles = tiles_n * tiles_m;
     if (tiles < 1 || tiles > 0x3fffffff) return PSD_E_INVALID;
     const int64_t u_bytes = B * ldu * 2, v_bytes = B * ldv * 2;          // one block
-    constexpr Rows on_lines = C::G == 1 ? ON_LINES : ANYWHERE, at_once = C::PATCHES ? ON_LINES_AT_ONCE : on_lines;   // what there is
     const Rows at = rows_at<C>(W, Mom, N, M, P * B);
-    auto kern = at == ON_LINES_AT_ONCE ? sfb_bf16_blocks_kernel<C, at_once>
-                                       : at == ON_LINES ? sfb_bf16_blocks_kernel<C, on_lines> : sfb_bf16_blocks_kernel<C, ANYWHERE>;
+    auto kern = at == ON_LINES_AT_ONCE ? sfb_bf16_blocks_kernel<C, kAtOnce<C>>
+                : at == ON_LINES       ? sfb_bf16_blocks_kernel<C, kOnLines<C>>
+                : at == ANYWHERE_FEW   ? sfb_bf16_blocks_kernel<C, kFew<C>> : sfb_bf16_blocks_kernel<C, ANYWHERE>;
     const size_t lds = at == ON_LINES_AT_ONCE ? C::LDS_BYTES : C::LDS_BYTES_ROWS;
     static std::atomic<bool> attr_done{false};
     if (!attr_done.load(std::memory_order_acquire)) {
-        for (auto k : {sfb_bf16_blocks_kernel<C, at_once>, sfb_bf16_blocks_kernel<C, on_lines>, sfb_bf16_blocks_kernel<C, ANYWHERE>})
+        for (auto k : {sfb_bf16_blocks_kernel<C, kAtOnce<C>>, sfb_bf16_blocks_kernel<C, kOnLines<C>>, sfb_bf16_blocks_kernel<C, kFew<C>>,
+                       sfb_bf16_blocks_kernel<C, ANYWHERE>})
             PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         attr_done.store(true, std::memory_order_release);
     }
@@ -503,18 +512,18 @@ psd_status launch_cfg(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t
     static_assert(C::NSTAGE <= kBf16Stages, "the reserve covers the ring");
     const int64_t u_bytes = K * ldu * 2, v_bytes = K * ldv * 2;
     constexpr bool alone = C::G == 1;            // groups are not split
-    constexpr Rows on_lines = alone ? ON_LINES : ANYWHERE, at_once = C::PATCHES ? ON_LINES_AT_ONCE : on_lines;   // what there is
     const Rows at = rows_at<C>(W, Mom, N, M, K);
     auto kern = splits > 1 ? sfb_bf16_kernel<C, alone, ANYWHERE>
-                : at == ON_LINES_AT_ONCE ? sfb_bf16_kernel<C, false, at_once>
-                : at == ON_LINES ? sfb_bf16_kernel<C, false, on_lines> : sfb_bf16_kernel<C, false, ANYWHERE>;
+                : at == ON_LINES_AT_ONCE ? sfb_bf16_kernel<C, false, kAtOnce<C>>
+                : at == ON_LINES         ? sfb_bf16_kernel<C, false, kOnLines<C>>
+                : at == ANYWHERE_FEW     ? sfb_bf16_kernel<C, false, kFew<C>> : sfb_bf16_kernel<C, false, ANYWHERE>;
     const size_t lds = splits > 1 || at == ON_LINES_AT_ONCE ? C::LDS_BYTES : C::LDS_BYTES_ROWS;
     // raise the dynamic LDS limit once per process (idempotent, so a race between two first
     // callers is harmless; the flag only saves the call on later launches)
     static std::atomic<bool> attr_done{false};
     if (!attr_done.load(std::memory_order_acquire)) {
-        for (auto k : {sfb_bf16_kernel<C, alone, ANYWHERE>, sfb_bf16_kernel<C, false, at_once>, sfb_bf16_kernel<C, false, on_lines>,
-                       sfb_bf16_kernel<C, false, ANYWHERE>})
+        for (auto k : {sfb_bf16_kernel<C, alone, ANYWHERE>, sfb_bf16_kernel<C, false, kAtOnce<C>>, sfb_bf16_kernel<C, false, kOnLines<C>>,
+                       sfb_bf16_kernel<C, false, kFew<C>>, sfb_bf16_kernel<C, false, ANYWHERE>})
             PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         attr_done.store(true, std::memory_order_release);
     }

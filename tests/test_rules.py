@@ -20,7 +20,7 @@ def rules(tmp_path_factory):
     for name, res, args in (("max_items", i64, []), ("dense_threads", i32, [i64, i64]), ("dense_chunks", i32, [i64, i32, i32]),
                             ("pack_rows", i64, [i64, i64]), ("divided", ctypes.c_uint32, [ctypes.c_uint32, ctypes.c_uint32]), ("f32_reach", i32, [i64, i64, i64]),
                             ("bf16_reach", i32, [i64, i64, i64, i64]), ("bf16_choice", i32, [i64, i64, i64, c_int, i64]),
-                            ("splits_asked", i32, [i64, i64, i64]), ("bf16_in_patches", i32, [i64, i64, i64, i64]), ("f32_choice", i32, [i64, i64, i64, i64]),
+                            ("splits_asked", i32, [i64, i64, i64]), ("bf16_in_patches", i32, [i64, i64, i64, i64]), ("bf16_few", i32, [i64, i64, i64]), ("f32_choice", i32, [i64, i64, i64, i64]),
                             ("f32_planes", i32, [i64, i64, i64, i64]), ("f32_splits", i32, [i64, i64, i64, c_int, i64])):
         getattr(L, name).restype, getattr(L, name).argtypes = res, args
     return L
@@ -138,6 +138,13 @@ def test_update_in_patches_is_for_long_sums_over_tiles_that_all_run_at_once(rule
     for M, N, K, patches in ((4096, 4096, 1024, 1), (4096, 4096, 1023, 0), (4096, 4097, 2048, 0), (4352, 3840, 2048, 1),
                              (4096, 8192, 1024, 0), (256, 128, 1024, 1)):
         assert rules.bf16_in_patches(N, M, K, CUS) == patches, (M, N, K)
+
+
+def test_few_tiles_off_quads_are_all_updated_as_at_the_edges(rules):
+    for M, N, few in ((20281, 187, 1), (20282, 187, 1), (20284, 187, 0), (8192 + 1, 448, 1), (128 * 64 + 1, 449, 0), (3543, 1273, 0)):
+        assert rules.bf16_few(N, M, CUS) == few, (M, N)
+    tiles = {(rules.bf16_choice(N, M, B * P, 1, CUS) // 10, M % 4 != 0, rules.bf16_few(N, M, CUS)) for M, N, B, P in parity.BF16_FEW_LAYERS}
+    assert tiles == {(3, True, 1), (3, True, 0)}
 
 
 def test_rows_off_lines_get_other_tiles_where_they_do_not_all_fit_the_compute_units(rules):
