@@ -128,9 +128,11 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// ON_LINES: the rows of W and Mom start on cache lines.  (Kernels of their own: with the code for other rows beside it 4096 -> 4096,
+// K = 512 takes 115 us, not 112.)
 // BLK = true: row k = p*B + b of U is row b of the p-th worker's block (V likewise); a slice lies in one block because SLICE
 // divides B.
-template <class C, bool BLK>
+template <class C, bool BLK, bool ON_LINES>
 __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks)
 {
     constexpr int G = C::G, WN = C::WN, PV = C::PV;
@@ -407,79 +409,87 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
         if constexpr (G > 1) __syncthreads();
     }
 
-    if (M % 4 == 0) {
+    // Every half wavefront a row of the tile, straight from the registers: rows on lines, and rows on quads of tiles that groups
+    // share, whose launches are short (1000 -> 3001, K = 512 26.6 us; by way of LDS, below, 29.6).
+    if (ON_LINES || (G > 1 && M % 4 == 0)) {
         const int64_t mc = m0 + 4 * l32;
         constexpr int DEPTH = NR < 8 ? NR : 8;
-        auto update = [&](auto lines) {
-            constexpr bool STREAM = decltype(lines)::value;
 #pragma unroll
-            for (int q0 = 0; q0 < NR; q0 += DEPTH) {
-                float4 wv[DEPTH], mo[DEPTH];
+        for (int q0 = 0; q0 < NR; q0 += DEPTH) {
+            float4 wv[DEPTH], mo[DEPTH];
 #pragma unroll
-                for (int q = q0; q < q0 + DEPTH; ++q) {
-                    const int64_t n = n0 + first + 8 * (q >> 2) + (q & 3), off = n * M + mc;
-                    if (n >= N || mc >= M) continue;
-                    wv[q - q0] = STREAM ? load_stream4(g.W + off) : *reinterpret_cast<const float4*>(g.W + off);
-                    mo[q - q0] = STREAM ? load_stream4(g.Mom + off) : *reinterpret_cast<const float4*>(g.Mom + off);
-                }
+            for (int q = q0; q < q0 + DEPTH; ++q) {
+                const int64_t n = n0 + first + 8 * (q >> 2) + (q & 3), off = n * M + mc;
+                if (n >= N || mc >= M) continue;
+                wv[q - q0] = ON_LINES ? load_stream4(g.W + off) : *reinterpret_cast<const float4*>(g.W + off);
+                mo[q - q0] = ON_LINES ? load_stream4(g.Mom + off) : *reinterpret_cast<const float4*>(g.Mom + off);
+            }
 #pragma unroll
-                for (int q = q0; q < q0 + DEPTH; ++q) {
-                    const int64_t n = n0 + first + 8 * (q >> 2) + (q & 3), off = n * M + mc;
-                    if (n >= N || mc >= M) continue;
-                    float4 &x = wv[q - q0], &y = mo[q - q0];
-                    upd(d[q][0], x.x, y.x, g.lr, g.mu, g.wd);
-                    upd(d[q][1], x.y, y.y, g.lr, g.mu, g.wd);
-                    upd(d[q][2], x.z, y.z, g.lr, g.mu, g.wd);
-                    upd(d[q][3], x.w, y.w, g.lr, g.mu, g.wd);
-                    if constexpr (STREAM) {
-                        store_stream4(g.Mom + off, y);
-                        store_stream4(g.W + off, x);
-                    } else {
-                        *reinterpret_cast<float4*>(g.Mom + off) = y;
-                        *reinterpret_cast<float4*>(g.W + off) = x;
-                    }
+            for (int q = q0; q < q0 + DEPTH; ++q) {
+                const int64_t n = n0 + first + 8 * (q >> 2) + (q & 3), off = n * M + mc;
+                if (n >= N || mc >= M) continue;
+                float4 &x = wv[q - q0], &y = mo[q - q0];
+                upd(d[q][0], x.x, y.x, g.lr, g.mu, g.wd);
+                upd(d[q][1], x.y, y.y, g.lr, g.mu, g.wd);
+                upd(d[q][2], x.z, y.z, g.lr, g.mu, g.wd);
+                upd(d[q][3], x.w, y.w, g.lr, g.mu, g.wd);
+                if constexpr (ON_LINES) {
+                    store_stream4(g.Mom + off, y);
+                    store_stream4(g.W + off, x);
+                } else {
+                    *reinterpret_cast<float4*>(g.Mom + off) = y;
+                    *reinterpret_cast<float4*>(g.W + off) = x;
                 }
             }
-        };
-        if (M % 32 == 0 && ((reinterpret_cast<uintptr_t>(g.W) | reinterpret_cast<uintptr_t>(g.Mom)) & 127) == 0) update(std::true_type{});
-        else update(std::false_type{});
+        }
         return;
     }
-    // Rows that start anywhere: 64 of them at a time go through LDS and come back as whole lines of W (RowUpdate).  Where one group
-    // holds all 32 rows of a wavefront (PASSES = 2 and G = 1) a pass takes 16 of each.
+    // Rows that start anywhere: 64 of them at a time go through LDS and come back as whole lines of W, by InnerUpdate in tiles inside
+    // W, by RowUpdate in the others.  Where one group holds all 32 rows of a wavefront (PASSES = 2 and G = 1) a pass takes 16 of each.
+    // us with RowUpdate for all tiles and rows on quads as above -> now, K = 512: 3001 -> 8192 175.7 -> 168.0, 3000 -> 8192
+    // 177.4 -> 167.1, 3000 -> 21841 458 -> 436, 5506 -> 133 16.4 -> 15.7; 3001 -> 8192, K = 2048 508 -> 500.
     float* buf = reinterpret_cast<float*>(lds);
 #pragma unroll
     for (int pass = 0; pass < C::PASSES; ++pass) {
         auto row_n = [&](int r) { return n0 + (C::PASSES == 1 ? r : (r >> 4) * 32 + 16 * pass + (r & 15)); };
-        RowUpdate<64, C::TM, C::WAVES, 4, 1, decltype(row_n)> rows(g.W, g.Mom, row_n, m0, N, M, wave, lane);
-        rows.template fetch<0>();
-        if (pass > 0) __syncthreads();           // the rows before are no longer read
-        if (C::PASSES == 1 || G == 1 || 2 * group / G == pass) {
+        auto update = [&](auto rows) {
+            rows.template fetch<0>();
+            if (pass > 0) __syncthreads();       // the rows before are no longer read
+            if (C::PASSES == 1 || G == 1 || 2 * group / G == pass) {
 #pragma unroll
-            for (int q = 0; q < NR; ++q) {
-                if (C::PASSES == 2 && G == 1 && (q >> 3) != pass) continue;
-                const int in_wave = (32 / G) * group + 4 * lhi + 8 * (q >> 2) + (q & 3);      // 0 .. 31
-                const int r = C::PASSES == 1 ? 32 * w + in_wave : 16 * w + (in_wave & 15);
-                float* to = buf + r * rows.stride + 4 * l32 + line_shift(g.W, row_n(r), M);
+                for (int q = 0; q < NR; ++q) {
+                    if (C::PASSES == 2 && G == 1 && (q >> 3) != pass) continue;
+                    const int in_wave = (32 / G) * group + 4 * lhi + 8 * (q >> 2) + (q & 3);      // 0 .. 31
+                    const int r = C::PASSES == 1 ? 32 * w + in_wave : 16 * w + (in_wave & 15);
+                    float* to = buf + r * rows.stride + 4 * l32 + line_shift(g.W, row_n(r), M);
+                    if (G == 1 && M % 4 == 0) {  // shifts are multiples of 4: 16-byte LDS writes
+                        *reinterpret_cast<float4*>(to) = make_float4(d[q][0], d[q][1], d[q][2], d[q][3]);
+                    } else {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) to[j] = d[q][j];
+                        for (int j = 0; j < 4; ++j) to[j] = d[q][j];
+                    }
+                }
             }
-        }
-        __syncthreads();
-        rows.run(buf, g.lr, g.mu, g.wd);
+            __syncthreads();
+            rows.run(buf, g.lr, g.mu, g.wd);
+        };
+        if (n0 + C::TN <= N && m0 + C::TM <= M)
+            update(InnerUpdate<64, C::TM, C::WAVES, 4, false, decltype(row_n)>(g.W, g.Mom, row_n, m0, M, wave, lane));
+        else
+            update(RowUpdate<64, C::TM, C::WAVES, 4, 1, decltype(row_n)>(g.W, g.Mom, row_n, m0, N, M, wave, lane));
     }
 }
 
-template <class C>
+template <class C, bool ON_LINES>
 __global__ void __launch_bounds__(C::THREADS, 2) sfb_f32_planes_kernel(const Args g)
 {
-    tile_body<C, false>(g, nullptr);
+    tile_body<C, false, ON_LINES>(g, nullptr);
 }
 
-template <class C>
+template <class C, bool ON_LINES>
 __global__ void __launch_bounds__(C::THREADS, 2) sfb_f32_planes_blocks_kernel(const Args g, const BlockPtrs blocks)
 {
-    tile_body<C, true>(g, &blocks);
+    tile_body<C, true, ON_LINES>(g, &blocks);
 }
 
 template <class C>
@@ -492,15 +502,21 @@ psd_status start(Args& g, const BlockPtrs* blocks, hipStream_t st)
     // raise the dynamic LDS limit once per process (idempotent, so a race between two first callers is harmless)
     static std::atomic<bool> attr_done{false};
     if (!attr_done.load(std::memory_order_acquire)) {
-        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_f32_planes_kernel<C>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
-        PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_f32_planes_blocks_kernel<C>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
+        for (auto k : {sfb_f32_planes_kernel<C, false>, sfb_f32_planes_kernel<C, true>})
+            PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
+        for (auto k : {sfb_f32_planes_blocks_kernel<C, false>, sfb_f32_planes_blocks_kernel<C, true>})
+            PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
         attr_done.store(true, std::memory_order_release);
     }
     const dim3 grid(static_cast<uint32_t>(tiles));
-    if (blocks) hipLaunchKernelGGL(sfb_f32_planes_blocks_kernel<C>, grid, dim3(C::THREADS), C::LDS_BYTES, st, g, *blocks);
-    else hipLaunchKernelGGL(sfb_f32_planes_kernel<C>, grid, dim3(C::THREADS), C::LDS_BYTES, st, g);
+    const bool lines = g.M % 32 == 0 && ((reinterpret_cast<uintptr_t>(g.W) | reinterpret_cast<uintptr_t>(g.Mom)) & 127) == 0;
+    if (blocks) {
+        auto kern = lines ? sfb_f32_planes_blocks_kernel<C, true> : sfb_f32_planes_blocks_kernel<C, false>;
+        hipLaunchKernelGGL(kern, grid, dim3(C::THREADS), C::LDS_BYTES, st, g, *blocks);
+    } else {
+        auto kern = lines ? sfb_f32_planes_kernel<C, true> : sfb_f32_planes_kernel<C, false>;
+        hipLaunchKernelGGL(kern, grid, dim3(C::THREADS), C::LDS_BYTES, st, g);
+    }
     PSD_HIP_TRY(hipGetLastError());
     return PSD_OK;
 }

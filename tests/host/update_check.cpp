@@ -110,6 +110,7 @@ template <class R> struct Bf16w192 { using type = psd::RowUpdate<64, 192, 4, 5, 
 template <class R> struct Bf16h128 { using type = psd::RowUpdate<64, 128, 4, 4, 1, R>; };
 template <class R> struct Bf16Two { using type = psd::RowUpdate<64, 128, 8, 5, 2, R>; };
 template <class R> struct Inner128 { using type = psd::InnerUpdate<64, 128, 4, 4, false, R>; };
+template <class R> struct Inner128w8 { using type = psd::InnerUpdate<64, 128, 8, 4, false, R>; };
 template <class R> struct Inner64 { using type = psd::InnerUpdate<64, 64, 4, 4, false, R>; };
 template <class R> struct Inner256 { using type = psd::InnerUpdate<64, 256, 4, 8, false, R>; };
 template <class R> struct Inner192 { using type = psd::InnerUpdate<64, 192, 4, 6, false, R>; };
@@ -135,6 +136,7 @@ int main()
                 ok = ok && layer<Bf16Two, 64, 128, 8, 2, 2, false, false>(N, M, lead, "bf16, two groups, 128 x 128");
             }
             ok = ok && layer<Inner128, 64, 128, 4, 1, 2, true, true>(133, M, lead, "fp32, inside, 128 x 128");
+            ok = ok && layer<Inner128w8, 64, 128, 8, 1, 1, false, true>(133, M, lead, "planes, inside, two groups");
             ok = ok && layer<Inner64, 64, 64, 4, 1, 1, true, true>(133, M, lead, "fp32, inside, 64 x 64");
             ok = ok && layer<Inner256, 64, 256, 4, 1, 2, false, true>(133, M, lead, "bf16, inside, 128 x 256");
             ok = ok && layer<Inner192, 64, 192, 4, 1, 2, false, true>(133, M, lead, "bf16, inside, 128 x 192");
