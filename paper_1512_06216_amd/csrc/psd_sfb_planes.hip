@@ -411,24 +411,33 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
 
     // Every half wavefront a row of the tile, straight from the registers: rows on lines, and rows on quads of tiles that groups
     // share, whose launches are short (1000 -> 3001, K = 512 26.6 us; by way of LDS, below, 29.6).
+    // The next eight rows of a lane are on their way while the present ones are updated: 4096 -> 4096, K = 256 83.3 -> 78.3 us,
+    // 9216 -> 4096, K = 512 240 -> 231, 21760 -> 1344, K = 256 151 -> 137, 4096 -> 4096, K = 2048 330 -> 326 (four at a time 2-4 %
+    // slower than before; all sixteen at once as eight).
     if (ON_LINES || (G > 1 && M % 4 == 0)) {
         const int64_t mc = m0 + 4 * l32;
-        constexpr int DEPTH = NR < 8 ? NR : 8;
+        constexpr int DEPTH = NR < 8 ? NR : 8, BATCHES = NR / DEPTH;
+        float4 wv[2][DEPTH], mo[2][DEPTH];
+        auto get = [&](int t) {
 #pragma unroll
-        for (int q0 = 0; q0 < NR; q0 += DEPTH) {
-            float4 wv[DEPTH], mo[DEPTH];
-#pragma unroll
-            for (int q = q0; q < q0 + DEPTH; ++q) {
+            for (int i = 0; i < DEPTH; ++i) {
+                const int q = t * DEPTH + i;
                 const int64_t n = n0 + first + 8 * (q >> 2) + (q & 3), off = n * M + mc;
                 if (n >= N || mc >= M) continue;
-                wv[q - q0] = ON_LINES ? load_stream4(g.W + off) : *reinterpret_cast<const float4*>(g.W + off);
-                mo[q - q0] = ON_LINES ? load_stream4(g.Mom + off) : *reinterpret_cast<const float4*>(g.Mom + off);
+                wv[t & 1][i] = ON_LINES ? load_stream4(g.W + off) : *reinterpret_cast<const float4*>(g.W + off);
+                mo[t & 1][i] = ON_LINES ? load_stream4(g.Mom + off) : *reinterpret_cast<const float4*>(g.Mom + off);
             }
+        };
+        get(0);
 #pragma unroll
-            for (int q = q0; q < q0 + DEPTH; ++q) {
+        for (int t = 0; t < BATCHES; ++t) {
+            if (t + 1 < BATCHES) get(t + 1);
+#pragma unroll
+            for (int i = 0; i < DEPTH; ++i) {
+                const int q = t * DEPTH + i;
                 const int64_t n = n0 + first + 8 * (q >> 2) + (q & 3), off = n * M + mc;
                 if (n >= N || mc >= M) continue;
-                float4 &x = wv[q - q0], &y = mo[q - q0];
+                float4 &x = wv[t & 1][i], &y = mo[t & 1][i];
                 upd(d[q][0], x.x, y.x, g.lr, g.mu, g.wd);
                 upd(d[q][1], x.y, y.y, g.lr, g.mu, g.wd);
                 upd(d[q][2], x.z, y.z, g.lr, g.mu, g.wd);
