@@ -217,7 +217,14 @@ inline double launch_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K, in
     // 128 x 192 that it gets fill the compute units one and a third times, which the cost of that tile counts as less than it is.
     const bool off_lines = M % 32 != 0;
     const double torn = off_lines && t.id == 4 && share > 4 && M < 8 * N ? 0.7 * share : off_lines && t.id == 2 && share > 2 ? 2 * share : 0;
-    return 5 + update * (share + tail) + torn + t.loop * k * rounds;
+    // On lines the 128 x 128 tile gained most when tiles inside W got an update of their own, and the 128 x 256 tile least.  us with
+    // the tile chosen before and with what they cost since then counted: 4096 -> 4096, K = 512 61.1 and 54.7, K = 1024 73.8 and
+    // 64.1; 16384 -> 2048, K = 1024 152 and 132; 8192 -> 4096, K = 1024 140 and 131; of 40 such
+    // layers 30 are faster, by 4 % on average, 4 slower, by 2 to 6 % (23712 -> 484, K = 280 39.5 and 42.0).  Whole steps of AlexNet: K = 256 285
+    // and 266, K = 512 305 and 289, K = 1024 337 and 328.  With longer sums a lone layer still gains (4096 -> 6144, K = 2048 142 and
+    // 133), but the larger tile reads less from L2, and a step is bound by power: AlexNet, K = 1536 381 and 386, K = 2048 432 and 455.
+    const double since = !off_lines && K >= 256 && K <= 1024 ? (t.id == 0 ? 1.06 : t.id == 2 ? 0.96 : 1) : 1;
+    return (5 + update * (share + tail) + torn + t.loop * k * rounds) * since;
 }
 
 // ... and when `splits` workgroups per tile store partial sums that a second launch adds up
