@@ -43,8 +43,8 @@ inline bool factors_in_reach(int64_t K, int64_t ldu, int64_t ldv, int64_t bytes,
 // one stage, 32 rows where two groups contract a tile.  96 rows is what the kernels of all tile sizes have always been given.
 constexpr int64_t kF32Reserve = 96;
 
-// The bf16 kernels add the row to every offset: the stages they request past the last row, up to `stages` - 1 of `rows` rows, and
-// its rounding up to whole stages have to fit as well.  One more stage for all of them, whatever the depth of the ring, so that
+// The bf16 kernels add the row to every offset: the stages they request past the last row, up to `stages` of `rows` rows, and
+// its rounding up to whole stages have to fit as well.  The same for all of them, whatever the depth of the ring, so that
 // the choice of the tile does not decide what is accepted; the long stages of grouped tiles fall back to a plain tile.
 constexpr int64_t kBf16Stages = 4, kBf16StageRows = 32;
 constexpr int64_t bf16_reserve(int64_t rows) { return (kBf16Stages + 1) * rows; }

@@ -3,14 +3,20 @@
 //     dW[n][m] = sum_k U[k][n] * V[k][m] ;  Mom = mu*Mom + lr*dW ;  W = W - Mom
 //
 // Layout problem.  The contraction index k is the OUTER dimension of both stacked factor
-// matrices, while v_mfma_f32_32x32x16_bf16 wants 8 consecutive k in one lane.  Tiles are
+// matrices, while v_mfma_f32_16x16x32_bf16 wants 8 consecutive k in one lane.  Tiles are
 // copied to LDS as they are (K-outer, 16-byte chunks) and read back with gfx950's
 // transposing LDS load (ds_read_b64_tr_b16): a 16-lane group reads four k rows x 16 columns
 // and each lane ends up with the 4 k values of its own column.
 //
+// Which MFMA.  Both bf16 shapes do the same flops in a clock, but long launches are bound by power, and 16 x 16 x 32 takes less of
+// it: 64 x 128 per wavefront, random operands, two workgroups per compute unit: operands from registers 1.79 PFLOP/s with
+// 32 x 32 x 16 and 2.04 with 16 x 16 x 32, read from LDS for every step 1.58 and 1.72.  Tiles of 64 x 64 are too short for that to
+// count and keep 32 x 32 x 16, whose operand reads fall evenly on the two halves of a stage (1024 -> 1000, K = 256 6.1 us and 6.3,
+// 4237 -> 256, K = 3072 27.2 and 27.5).
+//
 // Feeding the MFMA pipe.  One k-stage of MFMA work (~0.4 us) is much shorter than a loaded
 // L2/HBM round trip (>1 us at the tail), so the tiles travel global -> LDS without passing
-// through registers (buffer_load_dwordx4 ... lds) and NSTAGE-1 stages are kept in flight in
+// through registers (buffer_load_dwordx4 ... lds) and up to NSTAGE stages are in flight or read from in
 // an NSTAGE-deep ring of LDS buffers.  The DMA writes whole 1 KiB runs, so rows cannot be
 // padded; bank conflicts of the transposing reads are avoided by XOR-swizzling the 16-byte
 // chunk index of a row with its row number instead.  Rows past the end of K are zero-filled
@@ -27,16 +33,17 @@
 namespace psd {
 namespace {
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
-constexpr int SLICE = kBf16StageRows;   // k rows of a stage that one group of wavefronts contracts (two MFMA k-steps of 16)
+constexpr int SLICE = kBf16StageRows;   // k rows of a stage that one group of wavefronts contracts 
 constexpr int GROUP_N = 8;     // tile rows per raster group (L2 reuse of the V panels)
 constexpr int PLD = 36;        // epilogue patch row stride in floats (144 B: conflict-free)
 
-// WN x WM wavefronts, each owning BN x BM MFMA blocks of 32 x 32; NSTAGE LDS buffers;
+// WN x WM wavefronts, each owning 32 BN x 32 BM of the tile; NSTAGE LDS buffers;
 // OCC = wavefronts per SIMD the register budget is sized for
 // G > 1: that many groups of WN x WM wavefronts own the same tile; a stage holds G slices of k rows, one for each
 // group, and the groups' accumulators are added up in LDS before the update.  CH > 1: every group keeps that many sets of
@@ -46,6 +53,8 @@ struct Cfg {
     static constexpr int WN = WN_, WM = WM_, BN = BN_, BM = BM_, NSTAGE = NSTAGE_, OCC = OCC_, G = G_, CH = CH_;
     static constexpr int WAVES = WN * WM * G, THREADS = 64 * WAVES, KT = SLICE * G;
     static constexpr int TN = 32 * BN * WN, TM = 32 * BM * WM;   // workgroup tile
+    static constexpr bool SQUARES = BM == 1;                     // MFMA blocks of 32 x 32, 16 k rows each (16 x 16 and 32 otherwise)
+    static constexpr int F = SQUARES ? 32 : 16, FN = 32 * BN / F, FM = 32 * BM / F;      // a wavefront's MFMA blocks
     static constexpr int RA = TN * 2, RB = TM * 2;               // LDS row bytes (U tile, V tile)
     static constexpr int A_BYTES = KT * RA, B_BYTES = KT * RB, STAGE_BYTES = A_BYTES + B_BYTES;
     static constexpr int NI_A = A_BYTES / 1024 / WAVES;          // 1 KiB DMA instructions per wavefront
@@ -183,12 +192,16 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
     auto issue = [&](int t) {                    // stage t -> ring buffer t % NSTAGE (stages are requested in order)
         const uint32_t base = lds0 + static_cast<uint32_t>(t % C::NSTAGE) * C::STAGE_BYTES;
         const uint32_t row = static_cast<uint32_t>(BLK ? row_in_blk : t * KT);
+        uint32_t skip_a = row * row_a, skip_b = row * row_b;
+        // Added to the lanes' offsets here, not carried along in registers of their own: the 128 x 256 tile has none to spare.  (And
+        // stage_base likewise; the 64 x 64 tiles have, and lose 0.1 us with it.)
+        if constexpr (!C::SQUARES) asm("" : "+s"(skip_a), "+s"(skip_b));
 #pragma unroll
         for (int j = 0; j < C::NI_A; ++j)
-            dma_b128(base + (wave * C::NI_A + j) * 1024, voff_a[j] + row * row_a, rsrc_u);
+            dma_b128(base + (wave * C::NI_A + j) * 1024, voff_a[j] + skip_a, rsrc_u);
 #pragma unroll
         for (int j = 0; j < C::NI_B; ++j)
-            dma_b128(base + C::A_BYTES + (wave * C::NI_B + j) * 1024, voff_b[j] + row * row_b, rsrc_v);
+            dma_b128(base + C::A_BYTES + (wave * C::NI_B + j) * 1024, voff_b[j] + skip_b, rsrc_v);
         if constexpr (BLK) {
             row_in_blk += KT;
             if (row_in_blk >= block_rows) aim_block();
@@ -197,119 +210,153 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
 
     // ---- transposing-read plan.  A 16-lane group reads a (4 k) x (16 column) patch: lane L
     // supplies the address of 4 adjacent columns of row (L%16)/4 starting at column 4*(L%4), and
-    // ends up with rows 0..3 of column L%16.  Lane groups: columns +16*(grp%2), k rows +8*(grp/2).
-    // The byte address of this lane's piece inside a stage buffer, for k-step 0, low half:
-    uint32_t rd_a[C::BN], rd_b[C::BM];
+    // ends up with rows 0..3 of column L%16.  Blocks of 16 columns: lane group g takes k rows 8*g .. 8*g + 7 of a slice, in two
+    // reads; of 32 columns: columns 16*(g%2) .., k rows 8*(g/2) .. of half a slice.
+    // The byte address of this lane's piece inside a stage buffer, first read; columns that lie 64 apart are 128 bytes
+    // apart in LDS (the swizzle permutes inside 128 bytes).
+    constexpr int APART = 64 / C::F, RN = C::FN < APART ? C::FN : APART, RM = C::FM < APART ? C::FM : APART;
+    uint32_t rd_a[RN], rd_b[RM];
     {
-        const int row = group * SLICE + 8 * (grp >> 1) + (l16 >> 2);           // row & 3 == l16 >> 2
+        const int kg = C::SQUARES ? grp >> 1 : grp, column = C::SQUARES ? 16 * (grp & 1) : 0;
+        const int row = group * SLICE + 8 * kg + (l16 >> 2);                   // row & 3 == l16 >> 2
         const int sw = (l16 >> 2) << 1;
 #pragma unroll
-        for (int bn = 0; bn < C::BN; ++bn) {
-            const int chunk = (((wn0 + 32 * bn + 16 * (grp & 1)) >> 3) ^ sw) + ((l16 & 3) >> 1);
-            rd_a[bn] = static_cast<uint32_t>(row * C::RA + chunk * 16 + (l16 & 1) * 8);
+        for (int i = 0; i < RN; ++i) {
+            const int chunk = (((wn0 + C::F * i + column) >> 3) ^ sw) + ((l16 & 3) >> 1);
+            rd_a[i] = static_cast<uint32_t>(row * C::RA + chunk * 16 + (l16 & 1) * 8);
         }
 #pragma unroll
-        for (int bm = 0; bm < C::BM; ++bm) {
-            const int chunk = (((wm0 + 32 * bm + 16 * (grp & 1)) >> 3) ^ sw) + ((l16 & 3) >> 1);
-            rd_b[bm] = static_cast<uint32_t>(C::A_BYTES + row * C::RB + chunk * 16 + (l16 & 1) * 8);
+        for (int i = 0; i < RM; ++i) {
+            const int chunk = (((wm0 + C::F * i + column) >> 3) ^ sw) + ((l16 & 3) >> 1);
+            rd_b[i] = static_cast<uint32_t>(C::A_BYTES + row * C::RB + chunk * 16 + (l16 & 1) * 8);
         }
     }
 
-    f32x16 chain[C::CH][C::BN][C::BM];
+    typedef std::conditional_t<C::SQUARES, f32x16, f32x4> Block;
+    typedef Block Sums[C::FN][C::FM];
+    Sums chain[C::CH];
 #pragma unroll
     for (int i = 0; i < C::CH; ++i)
 #pragma unroll
-        for (int a = 0; a < C::BN; ++a)
+        for (int a = 0; a < C::FN; ++a)
 #pragma unroll
-            for (int c = 0; c < C::BM; ++c)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) chain[i][a][c][r] = 0.f;
+            for (int c = 0; c < C::FM; ++c) chain[i][a][c] = Block(0.f);
 
-    // this lane's 8 k values of a 16-row MFMA step: ks + 8*(grp/2) + 0..7 (the same for both operands)
-    auto load_frags = [&](uint32_t base, int ks, bf16x8 (&a)[C::BN], bf16x8 (&bb)[C::BM]) {
+    // this lane's 8 k values of an MFMA step (the same for both operands)
+    auto frag = [&](uint32_t at, int row_bytes) {
+        const bf16x4 lo = read_tr(at);
+        const bf16x4 hi = read_tr(at + 4 * row_bytes);
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+    // blocks of the wavefront's rows n (columns m) from the `first` on, k rows from ks on
+    auto load_n = [&](uint32_t base, int ks, auto& a) {
 #pragma unroll
-        for (int bn = 0; bn < C::BN; ++bn) {
-            const bf16x4 lo = read_tr(base + rd_a[bn] + ks * C::RA);
-            const bf16x4 hi = read_tr(base + rd_a[bn] + (ks + 4) * C::RA);
-            a[bn] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        }
+        for (int i = 0; i < C::FN; ++i) a[i] = frag(base + rd_a[i % APART] + (i / APART) * 128 + ks * C::RA, C::RA);
+    };
+    auto load_m = [&](uint32_t base, int ks, int first, auto& b) {
 #pragma unroll
-        for (int bm = 0; bm < C::BM; ++bm) {
-            const bf16x4 lo = read_tr(base + rd_b[bm] + ks * C::RB);
-            const bf16x4 hi = read_tr(base + rd_b[bm] + (ks + 4) * C::RB);
-            bb[bm] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        }
+        for (int i = 0; i < C::BM; ++i) b[i] = frag(base + rd_b[(first + i) % APART] + ((first + i) / APART) * 128 + ks * C::RB, C::RB);
     };
     // rows of the MFMA block = m (V operand), columns = n (U operand)
-    auto mma = [&](const bf16x8 (&a)[C::BN], const bf16x8 (&bb)[C::BM], f32x16 (&acc)[C::BN][C::BM]) {
+    auto mma = [&](const auto& a, const auto& b, int first, Sums& acc) {
 #pragma unroll
-        for (int bn = 0; bn < C::BN; ++bn)
+        for (int c = 0; c < C::BM; ++c)
 #pragma unroll
-            for (int bm = 0; bm < C::BM; ++bm)
-                acc[bn][bm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[bm], a[bn], acc[bn][bm], 0, 0, 0);
+            for (int i = 0; i < C::FN; ++i) {
+                if constexpr (C::SQUARES) acc[i][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[c], a[i], acc[i][c], 0, 0, 0);
+                else acc[i][first + c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[c], a[i], acc[i][first + c], 0, 0, 0);
+            }
     };
 
     const int steps = k_end > k_begin ? (k_end - k_begin + KT - 1) / KT : 0;
     constexpr int LPS = C::NI_A + C::NI_B;       // DMA instructions per wavefront per stage
-    auto stage_base = [&](int t) { return lds0 + static_cast<uint32_t>(t % C::NSTAGE) * C::STAGE_BYTES; };
+    auto stage_base = [&](int t) {
+        uint32_t at = lds0 + static_cast<uint32_t>(t % C::NSTAGE) * C::STAGE_BYTES;
+        if constexpr (!C::SQUARES) asm("" : "+s"(at));
+        return at;
+    };
 
-    // Software pipeline (one wavefront may be alone on its SIMD, so it has to overlap with itself):
-    // the operand reads of one MFMA step are always issued before the MFMAs of the step before,
-    // also across the stage boundary, and the barrier sits between the two steps of a stage.
-    //   F0 = step 0 of stage t (read during the previous iteration)
-    //   read F1 = step 1 of stage t | MFMA(F0) | stage t+1 landed? barrier | DMA stage t+NSTAGE-1 |
-    //   read F0 = step 0 of stage t+1 | MFMA(F1)
-    // The barrier tells both that every wavefront's share of stage t+1 is visible and that nobody
-    // still reads stage t-1, whose buffer the new DMA overwrites.  Stages past K are zeros.
-    bf16x8 a0[C::BN], b0[C::BM], a1[C::BN], b1[C::BM];
+    // Software pipeline (one wavefront may be alone on its SIMD, so it has to overlap with itself): a stage is contracted in two
+    // parts, halves of the columns m (blocks of 32 x 32: halves of the k rows); the operand reads of one part are always issued
+    // before the MFMAs of the part before, also across the stage boundary, and the barrier sits between the two.
+    //   read b1 = second half of stage t | MFMA(a, b0) | stage t+1 landed? barrier | DMA stage t+NSTAGE |
+    //   read the other a and b0 = first half of stage t+1 | MFMA(a, b1)
+    // The barrier tells both that every wavefront's share of stage t+1 is visible and that all of them have read the whole of stage
+    // t into registers (lgkmcnt), so that the new DMA may overwrite it.  Stages past K are zeros.
+    // us, K = 2048, before (32 x 32 x 16, and the buffer of stage t kept until the next barrier, one stage less in flight) -> now:
+    // 4096 -> 21841 456-470 -> 450-460, 25088 -> 4096 516-533 -> 511-528, 3000 -> 21841 365 -> 360, 4096 -> 6144 143 -> 130,
+    // 9216 -> 4096, K = 4096 318-326 -> 315-318; small ones by the stage more in flight: 512 -> 512, K = 4096 (split) 12.6 -> 11.2,
+    // 4237 -> 256, K = 3072 27.2 -> 26.6.  Branches that leave out the stages past K cost large layers 2 %.  Waves of 96 x 96 (tiles of
+    // 192 x 192: 11 % less LDS and L1 traffic) are no faster than 64 x 128 (431 and 432 for 4096 -> 21841).
+    bf16x8 a0[C::FN], a1[C::FN], b0[C::BM], b1[C::BM];
 #pragma unroll
-    for (int t = 0; t < C::NSTAGE - 1; ++t) issue(t);
-    wait_vmcnt<(C::NSTAGE - 2) * LPS>();
+    for (int t = 0; t < C::NSTAGE; ++t) issue(t);
+    wait_vmcnt<(C::NSTAGE - 1) * LPS>();
     __syncthreads();
-    load_frags(stage_base(0), 0, a0, b0);
-    // A wavefront issues at most one LDS instruction per ~16 cycles and one MFMA per 32, in program
-    // order; operand reads are therefore interleaved with the MFMAs they do not feed, two after each
+    load_n(stage_base(0), 0, a0);
+    load_m(stage_base(0), 0, 0, b0);
+    // A wavefront issues at most one LDS instruction per ~16 cycles and one MFMA per 16 (32 x 32: 32), in program
+    // order; operand reads are therefore interleaved with the MFMAs they do not feed, one (32 x 32: two) after each
     // of the first ones, so that their issue time hides under MFMA execution and the last of them is
-    // back before it is waited for (spread evenly to the end: 1-2 % slower).
-    auto interleave = [&]() { interleave_groups<2 * (C::BN + C::BM), C::BN * C::BM, 2>(); };
-    auto stage = [&](int t, f32x16 (&acc)[C::BN][C::BM]) {
-        load_frags(stage_base(t), 16, a1, b1);
-        mma(a0, b0, acc);
-        interleave();
-        __builtin_amdgcn_sched_barrier(0);
-        wait_vmcnt<(C::NSTAGE - 3) * LPS>();
+    // back before it is waited for (16 x 16, two after each: 9216 -> 4096 1-3 % slower).
+    auto next_stage = [&](int t) {
+        wait_vmcnt<(C::NSTAGE - 2) * LPS>();
+        asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
         __syncthreads();
-        issue(t + C::NSTAGE - 1);
-        load_frags(stage_base(t + 1), 0, a0, b0);
-        mma(a1, b1, acc);
-        interleave();
+        issue(t + C::NSTAGE);
+    };
+    auto stage = [&](int t, Sums& acc, auto& a, auto& next) {
+        if constexpr (C::SQUARES) {
+            load_n(stage_base(t), 16, next);
+            load_m(stage_base(t), 16, 0, b1);
+        } else {
+            load_m(stage_base(t), 0, C::BM, b1);
+        }
+        mma(a, b0, 0, acc);
+        interleave_groups<2 * (C::SQUARES ? C::FN + C::BM : C::BM), C::FN * C::BM, C::SQUARES ? 2 : 1>();
+        __builtin_amdgcn_sched_barrier(0);
+        next_stage(t);
+        load_n(stage_base(t + 1), 0, C::SQUARES ? a : next);
+        load_m(stage_base(t + 1), 0, 0, b0);
+        mma(C::SQUARES ? next : a, b1, C::BM, acc);
+        interleave_groups<2 * (C::FN + C::BM), C::FN * C::BM, C::SQUARES ? 2 : 1>();
         __builtin_amdgcn_sched_barrier(0);
     };
     static_assert(C::CH <= 2, "stages come singly or in pairs");
-    if constexpr (C::CH == 1) {
-        for (int t = 0; t < steps; ++t) stage(t, chain[0]);
-    } else {
-        int t = 0;
+    constexpr bool PAIRS = !C::SQUARES || C::CH == 2;
+    int t = 0;
+    if constexpr (PAIRS) {
         for (; t + 1 < steps; t += 2) {
-            stage(t, chain[0]);
-            stage(t + 1, chain[1]);
+            stage(t, chain[0], a0, a1);
+            stage(t + 1, chain[C::CH - 1], C::SQUARES ? a0 : a1, C::SQUARES ? a1 : a0);
         }
-        if (t < steps) stage(t, chain[0]);
+        if (t < steps) stage(t, chain[0], a0, a1);
+    } else {
+        for (; t < steps; ++t) stage(t, chain[0], a0, a1);
     }
     wait_vmcnt<0>();                             // trailing zero stages must not land on the epilogue patch
     __syncthreads();
-    f32x16 (&acc)[C::BN][C::BM] = chain[0];
+    Sums& acc = chain[0];
     if constexpr (C::CH == 2)
 #pragma unroll
-        for (int a = 0; a < C::BN; ++a)
+        for (int a = 0; a < C::FN; ++a)
 #pragma unroll
-            for (int c = 0; c < C::BM; ++c)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[a][c][r] += chain[1][a][c][r];
+            for (int c = 0; c < C::FM; ++c) acc[a][c] += chain[1][a][c];
 
-    // Epilogue.  Accumulator register r of block (bn, bm) holds MFMA row 8*(r/4) + 4*(lane/32) + r%4
-    // (= m offset) and column lane%32 (= n offset): four adjacent m per register quad.
-    const int l32 = lane & 31, lhi = lane >> 5;
+    // Epilogue.  An MFMA block's accumulators hold 4 adjacent m of a row n: 16 x 16: rows 4*(lane/16) .. + 3 (= m offset) of column
+    // lane%16 (= n offset); 32 x 32: register r row 8*(r/4) + 4*(lane/32) + r%4 of column lane%32.
+    // Quad q of the 32 x 32 weights (bn, bm): its values, and the places of its n and m.
+    auto quad = [&](int bn, int bm, int q) {
+        if constexpr (C::SQUARES) {
+            const f32x16& x = acc[bn][bm];
+            return make_float4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]);
+        } else {
+            const f32x4& x = acc[2 * bn + (q >> 1)][2 * bm + (q & 1)];
+            return make_float4(x[0], x[1], x[2], x[3]);
+        }
+    };
+    auto quad_n = [&](int q) { return C::SQUARES ? lane & 31 : 16 * (q >> 1) + l16; };
+    auto quad_m = [&](int q) { return C::SQUARES ? 8 * q + 4 * (lane >> 5) : 16 * (q & 1) + 4 * grp; };
     if constexpr (PART) {
         // Each 32 x 32 block is turned through a private LDS patch, as below: 128 contiguous bytes of a row per access instead of
         // 32, or, where rows are no multiples of 16 bytes, instead of single elements: 4160 -> 196, K = 4096 25.9 -> 25.2 us,
@@ -323,8 +370,7 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
             for (int bm = 0; bm < C::BM; ++bm) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<float4*>(patch + l32 * PLD + 8 * q + 4 * lhi) =
-                        make_float4(acc[bn][bm][4 * q], acc[bn][bm][4 * q + 1], acc[bn][bm][4 * q + 2], acc[bn][bm][4 * q + 3]);
+                    *reinterpret_cast<float4*>(patch + quad_n(q) * PLD + quad_m(q)) = quad(bn, bm, q);
                 const int64_t m = m0 + wm0 + 32 * bm + pcol;
                 float* const to = part + split * part_stride + m;
                 if (quads) {
@@ -357,9 +403,7 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
             for (int bm = 0; bm < C::BM; ++bm) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<float4*>(patch + l32 * PLD + 8 * q + 4 * lhi) =
-                        make_float4(acc[bn][bm][4 * q], acc[bn][bm][4 * q + 1], acc[bn][bm][4 * q + 2],
-                                    acc[bn][bm][4 * q + 3]);
+                    *reinterpret_cast<float4*>(patch + quad_n(q) * PLD + quad_m(q)) = quad(bn, bm, q);
                 float4 d[4], w[4], mo[4];
                 const int64_t m = m0 + wm0 + 32 * bm + pcol;
 #pragma unroll
@@ -406,18 +450,20 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
             auto update = [&](auto rows) {
                 rows.template fetch<0>();
                 if (bn > 0) __syncthreads();       // the rows before are no longer read
-                const int r = (wg / C::WM) * 32 + l32;
-                float* to = buf + (group * C::ROWS + r) * rows.stride + wm0 + 4 * lhi + (SHIFTED ? line_shift(W, row_n(r), M) : 0);
+                // (rows 16 apart start 16 M elements apart)
+                const int r = (wg / C::WM) * 32 + quad_n(0), shift = SHIFTED ? line_shift(W, row_n(r), M) : 0;
+                float* const top = buf + (group * C::ROWS + r) * rows.stride + wm0;
 #pragma unroll
                 for (int bm = 0; bm < C::BM; ++bm)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const f32x16& a = acc[bn][bm];
+                        const bool below = !C::SQUARES && q >= 2;
+                        float* to = top + 32 * bm + quad_m(q) + (below ? 16 * rows.stride + (SHIFTED ? shift ^ (M & 1) << 4 : 0) : shift);
+                        const float4 x = quad(bn, bm, q);
                         if (!SHIFTED || M % 4 == 0) {          // shifts are multiples of 4: 16-byte LDS writes
-                            *reinterpret_cast<float4*>(to + 32 * bm + 8 * q) = make_float4(a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]);
+                            *reinterpret_cast<float4*>(to) = x;
                         } else {
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) to[32 * bm + 8 * q + i] = a[4 * q + i];
+                            to[0] = x.x; to[1] = x.y; to[2] = x.z; to[3] = x.w;
                         }
                     }
                 __syncthreads();
