@@ -274,19 +274,6 @@ inline Bf16Tile choose_bf16_split(int64_t N, int64_t M, int64_t K, int most, int
     return best;
 }
 
-// How the update of a layer whose rows start on cache lines is applied by the 128 x 256 tile (others have no choice): by each
-// wavefront for itself, in patches of LDS, or in whole rows of the tile.  Whole rows are faster where tiles follow each other
-// on a compute unit, but for sums so long that every workgroup is in its loop at the same time, and with all tiles in one go, a
-// deeper queue of loads holds up the loops that are still running.  us in rows and in patches, on 256 compute units: 4096 -> 4096
-// (512 tiles), K = 2048 101.5 and 94.5, K = 1024 75.2 and 73.8; 8192 -> 2048, K = 2048 107 and 97.5; 4352 -> 3840 (510 tiles),
-// K = 2048 100.5 and 98.8, K = 512 63.7 and 68.3; 2304 -> 7168 (504), K = 1024 75.2 and 77.0; with more tiles 6400 -> 8767,
-// K = 180 186 and 195, 8576 -> 1431, K = 936 59.7 and 62.6, 4768 -> 3243, K = 320 58.0 and 61.7, 4096 -> 8192, K = 1024 133 and 139.
-constexpr int64_t kPatchRows = 1024;
-inline bool bf16_patches(int64_t N, int64_t M, int64_t K, int64_t tn, int64_t tm, int64_t cus)
-{
-    return K >= kPatchRows && ((N + tn - 1) / tn) * ((M + tm - 1) / tm) <= 2 * cus;
-}
-
 // Does the 64 x 128 tile apply the update of all tiles as at the edges of W (RowUpdate), where rows are not even on quads: with two
 // tiles for each compute unit at most the code for the tiles inside (InnerUpdate) costs more than it saves.  us with and without
 // it: 20281 -> 187, K = 352 (477 tiles) 17.6 and 15.7; 3523 -> 891, K = 92 (392) 15.4 and 13.8; 615 -> 2216, K = 32 (175) 9.0 and

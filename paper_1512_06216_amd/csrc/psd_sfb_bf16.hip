@@ -61,8 +61,7 @@ struct Cfg {
     static constexpr int NI_B = B_BYTES / 1024 / WAVES;
     static constexpr int PATCH_BYTES = WAVES * 32 * PLD * 4;
     static constexpr int ROWS = 32 * WN;                         // rows in the buffer of the update (RowUpdate, InnerUpdate)
-    static constexpr bool PATCHES = BM == 4 && G == 1;           // may it run ON_LINES_AT_ONCE
-    static constexpr bool FEW = BN == 1 && BM == 2 && G == 1;    // ... and ANYWHERE_FEW
+    static constexpr bool FEW = BN == 1 && BM == 2 && G == 1;    // may it run ANYWHERE_FEW
     static constexpr size_t larger(size_t a, size_t b) { return a > b ? a : b; }
     static constexpr size_t LDS_BYTES = larger(size_t(NSTAGE) * STAGE_BYTES, PATCH_BYTES);
     static constexpr size_t LDS_BYTES_ROWS = larger(LDS_BYTES, size_t(G) * ROWS * row_stride(TM, 0) * 4);
@@ -89,8 +88,8 @@ __device__ __forceinline__ bf16x4 read_tr(uint32_t lds_addr)
 struct BlockPtrs { const uint16_t* u[PSD_MAX_WORKERS]; const uint16_t* v[PSD_MAX_WORKERS]; };
 
 // Where the rows of W and Mom start, and with it how the update reaches them (see the epilogue): anywhere in a cache line, in a
-// launch of few tiles (bf16_few_tiles in psd_rules.h) or not; on lines, in a launch whose tiles all run at once (bf16_patches) or not.
-enum Rows { ANYWHERE, ANYWHERE_FEW, ON_LINES, ON_LINES_AT_ONCE };
+// launch of few tiles (bf16_few_tiles in psd_rules.h) or not, or on lines.
+enum Rows { ANYWHERE, ANYWHERE_FEW, ON_LINES };
 
 template <class C, bool PART, bool BLK, Rows AT>
 __device__ __forceinline__ void
@@ -102,7 +101,7 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
 {
     static_assert(!(PART && (BLK || C::G > 1)), "a split of K over workgroups is not combined with blocks read in place or groups");
     static_assert(AT == ANYWHERE || C::G == 1, "grouped tiles make no difference between rows");
-    static_assert((AT != ON_LINES_AT_ONCE || C::PATCHES) && (AT != ANYWHERE_FEW || C::FEW), "what is not launched is not compiled");
+    static_assert(AT != ANYWHERE_FEW || C::FEW, "what is not launched is not compiled");
     constexpr int KT = C::KT;
     // Measurement aid (off unless asked for): the workgroups that start first on the odd-numbered
     // XCDs wait skew_ticks of the 100 MHz wall clock, which puts the two halves of the chip out of
@@ -388,47 +387,6 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
                     }
                 }
             }
-    } else if constexpr (AT == ON_LINES_AT_ONCE) {
-        // Every wavefront by itself, no barrier, 8 loads of a lane in flight.
-        // Held as they are, the quads of one W row sit in 2 lanes x 4 registers, and a
-        // wavefront access would touch 32 rows x 32 bytes: measured at ~3.1 TB/s for the W/Mom
-        // read-modify-write, against ~4.9 TB/s once every row gets >= 128 contiguous bytes per
-        // instruction.  So each 32 x 32 block is turned through a private LDS patch: written as
-        // held, read back with 8 lanes per row, then 8 rows x 128 bytes per global access, streamed.
-        float* patch = reinterpret_cast<float*>(lds) + wave * (32 * PLD);
-        const int prow = lane >> 3, pcol = 4 * (lane & 7);
-#pragma unroll
-        for (int bn = 0; bn < C::BN; ++bn) {
-#pragma unroll
-            for (int bm = 0; bm < C::BM; ++bm) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<float4*>(patch + quad_n(q) * PLD + quad_m(q)) = quad(bn, bm, q);
-                float4 d[4], w[4], mo[4];
-                const int64_t m = m0 + wm0 + 32 * bm + pcol;
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) {
-                    const int64_t n = n0 + wn0 + 32 * bn + prow + 8 * jj;
-                    d[jj] = *reinterpret_cast<const float4*>(patch + (prow + 8 * jj) * PLD + pcol);
-                    if (n < N && m < M) {                  // m % 4 == 0 and M % 4 == 0: whole quad inside
-                        w[jj] = load_stream4(W + n * int64_t(M) + m);
-                        mo[jj] = load_stream4(Mom + n * int64_t(M) + m);
-                    }
-                }
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) {
-                    const int64_t n = n0 + wn0 + 32 * bn + prow + 8 * jj;
-                    if (n < N && m < M) {
-                        upd(d[jj].x, w[jj].x, mo[jj].x, lr, mu, wd);
-                        upd(d[jj].y, w[jj].y, mo[jj].y, lr, mu, wd);
-                        upd(d[jj].z, w[jj].z, mo[jj].z, lr, mu, wd);
-                        upd(d[jj].w, w[jj].w, mo[jj].w, lr, mu, wd);
-                        store_stream4(Mom + n * int64_t(M) + m, mo[jj]);
-                        store_stream4(W + n * int64_t(M) + m, w[jj]);
-                    }
-                }
-            }
-        }
     } else {
         // The rows of one bn of all wavefronts go through LDS at a time and come back as whole lines of W: a wavefront takes eight
         // rows of the tile's whole width, and while it updates them those of the next eight are on their way.  Tiles inside W of one
@@ -440,7 +398,8 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
         // 3000 -> 21841 395 -> 360, 3001 -> 21841 411 -> 370, 9999 -> 4095 262 -> 233, 2545 -> 15057, K = 1072 209 -> 164,
         // 20280 -> 1582, K = 296 124 -> 104.  (These launches are bound by power, 1.4 kW, or by HBM: RowUpdate has two to three times
         // the vector instructions.)  64 x 64 tiles off lines, of which a third and more are edges, gain nothing: 172 -> 11620,
-        // K = 88 9.9 and 10.5.
+        // K = 88 9.9 and 10.5.  Patches for lone 128 x 256 tiles of long sums, faster in rows too since the loop reads further ahead:
+        // 4096 -> 4096, K = 2048 95.0 -> 90.4, 8192 -> 2048 94.8 -> 92.5, 2304 -> 7168, K = 1280 86.6 -> 76.7.
         float* buf = reinterpret_cast<float*>(lds);
         constexpr bool SHIFTED = AT == ANYWHERE || AT == ANYWHERE_FEW, INNER = C::G == 1 && AT != ANYWHERE_FEW && (C::BM >= 2 || !SHIFTED);
         const bool inside = n0 + C::TN <= N && m0 + C::TM <= M;
@@ -510,13 +469,12 @@ Rows rows_at(const float* W, const float* Mom, int64_t N, int64_t M, int64_t K)
 {
     if (C::G > 1) return ANYWHERE;
     if (M % 32 == 0 && (reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(Mom)) % 128 == 0)
-        return C::PATCHES && bf16_patches(N, M, K, C::TN, C::TM, device_cu_count()) ? ON_LINES_AT_ONCE : ON_LINES;
+        return ON_LINES;
     return C::FEW && bf16_few_tiles(N, M, C::TN, C::TM, device_cu_count()) ? ANYWHERE_FEW : ANYWHERE;
 }
 
 // ... and what there is of a tile C
 template <class C> constexpr Rows kOnLines = C::G == 1 ? ON_LINES : ANYWHERE;
-template <class C> constexpr Rows kAtOnce = C::PATCHES ? ON_LINES_AT_ONCE : kOnLines<C>;
 template <class C> constexpr Rows kFew = C::FEW ? ANYWHERE_FEW : ANYWHERE;
 
 template <class C>
@@ -528,18 +486,16 @@ psd_status launch_cfg_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int6
     if (tiles < 1 || tiles > 0x3fffffff) return PSD_E_INVALID;
     const int64_t u_bytes = B * ldu * 2, v_bytes = B * ldv * 2;          // one block
     const Rows at = rows_at<C>(W, Mom, N, M, P * B);
-    auto kern = at == ON_LINES_AT_ONCE ? sfb_bf16_blocks_kernel<C, kAtOnce<C>>
-                : at == ON_LINES       ? sfb_bf16_blocks_kernel<C, kOnLines<C>>
-                : at == ANYWHERE_FEW   ? sfb_bf16_blocks_kernel<C, kFew<C>> : sfb_bf16_blocks_kernel<C, ANYWHERE>;
-    const size_t lds = at == ON_LINES_AT_ONCE ? C::LDS_BYTES : C::LDS_BYTES_ROWS;
+    auto kern = at == ON_LINES       ? sfb_bf16_blocks_kernel<C, kOnLines<C>>
+                : at == ANYWHERE_FEW ? sfb_bf16_blocks_kernel<C, kFew<C>> : sfb_bf16_blocks_kernel<C, ANYWHERE>;
     static std::atomic<bool> attr_done{false};
     if (!attr_done.load(std::memory_order_acquire)) {
-        for (auto k : {sfb_bf16_blocks_kernel<C, kAtOnce<C>>, sfb_bf16_blocks_kernel<C, kOnLines<C>>, sfb_bf16_blocks_kernel<C, kFew<C>>,
+        for (auto k : {sfb_bf16_blocks_kernel<C, kOnLines<C>>, sfb_bf16_blocks_kernel<C, kFew<C>>,
                        sfb_bf16_blocks_kernel<C, ANYWHERE>})
             PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         attr_done.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(tiles)), dim3(C::THREADS), lds, st,
+    hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(tiles)), dim3(C::THREADS), C::LDS_BYTES_ROWS, st,
                        blocks, static_cast<int>(P), static_cast<int>(B), ldu, ldv, W, Mom, static_cast<int>(N),
                        static_cast<int>(M), static_cast<int>(P * B), lr, mu, wd, static_cast<int>(tiles_n),
                        static_cast<int>(tiles_m), static_cast<uint32_t>(u_bytes), static_cast<uint32_t>(v_bytes));
@@ -560,15 +516,14 @@ psd_status launch_cfg(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t
     constexpr bool alone = C::G == 1;            // groups are not split
     const Rows at = rows_at<C>(W, Mom, N, M, K);
     auto kern = splits > 1 ? sfb_bf16_kernel<C, alone, ANYWHERE>
-                : at == ON_LINES_AT_ONCE ? sfb_bf16_kernel<C, false, kAtOnce<C>>
-                : at == ON_LINES         ? sfb_bf16_kernel<C, false, kOnLines<C>>
-                : at == ANYWHERE_FEW     ? sfb_bf16_kernel<C, false, kFew<C>> : sfb_bf16_kernel<C, false, ANYWHERE>;
-    const size_t lds = splits > 1 || at == ON_LINES_AT_ONCE ? C::LDS_BYTES : C::LDS_BYTES_ROWS;
+                : at == ON_LINES     ? sfb_bf16_kernel<C, false, kOnLines<C>>
+                : at == ANYWHERE_FEW ? sfb_bf16_kernel<C, false, kFew<C>> : sfb_bf16_kernel<C, false, ANYWHERE>;
+    const size_t lds = splits > 1 ? C::LDS_BYTES : C::LDS_BYTES_ROWS;
     // raise the dynamic LDS limit once per process (idempotent, so a race between two first
     // callers is harmless; the flag only saves the call on later launches)
     static std::atomic<bool> attr_done{false};
     if (!attr_done.load(std::memory_order_acquire)) {
-        for (auto k : {sfb_bf16_kernel<C, alone, ANYWHERE>, sfb_bf16_kernel<C, false, kAtOnce<C>>, sfb_bf16_kernel<C, false, kOnLines<C>>,
+        for (auto k : {sfb_bf16_kernel<C, alone, ANYWHERE>, sfb_bf16_kernel<C, false, kOnLines<C>>,
                        sfb_bf16_kernel<C, false, kFew<C>>, sfb_bf16_kernel<C, false, ANYWHERE>})
             PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         attr_done.store(true, std::memory_order_release);

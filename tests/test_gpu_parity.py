@@ -641,7 +641,7 @@ def test_sfb_bf16_groups_of_tile_rows_that_start_at_other_columns_bit_exact(M, N
 @pytest.mark.parametrize("tile", [0, 1, 2])           # 128 x 256, 128 x 192, 128 x 128
 @pytest.mark.parametrize("M,B", [(544, 5), (544, 342), (572, 11), (577, 11), (602, 5)])
 def test_sfb_bf16_tiles_inside_w_and_at_its_edges_bit_exact(M, B, tile, pinned_tile):
-    """Rows on lines (K = 1026: 128 x 256 tiles in patches), on quads, anywhere and on pairs; W and Mom that start in the middle of
+    """Rows on lines, on quads, anywhere and on pairs; W and Mom that start in the middle of
     a line, between guard values that must survive."""
     pinned_tile(psd.TUNE_SFB_BF16_TILE, tile)
     d = inputs.fc_layer_integer(M, 300, B=B, P=3, seed=M, amax=2)

@@ -20,7 +20,7 @@ def rules(tmp_path_factory):
     for name, res, args in (("max_items", i64, []), ("dense_threads", i32, [i64, i64]), ("dense_chunks", i32, [i64, i32, i32]),
                             ("pack_rows", i64, [i64, i64]), ("divided", ctypes.c_uint32, [ctypes.c_uint32, ctypes.c_uint32]), ("f32_reach", i32, [i64, i64, i64]),
                             ("bf16_reach", i32, [i64, i64, i64, i64]), ("bf16_choice", i32, [i64, i64, i64, c_int, i64]),
-                            ("splits_asked", i32, [i64, i64, i64]), ("bf16_in_patches", i32, [i64, i64, i64, i64]), ("bf16_few", i32, [i64, i64, i64]), ("f32_choice", i32, [i64, i64, i64, i64]),
+                            ("splits_asked", i32, [i64, i64, i64]), ("bf16_few", i32, [i64, i64, i64]), ("f32_choice", i32, [i64, i64, i64, i64]),
                             ("f32_planes", i32, [i64, i64, i64, i64]), ("f32_splits", i32, [i64, i64, i64, c_int, i64])):
         getattr(L, name).restype, getattr(L, name).argtypes = res, args
     return L
@@ -132,12 +132,6 @@ def test_pairs_of_grouped_tiles_are_for_layers_that_have_two_for_each_compute_un
     for M, N, K in ((64, 64, 512), (1024, 1000, 2048), (1024, 1024, 256), (5460, 384, 512), (4096, 1000, 512), (9216, 4096, 2048),
                     (2048, 1024, 255), (2017, 1001, 383), (2048, 1024, 3073)):
         assert rules.bf16_choice(N, M, K, 1, CUS) // 10 != 7
-
-
-def test_update_in_patches_is_for_long_sums_over_tiles_that_all_run_at_once(rules):
-    for M, N, K, patches in ((4096, 4096, 1024, 1), (4096, 4096, 1023, 0), (4096, 4097, 2048, 0), (4352, 3840, 2048, 1),
-                             (4096, 8192, 1024, 0), (256, 128, 1024, 1)):
-        assert rules.bf16_in_patches(N, M, K, CUS) == patches, (M, N, K)
 
 
 def test_few_tiles_off_quads_are_all_updated_as_at_the_edges(rules):
