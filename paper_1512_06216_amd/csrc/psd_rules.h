@@ -223,7 +223,12 @@ inline double launch_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K, in
     // layers 30 are faster, by 4 % on average, 4 slower, by 2 to 6 % (23712 -> 484, K = 280 39.5 and 42.0).  Whole steps of AlexNet: K = 256 285
     // and 266, K = 512 305 and 289, K = 1024 337 and 328.  With longer sums a lone layer still gains (4096 -> 6144, K = 2048 142 and
     // 133), but the larger tile reads less from L2, and a step is bound by power: AlexNet, K = 1536 381 and 386, K = 2048 432 and 455.
-    const double since = !off_lines && K >= 256 && K <= 1024 ? (t.id == 0 ? 1.06 : t.id == 2 ? 0.96 : 1) : 1;
+    // Since its loop runs on 16 x 16 MFMAs with a stage more in flight the 128 x 256 tile gains most where there are many of them and
+    // sums are long: 4096 -> 21841, K = 2048 449 with 128 x 192 and 434, 25088 -> 4096, K = 2048 510 and 503, 7614 -> 7538, K = 2400
+    // 360 and 348, 9490 -> 4633, K = 1400 209 and 203; with less than four for each compute unit others stay ahead (11776 -> 1635,
+    // K = 2328 127 and 135, 14905 -> 1495, K = 1944 129.5 and 134).
+    const double since = t.id == 0 && K > 1024 && share > 4 ? 0.935
+                         : off_lines || K < 256 || K > 1024 ? 1 : t.id == 0 ? 1.06 : t.id == 2 ? 0.96 : 1;
     return (5 + update * (share + tail) + torn + t.loop * k * rounds) * since;
 }
 
