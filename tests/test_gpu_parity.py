@@ -1009,10 +1009,10 @@ def test_sfb_vgg16_first_fc_layer_at_full_batch_integer_bit_exact():
     assert np.array_equal(Mg, Mr) and np.array_equal(Wg, Wr)
 
 
-@pytest.mark.parametrize("N,K", [(31, 1), (33, 255), (8192, 257), (8193, 64), (8321, 129)])
+@pytest.mark.parametrize("N,K", [(31, 1), (33, 255), (8192, 257), (8193, 64), (8321, 129), (16383, 513), (16385, 65), (16513, 257)])
 @pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
 def test_bias_column_blocks_bit_exact(N, K, dtype):
-    """Both column widths of the bias kernel (N up to and above 32 per compute unit), ragged last blocks and row rounds."""
+    """The column widths of the bias kernel (N up to 32 and 64 per compute unit and above), ragged last blocks and row rounds."""
     d = inputs.fc_layer_integer(8, N, K, 1, seed=N + K)
     plan, U, ldu, V, ldv = run_pack(d, dtype)
     b0, m0 = d["W"][:, 0].copy(), d["Mom"][:, 0].copy()
