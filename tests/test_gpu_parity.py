@@ -273,6 +273,19 @@ def test_sfb_bf16_every_tile_shape_bit_exact(tile, M, N, B, P, pinned_tile):
     assert np.array_equal(Mg, Mr) and np.array_equal(Wg, Wr)
 
 
+@pytest.mark.parametrize("K", [1, 32, 33, 64, 96, 97, 128, 129, 160, 193])
+@pytest.mark.parametrize("tile", [0, 1, 2])
+def test_sfb_bf16_stages_around_the_depth_of_the_ring_bit_exact(tile, K, pinned_tile):
+    """1 .. 7 stages of 32 k rows, even and odd in number, whole and not, on a ring of three or four; rows of W on lines and not."""
+    pinned_tile(psd.TUNE_SFB_BF16_TILE, tile)
+    for M in (416, 414):
+        d = inputs.fc_layer_integer(M=M, N=300, B=K, P=1, seed=tile + K)
+        Wg, Mg, _ = run_sfb(d, psd.BF16, 0.25, 0.5)
+        U, V = orc.pack_factors(d["delta"], d["act"])
+        Wr, Mr = orc.sync_fc_sfb(U, V, d["W"], d["Mom"], 0.25, 0.5)
+        assert np.array_equal(Mg, Mr) and np.array_equal(Wg, Wr), M
+
+
 def test_sfb_bf16_phase_skew_changes_no_bit(pinned_tile):
     """The measurement aid that starts half of the chip's first workgroups late only shifts work in time."""
     pinned_tile(psd.TUNE_SFB_BF16_SKEW_US, 15)
