@@ -89,7 +89,7 @@ def test_bf16_offsets_of_every_stage_requested_stay_below_2_to_the_32(rules):
                 if K * ld * 2 <= 2 ** 32 - 5 * 32 * ld * 2 - 4096:
                     assert rules.bf16_reach(K, ld, 8, 32)
                 if rules.bf16_reach(K, ld, 8, rows):
-                    last = -(-K // rows) * rows + 3 * rows - 1   # row of the last stage requested
+                    last = -(-K // rows) * rows + 4 * rows - 1   # row of the last stage requested
                     assert (last * ld + ld + 255) * 2 < 2 ** 32
 
 
