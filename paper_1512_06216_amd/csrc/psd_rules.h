@@ -174,12 +174,20 @@ inline int choose_planes(int64_t N, int64_t M, int64_t K, int64_t cus, double us
 }
 
 // ---- bf16 reconstruction: which tile covers W
-// What a tile costs, in us: `area` times the update of 64 x 64 weights at a compute unit's share of HBM (3.1 us) and `loop`
-// per 1024 k rows where compute units hold several tiles; `first` and `solo` per 1024 k rows where each holds one at most.
-// Fitted to 9216 -> 4096, 4096 -> 1000 and 1024 -> 1000 over K = 32 .. 2048.  Against what launches alone take: 3000 -> 21841 352
-// for 392 us, 4096 -> 21841 479 for 447, 25088 -> 4096 540 for 535, 4096 -> 4096 94 for 97, 3000 -> 3000 64 for 67, 4096 -> 1000
-// 27.5 for 30.5, 1024 -> 1000, K = 256 6.5 for 6.4; 9216 -> 4096 within 4 % for K = 512 .. 2048, 11 % short at K = 32, 12 % at
-// K = 4096.  The tiles contracted by several groups of wavefronts are for layers that have `most` of them for each compute unit
+// What a launch takes, in us.  Where compute units hold several tiles: `update` and, per 1024 k rows, `loop` for every tile of the
+// busiest one, of whose last round a part `tail` counts; less what of the smaller of the two hides behind the larger one once a
+// compute unit works through more tiles than the `slots` it holds at a time; and `torn` per tile where rows of W start off cache
+// lines, of which narrow tiles share more with their neighbours.  Where each holds one tile at most: `first`, and `solo` per 1024 k rows.
+// The former are fitted to what every tile takes on 665 layers of 0.1 to 110 M weights, K = 24 .. 4096, half of them off lines
+// (profiles/fit_bf16_tiles.txt): the tile chosen takes 1.3 % longer than the best one on average, 0.3 % on the 110 of
+// 8 M weights and more.  The fit before it was to kernels with other loops and updates and had factors that began and ended at
+// K = 256, K = 1024 and four tiles for each compute unit: 2.1 and 0.7 %.  Before and now: 4096 -> 4096, K = 224 56.0 and 50.3 us,
+// K = 1056 67.3 and 64.9; 16384 -> 2048, K = 512 131 and 114; 5243 -> 8018, K = 176 125 and 115; 2624 -> 6817, K = 200 67.5 and 58.2;
+// the other way 4096 -> 8192, K = 1024 118 and 122, 23232 -> 1517, K = 264 115 and 124, 24840 -> 3808, K = 40 303 and the best tile 278.
+// Of 722 further layers 120 have another tile now, by 3.4 % faster, 23 of them slower.  Predicted for measured: 4096 -> 21841,
+// K = 2048 437 for 430, 25088 -> 4096 507 for 500, 3000 -> 21841 345 for 359, 9216 -> 4096 195 for 193, 4096 -> 4096 102 for 90,
+// 4096 -> 1000 27.5 for 30.6, 1024 -> 1000, K = 256 6.5 for 6.1; 12 % rms.
+// The tiles contracted by several groups of wavefronts are for layers that have `most` of them for each compute unit
 // at most, which they fill: 1024 -> 1000, K = 2048 17.4 us with four wavefronts per 64 x 64 tile, 12.5 with sixteen.  Two tiles of
 // two groups each (id 7) against the better one of the tiles of four wavefronts, of which a compute unit then holds one or two:
 // 2048 -> 1024 11.7 -> 9.7 us at K = 384, 16.1 -> 12.8 at K = 1024, 23.5 -> 21.6 at K = 2560; 768 -> 2048, K = 1024 14.7 -> 12.2,
@@ -187,11 +195,12 @@ inline int choose_planes(int64_t N, int64_t M, int64_t K, int64_t cus, double us
 // short sums gain only where rows of W start on cache lines (224 -> 6787, K = 136 9.2 and 7.7, 12928 -> 96, K = 416 10.3 and 8.8;
 // 9964 -> 182, K = 160 8.6 and 9.1, 229 -> 5600, K = 312 9.4 and 9.7, 2149 -> 768, K = 384 10.4 and 10.1); and
 // from 4096 on a sum split over workgroups is the better one for some (1088 -> 1024 24.0 and 25.8, 320 -> 5280 43.4 and 38.1).
-struct Bf16Tile { int id, tn, tm, most; double area, loop, first, solo; };
-constexpr Bf16Tile kTiles[] = {{0, 128, 256, 0, 8, 9.9, 14.7, 15.1}, {1, 128, 192, 0, 6, 6.6, 11.9, 8.3},
-                               {2, 128, 128, 0, 4, 5.7, 8.6, 7.1},   {3, 64, 128, 0, 2, 3.8, 5.1, 6.6},
-                               {4, 64, 64, 0, 1, 2.5, 3.9, 6.0},     {5, 64, 64, 1, 1, 0, 3.75, 3.4},
-                               {6, 128, 128, 1, 4, 0, 8.3, 5.9},     {7, 64, 64, 2, 1, 0.3, 5.3, 4.6}};
+// `part`: the loop of tiles that store partial sums, per 1024 k rows.
+struct Bf16Tile { int id, tn, tm, most, slots; double update, tail, torn, loop, first, solo, part; };
+constexpr Bf16Tile kTiles[] = {{0, 128, 256, 0, 2, 23.4, 0.60, 0.5, 12.7, 14.7, 15.1, 9.9}, {1, 128, 192, 0, 2, 16.7, 0.80, 0.7, 10.3, 11.9, 8.3, 6.6},
+                               {2, 128, 128, 0, 2, 11.5, 0.70, 0.4, 8.3, 8.6, 7.1, 5.7},    {3, 64, 128, 0, 3, 5.3, 0.55, 0.5, 5.7, 5.1, 6.6, 3.8},
+                               {4, 64, 64, 0, 5, 2.7, 0.45, 0.8, 3.6, 3.9, 6.0, 2.5},       {5, 64, 64, 1, 1, 0, 0, 0, 0, 3.75, 3.4, 0},
+                               {6, 128, 128, 1, 1, 0, 0, 0, 0, 8.3, 5.9, 0},                {7, 64, 64, 2, 2, 0, 0, 0, 0.3, 5.3, 4.6, 0}};
 constexpr double kNever = 1e30;
 constexpr int64_t kMinPairRows = 256, kMinPairRowsOffLines = 384, kMaxPairRows = 3072;
 
@@ -199,37 +208,18 @@ constexpr int64_t kMinPairRows = 256, kMinPairRowsOffLines = 384, kMaxPairRows =
 inline double launch_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K, int64_t cus)
 {
     const int64_t tiles = ((N + t.tn - 1) / t.tn) * ((M + t.tm - 1) / t.tm);
-    const double k = static_cast<double>(K) / 1024, share = static_cast<double>(tiles) / cus, update = 3.1 * t.area;
+    const double k = static_cast<double>(K) / 1024, share = static_cast<double>(tiles) / cus;
+    const double lone_update = 3.1 * t.tn * t.tm / 4096;
+    const bool off_lines = M % 32 != 0;
     if (t.most > 0 && tiles > t.most * cus) return kNever;
     if (t.most == 2) {                              // (fitted to 50 layers of K = 36 .. 3584)
-        if (tiles <= cus || K < (M % 32 ? kMinPairRowsOffLines : kMinPairRows) || K > kMaxPairRows) return kNever;
-        return t.first + (M % 32 ? 1.1 : 0) + 0.4 * update * share + (t.solo + t.loop * share) * k;
+        if (tiles <= cus || K < (off_lines ? kMinPairRowsOffLines : kMinPairRows) || K > kMaxPairRows) return kNever;
+        return t.first + (off_lines ? 1.1 : 0) + 0.4 * lone_update * share + (t.solo + t.loop * share) * k;
     }
-    if (tiles <= cus) return t.first + (M % 32 ? 1.5 : 0) + 0.6 * update * share + t.solo * k;
-    // the last, partly filled round: the loop takes as long as a full one, the update shares HBM among fewer
-    const double rounds = static_cast<double>((tiles + cus - 1) / cus), tail = (rounds - share) * (t.area > 2 ? 0.5 : 0.2);
-    // Off cache lines, with more tiles than fit the compute units at once.  64 columns are pieces of three lines, two of which the
-    // neighbours have too: 64 x 128 tiles are faster (1428 -> 4174, K = 128 25.9 and 22.3 us, 4526 -> 1135, K = 100 24.5 and
-    // 20.8, 2807 -> 1518, K = 384 24.6 and 21.4), but for layers of few rows (9476 -> 442, K = 96 16.8 and 17.7).  The 128 x 128
-    // tile takes 175 registers there, 113 on lines, and half as many fit: 891 -> 12360, K = 280 56.3 and, 128 x 192, 44.8,
-    // 988 -> 19501, K = 263 84.2 and, 64 x 128, 74.3, 2643 -> 7618, K = 951 116 and, 128 x 192, 105.  Of 24 further layers whose
-    // tile this changes 22 are 2 to 16 % faster, 984 -> 12243 is the same, and 3100 -> 5022, K = 1098 is slower, 87.9 and 92.7: the 680 tiles of
-    // 128 x 192 that it gets fill the compute units one and a third times, which the cost of that tile counts as less than it is.
-    const bool off_lines = M % 32 != 0;
-    const double torn = off_lines && t.id == 4 && share > 4 && M < 8 * N ? 0.7 * share : off_lines && t.id == 2 && share > 2 ? 2 * share : 0;
-    // On lines the 128 x 128 tile gained most when tiles inside W got an update of their own, and the 128 x 256 tile least.  us with
-    // the tile chosen before and with what they cost since then counted: 4096 -> 4096, K = 512 61.1 and 54.7, K = 1024 73.8 and
-    // 64.1; 16384 -> 2048, K = 1024 152 and 132; 8192 -> 4096, K = 1024 140 and 131; of 40 such
-    // layers 30 are faster, by 4 % on average, 4 slower, by 2 to 6 % (23712 -> 484, K = 280 39.5 and 42.0).  Whole steps of AlexNet: K = 256 285
-    // and 266, K = 512 305 and 289, K = 1024 337 and 328.  With longer sums a lone layer still gains (4096 -> 6144, K = 2048 142 and
-    // 133), but the larger tile reads less from L2, and a step is bound by power: AlexNet, K = 1536 381 and 386, K = 2048 432 and 455.
-    // Since its loop runs on 16 x 16 MFMAs with a stage more in flight the 128 x 256 tile gains most where there are many of them and
-    // sums are long: 4096 -> 21841, K = 2048 449 with 128 x 192 and 434, 25088 -> 4096, K = 2048 510 and 503, 7614 -> 7538, K = 2400
-    // 360 and 348, 9490 -> 4633, K = 1400 209 and 203; with less than four for each compute unit others stay ahead (11776 -> 1635,
-    // K = 2328 127 and 135, 14905 -> 1495, K = 1944 129.5 and 134).
-    const double since = t.id == 0 && K > 1024 && share > 4 ? 0.935
-                         : off_lines || K < 256 || K > 1024 ? 1 : t.id == 0 ? 1.06 : t.id == 2 ? 0.96 : 1;
-    return (5 + update * (share + tail) + torn + t.loop * k * rounds) * since;
+    if (tiles <= cus) return t.first + (off_lines ? 1.5 : 0) + 0.6 * lone_update * share + t.solo * k;
+    const double rounds = static_cast<double>((tiles + cus - 1) / cus), most = share + t.tail * (rounds - share), loop = t.loop * k;
+    const double hidden = most > t.slots ? 0.9 * t.update * loop / (t.update + loop) * (most - t.slots) : 0;
+    return 4 + (t.update + loop) * most - hidden + (off_lines ? t.torn * share : 0);
 }
 
 // ... and when `splits` workgroups per tile store partial sums that a second launch adds up
@@ -238,7 +228,7 @@ inline double split_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K, int
     const int64_t groups = ((N + t.tn - 1) / t.tn) * ((M + t.tm - 1) / t.tm) * splits;
     if (t.most > 0) return kNever;
     const double k = static_cast<double>(K) / splits / 1024, sum = 4 + (16.0 + 4 * splits) * N * M / 5e6;
-    if (groups > cus) return sum + 5 + static_cast<double>((groups + cus - 1) / cus) * (0.8 * t.area + t.loop * k);
+    if (groups > cus) return sum + 5 + static_cast<double>((groups + cus - 1) / cus) * (0.8 * t.tn * t.tm / 4096 + t.part * k);
     return sum + t.first + t.solo * k;              // (the partial sums stay in the caches)
 }
 

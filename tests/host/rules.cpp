@@ -21,6 +21,7 @@ int32_t bf16_choice(int64_t N, int64_t M, int64_t K, int most, int64_t cus)
     const psd::Bf16Tile t = psd::choose_bf16_split(N, M, K, most, cus, -1, &splits);
     return 10 * t.id + splits;
 }
+double bf16_cost(int32_t tile, int64_t N, int64_t M, int64_t K, int64_t cus) { return psd::launch_cost(psd::kTiles[tile], N, M, K, cus); }
 int32_t bf16_few(int64_t N, int64_t M, int64_t cus) { return psd::bf16_few_tiles(N, M, 64, 128, cus); }
 int32_t splits_asked(int64_t tiles, int64_t cus, int64_t K) { return psd::sfb_splits_for(tiles, 2 * cus, K); }
 // bn, bm, whether there are 128 x 128 tiles before them, groups: as decimal digits

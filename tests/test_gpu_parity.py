@@ -309,9 +309,11 @@ def test_sfb_f32_both_tile_shapes_bit_exact(tile, pinned_tile):
 # Layers for which the rules choose each tile, with rows of W on cache lines and not, and K such that the ring of LDS buffers goes
 # round.  (tests/test_rules.py checks that the rules do choose them, on 256 compute units.)
 BF16_TILE_LAYERS = [  # tile, M, N, B, P
-    (0, 4768, 3055, 32, 6), (0, 4783, 3055, 32, 6), (1, 3040, 1642, 32, 6), (1, 1329, 4311, 32, 6), (2, 1952, 3683, 32, 6),
-    (2, 1957, 3683, 32, 6), (3, 5536, 130, 32, 6), (3, 5881, 130, 32, 6), (4, 288, 5567, 32, 6), (4, 5567, 130, 32, 6),
-    (5, 64, 64, 32, 20), (5, 65, 64, 64, 10), (6, 5536, 328, 32, 10), (6, 4939, 592, 64, 5)]
+    (0, 2240, 5481, 160, 8), (0, 2230, 5490, 128, 8), (1, 3776, 1381, 96, 4), (1, 801, 5086, 128, 4), (2, 3392, 1895, 96, 8),
+    (2, 3746, 2138, 160, 2), (3, 5536, 130, 32, 6), (3, 5881, 130, 32, 6), (4, 288, 5567, 32, 6), (4, 5567, 130, 32, 6),
+    (5, 64, 64, 32, 20), (5, 65, 64, 64, 10), (6, 4928, 602, 96, 3), (6, 4787, 476, 96, 4),
+    (4, 4768, 3055, 32, 6), (3, 4783, 3055, 32, 6), (4, 3040, 1642, 32, 6), (3, 1329, 4311, 32, 6), (3, 1952, 3683, 32, 6),
+    (3, 1957, 3683, 32, 6), (4, 5536, 328, 32, 10), (6, 4939, 592, 64, 5)]
 BF16_FEW_LAYERS = [(3523, 891, 32, 3), (615, 2216, 32, 1), (3543, 1273, 32, 2)]       # 64 x 128 off quads; M, N, B, P
 BF16_SPLIT_LAYERS = [  # tile, workgroups per tile, M, N, B, P
     (2, 2, 10944, 128, 1024, 8), (2, 3, 4155, 196, 512, 8), (3, 4, 2692, 65, 375, 8), (3, 4, 2689, 65, 375, 8),

@@ -20,7 +20,7 @@ def rules(tmp_path_factory):
     for name, res, args in (("max_items", i64, []), ("dense_threads", i32, [i64, i64]), ("dense_chunks", i32, [i64, i32, i32]),
                             ("pack_rows", i64, [i64, i64]), ("divided", ctypes.c_uint32, [ctypes.c_uint32, ctypes.c_uint32]), ("f32_reach", i32, [i64, i64, i64]),
                             ("bf16_reach", i32, [i64, i64, i64, i64]), ("bf16_choice", i32, [i64, i64, i64, c_int, i64]),
-                            ("splits_asked", i32, [i64, i64, i64]), ("bf16_few", i32, [i64, i64, i64]), ("f32_choice", i32, [i64, i64, i64, i64]),
+                            ("splits_asked", i32, [i64, i64, i64]), ("bf16_cost", ctypes.c_double, [i32, i64, i64, i64, i64]), ("bf16_few", i32, [i64, i64, i64]), ("f32_choice", i32, [i64, i64, i64, i64]),
                             ("f32_planes", i32, [i64, i64, i64, i64]), ("f32_splits", i32, [i64, i64, i64, c_int, i64])):
         getattr(L, name).restype, getattr(L, name).argtypes = res, args
     return L
@@ -142,10 +142,37 @@ def test_few_tiles_off_quads_are_all_updated_as_at_the_edges(rules):
 
 
 def test_rows_off_lines_get_other_tiles_where_they_do_not_all_fit_the_compute_units(rules):
-    for M, N, K, tile in ((1428, 4174, 128, 3), (1440, 4174, 128, 4), (4526, 1135, 100, 3), (1027, 4508, 207, 3), (9476, 442, 96, 4),
-                          (124, 17184, 244, 4), (3464, 610, 752, 4), (891, 12360, 280, 1), (896, 12360, 280, 2),
+    for M, N, K, tile in ((1428, 4174, 128, 3), (1440, 4174, 128, 4), (4526, 1135, 100, 3), (1027, 4508, 207, 3), (9476, 442, 96, 3),
+                          (124, 17184, 244, 4), (3464, 610, 752, 6), (891, 12360, 280, 3), (896, 12360, 280, 4),
                           (988, 19501, 263, 3), (5617, 3497, 327, 3)):
         assert rules.bf16_choice(N, M, K, 1, CUS) == 10 * tile + 1, (M, N, rules.bf16_choice(N, M, K, 1, CUS))
+
+
+def test_bf16_costs_have_no_steps(rules):
+    """One row of k more costs at most what the loop does with it, and more tiles never cost less.  (A factor that began or ended
+    at K = 256, K = 1024 and four tiles for each compute unit gave layers on one side of these another tile: 4096 -> 4096,
+    K = 224 56 us where another takes 50.)"""
+    for tile, tn, tm in ((0, 128, 256), (1, 128, 192), (2, 128, 128), (3, 64, 128), (4, 64, 64)):
+        for M, N in ((4096, 4096), (8192, 4096), (25088, 4096), (16384, 2048), (3000, 21841), (4096, 21841), (2643, 7618)):
+            for K in (*range(32, 300), *range(1000, 1060), 2048, 4095):
+                a, b = rules.bf16_cost(tile, N, M, K, CUS), rules.bf16_cost(tile, N, M, K + 1, CUS)
+                assert a < b < 1.0014 * a, (tile, M, N, K)     # 1024 rows cost at most 1.34 updates (64 x 64)
+        for M in (tm, tm + 1):
+            for K in (128, 1024, 1025, 2048):
+                costs = [rules.bf16_cost(tile, tn * n, M, K, CUS) for n in range(CUS + 1, 9 * CUS)]
+                assert all(a < b for a, b in zip(costs, costs[1:])), (tile, M, K)
+
+
+def test_bf16_tiles_of_layers_that_were_measured(rules):
+    """us of all tiles: profiles/fit_bf16_tiles.txt."""
+    for M, N, K, tile in ((4096, 21841, 2048, 0), (25088, 4096, 2048, 0), (4096, 4096, 2048, 0), (9216, 4096, 2048, 1), (3000, 21841, 2048, 1),
+                          (4096, 4096, 1024, 2), (4096, 4096, 1056, 2), (16384, 2048, 512, 3), (5243, 8018, 176, 3), (2624, 6817, 200, 3),
+                          (3753, 945, 48, 3), (9517, 3296, 168, 3), (4096, 1000, 2048, 6), (1024, 1000, 256, 5)):
+        assert rules.bf16_choice(N, M, K, 1, CUS) == 10 * tile + 1, (M, N, K, rules.bf16_choice(N, M, K, 1, CUS))
+    for K in range(900, 1200, 10):
+        assert rules.bf16_choice(4096, 8192, K, 1, CUS) == rules.bf16_choice(4096, 8192, 1024, 1, CUS)
+    for K in (64, 128, 224, 255, 256, 288):
+        assert rules.bf16_choice(4096, 4096, K, 1, CUS) // 10 in (3, 4)
 
 
 def test_layers_of_the_parity_tests_go_to_the_pipe_they_stand_for(rules):
