@@ -405,34 +405,22 @@ psd_status check_factor_layer(const psd_layer_task& t, float wd)
 // Only where nothing tells them apart: they name one readiness event, share no stream, and none of them will be refused (a layer
 // that is refused leaves those below it untouched, and those above it issued).  Without an event a layer's readiness is the order
 // of its own stream, which the library cannot see.
-// Beside packs and bf16 reconstructions the sum's accesses and theirs hinder each other, and the group's waits end up behind the
-// last reconstruction; first and by itself the sum is short and they fill the chip afterwards.  Taken with three reconstructions
-// or more that take 145 us together, alone on the chip, and a sum of 15 % of that at most (estimates: 3.1 us per M weights for the
-// update and as much again per 2450 rows of k; 8.7 us per M keys and 8 copies).  Forty networks in both orders, us a step, group
-// last -> first:
-//   taken: AlexNet 8 x 256 samples 473 -> 449, 8 x 32 289 -> 282, 4 x 128 308 -> 301, 16 x 64 375 -> 367, with a fifth of the conv
-//     keys 455 -> 442; 9216 -> 4096 -> 4096 -> 4096 -> 1000 598 -> 579; 9216 -> 3000 -> 3000 -> 21841 786 -> 769;
-//     8191 -> 3001 -> 2999 -> 1001 355 -> 343; 6000 -> 3000 -> 2000 -> 1000 307 -> 288; ten more gain 3-9 % and one,
-//     4096 -> 4096 -> 2048 -> 1000, loses 2 % (313 -> 319)
-//   left: VGG-16 with its 14.7 M conv keys 997 -> 1008, at 8 x 64 709 -> 725; 4096 -> 4096 -> 2048 -> 1000 at 8 x 32 199 -> 208;
-//     2048 -> 2048 -> 2048 -> 1000 193 -> 204; one and two layers 300 -> 319, 347 -> 350; of the smaller networks some lose up to
-//     4 % and some gain (3000 -> 3000 -> 3000 -> 1000 277 -> 253)
-// fp32 reconstructions leave HBM idle, which the sum fills beside them (AlexNet 1830 against 1860).
+// Whether that pays is for sum_goes_first (psd_rules.h) to say.
 int32_t group_to_issue_first(int32_t L, const psd_layer_task* layers, float wd, int32_t rule, int32_t* hi)
 {
-    constexpr int32_t kLayers = 3;
-    constexpr double kMicros = 145, kShare = 0.15;
     const void* ready = layers[L - 1].ev_ready;
     if (!ready) return -1;
     int32_t l = L - 1;
-    double us = 0, sum_us = 0;
+    double update_us = 0, loop_us = 0, sum_us = 0;
     for (; l >= 0; --l) {
         const psd_layer_task& t = layers[l];
         const int32_t route = rule == PSD_RULE_ALG3 ? t.plan.route_alg3 : t.plan.route_vs_dense;
         if (t.ev_ready != ready || (route != PSD_ROUTE_SFB && route != PSD_ROUTE_SF_PS) || t.factor_dtype != PSD_BF16) break;
-        us += 3.1e-6 * static_cast<double>(t.plan.M) * static_cast<double>(t.plan.N) * (1 + static_cast<double>(t.plan.P) * t.plan.B / 2450);
+        const double update = issue_update_us(static_cast<double>(t.plan.M) * static_cast<double>(t.plan.N));
+        update_us += update;
+        loop_us += issue_loop_us(update, static_cast<double>(t.plan.P) * static_cast<double>(t.plan.B));
     }
-    if (L - 1 - l < kLayers || us < kMicros) return -1;
+    if (!sum_goes_first(L - 1 - l, update_us, loop_us, 0)) return -1;
     int32_t lo = l + 1;
     while (lo > 0 && l - lo + 2 <= PSD_MAX_MULTI_SEGMENTS && fusable_ps_layer(layers[lo - 1], rule, ready)) --lo;
     if (lo >= l) return -1;
@@ -447,9 +435,9 @@ int32_t group_to_issue_first(int32_t L, const psd_layer_task* layers, float wd, 
         uint64_t n;
         if (mul_u64(static_cast<uint64_t>(t.plan.M), static_cast<uint64_t>(t.plan.N), &n) || n > (uint64_t(1) << 40)) return -1;
         if (check_dense(static_cast<int64_t>(n), static_cast<int32_t>(t.plan.P), PSD_MAX_MULTI_WORKERS, t.G, t.W, t.Mom, t.S) != PSD_OK) return -1;
-        sum_us += 8.7e-6 * static_cast<double>(n) * static_cast<double>(t.plan.P + 4) / 12;
+        sum_us += issue_sum_us(static_cast<double>(n), static_cast<double>(t.plan.P));
     }
-    if (sum_us > kShare * us) return -1;
+    if (!sum_goes_first(L - 1 - l, update_us, loop_us, sum_us)) return -1;
     *hi = l;
     return lo;
 }

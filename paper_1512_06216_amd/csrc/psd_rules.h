@@ -279,6 +279,29 @@ inline bool bf16_few_tiles(int64_t N, int64_t M, int64_t tn, int64_t tm, int64_t
     return M % 4 != 0 && ((N + tn - 1) / tn) * ((M + tm - 1) / tm) <= 2 * cus;
 }
 
+// ---- order of a step's launches
+// Does a parameter-server sum go before the bf16 reconstructions above it that wait for the same event?  Beside them its accesses and
+// theirs hinder each other, and it ends behind the last of them; first and by itself it is short and they fill the chip afterwards.
+// Estimated are what the reconstructions take alone, their updates and their loops, and the sum.  First, it has to be paid back: by
+// three reconstructions or more that take 145 us, and the more the longer their loops are, beside which a sum takes longest
+// (14.7 M keys beside VGG-16, K = 2048 480 to 850 us, by themselves 130).  Sixty networks in both orders, us a step, last -> first:
+//   taken: AlexNet (8 x 256 samples and 2.3 M conv keys unless said) 443 -> 431, 8 x 32 272 -> 260, 4 x 128 290 -> 276, 16 x 64
+//     355 -> 343, 4.7 M keys 502 -> 445, 9.3 M 556 -> 486, 8 x 128 with 4.7 M 367 -> 341; VGG-16 with its 14.7 M 997 -> 952;
+//     9216 -> 4096 -> 4096 -> 4096 -> 1000 607 -> 543; 9216 -> 3000 -> 3000 -> 21841 740 -> 726; 8191 -> 3001 -> 2999 -> 1001
+//     365 -> 342; 5000 -> 4000 -> 4000 -> 1000 with 6 M 438 -> 386; VGG-16 of 8 x 64 with 7 M is the one that loses, 553 -> 565
+//   left: VGG-16 of 8 x 64 with 14.7 M 686 -> 705, AlexNet of 8 x 64 with 7 M 330 -> 345, of 8 x 32 with 7 M 305 -> 315; one and two
+//     layers 288 -> 307, 333 -> 337; of 8 x 256 with 14 M 588 -> 537 and 22 M 643 -> 631, but VGG-16 with 30 M 1009 -> 1025
+// (With a limit of 15 % of the reconstructions, from the time of slower ones, VGG-16 had its sum last.)  fp32 reconstructions leave
+// HBM idle, which the sum fills beside them (AlexNet 1830 us last, 1860 first).
+inline double issue_update_us(double weights) { return 3.1e-6 * weights; }
+inline double issue_loop_us(double update_us, double rows) { return update_us * rows / 2450; }
+inline double issue_sum_us(double keys, double copies) { return 8.7e-6 * keys * (copies + 4) / 12; }
+inline bool sum_goes_first(int32_t layers, double update_us, double loop_us, double sum_us)
+{
+    const double us = update_us + loop_us, paid_back = 0.08 * update_us + 0.6 * loop_us;
+    return layers >= 3 && us >= 145 && sum_us <= (paid_back > 0.15 * us ? paid_back : 0.15 * us);
+}
+
 // ---- division by a number that a launch knows: multiplier and shifts of `divide` (psd_device.h)
 struct FastDiv { uint32_t d, mul, shift1, shift2; };
 

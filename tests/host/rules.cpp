@@ -21,6 +21,12 @@ int32_t bf16_choice(int64_t N, int64_t M, int64_t K, int most, int64_t cus)
     const psd::Bf16Tile t = psd::choose_bf16_split(N, M, K, most, cus, -1, &splits);
     return 10 * t.id + splits;
 }
+// `weights` of all layers together
+int32_t sum_first(int32_t layers, double weights, double K, double keys, double copies)
+{
+    const double update = psd::issue_update_us(weights);
+    return psd::sum_goes_first(layers, update, psd::issue_loop_us(update, K), psd::issue_sum_us(keys, copies));
+}
 double bf16_cost(int32_t tile, int64_t N, int64_t M, int64_t K, int64_t cus) { return psd::launch_cost(psd::kTiles[tile], N, M, K, cus); }
 int32_t bf16_few(int64_t N, int64_t M, int64_t cus) { return psd::bf16_few_tiles(N, M, 64, 128, cus); }
 int32_t splits_asked(int64_t tiles, int64_t cus, int64_t K) { return psd::sfb_splits_for(tiles, 2 * cus, K); }

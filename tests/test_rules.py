@@ -20,7 +20,8 @@ def rules(tmp_path_factory):
     for name, res, args in (("max_items", i64, []), ("dense_threads", i32, [i64, i64]), ("dense_chunks", i32, [i64, i32, i32]),
                             ("pack_rows", i64, [i64, i64]), ("divided", ctypes.c_uint32, [ctypes.c_uint32, ctypes.c_uint32]), ("f32_reach", i32, [i64, i64, i64]),
                             ("bf16_reach", i32, [i64, i64, i64, i64]), ("bf16_choice", i32, [i64, i64, i64, c_int, i64]),
-                            ("splits_asked", i32, [i64, i64, i64]), ("bf16_cost", ctypes.c_double, [i32, i64, i64, i64, i64]), ("bf16_few", i32, [i64, i64, i64]), ("f32_choice", i32, [i64, i64, i64, i64]),
+                            ("splits_asked", i32, [i64, i64, i64]), ("bf16_cost", ctypes.c_double, [i32, i64, i64, i64, i64]),
+                            ("sum_first", i32, [i32] + [ctypes.c_double] * 4), ("bf16_few", i32, [i64, i64, i64]), ("f32_choice", i32, [i64, i64, i64, i64]),
                             ("f32_planes", i32, [i64, i64, i64, i64]), ("f32_splits", i32, [i64, i64, i64, c_int, i64])):
         getattr(L, name).restype, getattr(L, name).argtypes = res, args
     return L
@@ -139,6 +140,19 @@ def test_few_tiles_off_quads_are_all_updated_as_at_the_edges(rules):
         assert rules.bf16_few(N, M, CUS) == few, (M, N)
     tiles = {(rules.bf16_choice(N, M, B * P, 1, CUS) // 10, M % 4 != 0, rules.bf16_few(N, M, CUS)) for M, N, B, P in parity.BF16_FEW_LAYERS}
     assert tiles == {(3, True, 1), (3, True, 0)}
+
+
+def test_a_parameter_server_sum_goes_first_where_that_was_measured_to_pay(rules):
+    alex, vgg = 9216 * 4096 + 4096 * 4096 + 4096 * 1000, 25088 * 4096 + 4096 * 4096 + 4096 * 1000
+    for layers, weights, K, keys, copies, first in (
+            (3, alex, 2048, 2.33e6, 8, 1), (3, alex, 256, 2.33e6, 8, 1), (3, alex, 512, 2.33e6, 4, 1), (3, alex, 1024, 2.33e6, 16, 1),
+            (3, alex, 2048, 4.7e6, 8, 1), (3, alex, 2048, 9.3e6, 8, 1), (3, alex, 1024, 4.7e6, 8, 1), (3, vgg, 2048, 14.7e6, 8, 1),
+            (3, vgg, 512, 14.7e6, 8, 0), (3, alex, 512, 7e6, 8, 0), (3, alex, 256, 7e6, 8, 0), (3, vgg, 2048, 30e6, 8, 0),
+            (2, 9216 * 4096 + 4096 * 1000, 2048, 2.33e6, 8, 0), (1, 9216 * 4096, 2048, 2.33e6, 8, 0), (3, 27e6, 256, 1e5, 8, 0)):
+        assert rules.sum_first(layers, weights, K, keys, copies) == first, (weights, K, keys)
+    for K in range(16, 8192, 64):                          # what went first by 15 % of the reconstructions still does
+        us = 3.1e-6 * vgg * (1 + K / 2450)
+        assert rules.sum_first(3, vgg, K, 0.149 * us / 8.7e-6, 8)
 
 
 def test_rows_off_lines_get_other_tiles_where_they_do_not_all_fit_the_compute_units(rules):
