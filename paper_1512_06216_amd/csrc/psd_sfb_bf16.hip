@@ -391,9 +391,9 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
         // The rows of one bn of all wavefronts go through LDS at a time and come back as whole lines of W: a wavefront takes eight
         // rows of the tile's whole width, and while it updates them those of the next eight are on their way.  Tiles inside W of one
         // group of wavefronts by InnerUpdate, whose batches are whole rows of the tile (768 bytes of W, then of Mom; half of that is
-        // up to 7 % slower than all of it: 25088 -> 4096 518 and 580 us); what is left at the edges of W, and the tiles of several
-        // groups, by RowUpdate.  us with a patch of LDS for each wavefront on lines (128 bytes of 32 rows, then the next) and
-        // RowUpdate for every tile off lines -> now, K = 2048 unless said: 25088 -> 4096 531 -> 514, 9216 -> 4096 198 -> 196,
+        // up to 7 % slower than all of it: 25088 -> 4096 518 and 580 us); what is left at the edges of W likewise, two lines at a
+        // time, on lines, and by RowUpdate off lines, as are the tiles of several groups.  us with a patch of LDS for each wavefront
+        // on lines (128 bytes of 32 rows, then the next) and RowUpdate for every tile off lines -> now, K = 2048 unless said: 25088 -> 4096 531 -> 514, 9216 -> 4096 198 -> 196,
         // 4096 -> 21841 465 -> 460, 3840 -> 2020, K = 56 30.3 -> 27.0, 4096 -> 8192 in 128 x 128, K = 1024 148 -> 128;
         // 3000 -> 21841 395 -> 360, 3001 -> 21841 411 -> 370, 9999 -> 4095 262 -> 233, 2545 -> 15057, K = 1072 209 -> 164,
         // 20280 -> 1582, K = 296 124 -> 104.  (These launches are bound by power, 1.4 kW, or by HBM: RowUpdate has two to three times
@@ -434,9 +434,14 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
                     continue;
                 }
             }
-            // (64 x 128 tiles beside InnerUpdate: no deeper than their 168 registers hold)
-            constexpr int DEPTH = C::BM == 4 ? 4 : C::BM == 1 ? 6 : C::FEW && INNER ? 4 : 5;
-            update(RowUpdate<C::ROWS, C::TM, C::WAVES, DEPTH, C::G, decltype(row_n)>(W, Mom, row_n, m0, N, M, wave, lane));
+            if constexpr (!SHIFTED) {
+                // (two lines ahead: with whole rows the 128 x 256 tile runs out of registers)
+                update(InnerUpdate<C::ROWS, C::TM, C::WAVES, 2, true, decltype(row_n), true>(W, Mom, row_n, m0, M, wave, lane, N));
+            } else {
+                // (64 x 128 tiles beside InnerUpdate: no deeper than their 168 registers hold)
+                constexpr int DEPTH = C::BM == 4 ? 4 : C::BM == 1 ? 6 : C::FEW && INNER ? 4 : 5;
+                update(RowUpdate<C::ROWS, C::TM, C::WAVES, DEPTH, C::G, decltype(row_n)>(W, Mom, row_n, m0, N, M, wave, lane));
+            }
         }
     }
 }

@@ -43,7 +43,7 @@ struct RowOf {
     int64_t operator()(int r) const { return n0 + (r >> 5) * 32 * bn + (pairs ? bn * (r & 31) + step : 32 * step + (r & 31)); }
 };
 
-template <template <class> class Make, int ROWS, int WIDTH, int WAVES, int PARTS, int BN, bool PAIRS, bool INNER>
+template <template <class> class Make, int ROWS, int WIDTH, int WAVES, int PARTS, int BN, bool PAIRS, bool INNER, bool EDGE = false>
 bool layer(int64_t N, int64_t M, int64_t lead, const char* name)
 {
     std::printf("%s: N %lld, M %lld, lead %lld\n", name, static_cast<long long>(N), static_cast<long long>(M), static_cast<long long>(lead));
@@ -71,7 +71,8 @@ bool layer(int64_t N, int64_t M, int64_t lead, const char* name)
                 std::vector<Update> lanes;
                 for (int wave = 0; wave < WAVES; ++wave)
                     for (int lane = 0; lane < 64; ++lane) {
-                        if constexpr (INNER) lanes.emplace_back(W.data(), Mom.data(), row_n, m0, M, wave, lane);
+                        if constexpr (EDGE) lanes.emplace_back(W.data(), Mom.data(), row_n, m0, M, wave, lane, N);
+                        else if constexpr (INNER) lanes.emplace_back(W.data(), Mom.data(), row_n, m0, M, wave, lane);
                         else lanes.emplace_back(W.data(), Mom.data(), row_n, m0, N, M, wave, lane);
                         lanes.back().template fetch<0>();
                     }
@@ -117,6 +118,10 @@ template <class R> struct Inner192 { using type = psd::InnerUpdate<64, 192, 4, 6
 template <class R> struct Lines256 { using type = psd::InnerUpdate<64, 256, 4, 8, true, R>; };
 template <class R> struct Lines192 { using type = psd::InnerUpdate<64, 192, 4, 6, true, R>; };
 template <class R> struct Lines64 { using type = psd::InnerUpdate<64, 64, 4, 2, true, R>; };
+template <class R> struct Edge256 { using type = psd::InnerUpdate<64, 256, 4, 2, true, R, true>; };
+template <class R> struct Edge192 { using type = psd::InnerUpdate<64, 192, 4, 2, true, R, true>; };
+template <class R> struct Edge128 { using type = psd::InnerUpdate<64, 128, 4, 2, true, R, true>; };
+template <class R> struct Edge64 { using type = psd::InnerUpdate<64, 64, 4, 2, true, R, true>; };
 template <class R> struct InnerLines { using type = psd::InnerUpdate<64, 128, 4, 4, true, R>; };
 
 }  // namespace
@@ -146,6 +151,14 @@ int main()
     ok = ok && layer<Lines256, 64, 256, 4, 1, 2, false, true>(130, 544, 0, "bf16, inside, on lines, 128 x 256");
     ok = ok && layer<Lines192, 64, 192, 4, 1, 2, false, true>(130, 416, 0, "bf16, inside, on lines, 128 x 192");
     ok = ok && layer<Lines64, 64, 64, 4, 1, 1, false, true>(130, 160, 0, "bf16, inside, on lines, 64 x 64");
+    for (int64_t M : {32, 64, 96, 160, 224, 256, 288, 544})
+        for (int64_t N : {1, 63, 70, 133}) {
+            ok = ok && layer<Edge256, 64, 256, 4, 1, 2, false, false, true>(N, M, 0, "bf16, edges, on lines, 128 x 256");
+            ok = ok && layer<Edge192, 64, 192, 4, 1, 2, false, false, true>(N, M, 0, "bf16, edges, on lines, 128 x 192");
+            ok = ok && layer<Edge128, 64, 128, 4, 1, 2, false, false, true>(N, M, 32, "bf16, edges, on lines, 128 x 128");
+            ok = ok && layer<Edge128, 64, 128, 4, 1, 1, false, false, true>(N, M, 0, "bf16, edges, on lines, 64 x 128");
+            ok = ok && layer<Edge64, 64, 64, 4, 1, 1, false, false, true>(N, M, 64, "bf16, edges, on lines, 64 x 64");
+        }
     std::printf(ok ? "all right\n" : "failed\n");
     return ok ? 0 : 1;
 }

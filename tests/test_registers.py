@@ -1,0 +1,69 @@
+"""Registers of the built kernels, as the library states them to the loader: what is launched beside them has to find room."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_1512_06216_amd import build
+
+SIMD_REGISTERS = 512
+
+
+def _code_objects(lib):
+    """The gfx950 code objects inside the library: every translation unit's bundle lists offset, size and name of its entries."""
+    data = open(lib, "rb").read()
+    magic = b"__CLANG_OFFLOAD_BUNDLE__"
+    for m in re.finditer(magic, data):
+        at = m.start()
+        n, = struct.unpack_from("<Q", data, at + 24)
+        if n > 8:                                  # the text of the magic elsewhere
+            continue
+        pos = at + 32
+        for _ in range(n):
+            off, size, length = struct.unpack_from("<QQQ", data, pos)
+            name = data[pos + 24:pos + 24 + length]
+            pos += 24 + length
+            if name.endswith(b"gfx950"):
+                yield data[at + off:at + off + size]
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    if not os.path.exists(build.LIB):
+        build.build_library()
+    readelf = os.path.join(os.path.dirname(os.path.dirname(build.HIPCC)), "lib", "llvm", "bin", "llvm-readelf")
+    found = {}
+    for i, co in enumerate(_code_objects(build.LIB)):
+        path = str(tmp_path_factory.mktemp("co") / ("%d.co" % i))
+        open(path, "wb").write(co)
+        notes = subprocess.run([readelf, "--notes", path], check=True, stdout=subprocess.PIPE, text=True).stdout
+        for block in notes.split("- .agpr_count")[1:]:
+            get = lambda key: re.search(r"\.%s:\s+(\S+)" % key, block).group(1)
+            found[get("name")] = (int(get("vgpr_count")), int(get("private_segment_fixed_size")))
+    assert found
+    return found
+
+
+def _tile(name):
+    """Rows and columns of a bf16 tile on cache lines with one group of wavefronts, from the parameters in its mangled name."""
+    m = re.search(r"sfb_bf16_\w*kernel\w*3CfgILi(\d)ELi(\d)ELi(\d)ELi(\d)ELi\dELi\dELi1ELi1EE.*RowsE2E", name)
+    return m and (32 * int(m.group(1)) * int(m.group(3)), 32 * int(m.group(2)) * int(m.group(4)))
+
+
+def test_no_bf16_reconstruction_spills(kernels):
+    bf16 = {n: k for n, k in kernels.items() if "sfb_bf16" in n}
+    assert len(bf16) > 20
+    assert not {n: k for n, k in bf16.items() if k[1] > 0}
+
+
+def test_the_parameter_server_sum_finds_registers_beside_two_bf16_tiles_on_lines(kernels):
+    """Two workgroups of a compute unit are two wavefronts on each SIMD.  (Tiles of 128 x 256 hold half of its registers in sums.)"""
+    up = lambda n: -(-n // 8) * 8
+    dense, = {up(k[0]) for n, k in kernels.items() if "dense_ps_table" in n}
+    tiles = {(_tile(n), up(k[0])) for n, k in kernels.items() if _tile(n)}
+    assert {t for t, _ in tiles} == {(128, 256), (128, 192), (128, 128), (64, 128), (64, 64)}
+    for tile, regs in tiles:
+        if tile != (128, 256):
+            assert 2 * regs + dense <= SIMD_REGISTERS, (tile, regs, dense)
