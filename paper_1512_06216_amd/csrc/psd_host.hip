@@ -218,9 +218,10 @@ size_t psd_sfb_workspace_bytes(const psd_plan* plan, int32_t factor_dtype)
     return static_cast<size_t>(splits) * static_cast<size_t>(sfb_part_stride(plan->N, plan->M)) * sizeof(float);
 }
 
-psd_status psd_sync_fc_sfb(const psd_plan* plan, int32_t factor_dtype, const void* U, int64_t ldu,
-                           const void* V, int64_t ldv, float* W, float* Mom, float lr, float mu, float wd,
-                           void* workspace, size_t workspace_bytes, void* stream)
+// beside: another large layer of the same step runs on another stream (choose_bf16)
+static psd_status sync_sfb(const psd_plan* plan, int32_t factor_dtype, const void* U, int64_t ldu, const void* V, int64_t ldv,
+                           float* W, float* Mom, float lr, float mu, float wd, void* workspace, size_t workspace_bytes,
+                           bool beside, void* stream)
 {
     int splits;
     const psd_status bad = check_sfb(plan, factor_dtype, U, ldu, V, ldv, W, Mom, wd, workspace, workspace_bytes, &splits);
@@ -232,7 +233,14 @@ psd_status psd_sync_fc_sfb(const psd_plan* plan, int32_t factor_dtype, const voi
         return launch_sfb_f32(static_cast<const float*>(U), ldu, static_cast<const float*>(V), ldv, W, Mom,
                               plan->N, plan->M, K, lr, mu, wd, part, splits, st);
     return launch_sfb_bf16(static_cast<const uint16_t*>(U), ldu, static_cast<const uint16_t*>(V), ldv, W, Mom,
-                           plan->N, plan->M, K, lr, mu, wd, part, splits, st);
+                           plan->N, plan->M, K, lr, mu, wd, part, splits, beside, st);
+}
+
+psd_status psd_sync_fc_sfb(const psd_plan* plan, int32_t factor_dtype, const void* U, int64_t ldu,
+                           const void* V, int64_t ldv, float* W, float* Mom, float lr, float mu, float wd,
+                           void* workspace, size_t workspace_bytes, void* stream)
+{
+    return sync_sfb(plan, factor_dtype, U, ldu, V, ldv, W, Mom, lr, mu, wd, workspace, workspace_bytes, false, stream);
 }
 
 int32_t psd_sfb_blocks_supported(const psd_plan* plan, int32_t factor_dtype, int64_t ldu, int64_t ldv)
@@ -242,9 +250,9 @@ int32_t psd_sfb_blocks_supported(const psd_plan* plan, int32_t factor_dtype, int
     return (factor_dtype == PSD_F32 ? sfb_f32_blocks_supported(plan->B) : sfb_bf16_blocks_supported(plan->B)) ? 1 : 0;
 }
 
-psd_status psd_sync_fc_sfb_blocks(const psd_plan* plan, int32_t factor_dtype, const void* const* U_p, int64_t ldu,
-                                  const void* const* V_p, int64_t ldv, float* W, float* Mom, float lr, float mu,
-                                  float wd, void* stream)
+static psd_status sync_sfb_blocks(const psd_plan* plan, int32_t factor_dtype, const void* const* U_p, int64_t ldu,
+                                  const void* const* V_p, int64_t ldv, float* W, float* Mom, float lr, float mu, float wd,
+                                  bool beside, void* stream)
 {
     const psd_status bad = check_blocks(plan, factor_dtype, U_p, ldu, V_p, ldv, W, Mom, wd);
     if (bad != PSD_OK) return bad;
@@ -255,7 +263,14 @@ psd_status psd_sync_fc_sfb_blocks(const psd_plan* plan, int32_t factor_dtype, co
                                      plan->M, lr, mu, wd, st);
     return launch_sfb_bf16_blocks(reinterpret_cast<const uint16_t* const*>(U_p), ldu,
                                   reinterpret_cast<const uint16_t* const*>(V_p), ldv, plan->P, plan->B, W, Mom, plan->N,
-                                  plan->M, lr, mu, wd, st);
+                                  plan->M, lr, mu, wd, beside, st);
+}
+
+psd_status psd_sync_fc_sfb_blocks(const psd_plan* plan, int32_t factor_dtype, const void* const* U_p, int64_t ldu,
+                                  const void* const* V_p, int64_t ldv, float* W, float* Mom, float lr, float mu,
+                                  float wd, void* stream)
+{
+    return sync_sfb_blocks(plan, factor_dtype, U_p, ldu, V_p, ldv, W, Mom, lr, mu, wd, false, stream);
 }
 
 psd_status psd_sync_fc_bias(const psd_plan* plan, int32_t factor_dtype, const void* U, int64_t ldu, float* bias,
@@ -389,6 +404,22 @@ psd_status sync_ps_group(const psd_layer_task* layers, int32_t lo, int32_t hi, f
     return PSD_OK;
 }
 
+// Do large bf16 reconstructions among these layers run on different streams?
+bool large_layers_meet(int32_t L, const psd_layer_task* layers, int32_t rule)
+{
+    const psd_layer_task* first = nullptr;
+    for (int32_t l = 0; l < L; ++l) {
+        const psd_layer_task& t = layers[l];
+        const int32_t route = rule == PSD_RULE_ALG3 ? t.plan.route_alg3 : t.plan.route_vs_dense;
+        if (t.factor_dtype != PSD_BF16 || (route != PSD_ROUTE_SFB && route != PSD_ROUTE_SF_PS) || !valid_plan_sizes(&t.plan) ||
+            !large_bf16(t.plan.N, t.plan.M, device_cu_count()))
+            continue;
+        if (!first) first = &t;
+        else if (first->stream != t.stream) return true;
+    }
+    return false;
+}
+
 // the arguments of an FC layer that goes through the factors, as its entry points will check them
 psd_status check_factor_layer(const psd_layer_task& t, float wd)
 {
@@ -456,6 +487,7 @@ psd_status psd_sync_iteration(int32_t L, const psd_layer_task* layers, float lr,
         const psd_status r = sync_ps_group(layers, first_lo, first_hi, lr, mu, wd);
         if (r != PSD_OK) return r;
     }
+    const bool beside = large_layers_meet(L, layers, rule);
     for (int32_t l = L - 1; l >= 0; --l) {
         const psd_layer_task& t = layers[l];
         const int32_t route = rule == PSD_RULE_ALG3 ? t.plan.route_alg3 : t.plan.route_vs_dense;
@@ -490,16 +522,16 @@ psd_status psd_sync_iteration(int32_t L, const psd_layer_task* layers, float lr,
             if (!t.U && !t.V) {
                 // no stacked buffers given: delta_p / act_p hold blocks of factor_dtype, read where they lie
                 if (t.ev_begin) PSD_HIP_TRY(hipEventRecord(static_cast<hipEvent_t>(t.ev_begin), st));
-                r = psd_sync_fc_sfb_blocks(&t.plan, t.factor_dtype, t.delta_p, t.ldu ? t.ldu : t.plan.N, t.act_p,
-                                           t.ldv ? t.ldv : t.plan.M, t.W, t.Mom, lr, mu, wd, t.stream);
+                r = sync_sfb_blocks(&t.plan, t.factor_dtype, t.delta_p, t.ldu ? t.ldu : t.plan.N, t.act_p,
+                                    t.ldv ? t.ldv : t.plan.M, t.W, t.Mom, lr, mu, wd, beside, t.stream);
             } else {
                 r = psd_pack_factors(&t.plan, static_cast<const float* const*>(static_cast<const void*>(t.delta_p)),
                                      static_cast<const float* const*>(static_cast<const void*>(t.act_p)), t.factor_dtype,
                                      t.U, t.ldu, t.V, t.ldv, t.stream);
                 if (r == PSD_OK && t.ev_begin) PSD_HIP_TRY(hipEventRecord(static_cast<hipEvent_t>(t.ev_begin), st));
                 if (r == PSD_OK)
-                    r = psd_sync_fc_sfb(&t.plan, t.factor_dtype, t.U, t.ldu, t.V, t.ldv, t.W, t.Mom, lr, mu, wd,
-                                        t.workspace, t.workspace_bytes, t.stream);
+                    r = sync_sfb(&t.plan, t.factor_dtype, t.U, t.ldu, t.V, t.ldv, t.W, t.Mom, lr, mu, wd,
+                                 t.workspace, t.workspace_bytes, beside, t.stream);
             }
         } else {
             return PSD_E_INVALID;

@@ -80,7 +80,7 @@ psd_status launch_sfb_f32_planes_blocks(int tile, const float* const* U_p, int64
                                         int64_t B, float* W, float* Mom, int64_t N, int64_t M, float lr, float mu, float wd, hipStream_t st);
 psd_status launch_sfb_bf16(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t ldv, float* W, float* Mom,
                            int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int most_splits,
-                           hipStream_t st);
+                           bool beside, hipStream_t st);       // beside: see choose_bf16
 // reconstruction straight from the P per-worker blocks (B x ld each, no stacked copy); served when a block
 // holds whole k-stages of the kernel (16 rows fp32, 32 rows bf16)
 bool sfb_f32_blocks_supported(int64_t B);
@@ -90,7 +90,7 @@ psd_status launch_sfb_f32_blocks(const float* const* U_p, int64_t ldu, const flo
                                  hipStream_t st);
 psd_status launch_sfb_bf16_blocks(const uint16_t* const* U_p, int64_t ldu, const uint16_t* const* V_p, int64_t ldv,
                                   int64_t P, int64_t B, float* W, float* Mom, int64_t N, int64_t M, float lr, float mu,
-                                  float wd, hipStream_t st);
+                                  float wd, bool beside, hipStream_t st);
 // how many ways each kernel may split K for this layer when it is given a workspace (1 = not at all)
 int sfb_f32_splits(int64_t N, int64_t M, int64_t K);
 int sfb_bf16_splits(int64_t N, int64_t M, int64_t K);

@@ -232,13 +232,28 @@ inline double split_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K, int
     return sum + t.first + t.solo * k;              // (the partial sums stay in the caches)
 }
 
-// tile choice for one layer; pinned: one of the first three tiles, or less than 0
-inline Bf16Tile choose_bf16(int64_t N, int64_t M, int64_t K, int64_t cus, int pinned)
+// A reconstruction that fills the chip for long: more than two rounds of 128 x 256 tiles, two to a compute unit.  Where another one
+// runs on another stream of the same step, an XCD's L2 holds panels of U and V of both, and the tile that reads least of them is the
+// better one, if not alone (9216 -> 4096 200 us with 128 x 192, 204 with 128 x 256).  AlexNet's convolution sums and two such layers,
+// us a step with the tiles chosen for lone layers and with this: 9216 -> 4096 and 4096 -> 21841, K = 2048 853 and 781 (820 with
+// 128 x 192 for both, before their loop and update became what they are);
+// 9216 -> 4096 and 4096 -> 12288, K = 512 368 and 363, K = 1024 433 and 424, K = 2048 654 and 580, K = 4096 1166 and 1036;
+// 6144 -> 6144 twice, K = 1024 391 and 383, K = 2048 586 and 522; 9217 -> 4097 and 4097 -> 21841, off lines, 848 and 856.  With two
+// rounds or less beside: 9216 -> 4096 and 4096 -> 8192, K = 2048 489 and 499, 4096 -> 6144, K = 4096 665 and 727; AlexNet 435 and 449.
+inline bool large_bf16(int64_t N, int64_t M, int64_t cus)
+{
+    return ((N + kTiles[0].tn - 1) / kTiles[0].tn) * ((M + kTiles[0].tm - 1) / kTiles[0].tm) > 4 * cus;
+}
+
+// tile choice for one layer; pinned: one of the first three tiles, or less than 0; beside: another large layer of the step runs
+// on another stream
+inline Bf16Tile choose_bf16(int64_t N, int64_t M, int64_t K, int64_t cus, int pinned, bool beside = false)
 {
     if (pinned >= 0 && pinned <= 2) return kTiles[pinned];
     const Bf16Tile* best = &kTiles[0];
     for (const Bf16Tile& t : kTiles)
         if (launch_cost(t, N, M, K, cus) < launch_cost(*best, N, M, K, cus)) best = &t;
+    if (beside && best->id == 1 && large_bf16(N, M, cus)) best = &kTiles[0];
     return *best;
 }
 
@@ -250,9 +265,9 @@ inline Bf16Tile choose_bf16(int64_t N, int64_t M, int64_t K, int64_t cus, int pi
 inline int lone_groups_bf16(int64_t K) { return K <= 896 ? 2 : 4; }
 
 // ... and how many ways to split the sum over k, at most `most`
-inline Bf16Tile choose_bf16_split(int64_t N, int64_t M, int64_t K, int most, int64_t cus, int pinned, int* splits)
+inline Bf16Tile choose_bf16_split(int64_t N, int64_t M, int64_t K, int most, int64_t cus, int pinned, int* splits, bool beside = false)
 {
-    Bf16Tile best = choose_bf16(N, M, K, cus, pinned);
+    Bf16Tile best = choose_bf16(N, M, K, cus, pinned, beside);
     *splits = 1;
     if (pinned >= 0) {
         *splits = most;

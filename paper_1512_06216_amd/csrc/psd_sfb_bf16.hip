@@ -567,10 +567,10 @@ int sfb_bf16_splits(int64_t N, int64_t M, int64_t K)
 
 psd_status launch_sfb_bf16(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t ldv, float* W, float* Mom,
                            int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int most_splits,
-                           hipStream_t st)
+                           bool beside, hipStream_t st)
 {
     int splits;
-    Bf16Tile t = choose_bf16_split(N, M, K, most_splits, device_cu_count(), tune_value(PSD_TUNE_SFB_BF16_TILE), &splits);
+    Bf16Tile t = choose_bf16_split(N, M, K, most_splits, device_cu_count(), tune_value(PSD_TUNE_SFB_BF16_TILE), &splits, beside);
     // the longer stages of the grouped tiles read further ahead than the 32-bit offsets reach in a very large factor matrix
     if (t.most > 0 && !factors_in_reach(K, ldu, ldv, 2, bf16_reserve(t.id == 5 ? Cfg64x64w16::KT : Cfg128x128w8::KT)))
         t = kTiles[t.id == 6 ? 2 : 4];
@@ -593,7 +593,7 @@ bool sfb_bf16_blocks_supported(int64_t B) { return B % SLICE == 0; }
 
 psd_status launch_sfb_bf16_blocks(const uint16_t* const* U_p, int64_t ldu, const uint16_t* const* V_p, int64_t ldv,
                                   int64_t P, int64_t B, float* W, float* Mom, int64_t N, int64_t M, float lr, float mu,
-                                  float wd, hipStream_t st)
+                                  float wd, bool beside, hipStream_t st)
 {
     if (P < 1 || P > PSD_MAX_WORKERS || !sfb_bf16_blocks_supported(B)) return PSD_E_UNSUPPORTED;
     BlockPtrs blocks;
@@ -601,7 +601,7 @@ psd_status launch_sfb_bf16_blocks(const uint16_t* const* U_p, int64_t ldu, const
         blocks.u[p] = p < P ? U_p[p] : nullptr;
         blocks.v[p] = p < P ? V_p[p] : nullptr;
     }
-    const Bf16Tile t = choose_bf16(N, M, P * B, device_cu_count(), tune_value(PSD_TUNE_SFB_BF16_TILE));
+    const Bf16Tile t = choose_bf16(N, M, P * B, device_cu_count(), tune_value(PSD_TUNE_SFB_BF16_TILE), beside);
     switch (t.id) {
         case 0: return launch_cfg_blocks<Cfg128x256w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         case 1: return launch_cfg_blocks<Cfg128x192w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);

@@ -1427,6 +1427,37 @@ def _oracle_layer(L):
     return orc.sync_fc_sfb(U, V, L["W"], L["Mom"], 0.25, 0.5)
 
 
+@pytest.mark.parametrize("blocks", [False, True])
+def test_iteration_of_two_large_layers_beside_each_other_has_the_bits_of_each_alone(blocks):
+    """On streams of their own both get the tile that reads least of the factors; rows of W on lines and anywhere."""
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    tasks, alone = [], []
+    for M, N in ((9216, 4096), (6147, 6200)):
+        plan = psd.plan_layer(psd.LAYER_FC, M, N, 128, 8)
+        one = psd.plan_layer(psd.LAYER_FC, M, N, 128, 1)
+        delta, act = ([torch.randn(128, cols, device=DEV, generator=gen) for _ in range(8)] for cols in (N, M))
+        W, Mom = (torch.randn(N, M, device=DEV, generator=gen) for _ in range(2))
+        t = dict(plan=plan, factor_dtype=psd.BF16, delta=delta, act=act, W=W.clone(), Mom=Mom.clone(), stream=torch.cuda.Stream(device=DEV))
+        if blocks:
+            U, ldu, V, ldv = zip(*[psd.alloc_factors(one, psd.BF16, DEV) for _ in range(8)])
+            for p in range(8):
+                psd.pack_factors(one, [delta[p]], [act[p]], psd.BF16, U[p], ldu[p], V[p], ldv[p])
+            t.update(U=None, V=None, delta=list(U), act=list(V), ldu=ldu[0], ldv=ldv[0])
+            psd.sync_fc_sfb_blocks(plan, psd.BF16, list(U), ldu[0], list(V), ldv[0], W, Mom, inputs.LR, inputs.MU)
+        else:
+            U, ldu, V, ldv = psd.alloc_factors(plan, psd.BF16, DEV)
+            t.update(U=U, V=V, ldu=ldu, ldv=ldv)
+            psd.pack_factors(plan, delta, act, psd.BF16, U, ldu, V, ldv)
+            psd.sync_fc_sfb(plan, psd.BF16, U, ldu, V, ldv, W, Mom, inputs.LR, inputs.MU)
+        tasks.append(t)
+        alone.append((W, Mom))
+    torch.cuda.synchronize()
+    psd.Iteration(tasks).run(inputs.LR, inputs.MU, psd.RULE_ALG3)
+    torch.cuda.synchronize()
+    for t, (W, Mom) in zip(tasks, alone):
+        assert torch.equal(t["W"], W) and torch.equal(t["Mom"], Mom)
+
+
 @pytest.mark.parametrize("streams_of", ["own", "shared", "default"])
 def test_iteration_of_layers_behind_one_event_that_fires_late(streams_of):
     """All layers name one event, which fires long after the call: the gradients are written by another stream meanwhile.  On

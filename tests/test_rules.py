@@ -21,7 +21,7 @@ def rules(tmp_path_factory):
                             ("pack_rows", i64, [i64, i64]), ("divided", ctypes.c_uint32, [ctypes.c_uint32, ctypes.c_uint32]), ("f32_reach", i32, [i64, i64, i64]),
                             ("bf16_reach", i32, [i64, i64, i64, i64]), ("bf16_choice", i32, [i64, i64, i64, c_int, i64]),
                             ("splits_asked", i32, [i64, i64, i64]), ("bf16_cost", ctypes.c_double, [i32, i64, i64, i64, i64]),
-                            ("sum_first", i32, [i32] + [ctypes.c_double] * 4), ("bf16_few", i32, [i64, i64, i64]), ("f32_choice", i32, [i64, i64, i64, i64]),
+                            ("sum_first", i32, [i32] + [ctypes.c_double] * 4), ("bf16_few", i32, [i64, i64, i64]), ("bf16_choice_beside", i32, [i64] * 4), ("bf16_large", i32, [i64] * 3), ("f32_choice", i32, [i64, i64, i64, i64]),
                             ("f32_planes", i32, [i64, i64, i64, i64]), ("f32_splits", i32, [i64, i64, i64, c_int, i64])):
         getattr(L, name).restype, getattr(L, name).argtypes = res, args
     return L
@@ -187,6 +187,16 @@ def test_bf16_tiles_of_layers_that_were_measured(rules):
         assert rules.bf16_choice(4096, 8192, K, 1, CUS) == rules.bf16_choice(4096, 8192, 1024, 1, CUS)
     for K in (64, 128, 224, 255, 256, 288):
         assert rules.bf16_choice(4096, 4096, K, 1, CUS) // 10 in (3, 4)
+
+
+def test_large_bf16_layers_beside_each_other_read_least_of_the_factors(rules):
+    for M, N, K, alone, beside, large in (
+            (9216, 4096, 2048, 1, 0, 1), (9216, 4096, 1024, 1, 0, 1), (9216, 4096, 1023, 1, 0, 1), (4096, 21841, 2048, 0, 0, 1),
+            (4096, 9216, 2048, 0, 0, 1), (6144, 6144, 2048, 1, 0, 1), (4096, 8192, 2048, 0, 0, 0), (4096, 4096, 2048, 0, 0, 0),
+            (3000, 3000, 2048, 1, 1, 0), (9216, 3000, 2048, 1, 1, 0), (4096, 1000, 2048, 6, 6, 0), (9216, 4096, 64, None, None, 1)):
+        choice = rules.bf16_choice(N, M, K, 1, CUS) // 10
+        assert alone in (None, choice) and rules.bf16_choice_beside(N, M, K, CUS) == (choice if beside is None else beside), (M, N, K)
+        assert rules.bf16_large(N, M, CUS) == large, (M, N, K)
 
 
 def test_layers_of_the_parity_tests_go_to_the_pipe_they_stand_for(rules):
