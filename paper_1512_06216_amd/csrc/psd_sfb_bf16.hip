@@ -470,7 +470,7 @@ sfb_bf16_blocks_kernel(BlockPtrs blocks, int n_blocks, int block_rows, int64_t l
 
 // where the rows of W and Mom start, for the tile C (cache lines have 128 bytes)
 template <class C>
-Rows rows_at(const float* W, const float* Mom, int64_t N, int64_t M, int64_t K)
+Rows rows_at(const float* W, const float* Mom, int64_t N, int64_t M)
 {
     if (C::G > 1) return ANYWHERE;
     if (M % 32 == 0 && (reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(Mom)) % 128 == 0)
@@ -490,7 +490,7 @@ psd_status launch_cfg_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int6
     const int64_t tiles = tiles_n * tiles_m;
     if (tiles < 1 || tiles > 0x3fffffff) return PSD_E_INVALID;
     const int64_t u_bytes = B * ldu * 2, v_bytes = B * ldv * 2;          // one block
-    const Rows at = rows_at<C>(W, Mom, N, M, P * B);
+    const Rows at = rows_at<C>(W, Mom, N, M);
     auto kern = at == ON_LINES       ? sfb_bf16_blocks_kernel<C, kOnLines<C>>
                 : at == ANYWHERE_FEW ? sfb_bf16_blocks_kernel<C, kFew<C>> : sfb_bf16_blocks_kernel<C, ANYWHERE>;
     static std::atomic<bool> attr_done{false};
@@ -519,7 +519,7 @@ psd_status launch_cfg(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t
     static_assert(C::NSTAGE <= kBf16Stages, "the reserve covers the ring");
     const int64_t u_bytes = K * ldu * 2, v_bytes = K * ldv * 2;
     constexpr bool alone = C::G == 1;            // groups are not split
-    const Rows at = rows_at<C>(W, Mom, N, M, K);
+    const Rows at = rows_at<C>(W, Mom, N, M);
     auto kern = splits > 1 ? sfb_bf16_kernel<C, alone, ANYWHERE>
                 : at == ON_LINES     ? sfb_bf16_kernel<C, false, kOnLines<C>>
                 : at == ANYWHERE_FEW ? sfb_bf16_kernel<C, false, kFew<C>> : sfb_bf16_kernel<C, false, ANYWHERE>;
