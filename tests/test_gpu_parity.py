@@ -273,17 +273,41 @@ def test_sfb_bf16_every_tile_shape_bit_exact(tile, M, N, B, P, pinned_tile):
     assert np.array_equal(Mg, Mr) and np.array_equal(Wg, Wr)
 
 
-@pytest.mark.parametrize("K", [1, 32, 33, 64, 96, 97, 128, 129, 160, 193])
-@pytest.mark.parametrize("tile", [0, 1, 2])
-def test_sfb_bf16_stages_around_the_depth_of_the_ring_bit_exact(tile, K, pinned_tile):
-    """1 .. 7 stages of 32 k rows, even and odd in number, whole and not, on a ring of three or four; rows of W on lines and not."""
-    pinned_tile(psd.TUNE_SFB_BF16_TILE, tile)
-    for M in (416, 414):
-        d = inputs.fc_layer_integer(M=M, N=300, B=K, P=1, seed=tile + K)
-        Wg, Mg, _ = run_sfb(d, psd.BF16, 0.25, 0.5)
-        U, V = orc.pack_factors(d["delta"], d["act"])
-        Wr, Mr = orc.sync_fc_sfb(U, V, d["W"], d["Mom"], 0.25, 0.5)
-        assert np.array_equal(Mg, Mr) and np.array_equal(Wg, Wr), M
+# Around the depth of the ring of LDS buffers, four stages and three for the first tile: sums of fewer, as many and more stages, whole
+# and not.  A stage is 32 k rows, and 64 or 128 where two or four groups share a tile.  The first three tiles are pinned, the others are what the
+# rules choose for these layers (tests/test_rules.py checks it); sums of less than four stages never get tiles 6 and 7, nor four groups.
+RING_K, RING_K2 = (1, 32, 33, 64, 96, 97, 128, 129, 160, 192, 193), (1, 64, 65, 128, 192, 193, 256, 257, 320, 385, 448)
+BF16_RING_LAYERS = [  # tile, M, N, K
+    (0, 416, 300, RING_K), (0, 414, 300, RING_K), (1, 416, 300, RING_K), (1, 414, 300, RING_K), (2, 416, 300, RING_K), (2, 414, 300, RING_K),
+    (3, 5504, 133, RING_K), (3, 5467, 136, RING_K), (4, 288, 5451, RING_K), (4, 134, 5466, RING_K),
+    (5, 64, 90, RING_K2 + (897, 960, 1024, 1025)), (5, 75, 121, RING_K2 + (897, 960, 1024, 1025)),
+    (6, 4928, 602, (288, 320, 384)), (6, 4939, 452, (320, 384, 385)),
+    (7, 5632, 129, (256, 257, 288, 320, 384, 385, 448, 512)), (7, 5497, 131, (384, 385, 448, 512))]
+
+
+@pytest.mark.parametrize("tile,M,N,sums", BF16_RING_LAYERS)
+def test_sfb_bf16_stages_around_the_depth_of_the_ring_bit_exact(tile, M, N, sums, pinned_tile):
+    """Rows of W on lines and not; stacked and, sums of whole slices, from blocks of one slice and of two, at each of which the
+    descriptors are aimed anew while stages of the block before are in flight."""
+    if tile <= 2:
+        pinned_tile(psd.TUNE_SFB_BF16_TILE, tile)
+    for K in sums:
+        B = 32 if K % 32 == 0 else K
+        d = inputs.fc_layer_integer(M=M, N=N, B=B, P=K // B, seed=tile + K)
+        plan, U, ldu, V, ldv = run_pack(d, psd.BF16)
+        Uo, Vo = orc.pack_factors(d["delta"], d["act"])
+        Wr, Mr = orc.sync_fc_sfb(Uo, Vo, d["W"], d["Mom"], 0.25, 0.5)
+        for rows in (0, 32, 64):
+            if rows and (K % rows or B % 32):
+                continue
+            W, Mom = dev(d["W"]), dev(d["Mom"])
+            if rows:
+                plan = psd.plan_layer(psd.LAYER_FC, M, N, rows, K // rows)
+                psd.sync_fc_sfb_blocks(plan, psd.BF16, list(U.split(rows)), ldu, list(V.split(rows)), ldv, W, Mom, 0.25, 0.5)
+            else:
+                psd.sync_fc_sfb(plan, psd.BF16, U, ldu, V, ldv, W, Mom, 0.25, 0.5)
+            torch.cuda.synchronize()
+            assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr), (K, rows)
 
 
 def test_sfb_bf16_phase_skew_changes_no_bit(pinned_tile):
@@ -657,22 +681,22 @@ def test_sfb_bf16_groups_of_tile_rows_that_start_at_other_columns_bit_exact(M, N
 @pytest.mark.parametrize("M,B", [(544, 5), (544, 342), (572, 11), (577, 11), (602, 5)])
 def test_sfb_bf16_tiles_inside_w_and_at_its_edges_bit_exact(M, B, tile, pinned_tile):
     """Rows on lines, on quads, anywhere and on pairs; W and Mom that start in the middle of
-    a line, between guard values that must survive."""
+    a line, at the same place of it and at different ones, between guard values that must survive."""
     pinned_tile(psd.TUNE_SFB_BF16_TILE, tile)
     d = inputs.fc_layer_integer(M, 300, B=B, P=3, seed=M, amax=2)
     plan, U, ldu, V, ldv = run_pack(d, psd.BF16)
     Uo, Vo = orc.pack_factors(d["delta"], d["act"])
     Wr, Mr = orc.sync_fc_sfb(Uo, Vo, d["W"], d["Mom"], 0.25, 0.5)
     n = 300 * M
-    for lead in (0, 12):
+    for leads in ((0, 0), (12, 12), (12, 20), (0, 4), (28, 32)):        # (bases are 16-byte aligned)
         flat = [torch.full((n + 64,), 77.0, device=DEV) for _ in range(2)]
-        W, Mom = (f[lead:lead + n].view(300, M) for f in flat)
+        W, Mom = (f[lead:lead + n].view(300, M) for f, lead in zip(flat, leads))
         W.copy_(dev(d["W"]))
         Mom.copy_(dev(d["Mom"]))
         psd.sync_fc_sfb(plan, psd.BF16, U, ldu, V, ldv, W, Mom, 0.25, 0.5)
         torch.cuda.synchronize()
         assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr)
-        for f in flat:
+        for f, lead in zip(flat, leads):
             assert bool((f[:lead] == 77).all()) and bool((f[lead + n:] == 77).all())
 
 

@@ -106,6 +106,12 @@ def test_the_parity_tests_reach_every_tile_stacked_from_blocks_and_split(rules):
         seen.add((tile, M % 32 == 0))
     assert seen == {(t, lines) for t in range(7) for lines in (True, False)}
     seen = set()
+    for tile, M, N, sums in parity.BF16_RING_LAYERS:
+        for K in sums:
+            assert tile <= 2 or rules.bf16_choice(N, M, K, 1, CUS) == 10 * tile + 1, (M, N, K)
+        seen.add((tile, M % 32 == 0))
+    assert seen == {(t, lines) for t in range(8) for lines in (True, False)}
+    seen = set()
     for tile, splits, M, N, B, P in parity.BF16_SPLIT_LAYERS:
         most = rules.splits_asked(-(-N // 128) * -(-M // 128), CUS, B * P)
         assert most >= splits and rules.bf16_choice(N, M, B * P, most, CUS) == 10 * tile + splits, (M, N)
