@@ -286,9 +286,11 @@ inline Bf16Tile choose_bf16_split(int64_t N, int64_t M, int64_t K, int most, int
 
 // Does the 64 x 128 tile apply the update of all tiles as at the edges of W (RowUpdate), where rows are not even on quads: with two
 // tiles for each compute unit at most the code for the tiles inside (InnerUpdate) costs more than it saves.  us with and without
-// it: 20281 -> 187, K = 352 (477 tiles) 17.6 and 15.7; 3523 -> 891, K = 92 (392) 15.4 and 13.8; 615 -> 2216, K = 32 (175) 9.0 and
-// 8.0; the other way 2383 -> 593, K = 114 (190) 7.9 and 8.6; of 15 such layers 11 lose 4 to 11 % with it, 4 gain.  On quads 4628 -> 337,
-// K = 140 (222) 8.2 and 8.7, with more tiles 3543 -> 1273, K = 42 (560) 18.5 and 19.1, 21485 -> 397, K = 456 (1176) 37.2 and 44.1.
+// it: 1311 -> 1202, K = 54 (209 tiles) 9.9 and 8.3; 3523 -> 891, K = 96 (392) 15.1 and 13.8; 615 -> 2216, K = 32 (175) 9.0 and
+// 7.6; the other way 4945 -> 728, K = 256 (468) 15.4 and 17.0.  Of the 25 such layers in profiles/fit_bf16_tiles.txt that get this
+// tile 14 take 4 to 19 % longer with it and 7 take 2 to 10 % less, 5 % longer on average; with more tiles 98 of
+// 100 layers take less with it, by 15 % on average, and on quads few tiles do too (4628 -> 337, K = 140, 222 tiles, 8.2 and 8.7, with
+// MFMAs of 32 x 32 x 16 for both).
 inline bool bf16_few_tiles(int64_t N, int64_t M, int64_t tn, int64_t tm, int64_t cus)
 {
     return M % 4 != 0 && ((N + tn - 1) / tn) * ((M + tm - 1) / tm) <= 2 * cus;

@@ -18,9 +18,10 @@
 // L2/HBM round trip (>1 us at the tail), so the tiles travel global -> LDS without passing
 // through registers (buffer_load_dwordx4 ... lds) and up to NSTAGE stages are in flight or read from in
 // an NSTAGE-deep ring of LDS buffers.  The DMA writes whole 1 KiB runs, so rows cannot be
-// padded; bank conflicts of the transposing reads are avoided by XOR-swizzling the 16-byte
-// chunk index of a row with its row number instead.  Rows past the end of K are zero-filled
-// by the buffer range check, so there is no tail code.
+// padded; the 16-byte chunk index of a row is XOR-swizzled with its row number instead.  That leaves the
+// transposing reads of 32 x 32 blocks without bank conflicts; of 16 x 16 blocks the two lane groups served at a time
+// read the same banks (16.5 M cycles in 9216 -> 4096, K = 2048), and an order of k rows without that takes the same time.
+// Rows past the end of K are zero-filled by the buffer range check, so there is no tail code.
 //
 // MFMA operand roles are swapped (rows = m, columns = n) so that the four consecutive
 // accumulator rows a lane owns are four adjacent m of one W row; the epilogue turns them
@@ -282,7 +283,8 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
     //   read the other a and b0 = first half of stage t+1 | MFMA(a, b1)
     // The barrier tells both that every wavefront's share of stage t+1 is visible and that all of them have read the whole of stage
     // t into registers (lgkmcnt), so that the new DMA may overwrite it.  Stages past K are zeros.
-    // us, K = 2048, before (32 x 32 x 16, and the buffer of stage t kept until the next barrier, one stage less in flight) -> now:
+    // us, K = 2048, before (32 x 32 x 16, and the buffer of stage t kept until the next barrier, one stage less in flight) -> with
+    // both, before tiles on lines were updated as now; what each of the two brings to large layers was not measured by itself:
     // 4096 -> 21841 456-470 -> 450-460, 25088 -> 4096 516-533 -> 511-528, 3000 -> 21841 365 -> 360, 4096 -> 6144 143 -> 130,
     // 9216 -> 4096, K = 4096 318-326 -> 315-318; small ones by the stage more in flight: 512 -> 512, K = 4096 (split) 12.6 -> 11.2,
     // 4237 -> 256, K = 3072 27.2 -> 26.6.  Branches that leave out the stages past K cost large layers 2 %.  Waves of 96 x 96 (tiles of
@@ -393,7 +395,8 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
         // group of wavefronts by InnerUpdate, whose batches are whole rows of the tile (768 bytes of W, then of Mom; half of that is
         // up to 7 % slower than all of it: 25088 -> 4096 518 and 580 us); what is left at the edges of W likewise, two lines at a
         // time, on lines, and by RowUpdate off lines, as are the tiles of several groups.  us with a patch of LDS for each wavefront
-        // on lines (128 bytes of 32 rows, then the next) and RowUpdate for every tile off lines -> now, K = 2048 unless said: 25088 -> 4096 531 -> 514, 9216 -> 4096 198 -> 196,
+        // on lines (128 bytes of 32 rows, then the next) and RowUpdate for every tile off lines -> whole rows, the tile the same and
+        // K = 2048 unless said: 25088 -> 4096 531 -> 514, 9216 -> 4096 198 -> 196,
         // 4096 -> 21841 465 -> 460, 3840 -> 2020, K = 56 30.3 -> 27.0, 4096 -> 8192 in 128 x 128, K = 1024 148 -> 128;
         // 3000 -> 21841 395 -> 360, 3001 -> 21841 411 -> 370, 9999 -> 4095 262 -> 233, 2545 -> 15057, K = 1072 209 -> 164,
         // 20280 -> 1582, K = 296 124 -> 104.  (These launches are bound by power, 1.4 kW, or by HBM: RowUpdate has two to three times
