@@ -394,7 +394,7 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
         // rows of the tile's whole width, and while it updates them those of the next eight are on their way.  Tiles inside W of one
         // group of wavefronts by InnerUpdate, whose batches are whole rows of the tile (768 bytes of W, then of Mom; half of that is
         // up to 7 % slower than all of it: 25088 -> 4096 518 and 580 us); what is left at the edges of W likewise, two lines at a
-        // time, on lines, and by RowUpdate off lines, as are the tiles of several groups.  us with a patch of LDS for each wavefront
+        // time, on lines, and by RowUpdate off lines and in the 128 x 256 tile, as are the tiles of several groups.  us with a patch of LDS for each wavefront
         // on lines (128 bytes of 32 rows, then the next) and RowUpdate for every tile off lines -> whole rows, the tile the same and
         // K = 2048 unless said: 25088 -> 4096 531 -> 514, 9216 -> 4096 198 -> 196,
         // 4096 -> 21841 465 -> 460, 3840 -> 2020, K = 56 30.3 -> 27.0, 4096 -> 8192 in 128 x 128, K = 1024 148 -> 128;
@@ -437,8 +437,10 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
                     continue;
                 }
             }
-            if constexpr (!SHIFTED) {
-                // (two lines ahead: with whole rows the 128 x 256 tile runs out of registers)
+            if constexpr (!SHIFTED && C::BM < 4) {
+                // (Not the 128 x 256 tile, which leaves nobody registers in either case and is the slower for it where the edge comes last:
+                // 4096 -> 21841, K = 2048 with its pack and bias 487.6-489.7 us with RowUpdate, 490.8-493.2 with this, and on another
+                // card 490.4 and, four lines ahead, 494.4.)
                 update(InnerUpdate<C::ROWS, C::TM, C::WAVES, 2, true, decltype(row_n), true>(W, Mom, row_n, m0, M, wave, lane, N));
             } else {
                 // (64 x 128 tiles beside InnerUpdate: no deeper than their 168 registers hold)

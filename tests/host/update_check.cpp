@@ -118,7 +118,6 @@ template <class R> struct Inner192 { using type = psd::InnerUpdate<64, 192, 4, 6
 template <class R> struct Lines256 { using type = psd::InnerUpdate<64, 256, 4, 8, true, R>; };
 template <class R> struct Lines192 { using type = psd::InnerUpdate<64, 192, 4, 6, true, R>; };
 template <class R> struct Lines64 { using type = psd::InnerUpdate<64, 64, 4, 2, true, R>; };
-template <class R> struct Edge256 { using type = psd::InnerUpdate<64, 256, 4, 2, true, R, true>; };
 template <class R> struct Edge192 { using type = psd::InnerUpdate<64, 192, 4, 2, true, R, true>; };
 template <class R> struct Edge128 { using type = psd::InnerUpdate<64, 128, 4, 2, true, R, true>; };
 template <class R> struct Edge64 { using type = psd::InnerUpdate<64, 64, 4, 2, true, R, true>; };
@@ -153,7 +152,7 @@ int main()
     ok = ok && layer<Lines64, 64, 64, 4, 1, 1, false, true>(130, 160, 0, "bf16, inside, on lines, 64 x 64");
     for (int64_t M : {32, 64, 96, 160, 224, 256, 288, 544})
         for (int64_t N : {1, 63, 70, 133}) {
-            ok = ok && layer<Edge256, 64, 256, 4, 1, 2, false, false, true>(N, M, 0, "bf16, edges, on lines, 128 x 256");
+            ok = ok && layer<Bf16w256, 64, 256, 4, 1, 2, false, false>(N, M, 0, "bf16, edges, on lines, 128 x 256");
             ok = ok && layer<Edge192, 64, 192, 4, 1, 2, false, false, true>(N, M, 0, "bf16, edges, on lines, 128 x 192");
             ok = ok && layer<Edge128, 64, 128, 4, 1, 2, false, false, true>(N, M, 32, "bf16, edges, on lines, 128 x 128");
             ok = ok && layer<Edge128, 64, 128, 4, 1, 1, false, false, true>(N, M, 0, "bf16, edges, on lines, 64 x 128");
