@@ -393,8 +393,8 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
         // The rows of one bn of all wavefronts go through LDS at a time and come back as whole lines of W: a wavefront takes eight
         // rows of the tile's whole width, and while it updates them those of the next eight are on their way.  Tiles inside W of one
         // group of wavefronts by InnerUpdate, whose batches are whole rows of the tile (768 bytes of W, then of Mom; half of that is
-        // up to 7 % slower than all of it: 25088 -> 4096 518 and 580 us); what is left at the edges of W likewise, two lines at a
-        // time, on lines, and by RowUpdate off lines and in the 128 x 256 tile, as are the tiles of several groups.  us with a patch of LDS for each wavefront
+        // up to 7 % slower than all of it: 25088 -> 4096 518 and 580 us); what is left at the edges of W likewise,
+        // on lines, and by RowUpdate off lines and in the 128 x 256 tile, as are the tiles of several groups.  us with a patch of LDS for each wavefront
         // on lines (128 bytes of 32 rows, then the next) and RowUpdate for every tile off lines -> whole rows, the tile the same and
         // K = 2048 unless said: 25088 -> 4096 531 -> 514, 9216 -> 4096 198 -> 196,
         // 4096 -> 21841 465 -> 460, 3840 -> 2020, K = 56 30.3 -> 27.0, 4096 -> 8192 in 128 x 128, K = 1024 148 -> 128;
@@ -438,10 +438,14 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
                 }
             }
             if constexpr (!SHIFTED && C::BM < 4) {
+                // Whole rows here too: a tile at the edge that comes last, or in the only round, is what the launch waits for.  us with two
+                // lines at a time, with whole rows, and with RowUpdate: 1120 -> 4096, K = 1024 35.2, 26.5 and 27.2; 3392 -> 1895, K = 768 34.9,
+                // 30.0 and 29.8; 2528 -> 3000, K = 1024 38.1, 34.9 and 34.5; 4128 -> 4096, K = 512 64.2, 63.0 and 63.0; 4096 -> 3089,
+                // K = 1024 54.6, 54.6 and 55.7.
                 // (Not the 128 x 256 tile, which leaves nobody registers in either case and is the slower for it where the edge comes last:
                 // 4096 -> 21841, K = 2048 with its pack and bias 487.6-489.7 us with RowUpdate, 490.8-493.2 with this, and on another
                 // card 490.4 and, four lines ahead, 494.4.)
-                update(InnerUpdate<C::ROWS, C::TM, C::WAVES, 2, true, decltype(row_n), true>(W, Mom, row_n, m0, M, wave, lane, N));
+                update(InnerUpdate<C::ROWS, C::TM, C::WAVES, C::TM / 32, true, decltype(row_n), true>(W, Mom, row_n, m0, M, wave, lane, N));
             } else {
                 // (64 x 128 tiles beside InnerUpdate: no deeper than their 168 registers hold)
                 constexpr int DEPTH = C::BM == 4 ? 4 : C::BM == 1 ? 6 : C::FEW && INNER ? 4 : 5;

@@ -212,7 +212,7 @@ struct RowUpdate {
 // before its first whole quad and behind its last are taken one by one, as in RowUpdate.  ON_LINES: rows of W and Mom start on
 // lines (no shift at all).  EDGE, on lines: a tile at the edges of W, of which rows past N (then to be given) and lines past M are
 // left out.  The lines are whole, so that it needs no more than two comparisons, and far fewer registers than RowUpdate: beside it
-// the bf16 tiles on lines take 188 (128 x 192), 140, 104 and 76 (64 x 64) registers; beside RowUpdate 232, 203, 144, 96.
+// the bf16 tiles on lines take 215 (128 x 192), 151, 124 and 76 (64 x 64) registers; beside RowUpdate 232, 203, 144, 96.
 template <int ROWS, int WIDTH, int WAVES, int DEPTH, bool ON_LINES, class RowN, bool EDGE = false>
 struct InnerUpdate {
     static constexpr int LINES = WIDTH / 32, GROUPS = ROWS / 8 / WAVES;       // a wavefront's groups of eight rows

@@ -118,8 +118,8 @@ template <class R> struct Inner192 { using type = psd::InnerUpdate<64, 192, 4, 6
 template <class R> struct Lines256 { using type = psd::InnerUpdate<64, 256, 4, 8, true, R>; };
 template <class R> struct Lines192 { using type = psd::InnerUpdate<64, 192, 4, 6, true, R>; };
 template <class R> struct Lines64 { using type = psd::InnerUpdate<64, 64, 4, 2, true, R>; };
-template <class R> struct Edge192 { using type = psd::InnerUpdate<64, 192, 4, 2, true, R, true>; };
-template <class R> struct Edge128 { using type = psd::InnerUpdate<64, 128, 4, 2, true, R, true>; };
+template <class R> struct Edge192 { using type = psd::InnerUpdate<64, 192, 4, 6, true, R, true>; };
+template <class R> struct Edge128 { using type = psd::InnerUpdate<64, 128, 4, 4, true, R, true>; };
 template <class R> struct Edge64 { using type = psd::InnerUpdate<64, 64, 4, 2, true, R, true>; };
 template <class R> struct InnerLines { using type = psd::InnerUpdate<64, 128, 4, 4, true, R>; };
 
