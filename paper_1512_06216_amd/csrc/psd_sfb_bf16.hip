@@ -441,7 +441,8 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
                 // Whole rows here too: a tile at the edge that comes last, or in the only round, is what the launch waits for.  us with two
                 // lines at a time, with whole rows, and with RowUpdate: 1120 -> 4096, K = 1024 35.2, 26.5 and 27.2; 3392 -> 1895, K = 768 34.9,
                 // 30.0 and 29.8; 2528 -> 3000, K = 1024 38.1, 34.9 and 34.5; 4128 -> 4096, K = 512 64.2, 63.0 and 63.0; 4096 -> 3089,
-                // K = 1024 54.6, 54.6 and 55.7.
+                // K = 1024 54.6, 54.6 and 55.7.  Three lines in the 128 x 192 tile leave a sum beside it 27 registers more on each wavefront and
+                // AlexNet's step the same (432.7 and 433.1), but 6080 -> 4096, K = 1536 takes 120.5 us and 117.3 with whole rows.
                 // (Not the 128 x 256 tile, which leaves nobody registers in either case and is the slower for it where the edge comes last:
                 // 4096 -> 21841, K = 2048 with its pack and bias 487.6-489.7 us with RowUpdate, 490.8-493.2 with this, and on another
                 // card 490.4 and, four lines ahead, 494.4.)
