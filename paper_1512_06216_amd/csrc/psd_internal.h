@@ -78,6 +78,12 @@ psd_status launch_sfb_f32_planes(int tile, const float* U, int64_t ldu, const fl
                                  int64_t M, int64_t K, float lr, float mu, float wd, hipStream_t st);
 psd_status launch_sfb_f32_planes_blocks(int tile, const float* const* U_p, int64_t ldu, const float* const* V_p, int64_t ldv, int64_t P,
                                         int64_t B, float* W, float* Mom, int64_t N, int64_t M, float lr, float mu, float wd, hipStream_t st);
+// ... for the smallest layers; `tile`: see choose_small_f32 and choose_small_bf16
+psd_status launch_sfb_small(int32_t dtype, const SmallTile& tile, const void* U, int64_t ldu, const void* V, int64_t ldv, float* W, float* Mom,
+                            int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, hipStream_t st);
+psd_status launch_sfb_small_blocks(int32_t dtype, const SmallTile& tile, const void* const* U_p, int64_t ldu, const void* const* V_p, int64_t ldv,
+                                   int64_t P, int64_t B, float* W, float* Mom, int64_t N, int64_t M, float lr, float mu, float wd,
+                                   hipStream_t st);
 psd_status launch_sfb_bf16(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t ldv, float* W, float* Mom,
                            int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, float* part, int most_splits,
                            bool beside, hipStream_t st);       // beside: see choose_bf16

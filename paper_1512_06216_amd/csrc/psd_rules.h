@@ -284,6 +284,32 @@ inline Bf16Tile choose_bf16_split(int64_t N, int64_t M, int64_t K, int most, int
     return best;
 }
 
+// ---- the smallest layers: tiles of 16a x 16b whose wavefronts deal the k rows out (psd_sfb_small.hip)
+// waves = 0: the kernels above are the better ones.  us below: factors from HBM, and in brackets where they have just been stacked.
+// One tile for each compute unit at most.  fp32, always, the smallest tile of which that holds: 32 x 32, 16 x 32 and 16 x 16 take
+// 12.0, 8.7 and 7.5 (11.4, 7.5 and 5.6) for 160 -> 192, K = 2048, but 14.6, 18.8 and 26.4 for 512 -> 512; the kernels above 33.2, and
+// in four by way of a workspace 13.2 (13.8); 768 -> 96, K = 3104 17.8 and 20.2 (14.4 and 17.4).  bf16, unless the sum is split:
+// 399 -> 391, K = 768 6.8 -> 4.8, 256 -> 256, K = 2048 9.9 -> 7.9 (8.5 -> 4.8), 1916 -> 64 14.5 -> 10.6 (8.9 -> 6.1); in four by way
+// of a workspace, which the rule above takes from K = 2048 or so, 1916 -> 64, K = 2048 10.4, 256 -> 256, K = 3072 8.2 and here 10.7.
+// Two tiles for some compute units: fp32 by cost, `us` is that of the kernels above: 3515 -> 125, K = 1024 20.9 -> 16.4, 891 -> 509,
+// K = 256 9.0 -> 6.8, 4091 -> 125, K = 2048 35.7 -> 30.6 but 25.8 when split, 4096 -> 128, K = 512 12.6 both; bf16 up to K = 256:
+// 1211 -> 256 5.5 -> 4.4, K = 64 4.9 -> 3.7, but K = 512 6.1 and 8.0 for 4096 -> 128, 6.2 and 5.8 for 1211 -> 256.
+// With three, 64 x 64 tiles are as fast or faster (550 tiles, fp32, K = 256 9.1 and 9.0, K = 1024 20.2 and 21.9).
+struct SmallTile { int a, b, waves; };
+inline int64_t small_tiles(int64_t N, int64_t M, int a, int b) { return ((N + 16 * a - 1) / (16 * a)) * ((M + 16 * b - 1) / (16 * b)); }
+inline SmallTile choose_small_f32(int64_t N, int64_t M, int64_t K, int64_t cus, double us)
+{
+    if (small_tiles(N, M, 1, 1) <= cus) return {1, 1, 16};
+    if (small_tiles(N, M, 1, 2) <= cus) return {1, 2, 16};
+    if (small_tiles(N, M, 2, 2) <= cus) return {2, 2, 16};
+    return {2, 2, small_tiles(N, M, 2, 2) <= 2 * cus && 3.2 + 12.6 * static_cast<double>(K) / 1024 < us ? 8 : 0};
+}
+inline SmallTile choose_small_bf16(int64_t N, int64_t M, int64_t K, int64_t cus, int splits)
+{
+    const int64_t tiles = small_tiles(N, M, 2, 2);
+    return {2, 2, splits > 1 ? 0 : tiles <= cus ? 16 : tiles <= 2 * cus && K <= 256 ? 8 : 0};
+}
+
 // Does the 64 x 128 tile apply the update of all tiles as at the edges of W (RowUpdate), where rows are not even on quads: with two
 // tiles for each compute unit at most the code for the tiles inside (InnerUpdate) costs more than it saves.  us with and without
 // it: 1311 -> 1202, K = 54 (209 tiles) 9.9 and 8.3; 3523 -> 891, K = 96 (392) 15.1 and 13.8; 615 -> 2216, K = 32 (175) 9.0 and

@@ -580,7 +580,10 @@ psd_status launch_sfb_bf16(const uint16_t* U, int64_t ldu, const uint16_t* V, in
                            bool beside, hipStream_t st)
 {
     int splits;
-    Bf16Tile t = choose_bf16_split(N, M, K, most_splits, device_cu_count(), tune_value(PSD_TUNE_SFB_BF16_TILE), &splits, beside);
+    const int pinned = tune_value(PSD_TUNE_SFB_BF16_TILE);
+    Bf16Tile t = choose_bf16_split(N, M, K, most_splits, device_cu_count(), pinned, &splits, beside);
+    const SmallTile small = choose_small_bf16(N, M, K, device_cu_count(), splits);
+    if (pinned < 0 && small.waves > 0) return launch_sfb_small(PSD_BF16, small, U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, st);
     // the longer stages of the grouped tiles read further ahead than the 32-bit offsets reach in a very large factor matrix
     if (t.most > 0 && !factors_in_reach(K, ldu, ldv, 2, bf16_reserve(t.id == 5 ? Cfg64x64w16::KT : Cfg128x128w8::KT)))
         t = kTiles[t.id == 6 ? 2 : 4];
@@ -606,12 +609,17 @@ psd_status launch_sfb_bf16_blocks(const uint16_t* const* U_p, int64_t ldu, const
                                   float wd, bool beside, hipStream_t st)
 {
     if (P < 1 || P > PSD_MAX_WORKERS || !sfb_bf16_blocks_supported(B)) return PSD_E_UNSUPPORTED;
+    const int pinned = tune_value(PSD_TUNE_SFB_BF16_TILE);
+    const SmallTile small = choose_small_bf16(N, M, P * B, device_cu_count(), 1);
+    if (pinned < 0 && small.waves > 0)
+        return launch_sfb_small_blocks(PSD_BF16, small, reinterpret_cast<const void* const*>(U_p), ldu,
+                                       reinterpret_cast<const void* const*>(V_p), ldv, P, B, W, Mom, N, M, lr, mu, wd, st);
     BlockPtrs blocks;
     for (int64_t p = 0; p < PSD_MAX_WORKERS; ++p) {
         blocks.u[p] = p < P ? U_p[p] : nullptr;
         blocks.v[p] = p < P ? V_p[p] : nullptr;
     }
-    const Bf16Tile t = choose_bf16(N, M, P * B, device_cu_count(), tune_value(PSD_TUNE_SFB_BF16_TILE), beside);
+    const Bf16Tile t = choose_bf16(N, M, P * B, device_cu_count(), pinned, beside);
     switch (t.id) {
         case 0: return launch_cfg_blocks<Cfg128x256w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);
         case 1: return launch_cfg_blocks<Cfg128x192w4>(blocks, P, B, ldu, ldv, W, Mom, N, M, lr, mu, wd, st);

@@ -1,0 +1,291 @@
+// SFB reconstruction with fused momentum-SGD update for the smallest layers, fp32 and bf16 factors (Section 4.3.1 step 3, Eq. 5;
+// Algorithm 3's update line):
+//     dW[n][m] = sum_k U[k][n] * V[k][m] ;  Mom = mu*Mom + lr*dW ;  W = W - Mom
+//
+// A layer with fewer tiles than compute units is bound by how long one tile takes: the fp32 MFMA pipe needs 13.6 us for 1024 k rows of
+// a 64 x 64 tile, and what is left of the chip idles.  Here a workgroup owns 32 x 32, 16 x 32 or 16 x 16 of W, and its 16 (8 where a
+// compute unit holds two) wavefronts deal the k rows out among themselves, 16 (bf16: 32) at a time, each with sums of its own for the
+// whole tile.  So nothing is shared until the end: no ring in LDS and no barrier in the loop; a lane loads from memory just what it
+// feeds to the MFMA (fp32: its columns of four rows; bf16: two neighbouring columns of eight rows, which a byte permutation puts next
+// to each other for the two MFMA blocks they belong to), three slices ahead (two or four: the same within 4 %).  The sums of the
+// wavefronts are added up in pairs in LDS by lanes that own a weight or two each, requested before the loop.
+// What is left is latency: launch, one round trip for W and the first slices, the sum.  us, the kernels for larger tiles -> here, factors
+// from HBM: fp32 256 -> 128, K = 128 5.8 -> 4.3 (launched back to back, which nothing on this host goes below), 300 -> 300, K = 512
+// 11.9 -> 4.4, 399 -> 391, K = 768 16.0 -> 7.2, 512 -> 512, K = 256 7.9 -> 4.4, K = 2048 34.5 -> 14.6 (in four by way of a workspace
+// 17.0), 256 -> 256 33.2 -> 8.3 (13.8), 64 -> 64, K = 4096 62 -> 11.3 (20.2); bf16 399 -> 391, K = 768 6.8 -> 4.8, 1000 -> 256,
+// K = 1024 8.1 -> 6.2, 256 -> 256, K = 2048 9.9 -> 7.9.  Error of dW against 64 bits: fp32 K = 2048 2.9e-7 -> 2.1e-7 with 8 runs over k
+// and 1.6e-7 with 16 (there 4), K = 128 9.0e-8 -> 7.8e-8; bf16, K = 2048 1.1e-7 -> 7.6e-8.
+// Which layers: choose_small_f32 and choose_small_bf16 in psd_rules.h.
+// Each XCD takes a contiguous run of the tiles, along the rows of W: they share columns of U in its L2, and lines of W at their borders
+// (dealt out one by one 731 -> 704, bf16, K = 1024 takes 12.1 us, not 10.0; fp32 the same within 5 %).
+#include <atomic>
+#include "psd_device.h"
+#include "psd_internal.h"
+
+namespace psd {
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int AHEAD = 3;            // slices of k on their way to a wavefront
+
+struct BlockPtrs { const void* u[PSD_MAX_WORKERS]; const void* v[PSD_MAX_WORKERS]; };
+
+struct Args {
+    const void* U; const void* V;
+    int64_t ldu, ldv;
+    float* W; float* Mom;
+    int N, M, K;
+    float lr, mu, wd;
+    int tiles_m, tiles;
+    uint32_t u_bytes, v_bytes;      // of the stacked matrices, or of ONE block
+    int n_blocks, block_rows;       // BLK
+};
+
+// WORDS neighbouring 32-bit words, 0 past the end of what is fed
+template <int WORDS>
+__device__ __forceinline__ void load_or_zero(uint32_t (&x)[WORDS], const Feed& f, uint32_t off)
+{
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(f.base), 0, static_cast<int>(f.left), 0x00020000);
+    if constexpr (WORDS == 2) {
+        const auto y = __builtin_amdgcn_raw_buffer_load_b64(rsrc, off, 0, 0);
+        x[0] = y[0];
+        x[1] = y[1];
+    } else {
+        x[0] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, off, 0, 0);
+    }
+}
+
+// The sums of a wavefront over its slices of k: A x B blocks of 16 x 16, of which block (i, c) stands for the rows n0 + A*r + i and the
+// columns m0 + B*l + c of W.  A lane's accumulator r of a block: row 4*(lane/16) + r, column lane%16.
+template <int A_, int B_>
+struct SumF32 {
+    static constexpr int A = A_, B = B_, SLICE = 16, BYTES = 4;       // k rows of a slice; bytes of an element
+    static constexpr int LOADS = 4, WU = A, WV = B;                   // of a slice, words of each load for the two factors
+    f32x4 acc[A][B] = {};
+    // load j of a lane: row 4*j + lane/16 of the slice, its column of every block
+    static __device__ __forceinline__ int row(int lane, int j) { return 4 * j + (lane >> 4); }
+    static __device__ __forceinline__ int column(int lane, int blocks) { return blocks * (lane & 15); }
+    __device__ __forceinline__ void add(const uint32_t (&u)[LOADS][WU], const uint32_t (&v)[LOADS][WV])
+    {
+#pragma unroll
+        for (int j = 0; j < LOADS; ++j)
+#pragma unroll
+            for (int i = 0; i < A; ++i)
+#pragma unroll
+                for (int c = 0; c < B; ++c)
+                    acc[i][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(u[j][i]), __uint_as_float(v[j][c]), acc[i][c], 0, 0, 0);
+    }
+};
+
+struct SumBf16 {
+    static constexpr int A = 2, B = 2, SLICE = 32, BYTES = 2, LOADS = 8, WU = 1, WV = 1;
+    f32x4 acc[2][2] = {};
+    // load j of a lane: row 8*(lane/16) + j of the slice, its column of both blocks
+    static __device__ __forceinline__ int row(int lane, int j) { return 8 * (lane >> 4) + j; }
+    static __device__ __forceinline__ int column(int lane, int) { return 2 * (lane & 15); }
+    static __device__ __forceinline__ bf16x8 operand(const uint32_t (&x)[LOADS][1], int block)
+    {
+        u32x4 o;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = __builtin_amdgcn_perm(x[2 * q + 1][0], x[2 * q][0], block ? 0x07060302u : 0x05040100u);
+        return __builtin_bit_cast(bf16x8, o);
+    }
+    __device__ __forceinline__ void add(const uint32_t (&u)[LOADS][1], const uint32_t (&v)[LOADS][1])
+    {
+        const bf16x8 a[2] = {operand(u, 0), operand(u, 1)}, b[2] = {operand(v, 0), operand(v, 1)};
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) acc[i][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[c], acc[i][c], 0, 0, 0);
+    }
+};
+
+template <class Sum, int WAVES, bool BLK>
+__device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks)
+{
+    constexpr int SLICE = Sum::SLICE, THREADS = 64 * WAVES, TN = 16 * Sum::A, TM = 16 * Sum::B;
+    constexpr int STRIDE = TM + 8;               // row of a wavefront's sums in LDS, in floats: rows 4 apart fall on other banks
+    constexpr int OWN = (TN * TM + THREADS - 1) / THREADS;         // weights of a lane in the update
+    extern __shared__ __attribute__((aligned(16))) float sums[];   // of each wavefront, TN rows
+    const int b = blockIdx.x, xcd = b & 7;
+    const int lin = xcd * (g.tiles >> 3) + (xcd < (g.tiles & 7) ? xcd : (g.tiles & 7)) + (b >> 3);
+    const int64_t n0 = int64_t(lin / g.tiles_m) * TN, m0 = int64_t(lin % g.tiles_m) * TM;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t M = g.M;
+
+    // this lane's weights, on their way while the sums are made
+    float w[OWN], mo[OWN];
+    int64_t off[OWN];
+    bool own[OWN];
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) {
+        const int at = i * THREADS + tid;
+        const int64_t n = n0 + at / TM, m = m0 + at % TM;
+        own[i] = at < TN * TM && n < g.N && m < M;
+        off[i] = n * M + m;
+        if (own[i]) {
+            w[i] = g.W[off[i]];
+            mo[i] = g.Mom[off[i]];
+        }
+    }
+
+    const uint32_t row_u = static_cast<uint32_t>(g.ldu * Sum::BYTES), row_v = static_cast<uint32_t>(g.ldv * Sum::BYTES);
+    uint32_t off_u[Sum::LOADS], off_v[Sum::LOADS];
+#pragma unroll
+    for (int j = 0; j < Sum::LOADS; ++j) {
+        off_u[j] = Sum::row(lane, j) * row_u + static_cast<uint32_t>(n0 + Sum::column(lane, Sum::A)) * Sum::BYTES;
+        off_v[j] = Sum::row(lane, j) * row_v + static_cast<uint32_t>(m0 + Sum::column(lane, Sum::B)) * Sum::BYTES;
+    }
+    Feed u, v;
+    int blk = 0;
+    uint32_t row = wave * SLICE;                 // of this wavefront's next slice; BLK: in its block
+    auto aim = [&]() {
+        if constexpr (BLK) {
+            while (row >= static_cast<uint32_t>(g.block_rows)) {
+                row -= g.block_rows;
+                ++blk;
+            }
+            const bool live = blk < g.n_blocks;
+            const int i = live ? blk : 0;        // the table is never indexed past its end
+            u.aim(uniform_ptr(static_cast<const char*>(blocks->u[i])), uint64_t(row) * row_u, live ? g.u_bytes : 0u);
+            v.aim(uniform_ptr(static_cast<const char*>(blocks->v[i])), uint64_t(row) * row_v, live ? g.v_bytes : 0u);
+        } else {
+            u.aim(g.U, uint64_t(row) * row_u, g.u_bytes);
+            v.aim(g.V, uint64_t(row) * row_v, g.v_bytes);
+        }
+    };
+    uint32_t xu[AHEAD][Sum::LOADS][Sum::WU], xv[AHEAD][Sum::LOADS][Sum::WV];
+    auto load = [&](int s) {                     // the wavefront's next slice; past K: zeros
+        aim();
+#pragma unroll
+        for (int j = 0; j < Sum::LOADS; ++j) load_or_zero(xu[s][j], u, off_u[j]);
+#pragma unroll
+        for (int j = 0; j < Sum::LOADS; ++j) load_or_zero(xv[s][j], v, off_v[j]);
+        row += SLICE * WAVES;
+    };
+    const int slices = g.K / SLICE + (g.K % SLICE > 0), steps = slices > wave ? (slices - wave + WAVES - 1) / WAVES : 0;
+    Sum sum;
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s)
+        if (s < steps) load(s);
+    for (int t = 0; t < steps; t += AHEAD) {
+#pragma unroll
+        for (int s = 0; s < AHEAD; ++s) {
+            if (t + s >= steps) break;
+            sum.add(xu[s], xv[s]);
+            if (t + s + AHEAD < steps) load(s);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < Sum::A; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float* to = sums + (wave * TN + Sum::A * (4 * (lane >> 4) + r) + i) * STRIDE + Sum::B * (lane & 15);
+#pragma unroll
+            for (int c = 0; c < Sum::B; ++c) to[c] = sum.acc[i][c][r];
+        }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) {
+        if (!own[i]) continue;
+        const int at = i * THREADS + tid;
+        const float* from = sums + at / TM * STRIDE + at % TM;
+        float d[WAVES];
+#pragma unroll
+        for (int s = 0; s < WAVES; ++s) d[s] = from[s * TN * STRIDE];
+#pragma unroll
+        for (int h = WAVES / 2; h > 0; h /= 2)   // in pairs
+#pragma unroll
+            for (int s = 0; s < h; ++s) d[s] += d[s + h];
+        upd(d[0], w[i], mo[i], g.lr, g.mu, g.wd);
+        g.Mom[off[i]] = mo[i];
+        g.W[off[i]] = w[i];
+    }
+}
+
+template <class Sum, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) sfb_small_kernel(const Args g)
+{
+    tile_body<Sum, WAVES, false>(g, nullptr);
+}
+
+template <class Sum, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) sfb_small_blocks_kernel(const Args g, const BlockPtrs blocks)
+{
+    tile_body<Sum, WAVES, true>(g, &blocks);
+}
+
+template <class Sum, int WAVES>
+psd_status start(Args& g, const BlockPtrs* blocks, hipStream_t st)
+{
+    constexpr int TN = 16 * Sum::A, TM = 16 * Sum::B, lds = WAVES * TN * (TM + 8) * 4;
+    g.tiles_m = (g.M + TM - 1) / TM;
+    g.tiles = (g.N + TN - 1) / TN * g.tiles_m;
+    if constexpr (lds > 65536) {
+        // raise the dynamic LDS limit once per process (idempotent, so a race between two first callers is harmless)
+        static std::atomic<bool> attr_done{false};
+        if (!attr_done.load(std::memory_order_acquire)) {
+            PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_small_kernel<Sum, WAVES>),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+            PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sfb_small_blocks_kernel<Sum, WAVES>),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+            attr_done.store(true, std::memory_order_release);
+        }
+    }
+    const dim3 grid(static_cast<uint32_t>(g.tiles));
+    if (blocks) hipLaunchKernelGGL((sfb_small_blocks_kernel<Sum, WAVES>), grid, dim3(64 * WAVES), lds, st, g, *blocks);
+    else hipLaunchKernelGGL((sfb_small_kernel<Sum, WAVES>), grid, dim3(64 * WAVES), lds, st, g);
+    PSD_HIP_TRY(hipGetLastError());
+    return PSD_OK;
+}
+
+// one launch of the kernel for `tile`
+psd_status dispatch(int32_t dtype, const SmallTile& tile, Args& g, const BlockPtrs* blocks, hipStream_t st)
+{
+    if (dtype == PSD_BF16) return tile.waves == 8 ? start<SumBf16, 8>(g, blocks, st) : start<SumBf16, 16>(g, blocks, st);
+    if (tile.b == 1) return start<SumF32<1, 1>, 16>(g, blocks, st);
+    if (tile.a == 1) return start<SumF32<1, 2>, 16>(g, blocks, st);
+    return tile.waves == 8 ? start<SumF32<2, 2>, 8>(g, blocks, st) : start<SumF32<2, 2>, 16>(g, blocks, st);
+}
+
+// `rows` k rows in each of P blocks
+Args args_for(int32_t dtype, int64_t ldu, int64_t ldv, int64_t P, int64_t rows, float* W, float* Mom, int64_t N, int64_t M, float lr, float mu,
+              float wd)
+{
+    const int64_t bytes = dtype == PSD_BF16 ? 2 : 4;
+    Args g = {};
+    g.ldu = ldu; g.ldv = ldv; g.W = W; g.Mom = Mom;
+    g.N = static_cast<int>(N); g.M = static_cast<int>(M); g.K = static_cast<int>(P * rows);
+    g.lr = lr; g.mu = mu; g.wd = wd;
+    g.u_bytes = static_cast<uint32_t>(rows * ldu * bytes); g.v_bytes = static_cast<uint32_t>(rows * ldv * bytes);
+    g.n_blocks = static_cast<int>(P); g.block_rows = static_cast<int>(rows);
+    return g;
+}
+
+}  // namespace
+
+psd_status launch_sfb_small(int32_t dtype, const SmallTile& tile, const void* U, int64_t ldu, const void* V, int64_t ldv, float* W,
+                            float* Mom, int64_t N, int64_t M, int64_t K, float lr, float mu, float wd, hipStream_t st)
+{
+    Args g = args_for(dtype, ldu, ldv, 1, K, W, Mom, N, M, lr, mu, wd);
+    g.U = U; g.V = V;
+    return dispatch(dtype, tile, g, nullptr, st);
+}
+
+psd_status launch_sfb_small_blocks(int32_t dtype, const SmallTile& tile, const void* const* U_p, int64_t ldu, const void* const* V_p,
+                                   int64_t ldv, int64_t P, int64_t B, float* W, float* Mom, int64_t N, int64_t M, float lr, float mu,
+                                   float wd, hipStream_t st)
+{
+    BlockPtrs blocks;
+    for (int64_t p = 0; p < PSD_MAX_WORKERS; ++p) {
+        blocks.u[p] = p < P ? U_p[p] : nullptr;
+        blocks.v[p] = p < P ? V_p[p] : nullptr;
+    }
+    Args g = args_for(dtype, ldu, ldv, P, B, W, Mom, N, M, lr, mu, wd);
+    return dispatch(dtype, tile, g, &blocks, st);
+}
+
+}  // namespace psd

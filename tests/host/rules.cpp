@@ -47,4 +47,19 @@ int32_t f32_planes(int64_t N, int64_t M, int64_t K, int64_t cus)
     return psd::choose_planes(N, M, K, cus, us);
 }
 int32_t f32_splits(int64_t N, int64_t M, int64_t K, int most, int64_t cus) { return psd::choose_f32_splits(N, M, K, most, cus, 0); }
+// 1000 * a + 100 * b + wavefronts of the tile of 16a x 16b, 0: none; `most`: how many ways the sum may be split
+int32_t f32_small(int64_t N, int64_t M, int64_t K, int most, int64_t cus)
+{
+    double us;
+    psd::choose_f32_splits(N, M, K, most, cus, 0, &us);
+    const psd::SmallTile t = psd::choose_small_f32(N, M, K, cus, us);
+    return t.waves ? 1000 * t.a + 100 * t.b + t.waves : 0;
+}
+int32_t bf16_small(int64_t N, int64_t M, int64_t K, int most, int64_t cus)
+{
+    int splits;
+    psd::choose_bf16_split(N, M, K, most, cus, -1, &splits);
+    const psd::SmallTile t = psd::choose_small_bf16(N, M, K, cus, splits);
+    return t.waves ? 1000 * t.a + 100 * t.b + t.waves : 0;
+}
 }

@@ -22,7 +22,8 @@ def rules(tmp_path_factory):
                             ("bf16_reach", i32, [i64, i64, i64, i64]), ("bf16_choice", i32, [i64, i64, i64, c_int, i64]),
                             ("splits_asked", i32, [i64, i64, i64]), ("bf16_cost", ctypes.c_double, [i32, i64, i64, i64, i64]),
                             ("sum_first", i32, [i32] + [ctypes.c_double] * 4), ("bf16_few", i32, [i64, i64, i64]), ("bf16_choice_beside", i32, [i64] * 4), ("bf16_large", i32, [i64] * 3), ("f32_choice", i32, [i64, i64, i64, i64]),
-                            ("f32_planes", i32, [i64, i64, i64, i64]), ("f32_splits", i32, [i64, i64, i64, c_int, i64])):
+                            ("f32_planes", i32, [i64, i64, i64, i64]), ("f32_splits", i32, [i64, i64, i64, c_int, i64]),
+                            ("f32_small", i32, [i64, i64, i64, c_int, i64]), ("bf16_small", i32, [i64, i64, i64, c_int, i64])):
         getattr(L, name).restype, getattr(L, name).argtypes = res, args
     return L
 

@@ -1,0 +1,77 @@
+"""Layers of few small tiles (csrc/psd_sfb_small.hip): edges of tiles and of the wavefronts' slices of k, both sides of the rule."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import psd_oracle as orc
+from paper_1512_06216_amd import binding as psd
+from paper_1512_06216_amd import inputs
+from tests.test_rules import rules  # noqa: F401  (a fixture)
+
+CUS = 256
+# M, N, B, P and 1000 * a + 100 * b + wavefronts of the tile of 16a x 16b for fp32 and bf16, 0: another kernel.
+# A slice is 16 rows (fp32) or 32 (bf16), a round of the wavefronts 128 and 256 (fp32) or 256 and 512 (bf16).
+CASES = [(1, 1, 1, 1, 1116, 2216), (31, 33, 5, 3, 1116, 2216), (32, 32, 16, 1, 1116, 2216), (33, 31, 32, 1, 1116, 2216),
+         (65, 64, 64, 8, 1116, 2216), (256, 256, 16, 16, 1116, 2216), (257, 256, 16, 17, 1216, 2216), (64, 67, 128, 4, 1116, 2216),
+         (257, 96, 43, 3, 1116, 2216), (500, 130, 17, 15, 1216, 2216), (512, 256, 48, 11, 1216, 2216), (512, 257, 32, 4, 2216, 2216),
+         (512, 512, 32, 4, 2216, 2216), (511, 509, 48, 3, 2216, 2216), (513, 512, 32, 4, 2208, 2208), (1000, 250, 96, 16, 2216, 2216),
+         (1024, 512, 64, 4, 2208, 2208), (1023, 505, 16, 17, 2208, 0), (1025, 512, 32, 4, 0, 0), (64, 8192, 33, 2, 2208, 2208)]
+LAYERS = [c[:4] for c in CASES]
+
+
+def test_small_layers_lie_on_both_sides_of_the_rule(rules):
+    for M, N, B, P, f32, bf16 in CASES:
+        assert (rules.f32_small(N, M, B * P, 1, CUS), rules.bf16_small(N, M, B * P, 1, CUS)) == (f32, bf16), (M, N, B, P)
+    assert rules.bf16_small(64, 64, 3000, 4, CUS) == 0 and rules.bf16_small(64, 64, 3000, 1, CUS) == 2216     # split by way of a workspace, or not
+    assert rules.f32_small(64, 64, 4096, 4, CUS) == 1116 and rules.f32_small(125, 4091, 2048, 4, CUS) == 0
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
+@pytest.mark.parametrize("M,N,B,P", LAYERS)
+def test_small_layer_bit_exact(M, N, B, P, dtype):
+    """Whole numbers: stacked and (whole slices in a block) read in place; W and Mom on cache lines and 16 bytes behind; what lies between
+    the rows of the factors is not a number."""
+    d = inputs.fc_layer_integer(M, N, B, P, seed=M + N + B)
+    plan = psd.plan_layer(psd.LAYER_FC, M, N, B, P)
+    U, ldu, V, ldv = psd.alloc_factors(plan, dtype, "cuda:0")
+    psd.pack_factors(plan, [dev(x) for x in d["delta"]], [dev(x) for x in d["act"]], dtype, U, ldu, V, ldv)
+    for X, cols in ((U, N), (V, M)):
+        X.view(torch.bfloat16 if dtype == psd.BF16 else torch.float32)[:, cols:] = float("nan")
+    Wr, Mr = orc.sync_fc_sfb(*orc.pack_factors(d["delta"], d["act"]), d["W"], d["Mom"], 0.25, 0.5, wd=0.25)
+    for blocks in (False, True)[:1 + (B % (32 if dtype == psd.BF16 else 16) == 0)]:
+        for behind in (0, 4):
+            room = torch.full((2, N * M + 40), 77.0, device="cuda:0")
+            W, Mom = (x[behind:behind + N * M].view(N, M) for x in (room[0], torch.empty_like(room[1]).fill_(77.0)))
+            W.copy_(dev(d["W"])), Mom.copy_(dev(d["Mom"]))
+            if blocks:
+                psd.sync_fc_sfb_blocks(plan, dtype, list(U.split(B)), ldu, list(V.split(B)), ldv, W, Mom, 0.25, 0.5, wd=0.25)
+            else:
+                psd.sync_fc_sfb(plan, dtype, U, ldu, V, ldv, W, Mom, 0.25, 0.5, wd=0.25)
+            torch.cuda.synchronize()
+            assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr), (blocks, behind)
+            assert bool((room[0, :behind] == 77).all()) and bool((room[0, behind + N * M:] == 77).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
+@pytest.mark.parametrize("M,N,K", [(500, 300, 2048), (700, 640, 200), (64, 64, 2400)])
+def test_small_layer_error_against_64_bits(M, N, K, dtype):
+    """8 or 16 runs over k, added up in pairs: K / 8 + 3 roundings of 2^-24 each at most, random ones grow with the root of their number.  The
+    fp32 kernel for larger tiles, four runs, has 2.9e-7 at K = 2048."""
+    g = torch.Generator().manual_seed(K)
+    u, v = torch.randn(K, N, generator=g).mul_(1e-3), torch.randn(K, M, generator=g).relu_()
+    plan = psd.plan_layer(psd.LAYER_FC, M, N, K, 1)
+    U, ldu, V, ldv = psd.alloc_factors(plan, dtype, "cuda:0")
+    psd.pack_factors(plan, [u.cuda()], [v.cuda()], dtype, U, ldu, V, ldv)
+    if dtype == psd.BF16:
+        u, v = u.bfloat16(), v.bfloat16()
+    W, Mom = torch.zeros(N, M, device="cuda:0"), torch.zeros(N, M, device="cuda:0")
+    psd.sync_fc_sfb(plan, dtype, U, ldu, V, ldv, W, Mom, 1.0, 0.0)
+    want = u.double().t().contiguous() @ v.double()
+    rel = ((Mom.cpu().double() - want).norm() / want.norm()).item()
+    assert rel <= 2.5e-7, rel
