@@ -322,6 +322,22 @@ inline bool bf16_few_tiles(int64_t N, int64_t M, int64_t tn, int64_t tm, int64_t
     return M % 4 != 0 && ((N + tn - 1) / tn) * ((M + tm - 1) / tm) <= 2 * cus;
 }
 
+// How many ticks of the 100 MHz clock the first workgroups of the odd XCDs wait in a launch of more than two bf16 tiles for each compute
+// unit (tiles of 128 rows; 0: none).  All first tiles are contracted at the same time and updated at the same time: nobody touches W
+// for the first 32 us of 9216 -> 4096, K = 2048, then 256 workgroups at once saturate HBM, behind which the other tiles' loops stand
+// still, and that goes on for five rounds of tiles.  With half of the chip 8 us behind the other half the bursts are half as high,
+// which is worth more than the wait (a quarter of a tile's loop; waits of 4, 8 and 10 us are alike, 16 too long).  us without and with
+// it, K = 2048: 9216 -> 4096 194.9 -> 188.6, 4096 -> 21841 432 -> 424, 25088 -> 4096 499 -> 491, 3000 -> 21841 338 -> 335,
+// 4096 -> 6144 137 -> 133, 6144 -> 6144 209 -> 202; 25088 -> 4096, K = 1536 431 -> 424, K = 4096 812 -> 809; K = 1024 9216 -> 4096 145.2
+// -> 143.8, 2048 -> 16384 143 -> 138, but 8192 -> 8192 234.0 and 234.9; shorter sums gain nothing: K = 512 129.0 and 130.9, 8192 ->
+// 8192, K = 768 207.0 and 208.3.  Two rounds and less: 4096 -> 4096 94.1 and 94.0.  Four or eight phases, phases inside an XCD (whose
+// tiles then share less in L2) and half tiles first instead of a wait (191 -> 190, 426 -> 421, 493 -> 487) are no better.
+inline int skew_ticks(int64_t tiles, int64_t tn, int64_t K, int64_t cus)
+{
+    if (tn < 128 || tiles <= 2 * cus || K < 1024) return 0;
+    return static_cast<int>(800 * (K < 2048 ? K : 2048) / 2048);
+}
+
 // ---- order of a step's launches
 // Does a parameter-server sum go before the bf16 reconstructions above it that wait for the same event?  Beside them its accesses and
 // theirs hinder each other, and it ends behind the last of them; first and by itself it is short and they fill the chip afterwards.

@@ -104,10 +104,9 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
     static_assert(AT == ANYWHERE || C::G == 1, "grouped tiles make no difference between rows");
     static_assert(AT != ANYWHERE_FEW || C::FEW, "what is not launched is not compiled");
     constexpr int KT = C::KT;
-    // Measurement aid (off unless asked for): the workgroups that start first on the odd-numbered
-    // XCDs wait skew_ticks of the 100 MHz wall clock, which puts the two halves of the chip out of
-    // phase (MFMA loop on one, W / Mom update on the other).  The wait ends by the clock; the
-    // iteration cap only bounds it should the clock not advance.
+    // The workgroups that start first on the odd-numbered XCDs wait skew_ticks of the 100 MHz wall clock, which puts the two
+    // halves of the chip out of phase (skew_ticks in psd_rules.h).  The wait ends by the clock; the iteration cap only bounds it
+    // should the clock not advance.
     if (skew_ticks > 0 && (blockIdx.x & 1) && static_cast<int>(blockIdx.x) < skew_blocks) {
         const long long t0 = wall_clock64();
         for (int i = 0; i < 200000 && wall_clock64() - t0 < skew_ticks; ++i) __builtin_amdgcn_s_sleep(8);
@@ -472,10 +471,10 @@ template <class C, Rows AT>
 __global__ void __launch_bounds__(C::THREADS, C::OCC)
 sfb_bf16_blocks_kernel(BlockPtrs blocks, int n_blocks, int block_rows, int64_t ldu, int64_t ldv,
                        float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
-                       int tiles_n, int tiles_m, uint32_t u_bytes, uint32_t v_bytes)
+                       int tiles_n, int tiles_m, uint32_t u_bytes, uint32_t v_bytes, int skew_blocks, int skew_ticks)
 {
     sfb_bf16_body<C, false, true, AT>(nullptr, ldu, nullptr, ldv, W, Mom, N, M, K, lr, mu, wd, tiles_n, tiles_m, u_bytes,
-                                  v_bytes, nullptr, 0, 0, 0, 0, &blocks, n_blocks, block_rows);
+                                  v_bytes, nullptr, 0, 0, skew_blocks, skew_ticks, &blocks, n_blocks, block_rows);
 }
 
 // where the rows of W and Mom start, for the tile C (cache lines have 128 bytes)
@@ -491,6 +490,14 @@ Rows rows_at(const float* W, const float* Mom, int64_t N, int64_t M)
 // ... and what there is of a tile C
 template <class C> constexpr Rows kOnLines = C::G == 1 ? ON_LINES : ANYWHERE;
 template <class C> constexpr Rows kFew = C::FEW ? ANYWHERE_FEW : ANYWHERE;
+
+// ticks by which the odd XCDs start late
+template <class C>
+int skew_for(int64_t tiles, int64_t K)
+{
+    const int asked = tune_value(PSD_TUNE_SFB_BF16_SKEW_US);
+    return asked >= 0 ? asked * 100 : C::G > 1 ? 0 : skew_ticks(tiles, C::TN, K, device_cu_count());
+}
 
 template <class C>
 psd_status launch_cfg_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int64_t ldu, int64_t ldv, float* W, float* Mom,
@@ -513,7 +520,8 @@ psd_status launch_cfg_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int6
     hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(tiles)), dim3(C::THREADS), C::LDS_BYTES_ROWS, st,
                        blocks, static_cast<int>(P), static_cast<int>(B), ldu, ldv, W, Mom, static_cast<int>(N),
                        static_cast<int>(M), static_cast<int>(P * B), lr, mu, wd, static_cast<int>(tiles_n),
-                       static_cast<int>(tiles_m), static_cast<uint32_t>(u_bytes), static_cast<uint32_t>(v_bytes));
+                       static_cast<int>(tiles_m), static_cast<uint32_t>(u_bytes), static_cast<uint32_t>(v_bytes),
+                       device_cu_count() * C::OCC, skew_for<C>(tiles, P * B));
     PSD_HIP_TRY(hipGetLastError());
     return PSD_OK;
 }
@@ -543,14 +551,13 @@ psd_status launch_cfg(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t
             PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         attr_done.store(true, std::memory_order_release);
     }
-    const int skew = tune_value(PSD_TUNE_SFB_BF16_SKEW_US);
     const int64_t stages = (K + C::KT - 1) / C::KT;
     const int sps = static_cast<int>((stages + splits - 1) / splits);
     hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(tiles * splits)), dim3(C::THREADS), lds, st, U, ldu, V,
                        ldv, W, Mom, static_cast<int>(N), static_cast<int>(M), static_cast<int>(K), lr, mu, wd,
                        static_cast<int>(tiles_n), static_cast<int>(tiles_m), static_cast<uint32_t>(u_bytes),
                        static_cast<uint32_t>(v_bytes), part, sfb_part_stride(N, M), sps,
-                       device_cu_count() * C::OCC, skew > 0 ? skew * 100 : 0);
+                       device_cu_count() * C::OCC, skew_for<C>(splits > 1 ? 0 : tiles, K));
     PSD_HIP_TRY(hipGetLastError());
     if (splits > 1) return launch_sfb_reduce(part, splits, N, M, W, Mom, lr, mu, wd, st);
     return PSD_OK;
