@@ -30,13 +30,6 @@ __device__ __forceinline__ void wait_vmcnt()
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
-// n / d for any 32-bit n (Granlund & Montgomery, division by invariant integers using multiplication)
-__device__ __forceinline__ uint32_t divide(uint32_t n, const FastDiv& f)
-{
-    const uint32_t t = __umulhi(f.mul, n);
-    return (t + ((n - t) >> f.shift1)) >> f.shift2;
-}
-
 // A pointer every lane holds alike, moved to scalar registers (buffer descriptors live there).
 template <class T>
 __device__ __forceinline__ const T* uniform_ptr(const T* p)

@@ -1,11 +1,38 @@
 // The rules by which the host shapes a launch: integer arithmetic and fitted costs, no HIP (not installed).
 #pragma once
 #include <stdint.h>
+#ifdef __HIPCC__
+#define PSD_HOST_DEVICE __host__ __device__ __forceinline__
+#else
+#define PSD_HOST_DEVICE inline
+#endif
 
 namespace psd {
 
 // HIP counts the work items of a launch in 32 bits.
 constexpr int64_t kMaxItems = (int64_t(1) << 32) - 1;
+
+// ---- division by a number that a launch knows: multiplier and shifts of `divide`
+struct FastDiv { uint32_t d, mul, shift1, shift2; };
+
+inline FastDiv fast_div(uint32_t d)
+{
+    int l = 0;                                         // ceil(log2(d))
+    while ((uint64_t(1) << l) < d) ++l;
+    FastDiv f;
+    f.d = d;
+    f.mul = static_cast<uint32_t>((uint64_t(1) << 32) * ((uint64_t(1) << l) - d) / d + 1);
+    f.shift1 = l < 1 ? l : 1;
+    f.shift2 = l < 1 ? 0 : l - 1;
+    return f;
+}
+
+// n / d for any 32-bit n (Granlund & Montgomery, division by invariant integers using multiplication)
+PSD_HOST_DEVICE uint32_t divide(uint32_t n, const FastDiv& f)
+{
+    const uint32_t t = static_cast<uint32_t>((uint64_t(f.mul) * n) >> 32);
+    return (t + ((n - t) >> f.shift1)) >> f.shift2;
+}
 
 // ---- parameter-server sum: one float4 of every array per lane
 // Lanes per workgroup of a launch over `keys` keys in `shards` shards.  One float4 per lane: with two, a workgroup's loads wait
@@ -328,14 +355,86 @@ inline bool bf16_few_tiles(int64_t N, int64_t M, int64_t tn, int64_t tm, int64_t
 // still, and that goes on for five rounds of tiles.  With half of the chip 8 us behind the other half the bursts are half as high,
 // which is worth more than the wait (a quarter of a tile's loop; waits of 4, 8 and 10 us are alike, 16 too long).  us without and with
 // it, K = 2048: 9216 -> 4096 194.9 -> 188.6, 4096 -> 21841 432 -> 424, 25088 -> 4096 499 -> 491, 3000 -> 21841 338 -> 335,
-// 4096 -> 6144 137 -> 133, 6144 -> 6144 209 -> 202; 25088 -> 4096, K = 1536 431 -> 424, K = 4096 812 -> 809; K = 1024 9216 -> 4096 145.2
-// -> 143.8, 2048 -> 16384 143 -> 138, but 8192 -> 8192 234.0 and 234.9; shorter sums gain nothing: K = 512 129.0 and 130.9, 8192 ->
-// 8192, K = 768 207.0 and 208.3.  Two rounds and less: 4096 -> 4096 94.1 and 94.0.  Four or eight phases, phases inside an XCD (whose
-// tiles then share less in L2) and half tiles first instead of a wait (191 -> 190, 426 -> 421, 493 -> 487) are no better.
+// 4096 -> 6144 137 -> 133, 6144 -> 6144 209 -> 202; K = 1536 25088 -> 4096 431 -> 424, 9216 -> 4096 174 -> 169; K = 4096 25088 -> 4096
+// 812 -> 809.  K = 1024: 9216 -> 4096 145.2 and 143.8, 8192 -> 8192 236 and 243.5, 982 -> 17846 87.6 and 90.1.  Two rounds and less:
+// 4096 -> 4096 94.1 and 94.0.  Four or eight phases, phases inside an XCD (whose tiles then share less in L2) and half tiles first
+// instead of a wait (191 -> 190, 426 -> 421, 493 -> 487) are no better.
 inline int skew_ticks(int64_t tiles, int64_t tn, int64_t K, int64_t cus)
 {
-    if (tn < 128 || tiles <= 2 * cus || K < 1024) return 0;
+    if (tn < 128 || tiles <= 2 * cus || K < 1400) return 0;
     return static_cast<int>(800 * (K < 2048 ? K : 2048) / 2048);
+}
+
+// ---- order of a bf16 launch's tiles
+// Workgroups go round-robin over the 8 XCDs, each of which has an L2 of its own.
+// band = 0: each XCD takes a contiguous run of the tile sequence, ordered in groups of 8 tile rows, so that the workgroups that share an
+// L2 re-use the same few panels of U and V.
+// band > 0: the whole chip goes over bands of that many tile rows, each XCD over an eighth of the columns.
+// band < 0: over one row of tiles after the other, dealt out tile by tile.
+struct TileOrder {
+    int band, tiles, tiles_m;
+    int rows, last, groups;        // tile rows of a group (band), of the last one, and how many groups
+    FastDiv by_tiles, by_group, by_rows, by_last;
+};
+inline TileOrder tile_order(int tiles_n, int tiles_m, int band)
+{
+    TileOrder o;
+    o.band = band;
+    o.tiles = tiles_n * tiles_m;
+    o.tiles_m = tiles_m;
+    o.rows = band > 0 ? band : band < 0 ? 1 : 8;
+    o.groups = (tiles_n + o.rows - 1) / o.rows;
+    o.last = tiles_n - (o.groups - 1) * o.rows;
+    o.by_tiles = fast_div(o.tiles);
+    o.by_group = fast_div(o.rows * tiles_m);
+    o.by_rows = fast_div(o.rows);
+    o.by_last = fast_div(o.last);
+    return o;
+}
+// workgroup b (of one split) -> tile.  (Divisions by multiplication: those of the hardware run on the vector ALU, twenty instructions each.)
+PSD_HOST_DEVICE void tile_of(int b, const TileOrder& o, int* tile_n, int* tile_m)
+{
+    auto run_of = [](int i, int n) {             // item i of n dealt out to 8 -> its place where each of the 8 takes a contiguous run
+        const int eighth = i & 7;
+        return eighth * (n >> 3) + (eighth < (n & 7) ? eighth : (n & 7)) + (i >> 3);
+    };
+    const int lin = o.band == 0 ? run_of(b, o.tiles) : b;
+    const int g = static_cast<int>(divide(lin, o.by_group)), in_g = lin - g * o.rows * o.tiles_m;
+    const bool last = g == o.groups - 1;
+    const int rows = last ? o.last : o.rows;
+    const int at = o.band > 0 ? run_of(in_g, rows * o.tiles_m) : in_g;
+    int m = static_cast<int>(last ? divide(at, o.by_last) : divide(at, o.by_rows));
+    *tile_n = g * o.rows + at - m * rows;
+    // Up to 8 groups, the XCDs work on several of them at the same time, and each group starts an eighth of the columns behind the
+    // one before: a panel of V that is not in the Infinity Cache is then fetched from HBM by one XCD and found there by the
+    // others.  All at the same columns, they all fetch it: 25088 -> 4096, K = 2048 with the factors cold 560 us, now 550 (790 and
+    // 777 mJ; warm 537 both).  Rows of W of a power of two also reach other channels of HBM then: 16384 -> 2048, K = 1024 165 -> 148.
+    // With more groups than XCDs these are spread already (3000 -> 21841 397 both, turned or not).
+    if (o.band == 0 && o.groups <= 8) {
+        m += g * o.tiles_m / 8;
+        if (m >= o.tiles_m) m -= o.tiles_m;
+    }
+    *tile_m = m;
+}
+
+// Which of them.  Short sums are bound by W and Mom in HBM, and HBM wants what is read and written together to lie together: a launch
+// that does nothing but read and write W and Mom of 9216 -> 4096 takes 102 us going over them linearly, 121 in tiles of band 0, 112
+// row by row; the panels of U and V are small.  Long sums are bound by the panels' way through the L2s.  us, band 0 -> 4 (-1 where
+// K <= 192, rows on lines): 9216 -> 4096, K = 64 123.7 -> 100.5, K = 256 121.3 -> 105.7, K = 512 132.7 -> 121.6, 25088 -> 4096, K = 128
+// 332 -> 280, K = 512 348 -> 322, 4096 -> 21841, K = 128 265 -> 226, K = 512 259 -> 251, 16384 -> 2048, K = 128 111 -> 92, 7072 -> 2322,
+// K = 40 53.6 -> 45.8, 2048 -> 16384, K = 256 108 -> 93 (-1: 96, and 94 for 89 with K = 128: narrow layers keep 4).
+// K = 640: 4096 -> 21841 266.5 and 266.7, 8192 -> 8192 214 and 226; wide layers gain longer, 9216 -> 4096, K = 768 135.8 -> 130.3,
+// 12000 -> 2500 112 -> 107, 25088 -> 4096 347 -> 341, K = 1024 369 and 374.
+// Off cache lines neighbouring tiles share lines, which are best left to one XCD: 7001 -> 5003, K = 256 105.7 -> 100.3, 10001 -> 4001,
+// K = 64 109 -> 104 (-1: 133), 5000 -> 9000 117.6 and 117.1, but 1500 -> 20000 78 and 88, 2500 -> 12000 79 and 84.
+// Layers of less than 5 M weights, which the chip covers at once: 608 -> 4068, K = 273 11.3 and 12.7, 2720 -> 1119, K = 153 14.0 and
+// 14.4; 5376 -> 991, K = 40 19.3 -> 17.9.  Of 175 layers of K = 32 .. 1100 the 116 that change their order gain 8 %, the worst of them
+// loses 3 (1024 -> 20000, K = 256).
+inline int band_for(int64_t N, int64_t M, int64_t K, int64_t tiles, bool on_lines, int64_t cus)
+{
+    if (tiles <= 2 * cus || N * M < 5000000) return 0;
+    if (on_lines && K <= 192 && M >= 3072) return -1;
+    return K <= (M >= 2 * N ? 768 : 512) && (on_lines || M >= 4000) ? 4 : 0;
 }
 
 // ---- order of a step's launches
@@ -359,21 +458,6 @@ inline bool sum_goes_first(int32_t layers, double update_us, double loop_us, dou
 {
     const double us = update_us + loop_us, paid_back = 0.08 * update_us + 0.6 * loop_us;
     return layers >= 3 && us >= 145 && sum_us <= (paid_back > 0.15 * us ? paid_back : 0.15 * us);
-}
-
-// ---- division by a number that a launch knows: multiplier and shifts of `divide` (psd_device.h)
-struct FastDiv { uint32_t d, mul, shift1, shift2; };
-
-inline FastDiv fast_div(uint32_t d)
-{
-    int l = 0;                                         // ceil(log2(d))
-    while ((uint64_t(1) << l) < d) ++l;
-    FastDiv f;
-    f.d = d;
-    f.mul = static_cast<uint32_t>((uint64_t(1) << 32) * ((uint64_t(1) << l) - d) / d + 1);
-    f.shift1 = l < 1 ? l : 1;
-    f.shift2 = l < 1 ? 0 : l - 1;
-    return f;
 }
 
 // ---- pack

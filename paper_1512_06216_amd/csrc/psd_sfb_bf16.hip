@@ -41,7 +41,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
 constexpr int SLICE = kBf16StageRows;   // k rows of a stage that one group of wavefronts contracts 
-constexpr int GROUP_N = 8;     // tile rows per raster group (L2 reuse of the V panels)
 constexpr int PLD = 36;        // epilogue patch row stride in floats (144 B: conflict-free)
 
 // WN x WM wavefronts, each owning 32 BN x 32 BM of the tile; NSTAGE LDS buffers;
@@ -96,7 +95,7 @@ template <class C, bool PART, bool BLK, Rows AT>
 __device__ __forceinline__ void
 sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __restrict__ V, int64_t ldv,
               float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
-              int tiles_n, int tiles_m, uint32_t u_bytes, uint32_t v_bytes, float* __restrict__ part,
+              const TileOrder& order, uint32_t u_bytes, uint32_t v_bytes, float* __restrict__ part,
               int64_t part_stride, int stages_per_split, int skew_blocks, int skew_ticks,
               const BlockPtrs* blocks, int n_blocks, int block_rows)
 {
@@ -115,24 +114,9 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
     const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
         (__attribute__((address_space(3))) void*)lds));
 
-    // Workgroup -> tile.  Consecutive workgroup ids go round-robin over the 8 XCDs; give each
-    // XCD a contiguous run of the tile sequence, and order that sequence in groups of GROUP_N
-    // tile rows so that the workgroups sharing an L2 re-use the same few U and V panels.
-    const int T = tiles_n * tiles_m;
-    const int split = PART ? __builtin_amdgcn_readfirstlane(blockIdx.x / T) : 0;   // (the division runs on the vector ALU)
-    const int b = PART ? blockIdx.x - split * T : blockIdx.x, xcd = b & 7;
-    const int lin = xcd * (T >> 3) + (xcd < (T & 7) ? xcd : (T & 7)) + (b >> 3);
-    const int per_group = GROUP_N * tiles_m;
-    const int g = lin / per_group, in_g = lin - g * per_group;
-    const int rows_g = tiles_n - g * GROUP_N < GROUP_N ? tiles_n - g * GROUP_N : GROUP_N;
-    // Up to 8 groups, the XCDs work on several of them at the same time, and each group starts an eighth of the columns behind the
-    // one before: a panel of V that is not in the Infinity Cache is then fetched from HBM by one XCD and found there by the
-    // others.  All at the same columns, they all fetch it: 25088 -> 4096, K = 2048 with the factors cold 560 us, now 550 (790 and
-    // 777 mJ; warm 537 both).  Rows of W of a power of two also reach other channels of HBM then: 16384 -> 2048, K = 1024 165 -> 148.
-    // With more groups than XCDs these are spread already (3000 -> 21841 397 both, turned or not).
-    int tile_m = in_g / rows_g + (tiles_n <= 8 * GROUP_N ? g * tiles_m / 8 : 0);
-    if (tile_m >= tiles_m) tile_m -= tiles_m;
-    const int tile_n = g * GROUP_N + in_g % rows_g;
+    const int split = PART ? static_cast<int>(divide(blockIdx.x, order.by_tiles)) : 0;
+    int tile_n, tile_m;
+    tile_of(blockIdx.x - split * order.tiles, order, &tile_n, &tile_m);
 
     const int64_t n0 = int64_t(tile_n) * C::TN, m0 = int64_t(tile_m) * C::TM;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -459,10 +443,10 @@ template <class C, bool PART, Rows AT>
 __global__ void __launch_bounds__(C::THREADS, C::OCC)
 sfb_bf16_kernel(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __restrict__ V, int64_t ldv,
                 float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
-                int tiles_n, int tiles_m, uint32_t u_bytes, uint32_t v_bytes, float* __restrict__ part,
+                const TileOrder order, uint32_t u_bytes, uint32_t v_bytes, float* __restrict__ part,
                 int64_t part_stride, int stages_per_split, int skew_blocks, int skew_ticks)
 {
-    sfb_bf16_body<C, PART, false, AT>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, tiles_n, tiles_m, u_bytes, v_bytes, part,
+    sfb_bf16_body<C, PART, false, AT>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, order, u_bytes, v_bytes, part,
                                   part_stride, stages_per_split, skew_blocks, skew_ticks, nullptr, 0, 0);
 }
 
@@ -471,9 +455,9 @@ template <class C, Rows AT>
 __global__ void __launch_bounds__(C::THREADS, C::OCC)
 sfb_bf16_blocks_kernel(BlockPtrs blocks, int n_blocks, int block_rows, int64_t ldu, int64_t ldv,
                        float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
-                       int tiles_n, int tiles_m, uint32_t u_bytes, uint32_t v_bytes, int skew_blocks, int skew_ticks)
+                       const TileOrder order, uint32_t u_bytes, uint32_t v_bytes, int skew_blocks, int skew_ticks)
 {
-    sfb_bf16_body<C, false, true, AT>(nullptr, ldu, nullptr, ldv, W, Mom, N, M, K, lr, mu, wd, tiles_n, tiles_m, u_bytes,
+    sfb_bf16_body<C, false, true, AT>(nullptr, ldu, nullptr, ldv, W, Mom, N, M, K, lr, mu, wd, order, u_bytes,
                                   v_bytes, nullptr, 0, 0, skew_blocks, skew_ticks, &blocks, n_blocks, block_rows);
 }
 
@@ -510,6 +494,8 @@ psd_status launch_cfg_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int6
     const Rows at = rows_at<C>(W, Mom, N, M);
     auto kern = at == ON_LINES       ? sfb_bf16_blocks_kernel<C, kOnLines<C>>
                 : at == ANYWHERE_FEW ? sfb_bf16_blocks_kernel<C, kFew<C>> : sfb_bf16_blocks_kernel<C, ANYWHERE>;
+    const TileOrder order = tile_order(static_cast<int>(tiles_n), static_cast<int>(tiles_m),
+                                       band_for(N, M, P * B, tiles, at == ON_LINES, device_cu_count()));
     static std::atomic<bool> attr_done{false};
     if (!attr_done.load(std::memory_order_acquire)) {
         for (auto k : {sfb_bf16_blocks_kernel<C, kOnLines<C>>, sfb_bf16_blocks_kernel<C, kFew<C>>,
@@ -519,9 +505,8 @@ psd_status launch_cfg_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int6
     }
     hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(tiles)), dim3(C::THREADS), C::LDS_BYTES_ROWS, st,
                        blocks, static_cast<int>(P), static_cast<int>(B), ldu, ldv, W, Mom, static_cast<int>(N),
-                       static_cast<int>(M), static_cast<int>(P * B), lr, mu, wd, static_cast<int>(tiles_n),
-                       static_cast<int>(tiles_m), static_cast<uint32_t>(u_bytes), static_cast<uint32_t>(v_bytes),
-                       device_cu_count() * C::OCC, skew_for<C>(tiles, P * B));
+                       static_cast<int>(M), static_cast<int>(P * B), lr, mu, wd, order, static_cast<uint32_t>(u_bytes),
+                       static_cast<uint32_t>(v_bytes), device_cu_count() * C::OCC, skew_for<C>(tiles, P * B));
     PSD_HIP_TRY(hipGetLastError());
     return PSD_OK;
 }
@@ -541,6 +526,8 @@ psd_status launch_cfg(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t
     auto kern = splits > 1 ? sfb_bf16_kernel<C, alone, ANYWHERE>
                 : at == ON_LINES     ? sfb_bf16_kernel<C, false, kOnLines<C>>
                 : at == ANYWHERE_FEW ? sfb_bf16_kernel<C, false, kFew<C>> : sfb_bf16_kernel<C, false, ANYWHERE>;
+    const TileOrder order = tile_order(static_cast<int>(tiles_n), static_cast<int>(tiles_m),
+                                       splits > 1 ? 0 : band_for(N, M, K, tiles, at == ON_LINES, device_cu_count()));
     const size_t lds = splits > 1 ? C::LDS_BYTES : C::LDS_BYTES_ROWS;
     // raise the dynamic LDS limit once per process (idempotent, so a race between two first
     // callers is harmless; the flag only saves the call on later launches)
@@ -555,8 +542,7 @@ psd_status launch_cfg(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t
     const int sps = static_cast<int>((stages + splits - 1) / splits);
     hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(tiles * splits)), dim3(C::THREADS), lds, st, U, ldu, V,
                        ldv, W, Mom, static_cast<int>(N), static_cast<int>(M), static_cast<int>(K), lr, mu, wd,
-                       static_cast<int>(tiles_n), static_cast<int>(tiles_m), static_cast<uint32_t>(u_bytes),
-                       static_cast<uint32_t>(v_bytes), part, sfb_part_stride(N, M), sps,
+                       order, static_cast<uint32_t>(u_bytes), static_cast<uint32_t>(v_bytes), part, sfb_part_stride(N, M), sps,
                        device_cu_count() * C::OCC, skew_for<C>(splits > 1 ? 0 : tiles, K));
     PSD_HIP_TRY(hipGetLastError());
     if (splits > 1) return launch_sfb_reduce(part, splits, N, M, W, Mom, lr, mu, wd, st);

@@ -1,4 +1,5 @@
 // C entry points over csrc/psd_rules.h for tests/test_rules.py.
+#include <vector>
 #include "psd_rules.h"
 
 extern "C" {
@@ -61,5 +62,19 @@ int32_t bf16_small(int64_t N, int64_t M, int64_t K, int most, int64_t cus)
     psd::choose_bf16_split(N, M, K, most, cus, -1, &splits);
     const psd::SmallTile t = psd::choose_small_bf16(N, M, K, cus, splits);
     return t.waves ? 1000 * t.a + 100 * t.b + t.waves : 0;
+}
+int32_t bf16_band(int64_t N, int64_t M, int64_t K, int64_t tiles, int on_lines, int64_t cus) { return psd::band_for(N, M, K, tiles, on_lines, cus); }
+// are the tiles of all workgroups tiles_n * tiles_m different ones
+int32_t tiles_covered(int tiles_n, int tiles_m, int band)
+{
+    const int T = tiles_n * tiles_m;
+    const psd::TileOrder order = psd::tile_order(tiles_n, tiles_m, band);
+    std::vector<char> seen(T, 0);
+    for (int b = 0; b < T; ++b) {
+        int n, m;
+        psd::tile_of(b, order, &n, &m);
+        if (n < 0 || n >= tiles_n || m < 0 || m >= tiles_m || seen[n * tiles_m + m]++) return 0;
+    }
+    return 1;
 }
 }

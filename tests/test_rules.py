@@ -23,7 +23,8 @@ def rules(tmp_path_factory):
                             ("splits_asked", i32, [i64, i64, i64]), ("bf16_cost", ctypes.c_double, [i32, i64, i64, i64, i64]),
                             ("sum_first", i32, [i32] + [ctypes.c_double] * 4), ("bf16_few", i32, [i64, i64, i64]), ("bf16_choice_beside", i32, [i64] * 4), ("bf16_large", i32, [i64] * 3), ("f32_choice", i32, [i64, i64, i64, i64]),
                             ("f32_planes", i32, [i64, i64, i64, i64]), ("f32_splits", i32, [i64, i64, i64, c_int, i64]),
-                            ("f32_small", i32, [i64, i64, i64, c_int, i64]), ("bf16_small", i32, [i64, i64, i64, c_int, i64])):
+                            ("f32_small", i32, [i64, i64, i64, c_int, i64]), ("bf16_small", i32, [i64, i64, i64, c_int, i64]),
+                            ("bf16_band", i32, [i64, i64, i64, i64, c_int, i64]), ("tiles_covered", i32, [c_int] * 3)):
         getattr(L, name).restype, getattr(L, name).argtypes = res, args
     return L
 
@@ -226,3 +227,10 @@ def test_short_contractions_and_small_layers_stay_on_the_fp32_pipe(rules):
         assert rules.f32_planes(N, M, K, CUS) == -1
     for M, N in ((4096, 1000), (4096, 4096), (9216, 4096), (3000, 21841)):
         assert rules.f32_planes(N, M, 2048, CUS) >= 0
+
+
+def test_every_order_of_tiles_covers_each_of_them_once(rules):
+    for tiles_n in (1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 33, 64, 65, 171):
+        for tiles_m in (1, 2, 3, 7, 8, 9, 12, 21, 48, 98):
+            for band in (-1, 0, 1, 2, 4, 8):
+                assert rules.tiles_covered(tiles_n, tiles_m, band), (tiles_n, tiles_m, band)
