@@ -405,13 +405,14 @@ PSD_HOST_DEVICE void tile_of(int b, const TileOrder& o, int* tile_n, int* tile_m
     const int at = o.band > 0 ? run_of(in_g, rows * o.tiles_m) : in_g;
     int m = static_cast<int>(last ? divide(at, o.by_last) : divide(at, o.by_rows));
     *tile_n = g * o.rows + at - m * rows;
-    // Up to 8 groups, the XCDs work on several of them at the same time, and each group starts an eighth of the columns behind the
+    // The XCDs work on several groups at the same time, and each group starts an eighth of the columns behind the
     // one before: a panel of V that is not in the Infinity Cache is then fetched from HBM by one XCD and found there by the
     // others.  All at the same columns, they all fetch it: 25088 -> 4096, K = 2048 with the factors cold 560 us, now 550 (790 and
-    // 777 mJ; warm 537 both).  Rows of W of a power of two also reach other channels of HBM then: 16384 -> 2048, K = 1024 165 -> 148.
-    // With more groups than XCDs these are spread already (3000 -> 21841 397 both, turned or not).
-    if (o.band == 0 && o.groups <= 8) {
-        m += g * o.tiles_m / 8;
+    // 777 mJ; warm 537 both).  Rows of W of a power of two also reach other channels of HBM then: 16384 -> 2048, K = 1024 165 -> 148;
+    // 2048 -> 16384, K = 640 170 -> 112, K = 2048 175 -> 169 (16 groups, which were not turned before; 3000 -> 21841, K = 1024 248 both,
+    // 2048 -> 8192, K = 1024 68 and 70).
+    if (o.band == 0) {
+        m += (g & 7) * o.tiles_m / 8;
         if (m >= o.tiles_m) m -= o.tiles_m;
     }
     *tile_m = m;

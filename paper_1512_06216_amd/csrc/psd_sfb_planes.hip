@@ -50,7 +50,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int SLICE = 16;           // k rows that one group of wavefronts contracts between two barriers
-constexpr int GROUP_N = 16;         // tile rows per raster group (as in the bf16 kernel; 8: 1 % slower)
 
 // WN wavefronts of 32 rows n and 128 columns m per group, G groups
 template <int WN_, int G_>
@@ -79,7 +78,7 @@ struct Args {
     float* W; float* Mom;
     int N, M, K;
     float lr, mu, wd;
-    int tiles_n, tiles_m;
+    TileOrder order;
     uint32_t u_bytes, v_bytes;      // of the stacked matrices, or of ONE block
     int n_blocks, block_rows;       // BLK
 };
@@ -137,13 +136,9 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
 {
     constexpr int G = C::G, WN = C::WN, PV = C::PV;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    // workgroup -> tile: a contiguous run of the tile sequence per XCD, in groups of GROUP_N tile rows
-    const int T = g.tiles_n * g.tiles_m, xcd = blockIdx.x & 7;
-    const int lin = xcd * (T >> 3) + (xcd < (T & 7) ? xcd : (T & 7)) + (blockIdx.x >> 3);
-    const int per_raster = GROUP_N * g.tiles_m;
-    const int raster = lin / per_raster, in_raster = lin - raster * per_raster;
-    const int rows_r = g.tiles_n - raster * GROUP_N < GROUP_N ? g.tiles_n - raster * GROUP_N : GROUP_N;
-    const int64_t n0 = int64_t(raster * GROUP_N + in_raster % rows_r) * C::TN, m0 = int64_t(in_raster / rows_r) * C::TM;
+    int tile_n, tile_m;
+    tile_of(blockIdx.x, g.order, &tile_n, &tile_m);
+    const int64_t n0 = int64_t(tile_n) * C::TN, m0 = int64_t(tile_m) * C::TM;
 
     const int N = g.N, M = g.M;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -504,10 +499,17 @@ __global__ void __launch_bounds__(C::THREADS, 2) sfb_f32_planes_blocks_kernel(co
 template <class C>
 psd_status start(Args& g, const BlockPtrs* blocks, hipStream_t st)
 {
-    g.tiles_n = (g.N + C::TN - 1) / C::TN;
-    g.tiles_m = (g.M + C::TM - 1) / C::TM;
-    const int64_t tiles = int64_t(g.tiles_n) * g.tiles_m;
+    const int tiles_n = (g.N + C::TN - 1) / C::TN, tiles_m = (g.M + C::TM - 1) / C::TM;
+    const int64_t tiles = int64_t(tiles_n) * tiles_m;
     if (tiles < 1 || tiles > 0x7fffffff) return PSD_E_INVALID;
+    // Layers with long rows: bands of tile rows over the whole chip, for W and Mom in HBM (see band_for in psd_rules.h) as well as for the
+    // factors; others: a run of groups of eight tile rows for each XCD, turned against each other.  us, runs of groups of 16, not turned
+    // -> now: 9216 -> 4096, K = 256 150.0 -> 146.4, K = 1024 379 -> 376, K = 2048 685 -> 681, 16384 -> 2048, K = 256 155 -> 137,
+    // 7001 -> 5003, K = 512 245 -> 242, 5024 -> 9000, K = 256 188 -> 183 (runs 187); 4096 -> 4096, K = 256 83.7 -> 73.3 (bands of four
+    // 75.2), 3500 -> 7000, K = 512 168 -> 164 (167), 1000 -> 12000, K = 1024 143 -> 142 (149), 2048 -> 16384, K = 256 139 -> 134.
+    // 4096 -> 21841, K = 4096 3312 -> 3109 with either; 25088 -> 2048, K = 4096 1838, in bands of four 1874, of eight 1844.  Few rows of
+    // tiles are one band: 18720 -> 1438, K = 278 123.2 us, in bands of four 125.3.
+    g.order = tile_order(tiles_n, tiles_m, g.M <= 4500 ? 0 : g.N <= 1600 ? 16 : g.K <= 2048 ? 4 : 8);
     // raise the dynamic LDS limit once per process (idempotent, so a race between two first callers is harmless)
     static std::atomic<bool> attr_done{false};
     if (!attr_done.load(std::memory_order_acquire)) {
