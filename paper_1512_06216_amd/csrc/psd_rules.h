@@ -200,6 +200,25 @@ inline int choose_planes(int64_t N, int64_t M, int64_t K, int64_t cus, double us
     return best;
 }
 
+// ... and sums of 128 to 255 rows, 128 x 128 or none: since W and Mom are gone over in bands (tile_order) the planes are the faster ones
+// there too for large layers.  us, fp32 pipe -> planes: 9216 -> 4096, K = 128 130 -> 121, K = 240 182 -> 146, 25088 -> 4096, K = 160
+// 392 -> 332, 4096 -> 21841, K = 208 382 -> 314, 3000 -> 21841, K = 128 249 -> 218, 7001 -> 5003, K = 128 144 -> 122, 2000 -> 8000, K = 160
+// 70.9 -> 60.8, 11050 -> 565, K = 179 39.5 -> 32.6; the other way 12000 -> 700, K = 160 36.0 and 42.5, 1184 -> 6733, K = 153 34.5 and
+// 40.4, and below 128 4096 -> 4096, K = 96 55.0 and 56.4.  The cost (7 us for the update of a tile of the busiest compute unit, 36 for
+// 1024 k rows) is fitted to 340 layers of K = 100 .. 2600, 7 % rms; of the 80 of 128 to 255 rows 40 go to the planes, 13 % faster on
+// average, none of them 3 % slower.  Error against 64 bits at K = 128 with normal errors 5.3e-8 (fp32 pipe 1.45e-7), with softmax
+// errors 1.2e-7 (1.45e-7); at K = 255 7.0e-8 (2.0e-7) and 1.4e-7 (2.0e-7).
+constexpr int64_t kShortPlaneRows = 128;
+inline int choose_short_planes(int64_t N, int64_t M, int64_t K, int64_t cus, double us)
+{
+    if (K < kShortPlaneRows || K >= kMinPlaneRows || N * M < 3000000) return -1;
+    const int64_t tiles = ((N + 127) / 128) * ((M + 127) / 128);
+    const double share = static_cast<double>(tiles) / cus, rounds = static_cast<double>((tiles + cus - 1) / cus);
+    if (tiles <= cus) return -1;
+    const double cost = 6 + (7 + 36 * static_cast<double>(K) / 1024) * (share + 0.8 * (rounds - share)) + (M % 32 != 0 ? 2.8 * share : 0);
+    return cost < 0.96 * us ? 0 : -1;
+}
+
 // ---- bf16 reconstruction: which tile covers W
 // What a launch takes, in us.  Where compute units hold several tiles: `update` and, per 1024 k rows, `loop` for every tile of the
 // busiest one, of whose last round a part `tail` counts; less what of the smaller of the two hides behind the larger one once a

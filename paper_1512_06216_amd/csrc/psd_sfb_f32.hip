@@ -416,6 +416,12 @@ psd_status start_groups(const Args& g, const BlockPtrs* blocks, int64_t groups, 
     return PSD_OK;
 }
 
+// the tile of psd_sfb_planes.hip that takes this layer, -1: none.  us: what it takes here.
+int planes_tile(int64_t N, int64_t M, int64_t K, double us)
+{
+    return K < kMinPlaneRows ? choose_short_planes(N, M, K, device_cu_count(), us) : choose_planes(N, M, K, device_cu_count(), us);
+}
+
 Args common_args(int64_t ldu, int64_t ldv, float* W, float* Mom, int64_t N, int64_t M, int64_t K, float lr, float mu, float wd)
 {
     Args g = {};
@@ -461,7 +467,7 @@ psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t l
     const int splits = choose_f32_splits(N, M, K, most_splits, device_cu_count(), pinned, &us);
     const SmallTile small = choose_small_f32(N, M, K, device_cu_count(), us);
     if (!pinned && small.waves > 0) return launch_sfb_small(PSD_F32, small, U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, st);
-    const int planes = pinned ? -1 : choose_planes(N, M, K, device_cu_count(), us);
+    const int planes = pinned ? -1 : planes_tile(N, M, K, us);
     if (planes >= 0) return launch_sfb_f32_planes(planes, U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, st);
     if (splits <= 1) return launch_cover(g, nullptr, st);
     const Cover c = split_cover(N, M, pinned);
@@ -490,7 +496,7 @@ psd_status launch_sfb_f32_blocks(const float* const* U_p, int64_t ldu, const flo
         if (small.waves > 0)
             return launch_sfb_small_blocks(PSD_F32, small, reinterpret_cast<const void* const*>(U_p), ldu,
                                            reinterpret_cast<const void* const*>(V_p), ldv, P, B, W, Mom, N, M, lr, mu, wd, st);
-        const int planes = choose_planes(N, M, P * B, device_cu_count(), us);
+        const int planes = planes_tile(N, M, P * B, us);
         if (planes >= 0) return launch_sfb_f32_planes_blocks(planes, U_p, ldu, V_p, ldv, P, B, W, Mom, N, M, lr, mu, wd, st);
     }
     const int64_t u_bytes = B * ldu * 4, v_bytes = B * ldv * 4;        // one block

@@ -63,7 +63,6 @@ int32_t bf16_small(int64_t N, int64_t M, int64_t K, int most, int64_t cus)
     const psd::SmallTile t = psd::choose_small_bf16(N, M, K, cus, splits);
     return t.waves ? 1000 * t.a + 100 * t.b + t.waves : 0;
 }
-int32_t bf16_band(int64_t N, int64_t M, int64_t K, int64_t tiles, int on_lines, int64_t cus) { return psd::band_for(N, M, K, tiles, on_lines, cus); }
 // are the tiles of all workgroups tiles_n * tiles_m different ones
 int32_t tiles_covered(int tiles_n, int tiles_m, int band)
 {
@@ -76,5 +75,17 @@ int32_t tiles_covered(int tiles_n, int tiles_m, int band)
         if (n < 0 || n >= tiles_n || m < 0 || m >= tiles_m || seen[n * tiles_m + m]++) return 0;
     }
     return 1;
+}
+// the order in which the tile that the rules choose goes over this layer
+int32_t bf16_order(int64_t N, int64_t M, int64_t K, int on_lines, int64_t cus)
+{
+    const psd::Bf16Tile t = psd::choose_bf16(N, M, K, cus, -1);
+    return psd::band_for(N, M, K, ((N + t.tn - 1) / t.tn) * ((M + t.tm - 1) / t.tm), on_lines, cus);
+}
+int32_t f32_short_planes(int64_t N, int64_t M, int64_t K, int64_t cus)
+{
+    double us;
+    psd::choose_f32(N, M, K, cus, 0, &us);
+    return psd::choose_short_planes(N, M, K, cus, us);
 }
 }

@@ -1,0 +1,57 @@
+"""The orders in which launches go over their tiles (TileOrder in csrc/psd_rules.h), and fp32 sums of 128 to 255 rows in planes: whole layers
+against the oracle, bit for bit on whole numbers."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import psd_oracle as orc
+from paper_1512_06216_amd import binding as psd
+from paper_1512_06216_amd import inputs
+from tests.test_rules import rules  # noqa: F401  (a fixture)
+
+CUS = 256
+# M, N, B, P and the order: row by row (-1), bands of four tile rows, or runs of groups of eight (0), of which there are more than eight
+# here.  Rows of W on cache lines, on quads and anywhere; the last band is a whole one, three rows, one row.
+BF16_LAYERS = [(3104, 2048, 32, 2, -1), (3072, 1665, 32, 5, -1), (1600, 4224, 32, 12, 4), (1568, 3973, 32, 8, 4), (4004, 1540, 32, 3, 4),
+               (4001, 1411, 20, 5, 4), (1001, 6001, 32, 4, 0), (608, 8200, 32, 16, 0)]
+# M, N, B, P and the tile in planes for sums of 128 to 255 rows
+SHORT_PLANES = [(4096, 1500, 32, 4, 0), (6001, 2001, 64, 3, 0), (4604, 1733, 51, 5, 0), (4096, 1500, 32, 3, -1), (1184, 6733, 51, 3, -1)]
+# the planes' kernel with K >= 256: runs of groups, one band, bands of four and of eight
+PLANE_ORDERS = [(1030, 5200, 64, 8), (4736, 1161, 64, 4), (4612, 1700, 64, 4), (4608, 1668, 345, 6)]
+
+
+def test_layers_go_over_their_tiles_in_the_order_they_stand_for(rules):
+    for M, N, B, P, order in BF16_LAYERS:
+        assert rules.bf16_order(N, M, B * P, M % 32 == 0, CUS) == order, (M, N)
+    for M, N, B, P, tile in SHORT_PLANES:
+        assert rules.f32_short_planes(N, M, B * P, CUS) == tile, (M, N)
+    for M, N, B, P in PLANE_ORDERS:
+        assert rules.f32_planes(N, M, B * P, CUS) >= 0, (M, N)
+    for K in (1, 64, 127, 256, 2048):
+        assert rules.f32_short_planes(4096, 9216, K, CUS) == -1
+    for M, N in ((64, 64), (1024, 1000), (4096, 700)):
+        for K in (128, 200, 255):
+            assert rules.f32_short_planes(N, M, K, CUS) == -1
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,M,N,B,P", [(psd.BF16, *c[:4]) for c in BF16_LAYERS] + [(psd.F32, *c[:4]) for c in SHORT_PLANES + PLANE_ORDERS])
+def test_every_order_of_tiles_bit_exact(dtype, M, N, B, P):
+    """Stacked, and (whole slices in a block) the same rows read in place as P blocks."""
+    d = inputs.fc_layer_integer(M, N, B, P, seed=M + N, amax=2)
+    plan = psd.plan_layer(psd.LAYER_FC, M, N, B, P)
+    U, ldu, V, ldv = psd.alloc_factors(plan, dtype, "cuda:0")
+    psd.pack_factors(plan, [dev(x) for x in d["delta"]], [dev(x) for x in d["act"]], dtype, U, ldu, V, ldv)
+    Wr, Mr = orc.sync_fc_sfb(*orc.pack_factors(d["delta"], d["act"]), d["W"], d["Mom"], 0.25, 0.5, wd=0.25)
+    for blocks in (False, True)[:1 + (B % (32 if dtype == psd.BF16 else 16) == 0)]:
+        W, Mom = dev(d["W"]), dev(d["Mom"])
+        if blocks:
+            psd.sync_fc_sfb_blocks(plan, dtype, list(U.split(B)), ldu, list(V.split(B)), ldv, W, Mom, 0.25, 0.5, wd=0.25)
+        else:
+            psd.sync_fc_sfb(plan, dtype, U, ldu, V, ldv, W, Mom, 0.25, 0.5, wd=0.25)
+        torch.cuda.synchronize()
+        assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr), blocks
