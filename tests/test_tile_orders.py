@@ -17,7 +17,7 @@ BF16_LAYERS = [(3104, 2048, 32, 2, -1), (3072, 1665, 32, 5, -1), (1600, 4224, 32
 # M, N, B, P and the tile in planes for sums of 128 to 255 rows
 SHORT_PLANES = [(4096, 1500, 32, 4, 0), (6001, 2001, 64, 3, 0), (4604, 1733, 51, 5, 0), (4096, 1500, 32, 3, -1), (1184, 6733, 51, 3, -1)]
 # the planes' kernel with K >= 256: runs of groups, one band, bands of four and of eight
-PLANE_ORDERS = [(1030, 5200, 64, 8), (4736, 1161, 64, 4), (4612, 1700, 64, 4), (4608, 1668, 345, 6)]
+PLANE_ORDERS = [(1030, 5200, 64, 8), (4736, 1161, 64, 8), (4612, 1700, 64, 4), (4608, 1668, 345, 6)]
 
 
 def test_layers_go_over_their_tiles_in_the_order_they_stand_for(rules):
