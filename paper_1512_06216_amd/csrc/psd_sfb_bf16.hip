@@ -433,7 +433,7 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
             } else {
                 // (64 x 128 tiles beside InnerUpdate: no deeper than their 168 registers hold)
                 constexpr int DEPTH = C::BM == 4 ? 4 : C::BM == 1 ? 6 : C::FEW && INNER ? 4 : 5;
-                update(RowUpdate<C::ROWS, C::TM, C::WAVES, DEPTH, C::G, decltype(row_n)>(W, Mom, row_n, m0, N, M, wave, lane));
+                update(RowUpdate<C::ROWS, C::TM, C::WAVES, DEPTH, C::G, decltype(row_n), AT == ANYWHERE_FEW>(W, Mom, row_n, m0, N, M, wave, lane));
             }
         }
     }

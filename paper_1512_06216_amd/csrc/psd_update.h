@@ -36,9 +36,84 @@ __device__ __forceinline__ void store_stream4(float* p, float4 x)
     __builtin_nontemporal_store(v, reinterpret_cast<f32x4_nt*>(p));
 }
 
+// A window of W or Mom: what eight rows of a tile are reached by.  Its base is the same for a whole wavefront and lies in scalar
+// registers, and so does the line of the rows; a lane has one offset for all lines.  Lanes that do not own their element ask for
+// one outside the window, which reads as zeros and is not written: no branches stand around the accesses, and the compiler knows
+// at each wait how many later ones may still be on their way.  With branches it waits for all of them, the stores before included,
+// once for every line, and a tile at the edge of W took 20 to 40 us where one inside takes 10.  us, K = 2048 unless said, branches
+// -> windows: 128 x 256 tiles off lines 9999 -> 4095 230.8 -> 216.4, 2545 -> 15057, K = 1072 160.6 -> 156.9; 64 x 128 tiles
+// 5001 -> 1001, K = 512 25.0 -> 23.8; fp32 3840 -> 2020, K = 100 35.1 -> 34.1, 4096 -> 21841, K = 100 266.9 -> 262.7; tiles inside on
+// lines the same (9216 -> 4096 187.1 and 186.4) with 10 registers less.  Not for what is one batch of accesses (BATCHES, LONE: tiles
+// that are alone on their compute unit; whole wavefronts skip what nobody owns there: 1024 -> 1000, K = 1024 8.4 and 9.3), nor for
+// tiles inside off lines of 192 columns and less, which own nearly all they ask for (9999 -> 4095, K = 512 129.5 and 133).
+// Offsets are in bytes and below 2^31: eight rows, at most two apart, of M elements, and M < 2^24 (factors_in_reach in psd_rules.h:
+// M times the reserve of 96 rows and more of factors is below 2^32 bytes).
+#ifdef __HIP_DEVICE_COMPILE__
+constexpr uint32_t kOutside = 0x80000000u;
+constexpr int kStream = 2;                         // the buffer instructions' hint that global ones call nt
+__device__ __forceinline__ auto window(float* at, bool open = true)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(at, 0, open ? 0x7fffffff : 0, 0x00020000);
+}
+typedef uint32_t u32x4_w __attribute__((ext_vector_type(4)));
+template <bool STREAM, class Window>
+__device__ __forceinline__ float4 get4(Window w, uint32_t at, bool own, uint32_t behind = 0)
+{
+    const u32x4_w v = __builtin_amdgcn_raw_buffer_load_b128(w, (own ? at : kOutside) + behind, 0, STREAM ? kStream : 0);
+    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
+}
+template <bool STREAM, class Window>
+__device__ __forceinline__ void put4(Window w, uint32_t at, bool own, float4 x, uint32_t behind = 0)
+{
+    const u32x4_w v = {__float_as_uint(x.x), __float_as_uint(x.y), __float_as_uint(x.z), __float_as_uint(x.w)};
+    __builtin_amdgcn_raw_buffer_store_b128(v, w, (own ? at : kOutside) + behind, 0, STREAM ? kStream : 0);
+}
+template <class Window>
+__device__ __forceinline__ float get1(Window w, uint32_t at, bool own)
+{
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(w, own ? at : kOutside, 0, 0));
+}
+template <class Window>
+__device__ __forceinline__ void put1(Window w, uint32_t at, bool own, float x)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), w, own ? at : kOutside, 0, 0);
+}
+#else
+#define PSD_WINDOW __host__ __device__ __forceinline__
+PSD_WINDOW float* window(float* at, bool open = true) { return open ? at : nullptr; }
+template <bool> PSD_WINDOW float4 get4(float* w, uint32_t at, bool own, uint32_t behind = 0)
+{
+    return own && w ? *reinterpret_cast<float4*>(w + (at + behind) / 4) : make_float4(0, 0, 0, 0);
+}
+template <bool> PSD_WINDOW void put4(float* w, uint32_t at, bool own, float4 x, uint32_t behind = 0)
+{
+    if (own && w) *reinterpret_cast<float4*>(w + (at + behind) / 4) = x;
+}
+PSD_WINDOW float get1(float* w, uint32_t at, bool own) { return own ? w[at / 4] : 0.f; }
+PSD_WINDOW void put1(float* w, uint32_t at, bool own, float x) { if (own) w[at / 4] = x; }
+#undef PSD_WINDOW
+#endif
+
+// ... and the same element by its address
+template <class Place>
+__device__ __forceinline__ float* element(float* X, const Place& p)
+{
+    return reinterpret_cast<float*>(reinterpret_cast<char*>(X + p.rows) + p.off + p.behind);
+}
+
+// What stands before is issued before what stands behind.  (The next batch's loads wait for the first of this one otherwise, where the
+// compiler has registers to spare: 64 x 128 tiles, 4096 -> 4096, K = 256 49.5 us and 48.9; wider tiles are 0.5 % slower with it.)
+__device__ __forceinline__ void in_order()
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+
 // The same number, of which the compiler does not know that it is: what is computed from it anew does not stay in registers
 // from where it was computed before.
-__device__ __forceinline__ int anew(int x)
+template <class T>
+__device__ __forceinline__ T anew(T x)
 {
 #ifdef __HIP_DEVICE_COMPILE__
     asm("" : "+v"(x));
@@ -68,14 +143,15 @@ __host__ __device__ constexpr int row_stride(int width, int64_t M) { return widt
 // are requested by fetch<0>() before the rows are even written, and those of the next DEPTH before the present ones are
 // used.  The quad in which a row begins and the one in which it ends, where M is not a multiple of 4, are shared with the
 // neighbouring tiles: their elements, three at most at each end, are read and written one by one, by lane 4 * end + i of the
-// eight that stand for a row, so that no workgroup touches an element of another's (nor one past the end of W).
+// eight that stand for a row, so that no workgroup touches an element of another's (nor one past the end of W).  LONE: few tiles.
 // Lines that lie inside the tile are streamed (see load_stream4), the ones it shares with its neighbours go
 // through the caches, but for the stores of the narrow tiles of small layers: what lies dirty in L2 when a kernel ends has
 // to be written back before the next one starts, a microsecond that large layers do not notice.
-template <int ROWS, int WIDTH, int WAVES, int DEPTH, int PARTS, class RowN>
+template <int ROWS, int WIDTH, int WAVES, int DEPTH, int PARTS, class RowN, bool LONE = false>
 struct RowUpdate {
     static constexpr int LINES = WIDTH / 32 + 1, GROUPS = ROWS / 8, ALL = GROUPS * LINES;       // units: one line of eight rows
     static constexpr int UNITS = (ALL + WAVES - 1) / WAVES, BATCHES = (UNITS + DEPTH - 1) / DEPTH;
+    static constexpr bool MASKED = BATCHES > 1 && !LONE;
     static constexpr int ENDS = (GROUPS + WAVES - 1) / WAVES;                                   // a wavefront's groups of eight rows
     static_assert(ROWS % 8 == 0 && WIDTH % 32 == 0, "whole lines of eight rows");
     float* W;
@@ -92,7 +168,8 @@ struct RowUpdate {
     {
     }
     struct Place {
-        int64_t off;                               // of this lane's quad in W
+        int64_t rows;                              // the line before the tile in the first of the eight rows, in W
+        uint32_t off, behind;                      // of this lane's quad from there, in bytes: in the first line, and the line
         int at;                                    // ... in the row buffer
         bool quad, whole_line;                     // does the tile own all of it, all of its line
     };
@@ -103,56 +180,77 @@ struct RowUpdate {
         // groups of rows, neighbouring wavefronts take neighbouring lines.
         constexpr bool WALK = GROUPS % WAVES == 0;
         const int id = wave + WAVES * u;
-        const int line = WALK ? u % LINES : id % LINES, r = (WALK ? wave + WAVES * (u / LINES) : id / LINES) * 8 + (lane >> 3);
-        const int q = 4 * (lane & 7);
-        const int64_t n = row_n(r);
+        const bool any = WALK || id < ALL;
+        const int line = WALK ? u % LINES : id % LINES, r0 = 8 * (WALK ? wave + WAVES * (u / LINES) : any ? id / LINES : 0);
+        const int r = r0 + (lane >> 3), q = 4 * (lane & 7);
+        const int64_t n = row_n(r), top = row_n(r0);
         const int first = 32 * line - line_shift(W, n, M);       // column of the line's first element
         const int c = first + q;
         Place p;
         p.at = r * stride + 32 * line + q;
-        p.off = n * M + m0 + c;
-        p.quad = n < N && (WALK || id < ALL) && c >= 0 && c + 3 < cols;
+        p.rows = top * M + m0 - 32;
+        p.off = anew(4 * (static_cast<uint32_t>(n - top) * static_cast<uint32_t>(M) + (c - 32 * line + 32)));
+        p.behind = 128 * line;
+        p.quad = n < N && any && c >= 0 && c + 3 < cols;
         p.whole_line = first >= 0 && first + 32 <= cols;
         return p;
     }
     struct End {
-        int64_t off;
+        int64_t rows;
+        uint32_t off, behind;
         int at;
         bool any;
     };
     __device__ __forceinline__ End end(int e, int lane) const
     {
-        const int group = wave + WAVES * e, r = group * 8 + (lane >> 3), i = lane & 3;
-        const int64_t n = row_n(r);
+        const int group = wave + WAVES * e, r0 = group < GROUPS ? group * 8 : 0, r = r0 + (lane >> 3), i = lane & 3;
+        const int64_t n = row_n(r), top = row_n(r0);
         const int shift = line_shift(W, n, M), before = -shift & 3;
         const int lead = before < cols ? before : cols;          // columns before the first whole quad
         const int last = ((cols + shift) & ~3) - shift;          // column where the quad begins that the tile owns in part
         const int c = lane & 4 ? (last > lead ? last : lead) + i : i;
-        return {n * M + m0 + c, r * stride + shift + c, n < N && group < GROUPS && c < (lane & 4 ? cols : lead)};
+        return {top * M + m0, anew(4 * (static_cast<uint32_t>(n - top) * static_cast<uint32_t>(M) + c)), 0, r * stride + shift + c,
+                n < N && group < GROUPS && c < (lane & 4 ? cols : lead)};
     }
+    static constexpr bool inner_line(int u) { return GROUPS % WAVES == 0 && u % LINES > 0 && u % LINES < LINES - 1; }
     template <int B>
     __device__ __forceinline__ void fetch()
     {
 #pragma unroll
         for (int j = 0; j < DEPTH; ++j) {
-            if (B * DEPTH + j >= UNITS) continue;
-            const Place p = place(B * DEPTH + j);
-            if (!p.quad) continue;
-            if (p.whole_line) {
-                w[B & 1][j] = load_stream4(W + p.off);
-                mo[B & 1][j] = load_stream4(Mom + p.off);
+            const int u = B * DEPTH + j;
+            if (u >= UNITS) continue;
+            const Place p = place(u);
+            float4 &wv = w[B & 1][j], &mv = mo[B & 1][j];
+            if constexpr (!MASKED) {
+                if (!p.quad) continue;
+                if (p.whole_line) {
+                    wv = load_stream4(element(W, p));
+                    mv = load_stream4(element(Mom, p));
+                } else {
+                    wv = *reinterpret_cast<const float4*>(element(W, p));
+                    mv = *reinterpret_cast<const float4*>(element(Mom, p));
+                }
+            } else if (inner_line(u)) {
+                wv = get4<true>(window(W + p.rows), p.off, p.quad, p.behind);
+                mv = get4<true>(window(Mom + p.rows), p.off, p.quad, p.behind);
             } else {
-                w[B & 1][j] = *reinterpret_cast<const float4*>(W + p.off);
-                mo[B & 1][j] = *reinterpret_cast<const float4*>(Mom + p.off);
+                wv = get4<false>(window(W + p.rows), p.off, p.quad, p.behind);
+                mv = get4<false>(window(Mom + p.rows), p.off, p.quad, p.behind);
             }
         }
         if (B == 0 && M % 4 != 0) {
 #pragma unroll
             for (int e = 0; e < ENDS; ++e) {
                 const End p = end(e, lane);
-                if (!p.any) continue;
-                w_end[e] = W[p.off];
-                mo_end[e] = Mom[p.off];
+                if constexpr (!MASKED) {
+                    if (!p.any) continue;
+                    w_end[e] = *element(W, p);
+                    mo_end[e] = *element(Mom, p);
+                } else {
+                    w_end[e] = get1(window(W + p.rows), p.off, p.any);
+                    mo_end[e] = get1(window(Mom + p.rows), p.off, p.any);
+                }
             }
         }
     }
@@ -165,7 +263,7 @@ struct RowUpdate {
             for (int j = 0; j < DEPTH; ++j) {
                 if (B * DEPTH + j >= UNITS) continue;
                 const Place p = place(B * DEPTH + j);
-                if (!p.quad) continue;
+                if (!MASKED && !p.quad) continue;
                 float4 d = *reinterpret_cast<const float4*>(buf + p.at);
 #pragma unroll
                 for (int i = 1; i < PARTS; ++i) {
@@ -177,12 +275,20 @@ struct RowUpdate {
                 upd(d.y, wv.y, mv.y, lr, mu, wd);
                 upd(d.z, wv.z, mv.z, lr, mu, wd);
                 upd(d.w, wv.w, mv.w, lr, mu, wd);
-                if (WIDTH < 128 || p.whole_line) {
-                    store_stream4(Mom + p.off, mv);
-                    store_stream4(W + p.off, wv);
+                const bool stream = WIDTH < 128 || p.whole_line;
+                if constexpr (MASKED) {
+                    put4<true>(window(Mom + p.rows), p.off, p.quad && stream, mv, p.behind);
+                    put4<true>(window(W + p.rows), p.off, p.quad && stream, wv, p.behind);
+                    if constexpr (WIDTH >= 128) {
+                        put4<false>(window(Mom + p.rows), p.off, p.quad && !stream, mv, p.behind);
+                        put4<false>(window(W + p.rows), p.off, p.quad && !stream, wv, p.behind);
+                    }
+                } else if (stream) {
+                    store_stream4(element(Mom, p), mv);
+                    store_stream4(element(W, p), wv);
                 } else {
-                    *reinterpret_cast<float4*>(Mom + p.off) = mv;
-                    *reinterpret_cast<float4*>(W + p.off) = wv;
+                    *reinterpret_cast<float4*>(element(Mom, p)) = mv;
+                    *reinterpret_cast<float4*>(element(W, p)) = wv;
                 }
             }
             if constexpr (B == 0) run_ends(buf, lr, mu, wd);
@@ -195,13 +301,19 @@ struct RowUpdate {
 #pragma unroll
         for (int e = 0; e < ENDS; ++e) {
             const End p = end(e, anew(lane));
-            if (!p.any) continue;
-            float d = buf[p.at];
+            if (!MASKED && !p.any) continue;
+            const int place = p.any ? p.at : 0;
+            float d = buf[place];
 #pragma unroll
-            for (int i = 1; i < PARTS; ++i) d += buf[i * ROWS * stride + p.at];
+            for (int i = 1; i < PARTS; ++i) d += buf[i * ROWS * stride + place];
             upd(d, w_end[e], mo_end[e], lr, mu, wd);
-            Mom[p.off] = mo_end[e];
-            W[p.off] = w_end[e];
+            if constexpr (MASKED) {
+                put1(window(Mom + p.rows), p.off, p.any, mo_end[e]);
+                put1(window(W + p.rows), p.off, p.any, w_end[e]);
+            } else {
+                *element(Mom, p) = mo_end[e];
+                *element(W, p) = w_end[e];
+            }
         }
     }
 };
@@ -212,11 +324,12 @@ struct RowUpdate {
 // before its first whole quad and behind its last are taken one by one, as in RowUpdate.  ON_LINES: rows of W and Mom start on
 // lines (no shift at all).  EDGE, on lines: a tile at the edges of W, of which rows past N (then to be given) and lines past M are
 // left out.  The lines are whole, so that it needs no more than two comparisons, and far fewer registers than RowUpdate: beside it
-// the bf16 tiles on lines take 215 (128 x 192), 151, 124 and 76 (64 x 64) registers; beside RowUpdate 232, 203, 144, 96.
+// the bf16 tiles on lines take 204 (128 x 192), 157, 119 and 67 (64 x 64) registers.
 template <int ROWS, int WIDTH, int WAVES, int DEPTH, bool ON_LINES, class RowN, bool EDGE = false>
 struct InnerUpdate {
     static constexpr int LINES = WIDTH / 32, GROUPS = ROWS / 8 / WAVES;       // a wavefront's groups of eight rows
     static constexpr int UNITS = GROUPS * LINES, BATCHES = (UNITS + DEPTH - 1) / DEPTH;
+    static constexpr bool MASKED = ON_LINES || WIDTH > 192;
     static_assert(ROWS % (8 * WAVES) == 0 && WIDTH % 32 == 0, "whole lines of eight rows");
     static_assert(ON_LINES || !EDGE, "what a tile owns of a line off lines is for RowUpdate to say");
     float* W;
@@ -233,37 +346,45 @@ struct InnerUpdate {
     {
     }
     struct Place {
-        int64_t off;                               // of this lane's quad in W
+        int64_t rows;                              // as in RowUpdate
+        uint32_t off, behind;
         int at;                                    // ... in the row buffer
         bool any;                                  // does the tile own all of it
+        bool line;                                 // EDGE: is the line inside W
     };
     __device__ __forceinline__ Place place(int u) const
     {
-        const int line = u % LINES, r = (wave + WAVES * (u / LINES)) * 8 + (lane >> 3), q = 4 * (lane & 7);
-        const int64_t n = row_n(r);
-        Place p = {n * M + m0 + 32 * line + q, r * stride + 32 * line + q, !EDGE || (n < N && m0 + 32 * line < M)};
-        if constexpr (ON_LINES) return p;
-        const int shift = line_shift(W, n, M);
-        p.off -= shift;
-        if (line == 0) {                           // the first line, and the last in the lanes before the row begins
+        const int line = u % LINES, r0 = (wave + WAVES * (u / LINES)) * 8, r = r0 + (lane >> 3), q = 4 * (lane & 7);
+        const int64_t n = row_n(r), top = row_n(r0);
+        const int shift = ON_LINES ? 0 : line_shift(W, n, M);
+        Place p;
+        p.rows = top * M + m0 - 32;
+        p.off = anew(4 * (static_cast<uint32_t>(n - top) * static_cast<uint32_t>(M) + (q - shift + 32)));
+        p.behind = 128 * line;
+        p.at = r * stride + 32 * line + q;
+        p.any = !EDGE || n < N;
+        p.line = !EDGE || m0 + 32 * line < M;
+        if (!ON_LINES && line == 0) {              // the first line, and the last in the lanes before the row begins
             const int far = q < shift ? WIDTH : 0;
-            p.off += far;
+            p.off += 4 * far;
             p.at += far;
             p.any = q >= shift || q + 3 < shift;
         }
         return p;
     }
     struct End {
-        int64_t off;
+        int64_t rows;
+        uint32_t off, behind;
         int at;
         bool any;
     };
     __device__ __forceinline__ End end(int e, int lane) const
     {
-        const int r = (wave + WAVES * e) * 8 + (lane >> 3), i = lane & 3;
-        const int64_t n = row_n(r);
+        const int r0 = (wave + WAVES * e) * 8, r = r0 + (lane >> 3), i = lane & 3;
+        const int64_t n = row_n(r), top = row_n(r0);
         const int shift = line_shift(W, n, M), behind = shift & 3, c = lane & 4 ? WIDTH - behind + i : i;
-        return {n * M + m0 + c, r * stride + shift + c, i < (lane & 4 ? behind : -shift & 3)};
+        return {top * M + m0, anew(4 * (static_cast<uint32_t>(n - top) * static_cast<uint32_t>(M) + c)), 0, r * stride + shift + c,
+                i < (lane & 4 ? behind : -shift & 3)};
     }
     template <int B>
     __device__ __forceinline__ void fetch()
@@ -273,22 +394,31 @@ struct InnerUpdate {
             const int u = B * DEPTH + j;
             if (u >= UNITS) continue;
             const Place p = place(u);
-            if (EDGE && !p.any) continue;
-            if (ON_LINES || u % LINES > 0) {
-                w[B & 1][j] = load_stream4(W + p.off);
-                mo[B & 1][j] = load_stream4(Mom + p.off);
+            if (MASKED && (ON_LINES || u % LINES > 0)) {
+                w[B & 1][j] = get4<true>(window(W + p.rows, p.line), p.off, p.any, p.behind);
+                mo[B & 1][j] = get4<true>(window(Mom + p.rows, p.line), p.off, p.any, p.behind);
+            } else if (MASKED) {
+                w[B & 1][j] = get4<false>(window(W + p.rows), p.off, p.any);
+                mo[B & 1][j] = get4<false>(window(Mom + p.rows), p.off, p.any);
+            } else if (ON_LINES || u % LINES > 0) {
+                w[B & 1][j] = load_stream4(element(W, p));
+                mo[B & 1][j] = load_stream4(element(Mom, p));
             } else if (p.any) {
-                w[B & 1][j] = *reinterpret_cast<const float4*>(W + p.off);
-                mo[B & 1][j] = *reinterpret_cast<const float4*>(Mom + p.off);
+                w[B & 1][j] = *reinterpret_cast<const float4*>(element(W, p));
+                mo[B & 1][j] = *reinterpret_cast<const float4*>(element(Mom, p));
             }
         }
         if (!ON_LINES && B == 0 && M % 4 != 0) {
 #pragma unroll
             for (int e = 0; e < GROUPS; ++e) {
                 const End p = end(e, lane);
-                if (!p.any) continue;
-                w_end[e] = W[p.off];
-                mo_end[e] = Mom[p.off];
+                if constexpr (MASKED) {
+                    w_end[e] = get1(window(W + p.rows), p.off, p.any);
+                    mo_end[e] = get1(window(Mom + p.rows), p.off, p.any);
+                } else if (p.any) {
+                    w_end[e] = *element(W, p);
+                    mo_end[e] = *element(Mom, p);
+                }
             }
         }
     }
@@ -305,20 +435,27 @@ struct InnerUpdate {
     {
         if constexpr (B < BATCHES) {
             if constexpr (B + 1 < BATCHES) fetch<B + 1>();
+            if constexpr (MASKED && WIDTH <= 128) in_order();
 #pragma unroll
             for (int j = 0; j < DEPTH; ++j) {
                 const int u = B * DEPTH + j;
                 if (u >= UNITS) continue;
                 const Place p = place(u);
-                if (!p.any) continue;
+                if (!MASKED && !p.any) continue;
                 float4 &wv = w[B & 1][j], &mv = mo[B & 1][j];
                 update(buf, p.at, wv, mv, lr, mu, wd);
-                if (ON_LINES || WIDTH < 128 || u % LINES > 0) {
-                    store_stream4(Mom + p.off, mv);
-                    store_stream4(W + p.off, wv);
+                if (MASKED && (ON_LINES || u % LINES > 0)) {
+                    put4<true>(window(Mom + p.rows, p.line), p.off, p.any, mv, p.behind);
+                    put4<true>(window(W + p.rows, p.line), p.off, p.any, wv, p.behind);
+                } else if (MASKED) {
+                    put4<false>(window(Mom + p.rows), p.off, p.any, mv);
+                    put4<false>(window(W + p.rows), p.off, p.any, wv);
+                } else if (ON_LINES || WIDTH < 128 || u % LINES > 0) {
+                    store_stream4(element(Mom, p), mv);
+                    store_stream4(element(W, p), wv);
                 } else {
-                    *reinterpret_cast<float4*>(Mom + p.off) = mv;
-                    *reinterpret_cast<float4*>(W + p.off) = wv;
+                    *reinterpret_cast<float4*>(element(Mom, p)) = mv;
+                    *reinterpret_cast<float4*>(element(W, p)) = wv;
                 }
             }
             if constexpr (!ON_LINES && B == 0) run_ends(buf, lr, mu, wd);
@@ -331,10 +468,15 @@ struct InnerUpdate {
 #pragma unroll
         for (int e = 0; e < GROUPS; ++e) {
             const End p = end(e, anew(lane));
-            if (!p.any) continue;
-            upd(buf[p.at], w_end[e], mo_end[e], lr, mu, wd);
-            Mom[p.off] = mo_end[e];
-            W[p.off] = w_end[e];
+            if (!MASKED && !p.any) continue;
+            upd(buf[p.any ? p.at : 0], w_end[e], mo_end[e], lr, mu, wd);
+            if constexpr (MASKED) {
+                put1(window(Mom + p.rows), p.off, p.any, mo_end[e]);
+                put1(window(W + p.rows), p.off, p.any, w_end[e]);
+            } else {
+                *element(Mom, p) = mo_end[e];
+                *element(W, p) = w_end[e];
+            }
         }
     }
 };

@@ -1,0 +1,48 @@
+"""The update at the edges of W on the GPU, for every tile that reaches it through windows (csrc/psd_update.h): whole layers against the
+oracle, bit for bit on whole numbers, and nothing around W and Mom touched."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import psd_oracle as orc
+from paper_1512_06216_amd import binding as psd
+from paper_1512_06216_amd import inputs
+
+# dtype, tile (-1: the rule's), M, N, elements before W in its cache line.  Rows of W on lines, on quads and anywhere; the last tile of a
+# row and of a column a single element, one less than whole, a line and a bit; tiles of 128 x 256, 128 x 192, 128 x 128, 64 x 128.
+EDGES = [(psd.BF16, t, *c) for t in (0, 1, 2) for c in ((513, 257, 0), (1023, 129, 0), (768, 130, 0), (992, 255, 0), (770, 385, 12), (1, 1, 0),
+                                                        (3, 129, 8), (1000, 300, 4))]
+EDGES += [(psd.BF16, -1, *c) for c in ((5001, 1001, 0), (4128, 1030, 0), (4100, 2051, 4), (9001, 3001, 20))]
+EDGES += [(psd.F32, t, *c) for t in (-1, 1, 2) for c in ((3841, 2021, 0), (1030, 515, 4), (1001, 1025, 0))]
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,tile,M,N,lead", EDGES)
+def test_edges_of_w_bit_exact_and_nothing_around_them(dtype, tile, M, N, lead):
+    B, P = 16, 4
+    d = inputs.fc_layer_integer(M, N, B, P, seed=M + N, amax=2)
+    plan = psd.plan_layer(psd.LAYER_FC, M, N, B, P)
+    U, ldu, V, ldv = psd.alloc_factors(plan, dtype, "cuda:0")
+    psd.pack_factors(plan, [dev(x) for x in d["delta"]], [dev(x) for x in d["act"]], dtype, U, ldu, V, ldv)
+    Wr, Mr = orc.sync_fc_sfb(*orc.pack_factors(d["delta"], d["act"]), d["W"], d["Mom"], 0.25, 0.5, wd=0.25)
+    room, around = 4096 + lead, 1234.5
+    wide = []
+    for x in (d["W"], d["Mom"]):
+        t = torch.full((2 * room + N * M,), around, device="cuda:0")
+        t[room:room + N * M] = dev(x).flatten()
+        wide.append(t)
+    W, Mom = (t[room:room + N * M].view(N, M) for t in wide)
+    knob = psd.TUNE_SFB_BF16_TILE if dtype == psd.BF16 else psd.TUNE_SFB_F32_TILE
+    psd.tune_set(knob, tile)
+    try:
+        psd.sync_fc_sfb(plan, dtype, U, ldu, V, ldv, W, Mom, 0.25, 0.5, wd=0.25)
+        torch.cuda.synchronize()
+    finally:
+        psd.tune_set(knob, -1)
+    assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr)
+    for t in wide:
+        assert bool((t[:room] == around).all()) and bool((t[room + N * M:] == around).all())
