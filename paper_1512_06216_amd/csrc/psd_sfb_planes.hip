@@ -408,19 +408,32 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
     // share, whose launches are short (1000 -> 3001, K = 512 26.6 us; by way of LDS, below, 29.6).
     // The next eight rows of a lane are on their way while the present ones are updated: 4096 -> 4096, K = 256 83.3 -> 78.3 us,
     // 9216 -> 4096, K = 512 240 -> 231, 21760 -> 1344, K = 256 151 -> 137, 4096 -> 4096, K = 2048 330 -> 326 (four at a time 2-4 %
-    // slower than before; all sixteen at once as eight).
+    // slower than before; all sixteen at once as eight).  Tiles of one group by windows (psd_update.h): with branches around the accesses
+    // every row's stores were waited for before the next row, 4096 -> 4096, K = 150 65.2 -> 63.1, K = 512 109.6 -> 108.7, 9216 -> 4096,
+    // K = 256 155.2 -> 153.7, 4096 -> 21841, K = 256 354.9 -> 351.5.  Tiles of several groups, where a lane has one batch of rows, are
+    // 1 % slower so (4096 -> 1000, K = 1024 52.3 and 53.2).
     if (ON_LINES || (G > 1 && M % 4 == 0)) {
         const int64_t mc = m0 + 4 * l32;
+        const int top = 32 * w + (32 / G) * group;
         constexpr int DEPTH = NR < 8 ? NR : 8, BATCHES = NR / DEPTH;
         float4 wv[2][DEPTH], mo[2][DEPTH];
+        const uint32_t off = anew(16 * (static_cast<uint32_t>(lhi) * static_cast<uint32_t>(M) + l32));
+        auto row = [&](int q) { return n0 + top + 8 * (q >> 2) + (q & 3); };       // of the first half of the wavefront
+        auto owned = [&](int q) { return mc < M && row(q) + 4 * lhi < N; };
         auto get = [&](int t) {
 #pragma unroll
             for (int i = 0; i < DEPTH; ++i) {
                 const int q = t * DEPTH + i;
-                const int64_t n = n0 + first + 8 * (q >> 2) + (q & 3), off = n * M + mc;
-                if (n >= N || mc >= M) continue;
-                wv[t & 1][i] = ON_LINES ? load_stream4(g.W + off) : *reinterpret_cast<const float4*>(g.W + off);
-                mo[t & 1][i] = ON_LINES ? load_stream4(g.Mom + off) : *reinterpret_cast<const float4*>(g.Mom + off);
+                const int64_t at = row(q) * M + m0;
+                const bool own = owned(q);
+                if constexpr (G == 1) {
+                    wv[t & 1][i] = get4<ON_LINES>(window(g.W + at), off, own);
+                    mo[t & 1][i] = get4<ON_LINES>(window(g.Mom + at), off, own);
+                } else if (own) {
+                    const int64_t o = at + off / 4;
+                    wv[t & 1][i] = ON_LINES ? load_stream4(g.W + o) : *reinterpret_cast<const float4*>(g.W + o);
+                    mo[t & 1][i] = ON_LINES ? load_stream4(g.Mom + o) : *reinterpret_cast<const float4*>(g.Mom + o);
+                }
             }
         };
         get(0);
@@ -430,19 +443,23 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
 #pragma unroll
             for (int i = 0; i < DEPTH; ++i) {
                 const int q = t * DEPTH + i;
-                const int64_t n = n0 + first + 8 * (q >> 2) + (q & 3), off = n * M + mc;
-                if (n >= N || mc >= M) continue;
+                const int64_t at = row(q) * M + m0;
+                const bool own = owned(q);
+                if (G > 1 && !own) continue;
                 float4 &x = wv[t & 1][i], &y = mo[t & 1][i];
                 upd(d[q][0], x.x, y.x, g.lr, g.mu, g.wd);
                 upd(d[q][1], x.y, y.y, g.lr, g.mu, g.wd);
                 upd(d[q][2], x.z, y.z, g.lr, g.mu, g.wd);
                 upd(d[q][3], x.w, y.w, g.lr, g.mu, g.wd);
-                if constexpr (ON_LINES) {
-                    store_stream4(g.Mom + off, y);
-                    store_stream4(g.W + off, x);
+                if constexpr (G == 1) {
+                    put4<ON_LINES>(window(g.Mom + at), off, own, y);
+                    put4<ON_LINES>(window(g.W + at), off, own, x);
+                } else if constexpr (ON_LINES) {
+                    store_stream4(g.Mom + at + off / 4, y);
+                    store_stream4(g.W + at + off / 4, x);
                 } else {
-                    *reinterpret_cast<float4*>(g.Mom + off) = y;
-                    *reinterpret_cast<float4*>(g.W + off) = x;
+                    *reinterpret_cast<float4*>(g.Mom + at + off / 4) = y;
+                    *reinterpret_cast<float4*>(g.W + at + off / 4) = x;
                 }
             }
         }
