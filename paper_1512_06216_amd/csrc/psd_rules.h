@@ -178,9 +178,9 @@ inline double planes_cost(const PlaneTile& t, int64_t N, int64_t M, int64_t K, i
     return t.first + loop * static_cast<double>(K) / 1024 + t.update * static_cast<double>(N) * M / 4194304;
 }
 
-// Which of them takes this layer, -1: none, the fp32 pipe does.  `us`: its cost there, split or not.  Short contractions stay: at
-// K = 128 the fp32 pipe is the faster one for every size of layer (2624 -> 5037 52 against 58 us for the best of the tiles), at
-// K = 192 for some (4720 -> 868 26.1 and 29.6, 1669 -> 780 12.5 and 12.2, 8404 -> 321 21.1 and 17.5), at K = 256 for hardly any
+// Which of them takes this layer, -1: none, the fp32 pipe does.  `us`: its cost there, split or not.  Sums of less than 256 rows are
+// for the rule below.  With a chip that went over W and Mom in runs of tiles the fp32 pipe was the faster one at K = 128 for every size
+// of layer (2624 -> 5037 52 against 58 us for the best of the tiles), at K = 192 for some (4720 -> 868 26.1 and 29.6, 1669 -> 780 12.5 and 12.2, 8404 -> 321 21.1 and 17.5), at K = 256 for hardly any
 // (672 -> 3462 19.8 and 20.4, 4096 -> 1024 26.1 and 24.5, 4096 -> 4096 90 and 84, 9216 -> 4096 192 and 159), and at K = 320 for
 // none (4096 -> 4096 106 and 89).  A tenth has to be gained by these costs: of 132 layers none then got slower, and the choice was
 // 0.8 % off the best one over the 114; with 6 % it was 0.7 % off, and 672 -> 3462 among the slower ones.  All of this was measured
@@ -341,14 +341,24 @@ inline Bf16Tile choose_bf16_split(int64_t N, int64_t M, int64_t K, int most, int
 // K = 256 9.0 -> 6.8, 4091 -> 125, K = 2048 35.7 -> 30.6 but 25.8 when split, 4096 -> 128, K = 512 12.6 both; bf16 up to K = 256:
 // 1211 -> 256 5.5 -> 4.4, K = 64 4.9 -> 3.7, but K = 512 6.1 and 8.0 for 4096 -> 128, 6.2 and 5.8 for 1211 -> 256.
 // With three, 64 x 64 tiles are as fast or faster (550 tiles, fp32, K = 256 9.1 and 9.0, K = 1024 20.2 and 21.9).
+// b = 4: fp32 on the bf16 pipe, 32 x 64 from 256 k rows on and 64 x 64 from 512 on, where they are alone on their compute unit.  us, the
+// kernels above -> here (factors from HBM; just stacked): 700 -> 700, K = 300 8.4 -> 7.5 (7.8 -> 7.0), K = 512 10.4 -> 9.1 (9.4 -> 8.3),
+// K = 1024 15.6 -> 13.5 (14.3 -> 12.3), 640 -> 640, K = 2048 24.7 -> 21.3 (22.6 -> 20.1), 1200 -> 300, K = 700 12.6 -> 11.4 (11.3 -> 10.3);
+// 64 x 64: 1024 -> 1000, K = 512 14.8 -> 13.9 (12.8 -> 11.4), K = 1024 21.1 -> 19.6 (20.7 -> 18.3), 992 -> 832, K = 1840 32.6 -> 29.1
+// (31.8 -> 27.2), 900 -> 900, K = 700 16.4 both (15.3 -> 14.2).  The other way: 700 -> 700, K = 200 7.0 and 6.9, 600 -> 520, K = 160 6.3 both
+// (5.8 and 6.2), 1024 -> 1000, K = 256 9.8 and 10.8 (9.1 and 8.8); two 64 x 64 for some compute units 1500 -> 1500 26.6 and 31.3.  In three by
+// way of a workspace, whose cost is estimated too high: 768 -> 404, K = 2000 19.4 and 20.9 (17.3 and 20.0).
 struct SmallTile { int a, b, waves; };
 inline int64_t small_tiles(int64_t N, int64_t M, int a, int b) { return ((N + 16 * a - 1) / (16 * a)) * ((M + 16 * b - 1) / (16 * b)); }
-inline SmallTile choose_small_f32(int64_t N, int64_t M, int64_t K, int64_t cus, double us)
+inline SmallTile choose_small_f32(int64_t N, int64_t M, int64_t K, int64_t cus, int splits, double us)
 {
     if (small_tiles(N, M, 1, 1) <= cus) return {1, 1, 16};
     if (small_tiles(N, M, 1, 2) <= cus) return {1, 2, 16};
     if (small_tiles(N, M, 2, 2) <= cus) return {2, 2, 16};
-    return {2, 2, small_tiles(N, M, 2, 2) <= 2 * cus && 3.2 + 12.6 * static_cast<double>(K) / 1024 < us ? 8 : 0};
+    const double k = static_cast<double>(K) / 1024, limit = (splits > 1 ? 0.8 : 1.0) * us;
+    if (small_tiles(N, M, 2, 4) <= cus && K >= 256 && 5 + 7.4 * k < limit) return {2, 4, 8};
+    if (small_tiles(N, M, 4, 4) <= cus && K >= 512 && 6 + 11.9 * k < limit) return {4, 4, 8};
+    return {2, 2, small_tiles(N, M, 2, 2) <= 2 * cus && 3.2 + 12.6 * k < us ? 8 : 0};
 }
 inline SmallTile choose_small_bf16(int64_t N, int64_t M, int64_t K, int64_t cus, int splits)
 {

@@ -2,9 +2,9 @@
 // Eq. 5; Algorithm 3's update line):
 //     dW[n][m] = sum_k U[k][n] * V[k][m] ;  Mom = mu*Mom + lr*dW ;  W = W - Mom
 //
-// Small layers and short contractions, on the fp32 MFMA pipe (v_mfma_f32_32x32x2_f32: one k per lane, which is exactly how the
-// K-outer stacked factors sit in memory -- no transpose is needed for fp32).  The others go to psd_sfb_planes.hip
-// (choose_planes): 4096 -> 1000, K = 2048 124 -> 88 us, 9216 -> 4096 1066 -> 700 us; the smallest to psd_sfb_small.hip.
+// Short contractions, on the fp32 MFMA pipe (v_mfma_f32_32x32x2_f32: one k per lane, which is exactly how the K-outer stacked factors
+// sit in memory -- no transpose is needed for fp32).  The others go to psd_sfb_planes.hip (choose_planes, choose_short_planes):
+// 9216 -> 4096, K = 2048 1066 -> 700 us; small layers to psd_sfb_small.hip (choose_small_f32).
 //
 // Tiling: a 256-lane workgroup (4 wavefronts, 2 x 2) owns a 128 x 128, 64 x 128 or 64 x 64 tile of W; each wavefront a
 // quarter of it in 32 x 32 MFMA blocks.  MFMA row i of block t stands for n = n0 + BN*i + t (columns m likewise), so one
@@ -465,7 +465,7 @@ psd_status launch_sfb_f32(const float* U, int64_t ldu, const float* V, int64_t l
     const int pinned = pinned_tile();
     double us;
     const int splits = choose_f32_splits(N, M, K, most_splits, device_cu_count(), pinned, &us);
-    const SmallTile small = choose_small_f32(N, M, K, device_cu_count(), us);
+    const SmallTile small = choose_small_f32(N, M, K, device_cu_count(), splits, us);
     if (!pinned && small.waves > 0) return launch_sfb_small(PSD_F32, small, U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, st);
     const int planes = pinned ? -1 : planes_tile(N, M, K, us);
     if (planes >= 0) return launch_sfb_f32_planes(planes, U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, st);
@@ -492,7 +492,7 @@ psd_status launch_sfb_f32_blocks(const float* const* U_p, int64_t ldu, const flo
     if (!pinned_tile()) {
         double us;
         choose_f32(N, M, P * B, device_cu_count(), 0, &us);
-        const SmallTile small = choose_small_f32(N, M, P * B, device_cu_count(), us);
+        const SmallTile small = choose_small_f32(N, M, P * B, device_cu_count(), 1, us);
         if (small.waves > 0)
             return launch_sfb_small_blocks(PSD_F32, small, reinterpret_cast<const void* const*>(U_p), ldu,
                                            reinterpret_cast<const void* const*>(V_p), ldv, P, B, W, Mom, N, M, lr, mu, wd, st);

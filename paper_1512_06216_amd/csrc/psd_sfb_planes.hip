@@ -1,5 +1,5 @@
 // SFB reconstruction with fused momentum-SGD update, fp32 factors on the bf16 MFMA pipe (the same contraction and update as
-// psd_sfb_f32.hip, which keeps the small layers):
+// psd_sfb_f32.hip, which keeps the short sums):
 //     dW[n][m] = sum_k U[k][n] * V[k][m] ;  Mom = mu*Mom + lr*dW ;  W = W - Mom
 //
 // An fp32 number is the exact sum of three bf16 numbers, x = h + m + l: each is the nearest bf16 to what is left, 8 significant

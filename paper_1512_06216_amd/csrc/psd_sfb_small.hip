@@ -1,4 +1,4 @@
-// SFB reconstruction with fused momentum-SGD update for the smallest layers, fp32 and bf16 factors (Section 4.3.1 step 3, Eq. 5;
+// SFB reconstruction with fused momentum-SGD update for small layers, fp32 and bf16 factors (Section 4.3.1 step 3, Eq. 5;
 // Algorithm 3's update line):
 //     dW[n][m] = sum_k U[k][n] * V[k][m] ;  Mom = mu*Mom + lr*dW ;  W = W - Mom
 //
@@ -15,21 +15,27 @@
 // 17.0), 256 -> 256 33.2 -> 8.3 (13.8), 64 -> 64, K = 4096 62 -> 11.3 (20.2); bf16 399 -> 391, K = 768 6.8 -> 4.8, 1000 -> 256,
 // K = 1024 8.1 -> 6.2, 256 -> 256, K = 2048 9.9 -> 7.9.  Error of dW against 64 bits: fp32 K = 2048 2.9e-7 -> 2.1e-7 with 8 runs over k
 // and 1.6e-7 with 16 (there 4), K = 128 9.0e-8 -> 7.8e-8; bf16, K = 2048 1.1e-7 -> 7.6e-8.
+// Somewhat larger fp32 layers in tiles of 32 x 64 and 64 x 64 in the same way, contracted in bf16 planes (SumPlanes) by eight wavefronts,
+// where the kernels for larger tiles leave most of the chip to idle or stay on the fp32 pipe.  256 more rows of a 64 x 64 tile take
+// 3.0 us, for 1.3 of which the matrix pipe is busy; the rest goes to the cutting, 11 vector instructions for two elements, and to
+// loads that are one slice ahead (two ahead 700 -> 700, K = 512 9.2 and 10.0 us, in 202 registers instead of 154).  700 -> 700,
+// K = 1024 15.6 -> 13.5, 640 -> 640, K = 2048 24.7 -> 21.3, 1024 -> 1000 38.4 -> 33.2; error against 64 bits there 1.6e-7 and 2.9e-7 -> 1.0e-7.
 // Which layers: choose_small_f32 and choose_small_bf16 in psd_rules.h.
 // Each XCD takes a contiguous run of the tiles, along the rows of W: they share columns of U in its L2, and lines of W at their borders
 // (dealt out one by one 731 -> 704, bf16, K = 1024 takes 12.1 us, not 10.0; fp32 the same within 5 %).
 #include <atomic>
 #include "psd_device.h"
 #include "psd_internal.h"
+#include "psd_planes.h"
 
 namespace psd {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int AHEAD = 3;            // slices of k on their way to a wavefront
 
 struct BlockPtrs { const void* u[PSD_MAX_WORKERS]; const void* v[PSD_MAX_WORKERS]; };
 
@@ -49,7 +55,13 @@ template <int WORDS>
 __device__ __forceinline__ void load_or_zero(uint32_t (&x)[WORDS], const Feed& f, uint32_t off)
 {
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(f.base), 0, static_cast<int>(f.left), 0x00020000);
-    if constexpr (WORDS == 2) {
+    if constexpr (WORDS == 4) {
+        const auto y = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0);
+        x[0] = y[0];
+        x[1] = y[1];
+        x[2] = y[2];
+        x[3] = y[3];
+    } else if constexpr (WORDS == 2) {
         const auto y = __builtin_amdgcn_raw_buffer_load_b64(rsrc, off, 0, 0);
         x[0] = y[0];
         x[1] = y[1];
@@ -64,8 +76,11 @@ template <int A_, int B_>
 struct SumF32 {
     static constexpr int A = A_, B = B_, SLICE = 16, BYTES = 4;       // k rows of a slice; bytes of an element
     static constexpr int LOADS = 4, WU = A, WV = B;                   // of a slice, words of each load for the two factors
+    static constexpr int PARTS = 1;                                   // of a slice, which need not be neighbours in memory
+    static constexpr int AHEAD = A * B > 4 ? 1 : 3;                   // slices of k on their way to a wavefront
+    static constexpr bool PLANES = false;
     f32x4 acc[A][B] = {};
-    // load j of a lane: row 4*j + lane/16 of the slice, its column of every block
+    // load j of a lane: row 4*j + lane/16 of the slice (of the load's part of it), its column of every block
     static __device__ __forceinline__ int row(int lane, int j) { return 4 * j + (lane >> 4); }
     static __device__ __forceinline__ int column(int lane, int blocks) { return blocks * (lane & 15); }
     __device__ __forceinline__ void add(const uint32_t (&u)[LOADS][WU], const uint32_t (&v)[LOADS][WV])
@@ -81,7 +96,8 @@ struct SumF32 {
 };
 
 struct SumBf16 {
-    static constexpr int A = 2, B = 2, SLICE = 32, BYTES = 2, LOADS = 8, WU = 1, WV = 1;
+    static constexpr int A = 2, B = 2, SLICE = 32, BYTES = 2, LOADS = 8, WU = 1, WV = 1, PARTS = 1, AHEAD = 3;
+    static constexpr bool PLANES = false;
     f32x4 acc[2][2] = {};
     // load j of a lane: row 8*(lane/16) + j of the slice, its column of both blocks
     static __device__ __forceinline__ int row(int lane, int j) { return 8 * (lane >> 4) + j; }
@@ -103,39 +119,71 @@ struct SumBf16 {
     }
 };
 
-template <class Sum, int WAVES, bool BLK>
-__device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks)
-{
-    constexpr int SLICE = Sum::SLICE, THREADS = 64 * WAVES, TN = 16 * Sum::A, TM = 16 * Sum::B;
-    constexpr int STRIDE = TM + 8;               // row of a wavefront's sums in LDS, in floats: rows 4 apart fall on other banks
-    constexpr int OWN = (TN * TM + THREADS - 1) / THREADS;         // weights of a lane in the update
-    extern __shared__ __attribute__((aligned(16))) float sums[];   // of each wavefront, TN rows
-    const int b = blockIdx.x, xcd = b & 7;
-    const int lin = xcd * (g.tiles >> 3) + (xcd < (g.tiles & 7) ? xcd : (g.tiles & 7)) + (b >> 3);
-    const int64_t n0 = int64_t(lin / g.tiles_m) * TN, m0 = int64_t(lin % g.tiles_m) * TM;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t M = g.M;
-
-    // this lane's weights, on their way while the sums are made
-    float w[OWN], mo[OWN];
-    int64_t off[OWN];
-    bool own[OWN];
+// fp32 factors in three bf16 planes, six products of which stand for the product (psd_sfb_planes.hip, which cuts for all wavefronts of
+// a workgroup; here each wavefront cuts what it feeds).  The five small ones of a slice are added up by themselves.
+template <int A_, int B_>
+struct SumPlanes {
+    static constexpr int A = A_, B = B_, SLICE = 32, BYTES = 4, LOADS = 8, WU = A, WV = B, PARTS = 2, AHEAD = 1;
+    static constexpr bool PLANES = true;
+    f32x4 acc[A][B] = {};
+    // load j of a lane: row 4*(lane/16) + j%4 of 16 rows, its column of every block
+    static __device__ __forceinline__ int row(int lane, int j) { return 4 * (lane >> 4) + (j & 3); }
+    static __device__ __forceinline__ int column(int lane, int blocks) { return blocks * (lane & 15); }
+    static __device__ __forceinline__ uint32_t to_bf16(float a, float b)
+    {
+        const f32x2 x = {a, b};
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
+    }
+    template <int WORDS>
+    static __device__ __forceinline__ void planes(const uint32_t (&x)[LOADS][WORDS], int i, u32x4 (&p)[3])
+    {
 #pragma unroll
-    for (int i = 0; i < OWN; ++i) {
-        const int at = i * THREADS + tid;
-        const int64_t n = n0 + at / TM, m = m0 + at % TM;
-        own[i] = at < TN * TM && n < g.N && m < M;
-        off[i] = n * M + m;
-        if (own[i]) {
-            w[i] = g.W[off[i]];
-            mo[i] = g.Mom[off[i]];
+        for (int q = 0; q < 4; ++q) {
+            uint32_t h, m, l;
+            cut(__uint_as_float(x[2 * q][i]), __uint_as_float(x[2 * q + 1][i]), h, m, l, to_bf16);
+            p[0][q] = h; p[1][q] = m; p[2][q] = l;
         }
     }
-
-    const uint32_t row_u = static_cast<uint32_t>(g.ldu * Sum::BYTES), row_v = static_cast<uint32_t>(g.ldv * Sum::BYTES);
-    uint32_t off_u[Sum::LOADS], off_v[Sum::LOADS];
+    __device__ __forceinline__ void add(const uint32_t (&u)[LOADS][WU], const uint32_t (&v)[LOADS][WV])
+    {
+        u32x4 a[A][3];
 #pragma unroll
-    for (int j = 0; j < Sum::LOADS; ++j) {
+        for (int i = 0; i < A; ++i) planes(u, i, a[i]);
+#pragma unroll
+        for (int c = 0; c < B; ++c) {
+            u32x4 b[3];
+            planes(v, c, b);
+            f32x4 low[A] = {};
+            auto product = [&](int pa, int pb, f32x4 (&to)[A]) {
+#pragma unroll
+                for (int i = 0; i < A; ++i)
+                    to[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[i][pa]), __builtin_bit_cast(bf16x8, b[pb]), to[i], 0, 0, 0);
+            };
+            product(2, 0, low);
+            product(0, 2, low);
+            product(1, 1, low);
+            product(1, 0, low);
+            product(0, 1, low);
+#pragma unroll
+            for (int i = 0; i < A; ++i) low[i] += acc[i][c];
+            product(0, 0, low);
+#pragma unroll
+            for (int i = 0; i < A; ++i) acc[i][c] = low[i];
+        }
+    }
+};
+
+constexpr int row_floats(int columns) { return columns + 8; }         // a row of sums in LDS: rows 4 apart fall on other banks
+
+// A wavefront's sums of the tile at (n0, m0), to its rows of `sums`.
+template <class Sum, int WAVES, bool BLK>
+__device__ __forceinline__ void contract(const Args& g, const BlockPtrs* blocks, int64_t n0, int64_t m0, int lane, int wave, float* sums)
+{
+    constexpr int SLICE = Sum::SLICE, TN = 16 * Sum::A, STRIDE = row_floats(16 * Sum::B), EACH = Sum::LOADS / Sum::PARTS;
+    const uint32_t row_u = static_cast<uint32_t>(g.ldu * Sum::BYTES), row_v = static_cast<uint32_t>(g.ldv * Sum::BYTES);
+    uint32_t off_u[EACH], off_v[EACH];
+#pragma unroll
+    for (int j = 0; j < EACH; ++j) {
         off_u[j] = Sum::row(lane, j) * row_u + static_cast<uint32_t>(n0 + Sum::column(lane, Sum::A)) * Sum::BYTES;
         off_v[j] = Sum::row(lane, j) * row_v + static_cast<uint32_t>(m0 + Sum::column(lane, Sum::B)) * Sum::BYTES;
     }
@@ -157,26 +205,29 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
             v.aim(g.V, uint64_t(row) * row_v, g.v_bytes);
         }
     };
-    uint32_t xu[AHEAD][Sum::LOADS][Sum::WU], xv[AHEAD][Sum::LOADS][Sum::WV];
+    uint32_t xu[Sum::AHEAD][Sum::LOADS][Sum::WU], xv[Sum::AHEAD][Sum::LOADS][Sum::WV];
     auto load = [&](int s) {                     // the wavefront's next slice; past K: zeros
-        aim();
 #pragma unroll
-        for (int j = 0; j < Sum::LOADS; ++j) load_or_zero(xu[s][j], u, off_u[j]);
+        for (int p = 0; p < Sum::PARTS; ++p) {
+            aim();
 #pragma unroll
-        for (int j = 0; j < Sum::LOADS; ++j) load_or_zero(xv[s][j], v, off_v[j]);
-        row += SLICE * WAVES;
+            for (int j = 0; j < EACH; ++j) load_or_zero(xu[s][p * EACH + j], u, off_u[j]);
+#pragma unroll
+            for (int j = 0; j < EACH; ++j) load_or_zero(xv[s][p * EACH + j], v, off_v[j]);
+            row += p + 1 < Sum::PARTS ? SLICE / Sum::PARTS : SLICE * WAVES - SLICE / Sum::PARTS * p;
+        }
     };
     const int slices = g.K / SLICE + (g.K % SLICE > 0), steps = slices > wave ? (slices - wave + WAVES - 1) / WAVES : 0;
     Sum sum;
 #pragma unroll
-    for (int s = 0; s < AHEAD; ++s)
+    for (int s = 0; s < Sum::AHEAD; ++s)
         if (s < steps) load(s);
-    for (int t = 0; t < steps; t += AHEAD) {
+    for (int t = 0; t < steps; t += Sum::AHEAD) {
 #pragma unroll
-        for (int s = 0; s < AHEAD; ++s) {
+        for (int s = 0; s < Sum::AHEAD; ++s) {
             if (t + s >= steps) break;
             sum.add(xu[s], xv[s]);
-            if (t + s + AHEAD < steps) load(s);
+            if (t + s + Sum::AHEAD < steps) load(s);
         }
     }
 #pragma unroll
@@ -187,22 +238,72 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
 #pragma unroll
             for (int c = 0; c < Sum::B; ++c) to[c] = sum.acc[i][c][r];
         }
-    __syncthreads();
+}
+
+template <class Sum, int WAVES, bool BLK>
+__device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks)
+{
+    constexpr int THREADS = 64 * WAVES, TN = 16 * Sum::A, TM = 16 * Sum::B, STRIDE = row_floats(TM);
+    constexpr int OWN = (TN * TM + THREADS - 1) / THREADS;         // weights of a lane in the update
+    extern __shared__ __attribute__((aligned(16))) float sums[];   // of each wavefront, TN rows
+    const int b = blockIdx.x, xcd = b & 7;
+    const int lin = xcd * (g.tiles >> 3) + (xcd < (g.tiles & 7) ? xcd : (g.tiles & 7)) + (b >> 3);
+    const int64_t n0 = int64_t(lin / g.tiles_m) * TN, m0 = int64_t(lin % g.tiles_m) * TM;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t M = g.M;
+
+    // this lane's weights, on their way while the sums are made: one column of every APART-th row of the tile
+    constexpr int APART = THREADS / TM;
+    static_assert(THREADS % TM == 0, "whole rows");
+    const int64_t n = n0 + tid / TM;
+    const uint32_t place = static_cast<uint32_t>(tid / TM) * static_cast<uint32_t>(M) + tid % TM;      // (below 2^32: 64 rows of less than 2^24)
+    float w[OWN], mo[OWN];
+    auto own = [&](int i) { return (OWN * APART <= TN || tid / TM < TN) && n + i * APART < g.N && m0 + tid % TM < M; };
+    auto from = [&](float* X, int i) { return X + (n0 + i * APART) * M + m0; };
+#pragma unroll
+    for (int i = 0; i < OWN; ++i)
+        if (own(i)) {
+            w[i] = from(g.W, i)[place];
+            mo[i] = from(g.Mom, i)[place];
+        }
+    float d[OWN];
+    auto gather = [&]() {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) {
+            const float* from = sums + (OWN * APART <= TN || tid / TM < TN ? tid / TM + i * APART : 0) * STRIDE + tid % TM;
+            float x[WAVES];
+#pragma unroll
+            for (int s = 0; s < WAVES; ++s) x[s] = from[s * TN * STRIDE];
+#pragma unroll
+            for (int h = WAVES / 2; h > 0; h /= 2)   // in pairs
+#pragma unroll
+                for (int s = 0; s < h; ++s) x[s] += x[s + h];
+            d[i] = x[0];
+        }
+    };
+    contract<Sum, WAVES, BLK>(g, blocks, n0, m0, lane, wave, sums);
+    gather();
+    if constexpr (Sum::PLANES) {
+        // A tile with a sum that is not finite (infinities, NaN, factors above 2^104, sums above 2^80) is contracted anew on the fp32 pipe.
+        float nan = 0.f;
+#pragma unroll
+        for (int i = 0; i < OWN; ++i)
+            if (own(i)) nan = __fmaf_rn(d[i], 0.f, nan);
+        if (__syncthreads_or(nan != 0.f)) {
+            contract<SumF32<Sum::A, Sum::B>, WAVES, BLK>(g, blocks, n0, m0, lane, wave, sums);
+            gather();
+        } else {
+#pragma unroll
+            for (int i = 0; i < OWN; ++i) d[i] *= kPlaneUnscale;
+        }
+    }
 #pragma unroll
     for (int i = 0; i < OWN; ++i) {
-        if (!own[i]) continue;
-        const int at = i * THREADS + tid;
-        const float* from = sums + at / TM * STRIDE + at % TM;
-        float d[WAVES];
-#pragma unroll
-        for (int s = 0; s < WAVES; ++s) d[s] = from[s * TN * STRIDE];
-#pragma unroll
-        for (int h = WAVES / 2; h > 0; h /= 2)   // in pairs
-#pragma unroll
-            for (int s = 0; s < h; ++s) d[s] += d[s + h];
-        upd(d[0], w[i], mo[i], g.lr, g.mu, g.wd);
-        g.Mom[off[i]] = mo[i];
-        g.W[off[i]] = w[i];
+        if (!own(i)) continue;
+        upd(d[i], w[i], mo[i], g.lr, g.mu, g.wd);
+        from(g.Mom, i)[place] = mo[i];
+        from(g.W, i)[place] = w[i];
     }
 }
 
@@ -221,7 +322,7 @@ __global__ void __launch_bounds__(64 * WAVES) sfb_small_blocks_kernel(const Args
 template <class Sum, int WAVES>
 psd_status start(Args& g, const BlockPtrs* blocks, hipStream_t st)
 {
-    constexpr int TN = 16 * Sum::A, TM = 16 * Sum::B, lds = WAVES * TN * (TM + 8) * 4;
+    constexpr int TN = 16 * Sum::A, TM = 16 * Sum::B, lds = WAVES * TN * row_floats(TM) * 4;
     g.tiles_m = (g.M + TM - 1) / TM;
     g.tiles = (g.N + TN - 1) / TN * g.tiles_m;
     if constexpr (lds > 65536) {
@@ -246,6 +347,8 @@ psd_status start(Args& g, const BlockPtrs* blocks, hipStream_t st)
 psd_status dispatch(int32_t dtype, const SmallTile& tile, Args& g, const BlockPtrs* blocks, hipStream_t st)
 {
     if (dtype == PSD_BF16) return tile.waves == 8 ? start<SumBf16, 8>(g, blocks, st) : start<SumBf16, 16>(g, blocks, st);
+    if (tile.b == 4)
+        return tile.a == 4 ? start<SumPlanes<4, 4>, 8>(g, blocks, st) : start<SumPlanes<2, 4>, 8>(g, blocks, st);
     if (tile.b == 1) return start<SumF32<1, 1>, 16>(g, blocks, st);
     if (tile.a == 1) return start<SumF32<1, 2>, 16>(g, blocks, st);
     return tile.waves == 8 ? start<SumF32<2, 2>, 8>(g, blocks, st) : start<SumF32<2, 2>, 16>(g, blocks, st);

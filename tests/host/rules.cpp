@@ -52,8 +52,8 @@ int32_t f32_splits(int64_t N, int64_t M, int64_t K, int most, int64_t cus) { ret
 int32_t f32_small(int64_t N, int64_t M, int64_t K, int most, int64_t cus)
 {
     double us;
-    psd::choose_f32_splits(N, M, K, most, cus, 0, &us);
-    const psd::SmallTile t = psd::choose_small_f32(N, M, K, cus, us);
+    const int splits = psd::choose_f32_splits(N, M, K, most, cus, 0, &us);
+    const psd::SmallTile t = psd::choose_small_f32(N, M, K, cus, splits, us);
     return t.waves ? 1000 * t.a + 100 * t.b + t.waves : 0;
 }
 int32_t bf16_small(int64_t N, int64_t M, int64_t K, int most, int64_t cus)

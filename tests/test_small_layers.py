@@ -15,7 +15,10 @@ CASES = [(1, 1, 1, 1, 1116, 2216), (31, 33, 5, 3, 1116, 2216), (32, 32, 16, 1, 1
          (65, 64, 64, 8, 1116, 2216), (256, 256, 16, 16, 1116, 2216), (257, 256, 16, 17, 1216, 2216), (64, 67, 128, 4, 1116, 2216),
          (257, 96, 43, 3, 1116, 2216), (500, 130, 17, 15, 1216, 2216), (512, 256, 48, 11, 1216, 2216), (512, 257, 32, 4, 2216, 2216),
          (512, 512, 32, 4, 2216, 2216), (511, 509, 48, 3, 2216, 2216), (513, 512, 32, 4, 2208, 2208), (1000, 250, 96, 16, 2216, 2216),
-         (1024, 512, 64, 4, 2208, 2208), (1023, 505, 16, 17, 2208, 0), (1025, 512, 32, 4, 0, 0), (64, 8192, 33, 2, 2208, 2208)]
+         (1024, 512, 51, 5, 2208, 2208), (1023, 505, 14, 18, 2208, 2208), (1025, 512, 32, 4, 0, 0), (64, 8192, 33, 2, 2208, 2208),
+         # fp32 on the bf16 pipe: slices of 32 rows in halves, a round of the wavefronts 256
+         (1024, 512, 64, 4, 2408, 2208), (1023, 505, 16, 17, 2408, 0), (700, 641, 48, 11, 2408, 0), (65, 8192, 33, 16, 4408, 0),
+         (1025, 512, 64, 4, 0, 0), (1025, 512, 64, 8, 4408, 0), (1024, 1024, 48, 11, 4408, 0), (257, 3200, 67, 9, 4408, 0), (1025, 1024, 64, 8, 0, 0)]
 LAYERS = [c[:4] for c in CASES]
 
 
@@ -23,7 +26,8 @@ def test_small_layers_lie_on_both_sides_of_the_rule(rules):
     for M, N, B, P, f32, bf16 in CASES:
         assert (rules.f32_small(N, M, B * P, 1, CUS), rules.bf16_small(N, M, B * P, 1, CUS)) == (f32, bf16), (M, N, B, P)
     assert rules.bf16_small(64, 64, 3000, 4, CUS) == 0 and rules.bf16_small(64, 64, 3000, 1, CUS) == 2216     # split by way of a workspace, or not
-    assert rules.f32_small(64, 64, 4096, 4, CUS) == 1116 and rules.f32_small(125, 4091, 2048, 4, CUS) == 0
+    assert rules.f32_small(64, 64, 4096, 4, CUS) == 1116
+    assert rules.f32_small(404, 768, 2000, 1, CUS) == 2408 and rules.f32_small(404, 768, 2000, 3, CUS) == 0
 
 
 def dev(a):
@@ -59,7 +63,7 @@ def test_small_layer_bit_exact(M, N, B, P, dtype):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [psd.F32, psd.BF16])
-@pytest.mark.parametrize("M,N,K", [(500, 300, 2048), (700, 640, 200), (64, 64, 2400)])
+@pytest.mark.parametrize("M,N,K", [(500, 300, 2048), (700, 640, 200), (64, 64, 2400), (700, 640, 2048), (1000, 1000, 2048)])
 def test_small_layer_error_against_64_bits(M, N, K, dtype):
     """8 or 16 runs over k, added up in pairs: K / 8 + 3 roundings of 2^-24 each at most, random ones grow with the root of their number.  The
     fp32 kernel for larger tiles, four runs, has 2.9e-7 at K = 2048."""
@@ -75,3 +79,32 @@ def test_small_layer_error_against_64_bits(M, N, K, dtype):
     want = u.double().t().contiguous() @ v.double()
     rel = ((Mom.cpu().double() - want).norm() / want.norm()).item()
     assert rel <= 2.5e-7, rel
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,B,P,tile", [(1000, 500, 64, 8, 2408), (1001, 1003, 64, 9, 4408)])
+def test_tiles_in_planes_with_sums_that_are_not_finite(rules, M, N, B, P, tile):
+    """Infinities, NaN and factors past 2^104 give what fp32 gives; the tiles without them are none the wiser."""
+    K = B * P
+    assert rules.f32_small(N, M, K, 1, CUS) == tile
+    g = torch.Generator().manual_seed(M)
+    u, v = torch.randn(K, N, generator=g).mul_(1e-3), torch.randn(K, M, generator=g).relu_()
+    u[7, 3], u[K - 1, N - 1], v[5, 70], v[40, M - 1] = float("inf"), float("-inf"), float("nan"), float("inf")
+    u[33, 200], v[33] = 2.0 ** 110, v[33] * 2.0 ** -20
+    plan = psd.plan_layer(psd.LAYER_FC, M, N, B, P)
+    want = (u.double().t().contiguous() @ v.double()).numpy()
+    scale = (u.double().abs().t().contiguous() @ v.double().abs()).numpy()
+    for blocks in (False, True):
+        U, ldu, V, ldv = psd.alloc_factors(plan, psd.F32, "cuda:0")
+        psd.pack_factors(plan, [x.cuda().contiguous() for x in u.split(B)], [x.cuda().contiguous() for x in v.split(B)], psd.F32, U, ldu, V, ldv)
+        W, Mom = torch.zeros(N, M, device="cuda:0"), torch.zeros(N, M, device="cuda:0")
+        if blocks:
+            psd.sync_fc_sfb_blocks(plan, psd.F32, list(U.split(B)), ldu, list(V.split(B)), ldv, W, Mom, 1.0, 0.0)
+        else:
+            psd.sync_fc_sfb(plan, psd.F32, U, ldu, V, ldv, W, Mom, 1.0, 0.0)
+        got = Mom.cpu().double().numpy()
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        inf = np.isinf(want)
+        assert np.array_equal(got[inf], want[inf])
+        ok = np.isfinite(want)
+        assert np.all(np.abs(got[ok] - want[ok]) <= (K / 8 + 16) * 2.0 ** -24 * scale[ok])      # at most so many roundings of a sum
