@@ -17,7 +17,7 @@
 namespace psd {
 namespace {
 
-constexpr int kThreads = 1024, kInFlight = 8;
+constexpr int kThreads = 512, kInFlight = 8;
 
 template <bool BF16, int COLS>
 __global__ void __launch_bounds__(kThreads)
