@@ -178,6 +178,30 @@ inline double planes_cost(const PlaneTile& t, int64_t N, int64_t M, int64_t K, i
     return t.first + loop * static_cast<double>(K) / 1024 + t.update * static_cast<double>(N) * M / 4194304;
 }
 
+// kPlaneHalves: tiles of 128 x 128 of which the last ones, those beyond whole rounds over the chip, are left to two workgroups each (64 x 128
+// with two groups), where that is one more workgroup for each compute unit at most: the others would idle while a few work through one
+// more tile.  us, the best of the tiles above -> halves: 5500 -> 768, K = 1040 (258 tiles) 74.8 -> 60.0, 4160 -> 1000, K = 2048 (264) 126.8 -> 102.7,
+// 3000 -> 3000, K = 2048 (576) 229.8 -> 205.8, K = 512 77.0 -> 70.1, 4096 -> 2176, K = 1024 (544) 126.0 -> 114.7, 3522 -> 4610, K = 1568 (1036) 299 -> 278,
+// 8671 -> 1039, K = 1656 (612) 194 -> 177; of 42 layers with a remainder of half a round at most none is more than 1.2 % slower.  More than half:
+// 3104 -> 2169, K = 2824 (425) 205 and 234, 10111 -> 594, K = 320 (395) 43.3 and 46.2.
+// Against the fp32 pipe nothing has to be gained by the costs: 11190 -> 423, K = 304 42.7 -> 32.6, 2788 -> 1849, K = 288 39.4 -> 32.5.  Where the last
+// rows of tiles are half empty 64 x 128 can be the better one and its cost says so (5504 -> 690, K = 320 26.7 us, in halves 29.8).
+// A round of halves beside lone tiles takes `beside` and `crowd` for the share of the compute units that have one, behind pairs `behind`.
+constexpr int kPlaneHalves = 4;
+inline bool planes_in_halves(int64_t N, int64_t M, int64_t cus)
+{
+    const int64_t tiles = ((N + 127) / 128) * ((M + 127) / 128), left = tiles % cus;
+    return tiles > cus && left > 0 && 2 * left <= cus;
+}
+inline double planes_halves_cost(int64_t N, int64_t M, int64_t K, int64_t cus)
+{
+    constexpr double beside = 2, crowd = 28, behind = 18;
+    const PlaneTile& t = kPlaneTiles[0];
+    const int64_t tiles = ((N + 127) / 128) * ((M + 127) / 128), rounds = tiles / cus;
+    const double last = rounds % 2 ? t.one + beside + crowd * static_cast<double>(tiles % cus) / cus : behind;
+    return t.first + (t.two * (rounds / 2) + last) * static_cast<double>(K) / 1024 + t.update * static_cast<double>(N) * M / 4194304;
+}
+
 // Which of them takes this layer, -1: none, the fp32 pipe does.  `us`: its cost there, split or not.  Sums of less than 256 rows are
 // for the rule below.  With a chip that went over W and Mom in runs of tiles the fp32 pipe was the faster one at K = 128 for every size
 // of layer (2624 -> 5037 52 against 58 us for the best of the tiles), at K = 192 for some (4720 -> 868 26.1 and 29.6, 1669 -> 780 12.5 and 12.2, 8404 -> 321 21.1 and 17.5), at K = 256 for hardly any
@@ -191,16 +215,18 @@ inline int choose_planes(int64_t N, int64_t M, int64_t K, int64_t cus, double us
 {
     if (K < kMinPlaneRows) return -1;
     int best = -1;
+    const double pipe = us;
     us *= 0.9;
     for (const PlaneTile& t : kPlaneTiles)
         if (planes_cost(t, N, M, K, cus) < us) {
             us = planes_cost(t, N, M, K, cus);
             best = t.id;
         }
+    if (planes_in_halves(N, M, cus) && planes_halves_cost(N, M, K, cus) < (best < 0 ? pipe : us)) return kPlaneHalves;
     return best;
 }
 
-// ... and sums of 128 to 255 rows, 128 x 128 or none: since W and Mom are gone over in bands (tile_order) the planes are the faster ones
+// ... and sums of 128 to 255 rows, 128 x 128 (or the last of them in halves) or none: since W and Mom are gone over in bands (tile_order) the planes are the faster ones
 // there too for large layers.  us, fp32 pipe -> planes: 9216 -> 4096, K = 128 130 -> 121, K = 240 182 -> 146, 25088 -> 4096, K = 160
 // 392 -> 332, 4096 -> 21841, K = 208 382 -> 314, 3000 -> 21841, K = 128 249 -> 218, 7001 -> 5003, K = 128 144 -> 122, 2000 -> 8000, K = 160
 // 70.9 -> 60.8, 11050 -> 565, K = 179 39.5 -> 32.6; the other way 12000 -> 700, K = 160 36.0 and 42.5, 1184 -> 6733, K = 153 34.5 and
@@ -215,8 +241,10 @@ inline int choose_short_planes(int64_t N, int64_t M, int64_t K, int64_t cus, dou
     const int64_t tiles = ((N + 127) / 128) * ((M + 127) / 128);
     const double share = static_cast<double>(tiles) / cus, rounds = static_cast<double>((tiles + cus - 1) / cus);
     if (tiles <= cus) return -1;
-    const double cost = 6 + (7 + 36 * static_cast<double>(K) / 1024) * (share + 0.8 * (rounds - share)) + (M % 32 != 0 ? 2.8 * share : 0);
-    return cost < 0.96 * us ? 0 : -1;
+    const bool halves = planes_in_halves(N, M, cus);
+    const double tail = halves && M % 32 != 0 ? 0.4 : 0.8;
+    const double cost = 6 + (7 + 36 * static_cast<double>(K) / 1024) * (share + tail * (rounds - share)) + (M % 32 != 0 ? 2.8 * share : 0);
+    return cost < 0.96 * us ? halves ? kPlaneHalves : 0 : -1;
 }
 
 // ---- bf16 reconstruction: which tile covers W

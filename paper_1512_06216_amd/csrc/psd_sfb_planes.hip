@@ -79,6 +79,7 @@ struct Args {
     int N, M, K;
     float lr, mu, wd;
     TileOrder order;
+    int whole;                      // HALVES: so many tiles are contracted whole
     uint32_t u_bytes, v_bytes;      // of the stacked matrices, or of ONE block
     int n_blocks, block_rows;       // BLK
 };
@@ -132,13 +133,10 @@ __device__ __forceinline__ void lds_barrier()
 // BLK = true: row k = p*B + b of U is row b of the p-th worker's block (V likewise); a slice lies in one block because SLICE
 // divides B.
 template <class C, bool BLK, bool ON_LINES>
-__device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks)
+__device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks, const int64_t n0, const int64_t m0)
 {
     constexpr int G = C::G, WN = C::WN, PV = C::PV;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    int tile_n, tile_m;
-    tile_of(blockIdx.x, g.order, &tile_n, &tile_m);
-    const int64_t n0 = int64_t(tile_n) * C::TN, m0 = int64_t(tile_m) * C::TM;
 
     const int N = g.N, M = g.M;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -501,24 +499,48 @@ __device__ __forceinline__ void tile_body(const Args& g, const BlockPtrs* blocks
     }
 }
 
-template <class C, bool ON_LINES>
+// HALVES: the tiles from the `whole`-th on are left to two workgroups each, 64 rows for one and 64 for the other, which two groups of
+// wavefronts contract.  (Whole rounds over the chip stay whole: a 128 x 128 tile takes 33 us for 1024 k rows where two share a compute
+// unit, two of 64 x 128 39.)  3000 -> 3000, K = 2048 230 -> 206 us; the rule is planes_in_halves in psd_rules.h.  A kernel of its own: 128 x 128
+// needs 243 registers without the code for halves, 245 with it, but from blocks 243 and 252.
+template <class C, bool BLK, bool ON_LINES, bool HALVES>
+__device__ __forceinline__ void one_tile(const Args& g, const BlockPtrs* blocks)
+{
+    const int b = blockIdx.x, tiles = g.order.tiles;
+    const bool lower = HALVES && b >= tiles;
+    int tile_n, tile_m;
+    tile_of(lower ? b - tiles + g.whole : b, g.order, &tile_n, &tile_m);
+    const int64_t n0 = int64_t(tile_n) * C::TN, m0 = int64_t(tile_m) * C::TM;
+    if (!HALVES || b < g.whole) {
+        tile_body<C, BLK, ON_LINES>(g, blocks, n0, m0);
+    } else if constexpr (HALVES) {
+        using Half = Cfg<C::WN / 2, 2 * C::G>;
+        static_assert(Half::THREADS == C::THREADS, "as many wavefronts for half of the rows");
+        const int64_t half = n0 + (lower ? Half::TN : 0);
+        if (half < g.N) tile_body<Half, BLK, ON_LINES>(g, blocks, half, m0);
+    }
+}
+
+template <class C, bool ON_LINES, bool HALVES>
 __global__ void __launch_bounds__(C::THREADS, 2) sfb_f32_planes_kernel(const Args g)
 {
-    tile_body<C, false, ON_LINES>(g, nullptr);
+    one_tile<C, false, ON_LINES, HALVES>(g, nullptr);
 }
 
-template <class C, bool ON_LINES>
+template <class C, bool ON_LINES, bool HALVES>
 __global__ void __launch_bounds__(C::THREADS, 2) sfb_f32_planes_blocks_kernel(const Args g, const BlockPtrs blocks)
 {
-    tile_body<C, true, ON_LINES>(g, &blocks);
+    one_tile<C, true, ON_LINES, HALVES>(g, &blocks);
 }
 
-template <class C>
+template <class C, bool HALVES = false>
 psd_status start(Args& g, const BlockPtrs* blocks, hipStream_t st)
 {
     const int tiles_n = (g.N + C::TN - 1) / C::TN, tiles_m = (g.M + C::TM - 1) / C::TM;
     const int64_t tiles = int64_t(tiles_n) * tiles_m;
-    if (tiles < 1 || tiles > 0x7fffffff) return PSD_E_INVALID;
+    if (tiles < 1 || tiles > 0x3fffffff) return PSD_E_INVALID;
+    const int64_t cus = device_cu_count();
+    g.whole = static_cast<int>(HALVES ? tiles / cus * cus : tiles);
     // Layers with long rows: bands of tile rows over the whole chip, for W and Mom in HBM (see band_for in psd_rules.h) as well as for the
     // factors; others: a run of groups of eight tile rows for each XCD, turned against each other.  us, runs of groups of 16, not turned
     // -> now: 9216 -> 4096, K = 256 150.0 -> 146.4, K = 1024 379 -> 376, K = 2048 685 -> 681, 16384 -> 2048, K = 256 155 -> 137,
@@ -527,23 +549,24 @@ psd_status start(Args& g, const BlockPtrs* blocks, hipStream_t st)
     // 4096 -> 21841, K = 4096 3312 -> 3109 with either; 25088 -> 2048, K = 4096 1838, in bands of four 1874, of eight 1844.  Few rows of
     // tiles are one band: 18720 -> 1438, K = 278 123.2 us, in bands of four 125.3.
     g.order = tile_order(tiles_n, tiles_m, g.M <= 4500 ? 0 : g.N <= 1600 ? 16 : g.K <= 2048 ? 4 : 8);
+    constexpr int lds = C::larger(C::LDS_BYTES, HALVES ? Cfg<2, 2>::LDS_BYTES : 0);
     // raise the dynamic LDS limit once per process (idempotent, so a race between two first callers is harmless)
     static std::atomic<bool> attr_done{false};
     if (!attr_done.load(std::memory_order_acquire)) {
-        for (auto k : {sfb_f32_planes_kernel<C, false>, sfb_f32_planes_kernel<C, true>})
-            PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
-        for (auto k : {sfb_f32_planes_blocks_kernel<C, false>, sfb_f32_planes_blocks_kernel<C, true>})
-            PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES));
+        for (auto k : {sfb_f32_planes_kernel<C, false, HALVES>, sfb_f32_planes_kernel<C, true, HALVES>})
+            PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        for (auto k : {sfb_f32_planes_blocks_kernel<C, false, HALVES>, sfb_f32_planes_blocks_kernel<C, true, HALVES>})
+            PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
         attr_done.store(true, std::memory_order_release);
     }
-    const dim3 grid(static_cast<uint32_t>(tiles));
+    const dim3 grid(static_cast<uint32_t>(tiles + (tiles - g.whole)));
     const bool lines = g.M % 32 == 0 && ((reinterpret_cast<uintptr_t>(g.W) | reinterpret_cast<uintptr_t>(g.Mom)) & 127) == 0;
     if (blocks) {
-        auto kern = lines ? sfb_f32_planes_blocks_kernel<C, true> : sfb_f32_planes_blocks_kernel<C, false>;
-        hipLaunchKernelGGL(kern, grid, dim3(C::THREADS), C::LDS_BYTES, st, g, *blocks);
+        auto kern = lines ? sfb_f32_planes_blocks_kernel<C, true, HALVES> : sfb_f32_planes_blocks_kernel<C, false, HALVES>;
+        hipLaunchKernelGGL(kern, grid, dim3(C::THREADS), lds, st, g, *blocks);
     } else {
-        auto kern = lines ? sfb_f32_planes_kernel<C, true> : sfb_f32_planes_kernel<C, false>;
-        hipLaunchKernelGGL(kern, grid, dim3(C::THREADS), C::LDS_BYTES, st, g);
+        auto kern = lines ? sfb_f32_planes_kernel<C, true, HALVES> : sfb_f32_planes_kernel<C, false, HALVES>;
+        hipLaunchKernelGGL(kern, grid, dim3(C::THREADS), lds, st, g);
     }
     PSD_HIP_TRY(hipGetLastError());
     return PSD_OK;
@@ -555,6 +578,7 @@ psd_status dispatch(int tile, Args& g, const BlockPtrs* blocks, hipStream_t st)
         case 1: return start<Cfg<4, 2>>(g, blocks, st);
         case 2: return start<Cfg<2, 2>>(g, blocks, st);
         case 3: return start<Cfg<2, 4>>(g, blocks, st);
+        case kPlaneHalves: return start<Cfg<4, 1>, true>(g, blocks, st);
         default: return start<Cfg<4, 1>>(g, blocks, st);
     }
 }

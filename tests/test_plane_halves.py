@@ -1,0 +1,98 @@
+"""fp32 layers in planes whose tiles beyond whole rounds over the chip are left to two workgroups each (kPlaneHalves in csrc/psd_rules.h)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import psd_oracle as orc
+from paper_1512_06216_amd import binding as psd
+from paper_1512_06216_amd import inputs
+from tests.test_rules import rules  # noqa: F401  (a fixture)
+
+CUS, HALVES = 256, 4
+# M, N, B, P: 258 tiles, rows of W on quads; 516, on cache lines and anywhere, behind pairs; the last row of tiles with one row in its lower half, with
+# nothing there, with all; half a round left; beside a lone tile; 128 to 255 k rows
+LAYERS = [(5500, 705, 64, 5), (5504, 705, 64, 5), (5497, 705, 51, 7), (5120, 2048, 16, 17), (3339, 3601, 64, 5), (3360, 3630, 51, 6),
+          (1410, 8830, 64, 5), (4096, 1500, 32, 4), (4611, 2170, 19, 8)]
+
+
+def test_layers_with_half_a_round_left_at_most_go_to_halves(rules):
+    for M, N, B, P in LAYERS:
+        K = B * P
+        assert (rules.f32_planes if K >= 256 else rules.f32_short_planes)(N, M, K, CUS) == HALVES, (M, N)
+    for M, N in ((4096, 1000), (4096, 4096), (9216, 4096), (3104, 2169), (4096, 1664)):      # whole rounds, more than half of one
+        assert rules.f32_planes(N, M, 1024, CUS) not in (-1, HALVES)
+    for M, N in ((4096, 1152), (5500, 768), (3000, 3000)):
+        assert rules.f32_planes(N, M, 1024, CUS) == HALVES
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+def sync(plan, blocks, U, ldu, V, ldv, B, W, Mom, lr, mu, wd=0.0):
+    if blocks:
+        psd.sync_fc_sfb_blocks(plan, psd.F32, list(U.split(B)), ldu, list(V.split(B)), ldv, W, Mom, lr, mu, wd=wd)
+    else:
+        psd.sync_fc_sfb(plan, psd.F32, U, ldu, V, ldv, W, Mom, lr, mu, wd=wd)
+    torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,B,P", LAYERS)
+def test_halves_bit_exact(M, N, B, P):
+    """Stacked, and (whole slices in a block) the same rows read in place as P blocks; nothing outside W and Mom is touched."""
+    d = inputs.fc_layer_integer(M, N, B, P, seed=M + N, amax=2)
+    plan = psd.plan_layer(psd.LAYER_FC, M, N, B, P)
+    U, ldu, V, ldv = psd.alloc_factors(plan, psd.F32, "cuda:0")
+    psd.pack_factors(plan, [dev(x) for x in d["delta"]], [dev(x) for x in d["act"]], psd.F32, U, ldu, V, ldv)
+    Wr, Mr = orc.sync_fc_sfb(*orc.pack_factors(d["delta"], d["act"]), d["W"], d["Mom"], 0.25, 0.5, wd=0.25)
+    for blocks in (False, True)[:1 + (B % 16 == 0)]:
+        room = torch.full((2, 64 + N * M + 64), 77.0, device="cuda:0")
+        W, Mom = (x[64:64 + N * M].view(N, M) for x in room) if M % 4 == 0 else (dev(d["W"]), dev(d["Mom"]))
+        W.copy_(dev(d["W"]))
+        Mom.copy_(dev(d["Mom"]))
+        sync(plan, blocks, U, ldu, V, ldv, B, W, Mom, 0.25, 0.5, wd=0.25)
+        assert np.array_equal(Mom.cpu().numpy(), Mr) and np.array_equal(W.cpu().numpy(), Wr), blocks
+        assert bool((room[:, :64] == 77).all()) and bool((room[:, 64 + N * M:] == 77).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,B,P", [LAYERS[0], LAYERS[2]])
+def test_halves_with_sums_that_are_not_finite(M, N, B, P):
+    """Infinities, NaN and factors past 2^104 in whole tiles and in halves: what fp32 gives."""
+    K = B * P
+    g = torch.Generator().manual_seed(M)
+    u, v = torch.randn(K, N, generator=g).mul_(1e-3), torch.randn(K, M, generator=g).relu_()
+    u[7, 3], u[K - 1, N - 1], v[5, 70], v[40, M - 1] = float("inf"), float("-inf"), float("nan"), float("inf")
+    u[33, 200], v[33] = 2.0 ** 110, v[33] * 2.0 ** -20
+    plan = psd.plan_layer(psd.LAYER_FC, M, N, B, P)
+    want = (u.double().t().contiguous() @ v.double()).numpy()
+    scale = (u.double().abs().t().contiguous() @ v.double().abs()).numpy()
+    U, ldu, V, ldv = psd.alloc_factors(plan, psd.F32, "cuda:0")
+    psd.pack_factors(plan, [x.cuda().contiguous() for x in u.split(B)], [x.cuda().contiguous() for x in v.split(B)], psd.F32, U, ldu, V, ldv)
+    for blocks in (False, True)[:1 + (B % 16 == 0)]:
+        W, Mom = torch.zeros(N, M, device="cuda:0"), torch.zeros(N, M, device="cuda:0")
+        sync(plan, blocks, U, ldu, V, ldv, B, W, Mom, 1.0, 0.0)
+        got = Mom.cpu().double().numpy()
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        inf = np.isinf(want)
+        assert np.array_equal(got[inf], want[inf])
+        ok = np.isfinite(want)
+        assert np.all(np.abs(got[ok] - want[ok]) <= (K + 4) * 2.0 ** -24 * scale[ok])          # an fp32 sum of K products
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(5500, 705, 1040), (4096, 1530, 2048)])
+def test_halves_error_against_64_bits(M, N, K):
+    """No further off than whole tiles, 2.1e-7 at K = 2048 with normal errors (one run over k, the small products by themselves)."""
+    g = torch.Generator().manual_seed(K)
+    u, v = torch.randn(K, N, generator=g).mul_(1e-3), torch.randn(K, M, generator=g).relu_()
+    plan = psd.plan_layer(psd.LAYER_FC, M, N, K, 1)
+    U, ldu, V, ldv = psd.alloc_factors(plan, psd.F32, "cuda:0")
+    psd.pack_factors(plan, [u.cuda()], [v.cuda()], psd.F32, U, ldu, V, ldv)
+    W, Mom = torch.zeros(N, M, device="cuda:0"), torch.zeros(N, M, device="cuda:0")
+    sync(plan, False, U, ldu, V, ldv, K, W, Mom, 1.0, 0.0)
+    want = u.double().t().contiguous() @ v.double()
+    rel = ((Mom.cpu().double() - want).norm() / want.norm()).item()
+    print("rel", M, N, K, rel)
+    assert rel <= 2.5e-7, rel

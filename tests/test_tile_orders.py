@@ -15,7 +15,7 @@ CUS = 256
 BF16_LAYERS = [(3104, 2048, 32, 2, -1), (3072, 1665, 32, 5, -1), (1600, 4224, 32, 12, 4), (1568, 3973, 32, 8, 4), (4004, 1540, 32, 3, 4),
                (4001, 1411, 20, 5, 4), (1001, 6001, 32, 4, 0), (608, 8200, 32, 16, 0)]
 # M, N, B, P and the tile in planes for sums of 128 to 255 rows
-SHORT_PLANES = [(4096, 1500, 32, 4, 0), (6001, 2001, 64, 3, 0), (4604, 1733, 51, 5, 0), (4096, 1500, 32, 3, -1), (1184, 6733, 51, 3, -1)]
+SHORT_PLANES = [(4096, 1500, 32, 4, 4), (6001, 2001, 64, 3, 0), (4604, 1733, 51, 5, 0), (4096, 1500, 32, 3, -1), (1184, 6733, 51, 3, -1)]
 # the planes' kernel with K >= 256: runs of groups, one band, bands of four and of eight
 PLANE_ORDERS = [(1030, 5200, 64, 8), (4736, 1161, 64, 8), (4612, 1700, 64, 4), (4608, 1668, 345, 6)]
 
