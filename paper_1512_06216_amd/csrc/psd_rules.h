@@ -261,6 +261,9 @@ inline int choose_short_planes(int64_t N, int64_t M, int64_t K, int64_t cus, dou
 // Of 722 further layers 120 have another tile now, by 3.4 % faster, 23 of them slower.  Predicted for measured: 4096 -> 21841,
 // K = 2048 437 for 430, 25088 -> 4096 507 for 500, 3000 -> 21841 345 for 359, 9216 -> 4096 195 for 193, 4096 -> 4096 102 for 90,
 // 4096 -> 1000 27.5 for 30.6, 1024 -> 1000, K = 256 6.5 for 6.1; 12 % rms.
+// The costs are those of whole tiles, also where the last of them go in halves (bf16_whole): of 6480 further layers of 2.2 to 60 M weights, K =
+// 100 .. 3500, which all have halves in one tile at least, the tile chosen takes 1.6 % longer than the best one (1.9 % without halves), and 1.4 % with
+// costs that count a last round of halves as 0.7 of one.
 // The tiles contracted by several groups of wavefronts are for layers that have `most` of them for each compute unit
 // at most, which they fill: 1024 -> 1000, K = 2048 17.4 us with four wavefronts per 64 x 64 tile, 12.5 with sixteen.  Two tiles of
 // two groups each (id 7) against the better one of the tiles of four wavefronts, of which a compute unit then holds one or two:
@@ -277,6 +280,20 @@ constexpr Bf16Tile kTiles[] = {{0, 128, 256, 0, 2, 23.4, 0.60, 0.5, 12.7, 14.7, 
                                {6, 128, 128, 1, 1, 0, 0, 0, 0, 8.3, 5.9, 0},                {7, 64, 64, 2, 2, 0, 0, 0, 0.3, 5.3, 4.6, 0}};
 constexpr double kNever = 1e30;
 constexpr int64_t kMinPairRows = 256, kMinPairRowsOffLines = 384, kMaxPairRows = 3072;
+
+// How many tiles of 128 rows are contracted whole: those beyond whole rounds over the chip are left to two workgroups each, 64 rows for
+// one and 64 for the other, where that is one for each compute unit at most (the same bits: the order of a sum does not change).  us, all
+// tiles whole and with halves, K = 2048 unless said: 128 x 256 3000 -> 21841 (2052 tiles) 363.5 and 355.5, 25088 -> 4096 (3136) 519 and 513,
+// 9216 -> 4096 (1152) 208 and 199, 1250 -> 6832, K = 2880 (270) 98 and 78; 128 x 192 3000 -> 3000 (384) 62.4 and 57.2, 4096 -> 6144 (1056)
+// 140.6 and 135.6, 1250 -> 6832, K = 2880 (378) 74.7 and 67.9; 128 x 128 3000 -> 3000 (576) 69.5 and 64.0, K = 1024 47.5 and 44.3, 8032 -> 6158,
+// K = 320 (3087) 145.4 and 145.8.  With more than half of a round left: 4096 -> 21841 (2736) 442.5 and 446.6, 1952 -> 5505, K = 1968 in 128 x 192 (484)
+// 66.4 and 77.9; two workgroups to a compute unit are the slots of a launch, but the tiles beyond whole rounds of those in halves, or more
+// of them, are no better (4096 -> 6144 in 128 x 256 (768) 135.2 and 143.7).
+inline int64_t bf16_whole(int64_t tiles, int64_t cus)
+{
+    const int64_t left = tiles % cus;
+    return tiles > cus && 2 * left <= cus ? tiles - left : tiles;
+}
 
 // us for the launch that covers N x M over K rows
 inline double launch_cost(const Bf16Tile& t, int64_t N, int64_t M, int64_t K, int64_t cus)

@@ -95,7 +95,7 @@ template <class C, bool PART, bool BLK, Rows AT>
 __device__ __forceinline__ void
 sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __restrict__ V, int64_t ldv,
               float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
-              const TileOrder& order, uint32_t u_bytes, uint32_t v_bytes, float* __restrict__ part,
+              const int64_t n0, const int64_t m0, const int split, uint32_t u_bytes, uint32_t v_bytes, float* __restrict__ part,
               int64_t part_stride, int stages_per_split, int skew_blocks, int skew_ticks,
               const BlockPtrs* blocks, int n_blocks, int block_rows)
 {
@@ -114,11 +114,6 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
     const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
         (__attribute__((address_space(3))) void*)lds));
 
-    const int split = PART ? static_cast<int>(divide(blockIdx.x, order.by_tiles)) : 0;
-    int tile_n, tile_m;
-    tile_of(blockIdx.x - split * order.tiles, order, &tile_n, &tile_m);
-
-    const int64_t n0 = int64_t(tile_n) * C::TN, m0 = int64_t(tile_m) * C::TM;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int group = wave / (C::WN * C::WM), wg = wave % (C::WN * C::WM);
@@ -439,26 +434,56 @@ sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __res
     }
 }
 
-template <class C, bool PART, Rows AT>
+// The tile at which a workgroup works.  HALVES: the tiles from the `whole`-th on are left to two workgroups each, half of the rows for one
+// and half for the other (bf16_whole in psd_rules.h): 3000 -> 3000, K = 2048 62.4 -> 57.2 us.  Kernels of their own, 1 more register at most.
+// (What is likely is said to the compiler because it otherwise keeps room in memory, of which nothing is used, for scalar registers in
+// four of the kernels that read blocks.)
+template <class C> using HalfOf = Cfg<C::WN, C::WM, C::BN / 2, C::BM, C::NSTAGE, C::OCC>;
+
+template <class C, bool PART, bool BLK, Rows AT, bool HALVES>
+__device__ __forceinline__ void
+one_tile(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t ldv, float* W, float* Mom, int N, int M, int K, float lr, float mu, float wd,
+         const TileOrder& order, int whole, uint32_t u_bytes, uint32_t v_bytes, float* part, int64_t part_stride, int stages_per_split,
+         int skew_blocks, int skew_ticks, const BlockPtrs* blocks, int n_blocks, int block_rows)
+{
+    static_assert(!HALVES || (!PART && C::G == 1 && C::BN == 2), "whole tiles only");
+    const int split = PART ? static_cast<int>(divide(blockIdx.x, order.by_tiles)) : 0;
+    const int b = blockIdx.x - split * order.tiles;
+    const bool lower = HALVES && b >= order.tiles;
+    int tile_n, tile_m;
+    tile_of(lower ? b - order.tiles + whole : b, order, &tile_n, &tile_m);
+    const int64_t n0 = int64_t(tile_n) * C::TN, m0 = int64_t(tile_m) * C::TM;
+    if (!HALVES || __builtin_expect(b < whole, 1)) {
+        sfb_bf16_body<C, PART, BLK, AT>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, n0, m0, split, u_bytes, v_bytes, part, part_stride,
+                                        stages_per_split, skew_blocks, skew_ticks, blocks, n_blocks, block_rows);
+    } else if constexpr (HALVES) {
+        const int64_t half = n0 + (lower ? HalfOf<C>::TN : 0);
+        if (half < N)
+            sfb_bf16_body<HalfOf<C>, PART, BLK, AT>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, half, m0, split, u_bytes, v_bytes, part,
+                                                    part_stride, stages_per_split, 0, 0, blocks, n_blocks, block_rows);
+    }
+}
+
+template <class C, bool PART, Rows AT, bool HALVES = false>
 __global__ void __launch_bounds__(C::THREADS, C::OCC)
 sfb_bf16_kernel(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __restrict__ V, int64_t ldv,
                 float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
-                const TileOrder order, uint32_t u_bytes, uint32_t v_bytes, float* __restrict__ part,
+                const TileOrder order, int whole, uint32_t u_bytes, uint32_t v_bytes, float* __restrict__ part,
                 int64_t part_stride, int stages_per_split, int skew_blocks, int skew_ticks)
 {
-    sfb_bf16_body<C, PART, false, AT>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, order, u_bytes, v_bytes, part,
-                                  part_stride, stages_per_split, skew_blocks, skew_ticks, nullptr, 0, 0);
+    one_tile<C, PART, false, AT, HALVES>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, order, whole, u_bytes, v_bytes, part,
+                                         part_stride, stages_per_split, skew_blocks, skew_ticks, nullptr, 0, 0);
 }
 
 // the P per-worker blocks read in place (u_bytes, v_bytes: the size of ONE block)
-template <class C, Rows AT>
+template <class C, Rows AT, bool HALVES = false>
 __global__ void __launch_bounds__(C::THREADS, C::OCC)
 sfb_bf16_blocks_kernel(BlockPtrs blocks, int n_blocks, int block_rows, int64_t ldu, int64_t ldv,
                        float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
-                       const TileOrder order, uint32_t u_bytes, uint32_t v_bytes, int skew_blocks, int skew_ticks)
+                       const TileOrder order, int whole, uint32_t u_bytes, uint32_t v_bytes, int skew_blocks, int skew_ticks)
 {
-    sfb_bf16_body<C, false, true, AT>(nullptr, ldu, nullptr, ldv, W, Mom, N, M, K, lr, mu, wd, order, u_bytes,
-                                  v_bytes, nullptr, 0, 0, skew_blocks, skew_ticks, &blocks, n_blocks, block_rows);
+    one_tile<C, false, true, AT, HALVES>(nullptr, ldu, nullptr, ldv, W, Mom, N, M, K, lr, mu, wd, order, whole, u_bytes,
+                                         v_bytes, nullptr, 0, 0, skew_blocks, skew_ticks, &blocks, n_blocks, block_rows);
 }
 
 // where the rows of W and Mom start, for the tile C (cache lines have 128 bytes)
@@ -483,6 +508,14 @@ int skew_for(int64_t tiles, int64_t K)
     return asked >= 0 ? asked * 100 : C::G > 1 ? 0 : skew_ticks(tiles, C::TN, K, device_cu_count());
 }
 
+// is there a kernel for the tile C with halves, and how many tiles of a launch are contracted whole
+template <class C> constexpr bool kHalves = C::G == 1 && C::BN == 2;
+template <class C>
+int whole_tiles(int64_t tiles)
+{
+    return static_cast<int>(kHalves<C> ? bf16_whole(tiles, device_cu_count()) : tiles);
+}
+
 template <class C>
 psd_status launch_cfg_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int64_t ldu, int64_t ldv, float* W, float* Mom,
                              int64_t N, int64_t M, float lr, float mu, float wd, hipStream_t st)
@@ -492,20 +525,23 @@ psd_status launch_cfg_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int6
     if (tiles < 1 || tiles > 0x3fffffff) return PSD_E_INVALID;
     const int64_t u_bytes = B * ldu * 2, v_bytes = B * ldv * 2;          // one block
     const Rows at = rows_at<C>(W, Mom, N, M);
-    auto kern = at == ON_LINES       ? sfb_bf16_blocks_kernel<C, kOnLines<C>>
+    const int whole = whole_tiles<C>(tiles);
+    auto kern = whole < tiles        ? at == ON_LINES ? sfb_bf16_blocks_kernel<C, kOnLines<C>, kHalves<C>> : sfb_bf16_blocks_kernel<C, ANYWHERE, kHalves<C>>
+                : at == ON_LINES     ? sfb_bf16_blocks_kernel<C, kOnLines<C>>
                 : at == ANYWHERE_FEW ? sfb_bf16_blocks_kernel<C, kFew<C>> : sfb_bf16_blocks_kernel<C, ANYWHERE>;
     const TileOrder order = tile_order(static_cast<int>(tiles_n), static_cast<int>(tiles_m),
                                        band_for(N, M, P * B, tiles, at == ON_LINES, device_cu_count()));
     static std::atomic<bool> attr_done{false};
     if (!attr_done.load(std::memory_order_acquire)) {
         for (auto k : {sfb_bf16_blocks_kernel<C, kOnLines<C>>, sfb_bf16_blocks_kernel<C, kFew<C>>,
-                       sfb_bf16_blocks_kernel<C, ANYWHERE>})
+                       sfb_bf16_blocks_kernel<C, ANYWHERE>, sfb_bf16_blocks_kernel<C, kOnLines<C>, kHalves<C>>,
+                       sfb_bf16_blocks_kernel<C, ANYWHERE, kHalves<C>>})
             PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         attr_done.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(tiles)), dim3(C::THREADS), C::LDS_BYTES_ROWS, st,
+    hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(2 * tiles - whole)), dim3(C::THREADS), C::LDS_BYTES_ROWS, st,
                        blocks, static_cast<int>(P), static_cast<int>(B), ldu, ldv, W, Mom, static_cast<int>(N),
-                       static_cast<int>(M), static_cast<int>(P * B), lr, mu, wd, order, static_cast<uint32_t>(u_bytes),
+                       static_cast<int>(M), static_cast<int>(P * B), lr, mu, wd, order, whole, static_cast<uint32_t>(u_bytes),
                        static_cast<uint32_t>(v_bytes), device_cu_count() * C::OCC, skew_for<C>(tiles, P * B));
     PSD_HIP_TRY(hipGetLastError());
     return PSD_OK;
@@ -523,7 +559,9 @@ psd_status launch_cfg(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t
     const int64_t u_bytes = K * ldu * 2, v_bytes = K * ldv * 2;
     constexpr bool alone = C::G == 1;            // groups are not split
     const Rows at = rows_at<C>(W, Mom, N, M);
+    const int whole = splits > 1 ? static_cast<int>(tiles) : whole_tiles<C>(tiles);
     auto kern = splits > 1 ? sfb_bf16_kernel<C, alone, ANYWHERE>
+                : whole < tiles      ? at == ON_LINES ? sfb_bf16_kernel<C, false, kOnLines<C>, kHalves<C>> : sfb_bf16_kernel<C, false, ANYWHERE, kHalves<C>>
                 : at == ON_LINES     ? sfb_bf16_kernel<C, false, kOnLines<C>>
                 : at == ANYWHERE_FEW ? sfb_bf16_kernel<C, false, kFew<C>> : sfb_bf16_kernel<C, false, ANYWHERE>;
     const TileOrder order = tile_order(static_cast<int>(tiles_n), static_cast<int>(tiles_m),
@@ -534,15 +572,16 @@ psd_status launch_cfg(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t
     static std::atomic<bool> attr_done{false};
     if (!attr_done.load(std::memory_order_acquire)) {
         for (auto k : {sfb_bf16_kernel<C, alone, ANYWHERE>, sfb_bf16_kernel<C, false, kOnLines<C>>,
-                       sfb_bf16_kernel<C, false, kFew<C>>, sfb_bf16_kernel<C, false, ANYWHERE>})
+                       sfb_bf16_kernel<C, false, kFew<C>>, sfb_bf16_kernel<C, false, ANYWHERE>,
+                       sfb_bf16_kernel<C, false, kOnLines<C>, kHalves<C>>, sfb_bf16_kernel<C, false, ANYWHERE, kHalves<C>>})
             PSD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, int(C::LDS_BYTES_ROWS)));
         attr_done.store(true, std::memory_order_release);
     }
     const int64_t stages = (K + C::KT - 1) / C::KT;
     const int sps = static_cast<int>((stages + splits - 1) / splits);
-    hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(tiles * splits)), dim3(C::THREADS), lds, st, U, ldu, V,
+    hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>((2 * tiles - whole) * splits)), dim3(C::THREADS), lds, st, U, ldu, V,
                        ldv, W, Mom, static_cast<int>(N), static_cast<int>(M), static_cast<int>(K), lr, mu, wd,
-                       order, static_cast<uint32_t>(u_bytes), static_cast<uint32_t>(v_bytes), part, sfb_part_stride(N, M), sps,
+                       order, whole, static_cast<uint32_t>(u_bytes), static_cast<uint32_t>(v_bytes), part, sfb_part_stride(N, M), sps,
                        device_cu_count() * C::OCC, skew_for<C>(splits > 1 ? 0 : tiles, K));
     PSD_HIP_TRY(hipGetLastError());
     if (splits > 1) return launch_sfb_reduce(part, splits, N, M, W, Mom, lr, mu, wd, st);

@@ -22,6 +22,7 @@ int32_t bf16_choice(int64_t N, int64_t M, int64_t K, int most, int64_t cus)
     const psd::Bf16Tile t = psd::choose_bf16_split(N, M, K, most, cus, -1, &splits);
     return 10 * t.id + splits;
 }
+int64_t bf16_whole(int64_t tiles, int64_t cus) { return psd::bf16_whole(tiles, cus); }
 int32_t bf16_choice_beside(int64_t N, int64_t M, int64_t K, int64_t cus) { return psd::choose_bf16(N, M, K, cus, -1, true).id; }
 int32_t bf16_large(int64_t N, int64_t M, int64_t cus) { return psd::large_bf16(N, M, cus); }
 // `weights` of all layers together
