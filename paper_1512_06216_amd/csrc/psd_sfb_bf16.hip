@@ -96,20 +96,12 @@ __device__ __forceinline__ void
 sfb_bf16_body(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __restrict__ V, int64_t ldv,
               float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
               const int64_t n0, const int64_t m0, const int split, uint32_t u_bytes, uint32_t v_bytes, float* __restrict__ part,
-              int64_t part_stride, int stages_per_split, int skew_blocks, int skew_ticks,
-              const BlockPtrs* blocks, int n_blocks, int block_rows)
+              int64_t part_stride, int stages_per_split, const BlockPtrs* blocks, int n_blocks, int block_rows)
 {
     static_assert(!(PART && (BLK || C::G > 1)), "a split of K over workgroups is not combined with blocks read in place or groups");
     static_assert(AT == ANYWHERE || C::G == 1, "grouped tiles make no difference between rows");
     static_assert(AT != ANYWHERE_FEW || C::FEW, "what is not launched is not compiled");
     constexpr int KT = C::KT;
-    // The workgroups that start first on the odd-numbered XCDs wait skew_ticks of the 100 MHz wall clock, which puts the two
-    // halves of the chip out of phase (skew_ticks in psd_rules.h).  The wait ends by the clock; the iteration cap only bounds it
-    // should the clock not advance.
-    if (skew_ticks > 0 && (blockIdx.x & 1) && static_cast<int>(blockIdx.x) < skew_blocks) {
-        const long long t0 = wall_clock64();
-        for (int i = 0; i < 200000 && wall_clock64() - t0 < skew_ticks; ++i) __builtin_amdgcn_s_sleep(8);
-    }
     extern __shared__ __attribute__((aligned(1024))) uint16_t lds[];
     const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
         (__attribute__((address_space(3))) void*)lds));
@@ -443,10 +435,18 @@ template <class C> using HalfOf = Cfg<C::WN, C::WM, C::BN / 2, C::BM, C::NSTAGE,
 template <class C, bool PART, bool BLK, Rows AT, bool HALVES>
 __device__ __forceinline__ void
 one_tile(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t ldv, float* W, float* Mom, int N, int M, int K, float lr, float mu, float wd,
-         const TileOrder& order, int whole, uint32_t u_bytes, uint32_t v_bytes, float* part, int64_t part_stride, int stages_per_split,
-         int skew_blocks, int skew_ticks, const BlockPtrs* blocks, int n_blocks, int block_rows)
+         const TileOrder& order, uint32_t u_bytes, uint32_t v_bytes, float* part, int64_t part_stride, int stages_per_split,
+         int skew_blocks, int skew_ticks, int whole, const BlockPtrs* blocks, int n_blocks, int block_rows)
 {
     static_assert(!HALVES || (!PART && C::G == 1 && C::BN == 2), "whole tiles only");
+    // The workgroups that start first on the odd-numbered XCDs wait skew_ticks of the 100 MHz wall clock, which puts the two
+    // halves of the chip out of phase (skew_ticks in psd_rules.h).  The wait ends by the clock; the iteration cap only bounds it
+    // should the clock not advance.  (Ahead of the tile: behind it, its arguments are one more round trip before the first load, 0.2 us:
+    // 1024 -> 1000, K = 256 6.5 and 6.7.)
+    if (skew_ticks > 0 && (blockIdx.x & 1) && static_cast<int>(blockIdx.x) < skew_blocks) {
+        const long long t0 = wall_clock64();
+        for (int i = 0; i < 200000 && wall_clock64() - t0 < skew_ticks; ++i) __builtin_amdgcn_s_sleep(8);
+    }
     const int split = PART ? static_cast<int>(divide(blockIdx.x, order.by_tiles)) : 0;
     const int b = blockIdx.x - split * order.tiles;
     const bool lower = HALVES && b >= order.tiles;
@@ -455,12 +455,12 @@ one_tile(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t ldv, float* 
     const int64_t n0 = int64_t(tile_n) * C::TN, m0 = int64_t(tile_m) * C::TM;
     if (!HALVES || __builtin_expect(b < whole, 1)) {
         sfb_bf16_body<C, PART, BLK, AT>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, n0, m0, split, u_bytes, v_bytes, part, part_stride,
-                                        stages_per_split, skew_blocks, skew_ticks, blocks, n_blocks, block_rows);
+                                        stages_per_split, blocks, n_blocks, block_rows);
     } else if constexpr (HALVES) {
         const int64_t half = n0 + (lower ? HalfOf<C>::TN : 0);
         if (half < N)
             sfb_bf16_body<HalfOf<C>, PART, BLK, AT>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, half, m0, split, u_bytes, v_bytes, part,
-                                                    part_stride, stages_per_split, 0, 0, blocks, n_blocks, block_rows);
+                                                    part_stride, stages_per_split, blocks, n_blocks, block_rows);
     }
 }
 
@@ -468,11 +468,11 @@ template <class C, bool PART, Rows AT, bool HALVES = false>
 __global__ void __launch_bounds__(C::THREADS, C::OCC)
 sfb_bf16_kernel(const uint16_t* __restrict__ U, int64_t ldu, const uint16_t* __restrict__ V, int64_t ldv,
                 float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
-                const TileOrder order, int whole, uint32_t u_bytes, uint32_t v_bytes, float* __restrict__ part,
-                int64_t part_stride, int stages_per_split, int skew_blocks, int skew_ticks)
+                const TileOrder order, uint32_t u_bytes, uint32_t v_bytes, float* __restrict__ part,
+                int64_t part_stride, int stages_per_split, int skew_blocks, int skew_ticks, int whole)
 {
-    one_tile<C, PART, false, AT, HALVES>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, order, whole, u_bytes, v_bytes, part,
-                                         part_stride, stages_per_split, skew_blocks, skew_ticks, nullptr, 0, 0);
+    one_tile<C, PART, false, AT, HALVES>(U, ldu, V, ldv, W, Mom, N, M, K, lr, mu, wd, order, u_bytes, v_bytes, part,
+                                         part_stride, stages_per_split, skew_blocks, skew_ticks, whole, nullptr, 0, 0);
 }
 
 // the P per-worker blocks read in place (u_bytes, v_bytes: the size of ONE block)
@@ -480,10 +480,10 @@ template <class C, Rows AT, bool HALVES = false>
 __global__ void __launch_bounds__(C::THREADS, C::OCC)
 sfb_bf16_blocks_kernel(BlockPtrs blocks, int n_blocks, int block_rows, int64_t ldu, int64_t ldv,
                        float* __restrict__ W, float* __restrict__ Mom, int N, int M, int K, float lr, float mu, float wd,
-                       const TileOrder order, int whole, uint32_t u_bytes, uint32_t v_bytes, int skew_blocks, int skew_ticks)
+                       const TileOrder order, uint32_t u_bytes, uint32_t v_bytes, int skew_blocks, int skew_ticks, int whole)
 {
-    one_tile<C, false, true, AT, HALVES>(nullptr, ldu, nullptr, ldv, W, Mom, N, M, K, lr, mu, wd, order, whole, u_bytes,
-                                         v_bytes, nullptr, 0, 0, skew_blocks, skew_ticks, &blocks, n_blocks, block_rows);
+    one_tile<C, false, true, AT, HALVES>(nullptr, ldu, nullptr, ldv, W, Mom, N, M, K, lr, mu, wd, order, u_bytes,
+                                         v_bytes, nullptr, 0, 0, skew_blocks, skew_ticks, whole, &blocks, n_blocks, block_rows);
 }
 
 // where the rows of W and Mom start, for the tile C (cache lines have 128 bytes)
@@ -541,8 +541,8 @@ psd_status launch_cfg_blocks(const BlockPtrs& blocks, int64_t P, int64_t B, int6
     }
     hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(2 * tiles - whole)), dim3(C::THREADS), C::LDS_BYTES_ROWS, st,
                        blocks, static_cast<int>(P), static_cast<int>(B), ldu, ldv, W, Mom, static_cast<int>(N),
-                       static_cast<int>(M), static_cast<int>(P * B), lr, mu, wd, order, whole, static_cast<uint32_t>(u_bytes),
-                       static_cast<uint32_t>(v_bytes), device_cu_count() * C::OCC, skew_for<C>(tiles, P * B));
+                       static_cast<int>(M), static_cast<int>(P * B), lr, mu, wd, order, static_cast<uint32_t>(u_bytes),
+                       static_cast<uint32_t>(v_bytes), device_cu_count() * C::OCC, skew_for<C>(tiles, P * B), whole);
     PSD_HIP_TRY(hipGetLastError());
     return PSD_OK;
 }
@@ -581,8 +581,8 @@ psd_status launch_cfg(const uint16_t* U, int64_t ldu, const uint16_t* V, int64_t
     const int sps = static_cast<int>((stages + splits - 1) / splits);
     hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>((2 * tiles - whole) * splits)), dim3(C::THREADS), lds, st, U, ldu, V,
                        ldv, W, Mom, static_cast<int>(N), static_cast<int>(M), static_cast<int>(K), lr, mu, wd,
-                       order, whole, static_cast<uint32_t>(u_bytes), static_cast<uint32_t>(v_bytes), part, sfb_part_stride(N, M), sps,
-                       device_cu_count() * C::OCC, skew_for<C>(splits > 1 ? 0 : tiles, K));
+                       order, static_cast<uint32_t>(u_bytes), static_cast<uint32_t>(v_bytes), part, sfb_part_stride(N, M), sps,
+                       device_cu_count() * C::OCC, skew_for<C>(splits > 1 ? 0 : tiles, K), whole);
     PSD_HIP_TRY(hipGetLastError());
     if (splits > 1) return launch_sfb_reduce(part, splits, N, M, W, Mom, lr, mu, wd, st);
     return PSD_OK;
