@@ -7,10 +7,11 @@
 // communication because U is already there.
 //
 // Column sum (K*N factor elements read once, N outputs), bound by how many bytes are in flight and by the latency of one
-// load.  A workgroup of 16 wavefronts owns COLS adjacent columns; every lane reads 16 bytes of a row (8 bf16 or 4 fp32
-// columns) and keeps 8 such loads in flight, so K = 2048 rows of 32 bf16 columns are one round of loads.  The row partials
-// of a column meet in LDS in two steps.  Measured against 128 columns and 2 columns per lane: N = 1000, K = 2048, fp32,
-// after the reconstruction 17.0 -> 6.5 us; N = 4096, bf16 10.6 -> 8 us.
+// load.  A workgroup of 8 wavefronts owns COLS adjacent columns; every lane reads 16 bytes of a row (8 bf16 or 4 fp32
+// columns) and keeps 8 such loads in flight, so K = 1024 rows of 32 bf16 columns are one round of loads.  The row partials
+// of a column meet in LDS in two steps.  us behind a pack, 16 wavefronts -> 8, 32 columns: N = 1000, bf16, K = 256 3.26 -> 3.02, K = 2048 6.4 -> 6.3,
+// N = 4096, K = 2048 6.8 -> 6.3, fp32 7.5 -> 7.3, N = 128, K = 128 2.5 -> 2.2; with 4 N = 1000, K = 2048 7.5, with 16 loads in flight
+// 0.3 more everywhere, with 16 columns the same up to N = 4096.
 #include "psd_device.h"
 #include "psd_internal.h"
 
@@ -105,10 +106,10 @@ psd_status launch_bias(const void* U, int64_t ldu, int32_t dtype, int64_t N, int
                        float lr, float mu, float wd, hipStream_t st)
 {
     // 32 columns put a workgroup on every compute unit as early as possible; once 32-column workgroups would queue (N above
-    // 32 x CUs) wide rows are the better choice: N = 21841, K = 2048, bf16 21.9 us with 32 columns, 20.7 with 64, 17.8 with 128
+    // 32 x CUs) wide rows are the better choice: N = 9216, K = 2048, bf16 11.3 us with 32 columns, 7.8 with 64, 9.3 with 128
     if (N <= 32 * int64_t(device_cu_count())) return launch_cols<32>(U, ldu, dtype, N, K, bias, mom, lr, mu, wd, st);
-    // ... and 64 while those still find a compute unit each: N = 12000, K = 2048, bf16 14.1 us with 128 columns, 10.8 with 64, fp32
-    // 25.2 and 17.6, K = 1024 6.6 and 5.9, 13.3 and 9.5; K = 64 2.7 and 2.7
+    // ... and 64 while those still find a compute unit each: N = 12000, K = 2048, bf16 8.3 us with 128 columns, 7.8 with 64, fp32
+    // 16.9 and 14.1, K = 128 3.15 and 2.99, 3.47 and 3.44; N = 21841, K = 2048 14.4 and 17.2, 30.5 and 36.3
     if (N <= 64 * int64_t(device_cu_count())) return launch_cols<64>(U, ldu, dtype, N, K, bias, mom, lr, mu, wd, st);
     return launch_cols<128>(U, ldu, dtype, N, K, bias, mom, lr, mu, wd, st);
 }
