@@ -244,7 +244,12 @@ inline int choose_short_planes(int64_t N, int64_t M, int64_t K, int64_t cus, dou
     const bool halves = planes_in_halves(N, M, cus);
     const double tail = halves && M % 32 != 0 ? 0.4 : 0.8;
     const double cost = 6 + (7 + 36 * static_cast<double>(K) / 1024) * (share + tail * (rounds - share)) + (M % 32 != 0 ? 2.8 * share : 0);
-    return cost < 0.96 * us ? halves ? kPlaneHalves : 0 : -1;
+    // (The cost of halves is estimated too high, less so on lines and for the shortest sums: over 91 layers that have halves the pipe chosen
+    // takes 0.3 % longer than the better one, 2.4 % where they too have to gain 4 % by it.  us, fp32 pipe -> halves: 7861 -> 2561, K = 136 97 -> 74, 3745 -> 3231,
+    // K = 136 60 -> 51, 3360 -> 2357, K = 176 42.0 -> 39.2, 3616 -> 2208, K = 232 51.8 -> 47.9; the other way 1184 -> 6733, K = 153 39.4 and 40.4, 800 -> 11569,
+    // K = 128 41.2 and 43.2.)
+    const double gain = !halves ? 0.96 : M % 32 != 0 ? 1.1 : K >= 160 ? 1.05 : 0.96;
+    return cost < gain * us ? halves ? kPlaneHalves : 0 : -1;
 }
 
 // ---- bf16 reconstruction: which tile covers W

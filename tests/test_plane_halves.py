@@ -12,7 +12,7 @@ CUS, HALVES = 256, 4
 # M, N, B, P: 258 tiles, rows of W on quads; 516, on cache lines and anywhere, behind pairs; the last row of tiles with one row in its lower half, with
 # nothing there, with all; half a round left; beside a lone tile; 128 to 255 k rows
 LAYERS = [(5500, 705, 64, 5), (5504, 705, 64, 5), (5497, 705, 51, 7), (5120, 2048, 16, 17), (3339, 3601, 64, 5), (3360, 3630, 51, 6),
-          (1410, 8830, 64, 5), (4096, 1500, 32, 4), (4611, 2170, 19, 8)]
+          (1410, 8830, 64, 5), (4096, 1500, 32, 4), (4611, 2170, 19, 8), (3745, 3231, 17, 8), (3360, 2357, 22, 8)]
 
 
 def test_layers_with_half_a_round_left_at_most_go_to_halves(rules):
