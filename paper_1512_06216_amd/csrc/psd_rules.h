@@ -506,7 +506,9 @@ PSD_HOST_DEVICE void tile_of(int b, const TileOrder& o, int* tile_n, int* tile_m
 // K = 640: 4096 -> 21841 266.5 and 266.7, 8192 -> 8192 214 and 226; wide layers gain longer, 9216 -> 4096, K = 768 135.8 -> 130.3,
 // 12000 -> 2500 112 -> 107, 25088 -> 4096 347 -> 341, K = 1024 369 and 374.
 // Off cache lines neighbouring tiles share lines, which are best left to one XCD: 7001 -> 5003, K = 256 105.7 -> 100.3, 10001 -> 4001,
-// K = 64 109 -> 104 (-1: 133), 5000 -> 9000 117.6 and 117.1, but 1500 -> 20000 78 and 88, 2500 -> 12000 79 and 84.
+// K = 64 109 -> 104 (-1: 133), 5000 -> 9000 117.6 and 117.1, but 1500 -> 20000 78 and 88, 2500 -> 12000 79 and 84,
+// 4118 -> 6976, K = 104 79.0 and 82.5, 4054 -> 8016, K = 80 86.9 and 89.9, 4204 -> 1620, K = 104 25.0 and 25.8.  Of 98 layers with M from 4600 on three
+// are up to 0.5 % slower, and they gain 4.1 % on average.
 // Layers of less than 5 M weights, which the chip covers at once: 608 -> 4068, K = 273 11.3 and 12.7, 2720 -> 1119, K = 153 14.0 and
 // 14.4; 5376 -> 991, K = 40 19.3 -> 17.9.  Of 175 layers of K = 32 .. 1100 the 116 that change their order gain 8 %, the worst of them
 // loses 3 (1024 -> 20000, K = 256).
@@ -514,7 +516,7 @@ inline int band_for(int64_t N, int64_t M, int64_t K, int64_t tiles, bool on_line
 {
     if (tiles <= 2 * cus || N * M < 5000000) return 0;
     if (on_lines && K <= 192 && M >= 3072) return -1;
-    return K <= (M >= 2 * N ? 768 : 512) && (on_lines || M >= 4000) ? 4 : 0;
+    return K <= (M >= 2 * N ? 768 : 512) && (on_lines || M >= 4600) ? 4 : 0;
 }
 
 // ---- order of a step's launches

@@ -12,8 +12,8 @@ from tests.test_rules import rules  # noqa: F401  (a fixture)
 CUS = 256
 # M, N, B, P and the order: row by row (-1), bands of four tile rows, or runs of groups of eight (0), of which there are more than eight
 # here.  Rows of W on cache lines, on quads and anywhere; the last band is a whole one, three rows, one row.
-BF16_LAYERS = [(3104, 2048, 32, 2, -1), (3072, 1665, 32, 5, -1), (1600, 4224, 32, 12, 4), (1568, 3973, 32, 8, 4), (4004, 1540, 32, 3, 4),
-               (4001, 1411, 20, 5, 4), (1001, 6001, 32, 4, 0), (608, 8200, 32, 16, 0)]
+BF16_LAYERS = [(3104, 2048, 32, 2, -1), (3072, 1665, 32, 5, -1), (1600, 4224, 32, 12, 4), (1568, 3973, 32, 8, 4), (4604, 1340, 32, 3, 4),
+               (4601, 1227, 20, 5, 4), (1001, 6001, 32, 4, 0), (608, 8200, 32, 16, 0)]
 # M, N, B, P and the tile in planes for sums of 128 to 255 rows
 SHORT_PLANES = [(4096, 1500, 32, 4, 4), (6001, 2001, 64, 3, 0), (4604, 1733, 51, 5, 0), (4096, 1500, 32, 3, -1), (1184, 6733, 51, 3, -1)]
 # the planes' kernel with K >= 256: runs of groups, one band, bands of four and of eight
